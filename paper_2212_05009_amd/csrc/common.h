@@ -77,18 +77,35 @@ struct ProfSuppress {
   ProfSuppress& operator=(const ProfSuppress&) = delete;
 };
 
-// RAII device buffer so that every error path frees what it allocated.
+// ---- device memory kept between calls (pool.hip) ---------------------------------------------
+// pool_free may be called only when no enqueued work can still touch the block.
+int pool_alloc(void** p, size_t bytes);
+void pool_free(void* p);
+// a pinned host page for numbers that a call reads back
+constexpr size_t kPinnedBytes = 16384;
+int pinned_take(void** p);
+void pinned_give(void* p);
+
+// The stream a call's temporaries are used on.  `done` is set once the call has waited for it; a call that leaves early
+// waits when its first temporary goes back.
+struct CallScope {
+  hipStream_t s;
+  bool done = false;
+  explicit CallScope(hipStream_t s_) : s(s_) {}
+  void quiesce() { if (!done) { (void)hipStreamSynchronize(s); done = true; } }
+};
+
+// RAII device buffer so that every path gives back what it allocated; declare it after its CallScope.
 struct DevBuf {
   void* p = nullptr;
+  CallScope* scope = nullptr;
   DevBuf() = default;
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
-  ~DevBuf() { if (p) (void)hipFree(p); }
-  int alloc(size_t bytes) {
-    if (p) { (void)hipFree(p); p = nullptr; }
-    hipError_t e = hipMalloc(&p, bytes ? bytes : 256);
-    if (e != hipSuccess) { p = nullptr; return fail(GCN_ENOMEM, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e)); }
-    return GCN_OK;
+  ~DevBuf() { if (p) { scope->quiesce(); pool_free(p); } }
+  int alloc(CallScope& sc, size_t bytes) {
+    scope = &sc;
+    return pool_alloc(&p, bytes);
   }
   template <class T> T* as() const { return (T*)p; }
   void* release() { void* q = p; p = nullptr; return q; }

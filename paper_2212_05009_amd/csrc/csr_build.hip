@@ -233,25 +233,26 @@ __global__ void k_chunk_bounds(const int32_t* __restrict__ wave_rows, const int6
 }
 
 void free_schedule(Schedule* sc) {
-  if (sc->wave_rows) (void)hipFree(sc->wave_rows);
-  if (sc->hub_rows) (void)hipFree(sc->hub_rows);
-  if (sc->hub_chunk_ptr) (void)hipFree(sc->hub_chunk_ptr);
-  if (sc->chunk_hub) (void)hipFree(sc->chunk_hub);
+  pool_free(sc->wave_rows);
+  pool_free(sc->hub_rows);
+  pool_free(sc->hub_chunk_ptr);
+  pool_free(sc->chunk_hub);
   *sc = Schedule();
 }
 
 int build_schedule(const int64_t* ptr, int64_t n, hipStream_t s, Schedule* out) {
   *out = Schedule();
+  CallScope sc(s);
   DevBuf keys_a, keys_b, hub_flag, hub_chunks, hub_pos, chunk_pos, tmp;
-  GCN_TRY(keys_a.alloc(sizeof(uint64_t) * (size_t)n));
-  GCN_TRY(keys_b.alloc(sizeof(uint64_t) * (size_t)n));
-  GCN_TRY(hub_flag.alloc(sizeof(uint32_t) * (size_t)n));
-  GCN_TRY(hub_chunks.alloc(sizeof(uint32_t) * (size_t)n));
-  GCN_TRY(hub_pos.alloc(sizeof(int64_t) * (size_t)(n + 1)));
-  GCN_TRY(chunk_pos.alloc(sizeof(int64_t) * (size_t)(n + 1)));
+  GCN_TRY(keys_a.alloc(sc, sizeof(uint64_t) * (size_t)n));
+  GCN_TRY(keys_b.alloc(sc, sizeof(uint64_t) * (size_t)n));
+  GCN_TRY(hub_flag.alloc(sc, sizeof(uint32_t) * (size_t)n));
+  GCN_TRY(hub_chunks.alloc(sc, sizeof(uint32_t) * (size_t)n));
+  GCN_TRY(hub_pos.alloc(sc, sizeof(int64_t) * (size_t)(n + 1)));
+  GCN_TRY(chunk_pos.alloc(sc, sizeof(int64_t) * (size_t)(n + 1)));
   size_t tb = sort_tmp_bytes(n);
   if (scan_tmp_bytes(n) > tb) tb = scan_tmp_bytes(n);
-  GCN_TRY(tmp.alloc(tb));
+  GCN_TRY(tmp.alloc(sc, tb));
 
   k_sched_keys<<<grid_for(n), kThreads, 0, s>>>(ptr, n, keys_a.as<uint64_t>(), hub_flag.as<uint32_t>(),
                                                  hub_chunks.as<uint32_t>());
@@ -268,12 +269,12 @@ int build_schedule(const int64_t* ptr, int64_t n, hipStream_t s, Schedule* out) 
                          &sorted, nullptr));
   DevBuf wave_rows, hub_rows, hub_chunk_ptr, chunk_hub;
   const int64_t n_wave = n - n_hub;
-  GCN_TRY(wave_rows.alloc(sizeof(int32_t) * (size_t)(n_wave > 0 ? n_wave : 1)));
-  GCN_TRY(hub_rows.alloc(sizeof(int32_t) * (size_t)(n_hub > 0 ? n_hub : 1)));
-  GCN_TRY(hub_chunk_ptr.alloc(sizeof(int64_t) * (size_t)(n_hub + 1)));
-  GCN_TRY(chunk_hub.alloc(sizeof(int32_t) * (size_t)(n_chunks > 0 ? n_chunks : 1)));
+  GCN_TRY(wave_rows.alloc(sc, sizeof(int32_t) * (size_t)(n_wave > 0 ? n_wave : 1)));
+  GCN_TRY(hub_rows.alloc(sc, sizeof(int32_t) * (size_t)(n_hub > 0 ? n_hub : 1)));
+  GCN_TRY(hub_chunk_ptr.alloc(sc, sizeof(int64_t) * (size_t)(n_hub + 1)));
+  GCN_TRY(chunk_hub.alloc(sc, sizeof(int32_t) * (size_t)(n_chunks > 0 ? n_chunks : 1)));
   DevBuf class_begin;
-  GCN_TRY(class_begin.alloc(sizeof(int64_t) * 34));
+  GCN_TRY(class_begin.alloc(sc, sizeof(int64_t) * 34));
   GCN_HIP(hipMemsetAsync(class_begin.p, 0, sizeof(int64_t) * 34, s));
   if (n_wave > 0) {
     k_take_low32<<<grid_for(n_wave), kThreads, 0, s>>>(sorted, n_wave, wave_rows.as<int32_t>());
@@ -290,8 +291,8 @@ int build_schedule(const int64_t* ptr, int64_t n, hipStream_t s, Schedule* out) 
   // the class lists and the hub list cut at kRowChunks row boundaries (multiples of 64 rows)
   DevBuf chunk_bound, chunk_cb;
   constexpr int kChunkTable = (kRowChunks + 1) * 35;
-  GCN_TRY(chunk_bound.alloc(sizeof(int64_t) * (kRowChunks + 1)));
-  GCN_TRY(chunk_cb.alloc(sizeof(int64_t) * kChunkTable));
+  GCN_TRY(chunk_bound.alloc(sc, sizeof(int64_t) * (kRowChunks + 1)));
+  GCN_TRY(chunk_cb.alloc(sc, sizeof(int64_t) * kChunkTable));
   int64_t chunk_table[kChunkTable];
   for (int j = 0; j <= kRowChunks; ++j) {
     const int64_t r = round_up(ceil_div(n * j, kRowChunks), 64);
@@ -303,7 +304,8 @@ int build_schedule(const int64_t* ptr, int64_t n, hipStream_t s, Schedule* out) 
       chunk_bound.as<int64_t>(), kRowChunks + 1, chunk_cb.as<int64_t>());
   GCN_CHECK_LAUNCH();
   GCN_HIP(hipMemcpyAsync(chunk_table, chunk_cb.p, sizeof(chunk_table), hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipStreamSynchronize(s));   // temporaries are freed on return
+  GCN_HIP(hipStreamSynchronize(s));   // temporaries go back on return
+  sc.done = true;
   for (int j = 0; j <= kRowChunks; ++j) {
     for (int c = 0; c < 33; ++c) out->chunk_class_begin[j][c] = chunk_table[j * 35 + c];
     out->chunk_hub_begin[j] = chunk_table[j * 35 + 33];
@@ -332,17 +334,18 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   const bool whole = (row_lo == 0 && row_hi == n_global);
   const int64_t m = n_edges + nr;          // candidate entries: edges + diagonal
 
+  CallScope sc(s);
   // -- validation and halo bitmap
   const int64_t words = ceil_div(n_global, 32);
   DevBuf bad, bitmap, wcnt, wprefix, tmp;
-  GCN_TRY(bad.alloc(sizeof(int)));
-  GCN_TRY(bitmap.alloc(sizeof(uint32_t) * (size_t)words));
-  GCN_TRY(wcnt.alloc(sizeof(uint32_t) * (size_t)words));
-  GCN_TRY(wprefix.alloc(sizeof(int64_t) * (size_t)(words + 1)));
+  GCN_TRY(bad.alloc(sc, sizeof(int)));
+  GCN_TRY(bitmap.alloc(sc, sizeof(uint32_t) * (size_t)words));
+  GCN_TRY(wcnt.alloc(sc, sizeof(uint32_t) * (size_t)words));
+  GCN_TRY(wprefix.alloc(sc, sizeof(int64_t) * (size_t)(words + 1)));
   size_t tb = sort_tmp_bytes(m);
   if (scan_tmp_bytes(m) > tb) tb = scan_tmp_bytes(m);
   if (scan_tmp_bytes(words) > tb) tb = scan_tmp_bytes(words);
-  GCN_TRY(tmp.alloc(tb));
+  GCN_TRY(tmp.alloc(sc, tb));
   GCN_HIP(hipMemsetAsync(bad.p, 0, sizeof(int), s));
   GCN_HIP(hipMemsetAsync(bitmap.p, 0, sizeof(uint32_t) * (size_t)words, s));
   if (n_edges > 0) {
@@ -366,7 +369,7 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   const int64_t nc = nr + nh;
   if (nc >= 0x7fffffffLL) return fail(GCN_EINVAL, "gcn_csr_build: more than 2^31-1 local columns");
   DevBuf halo_gid;
-  GCN_TRY(halo_gid.alloc(sizeof(int32_t) * (size_t)(nh > 0 ? nh : 1)));
+  GCN_TRY(halo_gid.alloc(sc, sizeof(int32_t) * (size_t)(nh > 0 ? nh : 1)));
   if (nh > 0) k_halo_list<<<grid_for(words), kThreads, 0, s>>>(bitmap.as<uint32_t>(), wprefix.as<int64_t>(), words, halo_gid.as<int32_t>());
   GCN_CHECK_LAUNCH();
 
@@ -375,8 +378,8 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   const int rowbits = bits_for(nr);
   if (colbits + rowbits > 62) return fail(GCN_EINVAL, "gcn_csr_build: block too large for 64-bit sort keys");
   DevBuf keys_a, keys_b, flag, pos;
-  GCN_TRY(keys_a.alloc(sizeof(uint64_t) * (size_t)m));
-  GCN_TRY(keys_b.alloc(sizeof(uint64_t) * (size_t)m));
+  GCN_TRY(keys_a.alloc(sc, sizeof(uint64_t) * (size_t)m));
+  GCN_TRY(keys_b.alloc(sc, sizeof(uint64_t) * (size_t)m));
   k_make_keys<<<grid_for(m), kThreads, 0, s>>>(d_src, d_dst, n_edges, row_lo, row_hi, nr, colbits,
                                                 bitmap.as<uint32_t>(), wprefix.as<int64_t>(), keys_a.as<uint64_t>());
   GCN_CHECK_LAUNCH();
@@ -384,8 +387,8 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   GCN_TRY(radix_sort_u64(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nullptr, nullptr, m, 0, colbits + rowbits,
                          tmp.p, s, &sorted, nullptr));
   uint64_t* other = (sorted == keys_a.as<uint64_t>()) ? keys_b.as<uint64_t>() : keys_a.as<uint64_t>();
-  GCN_TRY(flag.alloc(sizeof(uint32_t) * (size_t)m));
-  GCN_TRY(pos.alloc(sizeof(int64_t) * (size_t)(m + 1)));
+  GCN_TRY(flag.alloc(sc, sizeof(uint32_t) * (size_t)m));
+  GCN_TRY(pos.alloc(sc, sizeof(int64_t) * (size_t)(m + 1)));
   k_flag_unique<<<grid_for(m), kThreads, 0, s>>>(sorted, m, flag.as<uint32_t>());
   GCN_CHECK_LAUNCH();
   GCN_TRY(exclusive_scan_u32(flag.as<uint32_t>(), pos.as<int64_t>(), m, tmp.p, s));
@@ -396,10 +399,10 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   if (nnz >= 0xffffffffLL) return fail(GCN_EINVAL, "gcn_csr_build: more than 2^32-2 stored entries in one block");
 
   DevBuf rowptr, col, val, deg;
-  GCN_TRY(rowptr.alloc(sizeof(int64_t) * (size_t)(nr + 1)));
-  GCN_TRY(col.alloc(sizeof(int32_t) * (size_t)nnz));
-  GCN_TRY(val.alloc(sizeof(float) * (size_t)nnz));
-  GCN_TRY(deg.alloc(sizeof(int32_t) * (size_t)nr));
+  GCN_TRY(rowptr.alloc(sc, sizeof(int64_t) * (size_t)(nr + 1)));
+  GCN_TRY(col.alloc(sc, sizeof(int32_t) * (size_t)nnz));
+  GCN_TRY(val.alloc(sc, sizeof(float) * (size_t)nnz));
+  GCN_TRY(deg.alloc(sc, sizeof(int32_t) * (size_t)nr));
   uint64_t* ukeys = other;                  // unique keys, row-major order
   k_compact<<<grid_for(m), kThreads, 0, s>>>(sorted, flag.as<uint32_t>(), pos.as<int64_t>(), m, colbits, ukeys, col.as<int32_t>());
   k_boundaries<<<grid_for(nnz), kThreads, 0, s>>>(ukeys, nnz, colbits, nr, rowptr.as<int64_t>());
@@ -411,35 +414,33 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
 
   DevBuf mid;
   if (nh > 0) {
-    GCN_TRY(mid.alloc(sizeof(int64_t) * (size_t)nr));
+    GCN_TRY(mid.alloc(sc, sizeof(int64_t) * (size_t)nr));
     k_row_mid<<<grid_for(nr), kThreads, 0, s>>>(rowptr.as<int64_t>(), col.as<int32_t>(), nr, mid.as<int64_t>());
     GCN_CHECK_LAUNCH();
   }
 
   // -- column-major copy
-  DevBuf colptr, rowidx, val_t;
+  DevBuf colptr, rowidx, val_t, pay_a, pay_b, tk_b;
   if (flags & GCN_BUILD_CSC) {
-    DevBuf pay_a, pay_b;
-    GCN_TRY(pay_a.alloc(sizeof(uint32_t) * (size_t)nnz));
-    GCN_TRY(pay_b.alloc(sizeof(uint32_t) * (size_t)nnz));
-    GCN_TRY(colptr.alloc(sizeof(int64_t) * (size_t)(nc + 1)));
-    GCN_TRY(rowidx.alloc(sizeof(int32_t) * (size_t)nnz));
-    GCN_TRY(val_t.alloc(sizeof(float) * (size_t)nnz));
+    GCN_TRY(pay_a.alloc(sc, sizeof(uint32_t) * (size_t)nnz));
+    GCN_TRY(pay_b.alloc(sc, sizeof(uint32_t) * (size_t)nnz));
+    GCN_TRY(colptr.alloc(sc, sizeof(int64_t) * (size_t)(nc + 1)));
+    GCN_TRY(rowidx.alloc(sc, sizeof(int32_t) * (size_t)nnz));
+    GCN_TRY(val_t.alloc(sc, sizeof(float) * (size_t)nnz));
     uint64_t* tk_a = sorted;               // the sorted-with-duplicates buffer is free again
     k_make_tkeys<<<grid_for(nnz), kThreads, 0, s>>>(ukeys, nnz, colbits, tk_a, pay_a.as<uint32_t>());
     GCN_CHECK_LAUNCH();
     // ukeys lives in `other`; the sort ping-pongs between tk_a and a third buffer
-    DevBuf tk_b;
-    GCN_TRY(tk_b.alloc(sizeof(uint64_t) * (size_t)nnz));
+    GCN_TRY(tk_b.alloc(sc, sizeof(uint64_t) * (size_t)nnz));
     uint64_t* tsorted = nullptr; uint32_t* psorted = nullptr;
     GCN_TRY(radix_sort_u64(tk_a, tk_b.as<uint64_t>(), pay_a.as<uint32_t>(), pay_b.as<uint32_t>(), nnz, 32,
                            32 + colbits, tmp.p, s, &tsorted, &psorted));
     k_boundaries<<<grid_for(nnz), kThreads, 0, s>>>(tsorted, nnz, 32, nc, colptr.as<int64_t>());
     k_finish_csc<<<grid_for(nnz), kThreads, 0, s>>>(tsorted, psorted, val.as<float>(), nnz, rowidx.as<int32_t>(), val_t.as<float>());
     GCN_CHECK_LAUNCH();
-    GCN_HIP(hipStreamSynchronize(s));
   }
   GCN_HIP(hipStreamSynchronize(s));
+  sc.done = true;
 
   A->n_global = n_global; A->row_lo = row_lo;
   A->nr = nr; A->nh = nh; A->nc = nc; A->nnz = nnz;
@@ -465,12 +466,11 @@ int ensure_workspace(gcn_csr* A, size_t bytes) {
   if (bytes <= A->ws_bytes) return GCN_OK;
   if (A->ws) {
     GCN_HIP(hipDeviceSynchronize());
-    (void)hipFree(A->ws);
+    pool_free(A->ws);
     A->ws = nullptr; A->ws_bytes = 0;
   }
   size_t want = (size_t)round_up((int64_t)bytes, 1 << 20);
-  hipError_t e = hipMalloc(&A->ws, want);
-  if (e != hipSuccess) { A->ws = nullptr; return fail(GCN_ENOMEM, "workspace of %zu bytes: %s", want, hipGetErrorString(e)); }
+  GCN_TRY(pool_alloc(&A->ws, want));
   A->ws_bytes = want;
   return GCN_OK;
 }
@@ -531,7 +531,7 @@ extern "C" int gcn_csr_free(gcn_csr_t* A) {
   if (!A) return GCN_OK;
   (void)hipDeviceSynchronize();
   void* ptrs[] = {A->rowptr, A->col, A->val, A->deg, A->halo_gid, A->colptr, A->rowidx, A->val_t, A->mid, A->ws};
-  for (void* p : ptrs) if (p) (void)hipFree(p);
+  for (void* p : ptrs) pool_free(p);
   free_schedule(&A->sched);
   free_schedule(&A->sched_t);
   free_panel_plans(A);

@@ -72,12 +72,13 @@ extern "C" int gcn_csr_induced(const gcn_csr_t* A, const int32_t* d_vertices, in
   hipStream_t s = (hipStream_t)stream;
   const int64_t n = A->nr;
 
+  CallScope sc(s);
   DevBuf lid, len, off, tmp, bad;
-  GCN_TRY(lid.alloc(sizeof(int32_t) * (size_t)n));
-  GCN_TRY(len.alloc(sizeof(uint32_t) * (size_t)n_sub));
-  GCN_TRY(off.alloc(sizeof(int64_t) * (size_t)(n_sub + 1)));
-  GCN_TRY(tmp.alloc(scan_tmp_bytes(n_sub)));
-  GCN_TRY(bad.alloc(sizeof(int)));
+  GCN_TRY(lid.alloc(sc, sizeof(int32_t) * (size_t)n));
+  GCN_TRY(len.alloc(sc, sizeof(uint32_t) * (size_t)n_sub));
+  GCN_TRY(off.alloc(sc, sizeof(int64_t) * (size_t)(n_sub + 1)));
+  GCN_TRY(tmp.alloc(sc, scan_tmp_bytes(n_sub)));
+  GCN_TRY(bad.alloc(sc, sizeof(int)));
   GCN_HIP(hipMemsetAsync(bad.p, 0, sizeof(int), s));
   k_ind_fill<<<ind_grid(n), kIndThreads, 0, s>>>(lid.as<int32_t>(), n, -1);
   k_ind_scatter<<<ind_grid(n_sub), kIndThreads, 0, s>>>(d_vertices, n_sub, n, lid.as<int32_t>(), bad.as<int>());
@@ -97,10 +98,12 @@ extern "C" int gcn_csr_induced(const gcn_csr_t* A, const int32_t* d_vertices, in
   if (h_bad) return fail(GCN_EINVAL, "gcn_csr_induced: a vertex is listed twice");
 
   DevBuf src, dst;
-  GCN_TRY(src.alloc(sizeof(int32_t) * (size_t)total));
-  GCN_TRY(dst.alloc(sizeof(int32_t) * (size_t)total));
+  GCN_TRY(src.alloc(sc, sizeof(int32_t) * (size_t)total));
+  GCN_TRY(dst.alloc(sc, sizeof(int32_t) * (size_t)total));
   k_ind_edges<<<ind_grid(total), kIndThreads, 0, s>>>(d_vertices, n_sub, off.as<int64_t>(), total, A->rowptr, A->col,
                                                      lid.as<int32_t>(), src.as<int32_t>(), dst.as<int32_t>());
   GCN_CHECK_LAUNCH();
-  return gcn_csr_build(src.as<int32_t>(), dst.as<int32_t>(), total, n_sub, 0, n_sub, nullptr, flags, stream, out);
+  GCN_TRY(gcn_csr_build(src.as<int32_t>(), dst.as<int32_t>(), total, n_sub, 0, n_sub, nullptr, flags, stream, out));
+  sc.done = true;        // the build has waited for the stream
+  return GCN_OK;
 }

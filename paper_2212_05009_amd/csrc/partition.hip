@@ -106,8 +106,9 @@ extern "C" int gcn_partition_stats(const gcn_csr_t* A, const int32_t* d_part, in
   const int64_t n = A->nr, nnz = A->nnz;
 
   // results the caller does not ask for still have to land somewhere
+  CallScope sc(s);
   DevBuf spare;
-  GCN_TRY(spare.alloc(sizeof(int64_t) * (size_t)(5 * (int64_t)p + 2)));
+  GCN_TRY(spare.alloc(sc, sizeof(int64_t) * (size_t)(5 * (int64_t)p + 2)));
   int64_t* sp = spare.as<int64_t>();
   int64_t* load = d_load ? d_load : sp;
   int64_t* send_rows = d_send_rows ? d_send_rows : sp + p;
@@ -120,7 +121,7 @@ extern "C" int gcn_partition_stats(const gcn_csr_t* A, const int32_t* d_part, in
   GCN_CHECK_LAUNCH();
 
   DevBuf bad;
-  GCN_TRY(bad.alloc(sizeof(int)));
+  GCN_TRY(bad.alloc(sc, sizeof(int)));
   GCN_HIP(hipMemsetAsync(bad.p, 0, sizeof(int), s));
   k_ps_check<<<ps_grid(n), kPsThreads, 0, s>>>(d_part, n, p, bad.as<int>());
   GCN_CHECK_LAUNCH();
@@ -131,7 +132,7 @@ extern "C" int gcn_partition_stats(const gcn_csr_t* A, const int32_t* d_part, in
 
   k_ps_load<<<ps_grid(n), kPsThreads, 0, s>>>(A->rowptr, d_part, n, load);
   GCN_CHECK_LAUNCH();
-  if (nnz == 0) { GCN_HIP(hipStreamSynchronize(s)); return GCN_OK; }
+  if (nnz == 0) { GCN_HIP(hipStreamSynchronize(s)); sc.done = true; return GCN_OK; }
 
   int jbits = 1;
   while (((int64_t)1 << jbits) < n) ++jbits;
@@ -140,11 +141,11 @@ extern "C" int gcn_partition_stats(const gcn_csr_t* A, const int32_t* d_part, in
   const uint64_t first_invalid = ((uint64_t)p * (uint64_t)p) << jbits;
 
   DevBuf ka, kb, tmp, flag, pos;
-  GCN_TRY(ka.alloc(sizeof(uint64_t) * (size_t)nnz));
-  GCN_TRY(kb.alloc(sizeof(uint64_t) * (size_t)nnz));
-  GCN_TRY(tmp.alloc(std::max(sort_tmp_bytes(nnz), scan_tmp_bytes(nnz))));
-  GCN_TRY(flag.alloc(sizeof(uint32_t) * (size_t)nnz));
-  GCN_TRY(pos.alloc(sizeof(int64_t) * (size_t)(nnz + 1)));
+  GCN_TRY(ka.alloc(sc, sizeof(uint64_t) * (size_t)nnz));
+  GCN_TRY(kb.alloc(sc, sizeof(uint64_t) * (size_t)nnz));
+  GCN_TRY(tmp.alloc(sc, std::max(sort_tmp_bytes(nnz), scan_tmp_bytes(nnz))));
+  GCN_TRY(flag.alloc(sc, sizeof(uint32_t) * (size_t)nnz));
+  GCN_TRY(pos.alloc(sc, sizeof(int64_t) * (size_t)(nnz + 1)));
   k_ps_keys<<<ps_grid(nnz), kPsThreads, 0, s>>>(A->rowptr, A->col, nnz, n, d_part, p, jbits, ka.as<uint64_t>());
   GCN_CHECK_LAUNCH();
   uint64_t* sorted = nullptr; uint32_t* unused = nullptr;
@@ -156,6 +157,7 @@ extern "C" int gcn_partition_stats(const gcn_csr_t* A, const int32_t* d_part, in
   k_ps_pairs<<<ps_grid(nnz), kPsThreads, 0, s>>>(sorted, pos.as<int64_t>(), nnz, p, jbits, first_invalid, send_rows,
                                                recv_rows, send_msgs, recv_msgs, totals);
   GCN_CHECK_LAUNCH();
-  GCN_HIP(hipStreamSynchronize(s));      // the temporaries are released on return
+  GCN_HIP(hipStreamSynchronize(s));      // the temporaries go back on return
+  sc.done = true;
   return GCN_OK;
 }

@@ -512,7 +512,7 @@ int device_cus() {
 void free_plan(PanelPlan* p) {
   if (!p) return;
   void* ptrs[] = {p->ent, p->wb, p->nfull, p->cbend, p->obase, p->panel_row0, p->row_v, p->vlds, p->order, p->ctr};
-  for (void* q : ptrs) if (q) (void)hipFree(q);
+  for (void* q : ptrs) pool_free(q);
   delete p;
 }
 
@@ -638,11 +638,7 @@ static int build_plan_impl(gcn_csr* A, bool transposed, int ns, int sw, int lpg,
   struct Guard { PanelPlan* p; ~Guard() { if (p) free_plan(p); } } guard{P};
   P->transposed = transposed; P->ns = ns; P->sw = sw; P->lpg = lpg; P->cb_shift = cb_shift; P->part_len = part_len;
   P->nv_max = nv_max; P->n_panels = n_panels; P->n_rows = n; P->total_vrows = total_v;
-  auto dev_alloc = [&](void** p, size_t bytes) -> int {
-    hipError_t e = hipMalloc(p, bytes ? bytes : 256);
-    if (e != hipSuccess) { *p = nullptr; return fail(GCN_ENOMEM, "panel plan: hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e)); }
-    return GCN_OK;
-  };
+  auto dev_alloc = [](void** p, size_t bytes) { return pool_alloc(p, bytes); };
   const int64_t n_waves = (int64_t)n_panels * kPanelWaves, n_owners = (int64_t)n_panels * n_own;
   GCN_TRY(dev_alloc((void**)&P->wb, sizeof(int64_t) * ((size_t)n_waves + 1)));
   GCN_TRY(dev_alloc((void**)&P->nfull, sizeof(int32_t) * (size_t)n_waves));
@@ -658,18 +654,19 @@ static int build_plan_impl(gcn_csr* A, bool transposed, int ns, int sw, int lpg,
   GCN_TRY(dev_alloc((void**)&P->vlds, sizeof(int32_t) * (size_t)total_v));
   GCN_TRY(dev_alloc((void**)&P->order, sizeof(int32_t) * (size_t)n_panels));
   GCN_TRY(dev_alloc((void**)&P->ctr, sizeof(uint32_t) * 2 * kPanelLists));
+  CallScope sc(s);
   DevBuf d_vinfo, keys_a, keys_b, pay_a, pay_b, tmp, oseg, nb, seg;
-  GCN_TRY(d_vinfo.alloc(sizeof(uint32_t) * (size_t)total_v));
-  GCN_TRY(keys_a.alloc(sizeof(uint64_t) * (size_t)nnz));
-  GCN_TRY(keys_b.alloc(sizeof(uint64_t) * (size_t)nnz));
-  GCN_TRY(pay_a.alloc(sizeof(uint32_t) * (size_t)nnz));
-  GCN_TRY(pay_b.alloc(sizeof(uint32_t) * (size_t)nnz));
-  GCN_TRY(oseg.alloc(sizeof(int64_t) * ((size_t)n_owners + 1)));
-  GCN_TRY(seg.alloc(sizeof(int64_t) * ((size_t)n_seg + 1)));
-  GCN_TRY(nb.alloc(sizeof(uint32_t) * (size_t)n_waves));
+  GCN_TRY(d_vinfo.alloc(sc, sizeof(uint32_t) * (size_t)total_v));
+  GCN_TRY(keys_a.alloc(sc, sizeof(uint64_t) * (size_t)nnz));
+  GCN_TRY(keys_b.alloc(sc, sizeof(uint64_t) * (size_t)nnz));
+  GCN_TRY(pay_a.alloc(sc, sizeof(uint32_t) * (size_t)nnz));
+  GCN_TRY(pay_b.alloc(sc, sizeof(uint32_t) * (size_t)nnz));
+  GCN_TRY(oseg.alloc(sc, sizeof(int64_t) * ((size_t)n_owners + 1)));
+  GCN_TRY(seg.alloc(sc, sizeof(int64_t) * ((size_t)n_seg + 1)));
+  GCN_TRY(nb.alloc(sc, sizeof(uint32_t) * (size_t)n_waves));
   size_t tb = sort_tmp_bytes(nnz);
   if (scan_tmp_bytes(n_waves) > tb) tb = scan_tmp_bytes(n_waves);
-  GCN_TRY(tmp.alloc(tb));
+  GCN_TRY(tmp.alloc(sc, tb));
   GCN_HIP(hipMemcpyAsync(P->panel_row0, panel_row0.data(), sizeof(int32_t) * ((size_t)n_panels + 1), hipMemcpyHostToDevice, s));
   GCN_HIP(hipMemcpyAsync(P->row_v, row_v.data(), sizeof(int32_t) * ((size_t)n + 1), hipMemcpyHostToDevice, s));
   GCN_HIP(hipMemcpyAsync(P->order, order.data(), sizeof(int32_t) * (size_t)n_panels, hipMemcpyHostToDevice, s));
@@ -702,6 +699,7 @@ static int build_plan_impl(gcn_csr* A, bool transposed, int ns, int sw, int lpg,
   k_plan_scatter<<<grid, 256, 0, s>>>(sorted, spay, d_idx, d_val, nnz, kLidBits + cbbits, groups, epb, oseg.as<int64_t>(), P->wb, P->ent);
   GCN_CHECK_LAUNCH();
   GCN_HIP(hipStreamSynchronize(s));      // host vectors and temporaries go out of scope
+  sc.done = true;
   if (tune().panel_verbose)
     fprintf(stderr, "[panel plan] rows %lld nnz %lld ns %d sw %d lpg %d cb_shift %d part_len %d vrows %lld panels %d nv_max %d batches %lld (padding %.1f%%)\n",
             (long long)n, (long long)nnz, ns, sw, lpg, cb_shift, part_len, (long long)total_v, n_panels, nv_max,
