@@ -109,11 +109,15 @@ def _check(rc: int, what: str):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# torch.cuda.current_stream() builds a Stream object (2.7 us a call); only its handle is wanted here
+_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(_current_device())
 
 
 def _dtype_code(t: torch.Tensor) -> int:

@@ -40,6 +40,7 @@ struct Tuning {
   int panel_verbose = 0;        // column sweep: print the plan chosen
   int spmm_slices = 0;          // feature slices of the row kernel (0: by rule)
   int spmm_epg = 0;             // entries per lane group before a row is shared by more groups (0: default)
+  int spmm_short = -1;          // short-row form of the row kernel: -1 by rule, 0 never, 1 always
   int spmm_wide = 0;            // 64-bit gather addresses even where 32 bits suffice
   int gemm_direct = 1, gemm_fast = 1, gemm_tn_wide = 1, gemm_bf16 = 1, gemm_regw = 1;   // 0 switches a dense kernel family off
   int gemm_tn_lds = 1;          // A^T B with both operands streamed through LDS: 0 off, 1 for wide fp32 outputs, 2 wherever it fits
@@ -94,6 +95,9 @@ struct CallScope {
   explicit CallScope(hipStream_t s_) : s(s_) {}
   void quiesce() { if (!done) { (void)hipStreamSynchronize(s); done = true; } }
 };
+
+// bytes behind a handle's index and value arrays that the sparse product's 16-byte requests may read
+constexpr size_t kEntrySlack = 16;
 
 // RAII device buffer so that every path gives back what it allocated; declare it after its CallScope.
 struct DevBuf {
@@ -287,6 +291,8 @@ struct SpmmArgs {
   // true when every row of X, the last one included, is backed by ldx readable elements (library
   // buffers with a padded leading dimension): vector loads may then run past column d
   bool x_rows_padded = false;
+  // the same for writing the rows of Y and Y2 and for reading those of Zprev, up to 16 bytes
+  bool y_rows_padded = false, z_rows_padded = false;
   // a product split by column range (Sec. 4.1, the block form: local part first, then the received rows):
   // 0 whole rows; 1 entries [ptr[r], mid[r]) and plain store; 2 entries [mid[r], ptr[r+1]) added to Y
   int part = 0;
@@ -317,11 +323,12 @@ struct GemmEpilogue {
   void* C2 = nullptr;            // optional second output: value before ReLU
   int64_t ldc2 = 0;
   int max_blocks = 0;            // > 0: a kernel with one workgroup per compute unit launches at most this many
+  bool b_trans = false;          // B is stored [N x K] (ldb >= K): the product is A B^T
 };
 // true when gemm_nn runs this product on the kernel that occupies whole compute units, one workgroup each, and
 // therefore honours GemmEpilogue::max_blocks (the rest of the chip is left to a kernel on another stream)
 bool gemm_nn_limits_blocks(const void* A, int64_t lda, int64_t M, int N, int K, int dtype);
-// C[M x N] = A[M x K] * B[K x N];  A, C (and C2, mask) have element type dtype, B is f32.
+// C[M x N] = A[M x K] * B[K x N] (B^T where epi.b_trans);  A, C (and C2, mask) have element type dtype, B is f32.
 int gemm_nn(const void* A, int64_t lda, const float* B, int64_t ldb, void* C, int64_t ldc,
             int64_t M, int N, int K, int dtype, const GemmEpilogue& epi, hipStream_t s);
 // C[M x N] (f32) = A[Kdim x M]^T * B[Kdim x N], Kdim huge: split over blocks, partial tiles in ws
@@ -364,8 +371,6 @@ int gemm_tn_direct_partials(const void* A, int64_t lda, const void* B, int64_t l
 int stream_pause(hipStream_t s);
 // dst[rows x ld_dst] = src[rows x d] (leading dimension ld_src), zero in the padding columns
 int pad_rows(const void* src, int64_t ld_src, void* dst, int64_t ld_dst, int64_t rows, int d, int dtype, hipStream_t s);
-// Wt[N x K] = W[K x N]^T (f32, small)
-int transpose_f32(const float* W, int K, int N, float* Wt, hipStream_t s);
 // out[c] = sum_i G[i, c]  (deterministic), ws at least colsum_ws_bytes
 size_t colsum_ws_bytes(int64_t rows, int N);
 int colsum(const void* G, int64_t ldg, int64_t rows, int N, int dtype, float* out, void* ws,

@@ -400,8 +400,8 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
 
   DevBuf rowptr, col, val, deg;
   GCN_TRY(rowptr.alloc(sc, sizeof(int64_t) * (size_t)(nr + 1)));
-  GCN_TRY(col.alloc(sc, sizeof(int32_t) * (size_t)nnz));
-  GCN_TRY(val.alloc(sc, sizeof(float) * (size_t)nnz));
+  GCN_TRY(col.alloc(sc, sizeof(int32_t) * (size_t)nnz + kEntrySlack));
+  GCN_TRY(val.alloc(sc, sizeof(float) * (size_t)nnz + kEntrySlack));
   GCN_TRY(deg.alloc(sc, sizeof(int32_t) * (size_t)nr));
   uint64_t* ukeys = other;                  // unique keys, row-major order
   k_compact<<<grid_for(m), kThreads, 0, s>>>(sorted, flag.as<uint32_t>(), pos.as<int64_t>(), m, colbits, ukeys, col.as<int32_t>());
@@ -425,8 +425,8 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
     GCN_TRY(pay_a.alloc(sc, sizeof(uint32_t) * (size_t)nnz));
     GCN_TRY(pay_b.alloc(sc, sizeof(uint32_t) * (size_t)nnz));
     GCN_TRY(colptr.alloc(sc, sizeof(int64_t) * (size_t)(nc + 1)));
-    GCN_TRY(rowidx.alloc(sc, sizeof(int32_t) * (size_t)nnz));
-    GCN_TRY(val_t.alloc(sc, sizeof(float) * (size_t)nnz));
+    GCN_TRY(rowidx.alloc(sc, sizeof(int32_t) * (size_t)nnz + kEntrySlack));
+    GCN_TRY(val_t.alloc(sc, sizeof(float) * (size_t)nnz + kEntrySlack));
     uint64_t* tk_a = sorted;               // the sorted-with-duplicates buffer is free again
     k_make_tkeys<<<grid_for(nnz), kThreads, 0, s>>>(ukeys, nnz, colbits, tk_a, pay_a.as<uint32_t>());
     GCN_CHECK_LAUNCH();

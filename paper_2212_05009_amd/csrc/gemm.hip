@@ -67,6 +67,7 @@ struct NnArgs {
   const void* A; int64_t lda; const float* B; int64_t ldb; void* C; int64_t ldc;
   int64_t M; int N; int K; int vecA; int vecB;
   const float* bias; int relu; const void* mask; int64_t ldmask; int64_t mask_rows; void* C2; int64_t ldc2;
+  int trans;               // B is stored [N x K]
 };
 
 // WAVES_M x WAVES_N wavefronts; each owns TM x TN accumulator tiles of 32 x 32
@@ -97,7 +98,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   float ra[A_IT][4], rb[B_IT][4];
   // interior tiles of aligned operands take plain 16-byte loads; edges go element by element
   const bool a_in = a.vecA == 4 && m0 + BM <= a.M;
-  const bool b_in = a.vecB == 4 && n0 + BN <= a.N;
+  const bool b_in = a.vecB == 4 && n0 + BN <= a.N && !a.trans;
   auto fetch = [&](int k0) {
     const bool k_in = k0 + BK <= a.K;
     if (a_in && k_in) {
@@ -129,7 +130,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         const int q = it * 256 + t;                 // group id: k = q / (BN/4), n-quad = q % (BN/4)
         const int k = q / (BN / 4);
         const int nq = (q % (BN / 4)) * 4;
-        if (k < BK && k0 + k < a.K) load4<float>(a.B + (int64_t)(k0 + k) * a.ldb, n0 + nq, a.N, a.vecB, rb[it]);
+        if (a.trans) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            rb[it][i] = (k < BK && k0 + k < a.K && n0 + nq + i < a.N) ? a.B[(int64_t)(n0 + nq + i) * a.ldb + k0 + k] : 0.f;
+        } else if (k < BK && k0 + k < a.K) load4<float>(a.B + (int64_t)(k0 + k) * a.ldb, n0 + nq, a.N, a.vecB, rb[it]);
         else { rb[it][0] = rb[it][1] = rb[it][2] = rb[it][3] = 0.f; }
       }
     }
@@ -268,7 +273,7 @@ int gemm_nn(const void* A, int64_t lda, const float* B, int64_t ldb, void* C, in
     return gemm_nn_direct(A, lda, B, ldb, C, ldc, M, N, K, dtype, epi, s);
   }
   NnArgs a{A, lda, B, ldb, C, ldc, M, N, K, pick_vec(A, lda, K, es), pick_vec(B, ldb, N, 4),
-           epi.bias, epi.relu, epi.mask, epi.ldmask, epi.mask_rows, epi.C2, epi.ldc2};
+           epi.bias, epi.relu, epi.mask, epi.ldmask, epi.mask_rows, epi.C2, epi.ldc2, epi.b_trans ? 1 : 0};
   if (dtype == GCN_BF16 && a.vecA == 2) a.vecA = 1;
   return dtype == GCN_BF16 ? gemm_nn_t<bf16_t>(a, s) : gemm_nn_t<float>(a, s);
 }
@@ -487,21 +492,6 @@ int gemm_tn(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, in
 
 bool gemm_tn_limits_blocks(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype) {
   return use_direct() && !(dtype == GCN_BF16 && gemm_tn_bf16_ok(A, lda, B, ldb, Kd, M, N)) && gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype);
-}
-
-// ------------------------------------------------------------------------------------------
-__global__ void k_transpose(const float* __restrict__ W, int K, int N, float* __restrict__ Wt) {
-  int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (int64_t)K * N) return;
-  int n = (int)(e / K), k = (int)(e % K);
-  Wt[e] = W[(int64_t)k * N + n];
-}
-
-int transpose_f32(const float* W, int K, int N, float* Wt, hipStream_t s) {
-  ProfScope ps(GCN_K_OTHER, s, N, GCN_F32, K, 0, 8.0 * K * N, 8.0 * K * N, 0.0);
-  k_transpose<<<(unsigned)ceil_div((int64_t)K * N, 256), 256, 0, s>>>(W, K, N, Wt);
-  GCN_CHECK_LAUNCH();
-  return GCN_OK;
 }
 
 // column sums: block b adds rows [b*kRows, ...) per column into partial[b][c]; then fp64 finish

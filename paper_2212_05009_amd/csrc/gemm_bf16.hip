@@ -29,6 +29,7 @@ struct NnBf16Args {
   const bf16_t* A; int64_t lda; const float* W; int64_t ldw; bf16_t* C; int64_t ldc;
   int64_t M; int N; int K;
   const float* bias; int relu; const bf16_t* mask; int64_t ldmask; bf16_t* C2; int64_t ldc2;
+  int trans;              // W is stored [N x K]
   int wide_requests;      // rows of A aligned to 16 bytes and K in {32, 64, 128, 256}: 16-byte requests, 16x16x32 MFMA
 };
 
@@ -78,14 +79,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
   {
     bf16_t* wl = reinterpret_cast<bf16_t*>(lds_bf16);
     for (int e = threadIdx.x; e < KL * KS * NT * 16; e += kThreads) {      // zero beyond K and N
-      const int k = e / (NT * 16), n = e % (NT * 16);
+      // numbered along the rows of W as it is stored
+      const int k = a.trans ? e % (KL * KS) : e / (NT * 16), n = a.trans ? e / (KL * KS) : e % (NT * 16);
       const int s = k / KS, q = (k % KS) / LV, el = k % LV;
       int t = n >> 4, cc = n & 15;
       if constexpr (kPair) {           // column n is entry 4 (n % 32 / 8) + n % 4 of tile 2 (n / 32) + (n % 8) / 4
         t = 2 * (n >> 5) + ((n & 7) >> 2);
         cc = 4 * ((n & 31) >> 3) + (n & 3);
       }
-      wl[(((s * NT + t) * 64 + q * 16 + cc) * LV) + el] = (k < a.K && n < a.N) ? f32_to_bf16(a.W[(int64_t)k * a.ldw + n]) : (bf16_t)0;
+      wl[(((s * NT + t) * 64 + q * 16 + cc) * LV) + el] = (k < a.K && n < a.N) ? f32_to_bf16(a.W[a.trans ? (int64_t)n * a.ldw + k : (int64_t)k * a.ldw + n]) : (bf16_t)0;
     }
   }
   __syncthreads();
@@ -422,7 +424,7 @@ int gemm_nn_bf16(const void* A, int64_t lda, const float* W, int64_t ldw, void* 
                  const GemmEpilogue& epi, hipStream_t s) {
   NnBf16Args a{(const bf16_t*)A, lda, W, ldw, (bf16_t*)C, ldc, M, N, K,
                epi.bias, epi.relu, (const bf16_t*)epi.mask, epi.ldmask, (bf16_t*)epi.C2, epi.ldc2,
-               wide_requests(A, lda, K) ? 1 : 0};
+               epi.b_trans ? 1 : 0, wide_requests(A, lda, K) ? 1 : 0};
   switch (nn_tiles_bf16(N)) {
     case 1: return launch_k<1>(a, s);
     case 2: return launch_k<2>(a, s);

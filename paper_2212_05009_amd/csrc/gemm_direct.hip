@@ -69,7 +69,23 @@ struct NnDirectArgs {
   const void* A; int64_t lda; const float* W; int64_t ldw; void* C; int64_t ldc;
   int64_t M; int N; int K; int vecA; int vecC; int vecC2; int vecM;
   const float* bias; int relu; const void* mask; int64_t ldmask; int64_t mask_rows; void* C2; int64_t ldc2;
+  int trans;               // W is stored [N x K]
 };
+
+// put(k, n, W[k][n]) for every element of the LDS copy of W (Kp x NP elements, zero beyond K and N), walked along the
+// rows of W as it is stored in global memory
+template <int NP, typename F>
+__device__ __forceinline__ void walk_w(const float* __restrict__ W, int64_t ldw, int trans, int K, int N, int Kp, int threads, F put) {
+  if (trans) {
+    for (int n = threadIdx.x / 64; n < NP; n += threads / 64)
+      for (int k = threadIdx.x % 64; k < Kp; k += 64) put(k, n, (k < K && n < N) ? W[(int64_t)n * ldw + k] : 0.f);
+  } else {
+    for (int e = threadIdx.x; e < Kp * NP; e += threads) {
+      const int k = e / NP, n = e % NP;
+      put(k, n, (k < K && n < N) ? W[(int64_t)k * ldw + n] : 0.f);
+    }
+  }
+}
 
 constexpr int kNnThreads = 512;
 constexpr int kNnKU = 8;          // 16-wide k steps whose loads are issued together
@@ -81,10 +97,7 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(NT <
   extern __shared__ float Ws[];                      // [Kp][LDW], zero beyond K and N
   constexpr int LDW = NT * 16 + 4;                    // 4 k-rows apart land 16 banks apart
   const int Kp = (a.K + 15) & ~15;
-  for (int e = threadIdx.x; e < Kp * NT * 16; e += kNnThreads) {
-    const int k = e / (NT * 16), n = e % (NT * 16);
-    Ws[k * LDW + n] = (k < a.K && n < a.N) ? a.W[(int64_t)k * a.ldw + n] : 0.f;
-  }
+  walk_w<NT * 16>(a.W, a.ldw, a.trans, a.K, a.N, Kp, kNnThreads, [&](int k, int n, float v) { Ws[k * LDW + n] = v; });
   __syncthreads();
 
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -232,12 +245,10 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(NT <
   constexpr bool kQuad = NT % 4 == 0;
   constexpr int TQ = kQuad ? NT / 4 : 1;
   const int chunks = (a.K + 16 * KU - 1) / (16 * KU);   // k chunks per tile
-  for (int e = threadIdx.x; e < chunks * 16 * KU * NT * 16; e += kNnThreads) {      // zero beyond K and N
-    const int k = e / (NT * 16), n = e % (NT * 16);
+  walk_w<NT * 16>(a.W, a.ldw, a.trans, a.K, a.N, chunks * 16 * KU, kNnThreads, [&](int k, int n, float v) {
     const int t = n >> 4, cc = n & 15;
-    const int at = kQuad ? ((k * TQ + (t >> 2)) * 16 + cc) * 4 + (t & 3) : k * LDW + n;
-    Ws[at] = (k < a.K && n < a.N) ? a.W[(int64_t)k * a.ldw + n] : 0.f;
-  }
+    Ws[kQuad ? ((k * TQ + (t >> 2)) * 16 + cc) * 4 + (t & 3) : k * LDW + n] = v;
+  });
   __syncthreads();
 
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -474,7 +485,7 @@ int gemm_nn_direct(const void* A, int64_t lda, const float* W, int64_t ldw, void
   auto vec_of = [&](const void* p, int64_t ld) { return (p && (ld % 4) == 0 && ((uintptr_t)p % (4 * es)) == 0) ? 4 : 1; };
   NnDirectArgs a{A, lda, W, ldw, C, ldc, M, N, K, vec_of(A, lda), vec_of(C, ldc), vec_of(epi.C2, epi.ldc2),
                  vec_of(epi.mask, epi.ldmask),
-                 epi.bias, epi.relu, epi.mask, epi.ldmask, epi.mask_rows, epi.C2, epi.ldc2};
+                 epi.bias, epi.relu, epi.mask, epi.ldmask, epi.mask_rows, epi.C2, epi.ldc2, epi.b_trans ? 1 : 0};
   return dtype == GCN_BF16 ? nn_dispatch<bf16_t>(a, s) : nn_dispatch<float>(a, s);
 }
 
@@ -773,12 +784,20 @@ static bool tn_wide_ok(const void* A, int64_t lda, const void* B, int64_t ldb, i
 // column tiles of B per block in the vector variant: all of B for up to 256 columns
 int tn_wide_wn(int N) { return N <= 64 ? 1 : N <= 128 ? 2 : 4; }
 
+// Fewest rows per split.  A split costs its partial tile (written, then read by the sum), so wide outputs keep 512
+// rows; for narrow ones the tile is small and what counts is the chain of row chunks of a block: with 512 rows a
+// short sum (4096 rows x 64 x 16) ran on 8 workgroups for 19 us.
+static int64_t tn_min_rows(int M, int N) {
+  const int64_t r = (int64_t)M * N / 32;
+  return r < 64 ? 64 : r > 512 ? 512 : round_up(r, 64);
+}
+
 // splits of the vector variant: about two blocks per compute unit
 int tn_wide_splits(int64_t Kd, int M, int N) {
   const int blocks = tune().gemm_tn_blocks;
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, (N <= 32 ? 32 : 64) * tn_wide_wn(N));
   int64_t want = ceil_div(blocks, tiles);
-  int64_t max_by_k = ceil_div(Kd, 512);
+  int64_t max_by_k = ceil_div(Kd, tn_min_rows(M, N));
   int64_t ns = want < max_by_k ? want : max_by_k;
   return (int)(ns < 1 ? 1 : ns);
 }
@@ -788,7 +807,7 @@ static int tn_direct_tn(int N) { return N <= 32 ? 1 : 2; }
 static int tn_direct_splits(int64_t Kd, int M, int N) {
   const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 32 * tn_direct_tn(N));
   int64_t want = ceil_div(1024, tiles);                // about four blocks per compute unit
-  int64_t max_by_k = ceil_div(Kd, 512);                // at least 512 rows per block
+  int64_t max_by_k = ceil_div(Kd, tn_min_rows(M, N));
   int64_t ns = want < max_by_k ? want : max_by_k;
   return (int)(ns < 1 ? 1 : ns);
 }

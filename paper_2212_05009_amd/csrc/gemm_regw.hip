@@ -29,6 +29,7 @@ struct RegwArgs {
   const float* A; int64_t lda; const float* W; int64_t ldw; float* C; int64_t ldc;
   int64_t M; int N; int K;
   const float* bias; int relu; const float* mask; int64_t ldmask; int64_t mask_rows; float* C2; int64_t ldc2;
+  int trans;               // W is stored [N x K]
 };
 
 constexpr int kRegwTileFloats = 64 * 256;             // one tile of A in LDS: 64 rows of 64 quads
@@ -48,6 +49,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const float* __restrict__ Wg = a.W;
 
   // this wavefront's panel of W as MFMA operands
+  const int64_t sk = a.trans ? 1 : a.ldw, sn = a.trans ? a.ldw : 1;
   float wr[KS][4][2];
 #pragma unroll
   for (int s = 0; s < KS; ++s)
@@ -55,7 +57,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     for (int i = 0; i < 4; ++i) {
       const int k = 8 * s + 4 * h + i;
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct) wr[s][i][ct] = k < a.K ? Wg[(int64_t)k * a.ldw + n0 + 32 * ct + c] : 0.f;
+      for (int ct = 0; ct < 2; ++ct) {
+        const int n = n0 + 32 * ct + c;
+        wr[s][i][ct] = k < a.K ? Wg[k * sk + n * sn] : 0.f;
+      }
     }
 
   float bias[2];
@@ -202,7 +207,7 @@ static int regw_launch(const RegwArgs& a, unsigned blocks, hipStream_t s) {
 int gemm_nn_regw(const void* A, int64_t lda, const float* W, int64_t ldw, void* C, int64_t ldc, int64_t M, int N, int K,
                  const GemmEpilogue& epi, hipStream_t s) {
   RegwArgs a{(const float*)A, lda, W, ldw, (float*)C, ldc, M, N, K, epi.bias, epi.relu, (const float*)epi.mask,
-             epi.ldmask, epi.mask_rows, (float*)epi.C2, epi.ldc2};
+             epi.ldmask, epi.mask_rows, (float*)epi.C2, epi.ldc2, epi.b_trans ? 1 : 0};
   static const int cus = [] {
     int dev = 0;
     hipDeviceProp_t p;

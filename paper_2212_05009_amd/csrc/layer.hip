@@ -86,7 +86,20 @@ static int64_t padded_operand_ld(const gcn_csr* A, bool transposed, int d, int d
   const int64_t ldp = gather_ld_for(A, transposed, d, dtype);
   if (ldp == ldx) return ldx;
   const int64_t n_cols = transposed ? A->nr : A->nc;
+  // 2-byte elements in rows that start between words can only be gathered one by one (bf16, width 81, 45 entries per
+  // row: 580 us against 120 padded)
+  if ((ldx * es) % 4 != 0 && d > 1 && A->nnz >= 2 * n_cols) return ldp;
   if (A->nnz < 8 * n_cols) return ldx;
+  if ((ldx * es) % 16 != 0) {        // the column sweep, which takes 16-byte aligned rows only, is worth the copy
+    SpmmArgs probe{};
+    probe.owner = const_cast<gcn_csr*>(A);
+    probe.transposed = transposed;
+    probe.n_rows = transposed ? A->nc : A->nr;
+    probe.n_cols = n_cols;
+    probe.nnz = A->nnz; probe.d = d; probe.dtype = dtype;
+    probe.X = reinterpret_cast<const void*>((uintptr_t)256); probe.ldx = ldp; probe.x_rows_padded = true;
+    if (spmm_panel_wanted(probe)) return ldp;
+  }
   return lines_touched(ldp * es, (int64_t)d * es) <= 0.85 * lines_touched(ldx * es, (int64_t)d * es) ? ldp : ldx;
 }
 
@@ -155,15 +168,10 @@ struct Carver {              // hands out 256-byte aligned pieces of the workspa
 
 using namespace gcn;
 
-extern "C" int gcn_layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, const float* W, const float* bias,
-                             int d_in, int d_out, int act, int dtype, void* Z, void* Hout, void* AH_save,
-                             void* stream) {
-  return gcn_layer_fwd_ld(A, H, ldh, W, bias, d_in, d_out, act, dtype, Z, d_out, Hout, d_out, AH_save, d_in, stream);
-}
-
-extern "C" int gcn_layer_fwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, const float* W, const float* bias,
-                                int d_in, int d_out, int act, int dtype, void* Z, int64_t ldz, void* Hout, int64_t ldo,
-                                void* AH_save, int64_t ldah, void* stream) {
+// h_backed: a pitch of H beyond its row width is backed to the end of every row (the contract of the _ld calls)
+static int layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_backed, const float* W, const float* bias,
+                     int d_in, int d_out, int act, int dtype, void* Z, int64_t ldz, void* Hout, int64_t ldo,
+                     void* AH_save, int64_t ldah, void* stream) {
   clear_error();
   if (!A || !H || !W || !Hout) return fail(GCN_EINVAL, "gcn_layer_fwd: NULL argument");
   if (d_in < 1 || d_out < 1 || ldh < d_in) return fail(GCN_EINVAL, "gcn_layer_fwd: bad dimensions");
@@ -192,7 +200,8 @@ extern "C" int gcn_layer_fwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, 
         SpmmArgs sp{A->rowptr, A->col, A->val, &A->sched, A->nr, A->nc, A->nnz, false, A->nr, Hp ? Hp : H, Hp ? ldhp : ldh, AH, ldAH,
                     nullptr, 0, d_in, dtype, GCN_EPI_NONE, nullptr, nullptr, 0};
         sp.owner = Am;
-        sp.x_rows_padded = Hp != nullptr;
+        sp.x_rows_padded = Hp != nullptr || h_backed;
+        sp.y_rows_padded = true;            // a pitch of the outputs beyond their width comes from the _ld call
         GemmEpilogue epi;
         epi.bias = bias; epi.relu = relu; epi.C2 = Z; epi.ldc2 = ldz;
         const bool pipelined = side_chunks() > 0 && overlap_worthwhile(A->nr, A->nnz, d_in) && !spmm_panel_wanted(sp) &&
@@ -232,7 +241,7 @@ extern "C" int gcn_layer_fwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, 
         SpmmArgs sp{A->rowptr, A->col, A->val, &A->sched, A->nr, A->nc, A->nnz, false, A->nr, P, ldp, Hout, ldo, Z, ldz,
                     d_out, dtype, relu ? GCN_EPI_RELU : GCN_EPI_NONE, bias, nullptr, 0};
         sp.owner = Am;
-        sp.x_rows_padded = true;
+        sp.x_rows_padded = sp.y_rows_padded = true;
         GCN_TRY(spmm_launch(sp, hub, s));
       }
     }
@@ -241,16 +250,22 @@ extern "C" int gcn_layer_fwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, 
   return GCN_OK;
 }
 
-extern "C" int gcn_layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, const void* AH_saved, const float* W,
-                             int d_in, int d_out, int dtype, const void* G, const void* Zprev, float* dW,
-                             float* dbias, void* dH, void* stream) {
-  return gcn_layer_bwd_ld(A, H, ldh, AH_saved, d_in, W, d_in, d_out, dtype, G, d_out, Zprev, d_in, dW, dbias, dH, d_in, stream);
+extern "C" int gcn_layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, const float* W, const float* bias,
+                             int d_in, int d_out, int act, int dtype, void* Z, void* Hout, void* AH_save,
+                             void* stream) {
+  return layer_fwd(A, H, ldh, false, W, bias, d_in, d_out, act, dtype, Z, d_out, Hout, d_out, AH_save, d_in, stream);
 }
 
-extern "C" int gcn_layer_bwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, const void* AH_saved, int64_t ldah,
-                                const float* W, int d_in, int d_out, int dtype, const void* G, int64_t ldg,
-                                const void* Zprev, int64_t ldzp, float* dW, float* dbias, void* dH, int64_t lddh,
-                                void* stream) {
+extern "C" int gcn_layer_fwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, const float* W, const float* bias,
+                                int d_in, int d_out, int act, int dtype, void* Z, int64_t ldz, void* Hout, int64_t ldo,
+                                void* AH_save, int64_t ldah, void* stream) {
+  return layer_fwd(A, H, ldh, true, W, bias, d_in, d_out, act, dtype, Z, ldz, Hout, ldo, AH_save, ldah, stream);
+}
+
+static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_backed, const void* AH_saved, int64_t ldah,
+                     const float* W, int d_in, int d_out, int dtype, const void* G, int64_t ldg,
+                     const void* Zprev, int64_t ldzp, float* dW, float* dbias, void* dH, int64_t lddh,
+                     void* stream) {
   clear_error();
   if (!A || !H || !W || !G || !dW) return fail(GCN_EINVAL, "gcn_layer_bwd: NULL argument");
   if (d_in < 1 || d_out < 1 || ldh < d_in) return fail(GCN_EINVAL, "gcn_layer_bwd: bad dimensions");
@@ -271,24 +286,22 @@ extern "C" int gcn_layer_bwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, 
     size_t hub_bytes = spmm_ws_bytes(&A->sched, dmax);
     if (have_csc && spmm_ws_bytes(&A->sched_t, dmax) > hub_bytes) hub_bytes = spmm_ws_bytes(&A->sched_t, dmax);
     void* hub = ws.take(hub_bytes);
-    float* Wt = (float*)ws.take(sizeof(float) * (size_t)d_in * d_out);
     void* cs = dbias ? ws.take(colsum_ws_bytes(A->nr, d_out)) : nullptr;
     if (pass && dbias) GCN_TRY(colsum(G, ldg, A->nr, d_out, dtype, dbias, cs, s));
 
     if (via_T) {
-      const int64_t ldt = round_up(d_out, 4);
+      const int64_t ldt = round_up(d_out, 16 / (int64_t)es);
       void* T = ws.take((size_t)A->nc * ldt * es);
       const int64_t kd = AH_saved ? A->nr : A->nc;
       void* tn = ws.take(gemm_tn_ws_bytes(kd, d_in, d_out));
-      // rows of G whose pitch is not a multiple of 16 bytes are first copied to a padded buffer: the
-      // sparse product then gathers with vector loads
-      // a caller's G that the sparse product cannot gather with 16-byte requests, or only across more lines than
-      // need be, is first copied to a padded buffer
+      // a caller's G that the sparse product cannot gather with vector requests (2-byte elements in rows that start
+      // between words, rows shorter than a vector), or only across more lines than need be, is first copied to a padded buffer
       // (a pitched G is backed to the end of every row, the last included: the contract of the _ld entry points; so a
       // row that is no whole number of 16-byte vectors can still be gathered with them when the pitch leaves room)
       const bool g_rows_backed = ldg >= round_up(d_out, 16 / (int64_t)es);
-      const bool g_unaligned = (ldg * (int64_t)es) % 16 != 0 || ((uintptr_t)G % 16) != 0 ||
-                               ((d_out * (int64_t)es) % 16 != 0 && !g_rows_backed);
+      const int64_t g_bytes = d_out * (int64_t)es;
+      const bool g_unaligned = (ldg * (int64_t)es) % 4 != 0 || ((uintptr_t)G % 4) != 0 ||
+                               (!g_rows_backed && (g_bytes % 4 != 0 || (g_bytes < 16 && (g_bytes & (g_bytes - 1)) != 0)));
       const int64_t ldgp = g_unaligned ? gather_ld_for(A, true, d_out, dtype) : padded_operand_ld(A, true, d_out, dtype, ldg);
       const bool pad_g = g_unaligned || ldgp != ldg;
       void* Gp = pad_g ? ws.take((size_t)A->nr * ldgp * es) : nullptr;
@@ -297,6 +310,7 @@ extern "C" int gcn_layer_bwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, 
         SpmmArgs sp{A->colptr, A->rowidx, A->val_t, &A->sched_t, A->nc, A->nr, A->nnz, true, A->nr, pad_g ? Gp : G,
                     pad_g ? ldgp : ldg, T, ldt, nullptr, 0, d_out, dtype, GCN_EPI_NONE, nullptr, nullptr, 0};
         sp.x_rows_padded = pad_g || g_rows_backed;
+        sp.y_rows_padded = true;
         sp.owner = Am;
         // dW from a saved A^ H needs nothing of this product: it runs beside it
         SideStream side;
@@ -308,14 +322,17 @@ extern "C" int gcn_layer_bwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, 
         }
         GCN_TRY(spmm_launch(sp, hub, s));
         if (dH) {
-          GCN_TRY(transpose_f32(W, d_in, d_out, Wt, s));
           // owned rows carry the ReLU mask, halo rows do not: two calls, so that each is uniform in its epilogue
           GemmEpilogue epi;
           epi.mask = Zprev; epi.ldmask = ldzp; epi.mask_rows = Zprev ? A->nr : 0;
-          GCN_TRY(gemm_nn(T, ldt, Wt, d_in, dH, lddh, A->nr, d_in, d_out, dtype, epi, s));
-          if (A->nh > 0)
-            GCN_TRY(gemm_nn((const char*)T + (size_t)A->nr * ldt * es, ldt, Wt, d_in, (char*)dH + (size_t)A->nr * lddh * es, lddh,
-                            A->nh, d_in, d_out, dtype, GemmEpilogue(), s));
+          epi.b_trans = true;                // W^T
+          GCN_TRY(gemm_nn(T, ldt, W, d_out, dH, lddh, A->nr, d_in, d_out, dtype, epi, s));
+          if (A->nh > 0) {
+            GemmEpilogue plain;
+            plain.b_trans = true;
+            GCN_TRY(gemm_nn((const char*)T + (size_t)A->nr * ldt * es, ldt, W, d_out, (char*)dH + (size_t)A->nr * lddh * es, lddh,
+                            A->nh, d_in, d_out, dtype, plain, s));
+          }
         }
         if (beside) GCN_TRY(side.join());
         else if (AH_saved) GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, s));
@@ -334,9 +351,9 @@ extern "C" int gcn_layer_bwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, 
         const bool beside = dH && AH_saved && overlap_worthwhile(A->nc, A->nnz, d_in) &&
                             gemm_tn_limits_blocks(AH_saved, ldah, G, ldg, A->nr, d_in, d_out, dtype);
         if (dH) {
-          GCN_TRY(transpose_f32(W, d_in, d_out, Wt, s));
           GemmEpilogue epi;
-          GCN_TRY(gemm_nn(G, ldg, Wt, d_in, Q, ldq, A->nr, d_in, d_out, dtype, epi, s));
+          epi.b_trans = true;
+          GCN_TRY(gemm_nn(G, ldg, W, d_out, Q, ldq, A->nr, d_in, d_out, dtype, epi, s));
           if (beside) {        // after Q = G W^T, which wants the matrix pipes of every compute unit itself
             GCN_TRY(side.fork(Am, s));
             GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, side.side, tune().overlap_cus));
@@ -344,7 +361,7 @@ extern "C" int gcn_layer_bwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, 
           SpmmArgs sp{A->colptr, A->rowidx, A->val_t, &A->sched_t, A->nc, A->nr, A->nnz, true, A->nr, Q, ldq, dH, lddh, nullptr, 0,
                       d_in, dtype, Zprev ? GCN_EPI_MASK : GCN_EPI_NONE, nullptr, Zprev, ldzp};
           sp.owner = Am;
-          sp.x_rows_padded = true;
+          sp.x_rows_padded = sp.y_rows_padded = sp.z_rows_padded = true;
           GCN_TRY(spmm_launch(sp, hub, s));
         }
         const void* ah = AH_saved; int64_t ld_ah = ldah;
@@ -353,7 +370,8 @@ extern "C" int gcn_layer_bwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, 
           SpmmArgs sp{A->rowptr, A->col, A->val, &A->sched, A->nr, A->nc, A->nnz, false, A->nr, Hp ? Hp : H, Hp ? ldhp : ldh, AH, ldq,
                       nullptr, 0, d_in, dtype, GCN_EPI_NONE, nullptr, nullptr, 0};
           sp.owner = Am;
-          sp.x_rows_padded = Hp != nullptr;
+          sp.x_rows_padded = Hp != nullptr || h_backed;
+          sp.y_rows_padded = true;
           GCN_TRY(spmm_launch(sp, hub, s));
           ah = AH; ld_ah = ldq;
         }
@@ -364,6 +382,19 @@ extern "C" int gcn_layer_bwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, 
     if (!pass) GCN_TRY(ensure_workspace(Am, ws.used));
   }
   return GCN_OK;
+}
+
+extern "C" int gcn_layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, const void* AH_saved, const float* W,
+                             int d_in, int d_out, int dtype, const void* G, const void* Zprev, float* dW,
+                             float* dbias, void* dH, void* stream) {
+  return layer_bwd(A, H, ldh, false, AH_saved, d_in, W, d_in, d_out, dtype, G, d_out, Zprev, d_in, dW, dbias, dH, d_in, stream);
+}
+
+extern "C" int gcn_layer_bwd_ld(const gcn_csr_t* A, const void* H, int64_t ldh, const void* AH_saved, int64_t ldah,
+                                const float* W, int d_in, int d_out, int dtype, const void* G, int64_t ldg,
+                                const void* Zprev, int64_t ldzp, float* dW, float* dbias, void* dH, int64_t lddh,
+                                void* stream) {
+  return layer_bwd(A, H, ldh, true, AH_saved, ldah, W, d_in, d_out, dtype, G, ldg, Zprev, ldzp, dW, dbias, dH, lddh, stream);
 }
 
 extern "C" int gcn_dense_fwd(const void* X, int64_t ldx, int64_t rows, const float* W, const float* bias, int d_in,
@@ -397,7 +428,6 @@ extern "C" int gcn_layer_bwd_pull(const gcn_csr_t* A, int phase, const void* H, 
   for (int pass = 0; pass < 2; ++pass) {
     Carver ws{pass ? (char*)Am->ws : nullptr};
     void* hub = ws.take(spmm_ws_bytes(&A->sched, d_out));
-    float* Wt = finish && dH ? (float*)ws.take(sizeof(float) * (size_t)d_in * d_out) : nullptr;
     void* cs = finish && dbias ? ws.take(colsum_ws_bytes(A->nr, d_out)) : nullptr;
     void* tn = finish ? ws.take(gemm_tn_ws_bytes(A->nr, d_in, d_out)) : nullptr;
     if (pass) {
@@ -413,10 +443,10 @@ extern "C" int gcn_layer_bwd_pull(const gcn_csr_t* A, int phase, const void* H, 
       if (finish) {
         if (dbias) GCN_TRY(colsum(G, ldg, A->nr, d_out, dtype, dbias, cs, s));
         if (dH) {
-          GCN_TRY(transpose_f32(W, d_in, d_out, Wt, s));
           GemmEpilogue epi;
           epi.mask = Zprev; epi.ldmask = d_in; epi.mask_rows = Zprev ? A->nr : 0;
-          GCN_TRY(gemm_nn(T, d_out, Wt, d_in, dH, d_in, A->nr, d_in, d_out, dtype, epi, s));
+          epi.b_trans = true;
+          GCN_TRY(gemm_nn(T, d_out, W, d_out, dH, d_in, A->nr, d_in, d_out, dtype, epi, s));
         }
         GCN_TRY(gemm_tn(H, ldh, T, d_out, dW, d_out, A->nr, d_in, d_out, dtype, tn, s));
       }

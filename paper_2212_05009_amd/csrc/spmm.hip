@@ -37,11 +37,13 @@ static bool aligned(const void* p, size_t a) { return p == nullptr || ((uintptr_
 // channels (and memory channels) those addresses select when P is a power of two.  Measured on a 2.45 M x 256 fp32
 // operand (R-MAT, 126 M entries): pitch 8 lines 17.6 / 15.4 / 15.5 / 17.2 ms for S = 1 / 2 / 4 / 8, pitch 9 lines
 // 16.5 / 14.7 / 13.9 ms for S = 2 / 4 / 8 (L2 hits 19 % -> 33 %).  With an odd pitch every slice gets one line
-// (up to 8 slices); otherwise the earlier rule stands: two slices for operands above 100 MB whose halves are whole lines.
+// (up to 8 slices); otherwise two slices for operands above 32 MB whose halves are whole lines (67 MB, width 64 fp32,
+// 45 entries per row: 205 -> 190 us).
 // Returns S and sets *vps (vectors of V elements per slice; 0: split evenly).
-static int pick_slices(const SpmmArgs& a, size_t es, int V, int* vps) {
+static int pick_slices(const SpmmArgs& a, size_t es, int V, bool short_rows, int* vps) {
   *vps = 0;
   const int forced = tune().spmm_slices;                 // override for experiments
+  if (short_rows && forced <= 0) return 1;
   const int64_t row_bytes = (int64_t)a.d * (int64_t)es, pitch = a.ldx * (int64_t)es;
   const double xbytes = (double)a.n_cols * (double)row_bytes;
   const bool on_lines = pitch % 128 == 0 && aligned(a.X, 128) && (int64_t)V * (int64_t)es == 16;
@@ -56,7 +58,7 @@ static int pick_slices(const SpmmArgs& a, size_t es, int V, int* vps) {
   }
   int S = 1;
   if (forced > 0) S = forced;
-  else if (xbytes > 100e6) S = 2;
+  else if (xbytes > 32e6) S = 2;
   while (S > 1 && (double)row_bytes / S < 128.0) S >>= 1;
   // a slice that does not consist of whole 128-byte lines makes every gathered row touch more lines in all than
   // the undivided row does: 400-byte rows (width 100) in two slices took 11.7 ms where one slice takes 8.0 ms
@@ -90,11 +92,34 @@ int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s) {
   if (a.part == 0 && !a.no_alloc && a.row_chunk < 0) GCN_TRY(spmm_panel_try(a, s, &swept));
   if (swept) return GCN_OK;
   const size_t es = a.dtype == GCN_BF16 ? 2 : 4;
-  // widest vector such that every feature-row load stays aligned (and inside the row's storage)
+  // Widest vector the rows admit: 16 bytes where they start on a 4-byte word and are at least that long.  The last
+  // vector of a row that is no whole number of vectors reads into the row's padding where that is allowed, else it is
+  // moved back to end with the row.
   int V = a.dtype == GCN_BF16 ? 8 : 4;
-  while (V > 1 && !((a.ldx % V) == 0 && aligned(a.X, V * es) && ((a.d % V) == 0 || a.x_rows_padded))) V >>= 1;
-  k.y_vec = (a.ldy % V) == 0 && aligned(a.Y, V * es) && (!a.Y2 || ((a.ldy2 % V) == 0 && aligned(a.Y2, V * es)));
-  k.S = pick_slices(a, es, V, &k.vps);
+  while (V > 1) {
+    const bool words = aligned(a.X, 4) && (a.ldx * (int64_t)es) % 4 == 0;
+    const bool whole = a.d % V == 0 || (a.x_rows_padded && a.ldx >= round_up(a.d, V));
+    if (words && (whole || (a.d >= V && (a.d * (int64_t)es) % 4 == 0))) { k.c_last = whole ? (int)round_up(a.d, V) - V : a.d - V; break; }
+    V >>= 1;
+  }
+  if (V == 1) k.c_last = a.d - 1;
+  const bool at_end = k.c_last == (int)round_up(a.d, V) - V;       // the last vector sits where its number says
+  auto row_words = [&](const void* p, int64_t ld) { return p == nullptr || (aligned(p, 4) && (ld * (int64_t)es) % 4 == 0); };
+  auto whole_rows = [&](const void* p, int64_t ld, bool padded) {
+    return p == nullptr || a.d % V == 0 || (at_end && padded && ld >= round_up(a.d, V));
+  };
+  k.y_vec = V * es >= 4 && row_words(a.Y, a.ldy) && row_words(a.Y2, a.ldy2) && row_words(a.Zprev, a.ldz);
+  k.y_full = whole_rows(a.Y, a.ldy, a.y_rows_padded) && whole_rows(a.Y2, a.ldy2, a.y_rows_padded) && whole_rows(a.Zprev, a.ldz, a.z_rows_padded);
+  k.nvec = (int)ceil_div(a.d, V);
+  // Short rows of 9 to 16 vectors: undivided, on groups of 8 lanes with two vectors each.  What a wavefront costs is the
+  // chain of dependent loads (row, range, indices, features), so it should hold many rows, and slices would repeat the
+  // chain.  Measured, 500 K rows with 6.6 entries each, width 50: 32 lanes with 8-byte requests 164 us, two slices 190 us,
+  // this form 148 us (6.6 TB/s out of L2, the rate of the fabric).  With four vectors a lane (width 128, 8 entries per
+  // row) it loses to four slices, 466 against 417 us: wide rows are bound by what misses L2, of which slices keep more.
+  const double mean_len = (double)a.nnz / (double)a.n_rows * (a.part ? 0.5 : 1.0);
+  k.short_rows = V * (int)es == 16 && k.nvec > 8 && k.nvec <= 16 && (tune().spmm_short >= 0 ? tune().spmm_short != 0 : mean_len < 16.0);
+  k.S = pick_slices(a, es, V, k.short_rows != 0, &k.vps);
+  if (k.vps <= 0) k.vps = (int)ceil_div(k.nvec, k.S);
   SpmmProf pf;
   pf.kind = a.transposed ? GCN_K_SPMM_T : GCN_K_SPMM; pf.dtype = a.dtype; pf.rows = a.n_rows; pf.nnz = a.nnz;
   const double csr = 8.0 * (double)a.nnz + 8.0 * (double)(a.n_rows + 1), fe = (double)es * a.d;
@@ -109,11 +134,12 @@ int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s) {
     pf.nnz = (int64_t)((double)a.nnz * share);
     pf.row_chunk = a.row_chunk; pf.row_chunk_n = a.row_chunk_n;
   }
-  // 32-bit addressing of X: row index and row pitch below 2^24, whole matrix below 4 GiB
+  // 32-bit addressing of X: row index and row pitch below 2^24, whole matrix below 4 GiB (kNoOffset)
   const double xspan = (double)a.n_cols * (double)a.ldx * (double)es;
-  const bool narrow = a.n_cols < (1 << 24) && (double)a.ldx * (double)es < (double)(1 << 24) && xspan < 4294967296.0 &&
+  const bool narrow = a.n_cols < (1 << 24) && (double)a.ldx * (double)es < (double)(1 << 24) && xspan < (double)kNoOffset &&
                       !tune().spmm_wide;
   k.row_bytes = narrow ? (uint32_t)(a.ldx * (int64_t)es) : 0u;
+  k.x_bytes = narrow ? (uint32_t)(a.n_cols * a.ldx * (int64_t)es) : 0u;
   if (a.dtype == GCN_BF16) return spmm_dispatch_bf16(k, a.sched, pf, V, narrow, s);
   return spmm_dispatch_f32(k, a.sched, pf, V, narrow, s);
 }
