@@ -79,13 +79,10 @@ struct ProfSuppress {
 };
 
 // ---- device memory kept between calls (pool.hip) ---------------------------------------------
-// pool_free may be called only when no enqueued work can still touch the block.
+// idle: no enqueued work can still touch the block, so that any thread and stream may have it next; else it goes back to
+// the runtime, which waits for such work by itself.
 int pool_alloc(void** p, size_t bytes);
-void pool_free(void* p);
-// a pinned host page for numbers that a call reads back
-constexpr size_t kPinnedBytes = 16384;
-int pinned_take(void** p);
-void pinned_give(void* p);
+void pool_free(void* p, bool idle = true);
 
 // The stream a call's temporaries are used on.  `done` is set once the call has waited for it; a call that leaves early
 // waits when its first temporary goes back.
@@ -93,7 +90,7 @@ struct CallScope {
   hipStream_t s;
   bool done = false;
   explicit CallScope(hipStream_t s_) : s(s_) {}
-  void quiesce() { if (!done) { (void)hipStreamSynchronize(s); done = true; } }
+  bool quiesce() { return done || (done = hipStreamSynchronize(s) == hipSuccess); }
 };
 
 // bytes behind a handle's index and value arrays that the sparse product's 16-byte requests may read
@@ -106,7 +103,7 @@ struct DevBuf {
   DevBuf() = default;
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
-  ~DevBuf() { if (p) { scope->quiesce(); pool_free(p); } }
+  ~DevBuf() { if (p) { pool_free(p, scope->quiesce()); } }
   int alloc(CallScope& sc, size_t bytes) {
     scope = &sc;
     return pool_alloc(&p, bytes);
@@ -274,7 +271,7 @@ int radix_sort_u64(uint64_t* keys_a, uint64_t* keys_b, uint32_t* pay_a, uint32_t
 
 // ---- schedule construction (csr_build.hip) -------------------------------------------------
 int build_schedule(const int64_t* ptr, int64_t n_rows, hipStream_t s, Schedule* out);
-void free_schedule(Schedule* sc);
+void free_schedule(Schedule* sc, bool idle = true);
 
 // ---- kernels behind the public entry points -------------------------------------------------
 struct SpmmArgs {
@@ -311,7 +308,7 @@ int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s);
 int spmm_panel_try(const SpmmArgs& a, hipStream_t s, bool* used);
 // whether spmm_panel_try would take this product (a.X only matters for its alignment)
 bool spmm_panel_wanted(const SpmmArgs& a);
-void free_panel_plans(gcn_csr* A);
+void free_panel_plans(gcn_csr* A, bool idle);
 // ptr[q] = first position whose key >> shift is >= q, q in [0, n_seg]; keys sorted, n >= 1
 int segment_boundaries(const uint64_t* keys, int64_t n, int shift, int64_t n_seg, int64_t* ptr, hipStream_t s);
 

@@ -232,11 +232,11 @@ __global__ void k_chunk_bounds(const int32_t* __restrict__ wave_rows, const int6
   if (c == 33) out[j * 35 + 34] = hub_chunk_ptr[lo];
 }
 
-void free_schedule(Schedule* sc) {
-  pool_free(sc->wave_rows);
-  pool_free(sc->hub_rows);
-  pool_free(sc->hub_chunk_ptr);
-  pool_free(sc->chunk_hub);
+void free_schedule(Schedule* sc, bool idle) {
+  pool_free(sc->wave_rows, idle);
+  pool_free(sc->hub_rows, idle);
+  pool_free(sc->hub_chunk_ptr, idle);
+  pool_free(sc->chunk_hub, idle);
   *sc = Schedule();
 }
 
@@ -529,14 +529,18 @@ extern "C" int gcn_csr_arrays(const gcn_csr_t* A, const int64_t** rowptr, const 
 
 extern "C" int gcn_csr_free(gcn_csr_t* A) {
   if (!A) return GCN_OK;
-  (void)hipDeviceSynchronize();
+  int device = A->device;
+  (void)hipGetDevice(&device);
+  if (device != A->device) (void)hipSetDevice(A->device);
+  const bool idle = hipDeviceSynchronize() == hipSuccess;
   void* ptrs[] = {A->rowptr, A->col, A->val, A->deg, A->halo_gid, A->colptr, A->rowidx, A->val_t, A->mid, A->ws};
-  for (void* p : ptrs) pool_free(p);
-  free_schedule(&A->sched);
-  free_schedule(&A->sched_t);
-  free_panel_plans(A);
+  for (void* p : ptrs) pool_free(p, idle);
+  free_schedule(&A->sched, idle);
+  free_schedule(&A->sched_t, idle);
+  free_panel_plans(A, idle);
   for (hipEvent_t e : A->side_events) if (e) (void)hipEventDestroy(e);
   if (A->side_stream) (void)hipStreamDestroy(A->side_stream);
+  if (device != A->device) (void)hipSetDevice(device);
   delete A;
   return GCN_OK;
 }

@@ -6,8 +6,8 @@
 // from a pool of freed blocks.
 //
 //  * A block enters the pool only when no enqueued work can touch it: the temporaries of a call after the call has
-//    waited for its stream, a handle's arrays after gcn_csr_free has waited for the device.  Any thread and any stream
-//    may therefore take it at once.
+//    waited for its stream, a handle's arrays after gcn_csr_free has waited for the handle's device.  Any thread and any
+//    stream may therefore take it at once.  Where the wait fails (another thread captures a graph), it is not kept.
 //  * A block serves requests of at least 3/4 of its size, so what is held and not used stays small.
 //  * Bounded: at most 1/64 of the device's memory is kept (4.5 of 288 GB), least recently freed blocks go first; a block
 //    that lies unused over 256 later returns goes back to the runtime; a failed hipMalloc empties the pool and retries.
@@ -38,7 +38,6 @@ struct Pool {
   std::mutex mu;
   std::unordered_map<void*, std::pair<int, size_t>> live;   // block -> device, size
   DevicePool dev[kPoolDevices];
-  std::vector<void*> pinned;                                // idle pinned host pages
 };
 
 Pool& pool() {
@@ -99,66 +98,47 @@ int pool_alloc(void** out, size_t bytes) {
       e = hipMalloc(&p, want);
     }
     if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? GCN_ENOMEM : GCN_EHIP, "hipMalloc(%zu bytes): %s", want, hipGetErrorString(e));
-    if (pooled) {
-      std::lock_guard<std::mutex> lock(P.mu);
-      P.live.emplace(p, std::make_pair(device, want));
-    }
     *out = p;
+    if (pooled) {
+      try {
+        std::lock_guard<std::mutex> lock(P.mu);
+        P.live.emplace(p, std::make_pair(device, want));
+      } catch (const std::bad_alloc&) {        // not on the list: pool_free returns it to the runtime
+      }
+    }
     return GCN_OK;
   } catch (const std::bad_alloc&) {
     return fail(GCN_ENOMEM, "host allocation failed");
   }
 }
 
-void pool_free(void* p) {
+void pool_free(void* p, bool idle) {
   if (!p) return;
+  Pool& P = pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  auto i = P.live.find(p);
+  if (i == P.live.end()) { (void)hipFree(p); return; }
+  const int device = i->second.first;
+  const size_t bytes = i->second.second;
+  P.live.erase(i);
+  DevicePool& d = P.dev[device];
+  if (!d.limit) {
+    hipDeviceProp_t prop;
+    d.limit = hipGetDeviceProperties(&prop, device) == hipSuccess ? prop.totalGlobalMem / 64 : (size_t)1 << 30;
+  }
+  ++d.returns;
+  if (!idle || bytes > d.limit) { (void)hipFree(p); return; }
+  const size_t listed = d.by_age.size();
   try {
-    Pool& P = pool();
-    std::lock_guard<std::mutex> lock(P.mu);
-    auto i = P.live.find(p);
-    if (i == P.live.end()) { (void)hipFree(p); return; }
-    const int device = i->second.first;
-    const size_t bytes = i->second.second;
-    P.live.erase(i);
-    DevicePool& d = P.dev[device];
-    if (!d.limit) {
-      hipDeviceProp_t prop;
-      d.limit = hipGetDeviceProperties(&prop, device) == hipSuccess ? prop.totalGlobalMem / 64 : (size_t)1 << 30;
-    }
-    ++d.returns;
-    if (bytes > d.limit) { (void)hipFree(p); return; }
     d.by_age.push_back(Block{p, bytes, d.returns});
     d.by_size.emplace(bytes, std::prev(d.by_age.end()));
-    d.held += bytes;
-    while (d.held > d.limit || d.by_age.front().freed_at + kIdleReturns < d.returns) drop(d, d.by_age.begin());
   } catch (const std::bad_alloc&) {
+    if (d.by_age.size() > listed) d.by_age.pop_back();
     (void)hipFree(p);
+    return;
   }
-}
-
-// Pinned host pages for the few numbers a call reads back: kPinnedBytes each, at most kMaxPinned kept.
-constexpr size_t kMaxPinned = 16;
-
-int pinned_take(void** out) {
-  *out = nullptr;
-  {
-    Pool& P = pool();
-    std::lock_guard<std::mutex> lock(P.mu);
-    if (!P.pinned.empty()) { *out = P.pinned.back(); P.pinned.pop_back(); return GCN_OK; }
-  }
-  GCN_HIP(hipHostMalloc(out, kPinnedBytes, hipHostMallocPortable));
-  return GCN_OK;
-}
-
-void pinned_give(void* p) {
-  if (!p) return;
-  try {
-    Pool& P = pool();
-    std::lock_guard<std::mutex> lock(P.mu);
-    if (P.pinned.size() < kMaxPinned) { P.pinned.push_back(p); return; }
-  } catch (const std::bad_alloc&) {
-  }
-  (void)hipHostFree(p);
+  d.held += bytes;
+  while (d.held > d.limit || d.by_age.front().freed_at + kIdleReturns < d.returns) drop(d, d.by_age.begin());
 }
 
 }  // namespace gcn

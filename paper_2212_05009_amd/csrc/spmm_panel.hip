@@ -509,10 +509,10 @@ int device_cus() {
   return cus;
 }
 
-void free_plan(PanelPlan* p) {
+void free_plan(PanelPlan* p, bool idle = true) {
   if (!p) return;
   void* ptrs[] = {p->ent, p->wb, p->nfull, p->cbend, p->obase, p->panel_row0, p->row_v, p->vlds, p->order, p->ctr};
-  for (void* q : ptrs) pool_free(q);
+  for (void* q : ptrs) pool_free(q, idle);
   delete p;
 }
 
@@ -721,8 +721,8 @@ int build_plan(gcn_csr* A, bool transposed, int ns, int sw, int lpg, int cb_shif
   }
 }
 
-void free_panel_plans(gcn_csr* A) {
-  for (PanelPlan* p : A->plans) free_plan(p);
+void free_panel_plans(gcn_csr* A, bool idle) {
+  for (PanelPlan* p : A->plans) free_plan(p, idle);
   A->plans.clear();
 }
 
