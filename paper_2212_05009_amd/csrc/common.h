@@ -41,6 +41,7 @@ struct Tuning {
   int spmm_slices = 0;          // feature slices of the row kernel (0: by rule)
   int spmm_epg = 0;             // entries per lane group before a row is shared by more groups (0: default)
   int spmm_short = -1;          // short-row form of the row kernel: -1 by rule, 0 never, 1 always
+  int partition_sort = 0;       // partition figures by sorting even where columns can be counted
   int spmm_wide = 0;            // 64-bit gather addresses even where 32 bits suffice
   int gemm_direct = 1, gemm_fast = 1, gemm_tn_wide = 1, gemm_bf16 = 1, gemm_regw = 1;   // 0 switches a dense kernel family off
   int gemm_tn_lds = 1;          // A^T B with both operands streamed through LDS: 0 off, 1 for wide fp32 outputs, 2 wherever it fits

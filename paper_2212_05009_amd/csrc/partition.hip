@@ -5,10 +5,13 @@
 // in the net's connectivity set, so the rows moved per sparse product are sum_j (lambda(n_j) - 1).
 // Sec. 5 reports, per processor, the volume and the number of messages sent.
 //
-// One key per stored entry (i, j) whose ends lie in different parts:
-//     key = (part[j] * p + part[i]) << jbits | j          (sender, receiver, row)
-// Equal keys are the same transfer needed by several rows of the receiver: after a sort, the
-// distinct keys are the transfers, and the runs of equal (sender, receiver) are the messages.
+// Two ways of counting, the same integers:
+//   by columns  (handles with column-major arrays, p <= kPsMaxParts) every column's connectivity set is a bitmap of p
+//               bits in LDS; one pass over the stored entries, no sort.
+//   by sorting  one key per stored entry (i, j) whose ends lie in different parts:
+//                   key = (part[j] * p + part[i]) << jbits | j          (sender, receiver, row)
+//               Equal keys are the same transfer needed by several rows of the receiver: after a sort, the
+//               distinct keys are the transfers, and the runs of equal (sender, receiver) are the messages.
 #include <algorithm>
 
 #include "common.h"
@@ -18,9 +21,17 @@ namespace gcn {
 constexpr int kPsThreads = 256;
 static inline dim3 ps_grid(int64_t n) { return fold_grid(ceil_div(n > 0 ? n : 1, kPsThreads)); }
 
-__global__ void k_ps_zero(int64_t* __restrict__ a, int64_t n) {
-  int64_t i = block_id() * blockDim.x + threadIdx.x;
-  if (i < n) a[i] = 0;
+struct PsOut { int64_t *load, *send_rows, *recv_rows, *send_msgs, *recv_msgs, *totals; };
+
+__global__ void k_ps_zero(PsOut o, int p) {
+  const int64_t i = block_id() * blockDim.x + threadIdx.x;
+  if (i < p) o.load[i] = o.send_rows[i] = o.recv_rows[i] = o.send_msgs[i] = o.recv_msgs[i] = 0;
+  if (i < 2) o.totals[i] = 0;
+}
+
+__global__ void k_ps_zero_words(uint32_t* __restrict__ a, int64_t n) {
+  const int64_t i = block_id() * blockDim.x + threadIdx.x;
+  if (i < n) a[i] = 0u;
 }
 
 __global__ void k_ps_check(const int32_t* __restrict__ part, int64_t n, int p, int* __restrict__ bad) {
@@ -90,6 +101,185 @@ __global__ void k_ps_pairs(const uint64_t* __restrict__ keys, const int64_t* __r
   }
 }
 
+// ---- counting by columns -------------------------------------------------------------------------------------------
+// What bounds it is the two gathers per entry (the part of the row's vertex, and the word of the pair table), served by
+// L2, and the LDS atomics; the sort it replaces moved every entry's 8-byte key through memory ten times and more.
+// Lanes per column: a wavefront holds four columns at once, each lane four entries in flight, because most columns are
+// shorter than a wavefront (5 to 50 entries) and a column costs a chain of three dependent loads whatever its length.
+// Columns come in the order of the schedule, so that the four of a wavefront are of like length.
+constexpr int kPsLanes = 16;
+constexpr int kPsGroups = kPsThreads / kPsLanes;
+// The counters of a workgroup (entries, rows sent and rows received of every part) and its 16 bitmaps have to fit 64 KB
+// of LDS: 3 p words + p / 2 words.
+constexpr int kPsMaxParts = 4096;
+static size_t ps_lds_bytes(int p) { return sizeof(uint32_t) * ((size_t)3 * p + 2 + (size_t)kPsGroups * ceil_div(p, 32)); }
+
+// Connectivity sets of the long columns, which the schedule cuts into chunks of kHubChunkNnz entries: one workgroup per
+// chunk; a chunk's bitmap is OR-ed into its column's.
+__global__ __launch_bounds__(kPsThreads) void k_ps_hubs(const int64_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
+                                                        const int32_t* __restrict__ hub_cols, const int64_t* __restrict__ hub_chunk_ptr,
+                                                        const int32_t* __restrict__ chunk_hub, int64_t n_chunks,
+                                                        const int32_t* __restrict__ part, int pw, uint32_t* __restrict__ hub_bits,
+                                                        int64_t* __restrict__ totals) {
+  __shared__ uint32_t bm[kPsMaxParts / 32];
+  __shared__ uint32_t cut;
+  const int64_t c = block_id();
+  if (c >= n_chunks) return;
+  const int32_t h = chunk_hub[c];
+  const int64_t j = hub_cols[h];
+  for (int w = threadIdx.x; w < pw; w += kPsThreads) bm[w] = 0u;
+  if (threadIdx.x == 0) cut = 0u;
+  __syncthreads();
+  const int ps = part[j];
+  const int64_t s = colptr[j] + (c - hub_chunk_ptr[h]) * kHubChunkNnz, end = colptr[j + 1];
+  uint32_t cross = 0;
+#pragma unroll
+  for (int u = 0; u < kHubChunkNnz / kPsThreads; ++u) {
+    const int64_t e = s + u * kPsThreads + threadIdx.x;
+    if (e >= end) continue;
+    const int q = part[rowidx[e]];
+    if (q == ps) continue;
+    ++cross;
+    atomicOr(&bm[q >> 5], 1u << (q & 31));
+  }
+  if (cross) atomicAdd(&cut, cross);
+  __syncthreads();
+  for (int w = threadIdx.x; w < pw; w += kPsThreads)
+    if (bm[w]) atomicOr(&hub_bits[(int64_t)h * pw + w], bm[w]);
+  if (threadIdx.x == 0 && cut) atomicAdd(reinterpret_cast<unsigned long long*>(totals + 1), (unsigned long long)cut);
+}
+
+// partial[block] = { entries[p], rows sent[p], rows received[p], cut entries, rows moved } of the columns it took: 32
+// bits each, since a block has seen fewer than 2^32 entries.
+__global__ __launch_bounds__(kPsThreads) void k_ps_columns(const int64_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
+                                                           const int64_t* __restrict__ rowptr, const int32_t* __restrict__ cols,
+                                                           int64_t n_cols, const int32_t* __restrict__ hub_cols, int64_t n_hub,
+                                                           const uint32_t* __restrict__ hub_bits, const int32_t* __restrict__ part,
+                                                           int p, int pw, uint32_t* pair, uint32_t* __restrict__ partial) {
+  extern __shared__ uint32_t ps_lds[];
+  uint32_t* load = ps_lds;
+  uint32_t* send = ps_lds + p;
+  uint32_t* recv = ps_lds + 2 * p;
+  uint32_t* sums = ps_lds + 3 * p;                   // cut entries, rows moved
+  const int g = threadIdx.x / kPsLanes, l = threadIdx.x % kPsLanes;
+  uint32_t* bm = ps_lds + 3 * p + 2 + g * pw;
+  const int words = 3 * p + 2;
+  for (int i = threadIdx.x; i < words + kPsGroups * pw; i += kPsThreads) ps_lds[i] = 0u;
+  __syncthreads();
+
+  uint32_t cross = 0, moved = 0;
+  // part `ps` sends one more row to part q
+  auto transfer = [&](int ps, int q) {
+    atomicAdd(&recv[q], 1u);
+    uint32_t* word = pair + (int64_t)ps * pw + (q >> 5);
+    const uint32_t bit = 1u << (q & 31);
+    if (!(*word & bit)) atomicOr(word, bit);         // (an old value costs one more atomic, no more)
+  };
+  const int64_t stride = (int64_t)gridDim.x * kPsGroups;
+  const int64_t first = (int64_t)blockIdx.x * kPsGroups + g;
+  for (int64_t it = first; it < n_cols; it += stride) {
+    const int64_t j = cols[it];
+    const int ps = part[j];
+    const int64_t s = colptr[j];
+    const int n = (int)(colptr[j + 1] - s);          // at most kHubRowNnz
+    uint32_t fresh = 0;
+    for (int base = 0; base < n; base += 4 * kPsLanes) {
+      int q[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = base + u * kPsLanes + l;
+        q[u] = k < n ? rowidx[s + k] : (int)j;       // (a vertex of the column's own part counts for nothing)
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) q[u] = part[q[u]];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (q[u] == ps) continue;
+        ++cross;
+        const uint32_t bit = 1u << (q[u] & 31);
+        if (!(atomicOr(&bm[q[u] >> 5], bit) & bit)) { ++fresh; transfer(ps, q[u]); }
+      }
+    }
+    if (fresh) { atomicAdd(&send[ps], fresh); moved += fresh; }
+    if (l == 0) atomicAdd(&load[ps], (uint32_t)(rowptr[j + 1] - rowptr[j]));
+    // the lanes of a column are lanes of one wavefront, whose LDS operations are carried out in order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int w = l; w < pw; w += kPsLanes) bm[w] = 0u;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  for (int64_t h = first; h < n_hub; h += stride) {
+    const int64_t j = hub_cols[h];
+    const int ps = part[j];
+    uint32_t fresh = 0;
+    for (int w = l; w < pw; w += kPsLanes) {
+      uint32_t bits = hub_bits[h * pw + w];
+      fresh += (uint32_t)__popc(bits);
+      for (; bits; bits &= bits - 1) transfer(ps, w * 32 + __ffs(bits) - 1);
+    }
+    if (fresh) { atomicAdd(&send[ps], fresh); moved += fresh; }
+    if (l == 0) atomicAdd(&load[ps], (uint32_t)(rowptr[j + 1] - rowptr[j]));
+  }
+  if (cross) atomicAdd(&sums[0], cross);
+  if (moved) atomicAdd(&sums[1], moved);
+  __syncthreads();
+  for (int i = threadIdx.x; i < words; i += kPsThreads) partial[(int64_t)blockIdx.x * words + i] = ps_lds[i];
+}
+
+constexpr int kPsSplit = 32;         // blocks in y that share a sum over workgroups or over the rows of the pair table
+
+__global__ void k_ps_sum(const uint32_t* __restrict__ partial, int64_t n_blocks, int p, PsOut o) {
+  const int words = 3 * p + 2;
+  const int c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (c >= words) return;
+  unsigned long long v = 0;
+  for (int64_t b = blockIdx.y; b < n_blocks; b += kPsSplit) v += partial[b * words + c];
+  int64_t* to = c < p ? o.load + c : c < 2 * p ? o.send_rows + (c - p) : c < 3 * p ? o.recv_rows + (c - 2 * p) : o.totals + (c == 3 * p ? 1 : 0);
+  if (v) atomicAdd(reinterpret_cast<unsigned long long*>(to), v);
+}
+
+// bit (s, r) of the pair table: s sends to r
+__global__ void k_ps_messages(const uint32_t* __restrict__ pair, int p, int pw, PsOut o) {
+  const int r = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  unsigned long long got = 0;
+  for (int s = (int)blockIdx.y; s < p; s += kPsSplit) {
+    const bool bit = r < p && ((pair[(int64_t)s * pw + (r >> 5)] >> (r & 31)) & 1u);
+    got += bit ? 1u : 0u;
+    const unsigned long long sent = (unsigned long long)__popcll(__ballot(bit));
+    if ((threadIdx.x & 63) == 0 && sent) atomicAdd(reinterpret_cast<unsigned long long*>(o.send_msgs + s), sent);
+  }
+  if (got) atomicAdd(reinterpret_cast<unsigned long long*>(o.recv_msgs + r), got);
+}
+
+static int count_by_columns(const gcn_csr_t* A, const int32_t* d_part, int p, const PsOut& o, CallScope& sc) {
+  hipStream_t s = sc.s;
+  const Schedule& t = A->sched_t;
+  const int pw = (int)ceil_div(p, 32);
+  const size_t lds = ps_lds_bytes(p);
+  // as many workgroups as the chip holds at once (256 compute units of 160 KB of LDS and 8 such workgroups)
+  const int64_t per_cu = std::min<int64_t>(8, (int64_t)((size_t)160 * 1024 / lds));
+  const int64_t blocks = std::min<int64_t>(256 * per_cu, std::max<int64_t>(1, ceil_div(std::max(t.n_wave_rows, t.n_hub_rows), kPsGroups)));
+  const int64_t pair_words = (int64_t)p * pw, hub_words = t.n_hub_rows * pw;
+  DevBuf bits, partial;
+  GCN_TRY(bits.alloc(sc, sizeof(uint32_t) * (size_t)(pair_words + hub_words)));
+  GCN_TRY(partial.alloc(sc, sizeof(uint32_t) * (size_t)blocks * (size_t)(3 * (int64_t)p + 2)));
+  uint32_t* pair = bits.as<uint32_t>();
+  uint32_t* hub_bits = pair + pair_words;
+  k_ps_zero_words<<<ps_grid(pair_words + hub_words), kPsThreads, 0, s>>>(pair, pair_words + hub_words);
+  if (t.n_chunks > 0)
+    k_ps_hubs<<<fold_grid(t.n_chunks), kPsThreads, 0, s>>>(A->colptr, A->rowidx, t.hub_rows, t.hub_chunk_ptr, t.chunk_hub, t.n_chunks,
+                                                          d_part, pw, hub_bits, o.totals);
+  k_ps_columns<<<(unsigned)blocks, kPsThreads, lds, s>>>(A->colptr, A->rowidx, A->rowptr, t.wave_rows, t.n_wave_rows, t.hub_rows,
+                                                        t.n_hub_rows, hub_bits, d_part, p, pw, pair, partial.as<uint32_t>());
+  k_ps_sum<<<dim3((unsigned)ceil_div(3 * (int64_t)p + 2, kPsThreads), kPsSplit), kPsThreads, 0, s>>>(partial.as<uint32_t>(), blocks, p, o);
+  k_ps_messages<<<dim3((unsigned)ceil_div(p, kPsThreads), kPsSplit), kPsThreads, 0, s>>>(pair, p, pw, o);
+  GCN_CHECK_LAUNCH();
+  GCN_HIP(hipStreamSynchronize(s));      // the temporaries go back on return
+  sc.done = true;
+  return GCN_OK;
+}
+
 }  // namespace gcn
 
 using namespace gcn;
@@ -116,8 +306,8 @@ extern "C" int gcn_partition_stats(const gcn_csr_t* A, const int32_t* d_part, in
   int64_t* send_msgs = d_send_msgs ? d_send_msgs : sp + 3 * (int64_t)p;
   int64_t* recv_msgs = d_recv_msgs ? d_recv_msgs : sp + 4 * (int64_t)p;
   int64_t* totals = d_totals ? d_totals : sp + 5 * (int64_t)p;
-  for (int64_t* a : {load, send_rows, recv_rows, send_msgs, recv_msgs}) k_ps_zero<<<ps_grid(p), kPsThreads, 0, s>>>(a, p);
-  k_ps_zero<<<1, kPsThreads, 0, s>>>(totals, 2);
+  const PsOut o{load, send_rows, recv_rows, send_msgs, recv_msgs, totals};
+  k_ps_zero<<<ps_grid(p), kPsThreads, 0, s>>>(o, p);
   GCN_CHECK_LAUNCH();
 
   DevBuf bad;
@@ -129,6 +319,8 @@ extern "C" int gcn_partition_stats(const gcn_csr_t* A, const int32_t* d_part, in
   GCN_HIP(hipMemcpyAsync(&h_bad, bad.p, sizeof(int), hipMemcpyDeviceToHost, s));
   GCN_HIP(hipStreamSynchronize(s));
   if (h_bad) return fail(GCN_EINVAL, "gcn_partition_stats: a part id lies outside [0, p)");
+
+  if (A->colptr && p <= kPsMaxParts && !tune().partition_sort) return count_by_columns(A, d_part, p, o, sc);
 
   k_ps_load<<<ps_grid(n), kPsThreads, 0, s>>>(A->rowptr, d_part, n, load);
   GCN_CHECK_LAUNCH();

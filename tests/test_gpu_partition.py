@@ -121,3 +121,31 @@ def test_argument_errors(gcn, dev):
     B = gcn.gcn_csr_build(src, dst, n, 10, 60, deg_global=whole_deg)
     with pytest.raises(gcn.GcnError):
         gcn.gcn_partition_stats(B, torch.zeros(50, dtype=torch.int32, device=dev), 2)
+
+
+@pytest.mark.parametrize("p", [1, 2, 31, 32, 33, 64, 511, 1025, 4096, 4097])
+@pytest.mark.parametrize("directed", [False, True])
+def test_counting_by_columns_equals_sorting(gcn, dev, p, directed):
+    """Columns of 1 to 9000 entries (chunks of long columns included), part counts at the edges of a bitmap word and of
+    the form itself; against the oracle, against the sort, and against a handle without column-major arrays."""
+    import torch
+    from util import hub_graph
+    rng = np.random.default_rng(p)
+    n = 9001
+    src, dst = hub_graph(n, 3, 9.0, seed=11)
+    if directed:
+        keep = rng.random(src.size) < 0.7
+        src, dst = src[keep], dst[keep]
+    part = rng.integers(0, p, n)
+    og, A, want = both(gcn, dev, src, dst, n, part, p)
+    assert np.diff(og.colptr).max() > 2048
+    part_d = torch.from_numpy(part.astype(np.int32)).to(dev)
+    gcn.gcn_debug_set_tuning("GCN_PARTITION_SORT", 1)
+    try:
+        by_sort = gcn.gcn_partition_stats(A, part_d, p)
+    finally:
+        gcn.gcn_debug_set_tuning("GCN_PARTITION_SORT", None)
+    rows_only = gcn.gcn_csr_build(torch.from_numpy(src.astype(np.int32)).to(dev), torch.from_numpy(dst.astype(np.int32)).to(dev), n, flags=0)
+    for other in (gcn.gcn_partition_stats(A, part_d, p), gcn.gcn_partition_stats(rows_only, part_d, p)):
+        for k in by_sort:
+            assert torch.equal(by_sort[k], other[k]), k
