@@ -83,40 +83,87 @@ __global__ void k_make_keys(const int32_t* __restrict__ src, const int32_t* __re
 }
 
 // ---- step 4: duplicate removal ------------------------------------------------------------------
-__global__ void k_flag_unique(const uint64_t* __restrict__ keys, int64_t m, uint32_t* __restrict__ flag) {
-  int64_t k = block_id() * blockDim.x + threadIdx.x;
-  if (k >= m) return;
-  uint64_t v = keys[k];
-  flag[k] = (v != kInvalidKey && (k == 0 || keys[k - 1] != v)) ? 1u : 0u;
+// Two passes over the sorted keys with a scan of the blocks' counts between them: flags and positions of every candidate
+// in memory cost 28 bytes a key where this reads 16 (keys twice).
+constexpr int kUniqItems = 16;
+constexpr int kUniqTile = kThreads * kUniqItems;
+static_assert(kThreads / 64 * kUniqItems == 64, "k_compact scans the counts of a block's (round, wavefront) pairs in one wavefront");
+
+__device__ __forceinline__ bool first_of_equal(const uint64_t* __restrict__ keys, int64_t k, int64_t m, uint64_t* v) {
+  if (k >= m) return false;
+  *v = keys[k];
+  return *v != kInvalidKey && (k == 0 || keys[k - 1] != *v);
 }
 
-__global__ void k_compact(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ flag,
-                          const int64_t* __restrict__ pos, int64_t m, int colbits,
-                          uint64_t* __restrict__ ukeys, int32_t* __restrict__ col) {
-  int64_t k = block_id() * blockDim.x + threadIdx.x;
-  if (k >= m || !flag[k]) return;
-  uint64_t v = keys[k];
-  int64_t p = pos[k];
-  ukeys[p] = v;
-  col[p] = (int32_t)(v & ((1ull << colbits) - 1ull));
+__global__ __launch_bounds__(kThreads) void k_count_unique(const uint64_t* __restrict__ keys, int64_t m, int64_t nb,
+                                                           uint32_t* __restrict__ cnt) {
+  const int64_t blk = block_id();
+  if (blk >= nb) return;
+  __shared__ uint32_t wave_cnt[kThreads / 64];
+  uint32_t c = 0;
+#pragma unroll
+  for (int i = 0; i < kUniqItems; ++i) {
+    uint64_t v = 0;
+    c += (uint32_t)__popcll(__ballot(first_of_equal(keys, blk * kUniqTile + i * kThreads + threadIdx.x, m, &v)));
+  }
+  if ((threadIdx.x & 63) == 0) wave_cnt[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t tot = 0;
+    for (int i = 0; i < kThreads / 64; ++i) tot += wave_cnt[i];
+    cnt[blk] = tot;
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void k_compact(const uint64_t* __restrict__ keys, const int64_t* __restrict__ off,
+                                                      int64_t m, int64_t nb, int colbits, uint64_t* __restrict__ ukeys,
+                                                      int32_t* __restrict__ col) {
+  const int64_t blk = block_id();
+  if (blk >= nb) return;
+  __shared__ uint32_t part[64];            // keys kept by round i, wavefront w at [i * waves + w]; then those before it
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  uint64_t v[kUniqItems];
+  uint64_t kept[kUniqItems];
+#pragma unroll
+  for (int i = 0; i < kUniqItems; ++i) {
+    v[i] = 0;
+    kept[i] = __ballot(first_of_equal(keys, blk * kUniqTile + i * kThreads + threadIdx.x, m, &v[i]));
+    if (lane == 0) part[i * (kThreads / 64) + w] = (uint32_t)__popcll(kept[i]);
+  }
+  __syncthreads();
+  if (w == 0) {
+    const uint32_t mine = part[lane];
+    uint32_t inc = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t x = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += x;
+    }
+    part[lane] = inc - mine;
+  }
+  __syncthreads();
+  const int64_t base = off[blk];
+  const uint64_t lt = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int i = 0; i < kUniqItems; ++i) {
+    if (!((kept[i] >> lane) & 1ull)) continue;
+    const int64_t p = base + part[i * (kThreads / 64) + w] + __popcll(kept[i] & lt);
+    ukeys[p] = v[i];
+    col[p] = (int32_t)(v[i] & ((1ull << colbits) - 1ull));
+  }
 }
 
 // ptr[q] = first position whose segment id is >= q, for q in [0, n_seg]; seg ids are the bits
-// of key[k] from `shift` upwards and are non-decreasing in k.  Requires n >= 1.
-__global__ void k_boundaries(const uint64_t* __restrict__ key, int64_t n, int shift, int64_t n_seg,
+// of key[k] from `shift` upwards that are set in `mask` and are non-decreasing in k.  Requires n >= 1.
+__global__ void k_boundaries(const uint64_t* __restrict__ key, int64_t n, int shift, uint64_t mask, int64_t n_seg,
                              int64_t* __restrict__ ptr) {
   int64_t k = block_id() * blockDim.x + threadIdx.x;
   if (k >= n) return;
-  int64_t s = (int64_t)(key[k] >> shift);
-  int64_t sp = k == 0 ? -1 : (int64_t)(key[k - 1] >> shift);
+  int64_t s = (int64_t)((key[k] >> shift) & mask);
+  int64_t sp = k == 0 ? -1 : (int64_t)((key[k - 1] >> shift) & mask);
   for (int64_t q = sp + 1; q <= s; ++q) ptr[q] = k;
   if (k == n - 1)
     for (int64_t q = s + 1; q <= n_seg; ++q) ptr[q] = n;
-}
-
-__global__ void k_row_lengths(const int64_t* __restrict__ ptr, int64_t n, int32_t* __restrict__ len) {
-  int64_t i = block_id() * blockDim.x + threadIdx.x;
-  if (i < n) len[i] = (int32_t)(ptr[i + 1] - ptr[i]);
 }
 
 // first entry of each row whose (local) column is >= nr: columns are ascending, so the owned columns come first
@@ -141,41 +188,37 @@ __device__ __forceinline__ float inv_sqrt_deg(int32_t d) {
   return (float)(1.0 / (double)r);
 }
 
-__global__ void k_values(const uint64_t* __restrict__ ukeys, int64_t nnz, int colbits, int64_t nr,
-                         int64_t row_lo, const int32_t* __restrict__ deg_local,
-                         const int32_t* __restrict__ deg_global, const int32_t* __restrict__ halo_gid,
+// Degrees of the owned rows and fl(1/sqrt(d)) of every local column.  An owned vertex's degree is the entry count of its
+// row, which the block holds whole (Sec. 4.1); a halo vertex's row lives elsewhere: its degree comes from the caller's
+// global array.
+__global__ void k_degrees(const int64_t* __restrict__ ptr, int64_t nr, int64_t nc, const int32_t* __restrict__ deg_global,
+                          const int32_t* __restrict__ halo_gid, int32_t* __restrict__ deg, float* __restrict__ dinv) {
+  int64_t c = block_id() * blockDim.x + threadIdx.x;
+  if (c >= nc) return;
+  int32_t d;
+  if (c < nr) deg[c] = d = (int32_t)(ptr[c + 1] - ptr[c]);
+  else d = deg_global[halo_gid[c - nr]];
+  dinv[c] = inv_sqrt_deg(d);
+}
+
+__global__ void k_values(const uint64_t* __restrict__ ukeys, int64_t nnz, int colbits, const float* __restrict__ dinv,
                          float* __restrict__ val) {
   int64_t p = block_id() * blockDim.x + threadIdx.x;
   if (p >= nnz) return;
-  uint64_t v = ukeys[p];
-  int64_t i = (int64_t)(v >> colbits);
-  int64_t c = (int64_t)(v & ((1ull << colbits) - 1ull));
-  // an owned vertex's degree is the entry count of its row, which the block holds whole (Sec. 4.1); a halo
-  // vertex's row lives elsewhere: its degree comes from the caller's global array
-  (void)row_lo;
-  const int32_t di = deg_local[i];
-  const int32_t dj = c < nr ? deg_local[c] : deg_global[halo_gid[c - nr]];
-  val[p] = __fmul_rn(inv_sqrt_deg(di), inv_sqrt_deg(dj));
+  const uint64_t v = ukeys[p];
+  val[p] = __fmul_rn(dinv[v >> colbits], dinv[v & ((1ull << colbits) - 1ull)]);
 }
 
 // ---- step 6: column-major copy ------------------------------------------------------------------------
-__global__ void k_make_tkeys(const uint64_t* __restrict__ ukeys, int64_t nnz, int colbits,
-                             uint64_t* __restrict__ tkeys, uint32_t* __restrict__ pay) {
-  int64_t p = block_id() * blockDim.x + threadIdx.x;
-  if (p >= nnz) return;
-  uint64_t v = ukeys[p];
-  uint64_t i = v >> colbits, c = v & ((1ull << colbits) - 1ull);
-  tkeys[p] = (c << 32) | i;
-  pay[p] = (uint32_t)p;
-}
-
-__global__ void k_finish_csc(const uint64_t* __restrict__ tkeys, const uint32_t* __restrict__ pay,
-                             const float* __restrict__ val, int64_t nnz, int32_t* __restrict__ rowidx,
-                             float* __restrict__ val_t) {
+// The entries sorted by column, those of a column still in row order; a value is computed again, from the same two
+// factors, instead of being carried through the sort or fetched from its row-major place (124 us for 11.8 M entries).
+__global__ void k_finish_csc(const uint64_t* __restrict__ tkeys, int64_t nnz, int colbits, const float* __restrict__ dinv,
+                             int32_t* __restrict__ rowidx, float* __restrict__ val_t) {
   int64_t q = block_id() * blockDim.x + threadIdx.x;
   if (q >= nnz) return;
-  rowidx[q] = (int32_t)(tkeys[q] & 0xffffffffull);
-  val_t[q] = val[pay[q]];
+  const uint64_t v = tkeys[q];
+  rowidx[q] = (int32_t)(v >> colbits);
+  val_t[q] = __fmul_rn(dinv[v >> colbits], dinv[v & ((1ull << colbits) - 1ull)]);
 }
 
 // ---- schedules ------------------------------------------------------------------------------------------
@@ -278,7 +321,7 @@ int build_schedule(const int64_t* ptr, int64_t n, hipStream_t s, Schedule* out) 
   GCN_HIP(hipMemsetAsync(class_begin.p, 0, sizeof(int64_t) * 34, s));
   if (n_wave > 0) {
     k_take_low32<<<grid_for(n_wave), kThreads, 0, s>>>(sorted, n_wave, wave_rows.as<int32_t>());
-    k_boundaries<<<grid_for(n_wave), kThreads, 0, s>>>(sorted, n_wave, 32, 33, class_begin.as<int64_t>());
+    k_boundaries<<<grid_for(n_wave), kThreads, 0, s>>>(sorted, n_wave, 32, ~0ull, 33, class_begin.as<int64_t>());
   }
   GCN_HIP(hipMemcpyAsync(out->class_begin, class_begin.p, sizeof(int64_t) * 34, hipMemcpyDeviceToHost, s));
   GCN_HIP(hipMemsetAsync(hub_chunk_ptr.p, 0, sizeof(int64_t) * (size_t)(n_hub + 1), s));
@@ -377,7 +420,7 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   const int colbits = bits_for(nc);
   const int rowbits = bits_for(nr);
   if (colbits + rowbits > 62) return fail(GCN_EINVAL, "gcn_csr_build: block too large for 64-bit sort keys");
-  DevBuf keys_a, keys_b, flag, pos;
+  DevBuf keys_a, keys_b, cnt, off;
   GCN_TRY(keys_a.alloc(sc, sizeof(uint64_t) * (size_t)m));
   GCN_TRY(keys_b.alloc(sc, sizeof(uint64_t) * (size_t)m));
   k_make_keys<<<grid_for(m), kThreads, 0, s>>>(d_src, d_dst, n_edges, row_lo, row_hi, nr, colbits,
@@ -387,29 +430,30 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   GCN_TRY(radix_sort_u64(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nullptr, nullptr, m, 0, colbits + rowbits,
                          tmp.p, s, &sorted, nullptr));
   uint64_t* other = (sorted == keys_a.as<uint64_t>()) ? keys_b.as<uint64_t>() : keys_a.as<uint64_t>();
-  GCN_TRY(flag.alloc(sc, sizeof(uint32_t) * (size_t)m));
-  GCN_TRY(pos.alloc(sc, sizeof(int64_t) * (size_t)(m + 1)));
-  k_flag_unique<<<grid_for(m), kThreads, 0, s>>>(sorted, m, flag.as<uint32_t>());
+  const int64_t nb = ceil_div(m, kUniqTile);
+  GCN_TRY(cnt.alloc(sc, sizeof(uint32_t) * (size_t)nb));
+  GCN_TRY(off.alloc(sc, sizeof(int64_t) * (size_t)(nb + 1)));
+  k_count_unique<<<fold_grid(nb), kThreads, 0, s>>>(sorted, m, nb, cnt.as<uint32_t>());
   GCN_CHECK_LAUNCH();
-  GCN_TRY(exclusive_scan_u32(flag.as<uint32_t>(), pos.as<int64_t>(), m, tmp.p, s));
+  GCN_TRY(exclusive_scan_u32(cnt.as<uint32_t>(), off.as<int64_t>(), nb, tmp.p, s));
   int64_t nnz = 0;
-  GCN_HIP(hipMemcpyAsync(&nnz, pos.as<int64_t>() + m, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  GCN_HIP(hipMemcpyAsync(&nnz, off.as<int64_t>() + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s));
   GCN_HIP(hipStreamSynchronize(s));
   if (nnz < nr) return fail(GCN_EHIP, "gcn_csr_build: internal error (nnz %lld < rows %lld)", (long long)nnz, (long long)nr);
   if (nnz >= 0xffffffffLL) return fail(GCN_EINVAL, "gcn_csr_build: more than 2^32-2 stored entries in one block");
 
-  DevBuf rowptr, col, val, deg;
+  DevBuf rowptr, col, val, deg, dinv;
   GCN_TRY(rowptr.alloc(sc, sizeof(int64_t) * (size_t)(nr + 1)));
   GCN_TRY(col.alloc(sc, sizeof(int32_t) * (size_t)nnz + kEntrySlack));
   GCN_TRY(val.alloc(sc, sizeof(float) * (size_t)nnz + kEntrySlack));
   GCN_TRY(deg.alloc(sc, sizeof(int32_t) * (size_t)nr));
   uint64_t* ukeys = other;                  // unique keys, row-major order
-  k_compact<<<grid_for(m), kThreads, 0, s>>>(sorted, flag.as<uint32_t>(), pos.as<int64_t>(), m, colbits, ukeys, col.as<int32_t>());
-  k_boundaries<<<grid_for(nnz), kThreads, 0, s>>>(ukeys, nnz, colbits, nr, rowptr.as<int64_t>());
-  k_row_lengths<<<grid_for(nr), kThreads, 0, s>>>(rowptr.as<int64_t>(), nr, deg.as<int32_t>());
-  k_values<<<grid_for(nnz), kThreads, 0, s>>>(ukeys, nnz, colbits, nr, row_lo, deg.as<int32_t>(),
-                                               whole && !d_deg_global ? nullptr : d_deg_global,
-                                               halo_gid.as<int32_t>(), val.as<float>());
+  GCN_TRY(dinv.alloc(sc, sizeof(float) * (size_t)nc));
+  k_compact<<<fold_grid(nb), kThreads, 0, s>>>(sorted, off.as<int64_t>(), m, nb, colbits, ukeys, col.as<int32_t>());
+  k_boundaries<<<grid_for(nnz), kThreads, 0, s>>>(ukeys, nnz, colbits, ~0ull, nr, rowptr.as<int64_t>());
+  k_degrees<<<grid_for(nc), kThreads, 0, s>>>(rowptr.as<int64_t>(), nr, nc, d_deg_global, halo_gid.as<int32_t>(), deg.as<int32_t>(),
+                                               dinv.as<float>());
+  k_values<<<grid_for(nnz), kThreads, 0, s>>>(ukeys, nnz, colbits, dinv.as<float>(), val.as<float>());
   GCN_CHECK_LAUNCH();
 
   DevBuf mid;
@@ -420,23 +464,15 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   }
 
   // -- column-major copy
-  DevBuf colptr, rowidx, val_t, pay_a, pay_b, tk_b;
+  DevBuf colptr, rowidx, val_t;
   if (flags & GCN_BUILD_CSC) {
-    GCN_TRY(pay_a.alloc(sc, sizeof(uint32_t) * (size_t)nnz));
-    GCN_TRY(pay_b.alloc(sc, sizeof(uint32_t) * (size_t)nnz));
     GCN_TRY(colptr.alloc(sc, sizeof(int64_t) * (size_t)(nc + 1)));
     GCN_TRY(rowidx.alloc(sc, sizeof(int32_t) * (size_t)nnz + kEntrySlack));
     GCN_TRY(val_t.alloc(sc, sizeof(float) * (size_t)nnz + kEntrySlack));
-    uint64_t* tk_a = sorted;               // the sorted-with-duplicates buffer is free again
-    k_make_tkeys<<<grid_for(nnz), kThreads, 0, s>>>(ukeys, nnz, colbits, tk_a, pay_a.as<uint32_t>());
-    GCN_CHECK_LAUNCH();
-    // ukeys lives in `other`; the sort ping-pongs between tk_a and a third buffer
-    GCN_TRY(tk_b.alloc(sc, sizeof(uint64_t) * (size_t)nnz));
-    uint64_t* tsorted = nullptr; uint32_t* psorted = nullptr;
-    GCN_TRY(radix_sort_u64(tk_a, tk_b.as<uint64_t>(), pay_a.as<uint32_t>(), pay_b.as<uint32_t>(), nnz, 32,
-                           32 + colbits, tmp.p, s, &tsorted, &psorted));
-    k_boundaries<<<grid_for(nnz), kThreads, 0, s>>>(tsorted, nnz, 32, nc, colptr.as<int64_t>());
-    k_finish_csc<<<grid_for(nnz), kThreads, 0, s>>>(tsorted, psorted, val.as<float>(), nnz, rowidx.as<int32_t>(), val_t.as<float>());
+    uint64_t* tsorted = nullptr;           // (the buffer of the keys with duplicates is free again)
+    GCN_TRY(radix_sort_u64(ukeys, sorted, nullptr, nullptr, nnz, 0, colbits, tmp.p, s, &tsorted, nullptr));
+    k_boundaries<<<grid_for(nnz), kThreads, 0, s>>>(tsorted, nnz, 0, (1ull << colbits) - 1ull, nc, colptr.as<int64_t>());
+    k_finish_csc<<<grid_for(nnz), kThreads, 0, s>>>(tsorted, nnz, colbits, dinv.as<float>(), rowidx.as<int32_t>(), val_t.as<float>());
     GCN_CHECK_LAUNCH();
   }
   GCN_HIP(hipStreamSynchronize(s));
@@ -457,7 +493,7 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
 
 int segment_boundaries(const uint64_t* keys, int64_t n, int shift, int64_t n_seg, int64_t* ptr, hipStream_t s) {
   if (n < 1) return fail(GCN_EINVAL, "segment_boundaries: empty input");
-  k_boundaries<<<grid_for(n), kThreads, 0, s>>>(keys, n, shift, n_seg, ptr);
+  k_boundaries<<<grid_for(n), kThreads, 0, s>>>(keys, n, shift, ~0ull, n_seg, ptr);
   GCN_CHECK_LAUNCH();
   return GCN_OK;
 }

@@ -108,56 +108,66 @@ int exclusive_scan_u32(const uint32_t* in, int64_t* out, int64_t n, void* tmp, h
 // ------------------------------------------------------------------------------------------
 // Stable LSD radix sort, 8 bits per pass.
 // Per pass: (1) per-block digit histogram, (2) exclusive scan of the digit-major histogram
-// table gives each (digit, block) its output offset, (3) every block ranks its keys stably
-// and scatters them.  Stability inside a block: a wavefront owns a contiguous run of keys and
-// walks it 64 keys at a time; keys with equal digits inside one step are ordered by lane
+// table gives each (digit, block) its output offset, (3) every block ranks its keys stably,
+// orders them in LDS and writes them out digit by digit.  Stability inside a block: a wavefront owns a contiguous run
+// of keys and walks it 64 keys at a time; keys with equal digits inside one step are ordered by lane
 // (ballot match + popcount of lower lanes), steps are ordered by a running per-wave counter,
 // waves are ordered by a prefix over the per-wave counters.
+// A pass is bound by its writes: without the LDS step a wavefront's 64 keys go to up to 64 places, 8 bytes each; with it
+// the 4096 keys of a block leave in runs of 16 on the average, 128 bytes.
 // ------------------------------------------------------------------------------------------
 constexpr int kSortThreads = 256;
-constexpr int kSortItems = 8;
-constexpr int kSortTile = kSortThreads * kSortItems;
-constexpr int kSortWaveRun = 64 * kSortItems;
+static_assert(kSortThreads == kScanThreads, "k_sort_scatter scans one value per digit with block_exclusive_scan");
+// Keys per thread: 16, or 8 where that would leave compute units without a block (fewer than two each).
+static inline int sort_items(int64_t n) { return n >= (int64_t)2 * 256 * kSortThreads * 16 ? 16 : 8; }
+static inline int64_t sort_blocks(int64_t n) { return ceil_div(n > 0 ? n : 1, (int64_t)kSortThreads * sort_items(n)); }
 
+template <int ITEMS>
 __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const uint64_t* __restrict__ keys,
-                                                            int64_t n, int shift, int64_t nblocks,
+                                                            int64_t n, int shift, uint32_t mask, int64_t nblocks,
                                                             uint32_t* __restrict__ hist) {
   __shared__ uint32_t h[256];
   h[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
+  const int64_t base = (int64_t)blockIdx.x * kSortThreads * ITEMS;
 #pragma unroll
-  for (int i = 0; i < kSortItems; ++i) {
+  for (int i = 0; i < ITEMS; ++i) {
     int64_t idx = base + (int64_t)i * kSortThreads + threadIdx.x;
-    if (idx < n) atomicAdd(&h[(uint32_t)(keys[idx] >> shift) & 255u], 1u);
+    if (idx < n) atomicAdd(&h[(uint32_t)(keys[idx] >> shift) & mask], 1u);
   }
   __syncthreads();
   hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
+template <int ITEMS, bool PAY>
 __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
     const uint64_t* __restrict__ keys_in, uint64_t* __restrict__ keys_out,
-    const uint32_t* __restrict__ pay_in, uint32_t* __restrict__ pay_out, int64_t n, int shift,
+    const uint32_t* __restrict__ pay_in, uint32_t* __restrict__ pay_out, int64_t n, int shift, uint32_t mask,
     int64_t nblocks, const int64_t* __restrict__ offsets) {
   __shared__ uint32_t wave_cnt[kSortThreads / 64][256];
-  __shared__ int64_t digit_base[256];
+  __shared__ int64_t digit_base[256];              // output position of the digit's first key, less its position in the block
+  __shared__ uint64_t stage[kSortThreads * ITEMS];
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
 #pragma unroll
   for (int i = 0; i < kSortThreads / 64; ++i) wave_cnt[i][t] = 0;
   __syncthreads();
 
-  const int64_t wave_base = (int64_t)blockIdx.x * kSortTile + (int64_t)w * kSortWaveRun;
+  const int64_t tile_base = (int64_t)blockIdx.x * kSortThreads * ITEMS;
+  const int64_t wave_base = tile_base + (int64_t)w * 64 * ITEMS;
   const uint64_t lt_mask = (1ull << lane) - 1ull;
-  uint64_t key[kSortItems];
-  uint32_t pay[kSortItems];
-  uint32_t rank[kSortItems];
+  uint64_t key[ITEMS];
+  uint32_t pay[ITEMS];
+  uint32_t rank[ITEMS];
 #pragma unroll
-  for (int it = 0; it < kSortItems; ++it) {
+  for (int it = 0; it < ITEMS; ++it) {
     const int64_t idx = wave_base + (int64_t)it * 64 + lane;
-    const bool valid = idx < n;
-    key[it] = valid ? keys_in[idx] : 0ull;
-    pay[it] = (valid && pay_in) ? pay_in[idx] : 0u;
-    const uint32_t dg = (uint32_t)(key[it] >> shift) & 255u;
+    key[it] = idx < n ? keys_in[idx] : 0ull;
+    if constexpr (PAY) pay[it] = idx < n ? pay_in[idx] : 0u;
+  }
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) {
+    const bool valid = wave_base + (int64_t)it * 64 + lane < n;
+    const uint32_t dg = (uint32_t)(key[it] >> shift) & mask;
     uint64_t peers = __ballot(valid);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
@@ -179,33 +189,66 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(
   {
     uint32_t run = 0;
 #pragma unroll
+    for (int i = 0; i < kSortThreads / 64; ++i) run += wave_cnt[i][t];
+    int64_t total;
+    const uint32_t first = (uint32_t)block_exclusive_scan((int64_t)run, &total);
+    digit_base[t] = offsets[(int64_t)t * nblocks + blockIdx.x] - (int64_t)first;
+    run = first;
+#pragma unroll
     for (int i = 0; i < kSortThreads / 64; ++i) {
       uint32_t c = wave_cnt[i][t];
       wave_cnt[i][t] = run;
       run += c;
     }
-    digit_base[t] = offsets[(int64_t)t * nblocks + blockIdx.x];
   }
   __syncthreads();
+  // the valid keys of the block take the places 0 .. here - 1
+  const int here = (int)(n - tile_base < kSortThreads * ITEMS ? n - tile_base : kSortThreads * ITEMS);
 #pragma unroll
-  for (int it = 0; it < kSortItems; ++it) {
-    const int64_t idx = wave_base + (int64_t)it * 64 + lane;
-    if (idx < n) {
-      const uint32_t dg = (uint32_t)(key[it] >> shift) & 255u;
-      const int64_t dst = digit_base[dg] + wave_cnt[w][dg] + rank[it];
-      keys_out[dst] = key[it];
-      if (pay_out) pay_out[dst] = pay[it];
+  for (int it = 0; it < ITEMS; ++it) {
+    rank[it] += wave_cnt[w][(uint32_t)(key[it] >> shift) & mask];
+    if (wave_base + (int64_t)it * 64 + lane < n) stage[rank[it]] = key[it];
+  }
+  __syncthreads();
+  int64_t dst[ITEMS];
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) {
+    const int pos = it * kSortThreads + t;
+    if (pos < here) {
+      const uint64_t k = stage[pos];
+      dst[it] = digit_base[(uint32_t)(k >> shift) & mask] + pos;
+      keys_out[dst[it]] = k;
+    }
+  }
+  if constexpr (PAY) {
+    uint32_t* pstage = reinterpret_cast<uint32_t*>(stage);
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it)
+      if (wave_base + (int64_t)it * 64 + lane < n) pstage[rank[it]] = pay[it];
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+      const int pos = it * kSortThreads + t;
+      if (pos < here) pay_out[dst[it]] = pstage[pos];
     }
   }
 }
 
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// (for 8 keys per thread: enough for any sort of at most n keys)
 size_t sort_tmp_bytes(int64_t n) {
-  const int64_t nb = ceil_div(n > 0 ? n : 1, kSortTile);
-  const int64_t m = 256 * nb;
+  const int64_t m = 256 * ceil_div(n > 0 ? n : 1, (int64_t)kSortThreads * 8);
   return align256(sizeof(uint32_t) * (size_t)m) + align256(sizeof(int64_t) * (size_t)(m + 1)) +
          align256(scan_tmp_bytes(m));
+}
+
+template <int ITEMS>
+static void sort_pass(const uint64_t* kin, uint64_t* kout, const uint32_t* pin, uint32_t* pout, int64_t n, int shift,
+                      uint32_t mask, int64_t nb, const int64_t* offsets, hipStream_t s) {
+  if (pin) k_sort_scatter<ITEMS, true><<<dim3((unsigned)nb), dim3(kSortThreads), 0, s>>>(kin, kout, pin, pout, n, shift, mask, nb, offsets);
+  else k_sort_scatter<ITEMS, false><<<dim3((unsigned)nb), dim3(kSortThreads), 0, s>>>(kin, kout, nullptr, nullptr, n, shift, mask, nb, offsets);
 }
 
 int radix_sort_u64(uint64_t* keys_a, uint64_t* keys_b, uint32_t* pay_a, uint32_t* pay_b, int64_t n,
@@ -213,20 +256,23 @@ int radix_sort_u64(uint64_t* keys_a, uint64_t* keys_b, uint32_t* pay_a, uint32_t
                    uint32_t** pay_out) {
   if (n < 0 || bit_lo < 0 || bit_hi > 64 || bit_hi < bit_lo) return fail(GCN_EINVAL, "sort: bad arguments");
   uint64_t* kin = keys_a; uint64_t* kout = keys_b;
-  uint32_t* pin = pay_a;  uint32_t* pout = pay_b;
+  uint32_t* pin = pay_a;  uint32_t* pout = pay_a ? pay_b : nullptr;
   if (n > 0) {
-    const int64_t nb = ceil_div(n, kSortTile);
+    const int64_t nb = sort_blocks(n);
     if (nb * kSortThreads >= ((int64_t)1 << 32)) return fail(GCN_EINVAL, "sort: input too large for one launch");
     const int64_t m = 256 * nb;
+    const bool big = sort_items(n) == 16;
     char* p = (char*)tmp;
     uint32_t* hist = (uint32_t*)p;          p += align256(sizeof(uint32_t) * (size_t)m);
     int64_t* offsets = (int64_t*)p;         p += align256(sizeof(int64_t) * (size_t)(m + 1));
     void* scan_tmp = p;
     for (int shift = bit_lo; shift < bit_hi; shift += 8) {
-      k_sort_hist<<<dim3((unsigned)nb), dim3(kSortThreads), 0, s>>>(kin, n, shift, nb, hist);
+      const uint32_t mask = bit_hi - shift >= 8 ? 255u : (1u << (bit_hi - shift)) - 1u;     // no bit from bit_hi on counts
+      if (big) k_sort_hist<16><<<dim3((unsigned)nb), dim3(kSortThreads), 0, s>>>(kin, n, shift, mask, nb, hist);
+      else k_sort_hist<8><<<dim3((unsigned)nb), dim3(kSortThreads), 0, s>>>(kin, n, shift, mask, nb, hist);
       GCN_TRY(exclusive_scan_u32(hist, offsets, m, scan_tmp, s));
-      k_sort_scatter<<<dim3((unsigned)nb), dim3(kSortThreads), 0, s>>>(kin, kout, pin, pay_a ? pout : nullptr,
-                                                                        n, shift, nb, offsets);
+      if (big) sort_pass<16>(kin, kout, pin, pout, n, shift, mask, nb, offsets, s);
+      else sort_pass<8>(kin, kout, pin, pout, n, shift, mask, nb, offsets, s);
       GCN_CHECK_LAUNCH();
       uint64_t* tk = kin; kin = kout; kout = tk;
       uint32_t* tp = pin; pin = pout; pout = tp;

@@ -89,6 +89,16 @@ def test_build_hub_rows(gcn, dev):
     compare(gcn, dev, src, dst, 9000, 0, 100, deg_global=whole_deg, what="hub block")
 
 
+@pytest.mark.parametrize("n,m", [(1, 0), (3, 2045), (200, 1848), (200, 1849), (256, 4000), (65536, 200000), (65537, 200000),
+                                 (3001, 2094150), (3001, 2094151), (70000, 2200000)])
+def test_build_at_the_edges_of_sort_and_compaction(gcn, dev, n, m):
+    """Candidates (edges + diagonal) at a whole number of sort blocks and beside it (2048 keys up to 2^21 - 1 of them, 4096
+    from there on), long runs of equal keys across blocks, column numbers of 8, 9, 16 and 17 bits, more than 2^21
+    candidates of which fewer are distinct."""
+    rng = np.random.default_rng(m)
+    compare(gcn, dev, rng.integers(0, n, m), rng.integers(0, n, m) ** 2 // n if n > 1 else np.zeros(m, int), n, what="edges")
+
+
 def test_build_rejects_bad_input(gcn, dev):
     with pytest.raises(gcn.GcnError):
         gcn.gcn_csr_build(_dev_i32([0, 7], dev), _dev_i32([1, 2], dev), 4)
