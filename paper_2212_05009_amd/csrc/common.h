@@ -84,6 +84,10 @@ struct ProfSuppress {
 // the runtime, which waits for such work by itself.
 int pool_alloc(void** p, size_t bytes);
 void pool_free(void* p, bool idle = true);
+// a pinned host page for the numbers a call reads back (a copy to pageable memory waits for the stream, each by itself)
+constexpr size_t kPinnedBytes = 16384;
+int pinned_take(void** p);
+void pinned_give(void* p);
 
 // The stream a call's temporaries are used on.  `done` is set once the call has waited for it; a call that leaves early
 // waits when its first temporary goes back.
@@ -111,6 +115,19 @@ struct DevBuf {
   }
   template <class T> T* as() const { return (T*)p; }
   void* release() { void* q = p; p = nullptr; return q; }
+};
+
+// A pinned host page for the time of a call.  Its copies have ended, or have been waited for, when it goes back: declare
+// it after its CallScope.
+struct PinnedPage {
+  void* p = nullptr;
+  CallScope* scope = nullptr;
+  PinnedPage() = default;
+  PinnedPage(const PinnedPage&) = delete;
+  PinnedPage& operator=(const PinnedPage&) = delete;
+  ~PinnedPage() { if (p && scope->quiesce()) pinned_give(p); }
+  int take(CallScope& sc) { scope = &sc; return pinned_take(&p); }
+  int64_t* words() const { return (int64_t*)p; }
 };
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -271,7 +288,6 @@ int radix_sort_u64(uint64_t* keys_a, uint64_t* keys_b, uint32_t* pay_a, uint32_t
                    uint32_t** pay_out);
 
 // ---- schedule construction (csr_build.hip) -------------------------------------------------
-int build_schedule(const int64_t* ptr, int64_t n_rows, hipStream_t s, Schedule* out);
 void free_schedule(Schedule* sc, bool idle = true);
 
 // ---- kernels behind the public entry points -------------------------------------------------

@@ -1,6 +1,7 @@
 // gcn_csr_build: normalised adjacency block in CSR (+CSC), halo index list, degree counts and
 // the row-binned execution schedules, all built on the device (Sec. 3.1: A^ = D^-1/2 (A+I) D^-1/2;
 // Sec. 4.1: the non-owned columns of the block are the rows to receive, each listed once).
+#include <algorithm>
 #include <new>
 
 #include "common.h"
@@ -59,7 +60,7 @@ constexpr uint64_t kInvalidKey = ~0ull;
 __global__ void k_make_keys(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                             int64_t n_edges, int64_t row_lo, int64_t row_hi, int64_t nr, int colbits,
                             const uint32_t* __restrict__ bitmap, const int64_t* __restrict__ wprefix,
-                            uint64_t* __restrict__ keys) {
+                            uint64_t* __restrict__ keys, int* __restrict__ bad) {
   int64_t e = block_id() * blockDim.x + threadIdx.x;
   if (e >= n_edges + nr) return;
   if (e >= n_edges) {                      // the diagonal of I, one entry per owned row
@@ -69,7 +70,10 @@ __global__ void k_make_keys(const int32_t* __restrict__ src, const int32_t* __re
   }
   int64_t s = src[e], t = dst[e];
   uint64_t k = kInvalidKey;
-  if (s >= row_lo && s < row_hi && s != t) {
+  if (!bitmap) {                           // a whole graph, which has no halo: ids are checked here
+    if (s < row_lo || s >= row_hi || t < row_lo || t >= row_hi) atomicOr(bad, 1);
+    else if (s != t) k = ((uint64_t)(s - row_lo) << colbits) | (uint64_t)(t - row_lo);
+  } else if (s >= row_lo && s < row_hi && s != t) {
     uint64_t lc;
     if (t >= row_lo && t < row_hi) {
       lc = (uint64_t)(t - row_lo);
@@ -242,31 +246,40 @@ __global__ void k_take_low32(const uint64_t* __restrict__ keys, int64_t n, int32
 
 __global__ void k_hub_lists(const uint32_t* __restrict__ hub_flag, const int64_t* __restrict__ hub_pos,
                             const uint32_t* __restrict__ hub_chunks, const int64_t* __restrict__ chunk_pos,
-                            int64_t n, int64_t n_hub, int32_t* __restrict__ hub_rows,
+                            int64_t n, int32_t* __restrict__ hub_rows,
                             int64_t* __restrict__ hub_chunk_ptr, int32_t* __restrict__ chunk_hub) {
   int64_t i = block_id() * blockDim.x + threadIdx.x;
+  if (i == 0) hub_chunk_ptr[0] = 0;
   if (i >= n || !hub_flag[i]) return;
   int64_t h = hub_pos[i];
   hub_rows[h] = (int32_t)i;
   int64_t c0 = chunk_pos[i];
-  hub_chunk_ptr[h] = c0;
-  if (h == n_hub - 1) hub_chunk_ptr[n_hub] = c0 + hub_chunks[i];
+  hub_chunk_ptr[h + 1] = c0 + hub_chunks[i];
   for (uint32_t c = 0; c < hub_chunks[i]; ++c) chunk_hub[c0 + c] = (int32_t)h;
 }
 
-// Row boundaries in the schedule's lists.  For boundary j (row bound[j]): out[j * 35 + c], c < 33, = first position
+// What the host keeps of a schedule: class boundaries (kClassSegs + 1 words, of which the hub rows' class is the last that
+// counts), the table of k_chunk_bounds, the numbers of hub rows and of their chunks.
+constexpr int kClassSegs = 64;
+constexpr int kChunkTable = (kRowChunks + 1) * 35;
+constexpr int kSchedWords = kClassSegs + 1 + kChunkTable + 2;
+static_assert(2 * kSchedWords * sizeof(int64_t) <= kPinnedBytes, "both schedules of a handle are read back in one page");
+struct RowBounds { int64_t row[kRowChunks + 1]; };
+
+// Row boundaries in the schedule's lists.  For boundary j (row bounds.row[j]): out[j * 35 + c], c < 33, = first position
 // of class c (list positions cb[c] .. cb[c + 1], rows ascending) whose row is >= bound[j]; out[j * 35 + 33] = first
 // hub row (ascending list of n_hub rows) >= bound[j]; out[j * 35 + 34] = that hub row's first chunk of entries.
 __global__ void k_chunk_bounds(const int32_t* __restrict__ wave_rows, const int64_t* __restrict__ cb,
-                               const int32_t* __restrict__ hub_rows, int64_t n_hub,
-                               const int64_t* __restrict__ hub_chunk_ptr, const int64_t* __restrict__ bound,
-                               int n_bounds, int64_t* __restrict__ out) {
+                               const int32_t* __restrict__ hub_rows, const int64_t* __restrict__ n_hub,
+                               const int64_t* __restrict__ n_chunks, const int64_t* __restrict__ hub_chunk_ptr, RowBounds bounds,
+                               int64_t* __restrict__ out, int64_t* __restrict__ counts) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_bounds * 34) return;
+  if (t == 0) { counts[0] = *n_hub; counts[1] = *n_chunks; }
+  if (t >= (kRowChunks + 1) * 34) return;
   const int j = t / 34, c = t % 34;
   const int32_t* list = c < 33 ? wave_rows : hub_rows;
-  int64_t lo = c < 33 ? cb[c] : 0, hi = c < 33 ? cb[c + 1] : n_hub;
-  const int64_t r = bound[j];
+  int64_t lo = c < 33 ? cb[c] : 0, hi = c < 33 ? cb[c + 1] : *n_hub;
+  const int64_t r = bounds.row[j];
   while (lo < hi) {
     const int64_t mid = lo + (hi - lo) / 2;
     if ((int64_t)list[mid] < r) lo = mid + 1; else hi = mid;
@@ -283,86 +296,78 @@ void free_schedule(Schedule* sc, bool idle) {
   *sc = Schedule();
 }
 
-int build_schedule(const int64_t* ptr, int64_t n, hipStream_t s, Schedule* out) {
-  *out = Schedule();
-  CallScope sc(s);
-  DevBuf keys_a, keys_b, hub_flag, hub_chunks, hub_pos, chunk_pos, tmp;
-  GCN_TRY(keys_a.alloc(sc, sizeof(uint64_t) * (size_t)n));
-  GCN_TRY(keys_b.alloc(sc, sizeof(uint64_t) * (size_t)n));
-  GCN_TRY(hub_flag.alloc(sc, sizeof(uint32_t) * (size_t)n));
-  GCN_TRY(hub_chunks.alloc(sc, sizeof(uint32_t) * (size_t)n));
-  GCN_TRY(hub_pos.alloc(sc, sizeof(int64_t) * (size_t)(n + 1)));
-  GCN_TRY(chunk_pos.alloc(sc, sizeof(int64_t) * (size_t)(n + 1)));
-  size_t tb = sort_tmp_bytes(n);
-  if (scan_tmp_bytes(n) > tb) tb = scan_tmp_bytes(n);
-  GCN_TRY(tmp.alloc(sc, tb));
-
-  k_sched_keys<<<grid_for(n), kThreads, 0, s>>>(ptr, n, keys_a.as<uint64_t>(), hub_flag.as<uint32_t>(),
-                                                 hub_chunks.as<uint32_t>());
-  GCN_CHECK_LAUNCH();
-  GCN_TRY(exclusive_scan_u32(hub_flag.as<uint32_t>(), hub_pos.as<int64_t>(), n, tmp.p, s));
-  GCN_TRY(exclusive_scan_u32(hub_chunks.as<uint32_t>(), chunk_pos.as<int64_t>(), n, tmp.p, s));
-  int64_t n_hub = 0, n_chunks = 0;
-  GCN_HIP(hipMemcpyAsync(&n_hub, hub_pos.as<int64_t>() + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipMemcpyAsync(&n_chunks, chunk_pos.as<int64_t>() + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipStreamSynchronize(s));
-
-  uint64_t* sorted = nullptr;
-  GCN_TRY(radix_sort_u64(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nullptr, nullptr, n, 32, 40, tmp.p, s,
-                         &sorted, nullptr));
+// A schedule in two halves, so that one wait serves both of a handle: everything is enqueued against bounds on the numbers
+// of long rows and chunks (a row of more than kHubRowNnz entries needs that many), then read back.
+struct ScheduleBuild {
+  DevBuf keys_a, keys_b, hub_flag, hub_chunks, hub_pos, chunk_pos, tmp, info;
   DevBuf wave_rows, hub_rows, hub_chunk_ptr, chunk_hub;
-  const int64_t n_wave = n - n_hub;
-  GCN_TRY(wave_rows.alloc(sc, sizeof(int32_t) * (size_t)(n_wave > 0 ? n_wave : 1)));
-  GCN_TRY(hub_rows.alloc(sc, sizeof(int32_t) * (size_t)(n_hub > 0 ? n_hub : 1)));
-  GCN_TRY(hub_chunk_ptr.alloc(sc, sizeof(int64_t) * (size_t)(n_hub + 1)));
-  GCN_TRY(chunk_hub.alloc(sc, sizeof(int32_t) * (size_t)(n_chunks > 0 ? n_chunks : 1)));
-  DevBuf class_begin;
-  GCN_TRY(class_begin.alloc(sc, sizeof(int64_t) * 34));
-  GCN_HIP(hipMemsetAsync(class_begin.p, 0, sizeof(int64_t) * 34, s));
-  if (n_wave > 0) {
-    k_take_low32<<<grid_for(n_wave), kThreads, 0, s>>>(sorted, n_wave, wave_rows.as<int32_t>());
-    k_boundaries<<<grid_for(n_wave), kThreads, 0, s>>>(sorted, n_wave, 32, ~0ull, 33, class_begin.as<int64_t>());
-  }
-  GCN_HIP(hipMemcpyAsync(out->class_begin, class_begin.p, sizeof(int64_t) * 34, hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipMemsetAsync(hub_chunk_ptr.p, 0, sizeof(int64_t) * (size_t)(n_hub + 1), s));
-  if (n_hub > 0)
-    k_hub_lists<<<grid_for(n), kThreads, 0, s>>>(hub_flag.as<uint32_t>(), hub_pos.as<int64_t>(),
-                                                  hub_chunks.as<uint32_t>(), chunk_pos.as<int64_t>(), n, n_hub,
-                                                  hub_rows.as<int32_t>(), hub_chunk_ptr.as<int64_t>(),
+  RowBounds bounds;
+  const int64_t* host = nullptr;     // kSchedWords words, valid once the stream has been waited for
+
+  int enqueue(const int64_t* ptr, int64_t n, int64_t nnz, CallScope& sc, int64_t* host_words) {
+    hipStream_t s = sc.s;
+    host = host_words;
+    const int64_t max_hub = std::min(n, nnz / (kHubRowNnz + 1)), max_chunks = nnz / kHubChunkNnz + max_hub;
+    GCN_TRY(keys_a.alloc(sc, sizeof(uint64_t) * (size_t)n));
+    GCN_TRY(keys_b.alloc(sc, sizeof(uint64_t) * (size_t)n));
+    GCN_TRY(hub_flag.alloc(sc, sizeof(uint32_t) * (size_t)n));
+    GCN_TRY(hub_chunks.alloc(sc, sizeof(uint32_t) * (size_t)n));
+    GCN_TRY(hub_pos.alloc(sc, sizeof(int64_t) * (size_t)(n + 1)));
+    GCN_TRY(chunk_pos.alloc(sc, sizeof(int64_t) * (size_t)(n + 1)));
+    GCN_TRY(tmp.alloc(sc, std::max(sort_tmp_bytes(n), scan_tmp_bytes(n))));
+    GCN_TRY(info.alloc(sc, sizeof(int64_t) * kSchedWords));
+    GCN_TRY(wave_rows.alloc(sc, sizeof(int32_t) * (size_t)n));
+    GCN_TRY(hub_rows.alloc(sc, sizeof(int32_t) * (size_t)(max_hub + 1)));
+    GCN_TRY(hub_chunk_ptr.alloc(sc, sizeof(int64_t) * (size_t)(max_hub + 1)));
+    GCN_TRY(chunk_hub.alloc(sc, sizeof(int32_t) * (size_t)(max_chunks + 1)));
+    int64_t* class_begin = info.as<int64_t>();
+    int64_t* table = class_begin + kClassSegs + 1;
+
+    k_sched_keys<<<grid_for(n), kThreads, 0, s>>>(ptr, n, keys_a.as<uint64_t>(), hub_flag.as<uint32_t>(), hub_chunks.as<uint32_t>());
+    GCN_CHECK_LAUNCH();
+    GCN_TRY(exclusive_scan_u32(hub_flag.as<uint32_t>(), hub_pos.as<int64_t>(), n, tmp.p, s));
+    GCN_TRY(exclusive_scan_u32(hub_chunks.as<uint32_t>(), chunk_pos.as<int64_t>(), n, tmp.p, s));
+    uint64_t* sorted = nullptr;
+    GCN_TRY(radix_sort_u64(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nullptr, nullptr, n, 32, 40, tmp.p, s, &sorted, nullptr));
+    // hub rows carry the key ~0: they follow the ordinary rows, as segment 63
+    k_take_low32<<<grid_for(n), kThreads, 0, s>>>(sorted, n, wave_rows.as<int32_t>());
+    k_boundaries<<<grid_for(n), kThreads, 0, s>>>(sorted, n, 32, kClassSegs - 1, kClassSegs, class_begin);
+    k_hub_lists<<<grid_for(n), kThreads, 0, s>>>(hub_flag.as<uint32_t>(), hub_pos.as<int64_t>(), hub_chunks.as<uint32_t>(),
+                                                  chunk_pos.as<int64_t>(), n, hub_rows.as<int32_t>(), hub_chunk_ptr.as<int64_t>(),
                                                   chunk_hub.as<int32_t>());
-  GCN_CHECK_LAUNCH();
-  // the class lists and the hub list cut at kRowChunks row boundaries (multiples of 64 rows)
-  DevBuf chunk_bound, chunk_cb;
-  constexpr int kChunkTable = (kRowChunks + 1) * 35;
-  GCN_TRY(chunk_bound.alloc(sc, sizeof(int64_t) * (kRowChunks + 1)));
-  GCN_TRY(chunk_cb.alloc(sc, sizeof(int64_t) * kChunkTable));
-  int64_t chunk_table[kChunkTable];
-  for (int j = 0; j <= kRowChunks; ++j) {
-    const int64_t r = round_up(ceil_div(n * j, kRowChunks), 64);
-    out->chunk_row[j] = j == kRowChunks || r > n ? n : r;
+    // the class lists and the hub list cut at kRowChunks row boundaries (multiples of 64 rows)
+    for (int j = 0; j <= kRowChunks; ++j) {
+      const int64_t r = round_up(ceil_div(n * j, kRowChunks), 64);
+      bounds.row[j] = j == kRowChunks || r > n ? n : r;
+    }
+    k_chunk_bounds<<<(unsigned)ceil_div((kRowChunks + 1) * 34, 256), 256, 0, s>>>(
+        wave_rows.as<int32_t>(), class_begin, hub_rows.as<int32_t>(), hub_pos.as<int64_t>() + n, chunk_pos.as<int64_t>() + n,
+        hub_chunk_ptr.as<int64_t>(), bounds, table, table + kChunkTable);
+    GCN_CHECK_LAUNCH();
+    GCN_HIP(hipMemcpyAsync(host_words, info.p, sizeof(int64_t) * kSchedWords, hipMemcpyDeviceToHost, s));
+    return GCN_OK;
   }
-  GCN_HIP(hipMemcpyAsync(chunk_bound.p, out->chunk_row, sizeof(int64_t) * (kRowChunks + 1), hipMemcpyHostToDevice, s));
-  k_chunk_bounds<<<(unsigned)ceil_div((kRowChunks + 1) * 34, 256), 256, 0, s>>>(
-      wave_rows.as<int32_t>(), class_begin.as<int64_t>(), hub_rows.as<int32_t>(), n_hub, hub_chunk_ptr.as<int64_t>(),
-      chunk_bound.as<int64_t>(), kRowChunks + 1, chunk_cb.as<int64_t>());
-  GCN_CHECK_LAUNCH();
-  GCN_HIP(hipMemcpyAsync(chunk_table, chunk_cb.p, sizeof(chunk_table), hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipStreamSynchronize(s));   // temporaries go back on return
-  sc.done = true;
-  for (int j = 0; j <= kRowChunks; ++j) {
-    for (int c = 0; c < 33; ++c) out->chunk_class_begin[j][c] = chunk_table[j * 35 + c];
-    out->chunk_hub_begin[j] = chunk_table[j * 35 + 33];
-    out->chunk_hubchunk_begin[j] = chunk_table[j * 35 + 34];
+
+  // after the stream has been waited for
+  void finish(int64_t n, Schedule* out) {
+    const int64_t* table = host + kClassSegs + 1;
+    *out = Schedule();
+    out->n_hub_rows = table[kChunkTable];
+    out->n_chunks = table[kChunkTable + 1];
+    out->n_wave_rows = n - out->n_hub_rows;
+    for (int c = 0; c < 34; ++c) out->class_begin[c] = host[c];
+    for (int j = 0; j <= kRowChunks; ++j) {
+      out->chunk_row[j] = bounds.row[j];
+      for (int c = 0; c < 33; ++c) out->chunk_class_begin[j][c] = table[j * 35 + c];
+      out->chunk_hub_begin[j] = table[j * 35 + 33];
+      out->chunk_hubchunk_begin[j] = table[j * 35 + 34];
+    }
+    out->wave_rows = (int32_t*)wave_rows.release();
+    out->hub_rows = (int32_t*)hub_rows.release();
+    out->hub_chunk_ptr = (int64_t*)hub_chunk_ptr.release();
+    out->chunk_hub = (int32_t*)chunk_hub.release();
   }
-  out->wave_rows = (int32_t*)wave_rows.release();
-  out->n_wave_rows = n_wave;
-  out->hub_rows = (int32_t*)hub_rows.release();
-  out->n_hub_rows = n_hub;
-  out->hub_chunk_ptr = (int64_t*)hub_chunk_ptr.release();
-  out->chunk_hub = (int32_t*)chunk_hub.release();
-  out->n_chunks = n_chunks;
-  return GCN_OK;
-}
+};
 
 static int bits_for(int64_t max_value_exclusive) {   // smallest b with 2^b - 1 > max_value_exclusive - 1 ... i.e. 2^b > max_value_exclusive
   int b = 1;
@@ -378,37 +383,44 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   const int64_t m = n_edges + nr;          // candidate entries: edges + diagonal
 
   CallScope sc(s);
-  // -- validation and halo bitmap
+  PinnedPage page;
+  GCN_TRY(page.take(sc));
+  int64_t* read = page.words();
+  // -- validation and halo bitmap.  A whole graph has no halo, and its ids are checked while its keys are made: the
+  // verdict is read with the number of entries, and what is enqueued until then uses no id as an index.
   const int64_t words = ceil_div(n_global, 32);
   DevBuf bad, bitmap, wcnt, wprefix, tmp;
-  GCN_TRY(bad.alloc(sc, sizeof(int)));
-  GCN_TRY(bitmap.alloc(sc, sizeof(uint32_t) * (size_t)words));
-  GCN_TRY(wcnt.alloc(sc, sizeof(uint32_t) * (size_t)words));
-  GCN_TRY(wprefix.alloc(sc, sizeof(int64_t) * (size_t)(words + 1)));
+  GCN_TRY(bad.alloc(sc, sizeof(int64_t)));
   size_t tb = sort_tmp_bytes(m);
   if (scan_tmp_bytes(m) > tb) tb = scan_tmp_bytes(m);
   if (scan_tmp_bytes(words) > tb) tb = scan_tmp_bytes(words);
   GCN_TRY(tmp.alloc(sc, tb));
-  GCN_HIP(hipMemsetAsync(bad.p, 0, sizeof(int), s));
-  GCN_HIP(hipMemsetAsync(bitmap.p, 0, sizeof(uint32_t) * (size_t)words, s));
-  if (n_edges > 0) {
-    k_validate<<<grid_for(n_edges), kThreads, 0, s>>>(d_src, d_dst, n_edges, n_global, bad.as<int>());
-    GCN_CHECK_LAUNCH();
-  }
+  GCN_HIP(hipMemsetAsync(bad.p, 0, sizeof(int64_t), s));
   if (d_deg_global) k_validate_deg<<<grid_for(n_global), kThreads, 0, s>>>(d_deg_global, n_global, bad.as<int>());
-  int h_bad = 0;
-  GCN_HIP(hipMemcpyAsync(&h_bad, bad.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipStreamSynchronize(s));
-  if (h_bad & 1) return fail(GCN_EINVAL, "gcn_csr_build: a vertex id lies outside [0, n_global)");
-  if (h_bad & 2) return fail(GCN_EINVAL, "gcn_csr_build: d_deg_global holds a degree < 1");
-
-  if (n_edges > 0) k_mark_halo<<<grid_for(n_edges), kThreads, 0, s>>>(d_src, d_dst, n_edges, row_lo, row_hi, bitmap.as<uint32_t>());
-  k_popc<<<grid_for(words), kThreads, 0, s>>>(bitmap.as<uint32_t>(), words, wcnt.as<uint32_t>());
-  GCN_CHECK_LAUNCH();
-  GCN_TRY(exclusive_scan_u32(wcnt.as<uint32_t>(), wprefix.as<int64_t>(), words, tmp.p, s));
+  auto verdict = [&](int64_t v) {
+    if (v & 1) return fail(GCN_EINVAL, "gcn_csr_build: a vertex id lies outside [0, n_global)");
+    if (v & 2) return fail(GCN_EINVAL, "gcn_csr_build: d_deg_global holds a degree < 1");
+    return (int)GCN_OK;
+  };
   int64_t nh = 0;
-  GCN_HIP(hipMemcpyAsync(&nh, wprefix.as<int64_t>() + words, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipStreamSynchronize(s));
+  if (!whole) {
+    GCN_TRY(bitmap.alloc(sc, sizeof(uint32_t) * (size_t)words));
+    GCN_TRY(wcnt.alloc(sc, sizeof(uint32_t) * (size_t)words));
+    GCN_TRY(wprefix.alloc(sc, sizeof(int64_t) * (size_t)(words + 1)));
+    GCN_HIP(hipMemsetAsync(bitmap.p, 0, sizeof(uint32_t) * (size_t)words, s));
+    if (n_edges > 0) k_validate<<<grid_for(n_edges), kThreads, 0, s>>>(d_src, d_dst, n_edges, n_global, bad.as<int>());
+    GCN_CHECK_LAUNCH();
+    GCN_HIP(hipMemcpyAsync(read, bad.p, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    GCN_HIP(hipStreamSynchronize(s));
+    GCN_TRY(verdict(read[0]));
+    if (n_edges > 0) k_mark_halo<<<grid_for(n_edges), kThreads, 0, s>>>(d_src, d_dst, n_edges, row_lo, row_hi, bitmap.as<uint32_t>());
+    k_popc<<<grid_for(words), kThreads, 0, s>>>(bitmap.as<uint32_t>(), words, wcnt.as<uint32_t>());
+    GCN_CHECK_LAUNCH();
+    GCN_TRY(exclusive_scan_u32(wcnt.as<uint32_t>(), wprefix.as<int64_t>(), words, tmp.p, s));
+    GCN_HIP(hipMemcpyAsync(read, wprefix.as<int64_t>() + words, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    GCN_HIP(hipStreamSynchronize(s));
+    nh = read[0];
+  }
   const int64_t nc = nr + nh;
   if (nc >= 0x7fffffffLL) return fail(GCN_EINVAL, "gcn_csr_build: more than 2^31-1 local columns");
   DevBuf halo_gid;
@@ -424,7 +436,7 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   GCN_TRY(keys_a.alloc(sc, sizeof(uint64_t) * (size_t)m));
   GCN_TRY(keys_b.alloc(sc, sizeof(uint64_t) * (size_t)m));
   k_make_keys<<<grid_for(m), kThreads, 0, s>>>(d_src, d_dst, n_edges, row_lo, row_hi, nr, colbits,
-                                                bitmap.as<uint32_t>(), wprefix.as<int64_t>(), keys_a.as<uint64_t>());
+                                                bitmap.as<uint32_t>(), wprefix.as<int64_t>(), keys_a.as<uint64_t>(), bad.as<int>());
   GCN_CHECK_LAUNCH();
   uint64_t* sorted = nullptr;
   GCN_TRY(radix_sort_u64(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nullptr, nullptr, m, 0, colbits + rowbits,
@@ -436,9 +448,11 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   k_count_unique<<<fold_grid(nb), kThreads, 0, s>>>(sorted, m, nb, cnt.as<uint32_t>());
   GCN_CHECK_LAUNCH();
   GCN_TRY(exclusive_scan_u32(cnt.as<uint32_t>(), off.as<int64_t>(), nb, tmp.p, s));
-  int64_t nnz = 0;
-  GCN_HIP(hipMemcpyAsync(&nnz, off.as<int64_t>() + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  GCN_HIP(hipMemcpyAsync(read, bad.p, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  GCN_HIP(hipMemcpyAsync(read + 1, off.as<int64_t>() + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s));
   GCN_HIP(hipStreamSynchronize(s));
+  GCN_TRY(verdict(read[0]));
+  const int64_t nnz = read[1];
   if (nnz < nr) return fail(GCN_EHIP, "gcn_csr_build: internal error (nnz %lld < rows %lld)", (long long)nnz, (long long)nr);
   if (nnz >= 0xffffffffLL) return fail(GCN_EINVAL, "gcn_csr_build: more than 2^32-2 stored entries in one block");
 
@@ -475,13 +489,16 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
     k_finish_csc<<<grid_for(nnz), kThreads, 0, s>>>(tsorted, nnz, colbits, dinv.as<float>(), rowidx.as<int32_t>(), val_t.as<float>());
     GCN_CHECK_LAUNCH();
   }
+  ScheduleBuild by_row, by_col;
+  GCN_TRY(by_row.enqueue(rowptr.as<int64_t>(), nr, nnz, sc, read));
+  if (flags & GCN_BUILD_CSC) GCN_TRY(by_col.enqueue(colptr.as<int64_t>(), nc, nnz, sc, read + kSchedWords));
   GCN_HIP(hipStreamSynchronize(s));
   sc.done = true;
 
   A->n_global = n_global; A->row_lo = row_lo;
   A->nr = nr; A->nh = nh; A->nc = nc; A->nnz = nnz;
-  GCN_TRY(build_schedule(rowptr.as<int64_t>(), nr, s, &A->sched));
-  if (flags & GCN_BUILD_CSC) GCN_TRY(build_schedule(colptr.as<int64_t>(), nc, s, &A->sched_t));
+  by_row.finish(nr, &A->sched);
+  if (flags & GCN_BUILD_CSC) by_col.finish(nc, &A->sched_t);
   A->rowptr = (int64_t*)rowptr.release(); A->col = (int32_t*)col.release();
   A->val = (float*)val.release(); A->deg = (int32_t*)deg.release();
   A->halo_gid = (int32_t*)halo_gid.release();

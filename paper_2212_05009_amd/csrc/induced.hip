@@ -26,18 +26,20 @@ __global__ void k_ind_scatter(const int32_t* __restrict__ vertices, int64_t n_su
   int64_t k = block_id() * blockDim.x + threadIdx.x;
   if (k >= n_sub) return;
   const int32_t v = vertices[k];
-  if (v < 0 || v >= n) { *bad = 1; return; }
+  if (v < 0 || v >= n) { bad[0] = 1; return; }
   lid[v] = (int32_t)k;
 }
 
+// (an id outside the graph has been reported: it counts for no entry here)
 // a vertex listed twice keeps one of its two positions in lid: the other one sees a mismatch.
 // Also the number of stored entries of each selected row.
-__global__ void k_ind_rows(const int32_t* __restrict__ vertices, int64_t n_sub, const int32_t* __restrict__ lid,
+__global__ void k_ind_rows(const int32_t* __restrict__ vertices, int64_t n_sub, int64_t n, const int32_t* __restrict__ lid,
                            const int64_t* __restrict__ rowptr, uint32_t* __restrict__ len, int* __restrict__ bad) {
   int64_t k = block_id() * blockDim.x + threadIdx.x;
   if (k >= n_sub) return;
   const int32_t v = vertices[k];
-  if (lid[v] != (int32_t)k) *bad = 2;
+  if (v < 0 || v >= n) { len[k] = 0u; return; }
+  if (lid[v] != (int32_t)k) bad[1] = 1;
   len[k] = (uint32_t)(rowptr[v + 1] - rowptr[v]);
 }
 
@@ -78,24 +80,24 @@ extern "C" int gcn_csr_induced(const gcn_csr_t* A, const int32_t* d_vertices, in
   GCN_TRY(len.alloc(sc, sizeof(uint32_t) * (size_t)n_sub));
   GCN_TRY(off.alloc(sc, sizeof(int64_t) * (size_t)(n_sub + 1)));
   GCN_TRY(tmp.alloc(sc, scan_tmp_bytes(n_sub)));
-  GCN_TRY(bad.alloc(sc, sizeof(int)));
-  GCN_HIP(hipMemsetAsync(bad.p, 0, sizeof(int), s));
+  PinnedPage page;
+  GCN_TRY(page.take(sc));
+  int64_t* read = page.words();
+  GCN_TRY(bad.alloc(sc, 2 * sizeof(int)));
+  GCN_HIP(hipMemsetAsync(bad.p, 0, 2 * sizeof(int), s));
   k_ind_fill<<<ind_grid(n), kIndThreads, 0, s>>>(lid.as<int32_t>(), n, -1);
   k_ind_scatter<<<ind_grid(n_sub), kIndThreads, 0, s>>>(d_vertices, n_sub, n, lid.as<int32_t>(), bad.as<int>());
-  GCN_CHECK_LAUNCH();
-  int h_bad = 0;
-  GCN_HIP(hipMemcpyAsync(&h_bad, bad.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipStreamSynchronize(s));
-  if (h_bad) return fail(GCN_EINVAL, "gcn_csr_induced: a vertex id lies outside the graph");
-  k_ind_rows<<<ind_grid(n_sub), kIndThreads, 0, s>>>(d_vertices, n_sub, lid.as<int32_t>(), A->rowptr,
-                                                    len.as<uint32_t>(), bad.as<int>());
+  k_ind_rows<<<ind_grid(n_sub), kIndThreads, 0, s>>>(d_vertices, n_sub, n, lid.as<int32_t>(), A->rowptr, len.as<uint32_t>(),
+                                                    bad.as<int>());
   GCN_CHECK_LAUNCH();
   GCN_TRY(exclusive_scan_u32(len.as<uint32_t>(), off.as<int64_t>(), n_sub, tmp.p, s));
-  int64_t total = 0;
-  GCN_HIP(hipMemcpyAsync(&h_bad, bad.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipMemcpyAsync(&total, off.as<int64_t>() + n_sub, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  GCN_HIP(hipMemcpyAsync(read, bad.p, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+  GCN_HIP(hipMemcpyAsync(read + 1, off.as<int64_t>() + n_sub, sizeof(int64_t), hipMemcpyDeviceToHost, s));
   GCN_HIP(hipStreamSynchronize(s));
-  if (h_bad) return fail(GCN_EINVAL, "gcn_csr_induced: a vertex is listed twice");
+  const int* h_bad = (const int*)read;
+  if (h_bad[0]) return fail(GCN_EINVAL, "gcn_csr_induced: a vertex id lies outside the graph");
+  if (h_bad[1]) return fail(GCN_EINVAL, "gcn_csr_induced: a vertex is listed twice");
+  const int64_t total = read[1];
 
   DevBuf src, dst;
   GCN_TRY(src.alloc(sc, sizeof(int32_t) * (size_t)total));

@@ -15,6 +15,7 @@
 #include <map>
 #include <mutex>
 #include <unordered_map>
+#include <vector>
 
 #include "common.h"
 
@@ -38,6 +39,7 @@ struct Pool {
   std::mutex mu;
   std::unordered_map<void*, std::pair<int, size_t>> live;   // block -> device, size
   DevicePool dev[kPoolDevices];
+  std::vector<void*> pinned;                                // idle pinned host pages
 };
 
 Pool& pool() {
@@ -139,6 +141,31 @@ void pool_free(void* p, bool idle) {
   }
   d.held += bytes;
   while (d.held > d.limit || d.by_age.front().freed_at + kIdleReturns < d.returns) drop(d, d.by_age.begin());
+}
+
+// Pinned host pages: at most kMaxPinned are kept.
+constexpr size_t kMaxPinned = 16;
+
+int pinned_take(void** out) {
+  *out = nullptr;
+  {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    if (!P.pinned.empty()) { *out = P.pinned.back(); P.pinned.pop_back(); return GCN_OK; }
+  }
+  GCN_HIP(hipHostMalloc(out, kPinnedBytes, hipHostMallocPortable));
+  return GCN_OK;
+}
+
+void pinned_give(void* p) {
+  if (!p) return;
+  try {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    if (P.pinned.size() < kMaxPinned) { P.pinned.push_back(p); return; }
+  } catch (const std::bad_alloc&) {
+  }
+  (void)hipHostFree(p);
 }
 
 }  // namespace gcn

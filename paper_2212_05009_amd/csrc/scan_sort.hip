@@ -6,7 +6,9 @@
 namespace gcn {
 
 // ------------------------------------------------------------------------------------------
-// Exclusive scan, uint32 in -> int64 out, reduce-then-scan in three launches.
+// Exclusive scan, uint32 in -> int64 out, reduce-then-scan: block sums, then every block adds up the sums before its own
+// (up to kScanFewBlocks blocks) or finds them scanned by a launch of their own.  The scans of a graph build are short (a
+// few hundred blocks) and there are a dozen of them: what counts is the launch, about 5 us.
 // ------------------------------------------------------------------------------------------
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
@@ -42,11 +44,11 @@ __device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t* tota
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* __restrict__ in,
                                                               int64_t n, int64_t* __restrict__ sums) {
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  const int64_t base = (int64_t)blockIdx.x * kScanTile + threadIdx.x;
   int64_t s = 0;
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i)
-    if (base + i < n) s += in[base + i];
+    if (base + i * kScanThreads < n) s += in[base + i * kScanThreads];
   int64_t tot;
   block_exclusive_scan(s, &tot);
   if (threadIdx.x == 0) sums[blockIdx.x] = tot;
@@ -67,25 +69,58 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_sums(int64_t* __restrict_
   if (threadIdx.x == 0) *total_out = carry;
 }
 
+// SCANNED: sums[b] is the sum of all blocks before b; else it is block b's own, and the last block writes the total
+template <bool SCANNED>
 __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const uint32_t* __restrict__ in,
                                                              int64_t n, const int64_t* __restrict__ sums,
                                                              int64_t* __restrict__ out) {
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
   uint32_t v[kScanItems];
   int64_t s = 0;
+  // a thread's items are 64 bytes of the input and 128 of the output: whole requests where the arrays start on 16 bytes
+  const bool wide = base + kScanItems <= n && (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
+  if (wide) {
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    v[i] = (base + i < n) ? in[base + i] : 0u;
-    s += v[i];
+    for (int i = 0; i < kScanItems; i += 4) {
+      const uint4 x = *reinterpret_cast<const uint4*>(in + base + i);
+      v[i] = x.x; v[i + 1] = x.y; v[i + 2] = x.z; v[i + 3] = x.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) v[i] = (base + i < n) ? in[base + i] : 0u;
+  }
+#pragma unroll
+  for (int i = 0; i < kScanItems; ++i) s += v[i];
+  int64_t before;
+  if constexpr (SCANNED) {
+    before = sums[blockIdx.x];
+  } else {
+    int64_t p = 0;
+    for (int64_t i = threadIdx.x; i < blockIdx.x; i += kScanThreads) p += sums[i];
+    block_exclusive_scan(p, &before);
   }
   int64_t tot;
-  int64_t run = sums[blockIdx.x] + block_exclusive_scan(s, &tot);
+  int64_t run = before + block_exclusive_scan(s, &tot);
+  if (!SCANNED && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = before + tot;
+  if (wide) {
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    if (base + i < n) out[base + i] = run;
-    run += v[i];
+    for (int i = 0; i < kScanItems; i += 2) {
+      longlong2 y;
+      y.x = run;
+      y.y = run + v[i];
+      run = y.y + v[i + 1];
+      *reinterpret_cast<longlong2*>(out + base + i) = y;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+      if (base + i < n) out[base + i] = run;
+      run += v[i];
+    }
   }
 }
+
+constexpr int64_t kScanFewBlocks = 1024;         // (a block then reads at most 8 KB of sums)
 
 size_t scan_tmp_bytes(int64_t n) { return sizeof(int64_t) * (size_t)(ceil_div(n > 0 ? n : 1, kScanTile) + 1); }
 
@@ -99,8 +134,12 @@ int exclusive_scan_u32(const uint32_t* in, int64_t* out, int64_t n, void* tmp, h
   if (nb * kScanThreads >= ((int64_t)1 << 32)) return fail(GCN_EINVAL, "scan: input too large for one launch");
   int64_t* sums = (int64_t*)tmp;
   k_scan_reduce<<<dim3((unsigned)nb), dim3(kScanThreads), 0, s>>>(in, n, sums);
-  k_scan_sums<<<dim3(1), dim3(kScanThreads), 0, s>>>(sums, nb, out + n);
-  k_scan_apply<<<dim3((unsigned)nb), dim3(kScanThreads), 0, s>>>(in, n, sums, out);
+  if (nb <= kScanFewBlocks) {
+    k_scan_apply<false><<<dim3((unsigned)nb), dim3(kScanThreads), 0, s>>>(in, n, sums, out);
+  } else {
+    k_scan_sums<<<dim3(1), dim3(kScanThreads), 0, s>>>(sums, nb, out + n);
+    k_scan_apply<true><<<dim3((unsigned)nb), dim3(kScanThreads), 0, s>>>(in, n, sums, out);
+  }
   GCN_CHECK_LAUNCH();
   return GCN_OK;
 }
