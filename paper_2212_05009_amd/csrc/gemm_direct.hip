@@ -70,6 +70,8 @@ struct NnDirectArgs {
   int64_t M; int N; int K; int vecA; int vecC; int vecC2; int vecM;
   const float* bias; int relu; const void* mask; int64_t ldmask; int64_t mask_rows; void* C2; int64_t ldc2;
   int trans;               // W is stored [N x K]
+  // k_gemm_nn_fast: a row of A / of the outputs ends with its last element, nothing beyond may be touched
+  int endA = 0, endC = 0;
 };
 
 // put(k, n, W[k][n]) for every element of the LDS copy of W (Kp x NP elements, zero beyond K and N), walked along the
@@ -207,17 +209,23 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(NT <
 }
 
 // ---- the same product without a single data-dependent branch ----------------------------------------
-// For operands whose rows are 16-byte aligned (fp32; 8-byte for bf16), K up to 128 (KU = ceil(K / 16) k steps, the
-// whole row in one request batch, a tail of the row cleared by bit masks) or a multiple of 128 (KU = 8), N up to 256 and a mask that covers every row.  Every load is an
+// For operands whose rows start on a 4-byte word, K up to 128 (KU = ceil(K / 16) k steps, the
+// whole row in one request batch, a tail of the row cleared by bit masks) or a multiple of 128 (KU = 8), N up to 256 and a
+// mask that covers every row.  Rows on 16 bytes (bf16: 8) may be read and written up to the next multiple of 4 elements;
+// in other rows the request that would pass the end is moved back to end with the row and its elements are shifted into
+// place, and the last columns of the result are stored one by one.  Measured, 500 K x 50 x 50 in contiguous rows (200
+// bytes): general kernel 128 us, this one 69 us.  Every load is an
 // unconditional 16-byte (bf16: 8-byte) request - rows beyond M are clamped to the last row and dropped at
 // the store - so the compiler can keep the next step's operand loads in flight across the MFMAs of the
 // current one instead of waiting at every join of the general kernel's bounds checks.
+// (the global memory path takes 8- and 16-byte requests at any word address)
+typedef float floatx4w __attribute__((ext_vector_type(4), aligned(4)));
 template <typename T> __device__ __forceinline__ void vload4(const T* __restrict__ p, float (&o)[4]) {
   if constexpr (sizeof(T) == 4) {
-    const floatx4 v = *reinterpret_cast<const floatx4*>(p);
+    const floatx4w v = *reinterpret_cast<const floatx4w*>(p);
     o[0] = v[0]; o[1] = v[1]; o[2] = v[2]; o[3] = v[3];
   } else {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(4)));
     const u32x2 v = *reinterpret_cast<const u32x2*>(p);
     o[0] = __uint_as_float(v[0] << 16); o[1] = __uint_as_float(v[0] & 0xffff0000u);
     o[2] = __uint_as_float(v[1] << 16); o[3] = __uint_as_float(v[1] & 0xffff0000u);
@@ -225,9 +233,9 @@ template <typename T> __device__ __forceinline__ void vload4(const T* __restrict
 }
 template <typename T> __device__ __forceinline__ void vstore4(T* __restrict__ p, const float (&v)[4]) {
   if constexpr (sizeof(T) == 4) {
-    *reinterpret_cast<floatx4*>(p) = floatx4{v[0], v[1], v[2], v[3]};
+    *reinterpret_cast<floatx4w*>(p) = floatx4w{v[0], v[1], v[2], v[3]};
   } else {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(4)));
     bf16_t h[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) store_one<T>(&h[i], v[i]);
@@ -267,7 +275,9 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(NT <
   // or reach past it (the row is padded to 4 elements); `tail` clears what is not part of the product
   const int k_last = 16 * KU * chunks - 16 + 4 * q;
   const int n_ok = a.K - k_last;
-  const int last_off = n_ok > 0 ? k_last : 0;
+  // (endA: moved back to column K - 4, `shift` elements too early)
+  const int shift = !FULL && a.endA && n_ok > 0 && n_ok < 4 ? 4 - n_ok : 0;
+  const int last_off = n_ok > 0 ? k_last - shift : 0;
   uint32_t tail[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) tail[i] = i < n_ok ? 0xffffffffu : 0u;
@@ -318,6 +328,11 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(NT <
         for (int i = 0; i < 4; ++i) av[u][i] = a_nxt[u][i];
       if constexpr (!FULL) {
         if (chunk == chunks - 1) {
+          if (a.endA) {
+            float (&x)[4] = av[KU - 1];
+            if (shift & 1) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; }
+            if (shift & 2) { x[0] = x[2]; x[1] = x[3]; }
+          }
 #pragma unroll
           for (int i = 0; i < 4; ++i) av[KU - 1][i] = __uint_as_float(__float_as_uint(av[KU - 1][i]) & tail[i]);
         }
@@ -378,6 +393,17 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(NT <
           v[r] = a.relu ? (pre[r] > 0.f ? pre[r] : 0.f) : pre[r];
           if constexpr (MASK) v[r] = (kPrefetchMask ? keep[t][r] : kp[r]) > 0.f ? v[r] : 0.f;
         }
+        if constexpr (!FULL) {
+          if (a.endC && n + 3 >= a.N) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              if (n + r >= a.N) continue;
+              if constexpr (SAVE) store_one<T>(C2 + m * a.ldc2 + n + r, pre[r]);
+              store_one<T>(C + m * a.ldc + n + r, v[r]);
+            }
+            continue;
+          }
+        }
         if constexpr (SAVE) vstore4<T>(C2 + m * a.ldc2 + n, pre);
         vstore4<T>(C + m * a.ldc + n, v);
       }
@@ -430,12 +456,17 @@ static int nn_launch_fast(const NnDirectArgs& a, hipStream_t s) {
   return a.C2 ? go(k_gemm_nn_fast<T, NT, KU, false, true, false>) : go(k_gemm_nn_fast<T, NT, KU, false, false, false>);
 }
 
-// the branch-free kernel serves aligned rows with K up to 128 or a multiple of 128
+// the branch-free kernel serves rows on word boundaries with K up to 128 or a multiple of 128
 template <typename T>
-static bool nn_fast(const NnDirectArgs& a, hipStream_t s, int* rc) {
+static bool nn_fast(NnDirectArgs a, hipStream_t s, int* rc) {
   const bool off = tune().gemm_fast == 0;
   const int NT = nn_tiles(a.N);
-  if (off || a.vecA != 4 || a.vecC != 4 || (a.C2 && a.vecC2 != 4)) return false;
+  if (off) return false;
+  auto words = [](const void* p, int64_t ld) { return ((uintptr_t)p % 4) == 0 && (ld * (int64_t)sizeof(T)) % 4 == 0; };
+  a.endA = a.vecA != 4;
+  if (a.endA && (a.K < 4 || !words(a.A, a.lda) || (a.K * sizeof(T)) % 4 != 0)) return false;
+  a.endC = a.vecC != 4 || (a.C2 && a.vecC2 != 4);
+  if (a.endC && (!words(a.C, a.ldc) || (a.C2 && !words(a.C2, a.ldc2)))) return false;
   if (a.mask && (a.vecM != 4 || a.mask_rows < a.M || a.C2)) return false;
   const int ku = a.K % 128 == 0 ? 8 : a.K < 128 ? (a.K + 15) / 16 : 0;
   if (ku == 0) return false;

@@ -153,6 +153,37 @@ def test_dw_of_few_rows_against_fp64(gcn, dev, rows, k, n, bf16):
     A.free()
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("k,n", [(3, 5), (4, 4), (5, 16), (6, 7), (7, 33), (18, 50), (50, 50), (50, 7), (63, 64), (66, 17), (127, 130), (128, 41)])
+def test_dense_rows_that_start_on_any_word(gcn, dev, k, n, bf16):
+    """H W with rows of every alignment on both sides: the last request of a row of H ends with the row (NaN follows), the
+    last columns of a row of the result leave what follows as it was."""
+    import torch
+    rng = np.random.default_rng(10 * k + n)
+    rows = 1003
+    X = rng.standard_normal((rows, k)).astype(np.float32)
+    if bf16:
+        X = bf16_round(X)
+    W = rng.standard_normal((k, n)).astype(np.float32)
+    bias = rng.standard_normal(n).astype(np.float32)
+    X64, W64 = X.astype(np.float64), W.astype(np.float64)
+    ref, bound = X64 @ W64 + bias, np.abs(X64) @ np.abs(W64) + np.abs(bias)
+    tdt = torch.bfloat16 if bf16 else torch.float32
+    for off, pad in [(0, 0), (1, 0), (2, 2), (0, 3), (1, 1)]:
+        Xf = torch.full((rows * (k + pad) + off,), float("nan"), dtype=tdt, device=dev)
+        Yf = torch.full((rows * (n + pad) + off,), float("nan"), dtype=tdt, device=dev)
+        Xd = Xf[off:].view(rows, k + pad)[:, :k]
+        Yd = Yf[off:].view(rows, n + pad)[:, :n]
+        Xd.copy_(to_dev(X, dev, bf16))
+        say(f"dense rows {k}x{n} bf16={bf16} off={off} pad={pad}")
+        gcn.gcn_dense_fwd(Xd, to_dev(W, dev), Yd, bias=to_dev(bias, dev))
+        torch.cuda.synchronize()
+        check_bound(to_np(Yd), ref, bound, TOL_BF16 if bf16 else TOL_F32, what=f"dense {k}x{n} off={off} pad={pad}")
+        assert bool(torch.isnan(Yf[:off].float()).all())
+        if pad and (n + pad) % 4:
+            assert bool(torch.isnan(Yf[off:].view(rows, n + pad)[:, n:].float()).all()), "wrote outside the n columns"
+
+
 # ---- device memory kept between calls ------------------------------------------------------------------------------
 
 def test_builds_in_reused_memory_give_the_same_arrays(gcn, dev):
