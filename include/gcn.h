@@ -31,6 +31,8 @@
  *    builds an execution plan (a re-sorted copy of the matrix, 8 bytes per stored entry plus
  *    padding, kept in the handle until gcn_csr_free), which allocates and waits for the
  *    stream.  Later calls of that width class reuse the plan.
+ *  - Device memory of freed handles and of finished calls is kept for later calls of this process, at most 1/64 of the
+ *    device's memory; it goes back to the runtime when an allocation of the library fails or it lies unused.
  *  - Sizes: vertex ids and n_global lie below 2^31, edges + rows of a build below 2^32; dense buffers may
  *    run past 2^32 bytes and 2^31 elements (row offsets are 64-bit).  A size that a kernel cannot take is
  *    an error (GCN_EINVAL), never a truncated result.
