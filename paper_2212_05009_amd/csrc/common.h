@@ -338,6 +338,9 @@ struct GemmEpilogue {
   int64_t ldc2 = 0;
   int max_blocks = 0;            // > 0: a kernel with one workgroup per compute unit launches at most this many
   bool b_trans = false;          // B is stored [N x K] (ldb >= K): the product is A B^T
+  // the rows of C (and C2) may be written up to the next multiple of 16 bytes where their pitch reaches that far: buffers
+  // of the library and those of the _ld calls; else what follows column N belongs to the caller
+  bool c_rows_padded = false;
 };
 // true when gemm_nn runs this product on the kernel that occupies whole compute units, one workgroup each, and
 // therefore honours GemmEpilogue::max_blocks (the rest of the chip is left to a kernel on another stream)

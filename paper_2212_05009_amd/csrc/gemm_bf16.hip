@@ -8,7 +8,7 @@
 // sixteen times the fp32 matrix rate the kernel is a streaming kernel: it is bound by reading A and
 // writing C.
 //
-// Shapes: N <= 256 (N not a multiple of 16 only where the rows of C are padded to the store width), K = 32, 64,
+// Shapes: N <= 256 (N not a multiple of 16 only where the rows of C are pitched to the store width), K = 32, 64,
 // 128, 256 with 16-byte requests or any K <= 128 with 8-byte requests (rows of A aligned accordingly), W (as bf16)
 // within 128 KB of LDS.  Everything else stays on the fp32 path.
 #include <stdlib.h>
@@ -30,6 +30,7 @@ struct NnBf16Args {
   int64_t M; int N; int K;
   const float* bias; int relu; const bf16_t* mask; int64_t ldmask; bf16_t* C2; int64_t ldc2;
   int trans;              // W is stored [N x K]
+  int endC;               // nothing beyond column N of C and C2 may be written
   int wide_requests;      // rows of A aligned to 16 bytes and K in {32, 64, 128, 256}: 16-byte requests, 16x16x32 MFMA
 };
 
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
   constexpr bool kPair = NT % 2 == 0;
   // columns are stored (and mask values read) in groups of 8 (pairs) or 4; groups that start at or past N rounded
   // up to the group width are skipped, the last kept group may reach into the padding of the row (the host checks
-  // that the rows are that long)
+  // that the rows are that long), or is stored one by one where that padding is not the library's to write (endC)
   const int n_up = kPair ? (a.N + 7) & ~7 : (a.N + 3) & ~3;
   extern __shared__ u32x4 lds_bf16[];                 // [k step][column tile][lane]: LV values of W as bf16
   Raw* Wl = reinterpret_cast<Raw*>(lds_bf16);
@@ -161,6 +162,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 
     if (m < a.M) {
       u32x2 out[NT], out2[SAVE ? NT : 1];
+      auto store_tail = [&](bf16_t* row, int n, const u32x2& v) {         // columns n .. n + 3 of the row that exist
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (n + r < a.N) row[n + r] = (bf16_t)(v[r / 2] >> (16 * (r % 2)));
+      };
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const int n = kPair ? 32 * (t / 2) + 8 * q + 4 * (t % 2) : t * 16 + 4 * q;
@@ -181,6 +187,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
         for (int j = 0; j < NT / 2; ++j) {
           const int n = 32 * j + 8 * q;
           if (n >= n_up) continue;
+          if (a.endC && n + 8 > a.N) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              if constexpr (SAVE) store_tail(a.C2 + m * a.ldc2, n + 4 * i, out2[2 * j + i]);
+              store_tail(a.C + m * a.ldc, n + 4 * i, out[2 * j + i]);
+            }
+            continue;
+          }
           if constexpr (SAVE)
             *reinterpret_cast<u32x4*>(a.C2 + m * a.ldc2 + n) = u32x4{out2[2 * j][0], out2[2 * j][1], out2[2 * j + 1][0], out2[2 * j + 1][1]};
           *reinterpret_cast<u32x4*>(a.C + m * a.ldc + n) = u32x4{out[2 * j][0], out[2 * j][1], out[2 * j + 1][0], out[2 * j + 1][1]};
@@ -190,6 +204,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
         for (int t = 0; t < NT; ++t) {
           const int n = t * 16 + 4 * q;
           if (n >= n_up) continue;
+          if (a.endC && n + 4 > a.N) {
+            if constexpr (SAVE) store_tail(a.C2 + m * a.ldc2, n, out2[t]);
+            store_tail(a.C + m * a.ldc, n, out[t]);
+            continue;
+          }
           if constexpr (SAVE) *reinterpret_cast<u32x2*>(a.C2 + m * a.ldc2 + n) = out2[t];
           *reinterpret_cast<u32x2*>(a.C + m * a.ldc + n) = out[t];
         }
@@ -424,7 +443,8 @@ int gemm_nn_bf16(const void* A, int64_t lda, const float* W, int64_t ldw, void* 
                  const GemmEpilogue& epi, hipStream_t s) {
   NnBf16Args a{(const bf16_t*)A, lda, W, ldw, (bf16_t*)C, ldc, M, N, K,
                epi.bias, epi.relu, (const bf16_t*)epi.mask, epi.ldmask, (bf16_t*)epi.C2, epi.ldc2,
-               epi.b_trans ? 1 : 0, wide_requests(A, lda, K) ? 1 : 0};
+               epi.b_trans ? 1 : 0, N % (nn_tiles_bf16(N) % 2 == 0 ? 8 : 4) != 0 && !epi.c_rows_padded ? 1 : 0,
+               wide_requests(A, lda, K) ? 1 : 0};
   switch (nn_tiles_bf16(N)) {
     case 1: return launch_k<1>(a, s);
     case 2: return launch_k<2>(a, s);

@@ -211,9 +211,10 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(NT <
 // ---- the same product without a single data-dependent branch ----------------------------------------
 // For operands whose rows start on a 4-byte word, K up to 128 (KU = ceil(K / 16) k steps, the
 // whole row in one request batch, a tail of the row cleared by bit masks) or a multiple of 128 (KU = 8), N up to 256 and a
-// mask that covers every row.  Rows on 16 bytes (bf16: 8) may be read and written up to the next multiple of 4 elements;
-// in other rows the request that would pass the end is moved back to end with the row and its elements are shifted into
-// place, and the last columns of the result are stored one by one.  Measured, 500 K x 50 x 50 in contiguous rows (200
+// mask that covers every row.  Rows on 16 bytes (bf16: 8) may be read up to the next multiple of 4 elements, and written
+// that far where their owner allows it (GemmEpilogue::c_rows_padded); in other rows the request that would pass the end is
+// moved back to end with the row and its elements are shifted into place, and the last columns of the result are stored
+// one by one.  Measured, 500 K x 50 x 50 in contiguous rows (200
 // bytes): general kernel 128 us, this one 69 us.  Every load is an
 // unconditional 16-byte (bf16: 8-byte) request - rows beyond M are clamped to the last row and dropped at
 // the store - so the compiler can keep the next step's operand loads in flight across the MFMAs of the
@@ -465,7 +466,7 @@ static bool nn_fast(NnDirectArgs a, hipStream_t s, int* rc) {
   auto words = [](const void* p, int64_t ld) { return ((uintptr_t)p % 4) == 0 && (ld * (int64_t)sizeof(T)) % 4 == 0; };
   a.endA = a.vecA != 4;
   if (a.endA && (a.K < 4 || !words(a.A, a.lda) || (a.K * sizeof(T)) % 4 != 0)) return false;
-  a.endC = a.vecC != 4 || (a.C2 && a.vecC2 != 4);
+  a.endC |= a.vecC != 4 || (a.C2 && a.vecC2 != 4);
   if (a.endC && (!words(a.C, a.ldc) || (a.C2 && !words(a.C2, a.ldc2)))) return false;
   if (a.mask && (a.vecM != 4 || a.mask_rows < a.M || a.C2)) return false;
   const int ku = a.K % 128 == 0 ? 8 : a.K < 128 ? (a.K + 15) / 16 : 0;
@@ -516,7 +517,8 @@ int gemm_nn_direct(const void* A, int64_t lda, const float* W, int64_t ldw, void
   auto vec_of = [&](const void* p, int64_t ld) { return (p && (ld % 4) == 0 && ((uintptr_t)p % (4 * es)) == 0) ? 4 : 1; };
   NnDirectArgs a{A, lda, W, ldw, C, ldc, M, N, K, vec_of(A, lda), vec_of(C, ldc), vec_of(epi.C2, epi.ldc2),
                  vec_of(epi.mask, epi.ldmask),
-                 epi.bias, epi.relu, epi.mask, epi.ldmask, epi.mask_rows, epi.C2, epi.ldc2, epi.b_trans ? 1 : 0};
+                 epi.bias, epi.relu, epi.mask, epi.ldmask, epi.mask_rows, epi.C2, epi.ldc2, epi.b_trans ? 1 : 0,
+                 0, N % 4 != 0 && !epi.c_rows_padded};
   return dtype == GCN_BF16 ? nn_dispatch<bf16_t>(a, s) : nn_dispatch<float>(a, s);
 }
 

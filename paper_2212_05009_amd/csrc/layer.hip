@@ -204,6 +204,7 @@ static int layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
         sp.y_rows_padded = true;            // a pitch of the outputs beyond their width comes from the _ld call
         GemmEpilogue epi;
         epi.bias = bias; epi.relu = relu; epi.C2 = Z; epi.ldc2 = ldz;
+        epi.c_rows_padded = true;
         const bool pipelined = side_chunks() > 0 && overlap_worthwhile(A->nr, A->nnz, d_in) && !spmm_panel_wanted(sp) &&
                                gemm_nn_limits_blocks(AH, ldAH, A->nr, d_out, d_in, dtype);
         if (!pipelined) {
@@ -237,6 +238,7 @@ static int layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
       void* P = ws.take((size_t)A->nc * ldp * es);
       if (pass) {
         GemmEpilogue epi;
+        epi.c_rows_padded = true;
         GCN_TRY(gemm_nn(H, ldh, W, d_out, P, ldp, A->nc, d_out, d_in, dtype, epi, s));
         SpmmArgs sp{A->rowptr, A->col, A->val, &A->sched, A->nr, A->nc, A->nnz, false, A->nr, P, ldp, Hout, ldo, Z, ldz,
                     d_out, dtype, relu ? GCN_EPI_RELU : GCN_EPI_NONE, bias, nullptr, 0};
@@ -326,10 +328,11 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
           GemmEpilogue epi;
           epi.mask = Zprev; epi.ldmask = ldzp; epi.mask_rows = Zprev ? A->nr : 0;
           epi.b_trans = true;                // W^T
+          epi.c_rows_padded = true;
           GCN_TRY(gemm_nn(T, ldt, W, d_out, dH, lddh, A->nr, d_in, d_out, dtype, epi, s));
           if (A->nh > 0) {
             GemmEpilogue plain;
-            plain.b_trans = true;
+            plain.b_trans = plain.c_rows_padded = true;
             GCN_TRY(gemm_nn((const char*)T + (size_t)A->nr * ldt * es, ldt, W, d_out, (char*)dH + (size_t)A->nr * lddh * es, lddh,
                             A->nh, d_in, d_out, dtype, plain, s));
           }
@@ -352,7 +355,7 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
                             gemm_tn_limits_blocks(AH_saved, ldah, G, ldg, A->nr, d_in, d_out, dtype);
         if (dH) {
           GemmEpilogue epi;
-          epi.b_trans = true;
+          epi.b_trans = epi.c_rows_padded = true;
           GCN_TRY(gemm_nn(G, ldg, W, d_out, Q, ldq, A->nr, d_in, d_out, dtype, epi, s));
           if (beside) {        // after Q = G W^T, which wants the matrix pipes of every compute unit itself
             GCN_TRY(side.fork(Am, s));

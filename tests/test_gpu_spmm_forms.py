@@ -169,19 +169,20 @@ def test_dense_rows_that_start_on_any_word(gcn, dev, k, n, bf16):
     X64, W64 = X.astype(np.float64), W.astype(np.float64)
     ref, bound = X64 @ W64 + bias, np.abs(X64) @ np.abs(W64) + np.abs(bias)
     tdt = torch.bfloat16 if bf16 else torch.float32
-    for off, pad in [(0, 0), (1, 0), (2, 2), (0, 3), (1, 1)]:
-        Xf = torch.full((rows * (k + pad) + off,), float("nan"), dtype=tdt, device=dev)
-        Yf = torch.full((rows * (n + pad) + off,), float("nan"), dtype=tdt, device=dev)
-        Xd = Xf[off:].view(rows, k + pad)[:, :k]
-        Yd = Yf[off:].view(rows, n + pad)[:, :n]
+    # the last three: result rows on 16 bytes, with a whole request of room behind column n and without, beside operands of
+    # either kind
+    for off, px, py in [(0, 0, 0), (1, 0, 0), (2, 2, 2), (0, 3, 3), (1, 1, 1), (0, 0, -n % 8 + 8), (0, -k % 8, -n % 8), (0, -k % 8, -n % 4)]:
+        Xf = torch.full((rows * (k + px) + off,), float("nan"), dtype=tdt, device=dev)
+        Yf = torch.full((rows * (n + py) + off,), float("nan"), dtype=tdt, device=dev)
+        Xd = Xf[off:].view(rows, k + px)[:, :k]
+        Yd = Yf[off:].view(rows, n + py)[:, :n]
         Xd.copy_(to_dev(X, dev, bf16))
-        say(f"dense rows {k}x{n} bf16={bf16} off={off} pad={pad}")
+        say(f"dense rows {k}x{n} bf16={bf16} off={off} pads={px},{py}")
         gcn.gcn_dense_fwd(Xd, to_dev(W, dev), Yd, bias=to_dev(bias, dev))
         torch.cuda.synchronize()
-        check_bound(to_np(Yd), ref, bound, TOL_BF16 if bf16 else TOL_F32, what=f"dense {k}x{n} off={off} pad={pad}")
+        check_bound(to_np(Yd), ref, bound, TOL_BF16 if bf16 else TOL_F32, what=f"dense {k}x{n} off={off} pads={px},{py}")
         assert bool(torch.isnan(Yf[:off].float()).all())
-        if pad and (n + pad) % 4:
-            assert bool(torch.isnan(Yf[off:].view(rows, n + pad)[:, n:].float()).all()), "wrote outside the n columns"
+        assert bool(torch.isnan(Yf[off:].view(rows, n + py)[:, n:].float()).all()), "wrote outside the n columns"
 
 
 # ---- device memory kept between calls ------------------------------------------------------------------------------
