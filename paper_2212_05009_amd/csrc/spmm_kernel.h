@@ -410,6 +410,7 @@ __global__ __launch_bounds__(256) void k_spmm_hub_finish(SpmmK a) {
 struct SpmmProf {
   int kind; int dtype; int64_t rows, nnz; double alg, touched, flops;
   int row_chunk = -1, row_chunk_n = 1;   // rows Schedule::chunk_row[row_chunk .. row_chunk + row_chunk_n); -1: all rows
+  int64_t whole_nnz = 0;                 // entries of the whole matrix, also for a range of its rows
 };
 
 // Entries each lane group should get before a row is shared by more groups (GCN_SPMM_EPG overrides, for
@@ -426,9 +427,11 @@ template <typename T, int V, int LPR, int NV>
 static int launch_l(SpmmK& k, const Schedule* sc, const SpmmProf& pf, bool narrow, hipStream_t s) {
   constexpr int G = 64 / LPR;
   // A product too small to fill the chip is bound by the chain of gathers of a row: its rows are shared by more groups.
+  // (by the whole matrix: the sharing sets the order of a row's additions, which may not depend on how many launches the
+  // product is made of)
   int epg = tune().spmm_epg > 0 ? tune().spmm_epg : kEntriesPerGroup;
   if (tune().spmm_epg <= 0)
-    while (epg > kFewestPerGroup && pf.nnz / epg * k.S < (int64_t)kFullWaves * G) epg >>= 1;
+    while (epg > kFewestPerGroup && pf.whole_nnz / epg * k.S < (int64_t)kFullWaves * G) epg >>= 1;
   // bins of the ordinary rows: class c holds lengths in [2^(31-c), 2^(32-c)), class 32 empty rows
   int n_bins = 0;
   int64_t waves = 0;

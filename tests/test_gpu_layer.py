@@ -339,6 +339,47 @@ def test_results_do_not_depend_on_the_second_stream(gcn, dev, hubs, directed_blo
             gcn.gcn_debug_set_tuning(name, None)
 
 
+@pytest.fixture(scope="module")
+def middle(gcn, dev):
+    """12000 rows of about 30 entries: chosen by the entries of a launch, a row's lane groups would differ between the whole
+    product and its row ranges."""
+    rng = np.random.default_rng(41)
+    n, m = 12000, 175000
+    u = rng.integers(0, n, m); v = rng.integers(0, n, m)
+    return Case(gcn, dev, np.r_[u, v], np.r_[v, u], n)
+
+
+@pytest.mark.parametrize("d_in,d_out", [(100, 128), (128, 192), (72, 64)])
+def test_middle_sized_block_does_not_depend_on_the_second_stream(gcn, dev, middle, d_in, d_out):
+    import torch
+    og, A = middle.og, middle.A
+    H, W, G, Zp, b = _inputs(og, d_in, d_out, False, 78)
+    Hd, Wd, Gd, Zpd, bd = to_dev(H, dev), to_dev(W, dev), to_dev(G, dev), to_dev(Zp, dev), to_dev(b, dev)
+    for name, v in (("GCN_GEMM_REGW", 2), ("GCN_GEMM_TN_LDS", 2)):
+        gcn.gcn_debug_set_tuning(name, v)
+    try:
+        got = {}
+        for chunks in (0, 2, 4, 8):
+            gcn.gcn_debug_set_tuning("GCN_OVERLAP", 2 if chunks else 0)
+            gcn.gcn_debug_set_tuning("GCN_OVERLAP_CHUNKS", chunks)
+            Hout = torch.empty(og.nr, d_out, device=dev); Z = torch.empty_like(Hout)
+            AH = torch.empty(og.nr, d_in, device=dev)
+            say(f"chunks={chunks} layer_fwd nr={og.nr} {d_in}->{d_out}")
+            gcn.gcn_layer_fwd(A, Hd, Wd, Hout, act=gcn.ACT_RELU, bias=bd, Z=Z, AH_save=AH)
+            dW = torch.empty(d_in, d_out, device=dev)
+            dH = torch.empty(og.nc, d_in, device=dev)
+            say(f"chunks={chunks} layer_bwd nr={og.nr} {d_in}->{d_out}")
+            gcn.gcn_layer_bwd(A, Hd, Wd, Gd, dW, dH=dH, Zprev=Zpd, AH_saved=AH)
+            torch.cuda.synchronize()
+            got[chunks] = [to_np(t) for t in (Hout, Z, AH, dH)]
+        bad = [f"{what} with {c} row ranges" for c in (2, 4, 8)
+               for a, x, what in zip(got[0], got[c], ("Hout", "Z", "AH_save", "dH")) if not np.array_equal(a, x)]
+        assert not bad, bad
+    finally:
+        for name in ("GCN_OVERLAP", "GCN_OVERLAP_CHUNKS", "GCN_GEMM_REGW", "GCN_GEMM_TN_LDS"):
+            gcn.gcn_debug_set_tuning(name, None)
+
+
 # ----------------------------------------------------------------------------- softmax cross-entropy
 @pytest.mark.parametrize("d_in,d_out", [(128, 41), (41, 128), (256, 47), (200, 130), (130, 200)])
 def test_layer_with_the_column_sweep(gcn, dev, er, hubs, directed_block, d_in, d_out):
