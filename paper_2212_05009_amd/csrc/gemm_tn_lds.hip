@@ -13,6 +13,8 @@
 // i.e. both operands are read along a row of the chunk, consecutive lanes at consecutive addresses: no transposition
 // anywhere.  The two halves of a wavefront read rows k and k + 1, 1 KB apart; odd rows are stored with their
 // 32-column tiles swapped in pairs (the copy fetches quad q ^ 8), so the halves fall on different banks.
+#include <algorithm>
+
 #include "common.h"
 
 namespace gcn {
@@ -24,6 +26,7 @@ struct TnLdsArgs {
   int64_t Kd; int M; int N; int64_t rows_per_split;
   int wm, wn;          // wavefront grid, wm * wn = 4
   int mblocks;         // blocks of 256 columns of A
+  int nsplit;
   float* partial;      // [nsplit][M * N]
 };
 
@@ -41,8 +44,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int mb = (int)blockIdx.y % a.mblocks, nb = (int)blockIdx.y / a.mblocks;
   const int m0 = 256 * mb, n0 = 256 * nb;
   const int mwid = a.M - m0 < 256 ? a.M - m0 : 256, nwid = a.N - n0 < 256 ? a.N - n0 : 256;
-  const int64_t k_lo = (int64_t)blockIdx.x * a.rows_per_split;
-  const int64_t k_hi = k_lo + a.rows_per_split < a.Kd ? k_lo + a.rows_per_split : a.Kd;
   const int mt0 = (w / a.wn) * TMW, nt0 = (w % a.wn) * TNW;      // this wavefront's first tiles
   const float* __restrict__ A = a.A + m0;
   const float* __restrict__ B = a.B + n0;
@@ -65,14 +66,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
   };
 
-  floatx16 acc[TMW][TNW];
-#pragma unroll
-  for (int i = 0; i < TMW; ++i)
-#pragma unroll
-    for (int j = 0; j < TNW; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
   // a lane's element of tile t in the row of its half: the row (h), the tile as stored in a row of that parity, c
   int offA[TMW], offB[TNW];
 #pragma unroll
@@ -80,64 +73,82 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
   for (int j = 0; j < TNW; ++j) offB[j] = kTnlOpFloats + h * 256 + 32 * ((nt0 + j) ^ h) + c;
 
-  if (k_lo < k_hi) {
-    copy_chunk(k_lo, 0);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    int b = 0;
-    for (int64_t k = k_lo; k < k_hi; k += kTnlKC, b ^= 1) {
-      if (k + kTnlKC < k_hi) copy_chunk(k + kTnlKC, b ^ 1);
-      float* sb = S + b * kTnlBufFloats;
-      if (k + kTnlKC > k_hi) {                       // the last, shorter chunk of the sum: rows past the end count as zero
-        const int valid = (int)(k_hi - k);
-        for (int r = valid + w; r < kTnlKC; r += 4) {
-          *reinterpret_cast<float4*>(sb + r * 256 + 4 * lane) = float4{0.f, 0.f, 0.f, 0.f};
-          *reinterpret_cast<float4*>(sb + kTnlOpFloats + r * 256 + 4 * lane) = float4{0.f, 0.f, 0.f, 0.f};
-        }
-        __syncthreads();
-      }
-      float av[TMW], bv[TNW], an[TMW], bn[TNW];
+  // One split per workgroup, or several in turn where the launch is limited to fewer workgroups than there are splits: the
+  // number of splits sets the order of the sum, so it does not follow that limit.  (Several launches would not do: beside
+  // a sparse product only the first finds its compute units free.)
+  for (int split = (int)blockIdx.x; split < a.nsplit; split += (int)gridDim.x) {
+    const int64_t k_lo = (int64_t)split * a.rows_per_split;
+    const int64_t k_hi = k_lo + a.rows_per_split < a.Kd ? k_lo + a.rows_per_split : a.Kd;
+    floatx16 acc[TMW][TNW];
 #pragma unroll
-      for (int i = 0; i < TMW; ++i) an[i] = sb[offA[i]];
+    for (int i = 0; i < TMW; ++i)
 #pragma unroll
-      for (int j = 0; j < TNW; ++j) bn[j] = sb[offB[j]];
+      for (int j = 0; j < TNW; ++j)
 #pragma unroll
-      for (int p = 0; p < kTnlKC / 2; ++p) {
-#pragma unroll
-        for (int i = 0; i < TMW; ++i) av[i] = an[i];
-#pragma unroll
-        for (int j = 0; j < TNW; ++j) bv[j] = bn[j];
-        if (p + 1 < kTnlKC / 2) {
-#pragma unroll
-          for (int i = 0; i < TMW; ++i) an[i] = sb[offA[i] + 512 * (p + 1)];
-#pragma unroll
-          for (int j = 0; j < TNW; ++j) bn[j] = sb[offB[j] + 512 * (p + 1)];
-        }
-#pragma unroll
-        for (int i = 0; i < TMW; ++i)
-#pragma unroll
-          for (int j = 0; j < TNW; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
-      }
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    if (k_lo < k_hi) {
+      copy_chunk(k_lo, 0);
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
-    }
-  }
-
-  // register r of lane (c, h) holds C[m = 8 (r / 4) + 4 h + r % 4][n = c] of its tile
-  float* __restrict__ P = a.partial + (int64_t)blockIdx.x * a.M * a.N;
+      int b = 0;
+      for (int64_t k = k_lo; k < k_hi; k += kTnlKC, b ^= 1) {
+        if (k + kTnlKC < k_hi) copy_chunk(k + kTnlKC, b ^ 1);
+        float* sb = S + b * kTnlBufFloats;
+        if (k + kTnlKC > k_hi) {                       // the last, shorter chunk of the sum: rows past the end count as zero
+          const int valid = (int)(k_hi - k);
+          for (int r = valid + w; r < kTnlKC; r += 4) {
+            *reinterpret_cast<float4*>(sb + r * 256 + 4 * lane) = float4{0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<float4*>(sb + kTnlOpFloats + r * 256 + 4 * lane) = float4{0.f, 0.f, 0.f, 0.f};
+          }
+          __syncthreads();
+        }
+        float av[TMW], bv[TNW], an[TMW], bn[TNW];
 #pragma unroll
-  for (int i = 0; i < TMW; ++i)
+        for (int i = 0; i < TMW; ++i) an[i] = sb[offA[i]];
 #pragma unroll
-    for (int j = 0; j < TNW; ++j) {
-      const int n = n0 + 32 * (nt0 + j) + c;
-      if (32 * (nt0 + j) + c >= nwid) continue;
+        for (int j = 0; j < TNW; ++j) bn[j] = sb[offB[j]];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int ml = 32 * (mt0 + i) + 8 * (r / 4) + 4 * h + (r % 4);
-        if (ml < mwid) P[(int64_t)(m0 + ml) * a.N + n] = acc[i][j][r];
+        for (int p = 0; p < kTnlKC / 2; ++p) {
+#pragma unroll
+          for (int i = 0; i < TMW; ++i) av[i] = an[i];
+#pragma unroll
+          for (int j = 0; j < TNW; ++j) bv[j] = bn[j];
+          if (p + 1 < kTnlKC / 2) {
+#pragma unroll
+            for (int i = 0; i < TMW; ++i) an[i] = sb[offA[i] + 512 * (p + 1)];
+#pragma unroll
+            for (int j = 0; j < TNW; ++j) bn[j] = sb[offB[j] + 512 * (p + 1)];
+          }
+#pragma unroll
+          for (int i = 0; i < TMW; ++i)
+#pragma unroll
+            for (int j = 0; j < TNW; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
       }
     }
+
+    // (the store addresses are not worth registers over the whole loop)
+    int cs = c, hs = h;
+    asm volatile("" : "+v"(cs), "+v"(hs));
+    // register r of lane (c, h) holds C[m = 8 (r / 4) + 4 h + r % 4][n = c] of its tile
+    float* __restrict__ P = a.partial + (int64_t)split * a.M * a.N;
+#pragma unroll
+    for (int i = 0; i < TMW; ++i)
+#pragma unroll
+      for (int j = 0; j < TNW; ++j) {
+        const int n = n0 + 32 * (nt0 + j) + cs;
+        if (32 * (nt0 + j) + cs >= nwid) continue;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int ml = 32 * (mt0 + i) + 8 * (r / 4) + 4 * hs + (r % 4);
+          if (ml < mwid) P[(int64_t)(m0 + ml) * a.N + n] = acc[i][j][r];
+        }
+      }
+  }
 }
 
 namespace {
@@ -179,7 +190,8 @@ bool gemm_tn_lds_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int6
   return sh.tm * sh.tn >= 4 && M >= 64 && N >= 64;
 }
 
-static int tn_lds_splits(int64_t Kd, int M, int N, int max_blocks = 0) {
+// one workgroup per compute unit (its LDS is taken whole)
+static int tn_lds_splits(int64_t Kd, int M, int N) {
   static const int cus = [] {
     int dev = 0;
     hipDeviceProp_t p;
@@ -187,9 +199,7 @@ static int tn_lds_splits(int64_t Kd, int M, int N, int max_blocks = 0) {
       return p.multiProcessorCount;
     return 256;
   }();
-  // one workgroup per compute unit (its LDS is taken whole), or fewer: the rest is left to a concurrent kernel
-  int lim = tune().gemm_tn_lds_blocks > 0 && tune().gemm_tn_lds_blocks < cus ? tune().gemm_tn_lds_blocks : cus;
-  if (max_blocks > 0 && max_blocks < lim) lim = max_blocks;
+  const int lim = tune().gemm_tn_lds_blocks > 0 && tune().gemm_tn_lds_blocks < cus ? tune().gemm_tn_lds_blocks : cus;
   int64_t want = lim / tn_lds_blocks_mn(M, N);
   const int64_t max_by_k = ceil_div(Kd, 4 * kTnlKC);
   if (want > max_by_k) want = max_by_k;
@@ -204,12 +214,15 @@ int gemm_tn_lds_partials(const void* A, int64_t lda, const void* B, int64_t ldb,
                          int* nsplit_out, hipStream_t s, int max_blocks) {
   TnLdsShape sh;
   if (!tn_lds_shape(M < 256 ? M : 256, N < 256 ? N : 256, &sh)) return fail(GCN_EINVAL, "gemm_tn_lds: shape");
-  const int want = tn_lds_splits(Kd, M, N, max_blocks);
+  const int want = tn_lds_splits(Kd, M, N);
   const int64_t rps = round_up(ceil_div(Kd, want), kTnlKC);
   const int nsplit = (int)ceil_div(Kd, rps);            // every split holds at least one row
   *nsplit_out = nsplit;
-  TnLdsArgs a{(const float*)A, lda, (const float*)B, ldb, Kd, M, N, rps, sh.wm, sh.wn, (int)ceil_div(M, 256), partial};
-  dim3 grid((unsigned)nsplit, (unsigned)tn_lds_blocks_mn(M, N));
+  TnLdsArgs a{(const float*)A, lda, (const float*)B, ldb, Kd, M, N, rps, sh.wm, sh.wn, (int)ceil_div(M, 256), nsplit, partial};
+  // max_blocks: the rest of the compute units is left to a concurrent kernel
+  const int per_split = tn_lds_blocks_mn(M, N);
+  const int at_once = max_blocks > 0 ? std::min(nsplit, std::max(1, max_blocks / per_split)) : nsplit;
+  dim3 grid((unsigned)at_once, (unsigned)per_split);
 #define GCN_TNL(TM_, TN_)                                                                                       \
   if (sh.tm == TM_ && sh.tn == TN_) {                                                                           \
     auto kern = k_gemm_tn_lds<TM_, TN_>;                                                                        \

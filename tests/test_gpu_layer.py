@@ -342,7 +342,7 @@ def test_results_do_not_depend_on_the_second_stream(gcn, dev, hubs, directed_blo
 @pytest.fixture(scope="module")
 def middle(gcn, dev):
     """12000 rows of about 30 entries: chosen by the entries of a launch, a row's lane groups would differ between the whole
-    product and its row ranges."""
+    product and its row ranges; and the weight gradient is summed over more splits than a limited launch has workgroups."""
     rng = np.random.default_rng(41)
     n, m = 12000, 175000
     u = rng.integers(0, n, m); v = rng.integers(0, n, m)
@@ -371,9 +371,9 @@ def test_middle_sized_block_does_not_depend_on_the_second_stream(gcn, dev, middl
             say(f"chunks={chunks} layer_bwd nr={og.nr} {d_in}->{d_out}")
             gcn.gcn_layer_bwd(A, Hd, Wd, Gd, dW, dH=dH, Zprev=Zpd, AH_saved=AH)
             torch.cuda.synchronize()
-            got[chunks] = [to_np(t) for t in (Hout, Z, AH, dH)]
+            got[chunks] = [to_np(t) for t in (Hout, Z, AH, dW, dH)]
         bad = [f"{what} with {c} row ranges" for c in (2, 4, 8)
-               for a, x, what in zip(got[0], got[c], ("Hout", "Z", "AH_save", "dH")) if not np.array_equal(a, x)]
+               for a, x, what in zip(got[0], got[c], ("Hout", "Z", "AH_save", "dW", "dH")) if not np.array_equal(a, x)]
         assert not bad, bad
     finally:
         for name in ("GCN_OVERLAP", "GCN_OVERLAP_CHUNKS", "GCN_GEMM_REGW", "GCN_GEMM_TN_LDS"):
