@@ -67,11 +67,12 @@ struct NnArgs {
   const void* A; int64_t lda; const float* B; int64_t ldb; void* C; int64_t ldc;
   int64_t M; int N; int K; int vecA; int vecB;
   const float* bias; int relu; const void* mask; int64_t ldmask; int64_t mask_rows; void* C2; int64_t ldc2;
-  int trans;               // B is stored [N x K]
 };
 
 // WAVES_M x WAVES_N wavefronts; each owns TM x TN accumulator tiles of 32 x 32
-template <typename T, int BN, int WAVES_M, int WAVES_N>
+// TRANS: B is stored [N x K].  Its rows are then read along k, four lanes to the 64 bytes a row has in a step, and turned
+// while they are written to LDS, as the rows of A are; no copy of B^T is made.
+template <typename T, int BN, int WAVES_M, int WAVES_N, bool TRANS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_gemm_nn(NnArgs a) {
   static_assert(WAVES_M * WAVES_N == 4, "4 wavefronts per block");
   constexpr int TM = BM / WAVES_M / 32, TN = BN / WAVES_N / 32;
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   float ra[A_IT][4], rb[B_IT][4];
   // interior tiles of aligned operands take plain 16-byte loads; edges go element by element
   const bool a_in = a.vecA == 4 && m0 + BM <= a.M;
-  const bool b_in = a.vecB == 4 && n0 + BN <= a.N && !a.trans;
+  const bool b_in = a.vecB == 4 && n0 + BN <= a.N;
   auto fetch = [&](int k0) {
     const bool k_in = k0 + BK <= a.K;
     if (a_in && k_in) {
@@ -121,20 +122,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 #pragma unroll
       for (int it = 0; it < B_IT; ++it) {
         const int q = it * 256 + t;
-        if (B_IT * 256 == BK * BN / 4 || q < BK * BN / 4)
-          load4_fast<float>(a.B + (int64_t)(k0 + q / (BN / 4)) * a.ldb + n0 + (q % (BN / 4)) * 4, rb[it]);
+        if (B_IT * 256 == BK * BN / 4 || q < BK * BN / 4) {
+          if constexpr (TRANS) load4_fast<float>(a.B + (int64_t)(n0 + q / (BK / 4)) * a.ldb + k0 + (q % (BK / 4)) * 4, rb[it]);
+          else load4_fast<float>(a.B + (int64_t)(k0 + q / (BN / 4)) * a.ldb + n0 + (q % (BN / 4)) * 4, rb[it]);
+        }
       }
     } else {
 #pragma unroll
       for (int it = 0; it < B_IT; ++it) {
-        const int q = it * 256 + t;                 // group id: k = q / (BN/4), n-quad = q % (BN/4)
-        const int k = q / (BN / 4);
-        const int nq = (q % (BN / 4)) * 4;
-        if (a.trans) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            rb[it][i] = (k < BK && k0 + k < a.K && n0 + nq + i < a.N) ? a.B[(int64_t)(n0 + nq + i) * a.ldb + k0 + k] : 0.f;
-        } else if (k < BK && k0 + k < a.K) load4<float>(a.B + (int64_t)(k0 + k) * a.ldb, n0 + nq, a.N, a.vecB, rb[it]);
+        const int q = it * 256 + t;                 // group id: k = q / (BN/4), n-quad = q % (BN/4); TRANS: n, k-quad
+        const int row = TRANS ? n0 + q / (BK / 4) : k0 + q / (BN / 4), rows = TRANS ? a.N : a.K;
+        const int c = TRANS ? k0 + (q % (BK / 4)) * 4 : n0 + (q % (BN / 4)) * 4, cols = TRANS ? a.K : a.N;
+        if (q < BK * BN / 4 && row < rows) load4<float>(a.B + (int64_t)row * a.ldb, c, cols, a.vecB, rb[it]);
         else { rb[it][0] = rb[it][1] = rb[it][2] = rb[it][3] = 0.f; }
       }
     }
@@ -150,8 +149,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 #pragma unroll
     for (int it = 0; it < B_IT; ++it) {
       const int q = it * 256 + t;
-      const int k = q / (BN / 4), nq = (q % (BN / 4)) * 4;
-      if (k < BK) *reinterpret_cast<float4*>(&Bs[buf][k * LDB_S + nq]) = make_float4(rb[it][0], rb[it][1], rb[it][2], rb[it][3]);
+      if (q >= BK * BN / 4) continue;
+      if constexpr (TRANS) {
+        // (4 lanes of a row write 4 rows of 4 apart, 16 rows of B side by side: 64 different banks)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) Bs[buf][((q % (BK / 4)) * 4 + i) * LDB_S + q / (BK / 4)] = rb[it][i];
+      } else {
+        *reinterpret_cast<float4*>(&Bs[buf][q / (BN / 4) * LDB_S + (q % (BN / 4)) * 4]) = make_float4(rb[it][0], rb[it][1], rb[it][2], rb[it][3]);
+      }
     }
   };
 
@@ -225,7 +230,7 @@ static int pick_vec(const void* p, int64_t ld, int64_t extent, size_t es) {
   return v;
 }
 
-template <typename T>
+template <typename T, bool TRANS>
 static int gemm_nn_t(NnArgs& a, hipStream_t s) {
   const int64_t gm = ceil_div(a.M, BM);
   if (gm * 256 >= ((int64_t)1 << 32)) return fail(GCN_EINVAL, "gemm: too many rows for one launch");
@@ -234,11 +239,11 @@ static int gemm_nn_t(NnArgs& a, hipStream_t s) {
   ProfScope ps(GCN_K_GEMM_NN, s, a.N, sizeof(T) == 2 ? GCN_BF16 : GCN_F32, a.M, a.K, nb, nb,
                2.0 * (double)a.M * a.N * a.K);
   if (a.N <= 32) {
-    k_gemm_nn<T, 32, 4, 1><<<dim3((unsigned)gm, (unsigned)ceil_div(a.N, 32)), 256, 0, s>>>(a);
+    k_gemm_nn<T, 32, 4, 1, TRANS><<<dim3((unsigned)gm, (unsigned)ceil_div(a.N, 32)), 256, 0, s>>>(a);
   } else if (a.N <= 64) {
-    k_gemm_nn<T, 64, 4, 1><<<dim3((unsigned)gm, (unsigned)ceil_div(a.N, 64)), 256, 0, s>>>(a);
+    k_gemm_nn<T, 64, 4, 1, TRANS><<<dim3((unsigned)gm, (unsigned)ceil_div(a.N, 64)), 256, 0, s>>>(a);
   } else {
-    k_gemm_nn<T, 128, 2, 2><<<dim3((unsigned)gm, (unsigned)ceil_div(a.N, 128)), 256, 0, s>>>(a);
+    k_gemm_nn<T, 128, 2, 2, TRANS><<<dim3((unsigned)gm, (unsigned)ceil_div(a.N, 128)), 256, 0, s>>>(a);
   }
   GCN_CHECK_LAUNCH();
   return GCN_OK;
@@ -273,9 +278,10 @@ int gemm_nn(const void* A, int64_t lda, const float* B, int64_t ldb, void* C, in
     return gemm_nn_direct(A, lda, B, ldb, C, ldc, M, N, K, dtype, epi, s);
   }
   NnArgs a{A, lda, B, ldb, C, ldc, M, N, K, pick_vec(A, lda, K, es), pick_vec(B, ldb, N, 4),
-           epi.bias, epi.relu, epi.mask, epi.ldmask, epi.mask_rows, epi.C2, epi.ldc2, epi.b_trans ? 1 : 0};
+           epi.bias, epi.relu, epi.mask, epi.ldmask, epi.mask_rows, epi.C2, epi.ldc2};
   if (dtype == GCN_BF16 && a.vecA == 2) a.vecA = 1;
-  return dtype == GCN_BF16 ? gemm_nn_t<bf16_t>(a, s) : gemm_nn_t<float>(a, s);
+  if (epi.b_trans) return dtype == GCN_BF16 ? gemm_nn_t<bf16_t, true>(a, s) : gemm_nn_t<float, true>(a, s);
+  return dtype == GCN_BF16 ? gemm_nn_t<bf16_t, false>(a, s) : gemm_nn_t<float, false>(a, s);
 }
 
 // ------------------------------------------------------------------------------------------

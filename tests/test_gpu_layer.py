@@ -339,6 +339,35 @@ def test_results_do_not_depend_on_the_second_stream(gcn, dev, hubs, directed_blo
             gcn.gcn_debug_set_tuning(name, None)
 
 
+# d_in x d_out, off: W starts `off` floats past a 16-byte boundary.  Rows of W as the kernels read them (d_out floats, several
+# tiles of d_in of them) that are whole 16-byte quads, end inside one, or start between two; short and long sums.
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("d_in,d_out,off", [(200, 200, 0), (512, 16, 0), (260, 15, 0), (300, 7, 0), (257, 33, 0), (130, 515, 0),
+                                            (602, 128, 1), (290, 68, 2), (64, 700, 0), (31, 900, 3), (256, 256, 0), (192, 256, 1),
+                                            (128, 200, 0), (64, 76, 2), (256, 64, 0), (100, 128, 1), (47, 50, 0), (1, 3, 0)])
+def test_products_with_w_transposed_in_place(gcn, dev, identity, d_in, d_out, off, bf16):
+    """dH = G W^T on a graph without edges, against fp64; 1237 rows are no whole number of any kernel's row tiles."""
+    import torch
+    og, A = identity.og, identity.A
+    rng = np.random.default_rng(1000 * d_in + d_out)
+    G = rng.standard_normal((og.nr, d_out)).astype(np.float32); H = rng.standard_normal((og.nr, d_in)).astype(np.float32)
+    W = rng.standard_normal((d_in, d_out)).astype(np.float32)
+    if bf16:
+        G, H, W = bf16_round(G), bf16_round(H), bf16_round(W)
+    Wf = torch.full((d_in * d_out + 4,), float("nan"), device=dev)
+    Wd = Wf[off:off + d_in * d_out].view(d_in, d_out)
+    Wd.copy_(to_dev(W, dev))
+    Hd, Gd = to_dev(H, dev, bf16), to_dev(G, dev, bf16)
+    tdt = torch.bfloat16 if bf16 else torch.float32
+    ref, bound = G.astype(np.float64) @ W.T.astype(np.float64), np.abs(G).astype(np.float64) @ np.abs(W).T
+    for mask in (False, True):
+        dW = torch.empty(d_in, d_out, device=dev); dH = torch.full((og.nr, d_in), float("nan"), dtype=tdt, device=dev)
+        say(f"G W^T {d_in}x{d_out} off={off} bf16={bf16} mask={mask}")
+        gcn.gcn_layer_bwd(A, Hd, Wd, Gd, dW, dH=dH, Zprev=Hd if mask else None)
+        torch.cuda.synchronize()
+        check_bound(to_np(dH), ref * (H > 0) if mask else ref, bound, TOL_BF16 if bf16 else TOL_F32, f"G W^T {d_in}x{d_out}")
+
+
 @pytest.fixture(scope="module")
 def middle(gcn, dev):
     """12000 rows of about 30 entries: chosen by the entries of a launch, a row's lane groups would differ between the whole
