@@ -23,6 +23,7 @@
 namespace gcn {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx4w __attribute__((ext_vector_type(4), aligned(4)));     // W starts on any word
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 struct RegwArgs {
@@ -48,20 +49,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const float* __restrict__ A = a.A;
   const float* __restrict__ Wg = a.W;
 
-  // this wavefront's panel of W as MFMA operands
-  const int64_t sk = a.trans ? 1 : a.ldw, sn = a.trans ? a.ldw : 1;
+  // This wavefront's panel of W as MFMA operands.  Of a W stored [N x K] a lane takes the four k of a step with one
+  // request (K is a whole number of them): word by word, every request would touch 32 rows for 8 bytes of each, and the
+  // panel alone cost 25 us (256 x 256).
   float wr[KS][4][2];
+  if (a.trans) {
 #pragma unroll
-  for (int s = 0; s < KS; ++s)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = 8 * s + 4 * h + i;
+    for (int s = 0; s < KS; ++s)
 #pragma unroll
       for (int ct = 0; ct < 2; ++ct) {
-        const int n = n0 + 32 * ct + c;
-        wr[s][i][ct] = k < a.K ? Wg[k * sk + n * sn] : 0.f;
+        const int k = 8 * s + 4 * h;
+        floatx4w v = floatx4w{0.f, 0.f, 0.f, 0.f};
+        if (k < a.K) v = *reinterpret_cast<const floatx4w*>(Wg + (n0 + 32 * ct + c) * a.ldw + k);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wr[s][i][ct] = v[i];
       }
-    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int k = 8 * s + 4 * h + i;
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) wr[s][i][ct] = k < a.K ? Wg[(int64_t)k * a.ldw + n0 + 32 * ct + c] : 0.f;
+      }
+  }
 
   float bias[2];
 #pragma unroll
