@@ -79,16 +79,37 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
   Raw* Wl = reinterpret_cast<Raw*>(lds_bf16);
   {
     bf16_t* wl = reinterpret_cast<bf16_t*>(lds_bf16);
-    for (int e = threadIdx.x; e < KL * KS * NT * 16; e += kThreads) {      // zero beyond K and N
-      // numbered along the rows of W as it is stored
-      const int k = a.trans ? e % (KL * KS) : e / (NT * 16), n = a.trans ? e / (KL * KS) : e % (NT * 16);
+    auto at = [&](int k, int n) {      // where W[k][n] goes; zero beyond K and N
       const int s = k / KS, q = (k % KS) / LV, el = k % LV;
       int t = n >> 4, cc = n & 15;
       if constexpr (kPair) {           // column n is entry 4 (n % 32 / 8) + n % 4 of tile 2 (n / 32) + (n % 8) / 4
         t = 2 * (n >> 5) + ((n & 7) >> 2);
         cc = 4 * ((n & 31) >> 3) + (n & 3);
       }
-      wl[(((s * NT + t) * 64 + q * 16 + cc) * LV) + el] = (k < a.K && n < a.N) ? f32_to_bf16(a.W[a.trans ? (int64_t)n * a.ldw + k : (int64_t)k * a.ldw + n]) : (bf16_t)0;
+      return ((s * NT + t) * 64 + q * 16 + cc) * LV + el;
+    };
+    if (a.trans) {
+      // Four k of a row of W with one request: they are neighbours in LDS too.  Four lanes read 64 bytes of a row, the
+      // next four the row after it, whose place is beside theirs; lanes along one row alone would meet on one bank.
+      typedef float floatx4w __attribute__((ext_vector_type(4), aligned(4)));
+      for (int e = threadIdx.x; e < KL * KS / 4 * NT * 16; e += kThreads) {
+        const int n = (e >> 2) % (NT * 16), k = 4 * ((e & 3) + 4 * ((e >> 2) / (NT * 16)));
+        const float* __restrict__ row = a.W + (int64_t)n * a.ldw + k;
+        floatx4w v = floatx4w{0.f, 0.f, 0.f, 0.f};
+        if (n < a.N) {
+          if (k + 4 <= a.K) v = *reinterpret_cast<const floatx4w*>(row);
+          else
+#pragma unroll
+            for (int i = 0; i < 3; ++i) v[i] = k + i < a.K ? row[i] : 0.f;
+        }
+        *reinterpret_cast<u32x2*>(wl + at(k, n)) = u32x2{(uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16),
+                                                         (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16)};
+      }
+    } else {
+      for (int e = threadIdx.x; e < KL * KS * NT * 16; e += kThreads) {
+        const int k = e / (NT * 16), n = e % (NT * 16);
+        wl[at(k, n)] = (k < a.K && n < a.N) ? f32_to_bf16(a.W[(int64_t)k * a.ldw + n]) : (bf16_t)0;
+      }
     }
   }
   __syncthreads();
