@@ -71,7 +71,9 @@ struct NnArgs {
 
 // WAVES_M x WAVES_N wavefronts; each owns TM x TN accumulator tiles of 32 x 32
 // TRANS: B is stored [N x K].  Its rows are then read along k, four lanes to the 64 bytes a row has in a step, and turned
-// while they are written to LDS, as the rows of A are; no copy of B^T is made.
+// while they are written to LDS, as the rows of A are; no copy of B^T is made.  Against a copy and the product with it:
+// 20 K x 200 x 200 fp32 61 -> 56 us, 100 K x 512 x 512 549 -> 544; the longest fp32 sums lose 2.5 % (500 K x 602 x 128 1.91 ->
+// 1.96 ms: a step takes half a line of every row of B), those of bf16 features nothing.
 template <typename T, int BN, int WAVES_M, int WAVES_N, bool TRANS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_gemm_nn(NnArgs a) {
   static_assert(WAVES_M * WAVES_N == 4, "4 wavefronts per block");

@@ -74,13 +74,28 @@ struct NnDirectArgs {
   int endA = 0, endC = 0;
 };
 
-// put(k, n, W[k][n]) for every element of the LDS copy of W (Kp x NP elements, zero beyond K and N), walked along the
-// rows of W as it is stored in global memory
+typedef float floatx4w __attribute__((ext_vector_type(4), aligned(4)));
+
+// put(k, n, W[k][n]) for every element of the LDS copy of W (Kp x NP elements, Kp a multiple of 16, zero beyond K and N).
+// W stored [N x K]: a lane takes four k of a row with one request, four lanes 64 bytes of it and the next four the row
+// after, whose places in LDS are other banks (lanes along one row alone meet on few banks, in the layout of whole quads on
+// one: 128 x 128, 4 K rows 22 us that way, 16 us this way).
 template <int NP, typename F>
 __device__ __forceinline__ void walk_w(const float* __restrict__ W, int64_t ldw, int trans, int K, int N, int Kp, int threads, F put) {
   if (trans) {
-    for (int n = threadIdx.x / 64; n < NP; n += threads / 64)
-      for (int k = threadIdx.x % 64; k < Kp; k += 64) put(k, n, (k < K && n < N) ? W[(int64_t)n * ldw + k] : 0.f);
+    for (int e = threadIdx.x; e < Kp / 4 * NP; e += threads) {
+      const int n = (e >> 2) % NP, k = 4 * ((e & 3) + 4 * ((e >> 2) / NP));
+      const float* __restrict__ row = W + (int64_t)n * ldw + k;
+      floatx4w v = floatx4w{0.f, 0.f, 0.f, 0.f};
+      if (n < N) {
+        if (k + 4 <= K) v = *reinterpret_cast<const floatx4w*>(row);
+        else
+#pragma unroll
+          for (int i = 0; i < 3; ++i) v[i] = k + i < K ? row[i] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) put(k + i, n, v[i]);
+    }
   } else {
     for (int e = threadIdx.x; e < Kp * NP; e += threads) {
       const int k = e / NP, n = e % NP;
@@ -220,7 +235,6 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(NT <
 // the store - so the compiler can keep the next step's operand loads in flight across the MFMAs of the
 // current one instead of waiting at every join of the general kernel's bounds checks.
 // (the global memory path takes 8- and 16-byte requests at any word address)
-typedef float floatx4w __attribute__((ext_vector_type(4), aligned(4)));
 template <typename T> __device__ __forceinline__ void vload4(const T* __restrict__ p, float (&o)[4]) {
   if constexpr (sizeof(T) == 4) {
     const floatx4w v = *reinterpret_cast<const floatx4w*>(p);
