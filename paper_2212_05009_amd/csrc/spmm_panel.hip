@@ -635,7 +635,8 @@ static int build_plan_impl(gcn_csr* A, bool transposed, int ns, int sw, int lpg,
   // ---- device side: sort the entries into the interleaved group streams
   PanelPlan* P = new (std::nothrow) PanelPlan();
   if (!P) return fail(GCN_ENOMEM, "panel plan: host allocation failed");
-  struct Guard { PanelPlan* p; ~Guard() { if (p) free_plan(p); } } guard{P};
+  CallScope sc(s);
+  struct Guard { PanelPlan* p; CallScope& sc; ~Guard() { if (p) free_plan(p, sc.quiesce()); } } guard{P, sc};
   P->transposed = transposed; P->ns = ns; P->sw = sw; P->lpg = lpg; P->cb_shift = cb_shift; P->part_len = part_len;
   P->nv_max = nv_max; P->n_panels = n_panels; P->n_rows = n; P->total_vrows = total_v;
   auto dev_alloc = [](void** p, size_t bytes) { return pool_alloc(p, bytes); };
@@ -654,7 +655,6 @@ static int build_plan_impl(gcn_csr* A, bool transposed, int ns, int sw, int lpg,
   GCN_TRY(dev_alloc((void**)&P->vlds, sizeof(int32_t) * (size_t)total_v));
   GCN_TRY(dev_alloc((void**)&P->order, sizeof(int32_t) * (size_t)n_panels));
   GCN_TRY(dev_alloc((void**)&P->ctr, sizeof(uint32_t) * 2 * kPanelLists));
-  CallScope sc(s);
   DevBuf d_vinfo, keys_a, keys_b, pay_a, pay_b, tmp, oseg, nb, seg;
   GCN_TRY(d_vinfo.alloc(sc, sizeof(uint32_t) * (size_t)total_v));
   GCN_TRY(keys_a.alloc(sc, sizeof(uint64_t) * (size_t)nnz));

@@ -1,0 +1,128 @@
+// Host-side checks of the device memory kept between calls, run without a GPU: this program brings its own HIP runtime
+// (device memory is host memory, kernels do nothing, waits and frees do what a check asks for) and links the library.
+//   host_memory <check>       exit 0: holds, 1: does not (with a line that says what)
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <atomic>
+#include <chrono>
+#include <condition_variable>
+#include <mutex>
+#include <set>
+#include <thread>
+
+#include "common.h"
+
+namespace {
+std::mutex mu;
+std::condition_variable cv;
+std::set<void*> live;                      // blocks the runtime has handed out
+size_t mallocs = 0, frees = 0;
+int current = 0;                           // the current device
+int syncs = 0, first_failing_sync = 1 << 30;
+bool hold_frees = false;                   // hipFree does not return while this is set
+int frees_waiting = 0;
+size_t device_bytes = (size_t)64 << 26;    // 1/64 of it: 64 MiB
+size_t malloc_limit = ~(size_t)0;          // bytes that can be out at once
+size_t out_bytes = 0;
+std::set<std::pair<void*, size_t>> sizes;
+
+hipError_t sync_result() { return ++syncs >= first_failing_sync ? hipErrorStreamCaptureUnsupported : hipSuccess; }
+}  // namespace
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+  std::lock_guard<std::mutex> l(mu);
+  if (out_bytes + n > malloc_limit) { *p = nullptr; return hipErrorOutOfMemory; }
+  if (posix_memalign(p, 4096, n) != 0) return hipErrorOutOfMemory;
+  memset(*p, 0, n < 65536 ? n : 65536);
+  ++mallocs; out_bytes += n;
+  live.insert(*p);
+  sizes.insert({*p, n});
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  std::unique_lock<std::mutex> l(mu);
+  if (hold_frees) {
+    ++frees_waiting;
+    cv.notify_all();
+    cv.wait(l, [] { return !hold_frees; });
+    --frees_waiting;
+  }
+  if (p) {
+    ++frees;
+    live.erase(p);
+    auto i = sizes.lower_bound({p, 0});
+    if (i != sizes.end() && i->first == p) { out_bytes -= i->second; sizes.erase(i); }
+    free(p);
+  }
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = calloc(1, n); return hipSuccess; }
+hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = current; return hipSuccess; }
+hipError_t hipSetDevice(int d) { current = d; return hipSuccess; }
+hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) {       // (the header's macro names the version)
+  memset(p, 0, sizeof(*p));
+  p->totalGlobalMem = device_bytes;
+  p->multiProcessorCount = 256;
+  return hipSuccess;
+}
+hipError_t hipDeviceSynchronize() { return sync_result(); }
+hipError_t hipStreamSynchronize(hipStream_t) { return sync_result(); }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "stand-in error"; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* n, hipStream_t* s) { *g = *b = dim3(1); *n = 0; *s = nullptr; return hipSuccess; }
+}
+
+using namespace gcn;
+
+#define CHECK(c)                                                                  \
+  do {                                                                            \
+    if (!(c)) { printf("line %d: %s\n", __LINE__, #c); fflush(stdout); _Exit(1); } \
+  } while (0)
+
+// A graph of n vertices without edges, made by hand (kernels do nothing here).
+static gcn_csr* make_handle(int n) {
+  gcn_csr* A = new gcn_csr();
+  A->n_global = A->nr = A->nc = A->nnz = n;
+  CHECK(pool_alloc((void**)&A->rowptr, sizeof(int64_t) * (n + 1)) == GCN_OK);
+  CHECK(pool_alloc((void**)&A->col, sizeof(int32_t) * n + kEntrySlack) == GCN_OK);
+  CHECK(pool_alloc((void**)&A->val, sizeof(float) * n + kEntrySlack) == GCN_OK);
+  for (int i = 0; i <= n; ++i) A->rowptr[i] = i;
+  A->sched.n_wave_rows = n;
+  for (int c = 32; c < 34; ++c) A->sched.class_begin[c] = n;      // class 31: one entry
+  return A;
+}
+
+// A column-sweep plan whose last wait fails may still be written: none of its arrays is kept for other calls.
+static void plan() {
+  gcn_csr* A = make_handle(512);
+  CHECK(gcn_debug_set_tuning("GCN_SPMM_PANEL", 1) == GCN_OK);
+  float *X = (float*)aligned_alloc(256, 512 * 32 * 4), *Y = (float*)aligned_alloc(256, 512 * 32 * 4);
+  const size_t before = live.size();
+  for (int which = 2; which <= 3; ++which) {       // (the first wait is for the row pointers: nothing is allocated yet)
+    syncs = 0; first_failing_sync = which;
+    CHECK(gcn_spmm(A, X, 32, 32, GCN_F32, Y, 32, GCN_EPI_NONE, nullptr, nullptr, 0, nullptr) == GCN_EHIP);
+    CHECK(syncs >= which);
+    CHECK(live.size() == before + 1);              // the handle's workspace
+  }
+  first_failing_sync = 1 << 30;
+  CHECK(gcn_spmm(A, X, 32, 32, GCN_F32, Y, 32, GCN_EPI_NONE, nullptr, nullptr, 0, nullptr) == GCN_OK);
+  CHECK(A->plans.size() == 1);
+  CHECK(gcn_csr_free(A) == GCN_OK);
+}
+
+int main(int argc, char** argv) {
+  const struct { const char* name; void (*run)(); } checks[] = {{"plan", plan}};
+  for (auto& c : checks)
+    if (argc > 1 && !strcmp(argv[1], c.name)) { c.run(); printf("%s holds\n", c.name); fflush(stdout); _Exit(0); }
+  printf("no such check\n");
+  return 2;
+}
