@@ -11,6 +11,9 @@
 //  * A block serves requests of at least 3/4 of its size, so what is held and not used stays small.
 //  * Bounded: at most 1/64 of the device's memory is kept (4.5 of 288 GB), least recently freed blocks go first; a block
 //    that lies unused over 256 later returns goes back to the runtime; a failed hipMalloc empties the pool and retries.
+//  * The lock covers the lists only.  hipFree, which waits for the device, runs outside it: a thread that gives blocks back
+//    holds up no other thread's calls, on this GPU or another.
+#include <condition_variable>
 #include <list>
 #include <map>
 #include <mutex>
@@ -33,10 +36,12 @@ struct DevicePool {
   std::multimap<size_t, BlockList::iterator> by_size;
   size_t held = 0, limit = 0;
   uint64_t returns = 0;
+  int leaving = 0;                                        // threads with blocks taken off the lists but not yet freed
 };
 
 struct Pool {
   std::mutex mu;
+  std::condition_variable left;                             // some DevicePool::leaving has fallen
   std::unordered_map<void*, std::pair<int, size_t>> live;   // block -> device, size
   DevicePool dev[kPoolDevices];
   std::vector<void*> pinned;                                // idle pinned host pages
@@ -47,13 +52,25 @@ Pool& pool() {
   return *p;
 }
 
-void drop(DevicePool& d, BlockList::iterator b) {
+// moves the oldest block from the lists to `gone` (under the lock; no allocation)
+void drop_oldest(DevicePool& d, BlockList& gone) {
+  BlockList::iterator b = d.by_age.begin();
   auto r = d.by_size.equal_range(b->bytes);
   for (auto i = r.first; i != r.second; ++i)
     if (i->second == b) { d.by_size.erase(i); break; }
   d.held -= b->bytes;
-  (void)hipFree(b->p);
-  d.by_age.erase(b);
+  gone.splice(gone.end(), d.by_age, b);
+}
+
+// frees what has been taken off the lists of d; called with the lock held, which is open while hipFree runs
+void free_gone(Pool& P, DevicePool& d, BlockList& gone, std::unique_lock<std::mutex>& lock) {
+  if (gone.empty()) return;
+  ++d.leaving;
+  lock.unlock();
+  for (const Block& b : gone) (void)hipFree(b.p);
+  lock.lock();
+  --d.leaving;
+  P.left.notify_all();
 }
 
 // sizes in steps of 1/8 of a power of two, so that requests of similar size share blocks
@@ -93,9 +110,12 @@ int pool_alloc(void** out, size_t bytes) {
     if (e == hipErrorOutOfMemory && pooled) {
       (void)hipGetLastError();
       {
-        std::lock_guard<std::mutex> lock(P.mu);
+        std::unique_lock<std::mutex> lock(P.mu);
         DevicePool& d = P.dev[device];
-        while (!d.by_age.empty()) drop(d, d.by_age.begin());
+        BlockList gone;
+        while (!d.by_age.empty()) drop_oldest(d, gone);
+        free_gone(P, d, gone, lock);
+        P.left.wait(lock, [&] { return d.leaving == 0; });      // what other threads are giving back counts too
       }
       e = hipMalloc(&p, want);
     }
@@ -117,9 +137,13 @@ int pool_alloc(void** out, size_t bytes) {
 void pool_free(void* p, bool idle) {
   if (!p) return;
   Pool& P = pool();
-  std::lock_guard<std::mutex> lock(P.mu);
+  std::unique_lock<std::mutex> lock(P.mu);
   auto i = P.live.find(p);
-  if (i == P.live.end()) { (void)hipFree(p); return; }
+  if (i == P.live.end()) {
+    lock.unlock();
+    (void)hipFree(p);
+    return;
+  }
   const int device = i->second.first;
   const size_t bytes = i->second.second;
   P.live.erase(i);
@@ -129,18 +153,30 @@ void pool_free(void* p, bool idle) {
     d.limit = hipGetDeviceProperties(&prop, device) == hipSuccess ? prop.totalGlobalMem / 64 : (size_t)1 << 30;
   }
   ++d.returns;
-  if (!idle || bytes > d.limit) { (void)hipFree(p); return; }
-  const size_t listed = d.by_age.size();
-  try {
-    d.by_age.push_back(Block{p, bytes, d.returns});
-    d.by_size.emplace(bytes, std::prev(d.by_age.end()));
-  } catch (const std::bad_alloc&) {
-    if (d.by_age.size() > listed) d.by_age.pop_back();
-    (void)hipFree(p);
+  BlockList gone;
+  bool kept = false;
+  if (idle && bytes <= d.limit) {
+    const size_t listed = d.by_age.size();
+    try {
+      d.by_age.push_back(Block{p, bytes, d.returns});
+      d.by_size.emplace(bytes, std::prev(d.by_age.end()));
+      d.held += bytes;
+      kept = true;
+    } catch (const std::bad_alloc&) {
+      if (d.by_age.size() > listed) d.by_age.pop_back();
+    }
+  }
+  if (kept) {
+    while (d.held > d.limit || d.by_age.front().freed_at + kIdleReturns < d.returns) drop_oldest(d, gone);
+    free_gone(P, d, gone, lock);
     return;
   }
-  d.held += bytes;
-  while (d.held > d.limit || d.by_age.front().freed_at + kIdleReturns < d.returns) drop(d, d.by_age.begin());
+  ++d.leaving;
+  lock.unlock();
+  (void)hipFree(p);
+  lock.lock();
+  --d.leaving;
+  P.left.notify_all();
 }
 
 // Pinned host pages: at most kMaxPinned are kept.

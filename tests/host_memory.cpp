@@ -119,8 +119,67 @@ static void plan() {
   CHECK(gcn_csr_free(A) == GCN_OK);
 }
 
+// A free that the runtime holds up, be it an eviction or a block whose work may still run, holds up no other thread's calls.
+static void lock() {
+  void *big[2], *small, *busy;
+  for (void*& b : big) CHECK(pool_alloc(&b, (size_t)40 << 20) == GCN_OK);
+  CHECK(pool_alloc(&small, 100000) == GCN_OK);
+  CHECK(pool_alloc(&busy, 100000) == GCN_OK);
+  pool_free(small);
+  pool_free(big[0]);
+  for (int round = 0; round < 2; ++round) {
+    { std::lock_guard<std::mutex> l(mu); hold_frees = true; }
+    std::thread giver([&] {
+      if (round == 0) pool_free(big[1]);           // over the limit: an older block leaves
+      else pool_free(busy, false);
+    });
+    {
+      std::unique_lock<std::mutex> l(mu);
+      CHECK(cv.wait_for(l, std::chrono::seconds(20), [] { return frees_waiting > 0; }));
+    }
+    std::atomic<bool> done{false};
+    std::thread other([&] {
+      void* p = nullptr;
+      CHECK(pool_alloc(&p, 5000) == GCN_OK);
+      pool_free(p);
+      CHECK(pool_alloc(&p, (size_t)20 << 20) == GCN_OK);
+      pool_free(p);
+      done = true;
+    });
+    for (int i = 0; i < 1000 && !done; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(10));
+    CHECK(done);
+    { std::lock_guard<std::mutex> l(mu); hold_frees = false; }
+    cv.notify_all();
+    giver.join();
+    other.join();
+  }
+}
+
+// Memory that runs out: kept blocks go back first, also those that another thread is giving back at that moment.
+static void exhausted() {
+  void *a, *b, *c = nullptr;
+  CHECK(pool_alloc(&a, (size_t)40 << 20) == GCN_OK);
+  CHECK(pool_alloc(&b, (size_t)40 << 20) == GCN_OK);
+  pool_free(a);
+  { std::lock_guard<std::mutex> l(mu); hold_frees = true; malloc_limit = (size_t)100 << 20; }
+  std::thread giver([&] { pool_free(b); });        // evicts a
+  {
+    std::unique_lock<std::mutex> l(mu);
+    CHECK(cv.wait_for(l, std::chrono::seconds(20), [] { return frees_waiting > 0; }));
+  }
+  int rc = -100;
+  std::thread taker([&] { rc = pool_alloc(&c, (size_t)90 << 20); });
+  std::this_thread::sleep_for(std::chrono::milliseconds(200));
+  { std::lock_guard<std::mutex> l(mu); hold_frees = false; }
+  cv.notify_all();
+  giver.join();
+  taker.join();
+  CHECK(rc == GCN_OK && c);
+  CHECK(pool_alloc(&a, (size_t)90 << 20) == GCN_ENOMEM);
+}
+
 int main(int argc, char** argv) {
-  const struct { const char* name; void (*run)(); } checks[] = {{"plan", plan}};
+  const struct { const char* name; void (*run)(); } checks[] = {{"plan", plan}, {"lock", lock}, {"exhausted", exhausted}};
   for (auto& c : checks)
     if (argc > 1 && !strcmp(argv[1], c.name)) { c.run(); printf("%s holds\n", c.name); fflush(stdout); _Exit(0); }
   printf("no such check\n");
