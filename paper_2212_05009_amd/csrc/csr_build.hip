@@ -518,8 +518,10 @@ int segment_boundaries(const uint64_t* keys, int64_t n, int shift, int64_t n_seg
 int ensure_workspace(gcn_csr* A, size_t bytes) {
   if (bytes <= A->ws_bytes) return GCN_OK;
   if (A->ws) {
+    int device = -1;
+    GCN_HIP(hipGetDevice(&device));
     GCN_HIP(hipDeviceSynchronize());
-    pool_free(A->ws);
+    pool_free(A->ws, device == A->device);      // (another device than the handle's was waited for: hipFree waits for the right one)
     A->ws = nullptr; A->ws_bytes = 0;
   }
   size_t want = (size_t)round_up((int64_t)bytes, 1 << 20);

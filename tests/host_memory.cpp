@@ -178,8 +178,24 @@ static void exhausted() {
   CHECK(pool_alloc(&a, (size_t)90 << 20) == GCN_ENOMEM);
 }
 
+// A workspace that grows while another device is current: the wait was for that device, so the old one is not kept.
+static void workspace() {
+  gcn_csr* A = make_handle(512);
+  CHECK(ensure_workspace(A, 1 << 20) == GCN_OK);
+  size_t f = frees;
+  CHECK(ensure_workspace(A, 3 << 20) == GCN_OK && frees == f);      // device 0 was waited for: kept
+  current = 1;
+  f = frees;
+  CHECK(ensure_workspace(A, 9 << 20) == GCN_OK && frees == f + 1);
+  current = 0;
+  f = frees;
+  first_failing_sync = 0;                                           // (a capture goes on): the old one stays
+  void* ws = A->ws;
+  CHECK(ensure_workspace(A, 20 << 20) == GCN_EHIP && A->ws == ws && frees == f);
+}
+
 int main(int argc, char** argv) {
-  const struct { const char* name; void (*run)(); } checks[] = {{"plan", plan}, {"lock", lock}, {"exhausted", exhausted}};
+  const struct { const char* name; void (*run)(); } checks[] = {{"plan", plan}, {"lock", lock}, {"exhausted", exhausted}, {"workspace", workspace}};
   for (auto& c : checks)
     if (argc > 1 && !strcmp(argv[1], c.name)) { c.run(); printf("%s holds\n", c.name); fflush(stdout); _Exit(0); }
   printf("no such check\n");
