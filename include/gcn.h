@@ -32,7 +32,8 @@
  *    padding, kept in the handle until gcn_csr_free), which allocates and waits for the
  *    stream.  Later calls of that width class reuse the plan.
  *  - Device memory of freed handles and of finished calls is kept for later calls of this process, at most 1/64 of the
- *    device's memory; it goes back to the runtime when an allocation of the library fails or it lies unused.
+ *    device's memory.  A block goes back to the runtime when 256 blocks have been given back since without it being used,
+ *    when an allocation of the library fails, or by gcn_release_memory().
  *  - Sizes: vertex ids and n_global lie below 2^31, edges + rows of a build below 2^32; dense buffers may
  *    run past 2^32 bytes and 2^31 elements (row offsets are 64-bit).  A size that a kernel cannot take is
  *    an error (GCN_EINVAL), never a truncated result.
@@ -112,6 +113,11 @@ int gcn_csr_arrays(const gcn_csr_t* A, const int64_t** rowptr, const int32_t** c
 
 /* Free the handle, its device arrays and its workspace.  NULL is accepted. */
 int gcn_csr_free(gcn_csr_t* A);
+
+/* Give the device memory that is kept for later calls back to the runtime, of all devices: for a program that has built its
+ * graphs and wants the memory for other allocators.  Handles in use keep what they hold.  Waits for the devices; may run
+ * beside calls of other threads. */
+int gcn_release_memory(void);
 
 /*
  * Y[nr x d] = epilogue( A^_m X[nc x d] + bias )          (Sec. 4.1, the sum of the per-row task:

@@ -83,6 +83,8 @@ def _load():
     lib.gcn_profile_get.restype = C.c_int
     lib.gcn_debug_max_grid_x.argtypes = [C.c_int64]
     lib.gcn_debug_max_grid_x.restype = C.c_int
+    lib.gcn_release_memory.argtypes = []
+    lib.gcn_release_memory.restype = C.c_int
     lib.gcn_feature_ld.argtypes = [C.c_int, C.c_int]
     lib.gcn_feature_ld.restype = C.c_int64
     lib.gcn_debug_set_tuning.argtypes = [C.c_char_p, C.c_int]
@@ -465,6 +467,11 @@ def gcn_sgd_update(W: torch.Tensor, dW: torch.Tensor, lr: float):
         raise TypeError("gcn_sgd_update: W and dW must be contiguous and of one shape")
     _check(_lib.gcn_sgd_update(_ptr(W), _ptr(dW), W.numel(), float(lr), _stream()), "gcn_sgd_update")
     return W
+
+
+def gcn_release_memory():
+    """Give device memory that the library keeps for later calls back to the runtime (so that torch's allocator can have it)."""
+    _check(_lib.gcn_release_memory(), "gcn_release_memory")
 
 
 def gcn_debug_max_grid_x(blocks: int):

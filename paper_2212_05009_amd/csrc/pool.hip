@@ -10,7 +10,8 @@
 //    stream may therefore take it at once.  Where the wait fails (another thread captures a graph), it is not kept.
 //  * A block serves requests of at least 3/4 of its size, so what is held and not used stays small.
 //  * Bounded: at most 1/64 of the device's memory is kept (4.5 of 288 GB), least recently freed blocks go first; a block
-//    that lies unused over 256 later returns goes back to the runtime; a failed hipMalloc empties the pool and retries.
+//    that lies unused over 256 later returns goes back to the runtime; a failed hipMalloc empties the pool and retries; gcn_release_memory
+//    empties it on demand.
 //  * The lock covers the lists only.  hipFree, which waits for the device, runs outside it: a thread that gives blocks back
 //    holds up no other thread's calls, on this GPU or another.
 #include <condition_variable>
@@ -205,3 +206,20 @@ void pinned_give(void* p) {
 }
 
 }  // namespace gcn
+
+extern "C" int gcn_release_memory(void) {
+  using namespace gcn;
+  clear_error();
+  Pool& P = pool();
+  std::unique_lock<std::mutex> lock(P.mu);
+  for (DevicePool& d : P.dev) {
+    BlockList gone;
+    while (!d.by_age.empty()) drop_oldest(d, gone);
+    free_gone(P, d, gone, lock);
+  }
+  std::vector<void*> pages;
+  pages.swap(P.pinned);
+  lock.unlock();
+  for (void* p : pages) (void)hipHostFree(p);
+  return GCN_OK;
+}

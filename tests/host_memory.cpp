@@ -194,8 +194,23 @@ static void workspace() {
   CHECK(ensure_workspace(A, 20 << 20) == GCN_EHIP && A->ws == ws && frees == f);
 }
 
+// What is kept goes back on request; what is in use does not.
+static void release() {
+  void *a, *b, *c, *page;
+  CHECK(pool_alloc(&a, 1000) == GCN_OK && pool_alloc(&b, (size_t)30 << 20) == GCN_OK);
+  current = 1;
+  CHECK(pool_alloc(&c, 70000) == GCN_OK && pinned_take(&page) == GCN_OK);
+  pinned_give(page);
+  pool_free(b);
+  pool_free(c);
+  CHECK(frees == 0);
+  CHECK(gcn_release_memory() == GCN_OK && frees == 2 && live.size() == 1 && live.count(a));
+  CHECK(gcn_release_memory() == GCN_OK && frees == 2);
+  CHECK(pool_alloc(&b, 70000) == GCN_OK && mallocs == 4);           // nothing was left to take it from
+}
+
 int main(int argc, char** argv) {
-  const struct { const char* name; void (*run)(); } checks[] = {{"plan", plan}, {"lock", lock}, {"exhausted", exhausted}, {"workspace", workspace}};
+  const struct { const char* name; void (*run)(); } checks[] = {{"plan", plan}, {"lock", lock}, {"exhausted", exhausted}, {"workspace", workspace}, {"release", release}};
   for (auto& c : checks)
     if (argc > 1 && !strcmp(argv[1], c.name)) { c.run(); printf("%s holds\n", c.name); fflush(stdout); _Exit(0); }
   printf("no such check\n");
