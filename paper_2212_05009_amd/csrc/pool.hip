@@ -10,14 +10,15 @@
 //    stream may therefore take it at once.  Where the wait fails (another thread captures a graph), it is not kept.
 //  * A block serves requests of at least 3/4 of its size, so what is held and not used stays small.
 //  * Bounded: at most 1/64 of the device's memory is kept (4.5 of 288 GB), least recently freed blocks go first; a block
-//    that lies unused over 256 later returns goes back to the runtime; a failed hipMalloc empties the pool and retries; gcn_release_memory
-//    empties it on demand.
+//    that lies unused over 256 later returns goes back to the runtime; a failed hipMalloc empties the pool and retries;
+//    gcn_release_memory empties it on demand.
 //  * The lock covers the lists only.  hipFree, which waits for the device, runs outside it: a thread that gives blocks back
 //    holds up no other thread's calls, on this GPU or another.
 #include <condition_variable>
 #include <list>
 #include <map>
 #include <mutex>
+#include <new>
 #include <unordered_map>
 #include <vector>
 
@@ -48,8 +49,11 @@ struct Pool {
   std::vector<void*> pinned;                                // idle pinned host pages
 };
 
+// In memory of its own: the first use allocates nothing, so it cannot throw, and it is never destroyed (at process end the
+// runtime takes the device memory back).
 Pool& pool() {
-  static Pool* p = new Pool();      // never destroyed: at process end the runtime takes the memory back
+  alignas(Pool) static unsigned char place[sizeof(Pool)];
+  static Pool* p = new (place) Pool();
   return *p;
 }
 

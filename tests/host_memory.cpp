@@ -9,6 +9,7 @@
 #include <chrono>
 #include <condition_variable>
 #include <mutex>
+#include <new>
 #include <set>
 #include <thread>
 
@@ -28,8 +29,19 @@ size_t malloc_limit = ~(size_t)0;          // bytes that can be out at once
 size_t out_bytes = 0;
 std::set<std::pair<void*, size_t>> sizes;
 
+bool host_memory_out = false;              // operator new fails
+
 hipError_t sync_result() { return ++syncs >= first_failing_sync ? hipErrorStreamCaptureUnsupported : hipSuccess; }
 }  // namespace
+
+// (the library's allocations come here too)
+void* operator new(size_t n) {
+  void* p = host_memory_out ? nullptr : malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
 
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
@@ -38,8 +50,11 @@ hipError_t hipMalloc(void** p, size_t n) {
   if (posix_memalign(p, 4096, n) != 0) return hipErrorOutOfMemory;
   memset(*p, 0, n < 65536 ? n : 65536);
   ++mallocs; out_bytes += n;
+  const bool was = host_memory_out;
+  host_memory_out = false;                 // (these notes are not the library's)
   live.insert(*p);
   sizes.insert({*p, n});
+  host_memory_out = was;
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {
@@ -209,8 +224,24 @@ static void release() {
   CHECK(pool_alloc(&b, 70000) == GCN_OK && mallocs == 4);           // nothing was left to take it from
 }
 
+// Host memory that runs out before the first block or page is asked for: calls report it or do without, none throws.
+static void host() {
+  host_memory_out = true;
+  gcn_csr_t* A = (gcn_csr_t*)1;
+  int32_t e = 0;
+  CHECK(gcn_release_memory() == GCN_OK);
+  CHECK(gcn_csr_build(&e, &e, 1, 1, 0, 1, nullptr, 0, nullptr, &A) == GCN_ENOMEM && !A);
+  void *p = nullptr, *page = nullptr;
+  CHECK(pinned_take(&page) == GCN_OK);
+  pinned_give(page);
+  CHECK(pool_alloc(&p, 1000) == GCN_OK && live.count(p));          // a block that is on no list
+  pool_free(p);
+  host_memory_out = false;
+  CHECK(live.empty());
+}
+
 int main(int argc, char** argv) {
-  const struct { const char* name; void (*run)(); } checks[] = {{"plan", plan}, {"lock", lock}, {"exhausted", exhausted}, {"workspace", workspace}, {"release", release}};
+  const struct { const char* name; void (*run)(); } checks[] = {{"plan", plan}, {"lock", lock}, {"exhausted", exhausted}, {"workspace", workspace}, {"release", release}, {"host", host}};
   for (auto& c : checks)
     if (argc > 1 && !strcmp(argv[1], c.name)) { c.run(); printf("%s holds\n", c.name); fflush(stdout); _Exit(0); }
   printf("no such check\n");

@@ -22,7 +22,7 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("check", ["plan", "lock", "exhausted", "workspace", "release"])
+@pytest.mark.parametrize("check", ["plan", "lock", "exhausted", "workspace", "release", "host"])
 def test_kept_memory(program, check):
     res = subprocess.run([program, check], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stdout + res.stderr
