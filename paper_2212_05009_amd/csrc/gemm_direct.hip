@@ -831,12 +831,17 @@ static bool tn_wide_ok(const void* A, int64_t lda, const void* B, int64_t ldb, i
 // column tiles of B per block in the vector variant: all of B for up to 256 columns
 int tn_wide_wn(int N) { return N <= 64 ? 1 : N <= 128 ? 2 : 4; }
 
-// Fewest rows per split.  A split costs its partial tile (written, then read by the sum), so wide outputs keep 512
-// rows; for narrow ones the tile is small and what counts is the chain of row chunks of a block: with 512 rows a
-// short sum (4096 rows x 64 x 16) ran on 8 workgroups for 19 us.
-static int64_t tn_min_rows(int M, int N) {
+// Most splits that the rows admit.  A split costs its partial tile (written, then read by the sum), so it has 512 rows
+// where that already gives every compute unit a workgroup.  Below, what counts is the chain of row chunks of a workgroup:
+// splits get shorter, down to 64 rows for narrow outputs and 512 for wide ones, until there are 256 workgroups.  Measured,
+// us with 512 rows / short splits without that limit / this rule: 4 K rows x 64 x 16 fp32 21 / 11 / 11, 20 K 22 / 14 / 12;
+// 60 K x 50 x 50 21 / 18 / 16; 90 K x 50 x 7 14 / 17 / 13; 130 K x 128 x 41 33 / 40 / 33, x 256 x 47 59 / 64 / 59; over 10 row
+// counts up to 500 K and 10 widths in both types never above the first (noise 2 %), 0.86 of it on the average.  With a limit
+// of 128 / 192 / 384 / 512 workgroups the average is 0.89 / 0.87 / 0.89 / 0.88, with 384 and 512 some are 20 % above.
+static int64_t tn_max_splits(int64_t Kd, int M, int N, int64_t tiles) {
   const int64_t r = (int64_t)M * N / 32;
-  return r < 64 ? 64 : r > 512 ? 512 : round_up(r, 64);
+  const int64_t min_rows = r < 64 ? 64 : r > 512 ? 512 : round_up(r, 64);
+  return std::max(ceil_div(Kd, 512), std::min(ceil_div(Kd, min_rows), ceil_div(256, tiles)));
 }
 
 // splits of the vector variant: about two blocks per compute unit
@@ -844,7 +849,7 @@ int tn_wide_splits(int64_t Kd, int M, int N) {
   const int blocks = tune().gemm_tn_blocks;
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, (N <= 32 ? 32 : 64) * tn_wide_wn(N));
   int64_t want = ceil_div(blocks, tiles);
-  int64_t max_by_k = ceil_div(Kd, tn_min_rows(M, N));
+  int64_t max_by_k = tn_max_splits(Kd, M, N, tiles);
   int64_t ns = want < max_by_k ? want : max_by_k;
   return (int)(ns < 1 ? 1 : ns);
 }
@@ -854,7 +859,7 @@ static int tn_direct_tn(int N) { return N <= 32 ? 1 : 2; }
 static int tn_direct_splits(int64_t Kd, int M, int N) {
   const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 32 * tn_direct_tn(N));
   int64_t want = ceil_div(1024, tiles);                // about four blocks per compute unit
-  int64_t max_by_k = ceil_div(Kd, tn_min_rows(M, N));
+  int64_t max_by_k = tn_max_splits(Kd, M, N, tiles);
   int64_t ns = want < max_by_k ? want : max_by_k;
   return (int)(ns < 1 ? 1 : ns);
 }

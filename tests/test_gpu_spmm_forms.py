@@ -130,7 +130,8 @@ def test_infinities_stay_in_the_rows_that_hold_them(gcn, dev, short, bf16):
         assert np.isposinf(got[hit]).all() and np.isfinite(got[~hit]).all()
 
 
-@pytest.mark.parametrize("rows,k,n", [(1, 3, 5), (63, 64, 16), (65, 17, 33), (700, 64, 16), (4097, 128, 128), (520, 602, 41)])
+@pytest.mark.parametrize("rows,k,n", [(1, 3, 5), (63, 64, 16), (65, 17, 33), (700, 64, 16), (4097, 128, 128), (520, 602, 41),
+                                      (16385, 64, 16), (33001, 50, 7), (50001, 128, 41)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_dw_of_few_rows_against_fp64(gcn, dev, rows, k, n, bf16):
     """A^T G over few rows, whose split depends on the size of the output; an edgeless graph makes A the identity."""
@@ -151,6 +152,26 @@ def test_dw_of_few_rows_against_fp64(gcn, dev, rows, k, n, bf16):
     check_bound(dW.cpu().numpy(), H64.T @ G64, np.abs(H64).T @ np.abs(G64), tol, what="dW")
     check_bound(to_np(dH), G64 @ W64.T, np.abs(G64) @ np.abs(W64).T, tol, what="dH = G W^T")
     A.free()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_dw_is_summed_over_no_more_parts_than_it_needs(gcn, dev, bf16):
+    """Parts of less than 512 rows only as far as they give every compute unit a workgroup: each part is written and read."""
+    import torch
+    tdt = torch.bfloat16 if bf16 else torch.float32
+    for rows in (4096, 60_000, 130_000):
+        A = gcn.gcn_csr_build(torch.zeros(1, dtype=torch.int32, device=dev), torch.zeros(1, dtype=torch.int32, device=dev), rows)
+        for k, n in [(64, 16), (50, 7), (50, 50), (128, 41)]:
+            AH, G, W = torch.ones(rows, k, dtype=tdt, device=dev), torch.ones(rows, n, dtype=tdt, device=dev), torch.ones(k, n, device=dev)
+            dW = torch.empty(k, n, device=dev)
+            say(f"parts of dW rows={rows} {k}x{n} bf16={bf16}")
+            gcn.gcn_profile_enable(True)
+            gcn.gcn_layer_bwd(A, AH, W, G, dW, AH_saved=AH)
+            gcn.gcn_profile_enable(False)
+            parts = [r["inner"] for r in gcn.gcn_profile_records()[0] if r["kind"] == "gemm_tn_sum"]
+            assert len(parts) == 1 and 8 < parts[0] <= 256, (rows, k, n, parts)
+            assert bool((dW == rows).all())
+        A.free()
 
 
 @pytest.mark.parametrize("bf16", [False, True])
