@@ -319,7 +319,9 @@ int gcn_csr_induced(const gcn_csr_t* A, const int32_t* d_vertices, int64_t n_sub
  *   d_totals [2]     { sum_j (lambda(n_j) - 1): all rows moved per product (the paper's total without the constant
  *                      factors 2 and cost(n_j));  stored entries whose ends lie in different parts (what the graph
  *                      model charges instead) }
- * Integer work: exact.  Allocates temporaries (about 30 bytes per stored entry) and synchronises the stream.
+ * Integer work: exact.  Allocates temporaries and synchronises the stream.  Handles with column-major arrays and p <= 4096:
+ * p^2 / 8 bytes, p / 8 bytes per column of more than 2048 entries and 12 p bytes per workgroup (p = 512: 13 MB); others
+ * about 30 bytes per stored entry.
  */
 int gcn_partition_stats(const gcn_csr_t* A, const int32_t* d_part, int p, int64_t* d_load, int64_t* d_send_rows,
                         int64_t* d_recv_rows, int64_t* d_send_msgs, int64_t* d_recv_msgs, int64_t* d_totals,
@@ -360,7 +362,7 @@ int gcn_sgd_update(float* W, const float* dW, int64_t n, float lr, void* stream)
 #define GCN_K_GEMM_TN_SUM 5   /* sum of the partial tiles */
 #define GCN_K_SOFTMAX_XENT 6
 #define GCN_K_GATHER 7
-#define GCN_K_OTHER 8         /* small helpers: weight transpose, column sums, loss finish */
+#define GCN_K_OTHER 8         /* column sums, padded copies of operands, the weight update */
 
 typedef struct {
   int32_t kind, d, dtype, reserved;
@@ -401,7 +403,8 @@ int gcn_debug_max_grid_x(int64_t blocks);
  * this call (name = the variable's name, e.g. "GCN_SPMM_PANEL"; value = what the variable would hold;
  * GCN_TUNE_DEFAULT restores the built-in default).  Names: GCN_SPMM_PANEL (0 never / 1 always use the column
  * sweep; default by heuristic, -1), GCN_PANEL_NARROW, GCN_PANEL_NOSYNC, GCN_PANEL_VERBOSE, GCN_SPMM_SLICES
- * (1, 2, 4, 8; 0 = by rule), GCN_SPMM_EPG, GCN_SPMM_WIDE, GCN_GEMM_DIRECT, GCN_GEMM_FAST, GCN_GEMM_TN_WIDE,
+ * (1, 2, 4, 8; 0 = by rule), GCN_SPMM_EPG, GCN_SPMM_WIDE, GCN_SPMM_SHORT (short-row form: 0 never, 1 always; -1 = by rule),
+ * GCN_PARTITION_SORT (1 = partition figures by sorting), GCN_GEMM_DIRECT, GCN_GEMM_FAST, GCN_GEMM_TN_WIDE,
  * GCN_GEMM_BF16, GCN_GEMM_REGW, GCN_GEMM_TN_LDS (0 = that kernel family off), GCN_GEMM_TN_BLOCKS, GCN_GEMM_REGW_BLOCKS,
  * GCN_GEMM_TN_LDS_BLOCKS (workgroups of the kernels that take whole compute units), GCN_GATHER_HOST_BLOCKS, GCN_OVERLAP
  * (dense products beside sparse ones on a second stream: 0 never, 1 on large inputs, 2 wherever possible),

@@ -542,7 +542,8 @@ extern "C" int gcn_csr_build(const int32_t* d_src, const int32_t* d_dst, int64_t
   *out = nullptr;
   if (n_edges < 0 || (n_edges > 0 && (!d_src || !d_dst))) return fail(GCN_EINVAL, "gcn_csr_build: bad edge list");
   if (n_global < 1 || n_global > 0x7fffffffLL) return fail(GCN_EINVAL, "gcn_csr_build: n_global must be in [1, 2^31)");
-  // entry positions travel through the sorts as 32-bit payloads
+  // stored entries then stay below 2^32: the column sweep's plan sorts entry positions as 32-bit payloads, and partition
+  // figures count entries in 32 bits
   if (n_edges + n_global >= 0xffffffffLL) return fail(GCN_EINVAL, "gcn_csr_build: more than 2^32 - 1 edges and rows");
   if (row_lo < 0 || row_hi <= row_lo || row_hi > n_global) return fail(GCN_EINVAL, "gcn_csr_build: need 0 <= row_lo < row_hi <= n_global");
   if (!(row_lo == 0 && row_hi == n_global) && !d_deg_global)
