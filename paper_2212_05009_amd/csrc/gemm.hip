@@ -133,9 +133,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 #pragma unroll
       for (int it = 0; it < B_IT; ++it) {
         const int q = it * 256 + t;                 // group id: k = q / (BN/4), n-quad = q % (BN/4); TRANS: n, k-quad
-        const int row = TRANS ? n0 + q / (BK / 4) : k0 + q / (BN / 4), rows = TRANS ? a.N : a.K;
-        const int c = TRANS ? k0 + (q % (BK / 4)) * 4 : n0 + (q % (BN / 4)) * 4, cols = TRANS ? a.K : a.N;
-        if (q < BK * BN / 4 && row < rows) load4<float>(a.B + (int64_t)row * a.ldb, c, cols, a.vecB, rb[it]);
+        const int k = TRANS ? (q % (BK / 4)) * 4 : q / (BN / 4);
+        const int nq = TRANS ? q / (BK / 4) : (q % (BN / 4)) * 4;
+        if (TRANS && nq < BN && n0 + nq < a.N) load4<float>(a.B + (int64_t)(n0 + nq) * a.ldb, k0 + k, a.K, a.vecB, rb[it]);
+        else if (!TRANS && k < BK && k0 + k < a.K) load4<float>(a.B + (int64_t)(k0 + k) * a.ldb, n0 + nq, a.N, a.vecB, rb[it]);
         else { rb[it][0] = rb[it][1] = rb[it][2] = rb[it][3] = 0.f; }
       }
     }
@@ -151,13 +152,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 #pragma unroll
     for (int it = 0; it < B_IT; ++it) {
       const int q = it * 256 + t;
-      if (q >= BK * BN / 4) continue;
       if constexpr (TRANS) {
+        if (q >= BK * BN / 4) continue;
         // (4 lanes of a row write 4 rows of 4 apart, 16 rows of B side by side: 64 different banks)
 #pragma unroll
         for (int i = 0; i < 4; ++i) Bs[buf][((q % (BK / 4)) * 4 + i) * LDB_S + q / (BK / 4)] = rb[it][i];
       } else {
-        *reinterpret_cast<float4*>(&Bs[buf][q / (BN / 4) * LDB_S + (q % (BN / 4)) * 4]) = make_float4(rb[it][0], rb[it][1], rb[it][2], rb[it][3]);
+        const int k = q / (BN / 4), nq = (q % (BN / 4)) * 4;
+        if (k < BK) *reinterpret_cast<float4*>(&Bs[buf][k * LDB_S + nq]) = make_float4(rb[it][0], rb[it][1], rb[it][2], rb[it][3]);
       }
     }
   };
