@@ -131,7 +131,7 @@ __device__ __forceinline__ float lane_read(int byte_addr, float v) {
 // The team reads idx/val a batch of KB TL entries at a time, KB consecutive ones per lane with one request each (with
 // KB = 4 a request may reach past the row's end, not past the arrays' slack), the next batch before the current one is
 // used; a lane group then fetches the indices and values of its entries from the owning lanes by cross-lane reads and
-// keeps 4 NV gathered feature vectors in flight (a "round" of 4 entries).
+// keeps U NV gathered feature vectors in flight (a "round" of U entries).
 //   KB = 4: a line of the index streams is asked for once or twice and not once per short batch, of which the L1 would
 //           keep none (20 wavefronts with up to 16 teams each touch more lines than it has).  Measured on 2^18 rows with
 //           45 entries each, KB = 1 / 4: fp32 width 16 90 / 86 us, width 128 391 / 383, bf16 width 16 90 / 85.
@@ -149,8 +149,10 @@ template <> struct EntryRegs<1> { typedef int32_t idx; typedef float val; };
 template <typename T, int V, int LPR, int NV, bool NARROW, int LGR>
 __device__ __forceinline__ void team_accumulate(const SpmmK& a, XBuf xb, const int32_t* __restrict__ idx, const float* __restrict__ val, int n,
                                                 int lgr_rt, int team_lane0, int gg, int t, const uint32_t (&c0b)[NV], float (&acc)[NV][V]) {
-  constexpr int U = 4;                                            // entries per group and round
   constexpr int KB = LPR >= 8 && sizeof(T) == 2 ? 1 : 4;          // entries per lane and batch
+  // entries per group and round: 64 bytes in flight per lane, or 8 narrow requests (bf16 rows of odd width or pitch, R-MAT of
+  // 100 K rows with 23 entries, width 17 / 47 / 301: 86 / 157 / 775 us with 4 in flight, 62 / 108 / 523 with 8)
+  constexpr int U = KB == 1 && sizeof(T) * V < 16 ? 8 : 4;
   constexpr int ROUNDS = LPR * KB / U;
   typedef typename EntryRegs<KB>::idx JV;
   typedef typename EntryRegs<KB>::val WV;
