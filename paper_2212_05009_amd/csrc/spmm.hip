@@ -121,7 +121,7 @@ int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s) {
   k.S = pick_slices(a, es, V, k.short_rows != 0, &k.vps);
   if (k.vps <= 0) k.vps = (int)ceil_div(k.nvec, k.S);
   SpmmProf pf;
-  pf.kind = a.transposed ? GCN_K_SPMM_T : GCN_K_SPMM; pf.dtype = a.dtype; pf.rows = a.n_rows; pf.nnz = pf.whole_nnz = a.nnz;
+  pf.kind = a.transposed ? GCN_K_SPMM_T : GCN_K_SPMM; pf.dtype = a.dtype; pf.rows = a.n_rows; pf.nnz = pf.whole_nnz = a.nnz; pf.whole_rows = a.n_rows;
   const double csr = 8.0 * (double)a.nnz + 8.0 * (double)(a.n_rows + 1), fe = (double)es * a.d;
   pf.alg = csr + fe * (double)(a.n_cols + a.n_rows);
   pf.touched = csr + fe * (double)(a.nnz + a.n_rows);

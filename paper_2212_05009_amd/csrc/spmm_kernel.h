@@ -2,6 +2,7 @@
 #pragma once
 #include <stdlib.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(256) void k_spmm_hub_finish(SpmmK a) {
 struct SpmmProf {
   int kind; int dtype; int64_t rows, nnz; double alg, touched, flops;
   int row_chunk = -1, row_chunk_n = 1;   // rows Schedule::chunk_row[row_chunk .. row_chunk + row_chunk_n); -1: all rows
-  int64_t whole_nnz = 0;                 // entries of the whole matrix, also for a range of its rows
+  int64_t whole_nnz = 0, whole_rows = 0; // of the whole matrix, also for a range of its rows
 };
 
 // Entries each lane group should get before a row is shared by more groups (GCN_SPMM_EPG overrides, for
@@ -421,7 +422,11 @@ struct SpmmProf {
 // wavefront that holds more rows keeps more gathers in flight per round trip of its dependent loads.
 constexpr int kEntriesPerGroup = 32;
 constexpr int kFewestPerGroup = 4;
-constexpr int kFullWaves = 4096;      // wavefronts that keep every compute unit at four per SIMD
+// A product is short of lane groups (a row has at least one) below this many wavefronts, two per SIMD.  Measured on uniform
+// graphs, us with 4 / 8 / 16 / 32 entries per group: 60 K rows of 17 entries bf16 width 32 25 / 17 / 15 / 14, width 16 14 / 12 /
+// 10 / 11; of 7 entries, bf16 width 32 13 / 11 / 9 / 9; 30 K rows of 19 entries fp32 width 16 10 / 8 / 8 / 8, width 64 23 / 22 /
+// 19 / 17; on R-MAT ones of 20 K to 100 K rows within 3 %, but for width 128 of 100 K rows, 84 / 78 / 73 / 71.
+constexpr int kFullWaves = 2048;
 
 static inline int pow2_ceil_i(int x) { int p = 1; while (p < x) p <<= 1; return p; }
 
@@ -433,7 +438,7 @@ static int launch_l(SpmmK& k, const Schedule* sc, const SpmmProf& pf, bool narro
   // product is made of)
   int epg = tune().spmm_epg > 0 ? tune().spmm_epg : kEntriesPerGroup;
   if (tune().spmm_epg <= 0)
-    while (epg > kFewestPerGroup && pf.whole_nnz / epg * k.S < (int64_t)kFullWaves * G) epg >>= 1;
+    while (epg > kFewestPerGroup && std::max(pf.whole_rows, pf.whole_nnz / epg) * k.S < (int64_t)kFullWaves * G) epg >>= 1;
   // bins of the ordinary rows: class c holds lengths in [2^(31-c), 2^(32-c)), class 32 empty rows
   int n_bins = 0;
   int64_t waves = 0;
