@@ -87,8 +87,10 @@ static int64_t padded_operand_ld(const gcn_csr* A, bool transposed, int d, int d
   if (ldp == ldx) return ldx;
   const int64_t n_cols = transposed ? A->nr : A->nc;
   // 2-byte elements in rows that start between words can only be gathered one by one (bf16, width 81, 45 entries per
-  // row: 580 us against 120 padded)
-  if ((ldx * es) % 4 != 0 && d > 1 && A->nnz >= 2 * n_cols) return ldp;
+  // row: 580 us against 120 padded).  Rows of one such request (up to 32 elements) gain less than the copy and its launch cost
+  // where there are few entries: forward pass with / without the copy, width 5 / 9, 60 K rows of 17 entries 20 / 27 against
+  // 17 / 20 us, 100 K rows of 18 (R-MAT) 32 / 37 against 37 / 48.
+  if ((ldx * es) % 4 != 0 && d > 1 && A->nnz >= 2 * n_cols && (d > 32 || A->nnz >= 1500000)) return ldp;
   if (A->nnz < 8 * n_cols) return ldx;
   if ((ldx * es) % 16 != 0) {        // the column sweep, which takes 16-byte aligned rows only, is worth the copy
     SpmmArgs probe{};
