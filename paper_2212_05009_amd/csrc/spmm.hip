@@ -36,8 +36,12 @@ static bool aligned(const void* p, size_t a) { return p == nullptr || ((uintptr_
 // in lines, P: slice s of row j is line j * P + s, and an XCD that only asks for lines = s (mod P) uses the few L2
 // channels (and memory channels) those addresses select when P is a power of two.  Measured on a 2.45 M x 256 fp32
 // operand (R-MAT, 126 M entries): pitch 8 lines 17.6 / 15.4 / 15.5 / 17.2 ms for S = 1 / 2 / 4 / 8, pitch 9 lines
-// 16.5 / 14.7 / 13.9 ms for S = 2 / 4 / 8 (L2 hits 19 % -> 33 %).  With an odd pitch every slice gets one line
-// (up to 8 slices); otherwise two slices for operands above 32 MB whose halves are whole lines (67 MB, width 64 fp32,
+// 16.5 / 14.7 / 13.9 ms for S = 2 / 4 / 8 (L2 hits 19 % -> 33 %).  With an odd pitch every slice gets one line, up to 8
+// slices.  A line count that is no power of two leaves slices without a line, and their XCDs idle: from 2 M entries on, where
+// wavefronts are plenty, there are as many slices as leave at most one in eight so.  9 lines (288 fp32) in 8 / 4 / 2 slices, of
+// which 5 / 3 / 2 hold something: 1544 / 1184 / 1156 us on R-MAT 2^18 (50 entries per row), 1238 / 863 / 754 us on 250 K uniform
+// rows of 20; 5 lines 709 / 664 / 589 and 631 / 542 / 426; but 87 / 100 / 174 us on R-MAT of 45 K rows of 16, where narrow slices
+// spread its long rows over more lane groups.  With an even pitch two slices for operands above 32 MB whose halves are whole lines (67 MB, width 64 fp32,
 // 45 entries per row: 205 -> 190 us).
 // Returns S and sets *vps (vectors of V elements per slice; 0: split evenly).
 static int pick_slices(const SpmmArgs& a, size_t es, int V, bool short_rows, int* vps) {
@@ -51,6 +55,8 @@ static int pick_slices(const SpmmArgs& a, size_t es, int V, bool short_rows, int
   if (on_lines && nl >= 2 && ((pitch / 128) & 1) && (forced > 0 || xbytes > 16e6)) {
     int S = 2;
     while (S < nl && S < 8) S <<= 1;
+    if (forced <= 0 && a.nnz >= (1 << 21))
+      while (S > 2 && 8 * ceil_div(nl, ceil_div(nl, S)) < 7 * S) S >>= 1;
     if (forced > 0 && forced < S) S = forced;
     if (S != 1 && S != 2 && S != 4 && S != 8) S = 1;
     *vps = (int)(ceil_div(nl, S) * 8);                   // 8 vectors of 16 bytes per line
