@@ -41,8 +41,12 @@ static bool aligned(const void* p, size_t a) { return p == nullptr || ((uintptr_
 // wavefronts are plenty, there are as many slices as leave at most one in eight so.  9 lines (288 fp32) in 8 / 4 / 2 slices, of
 // which 5 / 3 / 2 hold something: 1544 / 1184 / 1156 us on R-MAT 2^18 (50 entries per row), 1238 / 863 / 754 us on 250 K uniform
 // rows of 20; 5 lines 709 / 664 / 589 and 631 / 542 / 426; but 87 / 100 / 174 us on R-MAT of 45 K rows of 16, where narrow slices
-// spread its long rows over more lane groups.  With an even pitch two slices for operands above 32 MB whose halves are whole lines (67 MB, width 64 fp32,
-// 45 entries per row: 205 -> 190 us).
+// spread its long rows over more lane groups.  With an even pitch two slices for operands above 32 MB
+// whose halves are whole lines.  Two slices over one, 18 to 60 entries per row, 34 to 99 MB: rows of four lines 0.86 to 1.00
+// (uniform columns); rows of two lines in fp32 0.87 to 1.05 with R-MAT columns, 0.92 to 1.01 up to 50 MB and 1.03 to 1.06
+// beyond with uniform ones, in bf16 (bound by instruction issue, which slices double) 0.95 to 1.07 and 0.95 to 1.10.  Rows of
+// two lines therefore stay whole up to 100 MB in bf16, and in fp32 from 56 MB on where no row is long (which goes with no
+// column being popular).
 // Returns S and sets *vps (vectors of V elements per slice; 0: split evenly).
 static int pick_slices(const SpmmArgs& a, size_t es, int V, bool short_rows, int* vps) {
   *vps = 0;
@@ -65,6 +69,7 @@ static int pick_slices(const SpmmArgs& a, size_t es, int V, bool short_rows, int
   int S = 1;
   if (forced > 0) S = forced;
   else if (xbytes > 32e6) S = 2;
+  if (forced <= 0 && row_bytes == 256 && xbytes <= 100e6 && (es == 2 || (xbytes > 56e6 && a.sched->n_hub_rows == 0))) S = 1;
   while (S > 1 && (double)row_bytes / S < 128.0) S >>= 1;
   // a slice that does not consist of whole 128-byte lines makes every gathered row touch more lines in all than
   // the undivided row does: 400-byte rows (width 100) in two slices took 11.7 ms where one slice takes 8.0 ms
@@ -122,6 +127,8 @@ int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s) {
   // chain.  Measured, 500 K rows with 6.6 entries each, width 50: 32 lanes with 8-byte requests 164 us, two slices 190 us,
   // this form 148 us (6.6 TB/s out of L2, the rate of the fabric).  With four vectors a lane (width 128, 8 entries per
   // row) it loses to four slices, 466 against 417 us: wide rows are bound by what misses L2, of which slices keep more.
+  // This form over the other by entries per row, widths 36 to 64 fp32 and 72 to 128 bf16, uniform columns, 30 K to 2 M rows: 0.83 to
+  // 1.01 with 4, 0.88 to 1.04 with 7 to 11, 0.91 to 1.06 with 13 to 24 (above 1.02 nearly always in bf16).
   const double mean_len = (double)a.nnz / (double)a.n_rows * (a.part ? 0.5 : 1.0);
   k.short_rows = V * (int)es == 16 && k.nvec > 8 && k.nvec <= 16 && (tune().spmm_short >= 0 ? tune().spmm_short != 0 : mean_len < 16.0);
   k.S = pick_slices(a, es, V, k.short_rows != 0, &k.vps);
