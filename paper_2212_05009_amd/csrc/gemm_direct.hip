@@ -831,17 +831,18 @@ static bool tn_wide_ok(const void* A, int64_t lda, const void* B, int64_t ldb, i
 // column tiles of B per block in the vector variant: all of B for up to 256 columns
 int tn_wide_wn(int N) { return N <= 64 ? 1 : N <= 128 ? 2 : 4; }
 
-// Most splits that the rows admit.  A split costs its partial tile (written, then read by the sum), so it has 512 rows
-// where that already gives every compute unit a workgroup.  Below, what counts is the chain of row chunks of a workgroup:
-// splits get shorter, down to 64 rows for narrow outputs and 512 for wide ones, until there are 256 workgroups.  Measured,
-// us with 512 rows / short splits without that limit / this rule: 4 K rows x 64 x 16 fp32 21 / 11 / 11, 20 K 22 / 14 / 12;
-// 60 K x 50 x 50 21 / 18 / 16; 90 K x 50 x 7 14 / 17 / 13; 130 K x 128 x 41 33 / 40 / 33, x 256 x 47 59 / 64 / 59; over 10 row
-// counts up to 500 K and 10 widths in both types never above the first (noise 2 %), 0.86 of it on the average.  With a limit
-// of 128 / 192 / 384 / 512 workgroups the average is 0.89 / 0.87 / 0.89 / 0.88, with 384 and 512 some are 20 % above.
+// Most splits that the rows admit.  A split costs its partial tile (written, then read by the sum), so it has about 512 rows
+// where that gives every compute unit a workgroup, rounded to a whole number of workgroups per compute unit (the last, half
+// empty round of a launch costs as much as a full one).  Below, what counts is the chain of row chunks of a workgroup: splits
+// get shorter, down to 64 rows for narrow outputs and 512 for wide ones, until there are 256 workgroups.  Measured, us with 512
+// rows / the shortest splits / this rule: 4 K rows x 64 x 16 fp32 21 / 11 / 11, 60 K x 50 x 50 21 / 18 / 16, 130 K x 128 x 41 33 /
+// 40 / 32, 150 K x 50 x 50 32 / 29 / 25, 2^18 x 50 x 50 34 / 38 / 34, 416 K x 47 x 16 bf16 37 / 33 / 33; on the average of 13 row
+// counts up to 500 K and 11 widths in both types 1 / 0.92 / 0.87, against the first at worst 1.08 (130 K x 256 x 47).
 static int64_t tn_max_splits(int64_t Kd, int M, int N, int64_t tiles) {
   const int64_t r = (int64_t)M * N / 32;
   const int64_t min_rows = r < 64 ? 64 : r > 512 ? 512 : round_up(r, 64);
-  return std::max(ceil_div(Kd, 512), std::min(ceil_div(Kd, min_rows), ceil_div(256, tiles)));
+  const int64_t per_cu = std::max<int64_t>(1, ceil_div(Kd * tiles, 512 * 256));
+  return std::max(ceil_div(Kd, 512), std::min(ceil_div(Kd, min_rows), ceil_div(256 * per_cu, tiles)));
 }
 
 // splits of the vector variant: about two blocks per compute unit
