@@ -1,7 +1,7 @@
 """Counter-based pseudo-random numbers for the synthetic workloads.
 
 Every draw is a pure function of (seed, stream, index): the value at an index never
-depends on how many other values were drawn, so the CPU checker and the GPU path are
+depends on how many other values were drawn, so the CPU oracle and the GPU path are
 handed bit-identical inputs regardless of chunking.  The mixer is the public
 splitmix64 finaliser applied to a 64-bit counter.
 
