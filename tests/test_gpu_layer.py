@@ -409,6 +409,29 @@ def test_middle_sized_block_does_not_depend_on_the_second_stream(gcn, dev, middl
             gcn.gcn_debug_set_tuning(name, None)
 
 
+@pytest.mark.parametrize("n", [63, 64, 65, 511, 512, 513, 2047, 2048, 2049, 4097, 8320])
+def test_schedule_lists_at_the_edges_of_its_blocks(gcn, dev, n):
+    """Rows of every length class (1, 2, 3 .. 1023, and from 2049 vertices on more than 2048 entries) at row counts around a
+    step (64 rows), a wavefront (512) and a block (2048) of the schedule's counting sort: the product on the whole matrix,
+    on 8 row ranges, and with the transposed arrays."""
+    src, dst = hub_graph(n, 3, 2.0, n)
+    lens = np.minimum(2 ** np.arange(3, 10), n - 1)
+    us = np.concatenate([np.full(k, (7 * i + 5) % n) for i, k in enumerate(lens)])
+    vs = np.concatenate([np.arange(k) for k in lens])
+    case = Case(gcn, dev, np.r_[src, us], np.r_[dst, vs], n)
+    gcn.gcn_debug_set_tuning("GCN_GEMM_REGW", 2)
+    try:
+        for overlap in (0, 2):
+            gcn.gcn_debug_set_tuning("GCN_OVERLAP", overlap)
+            gcn.gcn_debug_set_tuning("GCN_OVERLAP_CHUNKS", 8)
+            run_fwd(gcn, dev, case, 100, 192, save_ah=True)
+        run_bwd(gcn, dev, case, 100, 16)
+    finally:
+        for name in ("GCN_OVERLAP", "GCN_OVERLAP_CHUNKS", "GCN_GEMM_REGW"):
+            gcn.gcn_debug_set_tuning(name, None)
+        case.A.free()
+
+
 # ----------------------------------------------------------------------------- softmax cross-entropy
 @pytest.mark.parametrize("d_in,d_out", [(128, 41), (41, 128), (256, 47), (200, 130), (130, 200)])
 def test_layer_with_the_column_sweep(gcn, dev, er, hubs, directed_block, d_in, d_out):
