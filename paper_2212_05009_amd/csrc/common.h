@@ -281,11 +281,30 @@ int exclusive_scan_u32(const uint32_t* in, int64_t* out, int64_t n, void* tmp, h
 
 // Stable least-significant-digit radix sort of 64-bit keys on bits [bit_lo, bit_hi), with an
 // optional 32-bit payload.  Result ends in (keys_out, pay_out); both key buffers and both
-// payload buffers are clobbered.  tmp must hold sort_tmp_bytes(n).
+// payload buffers are clobbered.  tmp must hold sort_tmp_bytes(n), n < 2^32.  count: the number of keys on the device, n
+// then bounds it.  kept: keys of all ones are left out, the others counted there (plain keys only).
 size_t sort_tmp_bytes(int64_t n);
 int radix_sort_u64(uint64_t* keys_a, uint64_t* keys_b, uint32_t* pay_a, uint32_t* pay_b, int64_t n,
                    int bit_lo, int bit_hi, void* tmp, hipStream_t s, uint64_t** keys_out,
-                   uint32_t** pay_out);
+                   uint32_t** pay_out, const int64_t* count = nullptr, int64_t* kept = nullptr);
+
+// ---- handles from sorted entries (csr_build.hip) -------------------------------------------------
+// The second half of a build: m keys (row << key_bits(columns) | column) in keys_a, in any order and with repetitions, every
+// row's diagonal among them, become the arrays and schedules of A (the call has waited for its stream by then).
+// words: key_words_bytes(m) bytes of device memory.  Without a device-side count, keys of all ones are no entries and
+// key_verdict(words, m) holds the flags found while the keys were made; with one, m bounds the keys and all are entries.
+struct KeyBuild {
+  int64_t n_global = 0, row_lo = 0, nr = 0, nh = 0;
+  DevBuf *keys_a = nullptr, *keys_b = nullptr, *words = nullptr, *halo_gid = nullptr;
+  int64_t m = 0;
+  const int64_t* count = nullptr;
+  const int32_t* deg_global = nullptr;   // of every global vertex, for the halo columns
+  int flags = 0;
+};
+int key_bits(int64_t n);
+size_t key_words_bytes(int64_t m);
+int64_t* key_verdict(const DevBuf& words, int64_t m);
+int build_from_keys(const KeyBuild& in, CallScope& sc, PinnedPage& page, gcn_csr* A);
 
 // ---- schedule construction (csr_build.hip) -------------------------------------------------
 void free_schedule(Schedule* sc, bool idle = true);

@@ -88,27 +88,29 @@ __global__ void k_make_keys(const int32_t* __restrict__ src, const int32_t* __re
 
 // ---- step 4: duplicate removal ------------------------------------------------------------------
 // Two passes over the sorted keys with a scan of the blocks' counts between them: flags and positions of every candidate
-// in memory cost 28 bytes a key where this reads 16 (keys twice).
+// in memory cost 28 bytes a key where this reads 16 (keys twice).  m: a bound on the keys, of which there are *count.
 constexpr int kUniqItems = 16;
 constexpr int kUniqTile = kThreads * kUniqItems;
 static_assert(kThreads / 64 * kUniqItems == 64, "k_compact scans the counts of a block's (round, wavefront) pairs in one wavefront");
 
-__device__ __forceinline__ bool first_of_equal(const uint64_t* __restrict__ keys, int64_t k, int64_t m, uint64_t* v) {
+__device__ __forceinline__ bool first_of_equal(const uint64_t* __restrict__ keys, int64_t k, int64_t m, uint64_t* v, uint64_t* before) {
   if (k >= m) return false;
   *v = keys[k];
-  return *v != kInvalidKey && (k == 0 || keys[k - 1] != *v);
+  *before = k ? keys[k - 1] : 0;
+  return k == 0 || *before != *v;
 }
 
-__global__ __launch_bounds__(kThreads) void k_count_unique(const uint64_t* __restrict__ keys, int64_t m, int64_t nb,
-                                                           uint32_t* __restrict__ cnt) {
+__global__ __launch_bounds__(kThreads) void k_count_unique(const uint64_t* __restrict__ keys, const int64_t* __restrict__ count,
+                                                           int64_t nb, uint32_t* __restrict__ cnt) {
   const int64_t blk = block_id();
   if (blk >= nb) return;
+  const int64_t m = *count;
   __shared__ uint32_t wave_cnt[kThreads / 64];
   uint32_t c = 0;
 #pragma unroll
   for (int i = 0; i < kUniqItems; ++i) {
-    uint64_t v = 0;
-    c += (uint32_t)__popcll(__ballot(first_of_equal(keys, blk * kUniqTile + i * kThreads + threadIdx.x, m, &v)));
+    uint64_t v, before;
+    c += (uint32_t)__popcll(__ballot(first_of_equal(keys, blk * kUniqTile + i * kThreads + threadIdx.x, m, &v, &before)));
   }
   if ((threadIdx.x & 63) == 0) wave_cnt[threadIdx.x >> 6] = c;
   __syncthreads();
@@ -119,19 +121,23 @@ __global__ __launch_bounds__(kThreads) void k_count_unique(const uint64_t* __res
   }
 }
 
+// Also the row pointers: every row holds its diagonal, so a row starts where the row of the key before is another.
 __global__ __launch_bounds__(kThreads) void k_compact(const uint64_t* __restrict__ keys, const int64_t* __restrict__ off,
-                                                      int64_t m, int64_t nb, int colbits, uint64_t* __restrict__ ukeys,
-                                                      int32_t* __restrict__ col) {
+                                                      const int64_t* __restrict__ count, int64_t nb, int colbits, int64_t nnz,
+                                                      uint64_t* __restrict__ ukeys, int32_t* __restrict__ col,
+                                                      int64_t* __restrict__ rowptr) {
   const int64_t blk = block_id();
   if (blk >= nb) return;
+  const int64_t m = *count;
+  if (blk * kUniqTile >= m) return;
   __shared__ uint32_t part[64];            // keys kept by round i, wavefront w at [i * waves + w]; then those before it
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  uint64_t v[kUniqItems];
+  uint64_t v[kUniqItems], before[kUniqItems];
   uint64_t kept[kUniqItems];
 #pragma unroll
   for (int i = 0; i < kUniqItems; ++i) {
-    v[i] = 0;
-    kept[i] = __ballot(first_of_equal(keys, blk * kUniqTile + i * kThreads + threadIdx.x, m, &v[i]));
+    v[i] = before[i] = 0;
+    kept[i] = __ballot(first_of_equal(keys, blk * kUniqTile + i * kThreads + threadIdx.x, m, &v[i], &before[i]));
     if (lane == 0) part[i * (kThreads / 64) + w] = (uint32_t)__popcll(kept[i]);
   }
   __syncthreads();
@@ -154,6 +160,9 @@ __global__ __launch_bounds__(kThreads) void k_compact(const uint64_t* __restrict
     const int64_t p = base + part[i * (kThreads / 64) + w] + __popcll(kept[i] & lt);
     ukeys[p] = v[i];
     col[p] = (int32_t)(v[i] & ((1ull << colbits) - 1ull));
+    const uint64_t row = v[i] >> colbits;
+    if (p == 0 || row != before[i] >> colbits) rowptr[row] = p;
+    if (p == nnz - 1) rowptr[row + 1] = nnz;
   }
 }
 
@@ -205,24 +214,73 @@ __global__ void k_degrees(const int64_t* __restrict__ ptr, int64_t nr, int64_t n
   dinv[c] = inv_sqrt_deg(d);
 }
 
+// Four entries per thread, whole requests (what bounds the kernels below is the gather of a factor per entry out of L2, 11.8 M
+// entries in 51 and 59 us; a launch that found the column pointers alone took 20).
+constexpr int kEntriesPerThread = 4;
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+
+// entries [p, p + 4) of n in v (the last one again behind the end); their number
+__device__ __forceinline__ int load_keys(const uint64_t* __restrict__ keys, int64_t p, int64_t n, uint64_t (&v)[kEntriesPerThread]) {
+  if (p + kEntriesPerThread <= n) {
+    const u64x2 a = *reinterpret_cast<const u64x2*>(keys + p), b = *reinterpret_cast<const u64x2*>(keys + p + 2);
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+    return kEntriesPerThread;
+  }
+#pragma unroll
+  for (int i = 0; i < kEntriesPerThread; ++i) v[i] = keys[p + i < n ? p + i : n - 1];
+  return (int)(n - p);
+}
+
 __global__ void k_values(const uint64_t* __restrict__ ukeys, int64_t nnz, int colbits, const float* __restrict__ dinv,
                          float* __restrict__ val) {
-  int64_t p = block_id() * blockDim.x + threadIdx.x;
+  const int64_t p = (block_id() * blockDim.x + threadIdx.x) * kEntriesPerThread;
   if (p >= nnz) return;
-  const uint64_t v = ukeys[p];
-  val[p] = __fmul_rn(dinv[v >> colbits], dinv[v & ((1ull << colbits) - 1ull)]);
+  const uint64_t colmask = (1ull << colbits) - 1ull;
+  uint64_t v[kEntriesPerThread];
+  const int n = load_keys(ukeys, p, nnz, v);
+  f32x4 o;
+#pragma unroll
+  for (int i = 0; i < kEntriesPerThread; ++i) o[i] = __fmul_rn(dinv[v[i] >> colbits], dinv[v[i] & colmask]);
+  if (n == kEntriesPerThread) *reinterpret_cast<f32x4*>(val + p) = o;
+  else
+#pragma unroll
+    for (int i = 0; i < kEntriesPerThread; ++i)
+      if (i < n) val[p + i] = o[i];
 }
 
 // ---- step 6: column-major copy ------------------------------------------------------------------------
 // The entries sorted by column, those of a column still in row order; a value is computed again, from the same two
 // factors, instead of being carried through the sort or fetched from its row-major place (124 us for 11.8 M entries).
-__global__ void k_finish_csc(const uint64_t* __restrict__ tkeys, int64_t nnz, int colbits, const float* __restrict__ dinv,
-                             int32_t* __restrict__ rowidx, float* __restrict__ val_t) {
-  int64_t q = block_id() * blockDim.x + threadIdx.x;
+// Also the column pointers: colptr[c] = first entry of a column >= c.
+__global__ void k_finish_csc(const uint64_t* __restrict__ tkeys, int64_t nnz, int colbits, const float* __restrict__ dinv, int64_t nc,
+                             int32_t* __restrict__ rowidx, float* __restrict__ val_t, int64_t* __restrict__ colptr) {
+  const int64_t q = (block_id() * blockDim.x + threadIdx.x) * kEntriesPerThread;
   if (q >= nnz) return;
-  const uint64_t v = tkeys[q];
-  rowidx[q] = (int32_t)(v >> colbits);
-  val_t[q] = __fmul_rn(dinv[v >> colbits], dinv[v & ((1ull << colbits) - 1ull)]);
+  const uint64_t colmask = (1ull << colbits) - 1ull;
+  uint64_t v[kEntriesPerThread];
+  const int n = load_keys(tkeys, q, nnz, v);
+  int64_t before = q ? (int64_t)(tkeys[q - 1] & colmask) : -1;
+  i32x4 r; f32x4 o;
+#pragma unroll
+  for (int i = 0; i < kEntriesPerThread; ++i) {
+    const int64_t c = (int64_t)(v[i] & colmask);
+    r[i] = (int32_t)(v[i] >> colbits);
+    o[i] = __fmul_rn(dinv[v[i] >> colbits], dinv[c]);
+    if (i < n)
+      for (; before < c; ++before) colptr[before + 1] = q + i;
+  }
+  if (q + n == nnz)
+    for (; before < nc; ++before) colptr[before + 1] = nnz;
+  if (n == kEntriesPerThread) {
+    *reinterpret_cast<i32x4*>(rowidx + q) = r;
+    *reinterpret_cast<f32x4*>(val_t + q) = o;
+  } else {
+#pragma unroll
+    for (int i = 0; i < kEntriesPerThread; ++i)
+      if (i < n) { rowidx[q + i] = r[i]; val_t[q + i] = o[i]; }
+  }
 }
 
 // ---- schedules ------------------------------------------------------------------------------------------
@@ -235,7 +293,7 @@ __global__ void k_finish_csc(const uint64_t* __restrict__ tkeys, int64_t nnz, in
 constexpr int kSchedSlots = 16;
 constexpr int kSchedCodes = 13;                      // classes of ordinary rows
 constexpr int kHubCode = 13, kChunkSlot = 14;
-constexpr int kSchedSteps = 8;                       // rows per lane
+constexpr int kSchedSteps = 2;                       // rows per lane (8: longer code, 13 instead of 5 us for 40 K rows)
 constexpr int kSchedTile = kThreads * kSchedSteps;   // rows per block; a wavefront takes 64 kSchedSteps consecutive ones
 // What the host keeps: kSchedCodes + 1 class boundaries, then for each row boundary of the launches on row ranges the first
 // position of every class, the first hub row and its first chunk at or behind that row, then the number of hub rows and of chunks.
@@ -502,10 +560,100 @@ struct ScheduleBuild {
   }
 };
 
-static int bits_for(int64_t max_value_exclusive) {   // smallest b with 2^b - 1 > max_value_exclusive - 1 ... i.e. 2^b > max_value_exclusive
+int key_bits(int64_t n) {              // smallest b >= 1 with 2^b >= n
   int b = 1;
-  while ((1LL << b) <= max_value_exclusive) ++b;
+  while ((1LL << b) < n) ++b;
   return b;
+}
+
+static int64_t uniq_blocks(int64_t m) { return ceil_div(m, kUniqTile); }
+size_t key_words_bytes(int64_t m) { return sizeof(int64_t) * (size_t)(uniq_blocks(m) + 3); }
+int64_t* key_verdict(const DevBuf& words, int64_t m) { return words.as<int64_t>() + uniq_blocks(m) + 1; }
+
+static int verdict(int64_t v) {
+  if (v & 1) return fail(GCN_EINVAL, "gcn_csr_build: a vertex id lies outside [0, n_global)");
+  if (v & 2) return fail(GCN_EINVAL, "gcn_csr_build: d_deg_global holds a degree < 1");
+  return GCN_OK;
+}
+
+int build_from_keys(const KeyBuild& in, CallScope& sc, PinnedPage& page, gcn_csr* A) {
+  hipStream_t s = sc.s;
+  const int64_t nr = in.nr, nh = in.nh, nc = nr + nh, m = in.m;
+  const int colbits = key_bits(nc), rowbits = key_bits(nr);
+  int64_t* read = page.words();
+  uint64_t *keys_a = in.keys_a->as<uint64_t>(), *keys_b = in.keys_b->as<uint64_t>();
+  const int64_t nb = uniq_blocks(m);
+  DevBuf tmp, cnt;
+  GCN_TRY(tmp.alloc(sc, std::max(sort_tmp_bytes(m), scan_tmp_bytes(nb))));
+  GCN_TRY(cnt.alloc(sc, sizeof(uint32_t) * (size_t)nb));
+  // behind the offsets of the blocks: the number of entries, the verdict on the ids, the number of keys sorted
+  int64_t* off = in.words->as<int64_t>();
+  int64_t* bad = off + nb + 1;
+  int64_t* kept = off + nb + 2;
+  uint64_t* sorted = nullptr;
+  GCN_TRY(radix_sort_u64(keys_a, keys_b, nullptr, nullptr, m, 0, colbits + rowbits, tmp.p, s, &sorted, nullptr, in.count,
+                         in.count ? nullptr : kept));
+  const int64_t* count = in.count ? in.count : kept;
+  uint64_t* ukeys = sorted == keys_a ? keys_b : keys_a;       // unique keys, row-major order
+  k_count_unique<<<fold_grid(nb), kThreads, 0, s>>>(sorted, count, nb, cnt.as<uint32_t>());
+  GCN_CHECK_LAUNCH();
+  GCN_TRY(exclusive_scan_u32(cnt.as<uint32_t>(), off, nb, tmp.p, s));
+  GCN_HIP(hipMemcpyAsync(read, off + nb, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  GCN_HIP(hipStreamSynchronize(s));
+  if (!in.count) GCN_TRY(verdict(read[1]));
+  const int64_t nnz = read[0];
+  if (nnz < nr) return fail(GCN_EHIP, "gcn_csr_build: internal error (nnz %lld < rows %lld)", (long long)nnz, (long long)nr);
+  if (nnz >= 0xffffffffLL) return fail(GCN_EINVAL, "gcn_csr_build: more than 2^32-2 stored entries in one block");
+
+  DevBuf rowptr, col, val, deg, dinv;
+  GCN_TRY(rowptr.alloc(sc, sizeof(int64_t) * (size_t)(nr + 1)));
+  GCN_TRY(col.alloc(sc, sizeof(int32_t) * (size_t)nnz + kEntrySlack));
+  GCN_TRY(val.alloc(sc, sizeof(float) * (size_t)nnz + kEntrySlack));
+  GCN_TRY(deg.alloc(sc, sizeof(int32_t) * (size_t)nr));
+  GCN_TRY(dinv.alloc(sc, sizeof(float) * (size_t)nc));
+  k_compact<<<fold_grid(nb), kThreads, 0, s>>>(sorted, off, count, nb, colbits, nnz, ukeys, col.as<int32_t>(), rowptr.as<int64_t>());
+  k_degrees<<<grid_for(nc), kThreads, 0, s>>>(rowptr.as<int64_t>(), nr, nc, in.deg_global, in.halo_gid->as<int32_t>(), deg.as<int32_t>(),
+                                               dinv.as<float>());
+  k_values<<<grid_for(ceil_div(nnz, kEntriesPerThread)), kThreads, 0, s>>>(ukeys, nnz, colbits, dinv.as<float>(), val.as<float>());
+  GCN_CHECK_LAUNCH();
+
+  DevBuf mid;
+  if (nh > 0) {
+    GCN_TRY(mid.alloc(sc, sizeof(int64_t) * (size_t)nr));
+    k_row_mid<<<grid_for(nr), kThreads, 0, s>>>(rowptr.as<int64_t>(), col.as<int32_t>(), nr, mid.as<int64_t>());
+    GCN_CHECK_LAUNCH();
+  }
+
+  // -- column-major copy
+  DevBuf colptr, rowidx, val_t;
+  if (in.flags & GCN_BUILD_CSC) {
+    GCN_TRY(colptr.alloc(sc, sizeof(int64_t) * (size_t)(nc + 1)));
+    GCN_TRY(rowidx.alloc(sc, sizeof(int32_t) * (size_t)nnz + kEntrySlack));
+    GCN_TRY(val_t.alloc(sc, sizeof(float) * (size_t)nnz + kEntrySlack));
+    uint64_t* tsorted = nullptr;           // (the buffer of the keys with duplicates is free again)
+    GCN_TRY(radix_sort_u64(ukeys, sorted, nullptr, nullptr, nnz, 0, colbits, tmp.p, s, &tsorted, nullptr));
+    k_finish_csc<<<grid_for(ceil_div(nnz, kEntriesPerThread)), kThreads, 0, s>>>(tsorted, nnz, colbits, dinv.as<float>(), nc,
+                                                                                 rowidx.as<int32_t>(), val_t.as<float>(), colptr.as<int64_t>());
+    GCN_CHECK_LAUNCH();
+  }
+  ScheduleBuild sched;
+  GCN_TRY(sched.add(rowptr.as<int64_t>(), nr, nnz, sc));
+  if (in.flags & GCN_BUILD_CSC) GCN_TRY(sched.add(colptr.as<int64_t>(), nc, nnz, sc));
+  GCN_TRY(sched.enqueue(sc, read));
+  GCN_HIP(hipStreamSynchronize(s));
+  sc.done = true;
+
+  A->n_global = in.n_global; A->row_lo = in.row_lo;
+  A->nr = nr; A->nh = nh; A->nc = nc; A->nnz = nnz;
+  sched.finish(0, &A->sched);
+  if (in.flags & GCN_BUILD_CSC) sched.finish(1, &A->sched_t);
+  A->rowptr = (int64_t*)rowptr.release(); A->col = (int32_t*)col.release();
+  A->val = (float*)val.release(); A->deg = (int32_t*)deg.release();
+  A->halo_gid = (int32_t*)in.halo_gid->release();
+  A->colptr = (int64_t*)colptr.release(); A->rowidx = (int32_t*)rowidx.release();
+  A->val_t = (float*)val_t.release();
+  A->mid = nh > 0 ? (int64_t*)mid.release() : nullptr;
+  return GCN_OK;
 }
 
 static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edges, int64_t n_global,
@@ -522,28 +670,21 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   // -- validation and halo bitmap.  A whole graph has no halo, and its ids are checked while its keys are made: the
   // verdict is read with the number of entries, and what is enqueued until then uses no id as an index.
   const int64_t words = ceil_div(n_global, 32);
-  DevBuf bad, bitmap, wcnt, wprefix, tmp;
-  GCN_TRY(bad.alloc(sc, sizeof(int64_t)));
-  size_t tb = sort_tmp_bytes(m);
-  if (scan_tmp_bytes(m) > tb) tb = scan_tmp_bytes(m);
-  if (scan_tmp_bytes(words) > tb) tb = scan_tmp_bytes(words);
-  GCN_TRY(tmp.alloc(sc, tb));
-  GCN_HIP(hipMemsetAsync(bad.p, 0, sizeof(int64_t), s));
-  if (d_deg_global) k_validate_deg<<<grid_for(n_global), kThreads, 0, s>>>(d_deg_global, n_global, bad.as<int>());
-  auto verdict = [&](int64_t v) {
-    if (v & 1) return fail(GCN_EINVAL, "gcn_csr_build: a vertex id lies outside [0, n_global)");
-    if (v & 2) return fail(GCN_EINVAL, "gcn_csr_build: d_deg_global holds a degree < 1");
-    return (int)GCN_OK;
-  };
+  DevBuf off, bitmap, wcnt, wprefix, tmp;
+  GCN_TRY(off.alloc(sc, key_words_bytes(m)));
+  int64_t* bad = key_verdict(off, m);
+  GCN_HIP(hipMemsetAsync(bad, 0, sizeof(int64_t), s));
+  if (d_deg_global) k_validate_deg<<<grid_for(n_global), kThreads, 0, s>>>(d_deg_global, n_global, (int*)bad);
   int64_t nh = 0;
   if (!whole) {
+    GCN_TRY(tmp.alloc(sc, scan_tmp_bytes(words)));
     GCN_TRY(bitmap.alloc(sc, sizeof(uint32_t) * (size_t)words));
     GCN_TRY(wcnt.alloc(sc, sizeof(uint32_t) * (size_t)words));
     GCN_TRY(wprefix.alloc(sc, sizeof(int64_t) * (size_t)(words + 1)));
     GCN_HIP(hipMemsetAsync(bitmap.p, 0, sizeof(uint32_t) * (size_t)words, s));
-    if (n_edges > 0) k_validate<<<grid_for(n_edges), kThreads, 0, s>>>(d_src, d_dst, n_edges, n_global, bad.as<int>());
+    if (n_edges > 0) k_validate<<<grid_for(n_edges), kThreads, 0, s>>>(d_src, d_dst, n_edges, n_global, (int*)bad);
     GCN_CHECK_LAUNCH();
-    GCN_HIP(hipMemcpyAsync(read, bad.p, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    GCN_HIP(hipMemcpyAsync(read, bad, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     GCN_HIP(hipStreamSynchronize(s));
     GCN_TRY(verdict(read[0]));
     if (n_edges > 0) k_mark_halo<<<grid_for(n_edges), kThreads, 0, s>>>(d_src, d_dst, n_edges, row_lo, row_hi, bitmap.as<uint32_t>());
@@ -561,85 +702,20 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
   if (nh > 0) k_halo_list<<<grid_for(words), kThreads, 0, s>>>(bitmap.as<uint32_t>(), wprefix.as<int64_t>(), words, halo_gid.as<int32_t>());
   GCN_CHECK_LAUNCH();
 
-  // -- keys, sort, unique
-  const int colbits = bits_for(nc);
-  const int rowbits = bits_for(nr);
-  if (colbits + rowbits > 62) return fail(GCN_EINVAL, "gcn_csr_build: block too large for 64-bit sort keys");
-  DevBuf keys_a, keys_b, cnt, off;
+  // -- keys
+  const int colbits = key_bits(nc);
+  if (colbits + key_bits(nr) > 62) return fail(GCN_EINVAL, "gcn_csr_build: block too large for 64-bit sort keys");
+  DevBuf keys_a, keys_b;
   GCN_TRY(keys_a.alloc(sc, sizeof(uint64_t) * (size_t)m));
   GCN_TRY(keys_b.alloc(sc, sizeof(uint64_t) * (size_t)m));
   k_make_keys<<<grid_for(m), kThreads, 0, s>>>(d_src, d_dst, n_edges, row_lo, row_hi, nr, colbits,
-                                                bitmap.as<uint32_t>(), wprefix.as<int64_t>(), keys_a.as<uint64_t>(), bad.as<int>());
+                                                bitmap.as<uint32_t>(), wprefix.as<int64_t>(), keys_a.as<uint64_t>(), (int*)bad);
   GCN_CHECK_LAUNCH();
-  uint64_t* sorted = nullptr;
-  GCN_TRY(radix_sort_u64(keys_a.as<uint64_t>(), keys_b.as<uint64_t>(), nullptr, nullptr, m, 0, colbits + rowbits,
-                         tmp.p, s, &sorted, nullptr));
-  uint64_t* other = (sorted == keys_a.as<uint64_t>()) ? keys_b.as<uint64_t>() : keys_a.as<uint64_t>();
-  const int64_t nb = ceil_div(m, kUniqTile);
-  GCN_TRY(cnt.alloc(sc, sizeof(uint32_t) * (size_t)nb));
-  GCN_TRY(off.alloc(sc, sizeof(int64_t) * (size_t)(nb + 1)));
-  k_count_unique<<<fold_grid(nb), kThreads, 0, s>>>(sorted, m, nb, cnt.as<uint32_t>());
-  GCN_CHECK_LAUNCH();
-  GCN_TRY(exclusive_scan_u32(cnt.as<uint32_t>(), off.as<int64_t>(), nb, tmp.p, s));
-  GCN_HIP(hipMemcpyAsync(read, bad.p, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipMemcpyAsync(read + 1, off.as<int64_t>() + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  GCN_HIP(hipStreamSynchronize(s));
-  GCN_TRY(verdict(read[0]));
-  const int64_t nnz = read[1];
-  if (nnz < nr) return fail(GCN_EHIP, "gcn_csr_build: internal error (nnz %lld < rows %lld)", (long long)nnz, (long long)nr);
-  if (nnz >= 0xffffffffLL) return fail(GCN_EINVAL, "gcn_csr_build: more than 2^32-2 stored entries in one block");
-
-  DevBuf rowptr, col, val, deg, dinv;
-  GCN_TRY(rowptr.alloc(sc, sizeof(int64_t) * (size_t)(nr + 1)));
-  GCN_TRY(col.alloc(sc, sizeof(int32_t) * (size_t)nnz + kEntrySlack));
-  GCN_TRY(val.alloc(sc, sizeof(float) * (size_t)nnz + kEntrySlack));
-  GCN_TRY(deg.alloc(sc, sizeof(int32_t) * (size_t)nr));
-  uint64_t* ukeys = other;                  // unique keys, row-major order
-  GCN_TRY(dinv.alloc(sc, sizeof(float) * (size_t)nc));
-  k_compact<<<fold_grid(nb), kThreads, 0, s>>>(sorted, off.as<int64_t>(), m, nb, colbits, ukeys, col.as<int32_t>());
-  k_boundaries<<<grid_for(nnz), kThreads, 0, s>>>(ukeys, nnz, colbits, ~0ull, nr, rowptr.as<int64_t>());
-  k_degrees<<<grid_for(nc), kThreads, 0, s>>>(rowptr.as<int64_t>(), nr, nc, d_deg_global, halo_gid.as<int32_t>(), deg.as<int32_t>(),
-                                               dinv.as<float>());
-  k_values<<<grid_for(nnz), kThreads, 0, s>>>(ukeys, nnz, colbits, dinv.as<float>(), val.as<float>());
-  GCN_CHECK_LAUNCH();
-
-  DevBuf mid;
-  if (nh > 0) {
-    GCN_TRY(mid.alloc(sc, sizeof(int64_t) * (size_t)nr));
-    k_row_mid<<<grid_for(nr), kThreads, 0, s>>>(rowptr.as<int64_t>(), col.as<int32_t>(), nr, mid.as<int64_t>());
-    GCN_CHECK_LAUNCH();
-  }
-
-  // -- column-major copy
-  DevBuf colptr, rowidx, val_t;
-  if (flags & GCN_BUILD_CSC) {
-    GCN_TRY(colptr.alloc(sc, sizeof(int64_t) * (size_t)(nc + 1)));
-    GCN_TRY(rowidx.alloc(sc, sizeof(int32_t) * (size_t)nnz + kEntrySlack));
-    GCN_TRY(val_t.alloc(sc, sizeof(float) * (size_t)nnz + kEntrySlack));
-    uint64_t* tsorted = nullptr;           // (the buffer of the keys with duplicates is free again)
-    GCN_TRY(radix_sort_u64(ukeys, sorted, nullptr, nullptr, nnz, 0, colbits, tmp.p, s, &tsorted, nullptr));
-    k_boundaries<<<grid_for(nnz), kThreads, 0, s>>>(tsorted, nnz, 0, (1ull << colbits) - 1ull, nc, colptr.as<int64_t>());
-    k_finish_csc<<<grid_for(nnz), kThreads, 0, s>>>(tsorted, nnz, colbits, dinv.as<float>(), rowidx.as<int32_t>(), val_t.as<float>());
-    GCN_CHECK_LAUNCH();
-  }
-  ScheduleBuild sched;
-  GCN_TRY(sched.add(rowptr.as<int64_t>(), nr, nnz, sc));
-  if (flags & GCN_BUILD_CSC) GCN_TRY(sched.add(colptr.as<int64_t>(), nc, nnz, sc));
-  GCN_TRY(sched.enqueue(sc, read));
-  GCN_HIP(hipStreamSynchronize(s));
-  sc.done = true;
-
-  A->n_global = n_global; A->row_lo = row_lo;
-  A->nr = nr; A->nh = nh; A->nc = nc; A->nnz = nnz;
-  sched.finish(0, &A->sched);
-  if (flags & GCN_BUILD_CSC) sched.finish(1, &A->sched_t);
-  A->rowptr = (int64_t*)rowptr.release(); A->col = (int32_t*)col.release();
-  A->val = (float*)val.release(); A->deg = (int32_t*)deg.release();
-  A->halo_gid = (int32_t*)halo_gid.release();
-  A->colptr = (int64_t*)colptr.release(); A->rowidx = (int32_t*)rowidx.release();
-  A->val_t = (float*)val_t.release();
-  A->mid = nh > 0 ? (int64_t*)mid.release() : nullptr;
-  return GCN_OK;
+  KeyBuild in;
+  in.n_global = n_global; in.row_lo = row_lo; in.nr = nr; in.nh = nh;
+  in.keys_a = &keys_a; in.keys_b = &keys_b; in.words = &off; in.m = m;
+  in.halo_gid = &halo_gid; in.deg_global = d_deg_global; in.flags = flags;
+  return build_from_keys(in, sc, page, A);
 }
 
 int segment_boundaries(const uint64_t* keys, int64_t n, int shift, int64_t n_seg, int64_t* ptr, hipStream_t s) {

@@ -90,11 +90,14 @@ def test_build_hub_rows(gcn, dev):
 
 
 @pytest.mark.parametrize("n,m", [(1, 0), (3, 2045), (200, 1848), (200, 1849), (256, 4000), (65536, 200000), (65537, 200000),
-                                 (3001, 2094150), (3001, 2094151), (70000, 2200000)])
+                                 (3001, 2094150), (3001, 2094151), (70000, 2200000),
+                                 (512, 2000), (513, 2000), (5000, 1043576), (5000, 1043577), (262144, 2100000), (262145, 2100000),
+                                 (3001, 2098247), (3001, 2098248)])
 def test_build_at_the_edges_of_sort_and_compaction(gcn, dev, n, m):
-    """Candidates (edges + diagonal) at a whole number of sort blocks and beside it (2048 keys up to 2^21 - 1 of them, 4096
-    from there on), long runs of equal keys across blocks, column numbers of 8, 9, 16 and 17 bits, more than 2^21
-    candidates of which fewer are distinct."""
+    """Candidates (edges + diagonal) at a whole number of sort blocks and beside it (2048 keys up to 2^21 - 1 of them, 6144
+    from there on), 512 and 513 short blocks (offsets found by the blocks, by a scan), long runs of equal keys across blocks,
+    column numbers of 8, 9, 10, 13, 16 to 19 bits (one to three passes), a last vertex whose diagonal is a key of all ones in
+    its bits, more than 2^21 candidates of which fewer are distinct."""
     rng = np.random.default_rng(m)
     compare(gcn, dev, rng.integers(0, n, m), rng.integers(0, n, m) ** 2 // n if n > 1 else np.zeros(m, int), n, what="edges")
 

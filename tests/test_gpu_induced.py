@@ -46,6 +46,21 @@ def check_induced(gcn, dev, A, src, dst, n, V):
     return og, B
 
 
+@pytest.mark.parametrize("total", [2047, 2048, 2049, 4096])
+@pytest.mark.parametrize("short", [True, False])
+def test_induced_at_the_edges_of_its_blocks(gcn, dev, total, short):
+    """A whole number of blocks of 2048 selected entries and beside it: in rows of one entry (as many rows as a block can
+    hold), and in one row that fills a block followed by rows of one."""
+    n = 6000
+    hub = np.zeros(0, np.int64) if short else np.arange(1, 2048)         # vertex 0: 2048 entries with its diagonal
+    src, dst = np.zeros(hub.size, np.int64), hub
+    A = gcn.gcn_csr_build(dev_i32(src, dev), dev_i32(dst, dev), n)
+    V = np.r_[0, np.arange(n)[::-1][:total - (1 if short else 2048)]] if total > 2048 or short else np.r_[0, 5]
+    _, B = check_induced(gcn, dev, A, src, dst, n, V)
+    B.free()
+    A.free()
+
+
 @pytest.mark.parametrize("n,m,k,directed,seed", [
     (64, 300, 1, True, 1), (500, 4000, 37, True, 2), (5000, 60000, 1000, False, 3), (30000, 400000, 30000, True, 4),
     (30000, 400000, 4096, False, 5), (100000, 2000000, 25000, True, 6)])

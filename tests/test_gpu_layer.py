@@ -409,10 +409,10 @@ def test_middle_sized_block_does_not_depend_on_the_second_stream(gcn, dev, middl
             gcn.gcn_debug_set_tuning(name, None)
 
 
-@pytest.mark.parametrize("n", [63, 64, 65, 511, 512, 513, 2047, 2048, 2049, 4097, 8320])
+@pytest.mark.parametrize("n", [63, 64, 65, 127, 128, 129, 511, 512, 513, 2050, 8320])
 def test_schedule_lists_at_the_edges_of_its_blocks(gcn, dev, n):
     """Rows of every length class (1, 2, 3 .. 1023, and from 2049 vertices on more than 2048 entries) at row counts around a
-    step (64 rows), a wavefront (512) and a block (2048) of the schedule's counting sort: the product on the whole matrix,
+    step (64 rows), a wavefront (128) and a block (512) of the schedule's counting sort: the product on the whole matrix,
     on 8 row ranges, and with the transposed arrays."""
     src, dst = hub_graph(n, 3, 2.0, n)
     lens = np.minimum(2 ** np.arange(3, 10), n - 1)
