@@ -78,8 +78,7 @@ static int pick_slices(const SpmmArgs& a, size_t es, int V, bool short_rows, int
   return S;
 }
 
-int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s) {
-  SpmmK k{};
+int spmm_setup(const SpmmArgs& a, void* ws, SpmmK& k, SpmmProf& pf, int* V_out, bool* narrow_out) {
   k.ptr = a.ptr; k.idx = a.idx; k.val = a.val;
   k.lo = a.part == 2 ? a.mid : a.ptr;
   k.hi = a.part == 1 ? a.mid : a.ptr + 1;
@@ -90,7 +89,6 @@ int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s) {
   k.X = a.X; k.ldx = a.ldx; k.Y = a.Y; k.ldy = a.ldy; k.Y2 = a.Y2; k.ldy2 = a.ldy2;
   k.bias = a.bias; k.Zprev = a.Zprev; k.ldz = a.ldz; k.n_mask_rows = a.n_mask_rows;
   k.partial = (float*)ws; k.d = a.d; k.epilogue = a.epilogue;
-  if (a.n_rows == 0) return GCN_OK;
   if (a.row_chunk >= 0 && (a.row_chunk_n < 1 || a.row_chunk + a.row_chunk_n > kRowChunks)) return fail(GCN_EINVAL, "spmm: no such row chunks");
   const int rc1 = a.row_chunk + a.row_chunk_n;
   if (a.row_chunk >= 0) {          // the long rows of this row range, and their chunks of entries
@@ -98,10 +96,6 @@ int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s) {
     k.chunk_lo = sc->chunk_hubchunk_begin[a.row_chunk]; k.n_chunks = sc->chunk_hubchunk_begin[rc1] - k.chunk_lo;
     k.hub_lo = sc->chunk_hub_begin[a.row_chunk]; k.n_hub_rows = sc->chunk_hub_begin[rc1] - k.hub_lo;
   }
-  bool swept = false;
-  // the column-sweep plan covers whole rows of the whole matrix only
-  if (a.part == 0 && !a.no_alloc && a.row_chunk < 0) GCN_TRY(spmm_panel_try(a, s, &swept));
-  if (swept) return GCN_OK;
   const size_t es = a.dtype == GCN_BF16 ? 2 : 4;
   // Widest vector the rows admit: 16 bytes where they start on a 4-byte word and are at least that long.  The last
   // vector of a row that is no whole number of vectors reads into the row's padding where that is allowed, else it is
@@ -133,7 +127,6 @@ int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s) {
   k.short_rows = V * (int)es == 16 && k.nvec > 8 && k.nvec <= 16 && (tune().spmm_short >= 0 ? tune().spmm_short != 0 : mean_len < 16.0);
   k.S = pick_slices(a, es, V, k.short_rows != 0, &k.vps);
   if (k.vps <= 0) k.vps = (int)ceil_div(k.nvec, k.S);
-  SpmmProf pf;
   pf.kind = a.transposed ? GCN_K_SPMM_T : GCN_K_SPMM; pf.dtype = a.dtype; pf.rows = a.n_rows; pf.nnz = pf.whole_nnz = a.nnz; pf.whole_rows = a.n_rows;
   const double csr = 8.0 * (double)a.nnz + 8.0 * (double)(a.n_rows + 1), fe = (double)es * a.d;
   pf.alg = csr + fe * (double)(a.n_cols + a.n_rows);
@@ -153,6 +146,21 @@ int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s) {
                       !tune().spmm_wide;
   k.row_bytes = narrow ? (uint32_t)(a.ldx * (int64_t)es) : 0u;
   k.x_bytes = narrow ? (uint32_t)(a.n_cols * a.ldx * (int64_t)es) : 0u;
+  *V_out = V; *narrow_out = narrow;
+  return GCN_OK;
+}
+
+int spmm_launch(const SpmmArgs& a, void* ws, hipStream_t s) {
+  if (a.n_rows == 0) return GCN_OK;
+  bool swept = false;
+  // the column-sweep plan covers whole rows of the whole matrix only
+  if (a.part == 0 && !a.no_alloc && a.row_chunk < 0) GCN_TRY(spmm_panel_try(a, s, &swept));
+  if (swept) return GCN_OK;
+  SpmmK k{};
+  SpmmProf pf;
+  int V = 1;
+  bool narrow = false;
+  GCN_TRY(spmm_setup(a, ws, k, pf, &V, &narrow));
   if (a.dtype == GCN_BF16) return spmm_dispatch_bf16(k, a.sched, pf, V, narrow, s);
   return spmm_dispatch_f32(k, a.sched, pf, V, narrow, s);
 }

@@ -89,7 +89,8 @@ struct SpmmK {
   int short_rows;     // rows are short: two vectors per lane, so that a wavefront takes more rows (launch_v)
   // ordinary rows: bin b holds the rows wave_rows[bin_row_begin[b] .. bin_row_end[b]) of one length
   // class; 2^bin_log2gr[b] lane groups share a row, so a wavefront takes G >> bin_log2gr[b] rows and
-  // the bin's wavefronts are numbered from bin_wave_begin[b].
+  // the bin's wavefronts are numbered from bin_wave_begin[b].  More than all groups of a wavefront (2^bin_log2gr[b] > G): the
+  // four wavefronts of a block share a row, a quarter of its entries each.
   int64_t n_waves;
   int64_t bin_wave_begin[kMaxBins];      // n_waves where there is no such bin
   int64_t bin_row_begin[kMaxBins];
@@ -269,7 +270,9 @@ __device__ __forceinline__ void finish_vector(const SpmmK& a, int64_t row, int64
   store_vec<T, V>(reinterpret_cast<T*>(a.Y) + row * a.ldy + c0, v);
 }
 
-template <typename T, int V, int LPR, int NV, bool NARROW>
+// BLOCKS: there are rows that take a block each (make_bins).  A product without them, which large ones are, keeps the shorter
+// kernel: with the branch and its code in the same instance R-MAT 2^18 and 500 K short rows lost 0.6 %.
+template <typename T, int V, int LPR, int NV, bool NARROW, bool BLOCKS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_spmm(SpmmK a) {
   constexpr int G = 64 / LPR;
   constexpr int kLog2G = G == 1 ? 0 : G == 2 ? 1 : G == 4 ? 2 : G == 8 ? 3 : G == 16 ? 4 : G == 32 ? 5 : 6;
@@ -295,17 +298,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   // allowed (its leading elements then repeat the vector before it and are not stored)
   auto column = [&](int vi) -> int { return vi == a.nvec - 1 ? a.c_last : vi * V; };
 
-  if (item < a.n_chunks) {
-    // ---- hub chunk: the whole block works on kHubChunkNnz entries of one long row
-    const int64_t c = a.chunk_lo + item;
-    const int32_t h = a.chunk_hub[c];
-    const int64_t row = a.hub_rows[h];
-    const int64_t cs = a.ptr[row] + (c - a.hub_chunk_ptr[h]) * kHubChunkNnz;      // chunks are cut from the whole row
-    const int64_t row_lo = a.lo[row], row_hi = a.hi[row];
-    const int64_t s = cs > row_lo ? cs : row_lo;
-    const int64_t e = cs + kHubChunkNnz < row_hi ? cs + kHubChunkNnz : row_hi;
-    const int64_t ws = s + (int64_t)w * (kHubChunkNnz / 4);
-    const int64_t we = ws + kHubChunkNnz / 4 < e ? ws + kHubChunkNnz / 4 : e;
+  const bool chunk = item < a.n_chunks;
+  const int64_t wi = (item - a.n_chunks) * 4 + w;
+  int b = -1;
+  // ---- a block on one row: a run of entries per wavefront, which meet in LDS
+  auto on_one_row = [&]() {
+    int64_t row, ws; int n; float* partial = nullptr;
+    if (chunk) {           // kHubChunkNnz entries of a hub row
+      const int64_t c = a.chunk_lo + item;
+      const int32_t h = a.chunk_hub[c];
+      row = a.hub_rows[h];
+      const int64_t cs = a.ptr[row] + (c - a.hub_chunk_ptr[h]) * kHubChunkNnz;      // chunks are cut from the whole row
+      const int64_t row_lo = a.lo[row], row_hi = a.hi[row];
+      const int64_t s = cs > row_lo ? cs : row_lo;
+      const int64_t e = cs + kHubChunkNnz < row_hi ? cs + kHubChunkNnz : row_hi;
+      ws = s + (int64_t)w * (kHubChunkNnz / 4);
+      const int64_t we = ws + kHubChunkNnz / 4 < e ? ws + kHubChunkNnz / 4 : e;
+      n = ws < we ? (int)(we - ws) : 0;
+      partial = a.partial + c * a.d;
+    } else {               // a whole row: these bins come first, four wavefronts a row, so that all are of one block
+      row = a.wave_rows[a.bin_row_begin[b] + (wi - a.bin_wave_begin[b]) / 4];
+      const int64_t s = a.lo[row];
+      const int all = (int)(a.hi[row] - s), quarter = (all + 3) >> 2, left = all - w * quarter;
+      ws = s + (int64_t)w * quarter;
+      n = left < 0 ? 0 : left < quarter ? left : quarter;
+    }
     for (int t0 = v_lo; t0 < v_hi; t0 += TV) {
       uint32_t c0b[NV];
       float acc[NV][V];
@@ -316,7 +333,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[q][v] = 0.f;
       }
-      team_accumulate<T, V, LPR, NV, NARROW, kLog2G>(a, xb, a.idx + ws, a.val + ws, ws < we ? (int)(we - ws) : 0, kLog2G, 0, g, lane, c0b, acc);
+      team_accumulate<T, V, LPR, NV, NARROW, kLog2G>(a, xb, a.idx + ws, a.val + ws, n, kLog2G, 0, g, lane, c0b, acc);
       reduce_groups<V, LPR, NV>(acc, G);
       if (g == 0) {
 #pragma unroll
@@ -331,22 +348,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
       __syncthreads();
       const int f0 = t0 * V;
       const int f_end = v_hi * V < a.d ? v_hi * V : a.d;
-      for (int f = threadIdx.x; f < TW && f0 + f < f_end; f += 256)
-        a.partial[c * a.d + f0 + f] = (part[0][f] + part[1][f]) + (part[2][f] + part[3][f]);
+      for (int f = threadIdx.x; f < TW && f0 + f < f_end; f += 256) {
+        const float v = (part[0][f] + part[1][f]) + (part[2][f] + part[3][f]);
+        if (chunk) partial[f0 + f] = v;
+        else finish_element<T>(a, row, f0 + f, v);
+      }
       __syncthreads();
     }
-    return;
+  };
+  if constexpr (!BLOCKS) {
+    if (chunk) { on_one_row(); return; }
   }
-
-  // ---- ordinary rows: a wavefront takes R = G >> lgr rows of one length class
-  const int64_t wi = (item - a.n_chunks) * 4 + w;
   if (wi >= a.n_waves) return;
   // the bin of this wavefront: counted over all bins with their limits in scalar registers (a search would be a chain of
   // dependent loads of the arguments)
-  int b = -1;
 #pragma unroll
   for (int i = 0; i < kMaxBins; ++i) b += wi >= a.bin_wave_begin[i] ? 1 : 0;
-  const int lgr = a.bin_log2gr[b];
+  const int lgr = BLOCKS && chunk ? kLog2G + 1 : a.bin_log2gr[b];
+  if constexpr (BLOCKS) {
+    if (lgr > kLog2G) { on_one_row(); return; }
+  }
+
+  // ---- ordinary rows: a wavefront takes R = G >> lgr rows of one length class
   const int groups = 1 << lgr;
   const int q0 = g >> lgr, gg = g & (groups - 1);
   const int64_t ri = a.bin_row_begin[b] + (wi - a.bin_wave_begin[b]) * (G >> lgr) + q0;
@@ -414,6 +437,7 @@ struct SpmmProf {
   int kind; int dtype; int64_t rows, nnz; double alg, touched, flops;
   int row_chunk = -1, row_chunk_n = 1;   // rows Schedule::chunk_row[row_chunk .. row_chunk + row_chunk_n); -1: all rows
   int64_t whole_nnz = 0, whole_rows = 0; // of the whole matrix, also for a range of its rows
+  bool chunks_only = false;              // only the partial rows of long rows: another kernel adds them up
 };
 
 // Entries each lane group should get before a row is shared by more groups (GCN_SPMM_EPG overrides, for
@@ -430,15 +454,22 @@ constexpr int kFullWaves = 2048;
 
 static inline int pow2_ceil_i(int x) { int p = 1; while (p < x) p <<= 1; return p; }
 
-template <typename T, int V, int LPR, int NV>
-static int launch_l(SpmmK& k, const Schedule* sc, const SpmmProf& pf, bool narrow, hipStream_t s) {
-  constexpr int G = 64 / LPR;
+// The length classes of the ordinary rows: how many of a wavefront's g_max lane groups share a row of each, and the
+// wavefronts they take.  Returns the number of classes, or -1; *blocks: some rows take a block each.
+static inline int make_bins(SpmmK& k, const Schedule* sc, const SpmmProf& pf, int g_max, bool narrow, bool* blocks) {
+  bool block_rows = false;
   // A product too small to fill the chip is bound by the chain of gathers of a row: its rows are shared by more groups.
   // (by the whole matrix: the sharing sets the order of a row's additions, which may not depend on how many launches the
   // product is made of)
   int epg = tune().spmm_epg > 0 ? tune().spmm_epg : kEntriesPerGroup;
   if (tune().spmm_epg <= 0)
-    while (epg > kFewestPerGroup && std::max(pf.whole_rows, pf.whole_nnz / epg) * k.S < (int64_t)kFullWaves * G) epg >>= 1;
+    while (epg > kFewestPerGroup && std::max(pf.whole_rows, pf.whole_nnz / epg) * k.S < (int64_t)kFullWaves * g_max) epg >>= 1;
+  // Rows whose gathers, one after the other in a wavefront, would take half as long as the whole product does: a block each.
+  // A round of gathers (4 per group) takes about 0.6 us, the product its gathered bytes at 6 TB/s and a launch.  us without /
+  // with: R-MAT 8 K rows of 20, width 128 48 / 18, 25 K of 5 69 / 24, bf16 25 K of 20 63 / 23; log-normal 8 K of 45, width 256
+  // 113 / 40; 315 products of 2.5 K to 262 K rows and widths 7 to 256 0.84 in the geometric mean; uniform rows have none.
+  const double whole_us = 5.0 + (double)pf.whole_nnz * k.d * (pf.dtype == GCN_BF16 ? 2 : 4) / 6e6;
+  const int64_t block_from = std::max<int64_t>((int64_t)(4 * g_max * whole_us / (2 * 0.6)), std::max(epg, 16) * g_max);
   // bins of the ordinary rows: class c holds lengths in [2^(31-c), 2^(32-c)), class 32 empty rows
   int n_bins = 0;
   int64_t waves = 0;
@@ -446,30 +477,44 @@ static int launch_l(SpmmK& k, const Schedule* sc, const SpmmProf& pf, bool narro
     const int64_t row_begin = pf.row_chunk < 0 ? sc->class_begin[c] : sc->chunk_class_begin[pf.row_chunk][c];
     const int64_t row_end = pf.row_chunk < 0 ? sc->class_begin[c + 1] : sc->chunk_class_begin[pf.row_chunk + pf.row_chunk_n][c];
     const int64_t cnt = row_end - row_begin;
-    if (cnt <= 0) continue;
-    if (n_bins == kMaxBins) return fail(GCN_EINVAL, "spmm: more length classes than expected");
+    if (cnt <= 0 || pf.chunks_only) continue;
+    if (n_bins == kMaxBins) return -1;
     const int64_t len_hi = c >= 32 ? 0 : ((int64_t)1 << (32 - c)) - 1;
     const int64_t want = ceil_div(len_hi > 0 ? len_hi : 1, epg);
-    int groups = pow2_ceil_i((int)(want < G ? want : G));
-    if (groups > G) groups = G;
+    int groups = pow2_ceil_i((int)(want < g_max ? want : g_max));
+    if (groups > g_max) groups = g_max;
     int lg = 0; while ((1 << lg) < groups) ++lg;
+    const bool whole_block = narrow && (len_hi + 1) / 2 >= block_from;
+    block_rows |= whole_block;
+    if (whole_block) ++lg;               // (groups is g_max: block_from is a wavefront's share and more)
     const int b = n_bins++;
     k.bin_wave_begin[b] = waves;
     k.bin_row_begin[b] = row_begin;
     k.bin_row_end[b] = row_end;
     k.bin_log2gr[b] = lg;
-    waves += ceil_div(cnt, G >> lg);
+    waves += whole_block ? 4 * cnt : ceil_div(cnt, g_max >> lg);
   }
   for (int b = n_bins; b < kMaxBins; ++b) { k.bin_wave_begin[b] = waves; k.bin_row_begin[b] = k.bin_row_end[b] = 0; k.bin_log2gr[b] = 0; }
   k.n_waves = waves;
+  *blocks = block_rows;
+  return n_bins;
+}
+
+template <typename T, int V, int LPR, int NV>
+static int launch_l(SpmmK& k, const Schedule* sc, const SpmmProf& pf, bool narrow, hipStream_t s) {
+  constexpr int G = 64 / LPR;
+  bool own_blocks = false;
+  if (make_bins(k, sc, pf, G, narrow, &own_blocks) < 0) return fail(GCN_EINVAL, "spmm: more length classes than expected");
+  const int64_t waves = k.n_waves;
   const int64_t blocks = (k.n_chunks + ceil_div(waves, 4)) * k.S;
   if (!grid_fits(blocks)) return fail(GCN_EINVAL, "spmm: too many rows for one launch");
   if (blocks > 0) {
     ProfScope ps(pf.kind, s, k.d, pf.dtype, pf.rows, pf.nnz, pf.alg, pf.touched, pf.flops);
-    if (narrow) k_spmm<T, V, LPR, NV, true><<<fold_grid(blocks), dim3(256), 0, s>>>(k);
-    else k_spmm<T, V, LPR, NV, false><<<fold_grid(blocks), dim3(256), 0, s>>>(k);
+    if (own_blocks) k_spmm<T, V, LPR, NV, true, true><<<fold_grid(blocks), dim3(256), 0, s>>>(k);
+    else if (narrow) k_spmm<T, V, LPR, NV, true, false><<<fold_grid(blocks), dim3(256), 0, s>>>(k);
+    else k_spmm<T, V, LPR, NV, false, false><<<fold_grid(blocks), dim3(256), 0, s>>>(k);
   }
-  if (k.n_hub_rows > 0) {
+  if (k.n_hub_rows > 0 && !pf.chunks_only) {
     const double fb = 4.0 * (double)k.n_chunks * k.d + (double)sizeof(T) * (double)k.n_hub_rows * k.d;
     ProfScope ps(GCN_K_SPMM_FINISH, s, k.d, pf.dtype, k.n_hub_rows, k.n_chunks, fb, fb, (double)k.n_chunks * k.d);
     const int64_t fw = k.n_hub_rows * ceil_div(k.d, 64);
@@ -496,6 +541,10 @@ static int launch_v(SpmmK& k, const Schedule* sc, const SpmmProf& pf, bool narro
   if (k.vps <= 32) return launch_l<T, V, 32, 1>(k, sc, pf, narrow, s);
   return launch_l<T, V, 64, 1>(k, sc, pf, narrow, s);
 }
+
+// The kernel's arguments for product a (spmm.hip): everything but the length classes.  *V: elements per request, *narrow:
+// 32-bit gather addresses.
+int spmm_setup(const SpmmArgs& a, void* ws, SpmmK& k, SpmmProf& pf, int* V, bool* narrow);
 
 // implemented in spmm_f32.hip / spmm_bf16.hip
 int spmm_dispatch_f32(SpmmK& k, const Schedule* sc, const SpmmProf& pf, int V, bool narrow, hipStream_t s);

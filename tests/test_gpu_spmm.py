@@ -115,6 +115,27 @@ def test_spmm_widths_bf16(gcn, dev, er, d):
     run_spmm(gcn, dev, er, d, bf16=True)
 
 
+@pytest.fixture(scope="module")
+def ladder(gcn, dev):
+    """Rows around every length at which a wavefront, then a block, takes a row of a small matrix: 15 .. 2049 entries."""
+    n = 2600
+    lens = [k + e for k in (16, 32, 64, 128, 256, 512, 1024, 2048) for e in (-1, 0, 1)]
+    rng = np.random.default_rng(23)
+    src = np.concatenate([np.full(k - 1, 11 * i) for i, k in enumerate(lens)])
+    dst = np.concatenate([(11 * i + 1 + rng.permutation(n - 1)[:k - 1]) % n for i, k in enumerate(lens)])
+    case = Case(gcn, dev, src, dst, n)
+    assert sorted(case.og.deg)[-len(lens):] == sorted(lens)
+    return case
+
+
+@pytest.mark.parametrize("d", [3, 8, 16, 40, 64, 128, 200, 300])
+def test_long_rows_of_a_small_matrix(gcn, dev, ladder, d):
+    run_spmm(gcn, dev, ladder, d, epilogue="relu", bias=True)
+    run_spmm(gcn, dev, ladder, d, epilogue="mask", pad=1)
+    run_spmm(gcn, dev, ladder, d, bf16=True, epilogue="mask")
+    run_spmm(gcn, dev, ladder, d, transpose=True)
+
+
 @pytest.mark.parametrize("d,pad", [(16, 1), (41, 3), (128, 2), (100, 4), (64, 8)])
 def test_spmm_padded_leading_dimension(gcn, dev, er, d, pad):
     run_spmm(gcn, dev, er, d, pad=pad)
