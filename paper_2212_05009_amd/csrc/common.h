@@ -41,6 +41,7 @@ struct Tuning {
   int spmm_slices = 0;          // feature slices of the row kernel (0: by rule)
   int spmm_epg = 0;             // entries per lane group before a row is shared by more groups (0: default)
   int spmm_short = -1;          // short-row form of the row kernel: -1 by rule, 0 never, 1 always
+  int spmm_dense = 1;           // a layer's sparse and dense product in one launch: 0 never, 1 by rule, 2 wherever the kernel applies
   int partition_sort = 0;       // partition figures by sorting even where columns can be counted
   int spmm_wide = 0;            // 64-bit gather addresses even where 32 bits suffice
   int gemm_direct = 1, gemm_fast = 1, gemm_tn_wide = 1, gemm_bf16 = 1, gemm_regw = 1;   // 0 switches a dense kernel family off
@@ -361,6 +362,11 @@ struct GemmEpilogue {
   // of the library and those of the _ld calls; else what follows column N belongs to the caller
   bool c_rows_padded = false;
 };
+// C = epilogue((A X) W) in one launch (spmm_dense.hip): sparse rows through LDS into the dense product; they are also stored
+// to a.Y where that is not null.  ws as spmm_launch; W and epi as gemm_nn's (K = a.d).
+bool spmm_dense_ok(const SpmmArgs& a, int N);
+int spmm_dense(const SpmmArgs& a, void* ws, const float* W, int64_t ldw, void* C, int64_t ldc, int N, const GemmEpilogue& epi,
+               hipStream_t s);
 // true when gemm_nn runs this product on the kernel that occupies whole compute units, one workgroup each, and
 // therefore honours GemmEpilogue::max_blocks (the rest of the chip is left to a kernel on another stream)
 bool gemm_nn_limits_blocks(const void* A, int64_t lda, int64_t M, int N, int K, int dtype);

@@ -161,6 +161,27 @@ static bool overlap_worthwhile(int64_t rows, int64_t nnz, int d) {
   return tune().overlap == 1 && rows >= (1 << 17) && (double)nnz * (double)d >= 4e9;
 }
 
+// A layer's sparse product a and the dense product of its rows by a d x N matrix as one kernel: where both are launches and chains
+// of requests rather than bytes.  A workgroup of 16 wavefronts takes 16 rows; up to 4 K rows that is one per compute unit, and
+// from there on the two kernels, which move less per row, gain on it.  One kernel over two (forward pass / backward pass, replayed
+// graph, uniform and R-MAT rows of 5 to 45 entries): up to 4 K rows fp32 0.38 to 0.9 / 0.5 to 0.95, bf16 0.58 to 1.03 / 0.6 to
+// 0.85; 8 K rows 128 -> 128 and 100 -> 50 fp32 0.54 to 1.0 / 0.6 to 0.93, 32 -> 64 0.86 to 1.12 / 0.77 to 0.87, bf16 0.86 to 1.7 / 0.7 to 1.06;
+// 16 K rows 0.82 to 2.3.
+static bool one_launch(const SpmmArgs& a, int N) {
+  const Tuning& t = tune();
+  if (t.spmm_dense == 0 || !spmm_dense_ok(a, N)) return false;
+  if (t.spmm_dense == 2) return true;
+  // (an override of a dense kernel is a choice between two-kernel forms)
+  if (t.gemm_direct != 1 || t.gemm_fast != 1 || t.gemm_bf16 != 1 || t.gemm_regw != 1 || t.gemm_tn_lds != 1) return false;
+  return a.n_rows <= (a.dtype == GCN_F32 && a.d * N >= 4096 ? 8192 : 4096) && !spmm_panel_wanted(a);
+}
+
+// May the sparse product come first, and be wider than it need be, for the sake of one launch less?  Its extra gathers come out
+// of L2 (4 K rows of 20 entries 100 -> 50: 28 MB more, 15.8 -> 7.5 us).
+static bool short_chain(const gcn_csr* A, int d_wide, int d_narrow, int dtype) {
+  return (double)A->nnz * (double)(d_wide - d_narrow) * (double)es_of(dtype) <= 64e6;
+}
+
 struct Carver {              // hands out 256-byte aligned pieces of the workspace
   char* base; size_t used = 0;
   void* take(size_t bytes) { void* p = base ? base + used : nullptr; used += align256(bytes); return p; }
@@ -186,30 +207,37 @@ static int layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
   const size_t es = es_of(dtype);
   // sparse-first costs nnz*d_in gathers and a dense product over nr rows; dense-first costs
   // nnz*d_out gathers and a dense product over nc rows
-  const bool sparse_first = AH_save != nullptr || d_in <= d_out;
+  const int64_t ldhp = padded_operand_ld(A, false, d_in, dtype, ldh);
+  SpmmArgs sparse{A->rowptr, A->col, A->val, &A->sched, A->nr, A->nc, A->nnz, false, A->nr,
+                  ldhp != ldh ? reinterpret_cast<const void*>((uintptr_t)256) : H, ldhp, nullptr, 0,
+                  nullptr, 0, d_in, dtype, GCN_EPI_NONE, nullptr, nullptr, 0};      // A H, its operand as it will be
+  sparse.owner = Am;
+  sparse.x_rows_padded = ldhp != ldh || h_backed;
+  sparse.y_rows_padded = true;              // a pitch of the outputs beyond their width comes from the _ld call
+  const bool fused = (AH_save != nullptr || d_in <= d_out || short_chain(A, d_in, d_out, dtype)) && one_launch(sparse, d_out);
+  const bool sparse_first = AH_save != nullptr || d_in <= d_out || fused;
   const int relu = act == GCN_ACT_RELU;
 
   for (int pass = 0; pass < 2; ++pass) {      // pass 0 sizes the workspace, pass 1 runs
     Carver ws{pass ? (char*)Am->ws : nullptr};
     void* hub = ws.take(spmm_ws_bytes(&A->sched, sparse_first ? d_in : d_out));
     if (sparse_first) {
-      void* AH = AH_save ? AH_save : ws.take((size_t)A->nr * d_in * es);
+      void* AH = AH_save ? AH_save : fused ? nullptr : ws.take((size_t)A->nr * d_in * es);
       const int64_t ldAH = AH_save ? ldah : (int64_t)d_in;
-      const int64_t ldhp = padded_operand_ld(A, false, d_in, dtype, ldh);
       void* Hp = ldhp != ldh ? ws.take((size_t)A->nc * ldhp * es) : nullptr;
       if (pass) {
         if (Hp) GCN_TRY(pad_rows(H, ldh, Hp, ldhp, A->nc, d_in, dtype, s));
-        SpmmArgs sp{A->rowptr, A->col, A->val, &A->sched, A->nr, A->nc, A->nnz, false, A->nr, Hp ? Hp : H, Hp ? ldhp : ldh, AH, ldAH,
-                    nullptr, 0, d_in, dtype, GCN_EPI_NONE, nullptr, nullptr, 0};
-        sp.owner = Am;
-        sp.x_rows_padded = Hp != nullptr || h_backed;
-        sp.y_rows_padded = true;            // a pitch of the outputs beyond their width comes from the _ld call
+        SpmmArgs sp = sparse;
+        if (Hp) sp.X = Hp;
+        sp.Y = AH; sp.ldy = ldAH;
         GemmEpilogue epi;
         epi.bias = bias; epi.relu = relu; epi.C2 = Z; epi.ldc2 = ldz;
         epi.c_rows_padded = true;
-        const bool pipelined = side_chunks() > 0 && overlap_worthwhile(A->nr, A->nnz, d_in) && !spmm_panel_wanted(sp) &&
+        const bool pipelined = !fused && side_chunks() > 0 && overlap_worthwhile(A->nr, A->nnz, d_in) && !spmm_panel_wanted(sp) &&
                                gemm_nn_limits_blocks(AH, ldAH, A->nr, d_out, d_in, dtype);
-        if (!pipelined) {
+        if (fused) {
+          GCN_TRY(spmm_dense(sp, hub, W, d_out, Hout, ldo, d_out, epi, s));
+        } else if (!pipelined) {
           GCN_TRY(spmm_launch(sp, hub, s));
           GCN_TRY(gemm_nn(AH, ldAH, W, d_out, Hout, ldo, A->nr, d_out, d_in, dtype, epi, s));
         } else {
@@ -282,7 +310,30 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
   const size_t es = es_of(dtype);
   const bool have_csc = A->colptr != nullptr;
   // share one transposed sparse product of width d_out between dH and dW when that is narrower
-  const bool via_T = have_csc && d_out < d_in && (dH != nullptr || AH_saved == nullptr);
+  bool via_T = have_csc && d_out < d_in && (dH != nullptr || AH_saved == nullptr);
+  // a caller's G that the sparse product cannot gather with vector requests (2-byte elements in rows that start
+  // between words, rows shorter than a vector), or only across more lines than need be, is first copied to a padded buffer
+  // (a pitched G is backed to the end of every row, the last included: the contract of the _ld entry points; so a
+  // row that is no whole number of 16-byte vectors can still be gathered with them when the pitch leaves room)
+  const bool g_rows_backed = ldg >= round_up(d_out, 16 / (int64_t)es);
+  const int64_t g_bytes = d_out * (int64_t)es;
+  const bool g_unaligned = (ldg * (int64_t)es) % 4 != 0 || ((uintptr_t)G % 4) != 0 ||
+                           (!g_rows_backed && (g_bytes % 4 != 0 || (g_bytes < 16 && (g_bytes & (g_bytes - 1)) != 0)));
+  int64_t ldgp = ldg;
+  bool fused = false;                       // T and dH in one launch
+  SpmmArgs sparse_t{};                      // A^T G, its operand as it will be
+  if (have_csc && (via_T || dH)) {
+    ldgp = g_unaligned ? gather_ld_for(A, true, d_out, dtype) : padded_operand_ld(A, true, d_out, dtype, ldg);
+    const bool pad_g = g_unaligned || ldgp != ldg;
+    sparse_t = SpmmArgs{A->colptr, A->rowidx, A->val_t, &A->sched_t, A->nc, A->nr, A->nnz, true, A->nr,
+                        pad_g ? reinterpret_cast<const void*>((uintptr_t)256) : G, ldgp, nullptr, 0, nullptr, 0, d_out, dtype,
+                        GCN_EPI_NONE, nullptr, nullptr, 0};
+    sparse_t.x_rows_padded = pad_g || g_rows_backed;
+    sparse_t.y_rows_padded = true;
+    sparse_t.owner = Am;
+    fused = dH && (via_T || d_out == d_in || short_chain(A, d_out, d_in, dtype)) && one_launch(sparse_t, d_in);
+    via_T |= fused;
+  }
 
   for (int pass = 0; pass < 2; ++pass) {
     Carver ws{pass ? (char*)Am->ws : nullptr};
@@ -295,27 +346,16 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
 
     if (via_T) {
       const int64_t ldt = round_up(d_out, 16 / (int64_t)es);
-      void* T = ws.take((size_t)A->nc * ldt * es);
+      void* T = fused && AH_saved ? nullptr : ws.take((size_t)A->nc * ldt * es);
       const int64_t kd = AH_saved ? A->nr : A->nc;
       void* tn = ws.take(gemm_tn_ws_bytes(kd, d_in, d_out));
-      // a caller's G that the sparse product cannot gather with vector requests (2-byte elements in rows that start
-      // between words, rows shorter than a vector), or only across more lines than need be, is first copied to a padded buffer
-      // (a pitched G is backed to the end of every row, the last included: the contract of the _ld entry points; so a
-      // row that is no whole number of 16-byte vectors can still be gathered with them when the pitch leaves room)
-      const bool g_rows_backed = ldg >= round_up(d_out, 16 / (int64_t)es);
-      const int64_t g_bytes = d_out * (int64_t)es;
-      const bool g_unaligned = (ldg * (int64_t)es) % 4 != 0 || ((uintptr_t)G % 4) != 0 ||
-                               (!g_rows_backed && (g_bytes % 4 != 0 || (g_bytes < 16 && (g_bytes & (g_bytes - 1)) != 0)));
-      const int64_t ldgp = g_unaligned ? gather_ld_for(A, true, d_out, dtype) : padded_operand_ld(A, true, d_out, dtype, ldg);
       const bool pad_g = g_unaligned || ldgp != ldg;
       void* Gp = pad_g ? ws.take((size_t)A->nr * ldgp * es) : nullptr;
       if (pass) {
         if (pad_g) GCN_TRY(pad_rows(G, ldg, Gp, ldgp, A->nr, d_out, dtype, s));
-        SpmmArgs sp{A->colptr, A->rowidx, A->val_t, &A->sched_t, A->nc, A->nr, A->nnz, true, A->nr, pad_g ? Gp : G,
-                    pad_g ? ldgp : ldg, T, ldt, nullptr, 0, d_out, dtype, GCN_EPI_NONE, nullptr, nullptr, 0};
-        sp.x_rows_padded = pad_g || g_rows_backed;
-        sp.y_rows_padded = true;
-        sp.owner = Am;
+        SpmmArgs sp = sparse_t;
+        if (pad_g) sp.X = Gp;
+        sp.Y = T; sp.ldy = ldt;
         // dW from a saved A^ H needs nothing of this product: it runs beside it
         SideStream side;
         const bool beside = AH_saved && overlap_worthwhile(A->nc, A->nnz, d_out) &&
@@ -324,8 +364,15 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
           GCN_TRY(side.fork(Am, s));
           GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, side.side, tune().overlap_cus));
         }
-        GCN_TRY(spmm_launch(sp, hub, s));
-        if (dH) {
+        if (fused) {
+          GemmEpilogue epi;
+          epi.mask = Zprev; epi.ldmask = ldzp; epi.mask_rows = Zprev ? A->nr : 0;
+          epi.b_trans = true;                // W^T
+          GCN_TRY(spmm_dense(sp, hub, W, d_out, dH, lddh, d_in, epi, s));
+        } else {
+          GCN_TRY(spmm_launch(sp, hub, s));
+        }
+        if (dH && !fused) {
           // owned rows carry the ReLU mask, halo rows do not: two calls, so that each is uniform in its epilogue
           GemmEpilogue epi;
           epi.mask = Zprev; epi.ldmask = ldzp; epi.mask_rows = Zprev ? A->nr : 0;

@@ -511,6 +511,7 @@ const TuneField kTuneFields[] = {
     {"GCN_PANEL_NOSYNC", &Tuning::panel_nosync, 0, 1},      {"GCN_PANEL_VERBOSE", &Tuning::panel_verbose, 0, 1},
     {"GCN_SPMM_SLICES", &Tuning::spmm_slices, 0, 8},        {"GCN_SPMM_EPG", &Tuning::spmm_epg, 0, 1 << 20},
     {"GCN_SPMM_WIDE", &Tuning::spmm_wide, 0, 1},            {"GCN_SPMM_SHORT", &Tuning::spmm_short, -1, 1},
+    {"GCN_SPMM_DENSE", &Tuning::spmm_dense, 0, 2},
     {"GCN_PARTITION_SORT", &Tuning::partition_sort, 0, 1},  {"GCN_GEMM_DIRECT", &Tuning::gemm_direct, 0, 1},
     {"GCN_GEMM_FAST", &Tuning::gemm_fast, 0, 1},            {"GCN_GEMM_TN_WIDE", &Tuning::gemm_tn_wide, 0, 1},
     {"GCN_GEMM_BF16", &Tuning::gemm_bf16, 0, 1},            {"GCN_GEMM_REGW", &Tuning::gemm_regw, 0, 2},

@@ -409,6 +409,32 @@ def test_middle_sized_block_does_not_depend_on_the_second_stream(gcn, dev, middl
             gcn.gcn_debug_set_tuning(name, None)
 
 
+@pytest.fixture(scope="module")
+def many_long_rows(gcn, dev):
+    """Eight rows of 9000 entries (more chunks than a workgroup takes by itself), the others of 9."""
+    n = 9000
+    u = np.repeat(np.arange(8), n); v = np.tile(np.arange(n), 8)
+    return Case(gcn, dev, np.r_[u, v], np.r_[v, u], n)
+
+
+@pytest.mark.parametrize("dense", [0, 2])
+@pytest.mark.parametrize("d_in,d_out", [(4, 4), (16, 8), (64, 16), (7, 30), (50, 50), (47, 100), (100, 41), (128, 128), (17, 255), (128, 256)])
+def test_layer_as_one_kernel_and_as_two(gcn, dev, er, hubs, directed_block, many_long_rows, identity, dense, d_in, d_out):
+    """The sparse product and the dense product behind it in one launch wherever that kernel applies, and never: steps of 16
+    k and of 16 columns and beside them, rows of every share of a workgroup, long rows added up by it and in chunks, halo rows."""
+    gcn.gcn_debug_set_tuning("GCN_SPMM_DENSE", dense)
+    try:
+        for case in (er, hubs, directed_block, many_long_rows, identity):
+            run_fwd(gcn, dev, case, d_in, d_out, bias=True, save_ah=True)
+            run_bwd(gcn, dev, case, d_in, d_out, saved_ah=True)
+        run_fwd(gcn, dev, er, d_in, d_out, want_z=False, act="none")
+        run_bwd(gcn, dev, directed_block, d_in, d_out, dbias=True)
+        run_fwd(gcn, dev, hubs, d_in, d_out, bf16=True)
+        run_bwd(gcn, dev, hubs, d_in, d_out, bf16=True)
+    finally:
+        gcn.gcn_debug_set_tuning("GCN_SPMM_DENSE", None)
+
+
 @pytest.mark.parametrize("n", [63, 64, 65, 127, 128, 129, 511, 512, 513, 2050, 8320])
 def test_schedule_lists_at_the_edges_of_its_blocks(gcn, dev, n):
     """Rows of every length class (1, 2, 3 .. 1023, and from 2049 vertices on more than 2048 entries) at row counts around a
