@@ -16,6 +16,7 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -258,34 +259,79 @@ template <typename T> __device__ __forceinline__ void vstore4(T* __restrict__ p,
   }
 }
 
-// FULL: K is a multiple of 16 and N = 16 NT, so there is no tail to clear and no column group to skip
-template <typename T, int NT, int KU, bool MASK, bool SAVE, bool FULL>
-__global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(NT <= 8 ? 4 : 2, 8))) void k_gemm_nn_fast(NnDirectArgs a) {
+// A buffer of 16 rows, `left` of them backed: requests past its end are dropped (stores) or answered with zeros (loads) by the
+// range check, without a branch.  (0x00020000: a plain buffer of 32-bit words)
+typedef __amdgpu_buffer_rsrc_t RowsBuf;
+constexpr uint32_t kNoPlace = 0xfffffff0u;
+template <typename T>
+__device__ __forceinline__ RowsBuf rows_buf(const void* p, int64_t row0, int64_t ld, int left) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(reinterpret_cast<const char*>(p) + row0 * ld * (int64_t)sizeof(T)), 0,
+                                           left * (int)ld * (int)sizeof(T), 0x00020000);
+}
+template <typename T> __device__ __forceinline__ void buf_load4(RowsBuf b, uint32_t off, float (&o)[4]) {
+  if constexpr (sizeof(T) == 4) {
+    const auto q = __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = __uint_as_float(q[i]);
+  } else {
+    const auto q = __builtin_amdgcn_raw_buffer_load_b64(b, (int)off, 0, 0);
+    o[0] = __uint_as_float(q[0] << 16); o[1] = __uint_as_float(q[0] & 0xffff0000u);
+    o[2] = __uint_as_float(q[1] << 16); o[3] = __uint_as_float(q[1] & 0xffff0000u);
+  }
+}
+template <typename T> __device__ __forceinline__ void buf_store4(RowsBuf b, uint32_t off, const float (&v)[4]) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  if constexpr (sizeof(T) == 4) {
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])}, b,
+                                           (int)off, 0, 0);
+  } else {
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{(uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16),
+                                                (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16)}, b, (int)off, 0, 0);
+  }
+}
+template <typename T> __device__ __forceinline__ void buf_store1(RowsBuf b, uint32_t off, float v) {
+  if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), b, (int)off, 0, 0);
+  else __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(v), b, (int)off, 0, 0);
+}
+
+// whether the registers of an instance leave room for two blocks a compute unit
+constexpr bool nn_two_blocks(int NT, int KU, bool MASK) { return NT <= 8 && !(MASK && NT == 8 && KU > 4); }
+
+// FULL: K is a multiple of 16 and N = 16 NT, so there is no tail to clear and no column group to skip.  CH: k chunks per tile (0: by
+// the arguments).
+//
+// Nothing between the requests of a tile and their use may branch, stores included: loads and stores share one counter of
+// requests in flight, and behind a join at which some stores may not have been issued the only safe wait for the next tile's
+// operand is a wait for all, stores too - one round trip of the stores per tile, and the matrix pipe idle meanwhile.  So rows past M
+// and columns past N are dropped by the stores' range check, the mask of a tile is requested before its first MFMA, and
+// the chunks of a tile are unrolled.  Measured, us with conditional stores and bias loads between them / this way: 500 K rows 50 ->
+// 50 55 / 49, 64 -> 64 55 / 47 (5.4 TB/s, the rate of a copy), 48 -> 48 37 / 33; 2.45 M rows 47 -> 256 974 / 834, with the mask
+// 1396 / 1124; 2^18 rows 16 -> 128 with the mask 62 / 58; 2^20 rows 32 -> 128 189 / 176; 128 -> 128, bound by the matrix pipe, 163 / 160.
+template <typename T, int NT, int KU, int CH, bool MASK, bool SAVE, bool FULL>
+__global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(nn_two_blocks(NT, KU, MASK) ? 4 : 2, 8))) void k_gemm_nn_fast(NnDirectArgs a) {
   // W in LDS.  NT a multiple of 4: [k][t / 4][c][t % 4], so that the four column tiles 4 tq .. 4 tq + 3 of a
   // lane's (k, c) are one 16-byte read and the 16 lanes of a k row read 256 contiguous bytes.  Else [k][LDW].
   extern __shared__ float Ws[];
   constexpr int LDW = NT * 16 + 4;
   constexpr bool kQuad = NT % 4 == 0;
   constexpr int TQ = kQuad ? NT / 4 : 1;
-  const int chunks = (a.K + 16 * KU - 1) / (16 * KU);   // k chunks per tile
+  const int chunks = CH > 0 ? CH : (a.K + 16 * KU - 1) / (16 * KU);   // k chunks per tile
   walk_w<NT * 16>(a.W, a.ldw, a.trans, a.K, a.N, chunks * 16 * KU, kNnThreads, [&](int k, int n, float v) {
     const int t = n >> 4, cc = n & 15;
     Ws[kQuad ? ((k * TQ + (t >> 2)) * 16 + cc) * 4 + (t & 3) : k * LDW + n] = v;
   });
+  float* bias = Ws + chunks * 16 * KU * (kQuad ? NT * 16 : LDW);      // behind W; zeros where there is none
+  for (int n = threadIdx.x; n < NT * 16; n += kNnThreads) bias[n] = a.bias && n < a.N ? a.bias[n] : 0.f;
+  const uint32_t neg = a.relu ? 0u : 0xffffffffu;                     // what stays of a value that is not positive
   __syncthreads();
 
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, q = lane >> 4;
   const T* __restrict__ A = reinterpret_cast<const T*>(a.A);
-  T* __restrict__ C = reinterpret_cast<T*>(a.C);
-  T* __restrict__ C2 = reinterpret_cast<T*>(a.C2);
-  const T* __restrict__ Mk = reinterpret_cast<const T*>(a.mask);
   constexpr int WPB = kNnThreads / 64;
   const int64_t ntiles = (a.M + 15) / 16;
   const int64_t stride = (int64_t)gridDim.x * WPB;
-  // mask values of the next tile travel with its operand rows when a tile is a single chunk and they fit
-  constexpr bool kPrefetchMask = MASK && KU <= 2 && NT <= 8;
-
   // K that is no multiple of 16: the lane's request of the very last k step may start past K (moved to column 0)
   // or reach past it (the row is padded to 4 elements); `tail` clears what is not part of the product
   const int k_last = 16 * KU * chunks - 16 + 4 * q;
@@ -297,130 +343,158 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(NT <
 #pragma unroll
   for (int i = 0; i < 4; ++i) tail[i] = i < n_ok ? 0xffffffffu : 0u;
   const int n_up = FULL ? NT * 16 : (a.N + 3) & ~3;     // columns come in groups of 4; the rows are that long
-  auto load_a = [&](int64_t tile, int chunk, float (&av)[KU][4]) {
+  // part u of chunk `chunk` of the lane's row of a tile
+  auto a_row = [&](int64_t tile) -> const T* {
     const int64_t row = tile * 16 + c;
-    if constexpr (FULL) {
-      const T* __restrict__ arow = A + (row < a.M ? row : a.M - 1) * a.lda + chunk * (16 * KU) + 4 * q;
-#pragma unroll
-      for (int u = 0; u < KU; ++u) vload4<T>(arow + 16 * u, av[u]);
-    } else {
-      const T* __restrict__ arow = A + (row < a.M ? row : a.M - 1) * a.lda;
-      const bool last = chunk == chunks - 1;
-#pragma unroll
-      for (int u = 0; u < KU; ++u)
-        vload4<T>(arow + ((u == KU - 1 && last) ? last_off : chunk * (16 * KU) + 16 * u + 4 * q), av[u]);
-    }
+    return A + (row < a.M ? row : a.M - 1) * a.lda + (FULL ? 4 * q : 0);
   };
-  auto load_m = [&](int64_t tile, float (&keep)[NT][4]) {
-    const int64_t row = tile * 16 + c;
-    const T* __restrict__ mrow = Mk + (row < a.M ? row : a.M - 1) * a.ldmask;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) vload4<T>(mrow + ((FULL || 16 * t + 4 * q < n_up) ? 16 * t + 4 * q : 0), keep[t]);
+  auto load_a = [&](const T* __restrict__ arow, int chunk, int u, float (&x)[4]) {
+    if constexpr (FULL) vload4<T>(arow + chunk * (16 * KU) + 16 * u, x);
+    else vload4<T>(arow + ((u == KU - 1 && chunk == chunks - 1) ? last_off : chunk * (16 * KU) + 16 * u + 4 * q), x);
+  };
+  auto rows_left = [&](int64_t tile) { return (int)(a.M - tile * 16 < 16 ? a.M - tile * 16 : 16); };
+  // place of column n of the lane's row in a buffer of 16 rows
+  auto place = [&](int64_t ld, int n) -> uint32_t {
+    const uint32_t off = (uint32_t)(c * (int)ld + n) * (uint32_t)sizeof(T);
+    return FULL || n < n_up ? off : kNoPlace;
   };
 
   int64_t tile = (int64_t)blockIdx.x * WPB + w;
   if (tile >= ntiles) return;
-  float a_nxt[KU][4];
-  float m_nxt[kPrefetchMask ? NT : 1][4];
-  load_a(tile, 0, a_nxt);
-  if constexpr (kPrefetchMask) load_m(tile, m_nxt);
+  // Registers hold one operand row part and one mask quad of each kind: as soon as the MFMAs of a part are issued, the same
+  // part of the next chunk or tile is asked for, and the next tile's mask as soon as this one's is used.
+  float av[KU][4];
+  float keep[MASK ? NT : 1][4];
+  {
+    const T* __restrict__ arow = a_row(tile);
+#pragma unroll
+    for (int u = 0; u < KU; ++u) load_a(arow, 0, u, av[u]);
+    // The loop is entered with as many requests behind the operand's as it is repeated with, so that its waits need not tell
+    // the two apart: stores that the range check drops stand for those of a tile before.
+    const RowsBuf cb = rows_buf<T>(a.C, tile * 16, a.ldc, rows_left(tile));
+    RowsBuf mb = cb;
+    if constexpr (MASK) mb = rows_buf<T>(a.mask, tile * 16, a.ldmask, rows_left(tile));
+    const float none[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < (MASK ? NT : 0); ++t) buf_load4<T>(mb, place(a.ldmask, 16 * t + 4 * q), keep[t]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if constexpr (SAVE) buf_store4<T>(cb, kNoPlace - 32 * t - 16, none);
+      buf_store4<T>(cb, kNoPlace - 32 * t, none);
+    }
+  }
   for (; tile < ntiles; tile += stride) {
+    asm volatile("" ::: "memory");         // (the bias stays in LDS)
+    const int64_t after = tile + stride < ntiles ? tile + stride : tile;      // (at the end the same tile again, unused)
     floatx4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float keep[kPrefetchMask ? NT : 1][4];
-    if constexpr (kPrefetchMask) {
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) keep[t][i] = m_nxt[t][i];
-    }
-    for (int chunk = 0; chunk < chunks; ++chunk) {
-      float av[KU][4];
-#pragma unroll
-      for (int u = 0; u < KU; ++u)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) av[u][i] = a_nxt[u][i];
-      if constexpr (!FULL) {
-        if (chunk == chunks - 1) {
-          if (a.endA) {
-            float (&x)[4] = av[KU - 1];
-            if (shift & 1) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; }
-            if (shift & 2) { x[0] = x[2]; x[1] = x[3]; }
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i) av[KU - 1][i] = __uint_as_float(__float_as_uint(av[KU - 1][i]) & tail[i]);
-        }
-      }
-      // the next request: this tile's next chunk, else the first chunk of the wavefront's next tile
-      // (clamped to the last tile: a valid, wasted load at the very end)
+    auto do_chunk = [&](int chunk) {
       const bool same = chunk + 1 < chunks;
-      const int64_t nt = same ? tile : (tile + stride < ntiles ? tile + stride : ntiles - 1);
-      load_a(nt, same ? chunk + 1 : 0, a_nxt);
-      if constexpr (kPrefetchMask) load_m(nt, m_nxt);
+      const T* __restrict__ next = a_row(same ? tile : after);
+      const int next_chunk = same ? chunk + 1 : 0;
+      // kQuad: the W operands of step (u, i + 1) are read from LDS before the MFMAs of step (u, i) are issued
+      const floatx4* wq = reinterpret_cast<const floatx4*>(Ws) + ((chunk * (16 * KU) + 4 * q) * TQ) * 16 + c;
+      const float* wbase = Ws + (chunk * (16 * KU) + 4 * q) * LDW + c;
+      floatx4 wc[TQ], wn[TQ];
       if constexpr (kQuad) {
-        // the W operands of step (u, i + 1) are read from LDS before the MFMAs of step (u, i) are issued
-        const floatx4* wq = reinterpret_cast<const floatx4*>(Ws) + ((chunk * (16 * KU) + 4 * q) * TQ) * 16 + c;
-        floatx4 wc[TQ], wn[TQ];
 #pragma unroll
         for (int tq = 0; tq < TQ; ++tq) wc[tq] = wq[tq * 16];
+      }
 #pragma unroll
-        for (int st = 0; st < KU * 4; ++st) {
-          const int u = st >> 2, i = st & 3;
-          if (st + 1 < KU * 4) {
-            const int kn = 16 * ((st + 1) >> 2) + ((st + 1) & 3);
+      for (int u = 0; u < KU; ++u) {
+        float x[4];
 #pragma unroll
-            for (int tq = 0; tq < TQ; ++tq) wn[tq] = wq[(kn * TQ + tq) * 16];
+        for (int i = 0; i < 4; ++i) x[i] = av[u][i];
+        if constexpr (!FULL) {
+          if (u == KU - 1 && chunk == chunks - 1) {
+            if (a.endA) {
+              if (shift & 1) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; }
+              if (shift & 2) { x[0] = x[2]; x[1] = x[3]; }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = __uint_as_float(__float_as_uint(x[i]) & tail[i]);
           }
-#pragma unroll
-          for (int tq = 0; tq < TQ; ++tq)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              acc[tq * 4 + r] = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[tq][r], av[u][i], acc[tq * 4 + r], 0, 0, 0);
-#pragma unroll
-          for (int tq = 0; tq < TQ; ++tq) wc[tq] = wn[tq];
         }
-      } else {
-        const float* wbase = Ws + (chunk * (16 * KU) + 4 * q) * LDW + c;
 #pragma unroll
-        for (int u = 0; u < KU; ++u)
+        for (int i = 0; i < 4; ++i) {
+          if constexpr (kQuad) {
+            const int st = 4 * u + i, kn = 16 * ((st + 1) >> 2) + ((st + 1) & 3);
+            if (st + 1 < KU * 4) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
+              for (int tq = 0; tq < TQ; ++tq) wn[tq] = wq[(kn * TQ + tq) * 16];
+            }
+#pragma unroll
+            for (int tq = 0; tq < TQ; ++tq)
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                acc[tq * 4 + r] = __builtin_amdgcn_mfma_f32_16x16x4f32(wc[tq][r], x[i], acc[tq * 4 + r], 0, 0, 0);
+#pragma unroll
+            for (int tq = 0; tq < TQ; ++tq) wc[tq] = wn[tq];
+          } else {
             const float* wrow = wbase + (16 * u + i) * LDW;
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
-              acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wrow[t * 16], av[u][i], acc[t], 0, 0, 0);
+            for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wrow[t * 16], x[i], acc[t], 0, 0, 0);
           }
+          if (NT >= 8 || i == 3) __builtin_amdgcn_sched_barrier(0);      // (else all of W is read ahead, and spilled)
+        }
+        load_a(next, next_chunk, u, av[u]);
+        __builtin_amdgcn_sched_barrier(0);
       }
+    };
+    if constexpr (CH > 0) {
+#pragma unroll
+      for (int chunk = 0; chunk < CH; ++chunk) do_chunk(chunk);
+    } else {
+      for (int chunk = 0; chunk < chunks; ++chunk) do_chunk(chunk);
     }
     // register r of lane (c, q) holds output column 16t + 4q + r of row c
-    const int64_t m = tile * 16 + c;
-    if (m < a.M) {
+    float last[4] = {0.f, 0.f, 0.f, 0.f}, last2[4] = {0.f, 0.f, 0.f, 0.f};      // the quad that column N cuts, and where it starts
+    int at = a.N;
+    const RowsBuf cb = rows_buf<T>(a.C, tile * 16, a.ldc, rows_left(tile));
+    RowsBuf cb2 = cb, mb = cb;
+    if constexpr (MASK) mb = rows_buf<T>(a.mask, after * 16, a.ldmask, rows_left(after));
+    if constexpr (SAVE) cb2 = rows_buf<T>(a.C2, tile * 16, a.ldc2, rows_left(tile));
+    float v[NT][4];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int n = t * 16 + 4 * q;
-        if constexpr (!FULL) { if (n >= n_up) continue; }
-        float v[4], pre[4], kp[4];
-        if constexpr (MASK && !kPrefetchMask) vload4<T>(Mk + m * a.ldmask + n, kp);
+    for (int t = 0; t < NT; ++t) {
+      const floatx4 bv = *reinterpret_cast<const floatx4*>(bias + t * 16 + 4 * q);
+      acc[t] += bv;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        v[t][r] = acc[t][r] > 0.f ? acc[t][r] : __uint_as_float(__float_as_uint(acc[t][r]) & neg);
+        if constexpr (MASK) v[t][r] = keep[t][r] > 0.f ? v[t][r] : 0.f;
+      }
+      // (the next tile's mask ahead of this tile's stores: requests are answered in order)
+      if constexpr (MASK) buf_load4<T>(mb, place(a.ldmask, t * 16 + 4 * q), keep[t]);
+    }
+    if constexpr (MASK) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int n = t * 16 + 4 * q;
+      float pre[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) pre[r] = acc[t][r];
+      const bool part = !FULL && a.endC && n < a.N && n + 4 > a.N;
+      const uint32_t off = part ? kNoPlace : place(a.ldc, n), off2 = !SAVE || part ? kNoPlace : place(a.ldc2, n);
+      if constexpr (!FULL) {
+        if (2 * t + 2 > NT || NT <= 4) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) { last[r] = part ? v[t][r] : last[r]; last2[r] = SAVE && part ? pre[r] : last2[r]; }
+          at = part ? n : at;
+        }
+      }
+      if constexpr (SAVE) buf_store4<T>(cb2, off2, pre);
+      buf_store4<T>(cb, off, v[t]);
+    }
+    if constexpr (!FULL) {
+      if (a.endC) {        // the columns that a row ends in, one after the other
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          pre[r] = acc[t][r] + ((a.bias && (FULL || n + r < a.N)) ? a.bias[n + r] : 0.f);
-          v[r] = a.relu ? (pre[r] > 0.f ? pre[r] : 0.f) : pre[r];
-          if constexpr (MASK) v[r] = (kPrefetchMask ? keep[t][r] : kp[r]) > 0.f ? v[r] : 0.f;
+          const bool in = at + r < a.N;
+          if constexpr (SAVE) buf_store1<T>(cb2, in ? (uint32_t)(c * (int)a.ldc2 + at + r) * (uint32_t)sizeof(T) : kNoPlace, last2[r]);
+          buf_store1<T>(cb, in ? (uint32_t)(c * (int)a.ldc + at + r) * (uint32_t)sizeof(T) : kNoPlace, last[r]);
         }
-        if constexpr (!FULL) {
-          if (a.endC && n + 3 >= a.N) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              if (n + r >= a.N) continue;
-              if constexpr (SAVE) store_one<T>(C2 + m * a.ldc2 + n + r, pre[r]);
-              store_one<T>(C + m * a.ldc + n + r, v[r]);
-            }
-            continue;
-          }
-        }
-        if constexpr (SAVE) vstore4<T>(C2 + m * a.ldc2 + n, pre);
-        vstore4<T>(C + m * a.ldc + n, v);
       }
     }
   }
@@ -450,9 +524,9 @@ static int nn_launch(const NnDirectArgs& a, hipStream_t s) {
 
 template <typename T, int NT, int KU>
 static int nn_launch_fast(const NnDirectArgs& a, hipStream_t s) {
-  const size_t lds = gemm_nn_direct_lds_bytes(a.N, a.K);
+  const size_t lds = gemm_nn_direct_lds_bytes(a.N, a.K) + sizeof(float) * 16 * NT;      // (and the bias)
   const int64_t ntiles = ceil_div(a.M, 16);
-  const int per_cu = lds > 80 * 1024 ? 1 : 2;
+  const int per_cu = lds > 80 * 1024 || !nn_two_blocks(NT, KU, a.mask != nullptr) ? 1 : 2;
   int64_t blocks = ceil_div(ntiles, kNnThreads / 64);
   if (blocks > 256 * per_cu) blocks = 256 * per_cu;
   auto go = [&](auto kern) -> int {
@@ -461,14 +535,22 @@ static int nn_launch_fast(const NnDirectArgs& a, hipStream_t s) {
     GCN_CHECK_LAUNCH();
     return GCN_OK;
   };
-  if constexpr (KU == 1 || KU == 2 || KU == 4 || KU == 8) {
-    if ((a.K % 16) == 0 && a.N == NT * 16) {
-      if (a.mask) return go(k_gemm_nn_fast<T, NT, KU, true, false, true>);
-      return a.C2 ? go(k_gemm_nn_fast<T, NT, KU, false, true, true>) : go(k_gemm_nn_fast<T, NT, KU, false, false, true>);
+  auto pick = [&](auto ch) -> int {
+    constexpr int CH = decltype(ch)::value;
+    if constexpr (KU == 1 || KU == 2 || KU == 4 || KU == 8) {
+      if ((a.K % 16) == 0 && a.N == NT * 16) {
+        if (a.mask) return go(k_gemm_nn_fast<T, NT, KU, CH, true, false, true>);
+        return a.C2 ? go(k_gemm_nn_fast<T, NT, KU, CH, false, true, true>) : go(k_gemm_nn_fast<T, NT, KU, CH, false, false, true>);
+      }
     }
+    if (a.mask) return go(k_gemm_nn_fast<T, NT, KU, CH, true, false, false>);
+    return a.C2 ? go(k_gemm_nn_fast<T, NT, KU, CH, false, true, false>) : go(k_gemm_nn_fast<T, NT, KU, CH, false, false, false>);
+  };
+  if constexpr (KU == 8) {
+    if (a.K > 256) return pick(std::integral_constant<int, 0>());
+    if (a.K > 128) return pick(std::integral_constant<int, 2>());
   }
-  if (a.mask) return go(k_gemm_nn_fast<T, NT, KU, true, false, false>);
-  return a.C2 ? go(k_gemm_nn_fast<T, NT, KU, false, true, false>) : go(k_gemm_nn_fast<T, NT, KU, false, false, false>);
+  return pick(std::integral_constant<int, 1>());
 }
 
 // the branch-free kernel serves rows on word boundaries with K up to 128 or a multiple of 128
@@ -483,6 +565,7 @@ static bool nn_fast(NnDirectArgs a, hipStream_t s, int* rc) {
   a.endC |= a.vecC != 4 || (a.C2 && a.vecC2 != 4);
   if (a.endC && (!words(a.C, a.ldc) || (a.C2 && !words(a.C2, a.ldc2)))) return false;
   if (a.mask && (a.vecM != 4 || a.mask_rows < a.M || a.C2)) return false;
+  if (a.ldc >= 1 << 24 || a.ldc2 >= 1 << 24 || a.ldmask >= 1 << 24) return false;      // (16 rows are one buffer, with 32-bit offsets)
   const int ku = a.K % 128 == 0 ? 8 : a.K < 128 ? (a.K + 15) / 16 : 0;
   if (ku == 0) return false;
 #define GCN_NN_FAST(NTV)                                              \
