@@ -13,7 +13,7 @@
 // within 128 KB of LDS.  Everything else stays on the fp32 path.
 #include <stdlib.h>
 
-#include "common.h"
+#include "rows_buf.h"
 
 namespace gcn {
 
@@ -62,7 +62,13 @@ __device__ __forceinline__ void unpack4(const u32x2& v, float (&o)[4]) {
 // One wavefront per tile of 16 rows.  Lane (c, q) = (lane % 16, lane / 16) supplies row c of the tile as the
 // second MFMA operand (k = KS s + LV q .. + LV - 1 of k step s, KS = 4 LV) and the column 16 t + c of W as the
 // first, so register r of its accumulator t is column 16 t + 4 q + r of row c: four consecutive outputs.
-// KL = K / KS k steps per tile; the next tile's rows are requested before the current tile's MFMAs.
+// KL = K / KS k steps per tile; a part of a row is asked for again, from the next tile, as soon as its MFMAs are issued, the next
+// tile's mask as soon as this one's is used, and nothing branches between a tile's requests and their use, its stores included
+// (gemm_direct.hip, k_gemm_nn_fast, has the reason).  Measured, us with conditional stores and bias loads between them and W
+// taken value by value / this way, the bytes at a copy's 5.4 TB/s behind: 2^18 x 128 -> 128 38.9 / 30.0 (25), 2.4 M rows 100 ->
+// 256 664 / 611 (323), 256 -> 256 915 / 741 (464), 256 -> 47 484 / 472 (275), 256 <- 256 with a mask 787 / 594 (T was in the
+// last-level cache), 47 -> 256 with a mask 619 / 627 (507).  More wavefronts do not help (three blocks; 6 wavefronts and two
+// blocks with 256 columns: 668 for 100 -> 256): the rate of the requests bounds it, not their number in flight.
 template <int NT, int KL, int LV, bool MASK, bool SAVE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_gemm_nn_bf16(NnBf16Args a) {
   typedef typename Frag<LV>::raw Raw;
@@ -106,15 +112,52 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
                                                          (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16)};
       }
     } else {
-      for (int e = threadIdx.x; e < KL * KS * NT * 16; e += kThreads) {
-        const int k = e / (NT * 16), n = e % (NT * 16);
-        wl[at(k, n)] = (k < a.K && n < a.N) ? f32_to_bf16(a.W[(int64_t)k * a.ldw + n]) : (bf16_t)0;
+      // Blocks of 4 k x 4 n: four requests of 16 bytes, four places of 8 bytes, two blocks of a thread asked for before either is
+      // used: 256 x 256 takes 10 us, 128 x 128 3 (one value at a time 33 and 7).  A block that column N cuts is moved back onto its
+      // neighbour's columns (both write the same values there).
+      typedef float floatx4w __attribute__((ext_vector_type(4), aligned(4)));
+      const uint32_t nb = (uint32_t)(a.N + 3) / 4, total = KL * KS / 4 * nb;
+      for (uint32_t e0 = threadIdx.x; e0 < total; e0 += 2 * kThreads) {
+        floatx4w v[2][4];
+        int kk[2], nn[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const uint32_t e = e0 + u * kThreads < total ? e0 + u * kThreads : e0;
+          kk[u] = 4 * (int)(e / nb);
+          nn[u] = 4 * (int)(e % nb);
+          if (nn[u] + 4 > a.N) nn[u] = a.N >= 4 ? a.N - 4 : 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float* __restrict__ p = a.W + (int64_t)(kk[u] + i < a.K ? kk[u] + i : a.K - 1) * a.ldw + nn[u];
+            if (a.N >= 4) v[u][i] = *reinterpret_cast<const floatx4w*>(p);
+            else v[u][i] = floatx4w{p[0], a.N > 1 ? p[1] : 0.f, a.N > 2 ? p[2] : 0.f, 0.f};
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          uint32_t in[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) in[i] = kk[u] + i < a.K ? 0xffffffffu : 0u;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            bf16_t h[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) h[i] = f32_to_bf16(__uint_as_float(__float_as_uint(v[u][i][r]) & in[i]));
+            *reinterpret_cast<u32x2*>(wl + at(kk[u], nn[u] + r)) = u32x2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
+          }
+        }
       }
+      const int n0 = a.N < 4 ? 4 : a.N, pad = NT * 16 - n0;       // zeros beyond N
+      for (int e = threadIdx.x; e < KL * KS / 4 * pad; e += kThreads)
+        *reinterpret_cast<u32x2*>(wl + at(4 * (e / pad), n0 + e % pad)) = u32x2{0u, 0u};
     }
   }
+  float* bias = reinterpret_cast<float*>(Wl + KL * NT * 64);      // behind W; zeros where there is none
+  for (int n = threadIdx.x; n < NT * 16; n += kThreads) bias[n] = a.bias && n < a.N ? a.bias[n] : 0.f;
+  const uint32_t neg = a.relu ? 0u : 0xffffffffu;                 // what stays of a value that is not positive
   __syncthreads();
 
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, q = lane >> 4;
   constexpr int WPB = kThreads / 64;
   const int64_t ntiles = (a.M + 15) / 16;
@@ -127,42 +170,52 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
   const int last_off = n_ok > 0 ? k_last : 0;
   u32x2 tail = u32x2{0xffffffffu, 0xffffffffu};
   if (n_ok < 4) tail = u32x2{n_ok >= 2 ? 0xffffffffu : n_ok == 1 ? 0x0000ffffu : 0u, n_ok == 3 ? 0x0000ffffu : 0u};
-  auto load_a = [&](int64_t tile, Raw (&av)[KL]) {
+  auto a_row = [&](int64_t tile) -> const bf16_t* {
     const int64_t row = tile * 16 + c;
-    const bf16_t* __restrict__ arow = a.A + (row < a.M ? row : a.M - 1) * a.lda;
+    return a.A + (row < a.M ? row : a.M - 1) * a.lda;
+  };
+  auto load_a = [&](const bf16_t* __restrict__ arow, int s, Raw& x) { x = *reinterpret_cast<const Raw*>(arow + (s == KL - 1 ? last_off : KS * s + LV * q)); };
+  auto rows_left = [&](int64_t tile) { return (int)(a.M - tile * 16 < 16 ? a.M - tile * 16 : 16); };
+  // groups of columns of a lane, kG of them each
+  constexpr int kGroups = kPair ? NT / 2 : NT, kG = kPair ? 8 : 4;
+  typedef typename Frag<kG>::raw Group;
+  auto place = [&](int64_t ld, int n) -> uint32_t { return n < n_up ? (uint32_t)(c * (int)ld + n) * 2u : kNoPlace; };
+  auto load_mask = [&](int64_t tile, Group (&keep)[MASK ? kGroups : 1]) {
+    const RowsBuf mb = rows_buf<bf16_t>(a.mask, tile * 16, a.ldmask, rows_left(tile));
 #pragma unroll
-    for (int s = 0; s < KL; ++s) av[s] = *reinterpret_cast<const Raw*>(arow + (s == KL - 1 ? last_off : KS * s + LV * q));
+    for (int j = 0; j < kGroups; ++j) {
+      const uint32_t off = place(a.ldmask, (kPair ? 32 : 16) * j + kG * q);
+      if constexpr (kPair) keep[j] = __builtin_amdgcn_raw_buffer_load_b128(mb, (int)off, 0, 0);
+      else keep[j] = __builtin_amdgcn_raw_buffer_load_b64(mb, (int)off, 0, 0);
+    }
+  };
+  auto put = [&](RowsBuf b, uint32_t off, const Group& v) {
+    if constexpr (kPair) __builtin_amdgcn_raw_buffer_store_b128(v, b, (int)off, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b64(v, b, (int)off, 0, 0);
   };
 
   int64_t tile = (int64_t)blockIdx.x * WPB + w;
   if (tile >= ntiles) return;
-  Raw a_nxt[KL];
-  load_a(tile, a_nxt);
-  for (; tile < ntiles; tile += stride) {
-    Raw av[KL];
+  Raw av[KL];
+  Group keep[MASK ? kGroups : 1];
+  {
+    const bf16_t* __restrict__ arow = a_row(tile);
 #pragma unroll
-    for (int s = 0; s < KL; ++s) av[s] = a_nxt[s];
-    if constexpr (LV == 4) av[KL - 1] = u32x2{av[KL - 1][0] & tail[0], av[KL - 1][1] & tail[1]};
-    load_a(tile + stride < ntiles ? tile + stride : ntiles - 1, a_nxt);     // past the end: a valid, unused request
-    u32x2 keep[MASK ? NT : 1];
-    const int64_t m = tile * 16 + c;
-    const int64_t mc = m < a.M ? m : a.M - 1;
-    if constexpr (MASK) {
-      if constexpr (kPair) {
+    for (int s = 0; s < KL; ++s) load_a(arow, s, av[s]);
+    if constexpr (MASK) load_mask(tile, keep);
+    // (as many requests behind the operand's as the loop is repeated with: dropped stores for those of a tile before)
+    const RowsBuf cb = rows_buf<bf16_t>(a.C, tile * 16, a.ldc, rows_left(tile));
+    const Group none{};
 #pragma unroll
-        for (int j = 0; j < NT / 2; ++j) {
-          const int n = 32 * j + 8 * q;
-          const u32x4 kv = *reinterpret_cast<const u32x4*>(a.mask + mc * a.ldmask + (n < n_up ? n : 0));
-          keep[2 * j] = u32x2{kv[0], kv[1]}; keep[2 * j + 1] = u32x2{kv[2], kv[3]};
-        }
-      } else {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const int n = 16 * t + 4 * q;
-          keep[t] = *reinterpret_cast<const u32x2*>(a.mask + mc * a.ldmask + (n < n_up ? n : 0));
-        }
-      }
+    for (int j = 0; j < kGroups; ++j) {
+      if constexpr (SAVE) put(cb, kNoPlace - 32 * j - 16, none);
+      put(cb, kNoPlace - 32 * j, none);
     }
+  }
+  for (; tile < ntiles; tile += stride) {
+    asm volatile("" ::: "memory");         // (the bias stays in LDS)
+    const int64_t after = tile + stride < ntiles ? tile + stride : tile;      // (at the end the same tile again, unused)
+    const bf16_t* __restrict__ next = a_row(after);
     floatx4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -170,89 +223,95 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     // from hoisting all K / KS x NT reads to the top, which needs more registers than there are
     constexpr int TB = NT < 8 ? NT : 8;
 #pragma unroll
-    for (int s = 0; s < KL; ++s)
+    for (int s = 0; s < KL; ++s) {
+      Raw x = av[s];
+      if constexpr (LV == 4) { if (s == KL - 1) x = u32x2{x[0] & tail[0], x[1] & tail[1]}; }
 #pragma unroll
       for (int t0 = 0; t0 < NT; t0 += TB) {
         Raw wf[TB];
 #pragma unroll
         for (int t = 0; t < TB; ++t) wf[t] = Wl[(s * NT + t0 + t) * 64 + lane];
 #pragma unroll
-        for (int t = 0; t < TB; ++t) acc[t0 + t] = mfma<LV>(wf[t], av[s], acc[t0 + t]);
+        for (int t = 0; t < TB; ++t) acc[t0 + t] = mfma<LV>(wf[t], x, acc[t0 + t]);
         __builtin_amdgcn_sched_barrier(0);
       }
+      load_a(next, s, av[s]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 
-    if (m < a.M) {
-      u32x2 out[NT], out2[SAVE ? NT : 1];
-      auto store_tail = [&](bf16_t* row, int n, const u32x2& v) {         // columns n .. n + 3 of the row that exist
+    const RowsBuf cb = rows_buf<bf16_t>(a.C, tile * 16, a.ldc, rows_left(tile));
+    RowsBuf cb2 = cb;
+    if constexpr (SAVE) cb2 = rows_buf<bf16_t>(a.C2, tile * 16, a.ldc2, rows_left(tile));
+    Group out[kGroups], out2[SAVE ? kGroups : 1];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (n + r < a.N) row[n + r] = (bf16_t)(v[r / 2] >> (16 * (r % 2)));
-      };
+    for (int t = 0; t < NT; ++t) {
+      const int j = kPair ? t / 2 : t, half = kPair ? 2 * (t % 2) : 0;        // its words of the group
+      const floatx4 bv = *reinterpret_cast<const floatx4*>(bias + (kPair ? 32 * j + 8 * q + 2 * half : 16 * t + 4 * q));
+      float v[4], pre[4], kp[4];
+      if constexpr (MASK) unpack4(u32x2{keep[j][half], keep[j][half + 1]}, kp);
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int n = kPair ? 32 * (t / 2) + 8 * q + 4 * (t % 2) : t * 16 + 4 * q;
-        float v[4], pre[4], kp[4];
-        if constexpr (MASK) unpack4(keep[t], kp);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          pre[r] = acc[t][r] + ((a.bias && n + r < a.N) ? a.bias[n + r] : 0.f);
-          v[r] = a.relu ? (pre[r] > 0.f ? pre[r] : 0.f) : pre[r];
-          if constexpr (MASK) v[r] = kp[r] > 0.f ? v[r] : 0.f;
-        }
-        out[t] = u32x2{(uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16), (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16)};
-        if constexpr (SAVE)
-          out2[t] = u32x2{(uint32_t)f32_to_bf16(pre[0]) | ((uint32_t)f32_to_bf16(pre[1]) << 16), (uint32_t)f32_to_bf16(pre[2]) | ((uint32_t)f32_to_bf16(pre[3]) << 16)};
+      for (int r = 0; r < 4; ++r) {
+        pre[r] = acc[t][r] + bv[r];
+        v[r] = pre[r] > 0.f ? pre[r] : __uint_as_float(__float_as_uint(pre[r]) & neg);
+        if constexpr (MASK) v[r] = kp[r] > 0.f ? v[r] : 0.f;
       }
-      if constexpr (kPair) {
+      out[j][half] = (uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16);
+      out[j][half + 1] = (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16);
+      if constexpr (SAVE) {
+        out2[j][half] = (uint32_t)f32_to_bf16(pre[0]) | ((uint32_t)f32_to_bf16(pre[1]) << 16);
+        out2[j][half + 1] = (uint32_t)f32_to_bf16(pre[2]) | ((uint32_t)f32_to_bf16(pre[3]) << 16);
+      }
+    }
+    // (the next tile's mask ahead of this tile's stores: requests are answered in order)
+    if constexpr (MASK) {
+      __builtin_amdgcn_sched_barrier(0);
+      load_mask(after, keep);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    Group last{}, last2{};                 // the group that column N cuts where nothing may be written behind it, and where it starts
+    int at = a.N;
 #pragma unroll
-        for (int j = 0; j < NT / 2; ++j) {
-          const int n = 32 * j + 8 * q;
-          if (n >= n_up) continue;
-          if (a.endC && n + 8 > a.N) {
+    for (int j = 0; j < kGroups; ++j) {
+      const int n = (kPair ? 32 : 16) * j + kG * q;
+      const bool part = a.endC && n < a.N && n + kG > a.N;
+      if (2 * j + 2 > kGroups || kGroups <= 2) {
+        last = part ? out[j] : last;
+        if constexpr (SAVE) last2 = part ? out2[j] : last2;
+        at = part ? n : at;
+      }
+      if constexpr (SAVE) put(cb2, part ? kNoPlace : place(a.ldc2, n), out2[j]);
+      put(cb, part ? kNoPlace : place(a.ldc, n), out[j]);
+    }
+    if (a.endC) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-              if constexpr (SAVE) store_tail(a.C2 + m * a.ldc2, n + 4 * i, out2[2 * j + i]);
-              store_tail(a.C + m * a.ldc, n + 4 * i, out[2 * j + i]);
-            }
-            continue;
-          }
-          if constexpr (SAVE)
-            *reinterpret_cast<u32x4*>(a.C2 + m * a.ldc2 + n) = u32x4{out2[2 * j][0], out2[2 * j][1], out2[2 * j + 1][0], out2[2 * j + 1][1]};
-          *reinterpret_cast<u32x4*>(a.C + m * a.ldc + n) = u32x4{out[2 * j][0], out[2 * j][1], out[2 * j + 1][0], out[2 * j + 1][1]};
-        }
-      } else {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const int n = t * 16 + 4 * q;
-          if (n >= n_up) continue;
-          if (a.endC && n + 4 > a.N) {
-            if constexpr (SAVE) store_tail(a.C2 + m * a.ldc2, n, out2[t]);
-            store_tail(a.C + m * a.ldc, n, out[t]);
-            continue;
-          }
-          if constexpr (SAVE) *reinterpret_cast<u32x2*>(a.C2 + m * a.ldc2 + n) = out2[t];
-          *reinterpret_cast<u32x2*>(a.C + m * a.ldc + n) = out[t];
-        }
+      for (int r = 0; r < kG; ++r) {
+        const bool in = at + r < a.N;
+        if constexpr (SAVE)
+          __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(last2[r / 2] >> (16 * (r % 2))), cb2, (int)(in ? (uint32_t)(c * (int)a.ldc2 + at + r) * 2u : kNoPlace), 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(last[r / 2] >> (16 * (r % 2))), cb, (int)(in ? (uint32_t)(c * (int)a.ldc + at + r) * 2u : kNoPlace), 0, 0);
       }
     }
   }
 }
 
-template <int NT, int KL, int LV>
-int launch(const NnBf16Args& a, hipStream_t s) {
-  const size_t lds = (size_t)KL * 4 * LV * NT * 16 * sizeof(bf16_t);
+template <int NT, int KL, int LV, bool MASK, bool SAVE>
+int launch_one(const NnBf16Args& a, hipStream_t s) {
+  const auto kern = k_gemm_nn_bf16<NT, KL, LV, MASK, SAVE>;
+  const size_t lds = (size_t)KL * 4 * LV * NT * 16 * sizeof(bf16_t) + sizeof(float) * 16 * NT;      // W and the bias
   const int64_t ntiles = ceil_div(a.M, 16);
-  const int per_cu = lds > 64 * 1024 ? 1 : 2;
+  const int per_cu = NT == 16 || lds > 65 * 1024 ? 1 : 2;         // (256 columns: more registers than two blocks have)
   int64_t blocks = ceil_div(ntiles, kThreads / 64);
   if (blocks > 256 * per_cu) blocks = 256 * per_cu;
-  auto go = [&](auto kern) -> int {
-    GCN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    kern<<<dim3((unsigned)blocks), dim3(kThreads), lds, s>>>(a);
-    GCN_CHECK_LAUNCH();
-    return GCN_OK;
-  };
-  if (a.mask) return go(k_gemm_nn_bf16<NT, KL, LV, true, false>);
-  return a.C2 ? go(k_gemm_nn_bf16<NT, KL, LV, false, true>) : go(k_gemm_nn_bf16<NT, KL, LV, false, false>);
+  GCN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  kern<<<dim3((unsigned)blocks), dim3(kThreads), lds, s>>>(a);
+  GCN_CHECK_LAUNCH();
+  return GCN_OK;
+}
+
+template <int NT, int KL, int LV>
+int launch(const NnBf16Args& a, hipStream_t s) {
+  if (a.mask) return launch_one<NT, KL, LV, true, false>(a, s);
+  return a.C2 ? launch_one<NT, KL, LV, false, true>(a, s) : launch_one<NT, KL, LV, false, false>(a, s);
 }
 
 template <int NT>
@@ -455,6 +514,7 @@ bool gemm_nn_bf16_ok(const void* A, int64_t lda, void* C, int64_t ldc, int64_t M
   const int g = NT % 2 == 0 ? 8 : 4;
   const int64_t n_up = (N + g - 1) / g * g;
   if (!aligned_rows(C, ldc, 2 * g) || ldc < n_up) return false;
+  if (ldc >= 1 << 24 || (epi.C2 && epi.ldc2 >= 1 << 24) || (epi.mask && epi.ldmask >= 1 << 24)) return false;      // (16 rows are one buffer, with 32-bit offsets)
   if (epi.C2 && (!aligned_rows(epi.C2, epi.ldc2, 2 * g) || epi.ldc2 < n_up)) return false;
   if (epi.mask && (!aligned_rows(epi.mask, epi.ldmask, 2 * g) || epi.ldmask < n_up || epi.mask_rows < M || epi.C2)) return false;
   return true;

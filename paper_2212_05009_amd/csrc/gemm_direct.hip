@@ -18,7 +18,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "common.h"
+#include "rows_buf.h"
 
 namespace gcn {
 
@@ -259,15 +259,6 @@ template <typename T> __device__ __forceinline__ void vstore4(T* __restrict__ p,
   }
 }
 
-// A buffer of 16 rows, `left` of them backed: requests past its end are dropped (stores) or answered with zeros (loads) by the
-// range check, without a branch.  (0x00020000: a plain buffer of 32-bit words)
-typedef __amdgpu_buffer_rsrc_t RowsBuf;
-constexpr uint32_t kNoPlace = 0xfffffff0u;
-template <typename T>
-__device__ __forceinline__ RowsBuf rows_buf(const void* p, int64_t row0, int64_t ld, int left) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(reinterpret_cast<const char*>(p) + row0 * ld * (int64_t)sizeof(T)), 0,
-                                           left * (int)ld * (int)sizeof(T), 0x00020000);
-}
 template <typename T> __device__ __forceinline__ void buf_load4(RowsBuf b, uint32_t off, float (&o)[4]) {
   if constexpr (sizeof(T) == 4) {
     const auto q = __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, 0);
