@@ -116,15 +116,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
       // used: 256 x 256 takes 10 us, 128 x 128 3 (one value at a time 33 and 7).  A block that column N cuts is moved back onto its
       // neighbour's columns (both write the same values there).
       typedef float floatx4w __attribute__((ext_vector_type(4), aligned(4)));
-      const uint32_t nb = (uint32_t)(a.N + 3) / 4, total = KL * KS / 4 * nb;
-      for (uint32_t e0 = threadIdx.x; e0 < total; e0 += 2 * kThreads) {
-        floatx4w v[2][4];
-        int kk[2], nn[2];
+      constexpr int kBlocks = KL * KS / 4 * NT * 4, kBatch = kBlocks > kThreads ? 2 : 1;
+      for (int e0 = threadIdx.x; e0 < kBlocks; e0 += kBatch * kThreads) {
+        floatx4w v[kBatch][4];
+        int kk[kBatch], nn[kBatch];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const uint32_t e = e0 + u * kThreads < total ? e0 + u * kThreads : e0;
-          kk[u] = 4 * (int)(e / nb);
-          nn[u] = 4 * (int)(e % nb);
+        for (int u = 0; u < kBatch; ++u) {
+          const int e = e0 + u * kThreads < kBlocks ? e0 + u * kThreads : e0;
+          kk[u] = 4 * (e / (NT * 4));
+          nn[u] = 4 * (e % (NT * 4));
           if (nn[u] + 4 > a.N) nn[u] = a.N >= 4 ? a.N - 4 : 0;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
           }
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < kBatch; ++u) {
           uint32_t in[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) in[i] = kk[u] + i < a.K ? 0xffffffffu : 0u;
@@ -147,9 +147,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
           }
         }
       }
-      const int n0 = a.N < 4 ? 4 : a.N, pad = NT * 16 - n0;       // zeros beyond N
-      for (int e = threadIdx.x; e < KL * KS / 4 * pad; e += kThreads)
-        *reinterpret_cast<u32x2*>(wl + at(4 * (e / pad), n0 + e % pad)) = u32x2{0u, 0u};
+      const int n0 = a.N < 4 ? 4 : a.N;                            // zeros beyond N
+      if (n0 < NT * 16)
+        for (int e = threadIdx.x; e < KL * KS / 4 * NT * 16; e += kThreads)
+          if (e % (NT * 16) >= n0) *reinterpret_cast<u32x2*>(wl + at(4 * (e / (NT * 16)), e % (NT * 16))) = u32x2{0u, 0u};
     }
   }
   float* bias = reinterpret_cast<float*>(Wl + KL * NT * 64);      // behind W; zeros where there is none

@@ -179,6 +179,33 @@ def test_parts_argument_errors(gcn, dev, block):
         gcn.gcn_spmm_part(A, gcn.PART_HALO, X[:-1], Y)
 
 
+# Rows that start on 16 bytes whatever their width: the streaming kernels, whose copy of W and last group of columns have edges
+# of their own (fewer than 4 columns, a cut last block of W in either direction, 256 columns, K no whole number of steps).
+@pytest.mark.parametrize("d_in,d_out", [(16, 1), (32, 2), (64, 3), (1, 4), (3, 5), (5, 17), (20, 33), (100, 130), (128, 47), (33, 255), (256, 129)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_dense_fwd_of_pitched_rows(gcn, dev, d_in, d_out, bf16):
+    import torch
+    rows = 8 * 16 * 512 + 16 * 3 + 5                      # more tiles than wavefronts, the last of them cut
+    rng = np.random.default_rng(100 * d_in + d_out)
+    X = rng.standard_normal((rows, d_in)).astype(np.float32)
+    if bf16:
+        X = bf16_round(X)
+    W = (rng.standard_normal((d_in, d_out)) / np.sqrt(d_in)).astype(np.float32)
+    b = rng.standard_normal(d_out).astype(np.float32)
+    ref, bound = oracle.gemm("nn", X, W)
+    ref = ref + b.astype(np.float64); bound = bound + np.abs(b.astype(np.float64))
+    tdt = torch.bfloat16 if bf16 else torch.float32
+    up = lambda d: (d + 7) // 8 * 8 + 8
+    Xd = torch.full((rows, up(d_in)), float("nan"), dtype=tdt, device=dev); Xd[:, :d_in] = to_dev(X, dev, bf16)
+    Wd = torch.full((d_in + 1, d_out), float("nan"), device=dev); Wd[:d_in] = to_dev(W, dev)
+    Out = torch.full((rows + 1, up(d_out)), 7.0, dtype=tdt, device=dev)
+    say(f"dense_fwd of pitched rows d_in={d_in} d_out={d_out} bf16={bf16}")
+    gcn.gcn_dense_fwd(Xd[:, :d_in], Wd[:d_in], Out[:rows, :d_out], bias=to_dev(b, dev), act=gcn.ACT_RELU)
+    torch.cuda.synchronize()
+    check_bound(to_np(Out[:rows, :d_out]), np.maximum(ref, 0.0), bound, TOL_BF16 if bf16 else TOL_F32, what="dense_fwd Out")
+    assert (Out[rows] == 7).all() and (Out[:, d_out:] == 7).all()
+
+
 @pytest.mark.parametrize("rows,d_in,d_out", [(1, 5, 3), (777, 41, 16), (5000, 128, 128), (3001, 602, 47), (4097, 16, 41)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_dense_fwd(gcn, dev, rows, d_in, d_out, bf16):
