@@ -1,4 +1,4 @@
-// Device templates of the sparse-times-dense kernels (included by spmm.hip, spmm_f32.hip, spmm_bf16.hip).
+// Device templates of the sparse-times-dense kernels (included by spmm.hip, spmm_f32.hip, spmm_bf16.hip, spmm_dense.hip).
 #pragma once
 #include <stdlib.h>
 
