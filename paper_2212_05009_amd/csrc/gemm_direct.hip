@@ -760,7 +760,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // row half read 512 contiguous bytes.  The MFMA never sees the permutation; it is undone when the partial tile
 // is stored.  One request per four (TN = 1) or four requests per sixteen (TN = 2) MFMAs.  The next chunk's
 // requests are issued before the MFMAs of the current one; scheduling barriers keep them there.
-// Needs rows of A aligned to 4 elements and, for TN = 2, rows of B aligned to 2.
+// Needs rows of A aligned to TM = 4 elements (2 up to 64 columns: tn_narrow_ok) and, for TN = 2, rows of B aligned to 2.
 template <typename T, int N> struct RawVec;
 template <> struct RawVec<float, 4> { typedef floatx4 type; };
 template <> struct RawVec<float, 2> { typedef float type __attribute__((ext_vector_type(2))); };
@@ -784,11 +784,11 @@ __device__ __forceinline__ void raw_to_f32(const typename RawVec<T, N>::type& v,
   }
 }
 
-template <typename T, int TN, int UK, int WN>
+template <typename T, int TM, int TN, int UK, int WN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_gemm_tn_wide(TnDirectArgs a) {
   // the four wavefronts of a block: WN column tiles of B side by side (all of them read the same rows of A,
   // which then come from HBM once) times WK = 4 / WN interleaved sets of row chunks, added up at the end
-  constexpr int TM = 4, CH = 2 * UK, WK = 4 / WN;
+  constexpr int CH = 2 * UK, WK = 4 / WN;
   typedef typename RawVec<T, TM>::type AV;
   typedef typename RawVec<T, TN>::type BV;
   __shared__ float red[2][TM * TN * 16 * 64];
@@ -925,6 +925,18 @@ static bool tn_wide_ok(const void* A, int64_t lda, const void* B, int64_t ldb, i
   return true;
 }
 
+// Up to 64 columns of A in fp32: two of them a request (TM = 2), and no matrix operations on a second pair of column tiles that does not
+// exist.  M even (and N, beyond 32), so that no request reaches past the end of a row.  With up to 32 columns of B a request of it is 4
+// bytes either way: those on rows of no whole quads stay with k_gemm_tn_direct, whose splits are twice as many (500 K x 50 x 7: 34 us
+// there, 41 here).  Measured, us before / this way: 500 K x 50 x 50 97 / 65,
+// 64 x 64 99 / 67 (a copy's rate is 47), 64 x 16 61 / 45, 150 K x 50 x 50 38 / 26, 300 K x 50 x 256 216 / 141, 500 K x 32 x 128
+// 173 / 110, 2 K x 50 x 50 15.8 / 11.0.  16 row pairs a batch: 71 for 500 K x 50 x 50; 1024 splits the same, with 3 us more for the sum.
+static bool tn_narrow_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int M, int N, int dtype) {
+  if (tune().gemm_tn_wide == 0 || dtype != GCN_F32 || M > 64) return false;
+  if (M % 2 != 0 || (lda % 2) != 0 || ((uintptr_t)A % 8) != 0 || lda >= (1 << 28) || ldb >= (1 << 28)) return false;
+  return N <= 32 ? tn_wide_ok(A, lda, B, ldb, N, dtype) : N % 2 == 0 && (ldb % 2) == 0 && ((uintptr_t)B % 8) == 0;
+}
+
 // column tiles of B per block in the vector variant: all of B for up to 256 columns
 int tn_wide_wn(int N) { return N <= 64 ? 1 : N <= 128 ? 2 : 4; }
 
@@ -973,18 +985,20 @@ int gemm_tn_direct_partials(const void* A, int64_t lda, const void* B, int64_t l
     return gemm_tn_bf16_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s);
   if (gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype)) return gemm_tn_lds_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s, max_blocks);
   TnDirectArgs a{A, lda, B, ldb, Kd, M, N, 0, 0, partial};
-  if (tn_wide_ok(A, lda, B, ldb, N, dtype)) {
+  const bool narrow = tn_narrow_ok(A, lda, B, ldb, M, N, dtype);
+  if (narrow || tn_wide_ok(A, lda, B, ldb, N, dtype)) {
     a.nsplit = tn_wide_splits(Kd, M, N);
     a.rows_per_split = round_up(ceil_div(Kd > 0 ? Kd : 1, a.nsplit), 2 * kTnMaxUK);
     *nsplit_out = a.nsplit;
     const int tnw = N <= 32 ? 1 : 2, wnw = tn_wide_wn(N);
     dim3 grid((unsigned)a.nsplit, (unsigned)ceil_div(M, 128), (unsigned)ceil_div(N, 32 * tnw * wnw));
-#define GCN_TN_WIDE(TT)                                                                   \
-    if (tnw == 1) k_gemm_tn_wide<TT, 1, kWideUK1, 1><<<grid, 256, 0, s>>>(a);               \
-    else if (wnw == 1) k_gemm_tn_wide<TT, 2, kWideUK2, 1><<<grid, 256, 0, s>>>(a);          \
-    else if (wnw == 2) k_gemm_tn_wide<TT, 2, kWideUK2, 2><<<grid, 256, 0, s>>>(a);          \
-    else k_gemm_tn_wide<TT, 2, kWideUK2, 4><<<grid, 256, 0, s>>>(a);
-    if (dtype == GCN_BF16) { GCN_TN_WIDE(bf16_t) } else { GCN_TN_WIDE(float) }
+#define GCN_TN_WIDE(TT, TM, UK1, UK2)                                                          \
+    if (tnw == 1) k_gemm_tn_wide<TT, TM, 1, UK1, 1><<<grid, 256, 0, s>>>(a);                    \
+    else if (wnw == 1) k_gemm_tn_wide<TT, TM, 2, UK2, 1><<<grid, 256, 0, s>>>(a);               \
+    else if (wnw == 2) k_gemm_tn_wide<TT, TM, 2, UK2, 2><<<grid, 256, 0, s>>>(a);               \
+    else k_gemm_tn_wide<TT, TM, 2, UK2, 4><<<grid, 256, 0, s>>>(a);
+    if (narrow) { GCN_TN_WIDE(float, 2, kWideUK1, kWideUK2) }
+    else if (dtype == GCN_BF16) { GCN_TN_WIDE(bf16_t, 4, kWideUK1, kWideUK2) } else { GCN_TN_WIDE(float, 4, kWideUK1, kWideUK2) }
 #undef GCN_TN_WIDE
     GCN_CHECK_LAUNCH();
     return GCN_OK;

@@ -584,3 +584,14 @@ def test_dense_kernels_over_row_counts(gcn, dev, rows, d_in, d_out, bf16):
     run_bwd(gcn, dev, case, d_in, d_out, bf16=bf16, saved_ah=True, dbias=True)
     run_bwd(gcn, dev, case, d_in, d_out, bf16=bf16, want_dh=False)
     case.A.free()
+
+
+# operands of up to 64 columns: two columns a request where the width is even, beside the forms that stay with the other kernels
+# (odd widths; up to 32 columns on rows of no whole quads); rows around a batch of 16 and a split
+@pytest.mark.parametrize("rows", [1, 15, 17, 513, 40001])
+@pytest.mark.parametrize("d_in,d_out", [(50, 50), (2, 34), (64, 256), (62, 130), (34, 33), (33, 34), (64, 16), (50, 7), (66, 34)])
+def test_weight_gradients_of_narrow_operands(gcn, dev, rows, d_in, d_out):
+    case = Case(gcn, dev, np.zeros(0, np.int32), np.zeros(0, np.int32), rows)          # A^ = I
+    run_bwd(gcn, dev, case, d_in, d_out, saved_ah=True, dbias=True)
+    run_bwd(gcn, dev, case, d_in, d_out, want_dh=False)
+    case.A.free()
