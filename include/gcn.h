@@ -189,6 +189,9 @@ int gcn_halo_gather(const void* table, int64_t ld, int64_t n_table_rows, int d, 
  * (gcn_debug_set_tuning "GCN_OVERLAP" 0 keeps everything on `stream`).  Capture: once a first call has sized the
  * workspace and created the second stream, the layer calls only enqueue kernels and event waits, and can be captured
  * into a HIP graph through `stream` (the second stream joins the capture through its events).
+ * A result in the place of H (or, in the backward pass below, dH in the place of a G that dW does not read, d_out < d_in
+ * without AH_saved): only where everything of the call stays on `stream`.  Both products are then launches of their own, the first of
+ * which has read the operand when the second stores.
  */
 int gcn_layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, const float* W,
                   const float* bias, int d_in, int d_out, int act, int dtype, void* Z, void* Hout,

@@ -8,6 +8,8 @@
 //   backward  T = A^T G at width d_out, then dH = T W^T and dW = H^T T  (Sec. 4.2 notes that the
 //             sparse product with G is shared between S and dW), or
 //             Q = G W^T, dH = A^T Q at width d_in, and dW = (A H)^T G.
+#include <initializer_list>
+
 #include "common.h"
 
 namespace gcn {
@@ -176,6 +178,29 @@ static bool one_launch(const SpmmArgs& a, int N) {
   return a.n_rows <= (a.dtype == GCN_F32 && a.d * N >= 4096 ? 8192 : 4096) && !spmm_panel_wanted(a);
 }
 
+// n rows of a buffer: pitch and row length in bytes
+struct Rows { const void* p; int64_t n, ld, row; };
+
+// Do two buffers share a byte?  Those of one pitch in different columns of the same rows do not.
+static bool rows_overlap(const Rows& a, const Rows& b) {
+  if (!a.p || !b.p || a.n == 0 || b.n == 0) return false;
+  const uintptr_t a0 = (uintptr_t)a.p, b0 = (uintptr_t)b.p;
+  if (a0 + (uintptr_t)((a.n - 1) * a.ld + a.row) <= b0 || b0 + (uintptr_t)((b.n - 1) * b.ld + b.row) <= a0) return false;
+  if (a.ld != b.ld) return true;
+  const int64_t ahead = b0 >= a0 ? (int64_t)(b0 - a0) % a.ld : (a.ld - (int64_t)(a0 - b0) % a.ld) % a.ld;
+  return ahead < a.row || ahead + b.row > a.ld;
+}
+
+// Does a result C (or C2, or the stored sparse rows Y) take the place of an operand that the kernel for both products still reads, or Y
+// that of another result?  Of the two kernels the first has read all of X before the second stores, and W where the dense product
+// comes first: a layer whose output overwrites its input, or dH its G, is right there, and in one launch a race between
+// the workgroups that gather and those that store.
+static bool results_in_place(const Rows& X, const Rows& W, const Rows& C, const Rows& C2, const Rows& Y) {
+  for (const Rows* o : {&C, &C2, &Y})
+    if (rows_overlap(X, *o) || rows_overlap(W, *o)) return true;
+  return rows_overlap(Y, C) || rows_overlap(Y, C2);
+}
+
 // May the sparse product come first, and be wider than it need be, for the sake of one launch less?  Its extra gathers come out
 // of L2 (4 K rows of 20 entries 100 -> 50: 28 MB more, 15.8 -> 7.5 us).
 static bool short_chain(const gcn_csr* A, int d_wide, int d_narrow, int dtype) {
@@ -214,7 +239,11 @@ static int layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
   sparse.owner = Am;
   sparse.x_rows_padded = ldhp != ldh || h_backed;
   sparse.y_rows_padded = true;              // a pitch of the outputs beyond their width comes from the _ld call
-  const bool fused = (AH_save != nullptr || d_in <= d_out || short_chain(A, d_in, d_out, dtype)) && one_launch(sparse, d_out);
+  const int64_t eb = (int64_t)es;
+  const bool fused = (AH_save != nullptr || d_in <= d_out || short_chain(A, d_in, d_out, dtype)) && one_launch(sparse, d_out) &&
+                     !results_in_place({ldhp != ldh ? nullptr : H, A->nc, ldh * eb, d_in * eb}, {W, d_in, d_out * 4, d_out * 4},
+                                       {Hout, A->nr, ldo * eb, d_out * eb}, {Z, A->nr, ldz * eb, d_out * eb},
+                                       {AH_save, A->nr, ldah * eb, d_in * eb});
   const bool sparse_first = AH_save != nullptr || d_in <= d_out || fused;
   const int relu = act == GCN_ACT_RELU;
 
@@ -331,7 +360,10 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
     sparse_t.x_rows_padded = pad_g || g_rows_backed;
     sparse_t.y_rows_padded = true;
     sparse_t.owner = Am;
-    fused = dH && (via_T || d_out == d_in || short_chain(A, d_out, d_in, dtype)) && one_launch(sparse_t, d_in);
+    const int64_t eb = (int64_t)es;
+    fused = dH && (via_T || d_out == d_in || short_chain(A, d_out, d_in, dtype)) && one_launch(sparse_t, d_in) &&
+            !results_in_place({pad_g ? nullptr : G, A->nr, ldg * eb, d_out * eb}, {W, d_in, d_out * 4, d_out * 4},
+                              {dH, A->nc, lddh * eb, d_in * eb}, {}, {});
     via_T |= fused;
   }
 

@@ -435,6 +435,78 @@ def test_layer_as_one_kernel_and_as_two(gcn, dev, er, hubs, directed_block, many
         gcn.gcn_debug_set_tuning("GCN_SPMM_DENSE", None)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n", [2000, 4096])
+def test_small_layer_results_in_place_of_operands(gcn, dev, n, bf16):
+    """A result may overwrite an operand that the call has read by then, at sizes where both products take one launch: then they take
+    two, and give the bits of two; buffers beside each other in the same rows are no such case."""
+    import torch
+    rng = np.random.default_rng(n)
+    u, v = rng.integers(0, n, 6 * n), rng.integers(0, n, 6 * n)
+    case = Case(gcn, dev, np.r_[u, v], np.r_[v, u], n)
+    A, tdt = case.A, torch.bfloat16 if bf16 else torch.float32
+    kw = dict(dtype=tdt, device=dev)
+
+    def call(two_kernels, f):
+        gcn.gcn_debug_set_tuning("GCN_SPMM_DENSE", 0 if two_kernels else None)
+        gcn.gcn_profile_enable(True)
+        try:
+            f()
+            torch.cuda.synchronize()
+            return sum(r["kind"] == "gemm_nn" for r in gcn.gcn_profile_records()[0])
+        finally:
+            gcn.gcn_profile_enable(False)
+            gcn.gcn_debug_set_tuning("GCN_SPMM_DENSE", None)
+
+    def same(a, b):
+        return np.array_equal(to_np(a), to_np(b))
+
+    # widths, the columns of one buffer of pitch 128 that the operand and the result take, and whether these meet
+    for d, dn, at, out_at, meet in [(64, 64, 0, 0, True), (64, 64, 0, 32, True), (64, 64, 0, 64, False), (64, 64, 64, 0, False), (32, 64, 64, 0, False),
+                                    (100, 48, 0, 0, True), (48, 96, 0, 32, True), (32, 96, 96, 0, False)]:
+        for direction in ("fwd", "fwd Z", "bwd"):
+            say(f"{direction} {d}->{dn} n={n} bf16={bf16} columns {at} and {out_at}")
+            x0 = torch.randn(n, d, device=dev).to(tdt)
+            w = torch.randn(d, dn, device=dev) if direction != "bwd" else torch.randn(dn, d, device=dev)
+            H = torch.randn(n, dn, device=dev).to(tdt)
+            got = []
+            bufs = [torch.zeros(n + 1, 128, **kw) for _ in range(3)]
+            for buf_x, buf_o in [(bufs[0], bufs[1]), (bufs[2], bufs[2])]:
+                x, o = buf_x[:n, at:at + d], buf_o[:n, out_at:out_at + dn]
+                x.copy_(x0)
+                dW, other = torch.empty(dn, d, device=dev), torch.empty(n, dn, **kw)
+                if direction == "bwd":
+                    f = lambda: gcn.gcn_layer_bwd_ld(A, H, w, x, dW, dH=o)
+                elif direction == "fwd":
+                    f = lambda: gcn.gcn_layer_fwd_ld(A, x, w, o)
+                else:
+                    f = lambda: gcn.gcn_layer_fwd_ld(A, x, w, other, Z=o)
+                apart = buf_x is not buf_o
+                launches = call(apart and meet, f)      # (where they do not meet: one launch both times)
+                assert (launches > 0) == meet, (direction, d, dn, at, out_at, apart, launches)
+                got.append((o.clone(), dW if direction == "bwd" and d < dn else other if direction == "fwd Z" else o.clone()))
+            # (dW of d >= dn reads G itself, after dH has taken its place)
+            assert same(got[0][0], got[1][0]) and same(got[0][1], got[1][1]), (direction, d, dn, at, out_at)
+
+    # contiguous buffers: H, and W inside the result of a product that takes W first
+    x0, w = torch.randn(n, 64, device=dev).to(tdt), torch.randn(64, 64, device=dev)
+    two, x = torch.empty(n, 64, **kw), x0.clone()
+    say(f"Hout over H n={n} bf16={bf16}")
+    call(True, lambda: gcn.gcn_layer_fwd(A, x0, w, two))
+    call(False, lambda: gcn.gcn_layer_fwd(A, x, w, x))
+    assert same(two, x)
+    x0, w = torch.randn(n, 100, device=dev).to(tdt), torch.randn(100, 50, device=dev)
+    out = torch.empty(n * 50, **kw)
+    wo = out.view(torch.float32)[:5000].view(100, 50)
+    wo.copy_(w)
+    two = torch.empty(n, 50, **kw)
+    say(f"Hout over W n={n} bf16={bf16}")
+    call(True, lambda: gcn.gcn_layer_fwd(A, x0, w, two))
+    call(False, lambda: gcn.gcn_layer_fwd(A, x0, wo, out.view(n, 50)))
+    assert same(two, out.view(n, 50))
+    case.A.free()
+
+
 @pytest.mark.parametrize("n", [63, 64, 65, 127, 128, 129, 511, 512, 513, 2050, 8320])
 def test_schedule_lists_at_the_edges_of_its_blocks(gcn, dev, n):
     """Rows of every length class (1, 2, 3 .. 1023, and from 2049 vertices on more than 2048 entries) at row counts around a
