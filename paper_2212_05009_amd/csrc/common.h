@@ -365,6 +365,7 @@ struct GemmEpilogue {
 // C = epilogue((A X) W) in one launch (spmm_dense.hip): sparse rows through LDS into the dense product; they are also stored
 // to a.Y where that is not null.  ws as spmm_launch; W and epi as gemm_nn's (K = a.d).
 bool spmm_dense_ok(const SpmmArgs& a, int N);
+bool spmm_dense_pays(const SpmmArgs& a, int N, bool widened);   // (ok: where the kernel applies)
 int spmm_dense(const SpmmArgs& a, void* ws, const float* W, int64_t ldw, void* C, int64_t ldc, int N, const GemmEpilogue& epi,
                hipStream_t s);
 // true when gemm_nn runs this product on the kernel that occupies whole compute units, one workgroup each, and

@@ -40,12 +40,12 @@ struct DenseK {
   int N;
   int vec;                                 // C, C2 and mask rows start on words: four columns at a time
   int store_s;                             // the sparse rows go to s.Y too
-  // Blocks of ordinary rows come first, the longest rows before the others, then those of hub rows: rows [share_row[i],
+  // Blocks of hub rows come first, then those of ordinary rows, the longest before the others: rows [share_row[i],
   // share_row[i + 1]) of the schedule's list get 16, 4 and 1 wavefronts each, in blocks from share_block[i] on.
-  int64_t share_row[4], share_block[3], row_blocks, n_blocks;
+  int64_t share_row[4], share_block[3], hub_blocks, n_blocks;
   int hub_partials;                        // hub rows come as partial rows, kRows to a block; else one to a block
 };
-constexpr int kHubChunksDirect = 64;
+constexpr int kHubChunksDirect = 4;
 
 template <typename T>
 __device__ __forceinline__ void load4(const T* __restrict__ p, float (&v)[4]) {
@@ -66,13 +66,13 @@ __global__ __launch_bounds__(64 * kRows) __attribute__((amdgpu_waves_per_eu(V * 
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, q = lane >> 4;
   const int d = a.s.d, steps = (d + 15) >> 4;
-  const bool hubs = blk >= a.row_blocks, partials = hubs && a.hub_partials;
+  const bool hubs = blk < a.hub_blocks, partials = hubs && a.hub_partials;
 
   // this wavefront's row, or its part of one, and the entries
   int64_t row = -1, s = 0; int n = 0, lw = 4;
   if (!partials) {
     if (hubs) {
-      row = a.s.hub_rows[blk - a.row_blocks];
+      row = a.s.hub_rows[blk];
     } else {
       const int i = blk >= a.share_block[2] ? 2 : blk >= a.share_block[1] ? 1 : 0;
       lw = 4 - 2 * i;
@@ -115,14 +115,22 @@ __global__ __launch_bounds__(64 * kRows) __attribute__((amdgpu_waves_per_eu(V * 
 
   if (partials) {
     // ---- rows of many entries: their chunks' partial rows in chunk order
-    const int64_t h0 = (blk - a.row_blocks) * kRows;
+    const int64_t h0 = blk * kRows;
     const int rows = (int)(a.s.n_hub_rows - h0 < kRows ? a.s.n_hub_rows - h0 : kRows);
     if (tid < kRows) s_row[tid] = tid < rows ? a.s.hub_rows[h0 + tid] : -1;
     for (int e = tid; e < rows * d; e += 64 * kRows) {
       const int r = e / d, f = e - r * d;
       const int64_t c_lo = a.s.hub_chunk_ptr[h0 + r], c_hi = a.s.hub_chunk_ptr[h0 + r + 1];
       float v = 0.f;
-      for (int64_t k = c_lo; k < c_hi; ++k) v += a.s.partial[k * d + f];
+      int64_t k = c_lo;
+      for (; k + 8 <= c_hi; k += 8) {      // (eight requests in flight)
+        float p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) p[u] = a.s.partial[(k + u) * d + f];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += p[u];
+      }
+      for (; k < c_hi; ++k) v += a.s.partial[k * d + f];
       S[r * kLds + f] = v;
       if (a.store_s) store_one<T>(reinterpret_cast<T*>(a.s.Y) + (int64_t)a.s.hub_rows[h0 + r] * a.s.ldy + f, v);
     }
@@ -155,9 +163,12 @@ __global__ __launch_bounds__(64 * kRows) __attribute__((amdgpu_waves_per_eu(V * 
     }
     if (lw > 0) {          // the parts of a row, in order; a thread keeps to its column, and row r is not read again once it is written
       __syncthreads();
+      auto quad = [&](int k) {
+        const float* p = S + k * kLds + tid;
+        return (p[0] + p[kLds]) + (p[2 * kLds] + p[3 * kLds]);
+      };
       for (int r = 0; tid < d && r < (kRows >> lw); ++r) {
-        float v = 0.f;
-        for (int k = 0; k < (1 << lw); ++k) v += S[((r << lw) + k) * kLds + tid];
+        const float v = lw == 2 ? quad(4 * r) : (quad(0) + quad(4)) + (quad(8) + quad(12));
         S[r * kLds + tid] = v;
         if (a.store_s && s_row[r] >= 0) store_one<T>(reinterpret_cast<T*>(a.s.Y) + (int64_t)s_row[r] * a.s.ldy + tid, v);
       }
@@ -204,29 +215,61 @@ __global__ __launch_bounds__(64 * kRows) __attribute__((amdgpu_waves_per_eu(V * 
   }
 }
 
-// Wavefronts per row by its length class: a lane group gathers 4 entries at a time, each about 0.6 us, so that a row of 16 or
-// more such rounds gets 4 wavefronts and one of 64 or more 16.  (From 8 and 32 on, 4 K uniform rows of up to 72 entries 128 -> 128
-// take 15.6 instead of 9.9 us: workgroups for a second round.  Rows of one share lie one behind the other across classes:
-// a block more than compute units is a round more.)
-static void place(DenseK& k, const Schedule* sc, int g_max) {
+// Lanes per row of nvec vectors, and workgroups that run at once.
+int lanes_of(int nvec, int dtype) { return nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 || dtype == GCN_BF16 ? 16 : 32; }
+int64_t slots_of(int lanes, int dtype) { return (dtype == GCN_BF16 ? 8 : 4) * lanes <= 16 ? 512 : 256; }
+
+// Workgroups for the rows of a schedule, in the order of their numbers: hub rows, then ordinary ones, the longest first.
+struct Shares {
+  int64_t row[4], block[3], hub_blocks, n_blocks, slots;
+  bool hub_partials;
+  int chain;                               // rounds of gathers of the longest ordinary row (by its class), one after the other
+};
+
+// Wavefronts per row by its length class: a lane group gathers 4 entries at a time, each round about 0.6 us, so a row of 4 or
+// more rounds gets 4 wavefronts and one of 16 or more 16, as long as all workgroups still run at once; else these numbers
+// are 8 and 32, or 16 and 64.  (From 8 and 32 on whatever the workgroups, 4 K uniform rows of up to 72 entries 128 -> 128 take 15.6
+// instead of 9.9 us: a workgroup more than run at once is a round more.  1296 products of 1 K to 8 K R-MAT and log-normal rows,
+// one kernel over two in the geometric mean: 16 and 64 throughout 0.85, this way 0.78.)
+//
+// A hub row that has a workgroup to itself is 16 chains of up to 256 entries, as long as those of its chunks in the sparse kernel (and
+// as exact), if it has no more than kHubChunksDirect of them, which the sums over all hub rows decide: each has three chunks at least.
+// Where a wavefront has two lane groups (fp32, more than 64 columns) the chunks are faster.  Measured, two kernels / a workgroup a
+// hub row / chunks: one row of 60 K entries 128 -> 128 35 / 275 / 29 us, error against 64 bits 2.0e-7 / 8.3e-7 / 2.0e-7; one of 4 K
+// 16 -> 16 8.9 / 7.1 / 9.1, 128 -> 128 26 / 25 / 17.
+Shares shares_of(const Schedule* sc, int lanes, int dtype) {
+  Shares o{};
+  const int g = 64 / lanes;
   auto begin = [&](int64_t len) {          // first row of the list that is shorter than len, a power of two
     int c = 31;
     while (((int64_t)1 << (31 - c)) < len) --c;
     return sc->class_begin[c + 1];
   };
-  k.share_row[0] = 0; k.share_row[1] = begin(256 * g_max); k.share_row[2] = begin(64 * g_max); k.share_row[3] = sc->n_wave_rows;
-  int64_t blocks = 0;
-  for (int i = 0; i < 3; ++i) {
-    k.share_block[i] = blocks;
-    blocks += ceil_div(k.share_row[i + 1] - k.share_row[i], i == 0 ? 1 : i == 1 ? 4 : kRows);
+  o.slots = slots_of(lanes, dtype);
+  o.hub_partials = sc->n_hub_rows > 0 && (lanes > 16 || sc->n_chunks - 3 * (sc->n_hub_rows - 1) > kHubChunksDirect);
+  o.hub_blocks = o.hub_partials ? ceil_div(sc->n_hub_rows, kRows) : sc->n_hub_rows;
+  const int64_t fit = round_up(ceil_div(sc->n_wave_rows + sc->n_hub_rows, kRows), o.slots);
+  for (int rounds = 4; rounds <= 16; rounds *= 2) {
+    o.row[0] = 0; o.row[1] = begin(16 * rounds * g); o.row[2] = begin(4 * rounds * g); o.row[3] = sc->n_wave_rows;
+    o.n_blocks = o.hub_blocks;
+    for (int i = 0; i < 3; ++i) {
+      o.block[i] = o.n_blocks;
+      o.n_blocks += ceil_div(o.row[i + 1] - o.row[i], i == 0 ? 1 : i == 1 ? 4 : kRows);
+    }
+    if (o.n_blocks <= fit) break;
   }
-  k.row_blocks = blocks;
-  k.n_blocks = blocks + (k.hub_partials ? ceil_div(sc->n_hub_rows, kRows) : sc->n_hub_rows);
+  for (int i = 0; i < 3; ++i) {            // the longest row of each share is in the class of its first row
+    if (o.row[i + 1] <= o.row[i]) continue;
+    int c = 0;
+    while (sc->class_begin[c + 1] <= o.row[i]) ++c;
+    const int64_t len = c >= 32 ? 0 : (int64_t)1 << (31 - c);
+    o.chain = std::max(o.chain, (int)(len / ((i == 0 ? 16 : i == 1 ? 4 : 1) * 4 * g)));
+  }
+  return o;
 }
 
 template <typename T, int V, int LPR>
-int launch_k(DenseK& k, const Schedule* sc, const SpmmProf& pf, hipStream_t s) {
-  place(k, sc, 64 / LPR);
+int launch_k(DenseK& k, const SpmmProf& pf, hipStream_t s) {
   if (!grid_fits(k.n_blocks)) return fail(GCN_EINVAL, "spmm: too many rows for one launch");
   ProfScope ps(pf.kind, s, k.s.d, pf.dtype, pf.rows, pf.nnz, pf.alg, pf.touched, pf.flops);
   k_spmm_dense<T, V, LPR><<<fold_grid(k.n_blocks), dim3(64 * kRows), 0, s>>>(k);
@@ -249,6 +292,26 @@ bool spmm_dense_ok(const SpmmArgs& a, int N) {
   return narrow && V * (a.dtype == GCN_BF16 ? 2 : 4) == 16;
 }
 
+// Is it faster than the two kernels?  Not where long rows are many, so that the rows are shared by more workgroups than run at
+// once, each with W to read: 4096 rows of 1000 entries 128 -> 256 184 us against 77, 2048 of 300 64 -> 64 18.3 / 14.7, 8192 of 128 128 ->
+// 128 62 / 42, while less than twice that number gains (R-MAT 4 K rows of 45 128 -> 256 19.4 / 29.3); with more than 4 K rows, which
+// are two rounds anyway, up to half more, and an eighth for more than 128 columns (8 K R-MAT rows of 45 128 -> 256 46 / 38).  Nor where
+// a long row's chain of gathers outlasts the little that there is to save: narrow products (64 -> 16 on log-normal rows of 45 13.2 /
+// 10.4, 16 -> 16 on R-MAT 12.1 / 10.6), and products whose rows are gathered `widened`, wider than the two kernels would (bf16 50 -> 7 on
+// R-MAT rows of 20 17.8 / 11.1, 128 -> 32 on log-normal ones of 128 14.1 / 12.0; 100 -> 50 with a hub row 30.6 / 25.0).
+// Over 7020 products (1 K to 8 K uniform, R-MAT and log-normal rows of 4 to 128 entries, 14 pairs of widths, both directions and types)
+// 0.81 in the geometric mean, under 1 % of them slower by 3 % or more (at most 1.15); with the kernel wherever it applies 4 %, up to 1.8.
+bool spmm_dense_pays(const SpmmArgs& a, int N, bool widened) {
+  const bool bf16 = a.dtype == GCN_BF16;
+  const Shares h = shares_of(a.sched, lanes_of((int)ceil_div(a.d, bf16 ? 8 : 4), a.dtype), a.dtype);
+  const int64_t at_once = round_up(ceil_div(a.n_rows, kRows), h.slots);
+  if (h.n_blocks > (a.n_rows <= 4096 ? 2 * at_once - 1 : N <= 128 ? at_once + at_once / 2 : at_once + at_once / 8)) return false;
+  if (widened && a.sched->n_hub_rows > 0) return false;
+  const int kn = a.d * N;
+  if (h.chain >= 8 && kn < (bf16 && widened ? 4097 : 2048)) return false;
+  return !(bf16 && widened && a.d > 32 && kn < 1024 && h.chain >= 1);
+}
+
 int spmm_dense(const SpmmArgs& a, void* ws, const float* W, int64_t ldw, void* C, int64_t ldc, int N, const GemmEpilogue& epi,
                hipStream_t s) {
   DenseK k{};
@@ -257,7 +320,11 @@ int spmm_dense(const SpmmArgs& a, void* ws, const float* W, int64_t ldw, void* C
   bool narrow = false;
   GCN_TRY(spmm_setup(a, ws, k.s, pf, &V, &narrow));
   const int64_t es = a.dtype == GCN_BF16 ? 2 : 4;
-  k.hub_partials = a.sched->n_chunks > kHubChunksDirect;
+  const int lanes = lanes_of(k.s.nvec, a.dtype);
+  const Shares h = shares_of(a.sched, lanes, a.dtype);
+  std::copy(h.row, h.row + 4, k.share_row);
+  std::copy(h.block, h.block + 3, k.share_block);
+  k.hub_blocks = h.hub_blocks; k.n_blocks = h.n_blocks; k.hub_partials = h.hub_partials;
   if (k.hub_partials) {
     SpmmK chunks = k.s;
     SpmmProf cp = pf;
@@ -278,14 +345,14 @@ int spmm_dense(const SpmmArgs& a, void* ws, const float* W, int64_t ldw, void* C
                        (k.store_s ? 0.0 : (double)es * (double)a.n_rows * a.d);
   pf.alg += extra; pf.touched += extra; pf.flops += 2.0 * (double)a.n_rows * a.d * N;
   if (a.dtype == GCN_BF16) {
-    if (k.s.nvec <= 4) return launch_k<bf16_t, 8, 4>(k, a.sched, pf, s);
-    if (k.s.nvec <= 8) return launch_k<bf16_t, 8, 8>(k, a.sched, pf, s);
-    return launch_k<bf16_t, 8, 16>(k, a.sched, pf, s);
+    if (lanes == 4) return launch_k<bf16_t, 8, 4>(k, pf, s);
+    if (lanes == 8) return launch_k<bf16_t, 8, 8>(k, pf, s);
+    return launch_k<bf16_t, 8, 16>(k, pf, s);
   }
-  if (k.s.nvec <= 4) return launch_k<float, 4, 4>(k, a.sched, pf, s);
-  if (k.s.nvec <= 8) return launch_k<float, 4, 8>(k, a.sched, pf, s);
-  if (k.s.nvec <= 16) return launch_k<float, 4, 16>(k, a.sched, pf, s);
-  return launch_k<float, 4, 32>(k, a.sched, pf, s);
+  if (lanes == 4) return launch_k<float, 4, 4>(k, pf, s);
+  if (lanes == 8) return launch_k<float, 4, 8>(k, pf, s);
+  if (lanes == 16) return launch_k<float, 4, 16>(k, pf, s);
+  return launch_k<float, 4, 32>(k, pf, s);
 }
 
 }  // namespace gcn

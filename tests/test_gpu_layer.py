@@ -507,6 +507,71 @@ def test_small_layer_results_in_place_of_operands(gcn, dev, n, bf16):
     case.A.free()
 
 
+@pytest.mark.parametrize("d", [16, 64, 128])
+@pytest.mark.parametrize("lens", [[2049], [4097], [60000], [9000, 2500, 5000], [3000] * 20])
+def test_long_rows_of_small_blocks(gcn, dev, lens, d):
+    """Rows of more than 2048 entries among 600 of a few, with halo columns: no less exact in one launch than in two.  Added up in
+    chunks they have the bits of two launches; by a workgroup of their own (up to 4 chunks a row, up to 64 columns) they are chains of
+    256 entries by 4 or more lane groups, as a chunk's are, and trees of these: 64 + 7 roundings of 2^-24, and one a chunk."""
+    import torch
+    rng = np.random.default_rng(d + len(lens))
+    n, nr = 70000, 600
+    src = np.r_[np.repeat(np.arange(nr), 5), np.repeat(np.arange(0, 7 * len(lens), 7), lens)]
+    dst = np.r_[rng.integers(0, n, 5 * nr), np.concatenate([rng.permutation(n)[:k] for k in lens])]
+    case = Case(gcn, dev, src, dst, n, 0, nr, deg_global=np.full(n, 5, np.int32))
+    og, long_rows = case.og, np.arange(0, 7 * len(lens), 7)
+    H = rng.standard_normal((og.nc, d)).astype(np.float32)
+    Hd, W = to_dev(H, dev), torch.eye(d, device=dev)
+    got = {}
+    for dense in (0, 2):
+        gcn.gcn_debug_set_tuning("GCN_SPMM_DENSE", dense)
+        try:
+            AH, out = torch.full((nr, d), float("nan"), device=dev), torch.full((nr, d), float("nan"), device=dev)
+            say(f"long rows {lens[0]} x {len(lens)} d={d} dense={dense}")
+            gcn.gcn_layer_fwd(case.A, Hd, W, out, act=gcn.ACT_NONE, AH_save=AH)
+            torch.cuda.synchronize()
+            got[dense] = to_np(AH)[long_rows]
+        finally:
+            gcn.gcn_debug_set_tuning("GCN_SPMM_DENSE", None)
+    chunks = sum(-(-int(og.rowptr[r + 1] - og.rowptr[r]) // 1024) for r in long_rows)
+    if d > 64 or chunks - 3 * (len(lens) - 1) > 4:
+        assert np.array_equal(got[0], got[2])
+    ref, bound = oracle.spmm(og.rowptr, og.col, og.val, H, rows=long_rows)
+    check_bound(got[2], ref, bound, (64 + 7 + chunks) * 2.0 ** -24 if d <= 64 else TOL_F32, "A H")
+    case.A.free()
+
+
+def test_small_layers_in_one_launch_where_it_pays(gcn, dev):
+    """Uniform rows of a few entries take one launch; of so many that every row is shared by workgroups, two; R-MAT rows
+    narrowed from 50 to 7 columns in bf16 two, widened one."""
+    import torch
+
+    def launches(src, dst, n, d_in, d_out, bf16):
+        case = Case(gcn, dev, src, dst, n)
+        tdt = torch.bfloat16 if bf16 else torch.float32
+        H, out = torch.ones(n, d_in, dtype=tdt, device=dev), torch.empty(n, d_out, dtype=tdt, device=dev)
+        gcn.gcn_profile_enable(True)
+        gcn.gcn_layer_fwd(case.A, H, torch.ones(d_in, d_out, device=dev), out, act=gcn.ACT_NONE)
+        torch.cuda.synchronize()
+        kinds = [r["kind"] for r in gcn.gcn_profile_records()[0]]
+        gcn.gcn_profile_enable(False)
+        ref = oracle.layer_fwd(case.og, np.ones((n, d_in), np.float32), np.ones((d_in, d_out), np.float32), act="none")
+        check_bound(to_np(out), ref["Hout"], ref["Bz"], TOL_BF16 if bf16 else TOL_F32, "Hout")
+        case.A.free()
+        return 2 if "gemm_nn" in kinds else 1
+
+    rng = np.random.default_rng(8)
+    n = 2048
+    few = rng.integers(0, n, (2, 5 * n))
+    many = np.stack([np.repeat(np.arange(n), 700), (np.repeat(np.arange(n), 700) + np.tile(np.arange(700), n)) % n])
+    skewed = np.minimum((n * rng.random((2, 20 * n)) ** 4).astype(np.int64), n - 1)
+    assert launches(few[0], few[1], n, 128, 256, False) == 1
+    assert launches(few[0], few[1], n, 50, 7, True) == 1
+    assert launches(many[0], many[1], n, 128, 256, False) == 2
+    assert launches(skewed[0], skewed[1], n, 50, 7, True) == 2
+    assert launches(skewed[0], skewed[1], n, 32, 128, True) == 1
+
+
 @pytest.mark.parametrize("n", [63, 64, 65, 127, 128, 129, 511, 512, 513, 2050, 8320])
 def test_schedule_lists_at_the_edges_of_its_blocks(gcn, dev, n):
     """Rows of every length class (1, 2, 3 .. 1023, and from 2049 vertices on more than 2048 entries) at row counts around a
