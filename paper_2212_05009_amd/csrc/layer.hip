@@ -169,15 +169,20 @@ static bool overlap_worthwhile(int64_t rows, int64_t nnz, int d) {
 // graph, uniform and R-MAT rows of 5 to 45 entries): up to 4 K rows fp32 0.38 to 0.9 / 0.5 to 0.95, bf16 0.58 to 1.03 / 0.6 to
 // 0.85; 8 K rows 128 -> 128 and 100 -> 50 fp32 0.54 to 1.0 / 0.6 to 0.93, 32 -> 64 0.86 to 1.12 / 0.77 to 0.87, bf16 0.86 to 1.7 / 0.7 to 1.06;
 // 16 K rows 0.82 to 2.3.
-// widened: the rows are gathered wider than the two kernels would; saves_product: these would need another sparse product.
-static bool one_launch(const SpmmArgs& a, int N, bool widened, bool saves_product) {
+static bool few_rows(int64_t rows, int d, int N, int dtype) {
   const Tuning& t = tune();
-  if (t.spmm_dense == 0 || !spmm_dense_ok(a, N)) return false;
-  if (t.spmm_dense == 2) return true;
+  if (t.spmm_dense != 1) return t.spmm_dense == 2;
   // (an override of a dense kernel is a choice between two-kernel forms)
   if (t.gemm_direct != 1 || t.gemm_fast != 1 || t.gemm_bf16 != 1 || t.gemm_regw != 1 || t.gemm_tn_lds != 1) return false;
-  return a.n_rows <= (a.dtype == GCN_F32 && a.d * N >= 4096 ? 8192 : 4096) && (saves_product || spmm_dense_pays(a, N, widened)) &&
-         !spmm_panel_wanted(a);
+  return rows <= (dtype == GCN_F32 && (int64_t)d * N >= 4096 ? 8192 : 4096);
+}
+
+// The same with the form of the operands and the lengths of the rows, which is not asked of more rows.
+// widened: the rows are gathered wider than the two kernels would;
+// saves_product: these would need another sparse product.
+static bool one_launch(const SpmmArgs& a, int N, bool widened, bool saves_product) {
+  if (!spmm_dense_ok(a, N)) return false;
+  return tune().spmm_dense == 2 || ((saves_product || spmm_dense_pays(a, N, widened)) && !spmm_panel_wanted(a));
 }
 
 // n rows of a buffer: pitch and row length in bytes
@@ -234,7 +239,9 @@ static int layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
   const size_t es = es_of(dtype);
   // sparse-first costs nnz*d_in gathers and a dense product over nr rows; dense-first costs
   // nnz*d_out gathers and a dense product over nc rows
-  const int64_t ldhp = padded_operand_ld(A, false, d_in, dtype, ldh);
+  const bool first = AH_save != nullptr || d_in <= d_out;
+  const bool few = few_rows(A->nr, d_in, d_out, dtype) && (first || short_chain(A, d_in, d_out, dtype));
+  const int64_t ldhp = first || few ? padded_operand_ld(A, false, d_in, dtype, ldh) : ldh;
   SpmmArgs sparse{A->rowptr, A->col, A->val, &A->sched, A->nr, A->nc, A->nnz, false, A->nr,
                   ldhp != ldh ? reinterpret_cast<const void*>((uintptr_t)256) : H, ldhp, nullptr, 0,
                   nullptr, 0, d_in, dtype, GCN_EPI_NONE, nullptr, nullptr, 0};      // A H, its operand as it will be
@@ -242,12 +249,11 @@ static int layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
   sparse.x_rows_padded = ldhp != ldh || h_backed;
   sparse.y_rows_padded = true;              // a pitch of the outputs beyond their width comes from the _ld call
   const int64_t eb = (int64_t)es;
-  const bool fused = (AH_save != nullptr || d_in <= d_out || short_chain(A, d_in, d_out, dtype)) &&
-                     one_launch(sparse, d_out, !AH_save && d_in > d_out, false) &&
+  const bool fused = few && one_launch(sparse, d_out, !first, false) &&
                      !results_in_place({ldhp != ldh ? nullptr : H, A->nc, ldh * eb, d_in * eb}, {W, d_in, d_out * 4, d_out * 4},
                                        {Hout, A->nr, ldo * eb, d_out * eb}, {Z, A->nr, ldz * eb, d_out * eb},
                                        {AH_save, A->nr, ldah * eb, d_in * eb});
-  const bool sparse_first = AH_save != nullptr || d_in <= d_out || fused;
+  const bool sparse_first = first || fused;
   const int relu = act == GCN_ACT_RELU;
 
   for (int pass = 0; pass < 2; ++pass) {      // pass 0 sizes the workspace, pass 1 runs
@@ -354,7 +360,8 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
   int64_t ldgp = ldg;
   bool fused = false;                       // T and dH in one launch
   SpmmArgs sparse_t{};                      // A^T G, its operand as it will be
-  if (have_csc && (via_T || dH)) {
+  const bool few = have_csc && dH && few_rows(A->nc, d_out, d_in, dtype) && (via_T || d_out == d_in || short_chain(A, d_out, d_in, dtype));
+  if (via_T || few) {
     ldgp = g_unaligned ? gather_ld_for(A, true, d_out, dtype) : padded_operand_ld(A, true, d_out, dtype, ldg);
     const bool pad_g = g_unaligned || ldgp != ldg;
     sparse_t = SpmmArgs{A->colptr, A->rowidx, A->val_t, &A->sched_t, A->nc, A->nr, A->nnz, true, A->nr,
@@ -364,8 +371,7 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
     sparse_t.y_rows_padded = true;
     sparse_t.owner = Am;
     const int64_t eb = (int64_t)es;
-    fused = dH && (via_T || d_out == d_in || short_chain(A, d_out, d_in, dtype)) &&
-            one_launch(sparse_t, d_in, d_out > d_in, !AH_saved && d_out >= d_in) &&
+    fused = few && one_launch(sparse_t, d_in, d_out > d_in, !AH_saved && d_out >= d_in) &&
             !results_in_place({pad_g ? nullptr : G, A->nr, ldg * eb, d_out * eb}, {W, d_in, d_out * 4, d_out * 4},
                               {dH, A->nc, lddh * eb, d_in * eb}, {}, {});
     via_T |= fused;
