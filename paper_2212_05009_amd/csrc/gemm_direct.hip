@@ -784,11 +784,13 @@ __device__ __forceinline__ void raw_to_f32(const typename RawVec<T, N>::type& v,
   }
 }
 
+// Two columns a request (TM = 2) leave registers for two sums per column tile, even and odd row pairs: chains half as long for the
+// same number of splits.
 template <typename T, int TM, int TN, int UK, int WN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_gemm_tn_wide(TnDirectArgs a) {
   // the four wavefronts of a block: WN column tiles of B side by side (all of them read the same rows of A,
   // which then come from HBM once) times WK = 4 / WN interleaved sets of row chunks, added up at the end
-  constexpr int CH = 2 * UK, WK = 4 / WN;
+  constexpr int CH = 2 * UK, WK = 4 / WN, SUMS = TM == 2 ? 2 : 1;
   typedef typename RawVec<T, TM>::type AV;
   typedef typename RawVec<T, TN>::type BV;
   __shared__ float red[2][TM * TN * 16 * 64];
@@ -818,13 +820,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
   const uint32_t aoff = acol + (uint32_t)(h * a.lda * (int64_t)sizeof(T));
   const uint32_t boff = bcol + (uint32_t)(h * a.ldb * (int64_t)sizeof(T));
 
-  floatx16 acc[TM][TN];
+  floatx16 sum[SUMS][TM][TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int b = 0; b < SUMS; ++b)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[b][i][j][r] = 0.f;
 
   auto load = [&](int64_t k, AV (&av)[UK], BV (&bv)[UK]) {
 #pragma unroll
@@ -862,8 +866,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u][i], bv[u][j], acc[i][j], 0, 0, 0);
+          sum[u % SUMS][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u][i], bv[u][j], sum[u % SUMS][i][j], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
+  }
+
+  floatx16 (&acc)[TM][TN] = sum[0];
+  if constexpr (SUMS == 2) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] += sum[1][i][j];
   }
 
   // add up the row sets of a column tile
@@ -926,15 +938,21 @@ static bool tn_wide_ok(const void* A, int64_t lda, const void* B, int64_t ldb, i
 }
 
 // Up to 64 columns of A in fp32: two of them a request (TM = 2), and no matrix operations on a second pair of column tiles that does not
-// exist.  M even (and N, beyond 32), so that no request reaches past the end of a row.  With up to 32 columns of B a request of it is 4
-// bytes either way: those on rows of no whole quads stay with k_gemm_tn_direct, whose splits are twice as many (500 K x 50 x 7: 34 us
-// there, 41 here).  Measured, us before / this way: 500 K x 50 x 50 97 / 65,
-// 64 x 64 99 / 67 (a copy's rate is 47), 64 x 16 61 / 45, 150 K x 50 x 50 38 / 26, 300 K x 50 x 256 216 / 141, 500 K x 32 x 128
-// 173 / 110, 2 K x 50 x 50 15.8 / 11.0.  16 row pairs a batch: 71 for 500 K x 50 x 50; 1024 splits the same, with 3 us more for the sum.
-static bool tn_narrow_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int M, int N, int dtype) {
+// exist.  M even (and N, beyond 32), so that no request reaches past the end of a row.
+// Rows of whole quads otherwise take four columns a request; measured, us with four / two: 2 K rows x 50 x 50 22.6 / 17.3, 20 K x 50 x
+// 256 88 / 62, 150 K x 50 x 50 45 / 33, 500 K x 64 x 64 98 / 66 (a copy's rate is 47), 64 x 16 63 / 46, 32 x 128 167 / 109.
+// Other rows take k_gemm_tn_direct, and this form only where it gains on it: from 2^19 rows on with 65 to 128 columns of B, from 3 2^18 on
+// with up to 64 or all four column tiles.  us there / here: 2 K x 50 x 50 16.2 / 17.3, 2 K x 50 x 256 22 / 58, 150 K x 50 x 100 42 / 47,
+// 400 K x 50 x 100 88 / 90, 1 M x 50 x 100 229 / 200, 50 x 50 119 / 117, 50 x 256 407 / 387; never 50 x 160 (340 / 391) or 50 x 300
+// (550 / 760).  Its splits are half as many there, of two sums each: chains as long as k_gemm_tn_direct's, and the same error against 64
+// bits (500 K x 50 x 100 2.9e-7; 4.1e-7 with one sum).
+static bool tn_narrow_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype) {
   if (tune().gemm_tn_wide == 0 || dtype != GCN_F32 || M > 64) return false;
   if (M % 2 != 0 || (lda % 2) != 0 || ((uintptr_t)A % 8) != 0 || lda >= (1 << 28) || ldb >= (1 << 28)) return false;
-  return N <= 32 ? tn_wide_ok(A, lda, B, ldb, N, dtype) : N % 2 == 0 && (ldb % 2) == 0 && ((uintptr_t)B % 8) == 0;
+  if (tn_wide_ok(A, lda, B, ldb, N, dtype)) return N <= 32 || N % 2 == 0;
+  if (N <= 32 || N % 2 != 0 || (ldb % 2) != 0 || ((uintptr_t)B % 8) != 0) return false;
+  if (N > 256 || (N > 128 && N <= 192)) return false;
+  return Kd >= (N > 64 && N <= 128 ? 2 << 18 : 3 << 18);
 }
 
 // column tiles of B per block in the vector variant: all of B for up to 256 columns
@@ -985,20 +1003,20 @@ int gemm_tn_direct_partials(const void* A, int64_t lda, const void* B, int64_t l
     return gemm_tn_bf16_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s);
   if (gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype)) return gemm_tn_lds_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s, max_blocks);
   TnDirectArgs a{A, lda, B, ldb, Kd, M, N, 0, 0, partial};
-  const bool narrow = tn_narrow_ok(A, lda, B, ldb, M, N, dtype);
+  const bool narrow = tn_narrow_ok(A, lda, B, ldb, Kd, M, N, dtype);
   if (narrow || tn_wide_ok(A, lda, B, ldb, N, dtype)) {
     a.nsplit = tn_wide_splits(Kd, M, N);
     a.rows_per_split = round_up(ceil_div(Kd > 0 ? Kd : 1, a.nsplit), 2 * kTnMaxUK);
     *nsplit_out = a.nsplit;
     const int tnw = N <= 32 ? 1 : 2, wnw = tn_wide_wn(N);
     dim3 grid((unsigned)a.nsplit, (unsigned)ceil_div(M, 128), (unsigned)ceil_div(N, 32 * tnw * wnw));
-#define GCN_TN_WIDE(TT, TM, UK1, UK2)                                                          \
-    if (tnw == 1) k_gemm_tn_wide<TT, TM, 1, UK1, 1><<<grid, 256, 0, s>>>(a);                    \
-    else if (wnw == 1) k_gemm_tn_wide<TT, TM, 2, UK2, 1><<<grid, 256, 0, s>>>(a);               \
-    else if (wnw == 2) k_gemm_tn_wide<TT, TM, 2, UK2, 2><<<grid, 256, 0, s>>>(a);               \
-    else k_gemm_tn_wide<TT, TM, 2, UK2, 4><<<grid, 256, 0, s>>>(a);
-    if (narrow) { GCN_TN_WIDE(float, 2, kWideUK1, kWideUK2) }
-    else if (dtype == GCN_BF16) { GCN_TN_WIDE(bf16_t, 4, kWideUK1, kWideUK2) } else { GCN_TN_WIDE(float, 4, kWideUK1, kWideUK2) }
+#define GCN_TN_WIDE(TT, TM)                                                                    \
+    if (tnw == 1) k_gemm_tn_wide<TT, TM, 1, kWideUK1, 1><<<grid, 256, 0, s>>>(a);               \
+    else if (wnw == 1) k_gemm_tn_wide<TT, TM, 2, kWideUK2, 1><<<grid, 256, 0, s>>>(a);          \
+    else if (wnw == 2) k_gemm_tn_wide<TT, TM, 2, kWideUK2, 2><<<grid, 256, 0, s>>>(a);          \
+    else k_gemm_tn_wide<TT, TM, 2, kWideUK2, 4><<<grid, 256, 0, s>>>(a);
+    if (narrow) { GCN_TN_WIDE(float, 2) }
+    else if (dtype == GCN_BF16) { GCN_TN_WIDE(bf16_t, 4) } else { GCN_TN_WIDE(float, 4) }
 #undef GCN_TN_WIDE
     GCN_CHECK_LAUNCH();
     return GCN_OK;

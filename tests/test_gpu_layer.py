@@ -732,3 +732,28 @@ def test_weight_gradients_of_narrow_operands(gcn, dev, rows, d_in, d_out):
     run_bwd(gcn, dev, case, d_in, d_out, saved_ah=True, dbias=True)
     run_bwd(gcn, dev, case, d_in, d_out, want_dh=False)
     case.A.free()
+
+
+# Chains of fp32 additions in the weight gradient.  A sum of n products of zero mean in one chain: the k-th addition rounds a partial sum
+# of sqrt(k) by 0.41 units of 2^-24 (rms, over the binade), so the error is 0.29 n units, and 0.29 sqrt(n) of the result, with the partial
+# sums of the chains added up in fp64.  n per width: rows of a split over the four wavefronts that share it, as the kernel with one
+# request per matrix operation deals them (splits of 192 to 512 rows).
+@pytest.mark.parametrize("rows,d_in,d_out,n", [(3001, 50, 100, 48), (3001, 50, 256, 112), (3001, 50, 160, 64), (3001, 34, 300, 80), (3001, 62, 64, 32),
+                                               (300007, 50, 50, 98), (300007, 50, 100, 147), (300007, 50, 160, 220), (300007, 34, 256, 294),
+                                               (600011, 50, 100, 294), (1100003, 34, 256, 1076), (1100003, 50, 34, 270)])
+def test_weight_gradients_of_narrow_operands_are_as_exact_as_any(gcn, dev, rows, d_in, d_out, n):
+    import torch
+    case = gcn.gcn_csr_build(torch.zeros(0, dtype=torch.int32, device=dev), torch.zeros(0, dtype=torch.int32, device=dev), rows)
+    g = torch.Generator(device=dev)
+    g.manual_seed(d_out)
+    H, G = torch.randn(rows, d_in, generator=g, device=dev), torch.randn(rows, d_out, generator=g, device=dev)
+    dW = torch.full((d_in, d_out), float("nan"), device=dev)
+    say(f"dW {rows} x {d_in} x {d_out}")
+    gcn.gcn_layer_bwd(case, H, torch.zeros(d_in, d_out, device=dev), G, dW, AH_saved=H)
+    torch.cuda.synchronize()
+    h, gr = to_np(H).astype(np.float64), to_np(G).astype(np.float64)
+    ref = h.T @ gr
+    err = np.linalg.norm(to_np(dW) - ref) / np.linalg.norm(ref)
+    print(f"error {err:.3e}, of chains of {n} rows {0.29 * np.sqrt(n) * 2.0 ** -24:.3e}")
+    assert err <= 1.25 * 0.29 * np.sqrt(n) * 2.0 ** -24
+    case.free()
