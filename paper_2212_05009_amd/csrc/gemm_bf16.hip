@@ -62,13 +62,14 @@ __device__ __forceinline__ void unpack4(const u32x2& v, float (&o)[4]) {
 // One wavefront per tile of 16 rows.  Lane (c, q) = (lane % 16, lane / 16) supplies row c of the tile as the
 // second MFMA operand (k = KS s + LV q .. + LV - 1 of k step s, KS = 4 LV) and the column 16 t + c of W as the
 // first, so register r of its accumulator t is column 16 t + 4 q + r of row c: four consecutive outputs.
-// KL = K / KS k steps per tile; a part of a row is asked for again, from the next tile, as soon as its MFMAs are issued, the next
-// tile's mask as soon as this one's is used, and nothing branches between a tile's requests and their use, its stores included
+// KL = K / KS k steps per tile; a part of a row is asked for again, from the next tile, as soon as its MFMAs are issued, a tile's mask
+// before its first MFMA, and nothing branches between a tile's requests and their use, its stores included
 // (gemm_direct.hip, k_gemm_nn_fast, has the reason).  Measured, us with conditional stores and bias loads between them and W
 // taken value by value / this way, the bytes at a copy's 5.4 TB/s behind: 2^18 x 128 -> 128 38.9 / 30.0 (25), 2.4 M rows 100 ->
-// 256 664 / 611 (323), 256 -> 256 915 / 741 (464), 256 -> 47 484 / 472 (275), 256 <- 256 with a mask 787 / 594 (T was in the
-// last-level cache), 47 -> 256 with a mask 619 / 627 (507).  More wavefronts do not help (three blocks; 6 wavefronts and two
-// blocks with 256 columns: 668 for 100 -> 256): the rate of the requests bounds it, not their number in flight.
+// 256 664 / 611 (323), 256 -> 256 915 / 741 (464), 256 -> 47 484 / 472 (275); with a mask 256 -> 256 740 / 598 (T was in the last-level
+// cache), 47 -> 256 592 / 582 (507), 128 -> 256 640 / 658, on 300 K rows 47 -> 256 97 / 83.  (The mask asked for a tile ahead: 612, 692, 90.)
+// More wavefronts do not help (three blocks; 6 wavefronts and two blocks with 256 columns: 668 for 100 -> 256): the rate of the
+// requests bounds it, not their number in flight.
 template <int NT, int KL, int LV, bool MASK, bool SAVE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_gemm_nn_bf16(NnBf16Args a) {
   typedef typename Frag<LV>::raw Raw;
@@ -203,7 +204,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     const bf16_t* __restrict__ arow = a_row(tile);
 #pragma unroll
     for (int s = 0; s < KL; ++s) load_a(arow, s, av[s]);
-    if constexpr (MASK) load_mask(tile, keep);
     // (as many requests behind the operand's as the loop is repeated with: dropped stores for those of a tile before)
     const RowsBuf cb = rows_buf<bf16_t>(a.C, tile * 16, a.ldc, rows_left(tile));
     const Group none{};
@@ -217,6 +217,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     asm volatile("" ::: "memory");         // (the bias stays in LDS)
     const int64_t after = tile + stride < ntiles ? tile + stride : tile;      // (at the end the same tile again, unused)
     const bf16_t* __restrict__ next = a_row(after);
+    if constexpr (MASK) { load_mask(tile, keep); __builtin_amdgcn_sched_barrier(0); }
     floatx4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -262,12 +263,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
         out2[j][half] = (uint32_t)f32_to_bf16(pre[0]) | ((uint32_t)f32_to_bf16(pre[1]) << 16);
         out2[j][half + 1] = (uint32_t)f32_to_bf16(pre[2]) | ((uint32_t)f32_to_bf16(pre[3]) << 16);
       }
-    }
-    // (the next tile's mask ahead of this tile's stores: requests are answered in order)
-    if constexpr (MASK) {
-      __builtin_amdgcn_sched_barrier(0);
-      load_mask(after, keep);
-      __builtin_amdgcn_sched_barrier(0);
     }
     Group last{}, last2{};                 // the group that column N cuts where nothing may be written behind it, and where it starts
     int at = a.N;

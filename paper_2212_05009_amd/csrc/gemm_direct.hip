@@ -319,9 +319,11 @@ constexpr bool nn_two_blocks(int NT, int KU, bool MASK) { return NT <= 8 && !(MA
 // requests in flight, and behind a join at which some stores may not have been issued the only safe wait for the next tile's
 // operand is a wait for all, stores too - one round trip of the stores per tile, and the matrix pipe idle meanwhile.  So rows past M
 // and columns past N are dropped by the stores' range check, the mask of a tile is requested before its first MFMA, and
-// the chunks of a tile are unrolled.  Measured, us with conditional stores and bias loads between them / this way: 500 K rows 50 ->
-// 50 55 / 49, 64 -> 64 55 / 47 (5.4 TB/s, the rate of a copy), 48 -> 48 37 / 33; 2.45 M rows 47 -> 256 974 / 834, with the mask
-// 1396 / 1124; 2^18 rows 16 -> 128 with the mask 62 / 58; 2^20 rows 32 -> 128 189 / 176; 128 -> 128, bound by the matrix pipe, 163 / 160.
+// the chunks of a tile are unrolled.  (Asked for a tile ahead instead, with this tile's stores behind it, the mask costs up to 20 %:
+// 40 K rows 16 -> 128 17.4 us against 14.0, 100 K 47 -> 256 68 / 60, 2.45 M 1107 / 1086.)  Measured on rows of whole lines, us with
+// conditional stores and bias loads between them / this way: 300 K rows 50 -> 50 41 / 33, 64 -> 64 36.5 / 31.0, 32 -> 128 42 / 38,
+// 47 -> 256 144 / 124, 128 -> 128 114 / 98 (100 TFLOP/s: the matrix pipe); with the mask 50 -> 50 40 / 35, 41 -> 128 95 / 73, 47 -> 256
+// 179 / 136, on 2.45 M rows 1389 / 1086; but 64 -> 64 and 50 -> 50 with the mask on 1 M rows and more 107 / 114 and 126 / 136.
 template <typename T, int NT, int KU, int CH, bool MASK, bool SAVE, bool FULL>
 __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(nn_two_blocks(NT, KU, MASK) ? 4 : 2, 8))) void k_gemm_nn_fast(NnDirectArgs a) {
   // W in LDS.  NT a multiple of 4: [k][t / 4][c][t % 4], so that the four column tiles 4 tq .. 4 tq + 3 of a
@@ -375,8 +377,8 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(nn_t
 
   int64_t tile = (int64_t)blockIdx.x * WPB + w;
   if (tile >= ntiles) return;
-  // Registers hold one operand row part and one mask quad of each kind: as soon as the MFMAs of a part are issued, the same
-  // part of the next chunk or tile is asked for, and the next tile's mask as soon as this one's is used.
+  // Registers hold one operand row part of each kind: as soon as its MFMAs are issued, the same part of the next chunk or tile is
+  // asked for.
   float av[KU][4];
   float keep[MASK ? NT : 1][4];
   {
@@ -386,11 +388,7 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(nn_t
     // The loop is entered with as many requests behind the operand's as it is repeated with, so that its waits need not tell
     // the two apart: stores that the range check drops stand for those of a tile before.
     const RowsBuf cb = rows_buf<T>(a.C, tile * 16, a.ldc, rows_left(tile));
-    RowsBuf mb = cb;
-    if constexpr (MASK) mb = rows_buf<T>(a.mask, tile * 16, a.ldmask, rows_left(tile));
     const float none[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < (MASK ? NT : 0); ++t) buf_load4<T>(mb, place(a.ldmask, 16 * t + 4 * q), keep[t]);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       if constexpr (SAVE) buf_store4<T>(cb, kNoPlace - 32 * t - 16, none);
@@ -400,6 +398,12 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(nn_t
   for (; tile < ntiles; tile += stride) {
     asm volatile("" ::: "memory");         // (the bias stays in LDS)
     const int64_t after = tile + stride < ntiles ? tile + stride : tile;      // (at the end the same tile again, unused)
+    if constexpr (MASK) {
+      const RowsBuf mb = rows_buf<T>(a.mask, tile * 16, a.ldmask, rows_left(tile));
+#pragma unroll
+      for (int t = 0; t < NT; ++t) buf_load4<T>(mb, place(a.ldmask, 16 * t + 4 * q), keep[t]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     floatx4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -466,8 +470,7 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(nn_t
     float last[4] = {0.f, 0.f, 0.f, 0.f}, last2[4] = {0.f, 0.f, 0.f, 0.f};      // the quad that column N cuts, and where it starts
     int at = a.N;
     const RowsBuf cb = rows_buf<T>(a.C, tile * 16, a.ldc, rows_left(tile));
-    RowsBuf cb2 = cb, mb = cb;
-    if constexpr (MASK) mb = rows_buf<T>(a.mask, after * 16, a.ldmask, rows_left(after));
+    RowsBuf cb2 = cb;
     if constexpr (SAVE) cb2 = rows_buf<T>(a.C2, tile * 16, a.ldc2, rows_left(tile));
     float v[NT][4];
 #pragma unroll
@@ -479,10 +482,7 @@ __global__ __launch_bounds__(kNnThreads) __attribute__((amdgpu_waves_per_eu(nn_t
         v[t][r] = acc[t][r] > 0.f ? acc[t][r] : __uint_as_float(__float_as_uint(acc[t][r]) & neg);
         if constexpr (MASK) v[t][r] = keep[t][r] > 0.f ? v[t][r] : 0.f;
       }
-      // (the next tile's mask ahead of this tile's stores: requests are answered in order)
-      if constexpr (MASK) buf_load4<T>(mb, place(a.ldmask, t * 16 + 4 * q), keep[t]);
     }
-    if constexpr (MASK) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const int n = t * 16 + 4 * q;
