@@ -46,17 +46,46 @@ def check_induced(gcn, dev, A, src, dst, n, V):
     return og, B
 
 
-@pytest.mark.parametrize("total", [2047, 2048, 2049, 4096])
-@pytest.mark.parametrize("short", [True, False])
-def test_induced_at_the_edges_of_its_blocks(gcn, dev, total, short):
-    """A whole number of blocks of 2048 selected entries and beside it: in rows of one entry (as many rows as a block can
-    hold), and in one row that fills a block followed by rows of one."""
-    n = 6000
-    hub = np.zeros(0, np.int64) if short else np.arange(1, 2048)         # vertex 0: 2048 entries with its diagonal
-    src, dst = np.zeros(hub.size, np.int64), hub
+def check_selected(A, V, total, kept, og):
+    """The case is the one meant: entries of the selected rows in the parent, and those off the diagonal that stay."""
+    rowptr = A.arrays()["rowptr"].cpu().numpy()
+    assert int((rowptr[V + 1] - rowptr[V]).sum()) == total
+    assert og.nnz - len(V) == kept
+
+
+@pytest.mark.parametrize("total", [2047, 2048, 2049, 4096, 6145])
+@pytest.mark.parametrize("kept", ["none", "all"])
+def test_induced_at_the_edges_of_its_blocks(gcn, dev, total, kept):
+    """A whole number of blocks of 2048 selected entries and beside it: in rows of one entry (as many rows as a block can hold),
+    and in k rows of k entries that are all kept, the first and the last of every block among them.  (Rows of falling
+    ids: a row's diagonal is neither the first entry of the first row nor the last of the others.)"""
+    n = 9200
+    k = 0 if kept == "none" else int(total ** 0.5)
+    ids = 3000 + np.arange(k)
+    src, dst = np.repeat(ids, k), np.tile(ids, k)
     A = gcn.gcn_csr_build(dev_i32(src, dev), dev_i32(dst, dev), n)
-    V = np.r_[0, np.arange(n)[::-1][:total - (1 if short else 2048)]] if total > 2048 or short else np.r_[0, 5]
-    _, B = check_induced(gcn, dev, A, src, dst, n, V)
+    V = np.r_[ids[::-1][:k // 2], np.r_[np.arange(3000), np.arange(4000, n)][:total - k * k], ids[::-1][k // 2:]]
+    og, B = check_induced(gcn, dev, A, src, dst, n, V)
+    check_selected(A, V, total, k * (k - 1), og)
+    B.free()
+    A.free()
+
+
+@pytest.mark.parametrize("length", [2047, 2048, 2049, 4096, 4097])
+@pytest.mark.parametrize("before", [0, 1, 2047])
+def test_induced_keeps_the_ends_of_its_blocks(gcn, dev, length, before):
+    """One row of several blocks, behind `before` rows of one entry: only the first and the last entry of every block of 2048 that
+    lies in it are kept, and the row's ends."""
+    n, hub = 12000, 4000
+    cols = hub - length // 3 + np.arange(length)          # its entries, the diagonal among them
+    ends = [s for s in range(length) if s in (0, length - 1) or (before + s) % 2048 in (0, 2047)]
+    ends = [s for s in ends if cols[s] != hub]
+    src, dst = np.full(length, hub), cols
+    A = gcn.gcn_csr_build(dev_i32(src, dev), dev_i32(dst, dev), n)
+    V = np.r_[9000 + np.arange(before), hub, cols[ends]]
+    og, B = check_induced(gcn, dev, A, src, dst, n, V)
+    check_selected(A, V, before + length + len(ends), len(ends), og)
+    assert len(ends) >= 2
     B.free()
     A.free()
 
