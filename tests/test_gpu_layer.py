@@ -27,6 +27,20 @@ def dev():
     return torch.device("cuda:0")
 
 
+@pytest.fixture
+def tuned(gcn):
+    """Sets kernel-selection overrides (None: the default) for the length of a test."""
+    names = set()
+
+    def put(name, value):
+        names.add(name)
+        gcn.gcn_debug_set_tuning(name, value)
+
+    yield put
+    for name in names:
+        gcn.gcn_debug_set_tuning(name, None)
+
+
 class Case:
     def __init__(self, gcn, dev, src, dst, n, lo=0, hi=None, deg_global=None):
         import torch
@@ -263,9 +277,11 @@ def test_forward_dense_product_follows_the_sparse_product_by_row_chunks(gcn, dev
 # The layer calls with a leading dimension per buffer: every feature buffer a view of a wider allocation
 # (gcn_feature_ld's pitch) whose padding holds NaN: nothing of it may reach a result, and an output's padding is
 # written at most up to the next multiple of 16 bytes of the row width.
+@pytest.mark.parametrize("dense", [None, 0])
 @pytest.mark.parametrize("d_in,d_out", [(100, 47), (47, 100), (128, 41), (256, 256)])
-def test_layer_calls_with_pitched_buffers(gcn, dev, er, directed_block, d_in, d_out):
+def test_layer_calls_with_pitched_buffers(gcn, dev, er, directed_block, tuned, d_in, d_out, dense):
     import torch
+    tuned("GCN_SPMM_DENSE", dense)
 
     def pitched(a, rows, d):
         buf = gcn.feature_buffer(rows, d, torch.float32, dev)
@@ -341,13 +357,16 @@ def test_results_do_not_depend_on_the_second_stream(gcn, dev, hubs, directed_blo
 
 # d_in x d_out, off: W starts `off` floats past a 16-byte boundary.  Rows of W as the kernels read them (d_out floats, several
 # tiles of d_in of them) that are whole 16-byte quads, end inside one, or start between two; short and long sums.
+@pytest.mark.parametrize("dense", [None, 0])
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("d_in,d_out,off", [(200, 200, 0), (512, 16, 0), (260, 15, 0), (300, 7, 0), (257, 33, 0), (130, 515, 0),
                                             (602, 128, 1), (290, 68, 2), (64, 700, 0), (31, 900, 3), (256, 256, 0), (192, 256, 1),
                                             (128, 200, 0), (64, 76, 2), (256, 64, 0), (100, 128, 1), (47, 50, 0), (1, 3, 0)])
-def test_products_with_w_transposed_in_place(gcn, dev, identity, d_in, d_out, off, bf16):
-    """dH = G W^T on a graph without edges, against fp64; 1237 rows are no whole number of any kernel's row tiles."""
+def test_products_with_w_transposed_in_place(gcn, dev, identity, tuned, d_in, d_out, off, bf16, dense):
+    """dH = G W^T on a graph without edges, against fp64; 1237 rows are no whole number of any kernel's row tiles.  In one launch with
+    the sparse product where that takes them, and by the dense kernels."""
     import torch
+    tuned("GCN_SPMM_DENSE", dense)
     og, A = identity.og, identity.A
     rng = np.random.default_rng(1000 * d_in + d_out)
     G = rng.standard_normal((og.nr, d_out)).astype(np.float32); H = rng.standard_normal((og.nr, d_in)).astype(np.float32)
@@ -419,20 +438,22 @@ def many_long_rows(gcn, dev):
 
 @pytest.mark.parametrize("dense", [0, 2])
 @pytest.mark.parametrize("d_in,d_out", [(4, 4), (16, 8), (64, 16), (7, 30), (50, 50), (47, 100), (100, 41), (128, 128), (17, 255), (128, 256)])
-def test_layer_as_one_kernel_and_as_two(gcn, dev, er, hubs, directed_block, many_long_rows, identity, dense, d_in, d_out):
+def test_layer_as_one_kernel_and_as_two(gcn, dev, er, hubs, directed_block, many_long_rows, identity, tuned, dense, d_in, d_out):
     """The sparse product and the dense product behind it in one launch wherever that kernel applies, and never: steps of 16
     k and of 16 columns and beside them, rows of every share of a workgroup, long rows added up by it and in chunks, halo rows."""
-    gcn.gcn_debug_set_tuning("GCN_SPMM_DENSE", dense)
-    try:
+    tuned("GCN_SPMM_DENSE", dense)
+    for bf16 in (False, True):
         for case in (er, hubs, directed_block, many_long_rows, identity):
-            run_fwd(gcn, dev, case, d_in, d_out, bias=True, save_ah=True)
-            run_bwd(gcn, dev, case, d_in, d_out, saved_ah=True)
-        run_fwd(gcn, dev, er, d_in, d_out, want_z=False, act="none")
-        run_bwd(gcn, dev, directed_block, d_in, d_out, dbias=True)
-        run_fwd(gcn, dev, hubs, d_in, d_out, bf16=True)
-        run_bwd(gcn, dev, hubs, d_in, d_out, bf16=True)
-    finally:
-        gcn.gcn_debug_set_tuning("GCN_SPMM_DENSE", None)
+            gcn.gcn_profile_enable(True)
+            run_fwd(gcn, dev, case, d_in, d_out, bf16=bf16, bias=True, save_ah=True)
+            run_bwd(gcn, dev, case, d_in, d_out, bf16=bf16, saved_ah=True)
+            kinds = [r["kind"] for r in gcn.gcn_profile_records()[0]]
+            gcn.gcn_profile_enable(False)
+            # (rows of a whole number of words that hold a request of 16 bytes: every graph here takes the kernel meant)
+            if d_in % 2 == d_out % 2 == 0 and min(d_in, d_out) >= 8 and d_out <= 128:
+                assert ("gemm_nn" in kinds) == (dense == 0), (dense, bf16, kinds)
+        run_fwd(gcn, dev, er, d_in, d_out, bf16=bf16, want_z=False, act="none")
+        run_bwd(gcn, dev, directed_block, d_in, d_out, bf16=bf16, dbias=True)
 
 
 @pytest.mark.parametrize("bf16", [False, True])
@@ -715,11 +736,13 @@ def test_two_layer_epoch_config1(gcn, dev, er, c1, bf16):
                                                (64, 40, False), (32, 200, True), (36, 129, False), (7, 5, False),
                                                (128, 128, True), (100, 256, True), (256, 47, True), (47, 256, True),
                                                (256, 256, True), (44, 41, True), (47, 256, False), (256, 47, False)])
-def test_dense_kernels_over_row_counts(gcn, dev, rows, d_in, d_out, bf16):
+def test_dense_kernels_over_row_counts(gcn, dev, tuned, rows, d_in, d_out, bf16):
     case = Case(gcn, dev, np.zeros(0, np.int32), np.zeros(0, np.int32), rows)          # A^ = I
-    run_fwd(gcn, dev, case, d_in, d_out, bf16=bf16, bias=True, save_ah=True)
-    run_bwd(gcn, dev, case, d_in, d_out, bf16=bf16, saved_ah=True, dbias=True)
-    run_bwd(gcn, dev, case, d_in, d_out, bf16=bf16, want_dh=False)
+    for dense in (0, None) if rows <= 8192 else (None,):       # (few rows take one launch with the sparse product by themselves)
+        tuned("GCN_SPMM_DENSE", dense)
+        run_fwd(gcn, dev, case, d_in, d_out, bf16=bf16, bias=True, save_ah=True)
+        run_bwd(gcn, dev, case, d_in, d_out, bf16=bf16, saved_ah=True, dbias=True)
+        run_bwd(gcn, dev, case, d_in, d_out, bf16=bf16, want_dh=False)
     case.A.free()
 
 
