@@ -357,9 +357,11 @@ int gcn_sgd_update(float* W, const float* dW, int64_t n, float lr, void* stream)
  *   flops      2 * multiply-adds.
  *   ms         elapsed time between the two events.
  */
+/* The sparse kinds: also the launch that multiplies a small layer's sparse rows by W (or W^T) as it goes, with the bytes and operations of
+ * both products; there is no GCN_K_GEMM_NN record then. */
 #define GCN_K_SPMM 0          /* A X, main kernel */
 #define GCN_K_SPMM_T 1        /* A^T X, main kernel */
-#define GCN_K_SPMM_FINISH 2   /* sum of the partial rows of long rows + epilogue */
+#define GCN_K_SPMM_FINISH 2   /* sum of the partial rows of long rows + epilogue; the partial rows, where the launch above adds them up */
 #define GCN_K_GEMM_NN 3
 #define GCN_K_GEMM_TN 4       /* partial tiles of A^T B */
 #define GCN_K_GEMM_TN_SUM 5   /* sum of the partial tiles */

@@ -167,13 +167,12 @@ __global__ __launch_bounds__(kThreads) void k_compact(const uint64_t* __restrict
 }
 
 // ptr[q] = first position whose segment id is >= q, for q in [0, n_seg]; seg ids are the bits
-// of key[k] from `shift` upwards that are set in `mask` and are non-decreasing in k.  Requires n >= 1.
-__global__ void k_boundaries(const uint64_t* __restrict__ key, int64_t n, int shift, uint64_t mask, int64_t n_seg,
-                             int64_t* __restrict__ ptr) {
+// of key[k] from `shift` upwards and are non-decreasing in k.  Requires n >= 1.
+__global__ void k_boundaries(const uint64_t* __restrict__ key, int64_t n, int shift, int64_t n_seg, int64_t* __restrict__ ptr) {
   int64_t k = block_id() * blockDim.x + threadIdx.x;
   if (k >= n) return;
-  int64_t s = (int64_t)((key[k] >> shift) & mask);
-  int64_t sp = k == 0 ? -1 : (int64_t)((key[k - 1] >> shift) & mask);
+  const int64_t s = (int64_t)(key[k] >> shift);
+  const int64_t sp = k == 0 ? -1 : (int64_t)(key[k - 1] >> shift);
   for (int64_t q = sp + 1; q <= s; ++q) ptr[q] = k;
   if (k == n - 1)
     for (int64_t q = s + 1; q <= n_seg; ++q) ptr[q] = n;
@@ -720,7 +719,7 @@ static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edge
 
 int segment_boundaries(const uint64_t* keys, int64_t n, int shift, int64_t n_seg, int64_t* ptr, hipStream_t s) {
   if (n < 1) return fail(GCN_EINVAL, "segment_boundaries: empty input");
-  k_boundaries<<<grid_for(n), kThreads, 0, s>>>(keys, n, shift, ~0ull, n_seg, ptr);
+  k_boundaries<<<grid_for(n), kThreads, 0, s>>>(keys, n, shift, n_seg, ptr);
   GCN_CHECK_LAUNCH();
   return GCN_OK;
 }

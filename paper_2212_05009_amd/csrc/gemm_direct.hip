@@ -270,18 +270,6 @@ template <typename T> __device__ __forceinline__ void vload4(const T* __restrict
     o[2] = __uint_as_float(v[1] << 16); o[3] = __uint_as_float(v[1] & 0xffff0000u);
   }
 }
-template <typename T> __device__ __forceinline__ void vstore4(T* __restrict__ p, const float (&v)[4]) {
-  if constexpr (sizeof(T) == 4) {
-    *reinterpret_cast<floatx4w*>(p) = floatx4w{v[0], v[1], v[2], v[3]};
-  } else {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(4)));
-    bf16_t h[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) store_one<T>(&h[i], v[i]);
-    *reinterpret_cast<u32x2*>(p) = u32x2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-  }
-}
-
 template <typename T> __device__ __forceinline__ void buf_load4(RowsBuf b, uint32_t off, float (&o)[4]) {
   if constexpr (sizeof(T) == 4) {
     const auto q = __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, 0);
