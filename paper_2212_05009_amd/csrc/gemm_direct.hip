@@ -929,9 +929,10 @@ static bool tn_wide_ok(const void* A, int64_t lda, const void* B, int64_t ldb, i
 // exist.  M even (and N, beyond 32), so that no request reaches past the end of a row.
 // Rows of whole quads otherwise take four columns a request; measured, us with four / two: 2 K rows x 50 x 50 22.6 / 17.3, 20 K x 50 x
 // 256 88 / 62, 150 K x 50 x 50 45 / 33, 500 K x 64 x 64 98 / 66 (a copy's rate is 47), 64 x 16 63 / 46, 32 x 128 167 / 109.
-// Other rows take k_gemm_tn_direct, and this form only where it gains on it: from 2^19 rows on with 65 to 128 columns of B, from 3 2^18 on
-// with up to 64 or all four column tiles.  us there / here: 2 K x 50 x 50 16.2 / 17.3, 2 K x 50 x 256 22 / 58, 150 K x 50 x 100 42 / 47,
-// 400 K x 50 x 100 88 / 90, 1 M x 50 x 100 229 / 200, 50 x 50 119 / 117, 50 x 256 407 / 387; never 50 x 160 (340 / 391) or 50 x 300
+// Other rows take k_gemm_tn_direct, and this form only where it gains on it: from 3 2^17 rows on with up to 64 columns of B, from 2^19 on
+// with up to 128, from 3 2^18 on with all four column tiles.  us there / here, each pass on other operands: 2 K x 50 x 50 16.2 / 17.3, 140 K
+// 27 / 30, 330 K 48 / 50, 400 K 59 / 56, 500 K 68.8 / 68.0, 780 K 97 / 93 (34 x 62, 62 x 34 and 50 x 64 alike, at pitches of 50, 52 and 96);
+// 2 K x 50 x 256 22 / 58, 150 K x 50 x 100 42 / 47, 400 K x 50 x 100 88 / 90, 1 M x 50 x 100 229 / 200, 50 x 256 407 / 387; never 50 x 160 (340 / 391) or 50 x 300
 // (550 / 760).  Its splits are half as many there, of two sums each: chains as long as k_gemm_tn_direct's, and the same error against 64
 // bits (500 K x 50 x 100 2.9e-7; 4.1e-7 with one sum).
 static bool tn_narrow_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype) {
@@ -940,7 +941,7 @@ static bool tn_narrow_ok(const void* A, int64_t lda, const void* B, int64_t ldb,
   if (tn_wide_ok(A, lda, B, ldb, N, dtype)) return N <= 32 || N % 2 == 0;
   if (N <= 32 || N % 2 != 0 || (ldb % 2) != 0 || ((uintptr_t)B % 8) != 0) return false;
   if (N > 256 || (N > 128 && N <= 192)) return false;
-  return Kd >= (N > 64 && N <= 128 ? 2 << 18 : 3 << 18);
+  return Kd >= (N <= 64 ? 3 << 17 : N <= 128 ? 2 << 18 : 3 << 18);
 }
 
 // column tiles of B per block in the vector variant: all of B for up to 256 columns

@@ -762,7 +762,7 @@ def test_weight_gradients_of_narrow_operands(gcn, dev, rows, d_in, d_out):
 # sums of the chains added up in fp64.  n per width: rows of a split over the four wavefronts that share it, as the kernel with one
 # request per matrix operation deals them (splits of 192 to 512 rows).
 @pytest.mark.parametrize("rows,d_in,d_out,n", [(3001, 50, 100, 48), (3001, 50, 256, 112), (3001, 50, 160, 64), (3001, 34, 300, 80), (3001, 62, 64, 32),
-                                               (300007, 50, 50, 98), (300007, 50, 100, 147), (300007, 50, 160, 220), (300007, 34, 256, 294),
+                                               (300007, 50, 50, 98), (400003, 50, 50, 98), (500009, 50, 50, 123), (300007, 50, 100, 147), (300007, 50, 160, 220), (300007, 34, 256, 294),
                                                (600011, 50, 100, 294), (1100003, 34, 256, 1076), (1100003, 50, 34, 270)])
 def test_weight_gradients_of_narrow_operands_are_as_exact_as_any(gcn, dev, rows, d_in, d_out, n):
     import torch
