@@ -496,6 +496,26 @@ def host_mem_gib():
     return None
 
 
+def brief(rec):
+    """What the printed line holds of a configuration beside the headline one.  Whoever keeps the last 10 KB of the output keeps the
+    whole line then; --full prints the records with the tables of their kernels."""
+    if "skipped" in rec:
+        return rec
+    roof = rec["roofline"]
+    out = {k: rec[k] for k in ("value", "unit", "median_ms", "min_ms", "dtype", "loss", "csr_csc_build_ms", "launches_per_epoch", "epoch_us") if k in rec}
+    out["config"] = {k: rec["config"][k] for k in ("workload", "owned_rows", "nnz", "dims")}
+    out["roofline"] = {k: roof[k] for k in ("bound", "frac", "kernel", "avg_launch_ms", "traffic_GBps", "traffic_stale") if k in roof}
+    if rec["dense_roofline"]:
+        out["dense_roofline_frac"] = rec["dense_roofline"]["frac"]
+    if "graph_replay" in rec:
+        out["graph_replay_ms"] = rec["graph_replay"]["ms_per_step"]
+    if "host_link" in rec:
+        out["gather_frac_of_link"] = rec["host_link"]["gather_frac_of_link"]
+    if "cpu_baseline_1thread" in rec:
+        out["cpu_baseline_1thread_ms"] = rec["cpu_baseline_1thread"]["value"]
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -520,6 +540,8 @@ def main():
                     help="keep every kernel on the caller's stream (GCN_OVERLAP=0): no dense product beside a sparse one")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run two row copies of known size (for scaling hardware byte counters)")
+    ap.add_argument("--full", action="store_true",
+                    help="print the records of the other configurations whole, with the tables of their kernels")
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
         print("bench.py: this build runs on ONE GPU only (the row block of one processor); "
@@ -573,6 +595,9 @@ def main():
                 for rec in others:
                     if rec["config"]["workload"] == name and "skipped" not in rec:
                         rec["cpu_baseline_1thread"] = one
+    if others and not args.full:
+        others = [brief(rec) for rec in others]
+        out["kernels"] = [{k: rec[k] for k in ("kind", "d", "rows", "launches_per_step", "avg_ms", "TFLOPps")} for rec in out["kernels"]]
     out["others"] = others
     print(json.dumps(out), flush=True)
 
