@@ -240,11 +240,8 @@ struct Shares {
 Shares shares_of(const Schedule* sc, int lanes, int dtype) {
   Shares o{};
   const int g = 64 / lanes;
-  auto begin = [&](int64_t len) {          // first row of the list that is shorter than len, a power of two
-    int c = 31;
-    while (((int64_t)1 << (31 - c)) < len) --c;
-    return sc->class_begin[c + 1];
-  };
+  // first row of the list that is shorter than len, a power of two
+  auto begin = [&](int64_t len) { return sc->class_begin[32 - __builtin_ctzll((unsigned long long)len)]; };
   o.slots = slots_of(lanes, dtype);
   o.hub_partials = sc->n_hub_rows > 0 && (lanes > 16 || sc->n_chunks - 3 * (sc->n_hub_rows - 1) > kHubChunksDirect);
   o.hub_blocks = o.hub_partials ? ceil_div(sc->n_hub_rows, kRows) : sc->n_hub_rows;
@@ -258,9 +255,9 @@ Shares shares_of(const Schedule* sc, int lanes, int dtype) {
     }
     if (o.n_blocks <= fit) break;
   }
+  int c = 0;
   for (int i = 0; i < 3; ++i) {            // the longest row of each share is in the class of its first row
     if (o.row[i + 1] <= o.row[i]) continue;
-    int c = 0;
     while (sc->class_begin[c + 1] <= o.row[i]) ++c;
     const int64_t len = c >= 32 ? 0 : (int64_t)1 << (31 - c);
     o.chain = std::max(o.chain, (int)(len / ((i == 0 ? 16 : i == 1 ? 4 : 1) * 4 * g)));
