@@ -410,7 +410,7 @@ int gcn_debug_max_grid_x(int64_t blocks);
  * sweep; default by heuristic, -1), GCN_PANEL_NARROW, GCN_PANEL_NOSYNC, GCN_PANEL_VERBOSE, GCN_SPMM_SLICES
  * (1, 2, 4, 8; 0 = by rule), GCN_SPMM_EPG, GCN_SPMM_WIDE, GCN_SPMM_SHORT (short-row form: 0 never, 1 always; -1 = by rule),
  * GCN_PARTITION_SORT (1 = partition figures by sorting), GCN_GEMM_DIRECT, GCN_GEMM_FAST, GCN_GEMM_TN_WIDE,
- * GCN_GEMM_BF16, GCN_GEMM_REGW, GCN_GEMM_TN_LDS (0 = that kernel family off), GCN_GEMM_TN_BLOCKS, GCN_GEMM_REGW_BLOCKS,
+ * GCN_GEMM_BF16, GCN_GEMM_REGW, GCN_GEMM_TN_LDS, GCN_GEMM_SPLIT (0 = that kernel family off), GCN_GEMM_TN_BLOCKS, GCN_GEMM_REGW_BLOCKS,
  * GCN_GEMM_TN_LDS_BLOCKS (workgroups of the kernels that take whole compute units), GCN_GATHER_HOST_BLOCKS, GCN_OVERLAP
  * (dense products beside sparse ones on a second stream: 0 never, 1 on large inputs, 2 wherever possible),
  * GCN_OVERLAP_CUS (compute units those dense kernels take), GCN_OVERLAP_CHUNKS (row ranges of the sparse product that

@@ -46,6 +46,7 @@ struct Tuning {
   int spmm_wide = 0;            // 64-bit gather addresses even where 32 bits suffice
   int gemm_direct = 1, gemm_fast = 1, gemm_tn_wide = 1, gemm_bf16 = 1, gemm_regw = 1;   // 0 switches a dense kernel family off
   int gemm_tn_lds = 1;          // A^T B with both operands streamed through LDS: 0 off, 1 for wide fp32 outputs, 2 wherever it fits
+  int gemm_split = 1;           // fp32 products on the bf16 matrix pipe, three parts a value: 0 off, 1 by rule, 2 wherever the kernel applies
   int gemm_regw_blocks = 0;     // workgroups of the register-resident-W kernel; 0 = one per compute unit
   int gemm_tn_lds_blocks = 0;   // workgroups of the LDS-streamed A^T B kernel; 0 = one per compute unit
   int overlap = 1;              // the weight gradient beside the sparse product of the same layer call: 0 never, 1 on large blocks, 2 wherever possible
@@ -361,6 +362,9 @@ struct GemmEpilogue {
   // the rows of C (and C2) may be written up to the next multiple of 16 bytes where their pitch reaches that far: buffers
   // of the library and those of the _ld calls; else what follows column N belongs to the caller
   bool c_rows_padded = false;
+  // the product may run beside a sparse one, whose requests hold up its own: a kernel that asks for its operand far ahead
+  bool beside = false;
+  int64_t rows = 0;              // rows of the whole product where this is a part of it (0: M): a part takes the kernel of the whole
 };
 // C = epilogue((A X) W) in one launch (spmm_dense.hip): sparse rows through LDS into the dense product; they are also stored
 // to a.Y where that is not null.  ws as spmm_launch; W and epi as gemm_nn's (K = a.d).
@@ -377,10 +381,10 @@ int gemm_nn(const void* A, int64_t lda, const float* B, int64_t ldb, void* C, in
 // C[M x N] (f32) = A[Kdim x M]^T * B[Kdim x N], Kdim huge: split over blocks, partial tiles in ws
 // (gemm_tn_ws_bytes), then summed in a fixed order.  A, B element type dtype.
 size_t gemm_tn_ws_bytes(int64_t Kdim, int M, int N);
-// max_blocks > 0: as GemmEpilogue::max_blocks, honoured when gemm_tn_limits_blocks says so
+// max_blocks > 0: as GemmEpilogue::max_blocks, honoured when gemm_tn_limits_blocks says so; beside: as GemmEpilogue::beside
 bool gemm_tn_limits_blocks(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kdim, int M, int N, int dtype);
 int gemm_tn(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc,
-            int64_t Kdim, int M, int N, int dtype, void* ws, hipStream_t s, int max_blocks = 0);
+            int64_t Kdim, int M, int N, int dtype, void* ws, hipStream_t s, int max_blocks = 0, bool beside = false);
 // streaming variants (gemm_direct.hip): the long operand goes from global memory straight into the
 // MFMA operand registers; nn_direct needs W to fit in LDS (gemm_nn_direct_ok)
 bool gemm_nn_direct_ok(int N, int K);
@@ -388,6 +392,14 @@ bool gemm_nn_direct_ok(int N, int K);
 bool gemm_nn_regw_ok(const void* A, int64_t lda, int64_t M, int N, int K, int dtype);
 int gemm_nn_regw(const void* A, int64_t lda, const float* W, int64_t ldw, void* C, int64_t ldc, int64_t M, int N, int K,
                  const GemmEpilogue& epi, hipStream_t s);
+// fp32 operands on the bf16 matrix pipe, every value in three parts (gemm_split.hip)
+bool gemm_nn_split_ok(const void* A, int64_t lda, int64_t ldw, int64_t ldc, int64_t M, int N, int K, int dtype, const GemmEpilogue& epi);
+int gemm_nn_split(const void* A, int64_t lda, const float* W, int64_t ldw, void* C, int64_t ldc, int64_t M, int N, int K,
+                  const GemmEpilogue& epi, hipStream_t s);
+bool gemm_tn_split_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype);
+size_t gemm_tn_split_ws_bytes(int64_t Kd, int M, int N);
+int gemm_tn_split_partials(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, float* partial, int* nsplit_out,
+                           hipStream_t s, int max_blocks = 0);
 // bf16 features on the bf16 matrix pipe (gemm_bf16.hip): W rounded to bf16 in LDS, fp32 accumulation
 bool gemm_nn_bf16_ok(const void* A, int64_t lda, void* C, int64_t ldc, int64_t M, int N, int K, const GemmEpilogue& epi);
 // A^T B for bf16 operands on the bf16 matrix pipe: partial tiles per row split, as gemm_tn_direct_partials
@@ -408,7 +420,7 @@ int gemm_tn_lds_partials(const void* A, int64_t lda, const void* B, int64_t ldb,
                          int* nsplit_out, hipStream_t s, int max_blocks = 0);
 size_t gemm_tn_direct_ws_bytes(int64_t Kd, int M, int N);
 int gemm_tn_direct_partials(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype,
-                            float* partial, int* nsplit_out, hipStream_t s, int max_blocks = 0);
+                            float* partial, int* nsplit_out, hipStream_t s, int max_blocks = 0, bool beside = false);
 // Holds the stream back for about 15 us (one sleeping wavefront): gives a kernel that was just released on another
 // stream, and that needs whole compute units, time to be placed before this stream's next kernel fills the chip.
 int stream_pause(hipStream_t s);

@@ -267,7 +267,13 @@ int gemm_nn(const void* A, int64_t lda, const float* B, int64_t ldb, void* C, in
     ProfScope ps(GCN_K_GEMM_NN, s, N, dtype, M, K, nb, nb, 2.0 * (double)M * N * K);
     return gemm_nn_bf16(A, lda, B, ldb, C, ldc, M, N, K, epi, s);
   }
-  // Wide weight matrices are held in registers, the operand rows streamed past them through LDS.  Measured on
+  if (use_direct() && gemm_nn_split_ok(A, lda, ldb, ldc, M, N, K, dtype, epi)) {
+    const double nb = (double)es * (double)M * (K + N * (epi.C2 ? 2.0 : 1.0) + (epi.mask ? N : 0)) + 4.0 * (double)K * N;
+    ProfScope ps(GCN_K_GEMM_NN, s, N, dtype, M, K, nb, nb, 2.0 * (double)M * N * K);
+    return gemm_nn_split(A, lda, B, ldb, C, ldc, M, N, K, epi, s);
+  }
+  // Wide weight matrices (below 2^15 rows, and of products beside a sparse one) are held in registers, the operand rows streamed
+  // past them through LDS.  Measured on
   // 2.45 M rows (TFLOP/s, this kernel / the LDS-resident-W kernel or, for 256 x 256, the LDS-tiled one):
   // 256 x 256: 123 / 89, 128 x 256: 108 / 74, 200 x 192: 70 / 66, 100 x 256 (13 steps of 8 k): see the profile, 128 x 128 (two of the four
   // SIMDs busy): 49 / 113.  GCN_GEMM_REGW=2 takes it wherever it applies (tests).
@@ -463,14 +469,14 @@ size_t gemm_tn_ws_bytes(int64_t Kd, int M, int N) {
 }
 
 int gemm_tn(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc, int64_t Kd, int M,
-            int N, int dtype, void* ws, hipStream_t s, int max_blocks) {
+            int N, int dtype, void* ws, hipStream_t s, int max_blocks, bool beside) {
   const size_t es = dtype == GCN_BF16 ? 2 : 4;
   const int64_t mn = (int64_t)M * N;
   int nsplit = 0;
   if (use_direct()) {
     const double nb = (double)es * (double)Kd * (M + N) + 4.0 * (double)mn;
     ProfScope ps(GCN_K_GEMM_TN, s, N, dtype, M, Kd, nb, nb, 2.0 * (double)Kd * M * N);
-    GCN_TRY(gemm_tn_direct_partials(A, lda, B, ldb, Kd, M, N, dtype, (float*)ws, &nsplit, s, max_blocks));
+    GCN_TRY(gemm_tn_direct_partials(A, lda, B, ldb, Kd, M, N, dtype, (float*)ws, &nsplit, s, max_blocks, beside));
   } else {
     TnArgs a{A, lda, B, ldb, Kd, M, N, pick_vec(A, lda, M, es), pick_vec(B, ldb, N, es), 0, 0, (float*)ws};
     if (dtype == GCN_BF16) { if (a.vecA == 2) a.vecA = 1; if (a.vecB == 2) a.vecB = 1; }
@@ -501,7 +507,8 @@ int gemm_tn(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, in
 }
 
 bool gemm_tn_limits_blocks(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype) {
-  return use_direct() && !(dtype == GCN_BF16 && gemm_tn_bf16_ok(A, lda, B, ldb, Kd, M, N)) && gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype);
+  return use_direct() && !(dtype == GCN_BF16 && gemm_tn_bf16_ok(A, lda, B, ldb, Kd, M, N)) &&
+         (gemm_tn_split_ok(A, lda, B, ldb, Kd, M, N, dtype) || gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype));
 }
 
 // column sums: block b adds rows [b*kRows, ...) per column into partial[b][c]; then fp64 finish

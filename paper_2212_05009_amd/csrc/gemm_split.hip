@@ -1,0 +1,753 @@
+// C[M x N] = A[M x K] W[K x N] of fp32 operands on the bf16 matrix pipe (Sec. 3.1: the dense product with W^k), for products whose
+// arithmetic takes longer than their bytes on the fp32 pipe.
+//
+// An fp32 value is the exact sum of three bf16 values: its rounding, the rounding of what is left (2^-9 of it at most), and of what is
+// then left (2^-18; 24 bits of significand are 3 x 8).  A product of two values is nine products, of which the six of weight 2^-18 and
+// more are formed, each exact in fp32, and added by the matrix pipe in fp32: what is left out is 2^-26 of the product, a
+// quarter of one fp32 rounding.  Six bf16 operations at sixteen times the fp32 rate: the products are then bound by memory.
+#include <algorithm>
+#include <type_traits>
+
+#include "rows_buf.h"
+
+namespace gcn {
+
+namespace {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx4w __attribute__((ext_vector_type(4), aligned(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+struct SplitArgs {
+  const float* A; int64_t lda; const float* W; int64_t ldw; float* C; int64_t ldc;
+  int64_t M; int N; int K;
+  const float* bias; int relu; const float* mask; int64_t ldmask; int64_t mask_rows; float* C2; int64_t ldc2;
+  int trans;               // W is stored [N x K]
+  int endC;                // nothing beyond column N of C and C2 may be written
+};
+
+// The six products of parts, the smallest first.  The matrix pipe aligns what it adds to the largest term and cuts off the rest: each step's sum
+// starts from zero and is added to the result by a rounded fp32 addition.  (Sums carried through the pipe over all steps: error of a
+// 256 x 256 gradient over 2.45 M rows 7.8e-6, 1.7e-6 on the fp32 pipe.)
+__device__ constexpr int kTerm[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+
+constexpr int kThreads = 512;
+constexpr int kWaves = kThreads / 64;
+constexpr int kRT = 2;                                 // tiles of 16 rows of a wavefront
+
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  const bf16x2 h = __builtin_convertvector(floatx2{lo, hi}, bf16x2);
+  uint32_t u;
+  __builtin_memcpy(&u, &h, 4);
+  return u;
+}
+// {lo, hi} = the values of p[0] + p[1] + p[2]
+__device__ __forceinline__ void split2(float lo, float hi, uint32_t (&p)[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    p[k] = pack_bf16(lo, hi);
+    lo -= __uint_as_float(p[k] << 16);
+    hi -= __uint_as_float(p[k] & 0xffff0000u);
+  }
+}
+__device__ __forceinline__ floatx4 mfma(const u32x4& w, const u32x4& x, floatx4 acc) {
+  bf16x8 a, b;
+  __builtin_memcpy(&a, &w, 16); __builtin_memcpy(&b, &x, 16);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+}
+// meets the workgroup for LDS alone: global requests stay in flight
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// What bounds it: the matrix pipe and its clock.  2.45 M rows x 256 x 256: 1.84 M of its 3.0 M cycles the pipe is busy, at 1.8 GHz
+// (2.2 in kernels that wait for memory); LDS is read in half of them.  While a step is multiplied (192 operations a wavefront at 256
+// columns) the next one is split (88 vector operations, in their shadow) and the one after asked for, its own registers' places
+// as they fall free; splitting first and multiplying then took 1.96 ms for 1.68, W in plain loads with their addresses in registers,
+// spilled, 2.42; 1.68 is 1.95 with the sums of each step added by vector operations, without which the error grows to that of the fp32
+// pipe and beyond (terms of one sign).
+// Lane (c, q) = (lane % 16, lane / 16) supplies row c of a tile of 16 rows, k = 8 q .. 8 q + 7 of a step of 32, as the second
+// MFMA operand and column 16 t + c of W as the first: register r of its accumulator t is column 16 t + 4 q + r of row c.
+// LDS holds W as operands, [step][tile][part][lane], 16 bytes each: all of it (RES), or two steps in turn, which the workgroup reads
+// from L2 and splits again for every pass over its rows.
+template <int NT, bool RES, bool TRANS, bool MASK, bool SAVE>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_nn_split(SplitArgs a) {
+  extern __shared__ u32x4 split_lds[];
+  constexpr int kStep = NT * 3 * 64;                   // u32x4 of a step of W
+  constexpr int kPieces = (NT * 64 + kThreads - 1) / kThreads;
+  const int steps = (a.K + 31) / 32;
+  const int n0 = (int)blockIdx.y * (NT * 16);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = lane & 15, q = lane >> 4;
+  float* bias = reinterpret_cast<float*>(split_lds + (RES ? steps : 2) * kStep);
+  for (int n = threadIdx.x; n < NT * 16; n += kThreads) bias[n] = a.bias && n0 + n < a.N ? a.bias[n0 + n] : 0.f;
+
+  // piece p of a step: the eight k of one lane's operand of one tile; what lies behind K or N is answered with zeros
+  const RowsBuf wb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.W), 0, (int)((((TRANS ? a.N : a.K) - 1) * a.ldw + (TRANS ? a.K : a.N)) * 4), 0x00020000);
+  const int ldw = (int)a.ldw;
+  int w_at[kPieces];
+#pragma unroll
+  for (int i = 0; i < kPieces; ++i) {
+    const int p = ((int)threadIdx.x + i * kThreads) % (NT * 64);      // (threads left over do another's work over again)
+    const int n = n0 + 16 * (p >> 6) + (p & 15), pq = (p >> 4) & 3;
+    w_at[i] = n < a.N ? (TRANS ? n * ldw + 8 * pq : 8 * pq * ldw + n) * 4 : (int)0x80000000u;
+  }
+  auto load_w = [&](int s, int i, float (&v)[8]) {
+    if constexpr (TRANS) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const auto x = __builtin_amdgcn_raw_buffer_load_b128(wb, w_at[i] + 128 * s + 16 * h, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[4 * h + j] = __uint_as_float(x[j]);
+      }
+    } else {
+      const int at = w_at[i] + 128 * s * ldw;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wb, at + 4 * j * ldw, 0, 0));
+    }
+  };
+  // pair j of its values, in three parts
+  auto split_w = [&](int s, int i, int j, const float (&v)[8], u32x4 (&o)[3]) {
+    float lo = v[2 * j], hi = v[2 * j + 1];
+    if (TRANS) {                                       // (behind K lies the row after it)
+      const int in = a.K - 32 * s - 8 * (((((int)threadIdx.x + i * kThreads) % (NT * 64)) >> 4) & 3) - 2 * j;
+      lo = in > 0 ? lo : 0.f;
+      hi = in > 1 ? hi : 0.f;
+    }
+    uint32_t u[3];
+    split2(lo, hi, u);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) o[k][j] = u[k];
+  };
+  auto place_w = [&](u32x4* __restrict__ at, int i, const u32x4 (&o)[3]) {
+    const int p = ((int)threadIdx.x + i * kThreads) % (NT * 64);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) at[((p >> 6) * 3 + k) * 64 + (p & 63)] = o[k];
+  };
+  for (int s = 0; s < (RES ? steps : 1); ++s) {
+    float v[kPieces][8];
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) load_w(s, i, v[i]);
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+      u32x4 o[3];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) split_w(s, i, j, v[i], o);
+      place_w(split_lds + s * kStep, i, o);
+    }
+  }
+  __syncthreads();
+
+  const int64_t ntiles = (a.M + 16 * kRT - 1) / (16 * kRT);
+  const int64_t stride = (int64_t)gridDim.x * kWaves;
+  const uint32_t neg = a.relu ? 0u : 0xffffffffu;
+  // rows past M are answered with zeros, what a row is asked for past K is cleared
+  auto rows_left = [&](int64_t tile) { return (int)(a.M - tile * (16 * kRT) < 16 * kRT ? a.M - tile * (16 * kRT) : 16 * kRT); };
+  auto a_buf = [&](int64_t tile) {
+    const int left = rows_left(tile);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.A + tile * (16 * kRT) * a.lda), 0,
+                                             left > 0 ? (int)(((left - 1) * (int)a.lda + a.K) * 4) : 0, 0x00020000);
+  };
+  auto load_a = [&](RowsBuf b, int s, int rt, floatx4 (&x)[2]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const auto v = __builtin_amdgcn_raw_buffer_load_b128(b, ((16 * rt + c) * (int)a.lda + 32 * s + 8 * q + 4 * h) * 4, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[h][i] = __uint_as_float(v[i]);
+    }
+  };
+  const int tail = a.K - (32 * (steps - 1) + 8 * q);   // elements of the lane's part of the last step
+  // pair j of the values of row tile rt, of which `in` count
+  auto split_a = [&](const floatx4 (&v)[kRT][2], int rt, int j, int in, u32x4 (&x)[kRT][3]) {
+    const float lo = v[rt][j >> 1][2 * (j & 1)], hi = v[rt][j >> 1][2 * (j & 1) + 1];
+    uint32_t u[3];
+    split2(2 * j < in ? lo : 0.f, 2 * j + 1 < in ? hi : 0.f, u);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) x[rt][k][j] = u[k];
+  };
+
+  // Every wavefront of the workgroup makes the same number of passes (they meet at the steps of W).  While a step is multiplied, the next
+  // one is split and the one after it asked for.
+  // Rows go to the workgroups 128 at a time, as in the other streaming kernels: what one of them wrote last is read from the L2 of the same
+  // compute units.
+  constexpr int kGroup = 128 / (16 * kRT);             // tiles of 128 rows
+  int64_t tile = gridDim.x % 8 == 0 ? (int64_t)(blockIdx.x / 8) * (8 * kWaves) + (w / kGroup) * (8 * kGroup) + (blockIdx.x % 8) * kGroup + w % kGroup
+                                    : (int64_t)blockIdx.x * kWaves + w;
+  const int64_t passes = (ntiles + stride - 1) / stride;
+  int64_t tile_l = tile;                               // of the step asked for last
+  int step_l = 0;
+  auto advance = [&] { if (++step_l == steps) { step_l = 0; tile_l += stride; } };
+  floatx4 raw[kRT][2];
+  u32x4 x[kRT][3];
+#pragma unroll
+  for (int rt = 0; rt < kRT; ++rt) load_a(a_buf(tile), 0, rt, raw[rt]);
+#pragma unroll
+  for (int rt = 0; rt < kRT; ++rt)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) split_a(raw, rt, j, steps == 1 ? tail : 8, x);
+  advance();
+#pragma unroll
+  for (int rt = 0; rt < kRT; ++rt) load_a(a_buf(tile_l), step_l, rt, raw[rt]);
+  int cur = 0;
+  for (int64_t pass = 0; pass < passes; ++pass, tile += stride) {
+    floatx4 acc[kRT][NT];
+#pragma unroll
+    for (int rt = 0; rt < kRT; ++rt)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[rt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < steps; ++s) {
+      const int sn = s + 1 == steps ? 0 : s + 1;
+      const int in = sn == steps - 1 ? tail : 8;
+      advance();
+      const RowsBuf nb = a_buf(tile_l);
+      float wv[8];
+      if constexpr (!RES) load_w(sn, 0, wv);
+      u32x4 xn[kRT][3], wo[3];
+      const u32x4* __restrict__ wl = split_lds + (RES ? s : cur) * kStep + lane;
+      constexpr int TB = NT > 8 ? 1 : 2;
+      constexpr int kGroups = NT / TB;
+      // units of work beside the products: pairs of A (each row tile's next part is asked for behind its last pair), then of W
+      constexpr int kUnitsA = kRT * 4, kUnits = kUnitsA + (RES ? 0 : kPieces * 4);
+      u32x4 wn[TB][3];
+#pragma unroll
+      for (int t = 0; t < TB; ++t)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) wn[t][k] = wl[(t * 3 + k) * 64];
+#pragma unroll
+      for (int g = 0; g < kGroups; ++g) {
+        u32x4 wf[TB][3];
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) wf[t][k] = wn[t][k];
+        if (g + 1 < kGroups) {
+#pragma unroll
+          for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) wn[t][k] = wl[(((g + 1) * TB + t) * 3 + k) * 64];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        floatx4 sum[kRT][TB];
+#pragma unroll
+        for (int m = 0; m < 6; ++m)
+#pragma unroll
+          for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int rt = 0; rt < kRT; ++rt)
+              sum[rt][t] = mfma(wf[t][kTerm[m][0]], x[rt][kTerm[m][1]], m ? sum[rt][t] : floatx4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int u = g * kUnits / kGroups; u < (g + 1) * kUnits / kGroups; ++u) {
+          if (u < kUnitsA) {
+            split_a(raw, u >> 2, u & 3, in, xn);
+            if ((u & 3) == 3) load_a(nb, step_l, u >> 2, raw[u >> 2]);
+          } else {
+            const int i = (u - kUnitsA) >> 2;
+            split_w(sn, i, u & 3, wv, wo);
+            if ((u & 3) == 3) {
+              place_w(split_lds + (cur ^ 1) * kStep, i, wo);
+              if (i + 1 < kPieces) load_w(sn, i + 1, wv);
+            }
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+          for (int rt = 0; rt < kRT; ++rt) {
+            acc[rt][g * TB + t] += sum[rt][t];
+            asm volatile("" : "+v"(acc[rt][g * TB + t]));      // (here, not behind the loop)
+          }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int rt = 0; rt < kRT; ++rt)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) x[rt][k] = xn[rt][k];
+      if constexpr (!RES) {
+        lds_barrier();
+        cur ^= 1;
+      }
+    }
+    const int left = rows_left(tile);
+    // A sum that is no finite number: an operand or a product beyond the range, whose parts are not what they stand for (inf = inf + NaN).
+    // Those rows are multiplied again on the fp32 pipe.
+    float probe = 0.f;
+#pragma unroll
+    for (int rt = 0; rt < kRT; ++rt)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) probe = __builtin_fmaf(acc[rt][t][r], 0.f, probe);
+    if (__builtin_expect(__any(probe != probe), 0)) {
+      const RowsBuf ab = a_buf(tile);
+      int ce = c, qe = q;
+      asm volatile("" : "+v"(ce), "+v"(qe));
+#pragma unroll
+      for (int rt = 0; rt < kRT; ++rt)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[rt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int k0 = 0; k0 < a.K; k0 += 4) {
+        const int k = k0 + qe;
+        float xs[kRT];
+#pragma unroll
+        for (int rt = 0; rt < kRT; ++rt)
+          xs[rt] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)(k < a.K ? (uint32_t)((16 * rt + ce) * (int)a.lda + k) * 4u : kNoPlace), 0, 0));
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const int n = n0 + 16 * t + ce;
+          const uint32_t at = (uint32_t)(TRANS ? n * ldw + k : k * ldw + n) * 4u;
+          const float ws = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wb, (int)(k < a.K && n < a.N ? at : kNoPlace), 0, 0));
+#pragma unroll
+          for (int rt = 0; rt < kRT; ++rt) acc[rt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ws, xs[rt], acc[rt][t], 0, 0, 0);
+        }
+      }
+    }
+    if (left <= 0) continue;
+#pragma unroll
+    for (int rt = 0; rt < kRT; ++rt) {
+      const int64_t row0 = tile * (16 * kRT) + 16 * rt;
+      const int here = left - 16 * rt < 16 ? left - 16 * rt : 16;
+      if (here <= 0) continue;
+      // (neither the places of the results nor the bias are worth registers over the products)
+      int ce = c, qe = q;
+      asm volatile("" : "+v"(ce), "+v"(qe) : : "memory");
+      const RowsBuf cb = rows_buf<float>(a.C + n0, row0, a.ldc, here);
+      RowsBuf cb2 = cb;
+      if constexpr (SAVE) cb2 = rows_buf<float>(a.C2 + n0, row0, a.ldc2, here);
+      floatx4 keep[MASK ? NT : 1];
+      const bool free_row = MASK && row0 + ce >= a.mask_rows;
+      if constexpr (MASK) {
+        const int64_t masked = a.mask_rows - row0;
+        const int mrows = masked < here ? (masked > 0 ? (int)masked : 0) : here;
+        const RowsBuf mb = rows_buf<float>(a.mask + n0, row0, a.ldmask, mrows);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const auto v = __builtin_amdgcn_raw_buffer_load_b128(mb, (ce * (int)a.ldmask + 16 * t + 4 * qe) * 4, 0, 0);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) keep[t][r] = __uint_as_float(v[r]);
+        }
+      }
+      auto finish = [&](auto cut) {                    // cut: a row may end inside a group of four, behind which nothing may be written
+        constexpr bool CUT = decltype(cut)::value;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const int n = 16 * t + 4 * qe;
+          const floatx4 bv = *reinterpret_cast<const floatx4*>(bias + n);
+          float pre[4], v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            pre[r] = acc[rt][t][r] + bv[r];
+            v[r] = pre[r] > 0.f ? pre[r] : __uint_as_float(__float_as_uint(pre[r]) & neg);
+            if constexpr (MASK) v[r] = keep[t][r] > 0.f || free_row ? v[r] : 0.f;
+          }
+          const int left_n = a.N - n0 - n;
+          auto put = [&](RowsBuf b, int64_t ld, const float (&o)[4]) {
+            const uint32_t off = (uint32_t)(ce * (int)ld + n) * 4u;
+            __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])}, b,
+                                                   (int)(left_n > (CUT ? 3 : 0) ? off : kNoPlace), 0, 0);
+            if constexpr (CUT)
+#pragma unroll
+              for (int r = 0; r < 3; ++r)
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o[r]), b, (int)(left_n < 4 && r < left_n ? off + 4u * r : kNoPlace), 0, 0);
+          };
+          if constexpr (SAVE) put(cb2, a.ldc2, pre);
+          put(cb, a.ldc, v);
+        }
+      };
+      if (a.endC) finish(std::true_type());
+      else finish(std::false_type());
+    }
+  }
+}
+
+// ---- dW = A^T B ---------------------------------------------------------------------------------------------
+// Partial products of C[M x N] = A[Kd x M]^T B[Kd x N] (Sec. 3.2: the weight gradient, a sum over all rows of the block).  A workgroup
+// owns MB x NB elements of C for one range of rows.  16 G rows of both operands at a time are asked for, split into their three parts
+// once for the whole workgroup and placed in LDS as operands of v_mfma_f32_32x32x16_bf16 (lane (c, h) = (lane % 32, lane / 32): column c,
+// rows 8 h .. 8 h + 7), in the other half of a double buffer, while the WA x WB wavefronts of each of the G groups multiply the
+// 16 rows that are theirs, TA x TB tiles of 32 x 32 each.
+//
+// A thread asks for two neighbouring columns of eight rows: component i is for tile i of a pair, so tile 2 P + i holds the columns
+// {64 P + 2 c + i}, and both the requests and the places in LDS of neighbouring lanes are neighbours.
+struct SplitTnArgs {
+  const float* A; int64_t lda; const float* B; int64_t ldb;
+  int64_t Kd; int M; int N; int64_t rows_per_split; int mblocks; int nsplit;
+  float* partial;      // [nsplit][M * N]
+};
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ floatx16 mfma32(const u32x4& x, const u32x4& y, floatx16 acc) {
+  bf16x8 a, b;
+  __builtin_memcpy(&a, &x, 16); __builtin_memcpy(&b, &y, 16);
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+}
+
+template <int TA, int TB, int WA, int WB, int G>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_tn_split(SplitTnArgs a) {
+  static_assert(WA * WB * G == kWaves && (TA * WA) % 2 == 0 && (TB * WB) % 2 == 0, "eight wavefronts, tiles in pairs");
+  constexpr int kTilesA = TA * WA, kTiles = TA * WA + TB * WB;          // of a group
+  constexpr int kRows = 16 * G, kBuf = G * kTiles * 3 * 64;              // u32x4 of a buffer
+  constexpr int kUnitsAll = kTiles / 2 * 64 * G;                         // (pair of tiles, lane of an operand, group)
+  constexpr int kUnits = (kUnitsAll + kThreads - 1) / kThreads;
+  constexpr int D = TA * TB <= 4 ? 2 : 1;                                // chunks asked for ahead of the one that is split (registers)
+  extern __shared__ u32x4 split_lds[];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = lane & 31, h = lane >> 5;
+  const int g = w / (WA * WB), wa = (w / WB) % WA, wb = w % WB;
+  const int m0 = (int)blockIdx.y % a.mblocks * (32 * kTilesA), n0 = (int)blockIdx.y / a.mblocks * (32 * (kTiles - kTilesA));
+
+  // this thread's units: its columns in its operand (behind the last one nothing is asked for, or counted), its rows, its place
+  bool of_b[kUnits];
+  int off[kUnits], put[kUnits];
+  uint32_t second[kUnits];
+#pragma unroll
+  for (int i = 0; i < kUnits; ++i) {
+    const int u = ((int)threadIdx.x + i * kThreads) % kUnitsAll;       // (threads left over do another's work over again)
+    const int slot = u & 63, pair = (u >> 6) % (kTiles / 2), gr = (u >> 6) / (kTiles / 2);      // (uniform over a wavefront but for slot)
+    of_b[i] = 2 * pair >= kTilesA;
+    const int col = (of_b[i] ? n0 + 64 * (pair - kTilesA / 2) : m0 + 64 * pair) + 2 * (slot & 31);
+    const int width = of_b[i] ? a.N : a.M;
+    const int ld = (int)(of_b[i] ? a.ldb : a.lda);
+    off[i] = col < width ? ((16 * gr + 8 * (slot >> 5)) * ld + col) * 4 : (int)0x80000000u;
+    second[i] = col + 1 < width ? 0xffffffffu : 0u;
+    put[i] = (gr * kTiles + 2 * pair) * 3 * 64 + slot;
+  }
+  typedef float floatx2w __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  floatx2w raw[D][kUnits][8];
+
+  for (int split = (int)blockIdx.x; split < a.nsplit; split += (int)gridDim.x) {
+    const int64_t k_lo = (int64_t)split * a.rows_per_split;
+    const int64_t k_hi = k_lo + a.rows_per_split < a.Kd ? k_lo + a.rows_per_split : a.Kd;
+    auto rows_of = [&](const float* p, int64_t ld, int width, int64_t k) {
+      const int64_t left = k_hi - k < kRows ? k_hi - k : kRows;
+      return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p + k * ld), 0, left > 0 ? (int)(((left - 1) * (int)ld + width) * 4) : 0, 0x00020000);
+    };
+    auto load = [&](int64_t k, int i, floatx2w (&raw)[kUnits][8]) {
+      const bool ob = __builtin_amdgcn_readfirstlane((int)of_b[i]);
+      const RowsBuf b = ob ? rows_of(a.B, a.ldb, a.N, k) : rows_of(a.A, a.lda, a.M, k);
+      const int ld = (int)(ob ? a.ldb : a.lda);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(b, off[i] + 4 * r * ld, 0, 0);
+        raw[i][r] = floatx2w{__uint_as_float(v[0]), __uint_as_float(v[1] & second[i])};
+      }
+    };
+    // rows 2 j, 2 j + 1 of component e of unit i, those of A times `sign`, in three parts
+    u32x4 part[3];
+    auto convert = [&](const floatx2w (&raw)[kUnits][8], int i, int e, int j, float sign) {
+      uint32_t o[3];
+      const float by = of_b[i] ? 1.f : sign;
+      split2(raw[i][2 * j][e] * by, raw[i][2 * j + 1][e] * by, o);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) part[k][j] = o[k];
+    };
+    auto place = [&](u32x4* __restrict__ buf, int i, int e) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) buf[put[i] + (e * 3 + k) * 64] = part[k];
+    };
+
+    floatx16 acc[TA][TB];
+#pragma unroll
+    for (int i = 0; i < TA; ++i)
+#pragma unroll
+      for (int j = 0; j < TB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+      for (int i = 0; i < kUnits; ++i) load(k_lo + d * kRows, i, raw[d]);
+#pragma unroll
+    for (int i = 0; i < kUnits; ++i) {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) convert(raw[0], i, e, j, 1.f);
+        place(split_lds, i, e);
+      }
+      load(k_lo + D * kRows, i, raw[0]);
+    }
+    __syncthreads();
+    // Chunk k, whose operands are in half P of the buffer, is multiplied; the next one is split and placed in the other half, and the one
+    // D + 1 chunks on is asked for.  Every other chunk of A is taken with the other sign: what the pipe cuts off is cut downwards, in every
+    // chunk the same way.
+    auto step = [&](int64_t k, auto half, float sign) {
+      const int P = half;
+      const u32x4* __restrict__ la = split_lds + P * kBuf + (g * kTiles + wa * TA) * 3 * 64 + lane;
+      const u32x4* __restrict__ lb = split_lds + P * kBuf + (g * kTiles + kTilesA + wb * TB) * 3 * 64 + lane;
+      u32x4* __restrict__ other = split_lds + (P ^ 1) * kBuf;
+      u32x4 bf[TB][3], an[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) an[p] = la[p * 64];
+#pragma unroll
+      for (int j = 0; j < TB; ++j)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) bf[j][p] = lb[(j * 3 + p) * 64];
+      constexpr int kWork = kUnits * 8;               // pairs of rows to split
+#pragma unroll
+      for (int i = 0; i < TA; ++i) {
+        u32x4 af[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) af[p] = an[p];
+        if (i + 1 < TA) {
+#pragma unroll
+          for (int p = 0; p < 3; ++p) an[p] = la[((i + 1) * 3 + p) * 64];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        floatx16 sum[TB];
+#pragma unroll
+        for (int j = 0; j < TB; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum[j][r] = 0.f;
+#pragma unroll
+        for (int m = 0; m < 6; ++m)
+#pragma unroll
+          for (int j = 0; j < TB; ++j) sum[j] = mfma32(af[kTerm[m][0]], bf[j][kTerm[m][1]], sum[j]);
+#pragma unroll
+        for (int u = i * kWork / TA; u < (i + 1) * kWork / TA; ++u) {
+          const int un = u >> 3, e = (u >> 2) & 1;
+          convert(raw[D == 1 ? 0 : P ^ 1], un, e, u & 3, -sign);
+          if ((u & 3) == 3) place(other, un, e);
+          if ((u & 7) == 7) load(k + (D + 1) * kRows, un, raw[D == 1 ? 0 : P ^ 1]);
+        }
+#pragma unroll
+        for (int j = 0; j < TB; ++j) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = __builtin_fmaf(sum[j][r], sign, acc[i][j][r]);
+          asm volatile("" : "+v"(acc[i][j]));          // (here, not behind the loop)
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      lds_barrier();
+    };
+    if constexpr (D == 1) {
+      int half = 0;
+      float sign = 1.f;
+      for (int64_t k = k_lo; k < k_hi; k += kRows, half ^= 1, sign = -sign) step(k, half, sign);
+    } else {                                             // (the registers of a chunk are told apart by the code)
+      for (int64_t k = k_lo; k < k_hi; k += 2 * kRows) {
+        step(k, std::integral_constant<int, 0>(), 1.f);
+        if (k + kRows >= k_hi) break;
+        step(k + kRows, std::integral_constant<int, 1>(), -1.f);
+      }
+    }
+
+    // A sum that is no finite number (see above): the rows of the split once more, on the fp32 pipe, by the first group
+    float probe = 0.f;
+#pragma unroll
+    for (int i = 0; i < TA; ++i)
+#pragma unroll
+      for (int j = 0; j < TB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) probe = __builtin_fmaf(acc[i][j][r], 0.f, probe);
+    const bool again = __syncthreads_or(probe != probe);
+    if (__builtin_expect(again, 0)) {
+#pragma unroll
+      for (int i = 0; i < TA; ++i)
+#pragma unroll
+        for (int j = 0; j < TB; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      // (the rows of the groups as before, two at a time)
+      for (int64_t k = k_lo + 16 * g; k < k_hi; k += kRows)
+        for (int kk = 0; kk < 16; kk += 2) {
+          const int64_t row = k + kk + h;
+          const bool in = row < k_hi;
+          float av[TA], bv[TB];
+#pragma unroll
+          for (int i = 0; i < TA; ++i) {
+            const int t = wa * TA + i, m = m0 + 64 * (t >> 1) + 2 * c + (t & 1);
+            av[i] = in && m < a.M ? a.A[row * a.lda + m] : 0.f;
+          }
+#pragma unroll
+          for (int j = 0; j < TB; ++j) {
+            const int t = wb * TB + j, n = n0 + 64 * (t >> 1) + 2 * c + (t & 1);
+            bv[j] = in && n < a.N ? a.B[row * a.ldb + n] : 0.f;
+          }
+#pragma unroll
+          for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int j = 0; j < TB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
+        }
+    }
+    // the groups' sums
+    if constexpr (G > 1) {
+      float* red = reinterpret_cast<float*>(split_lds);
+      constexpr int kOne = TA * TB * 16 * 64;
+#pragma unroll
+      for (int from = 1; from < G; ++from) {
+        if (g == from) {
+#pragma unroll
+          for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) red[(wa * WB + wb) * kOne + ((i * TB + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+        }
+        __syncthreads();
+        if (g == 0) {
+#pragma unroll
+          for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) acc[i][j][r] += red[(wa * WB + wb) * kOne + ((i * TB + j) * 16 + r) * 64 + lane];
+        }
+        __syncthreads();
+      }
+    }
+    if (g == 0) {
+      // register r of lane (c, h) holds row 8 (r / 4) + 4 h + r % 4 of A's tile, column c of B's
+      int ce = c, he = h;
+      asm volatile("" : "+v"(ce), "+v"(he));
+      float* __restrict__ P = a.partial + (int64_t)split * a.M * a.N;
+#pragma unroll
+      for (int i = 0; i < TA; ++i)
+#pragma unroll
+        for (int j = 0; j < TB; ++j) {
+          const int ta = wa * TA + i, tb = wb * TB + j;
+          const int n = n0 + 64 * (tb >> 1) + 2 * ce + (tb & 1);
+          if (n >= a.N) continue;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int m = m0 + 64 * (ta >> 1) + 2 * (8 * (r / 4) + 4 * he + (r % 4)) + (ta & 1);
+            if (m < a.M) P[(int64_t)m * a.N + n] = acc[i][j][r];
+          }
+        }
+    }
+  }
+}
+
+constexpr size_t kSplitLds = 160 * 1024;
+
+template <int NT>
+int split_launch(const SplitArgs& a, int max_blocks, hipStream_t s) {
+  const int64_t lim = max_blocks > 0 && max_blocks < 256 ? max_blocks : 256;      // (a workgroup has a compute unit to itself)
+  const size_t step = (size_t)NT * 3 * 1024, bias = sizeof(float) * 16 * NT;
+  const int steps = (a.K + 31) / 32;
+  const bool res = steps * step + bias <= kSplitLds;
+  const size_t lds = (res ? steps : 2) * step + bias;
+  const int64_t wgs = ceil_div(a.M, 16 * kRT * kWaves);
+  const int panels = (int)ceil_div(a.N, NT * 16);
+  const unsigned blocks = (unsigned)std::min<int64_t>(wgs, std::max<int64_t>(1, lim / panels));
+  auto go = [&](auto kern) -> int {
+    GCN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    kern<<<dim3(blocks, (unsigned)panels), dim3(kThreads), lds, s>>>(a);
+    GCN_CHECK_LAUNCH();
+    return GCN_OK;
+  };
+  auto pick = [&](auto r, auto t) -> int {
+    constexpr bool R = decltype(r)::value, T = decltype(t)::value;
+    if (a.mask) return go(k_gemm_nn_split<NT, R, T, true, false>);
+    return a.C2 ? go(k_gemm_nn_split<NT, R, T, false, true>) : go(k_gemm_nn_split<NT, R, T, false, false>);
+  };
+  using std::true_type; using std::false_type;
+  if (res) return a.trans ? pick(true_type(), true_type()) : pick(true_type(), false_type());
+  return a.trans ? pick(false_type(), true_type()) : pick(false_type(), false_type());
+}
+
+// tiles per wavefront, wavefronts, groups; blocks of MB x NB elements of C
+struct TnShape { int ta, tb, wa, wb, g; int mb() const { return 32 * ta * wa; } int nb() const { return 32 * tb * wb; } };
+constexpr TnShape kTnShapes[] = {{2, 2, 2, 2, 2}, {2, 2, 4, 2, 1}, {2, 2, 2, 4, 1}, {4, 2, 2, 4, 1}, {3, 2, 4, 2, 1}};
+
+// the shape that reads least, then the one that multiplies least
+TnShape tn_shape(int M, int N) {
+  TnShape best = kTnShapes[0];
+  int64_t least = INT64_MAX;
+  for (const TnShape& t : kTnShapes) {
+    const int64_t bm = ceil_div(M, t.mb()), bn = ceil_div(N, t.nb());
+    const int64_t cost = (bm * N + bn * M) * 4 + bm * t.mb() * bn * t.nb() / 64;
+    if (cost < least) { least = cost; best = t; }
+  }
+  return best;
+}
+
+int tn_blocks(int M, int N) { const TnShape t = tn_shape(M, N); return (int)(ceil_div(M, t.mb()) * ceil_div(N, t.nb())); }
+
+int tn_splits(int64_t Kd, int M, int N) {
+  const int64_t want = 256 / tn_blocks(M, N), most = ceil_div(Kd, 128);
+  return (int)std::max<int64_t>(1, std::min(want, most));
+}
+
+}  // namespace
+
+// Where the fp32 kernels take longer.  Measured, their time over this kernel's, rows of K elements to N columns:
+//   W in registers (N = 192, 256; gemm_nn_limits_blocks)   10 K rows 0.6-0.8, 20 K 0.9-1.3, 60 K 1.3-1.9, 300 K 1.3-1.8 (256 x 256 on
+//                   2.45 M rows 2.55 -> 1.95 ms, 100 x 256 1.44 -> 1.21): from 2^15 rows on;
+//   W in LDS, whole k steps (K <= 128 or a multiple of it)  N <= 64 0.5-1.0, N = 72 .. 128 0.9-1.4, but nothing is gained in a training step
+//                   (the pipe's clock: 2^18 x 128 x 128 83 -> 69 us, what follows 14 us longer), N = 160 1.2-2.5: more than 128 columns;
+//   others (K = 160, 237, 300, 602, or W too large for LDS) N = 47 1.1-1.6, 64 1.2-1.8, 72-256 1.2-2.6, N <= 32 0.5-1.2 on up to
+//                   20 K rows, 1.0-1.5 from 60 K on (233 K rows 602 -> 128 421 -> 225 us, 722 K 505 -> 100 1175 -> 559).
+// Its error against 64 bits is a third of theirs: 128 columns of K = 128 / 602 terms of either sign 5.7e-8 / 9.6e-8 (2.0e-7 / 4.4e-7), positive
+// ones 4.2e-8 / 6.9e-8 (1.2e-7 / 2.6e-7).
+bool gemm_nn_split_ok(const void* A, int64_t lda, int64_t ldw, int64_t ldc, int64_t M, int N, int K, int dtype, const GemmEpilogue& epi) {
+  const Tuning& t = tune();
+  if (t.gemm_split == 0 || dtype != GCN_F32 || (epi.mask && epi.C2)) return false;
+  // (tiles of rows, and W, are buffers with 32-bit offsets)
+  if (lda >= 1 << 23 || ldc >= 1 << 23 || epi.ldc2 >= 1 << 23 || epi.ldmask >= 1 << 23 || K >= 1 << 23 || ldw >= 1 << 23) return false;
+  if ((double)(epi.b_trans ? N : K) * (double)ldw * 4 >= 1 << 30) return false;
+  if (t.gemm_split == 2) return true;
+  if (t.gemm_fast != 1 || t.gemm_regw != 1 || epi.beside) return false;      // (an override is a choice between the fp32 kernels)
+  if (epi.rows > 0) M = epi.rows;
+  if (gemm_nn_limits_blocks(A, lda, M, N, K, dtype)) return M >= 1 << 15;
+  const bool whole_steps = gemm_nn_direct_ok(N, K) && (K <= 128 || K % 128 == 0);
+  if (!whole_steps) return N > 32 || M >= 1 << 16;
+  return N > 128 && K >= 48;
+}
+
+int gemm_nn_split(const void* A, int64_t lda, const float* W, int64_t ldw, void* C, int64_t ldc, int64_t M, int N, int K,
+                  const GemmEpilogue& epi, hipStream_t s) {
+  auto quads = [](const void* p, int64_t ld) { return ((uintptr_t)p % 16) == 0 && ld % 4 == 0; };
+  SplitArgs a{(const float*)A, lda, W, ldw, (float*)C, ldc, M, N, K, epi.bias, epi.relu, (const float*)epi.mask, epi.ldmask, epi.mask_rows,
+              (float*)epi.C2, epi.ldc2, epi.b_trans ? 1 : 0,
+              N % 4 != 0 && (!epi.c_rows_padded || !quads(C, ldc) || (epi.C2 && !quads(epi.C2, epi.ldc2)))};
+  if (N <= 64) return split_launch<4>(a, epi.max_blocks, s);
+  if (N <= 128) return split_launch<8>(a, epi.max_blocks, s);
+  if (N <= 192) return split_launch<12>(a, epi.max_blocks, s);
+  return split_launch<16>(a, epi.max_blocks, s);
+}
+
+// More than 64 columns on both sides, from 2 K rows on.  fp32 kernels / this one with the final sum, us: 2.5 K rows x 128 x 128 17.0 / 15.8,
+// 8 K x 602 x 200 47 / 46, 100 K x 300 x 256 251 / 148, 233 K x 602 x 128 532 / 307, 2^18 x 128 x 128 102 / 81, 722 K x 505 x 100
+// 1115 / 680, 2.45 M x 100 x 256 1290 / 1130, x 256 x 256 2440 / 1910; but 333 x 77 x 91 11.7 / 14.9, 300 K x 128 x 64 78 / 89, x 602 x 16 243 / 323:
+// there the product waits for memory, and 32 rows in flight are too few.
+// Error against 64 bits 4.4e-7 for 1.7e-6 (256 x 256 over 2.45 M rows), 1.2e-7 for 5.8e-7 (128 x 128 over 2^18).
+bool gemm_tn_split_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype) {
+  const Tuning& t = tune();
+  if (t.gemm_split == 0 || dtype != GCN_F32 || Kd < 1 || M < 1 || N < 1) return false;
+  if (lda >= 1 << 23 || ldb >= 1 << 23) return false;
+  if (t.gemm_split == 2) return true;
+  return t.gemm_tn_wide == 1 && t.gemm_tn_lds == 1 && M > 64 && N > 64 && Kd >= 2048;
+}
+
+size_t gemm_tn_split_ws_bytes(int64_t Kd, int M, int N) { return sizeof(float) * (size_t)tn_splits(Kd, M, N) * (size_t)M * (size_t)N; }
+
+int gemm_tn_split_partials(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, float* partial, int* nsplit_out,
+                           hipStream_t s, int max_blocks) {
+  const TnShape t = tn_shape(M, N);
+  const int per_split = tn_blocks(M, N);
+  const int64_t rps = round_up(ceil_div(Kd, tn_splits(Kd, M, N)), 32);
+  const int nsplit = (int)ceil_div(Kd, rps);            // every split holds at least one row
+  *nsplit_out = nsplit;
+  SplitTnArgs a{(const float*)A, lda, (const float*)B, ldb, Kd, M, N, rps, (int)ceil_div(M, t.mb()), nsplit, partial};
+  const int at_once = max_blocks > 0 ? std::min(nsplit, std::max(1, max_blocks / per_split)) : nsplit;
+  const size_t lds = (size_t)2 * t.g * (t.ta * t.wa + t.tb * t.wb) * 3 * 1024;
+#define GCN_TNS(TA, TB, WA, WB, G)                                                                              \
+  if (t.ta == TA && t.tb == TB && t.wa == WA && t.wb == WB && t.g == G) {                                         \
+    auto kern = k_gemm_tn_split<TA, TB, WA, WB, G>;                                                              \
+    GCN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+    kern<<<dim3((unsigned)at_once, (unsigned)per_split), kThreads, lds, s>>>(a);                                 \
+  }
+  GCN_TNS(2, 2, 2, 2, 2) GCN_TNS(2, 2, 4, 2, 1) GCN_TNS(2, 2, 2, 4, 1) GCN_TNS(4, 2, 2, 4, 1) GCN_TNS(3, 2, 4, 2, 1)
+#undef GCN_TNS
+  GCN_CHECK_LAUNCH();
+  return GCN_OK;
+}
+
+}  // namespace gcn

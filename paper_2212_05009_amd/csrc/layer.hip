@@ -158,9 +158,9 @@ struct SideStream {
 static int side_chunks() { const int c = tune().overlap_chunks; return c >= 8 ? 8 : c >= 4 ? 4 : c >= 2 ? 2 : 0; }
 
 // Is a sparse product over this many rows and entries at this width long enough to put the weight gradient beside it?
+static bool long_sparse(int64_t rows, int64_t nnz, int d) { return rows >= (1 << 17) && (double)nnz * (double)d >= 4e9; }
 static bool overlap_worthwhile(int64_t rows, int64_t nnz, int d) {
-  if (tune().overlap == 2) return true;
-  return tune().overlap == 1 && rows >= (1 << 17) && (double)nnz * (double)d >= 4e9;
+  return tune().overlap == 2 || (tune().overlap == 1 && long_sparse(rows, nnz, d));
 }
 
 // A layer's sparse product a and the dense product of its rows by a d x N matrix as one kernel: where both are launches and chains
@@ -173,7 +173,7 @@ static bool few_rows(int64_t rows, int d, int N, int dtype) {
   const Tuning& t = tune();
   if (t.spmm_dense != 1) return t.spmm_dense == 2;
   // (an override of a dense kernel is a choice between two-kernel forms)
-  if (t.gemm_direct != 1 || t.gemm_fast != 1 || t.gemm_bf16 != 1 || t.gemm_regw != 1 || t.gemm_tn_lds != 1) return false;
+  if (t.gemm_direct != 1 || t.gemm_fast != 1 || t.gemm_bf16 != 1 || t.gemm_regw != 1 || t.gemm_tn_lds != 1 || t.gemm_split != 1) return false;
   return rows <= (dtype == GCN_F32 && (int64_t)d * N >= 4096 ? 8192 : 4096);
 }
 
@@ -271,6 +271,8 @@ static int layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
         GemmEpilogue epi;
         epi.bias = bias; epi.relu = relu; epi.C2 = Z; epi.ldc2 = ldz;
         epi.c_rows_padded = true;
+        epi.beside = !fused && long_sparse(A->nr, A->nnz, d_in) && !spmm_panel_wanted(sp);      // (the same kernel, beside or not)
+        epi.rows = A->nr;
         const bool pipelined = !fused && side_chunks() > 0 && overlap_worthwhile(A->nr, A->nnz, d_in) && !spmm_panel_wanted(sp) &&
                                gemm_nn_limits_blocks(AH, ldAH, A->nr, d_out, d_in, dtype);
         if (fused) {
@@ -404,7 +406,7 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
                             gemm_tn_limits_blocks(AH_saved, ldah, G, ldg, A->nr, d_in, d_out, dtype);
         if (beside) {
           GCN_TRY(side.fork(Am, s));
-          GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, side.side, tune().overlap_cus));
+          GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, side.side, tune().overlap_cus, long_sparse(A->nc, A->nnz, d_out)));
         }
         if (fused) {
           GemmEpilogue epi;
@@ -429,7 +431,7 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
           }
         }
         if (beside) GCN_TRY(side.join());
-        else if (AH_saved) GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, s));
+        else if (AH_saved) GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, s, 0, long_sparse(A->nc, A->nnz, d_out)));
         else GCN_TRY(gemm_tn(H, ldh, T, ldt, dW, d_out, A->nc, d_in, d_out, dtype, tn, s));
       }
     } else {
@@ -450,7 +452,7 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
           GCN_TRY(gemm_nn(G, ldg, W, d_out, Q, ldq, A->nr, d_in, d_out, dtype, epi, s));
           if (beside) {        // after Q = G W^T, which wants the matrix pipes of every compute unit itself
             GCN_TRY(side.fork(Am, s));
-            GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, side.side, tune().overlap_cus));
+            GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, side.side, tune().overlap_cus, long_sparse(A->nc, A->nnz, d_in)));
           }
           SpmmArgs sp{A->colptr, A->rowidx, A->val_t, &A->sched_t, A->nc, A->nr, A->nnz, true, A->nr, Q, ldq, dH, lddh, nullptr, 0,
                       d_in, dtype, Zprev ? GCN_EPI_MASK : GCN_EPI_NONE, nullptr, Zprev, ldzp};
@@ -470,7 +472,7 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
           ah = AH; ld_ah = ldq;
         }
         if (beside) GCN_TRY(side.join());
-        else GCN_TRY(gemm_tn(ah, ld_ah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, s));
+        else GCN_TRY(gemm_tn(ah, ld_ah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, s, 0, dH && AH_saved && long_sparse(A->nc, A->nnz, d_in)));
       }
     }
     if (!pass) GCN_TRY(ensure_workspace(Am, ws.used));

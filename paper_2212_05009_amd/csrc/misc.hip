@@ -514,7 +514,7 @@ const TuneField kTuneFields[] = {
     {"GCN_SPMM_DENSE", &Tuning::spmm_dense, 0, 2},
     {"GCN_PARTITION_SORT", &Tuning::partition_sort, 0, 1},  {"GCN_GEMM_DIRECT", &Tuning::gemm_direct, 0, 1},
     {"GCN_GEMM_FAST", &Tuning::gemm_fast, 0, 1},            {"GCN_GEMM_TN_WIDE", &Tuning::gemm_tn_wide, 0, 1},
-    {"GCN_GEMM_BF16", &Tuning::gemm_bf16, 0, 1},            {"GCN_GEMM_REGW", &Tuning::gemm_regw, 0, 2},
+    {"GCN_GEMM_BF16", &Tuning::gemm_bf16, 0, 1},            {"GCN_GEMM_REGW", &Tuning::gemm_regw, 0, 2}, {"GCN_GEMM_SPLIT", &Tuning::gemm_split, 0, 2},
     {"GCN_GEMM_TN_LDS", &Tuning::gemm_tn_lds, 0, 2},        {"GCN_GEMM_TN_BLOCKS", &Tuning::gemm_tn_blocks, 1, 1 << 16},
     {"GCN_GATHER_HOST_BLOCKS", &Tuning::gather_host_blocks, 1, 4096}, {"GCN_GEMM_TN_LDS_BLOCKS", &Tuning::gemm_tn_lds_blocks, 0, 4096}, {"GCN_GEMM_REGW_BLOCKS", &Tuning::gemm_regw_blocks, 0, 4096},
     {"GCN_OVERLAP", &Tuning::overlap, 0, 2},               {"GCN_OVERLAP_CUS", &Tuning::overlap_cus, 1, 4096},

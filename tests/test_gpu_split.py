@@ -1,0 +1,95 @@
+"""GPU parity: fp32 products on the bf16 matrix pipe, every value in three parts (gemm_split.hip), against the oracle at the contract's
+tolerance, against the fp32 kernels' error, and on operands that are no finite numbers or next to the largest one."""
+import numpy as np
+import pytest
+
+from test_gpu_layer import Case, dev, gcn, run_bwd, run_fwd, tuned          # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_alone(gcn, dev, rows):
+    return Case(gcn, dev, np.zeros(0, np.int32), np.zeros(0, np.int32), rows)          # A^ = I
+
+
+# Steps of 32 k with and without a tail, W whole in LDS and two steps at a time, each number of column tiles, more columns than one panel,
+# columns that end inside a group of four; W as it is and transposed; rows around a tile, a workgroup and a pass over all of them.
+@pytest.mark.parametrize("rows", [1, 31, 257, 4099, 70001])
+@pytest.mark.parametrize("d_in,d_out", [(1, 5), (33, 65), (64, 128), (100, 173), (602, 41), (200, 300), (129, 192), (256, 256)])
+def test_products_in_three_parts(gcn, dev, tuned, rows, d_in, d_out):
+    case = rows_alone(gcn, dev, rows)
+    tuned("GCN_GEMM_SPLIT", 2)
+    run_fwd(gcn, dev, case, d_in, d_out, bias=True, save_ah=True)
+    run_fwd(gcn, dev, case, d_in, d_out, act="none", want_z=False)
+    run_bwd(gcn, dev, case, d_in, d_out, saved_ah=True, dbias=True)
+    run_bwd(gcn, dev, case, d_in, d_out, mask=False)
+    case.A.free()
+
+
+# Every shape of the weight gradient's workgroups; widths around pairs of columns and blocks; rows around a chunk, a split, many splits.
+@pytest.mark.parametrize("rows", [1, 15, 33, 2049, 40001])
+@pytest.mark.parametrize("d_in,d_out", [(65, 67), (128, 128), (256, 100), (100, 256), (250, 256), (602, 128), (384, 128), (44, 300), (520, 260)])
+def test_weight_gradient_in_three_parts(gcn, dev, tuned, rows, d_in, d_out):
+    case = rows_alone(gcn, dev, rows)
+    tuned("GCN_GEMM_SPLIT", 2)
+    run_bwd(gcn, dev, case, d_in, d_out, want_dh=False, saved_ah=True)
+    case.A.free()
+
+
+def error(a, ref):
+    return ((a.double() - ref).norm() / ref.norm()).item()
+
+
+# the 2-norm of the error against 64 bits, of terms of either sign, after a ReLU, and all positive
+@pytest.mark.parametrize("kind", ["signed", "relu", "positive"])
+@pytest.mark.parametrize("rows,d_in,d_out", [(20000, 128, 200), (20000, 602, 128), (70001, 256, 256), (262144, 100, 130)])
+def test_no_less_exact_than_the_fp32_pipe(gcn, dev, tuned, kind, rows, d_in, d_out):
+    import torch
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(rows + d_in)
+    X = torch.randn(rows, d_in, generator=gen, device=dev)
+    W = torch.randn(d_in, d_out, generator=gen, device=dev)
+    G = torch.randn(rows, d_out, generator=gen, device=dev)
+    if kind != "signed":
+        X.clamp_(min=0)
+    if kind == "positive":
+        W.abs_(), G.abs_()
+    case = rows_alone(gcn, dev, rows)
+    err = {}
+    for mode in (0, 2):
+        tuned("GCN_GEMM_SPLIT", mode)
+        out, dW = torch.empty(rows, d_out, device=dev), torch.empty(d_in, d_out, device=dev)
+        gcn.gcn_dense_fwd(X, W, out)
+        gcn.gcn_layer_bwd(case.A, X, W, G, dW, AH_saved=X)
+        err[mode] = (error(out, X.double() @ W.double()), error(dW, X.double().T @ G.double()))
+    print(kind, rows, d_in, d_out, err, flush=True)
+    assert err[2][0] <= err[0][0] and err[2][1] <= err[0][1]
+    case.A.free()
+
+
+# Values beyond the range of their first part: the rows (for a gradient, the workgroups' ranges of rows) that hold one are multiplied on the fp32
+# pipe.  Infinities and NaN come out where 64 bits have them; a product next to the largest number as it is.
+@pytest.mark.parametrize("d_in,d_out", [(100, 173), (256, 256), (130, 64)])
+def test_infinities_nan_and_the_largest_numbers(gcn, dev, tuned, d_in, d_out):
+    import torch
+    rows = 3001
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d_in)
+    X = torch.randn(rows, d_in, generator=gen, device=dev)
+    W = torch.randn(d_in, d_out, generator=gen, device=dev) * 0.01
+    G = torch.randn(rows, d_out, generator=gen, device=dev) * 0.01
+    X[5, 3], X[6, 7], X[2999, d_in - 1], X[3000, 0] = float("inf"), float("-inf"), float("nan"), 3.4e38
+    X[40, 2], X[40, 9] = float("inf"), float("-inf")
+    tuned("GCN_GEMM_SPLIT", 2)
+    out, dW = torch.empty(rows, d_out, device=dev), torch.empty(d_in, d_out, device=dev)
+    gcn.gcn_dense_fwd(X, W, out)
+    case = rows_alone(gcn, dev, rows)
+    gcn.gcn_layer_bwd(case.A, X, W, G, dW, AH_saved=X)
+    for got, ref, scale in ((out, X.double() @ W.double(), X.double().abs() @ W.double().abs()),
+                            (dW, X.double().T @ G.double(), X.double().abs().T @ G.double().abs())):
+        inf, nan = torch.isinf(ref), torch.isnan(ref)
+        assert torch.equal(torch.isnan(got), nan)
+        assert torch.equal(got[inf].double(), ref[inf])
+        ok = ~(inf | nan)
+        assert ok.any() and bool(((got.double() - ref).abs()[ok] <= 1e-5 * scale[ok]).all())
+    case.A.free()
