@@ -149,3 +149,32 @@ def test_counting_by_columns_equals_sorting(gcn, dev, p, directed):
     for other in (gcn.gcn_partition_stats(A, part_d, p), gcn.gcn_partition_stats(rows_only, part_d, p)):
         for k in by_sort:
             assert torch.equal(by_sort[k], other[k]), k
+
+
+# Columns whose lengths lie at the bounds of the ways they are counted in (4 lanes, 16, a wavefront with one and more batches, chunks of hub
+# columns), every neighbour in another part and all of them in few; part counts around whole words and where the pair table leaves LDS.
+@pytest.mark.parametrize("p", [1, 31, 33, 512, 513, 4096])
+def test_columns_of_every_length_class(gcn, dev, p):
+    lens = [0, 1, 2, 3, 4, 7, 11, 14, 15, 16, 47, 61, 62, 63, 64, 127, 255, 511, 512, 513, 1023, 1024, 2046, 2047, 2048, 3071, 5000]
+    n = 8000
+    rng = np.random.default_rng(p)
+    cols = rng.permutation(n)[:3 * len(lens)]
+    src = np.concatenate([rng.permutation(n)[:k] for c, k in zip(cols, 3 * lens)])
+    dst = np.concatenate([np.full(k, c) for c, k in zip(cols, 3 * lens)])
+    for part in (rng.integers(0, p, n), np.minimum(rng.integers(0, 3, n), p - 1), np.arange(n) % p):
+        both(gcn, dev, src, dst, n, part, p)
+
+
+def test_a_part_out_of_range_is_refused_wherever_it_is(gcn, dev):
+    import torch
+    n, p = 3000, 40
+    rng = np.random.default_rng(3)
+    src, dst = rng.integers(0, n, 9000), rng.integers(0, n, 9000)
+    src, dst = np.r_[src, np.arange(n)], np.r_[dst, np.full(n, 7)]                     # vertex 7: a hub column
+    A = gcn.gcn_csr_build(torch.from_numpy(src.astype(np.int32)).to(dev), torch.from_numpy(dst.astype(np.int32)).to(dev), n, 0, n)
+    for at, bad in ((0, -1), (7, p), (n - 1, 2**31 - 1), (1234, -2**31)):
+        part = rng.integers(0, p, n)
+        part[at] = bad
+        with pytest.raises(Exception, match="part id"):
+            gcn.gcn_partition_stats(A, torch.from_numpy(part.astype(np.int32)).to(dev), p)
+    A.free()
