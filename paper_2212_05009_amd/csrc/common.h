@@ -153,6 +153,14 @@ static inline bool grid_fits(int64_t blocks) { return blocks <= max_grid_x() * 6
 #ifdef __HIPCC__
 __device__ __forceinline__ int64_t block_id() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 
+// val(i,j) = fl(1/sqrt(d_i)) * fl(1/sqrt(d_j)), each operation correctly rounded in fp32.
+// Both steps go through fp64: an fp64 square root or quotient rounded once more to fp32 equals the
+// correctly rounded fp32 result (53 >= 2*24 + 2 bits), whatever the fp32 code generation options are.
+__device__ __forceinline__ float inv_sqrt_deg(int32_t d) {
+  const float r = (float)sqrt((double)(float)d);
+  return (float)(1.0 / (double)r);
+}
+
 // bf16 features: a value is the upper half of the fp32 pattern.  Stores round to nearest even; NaN stays NaN.
 typedef uint16_t bf16_t;
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float((uint32_t)b << 16); }
@@ -303,6 +311,13 @@ struct KeyBuild {
   const int32_t* deg_global = nullptr;   // of every global vertex, for the halo columns
   int flags = 0;
 };
+// The arrays of a handle, those of a column-major copy empty where none is wanted: its schedules are built, the stream is waited for, and A
+// takes them.
+struct HandleArrays {
+  int64_t n_global, row_lo, nr, nh, nnz;
+  DevBuf *rowptr, *col, *val, *deg, *halo_gid, *colptr, *rowidx, *val_t, *mid;
+};
+int adopt_arrays(const HandleArrays& h, CallScope& sc, PinnedPage& page, gcn_csr* A);
 int key_bits(int64_t n);
 size_t key_words_bytes(int64_t m);
 int64_t* key_verdict(const DevBuf& words, int64_t m);

@@ -192,14 +192,6 @@ __global__ void k_row_mid(const int64_t* __restrict__ ptr, const int32_t* __rest
 }
 
 // ---- step 5: values ---------------------------------------------------------------------------------
-// val(i,j) = fl(1/sqrt(d_i)) * fl(1/sqrt(d_j)), each operation correctly rounded in fp32.
-// Both steps go through fp64: an fp64 square root or quotient rounded once more to fp32 equals the
-// correctly rounded fp32 result (53 >= 2*24 + 2 bits), whatever the fp32 code generation options are.
-__device__ __forceinline__ float inv_sqrt_deg(int32_t d) {
-  const float r = (float)sqrt((double)(float)d);
-  return (float)(1.0 / (double)r);
-}
-
 // Degrees of the owned rows and fl(1/sqrt(d)) of every local column.  An owned vertex's degree is the entry count of its
 // row, which the block holds whole (Sec. 4.1); a halo vertex's row lives elsewhere: its degree comes from the caller's
 // global array.
@@ -575,6 +567,29 @@ static int verdict(int64_t v) {
   return GCN_OK;
 }
 
+int adopt_arrays(const HandleArrays& h, CallScope& sc, PinnedPage& page, gcn_csr* A) {
+  const bool csc = h.colptr->p != nullptr;
+  const int64_t nc = h.nr + h.nh;
+  ScheduleBuild sched;
+  GCN_TRY(sched.add(h.rowptr->as<int64_t>(), h.nr, h.nnz, sc));
+  if (csc) GCN_TRY(sched.add(h.colptr->as<int64_t>(), nc, h.nnz, sc));
+  GCN_TRY(sched.enqueue(sc, page.words()));
+  GCN_HIP(hipStreamSynchronize(sc.s));
+  sc.done = true;
+
+  A->n_global = h.n_global; A->row_lo = h.row_lo;
+  A->nr = h.nr; A->nh = h.nh; A->nc = nc; A->nnz = h.nnz;
+  sched.finish(0, &A->sched);
+  if (csc) sched.finish(1, &A->sched_t);
+  A->rowptr = (int64_t*)h.rowptr->release(); A->col = (int32_t*)h.col->release();
+  A->val = (float*)h.val->release(); A->deg = (int32_t*)h.deg->release();
+  A->halo_gid = (int32_t*)h.halo_gid->release();
+  A->colptr = (int64_t*)h.colptr->release(); A->rowidx = (int32_t*)h.rowidx->release();
+  A->val_t = (float*)h.val_t->release();
+  A->mid = h.nh > 0 ? (int64_t*)h.mid->release() : nullptr;
+  return GCN_OK;
+}
+
 int build_from_keys(const KeyBuild& in, CallScope& sc, PinnedPage& page, gcn_csr* A) {
   hipStream_t s = sc.s;
   const int64_t nr = in.nr, nh = in.nh, nc = nr + nh, m = in.m;
@@ -635,24 +650,8 @@ int build_from_keys(const KeyBuild& in, CallScope& sc, PinnedPage& page, gcn_csr
                                                                                  rowidx.as<int32_t>(), val_t.as<float>(), colptr.as<int64_t>());
     GCN_CHECK_LAUNCH();
   }
-  ScheduleBuild sched;
-  GCN_TRY(sched.add(rowptr.as<int64_t>(), nr, nnz, sc));
-  if (in.flags & GCN_BUILD_CSC) GCN_TRY(sched.add(colptr.as<int64_t>(), nc, nnz, sc));
-  GCN_TRY(sched.enqueue(sc, read));
-  GCN_HIP(hipStreamSynchronize(s));
-  sc.done = true;
-
-  A->n_global = in.n_global; A->row_lo = in.row_lo;
-  A->nr = nr; A->nh = nh; A->nc = nc; A->nnz = nnz;
-  sched.finish(0, &A->sched);
-  if (in.flags & GCN_BUILD_CSC) sched.finish(1, &A->sched_t);
-  A->rowptr = (int64_t*)rowptr.release(); A->col = (int32_t*)col.release();
-  A->val = (float*)val.release(); A->deg = (int32_t*)deg.release();
-  A->halo_gid = (int32_t*)in.halo_gid->release();
-  A->colptr = (int64_t*)colptr.release(); A->rowidx = (int32_t*)rowidx.release();
-  A->val_t = (float*)val_t.release();
-  A->mid = nh > 0 ? (int64_t*)mid.release() : nullptr;
-  return GCN_OK;
+  HandleArrays h{in.n_global, in.row_lo, nr, nh, nnz, &rowptr, &col, &val, &deg, in.halo_gid, &colptr, &rowidx, &val_t, &mid};
+  return adopt_arrays(h, sc, page, A);
 }
 
 static int build_impl(const int32_t* d_src, const int32_t* d_dst, int64_t n_edges, int64_t n_global,

@@ -7,7 +7,9 @@
 // those of the subgraph.  The entries of the selected rows whose columns are selected too become
 // (row, column) keys in subgraph numbering, one pass over those rows, and the keys go through the
 // builder's second half, so sorting, normalisation and the column-major copy are the builder's.
+#include <algorithm>
 #include <new>
+#include <type_traits>
 
 #include "common.h"
 
@@ -17,10 +19,11 @@ constexpr int kIndThreads = 256;
 static inline dim3 ind_grid(int64_t n) { return fold_grid(ceil_div(n > 0 ? n : 1, kIndThreads)); }
 
 // lid[v] = -1 for every vertex of the parent; the flags and the number of keys (the diagonals come first)
-__global__ void k_ind_init(int32_t* __restrict__ lid, int64_t n, int64_t n_sub, int* __restrict__ bad, int64_t* __restrict__ cursor) {
+__global__ void k_ind_init(int32_t* __restrict__ lid, int64_t n, int64_t n_sub, int* __restrict__ bad, int64_t* __restrict__ cursor, int cursors) {
   int64_t i = block_id() * blockDim.x + threadIdx.x;
   if (i < n) lid[i] = -1;
-  if (i == 0) { bad[0] = bad[1] = 0; *cursor = n_sub; }
+  if (i == 0) bad[0] = bad[1] = 0;
+  if (i < cursors) cursor[i] = n_sub;
 }
 
 // lid[vertices[k]] = k; ids out of range are reported, never used as an index
@@ -122,7 +125,461 @@ __global__ __launch_bounds__(kIndThreads) void k_ind_keys(const int32_t* __restr
     if ((kept[i] >> lane) & 1ull) keys[base + wave_cnt[i][w] + __popcll(kept[i] & ((1ull << lane) - 1ull))] = key[i];
 }
 
-static int induced_impl(const gcn_csr_t* A, const int32_t* d_vertices, int64_t n_sub, int flags, hipStream_t s, gcn_csr* B) {
+// ---- row by row ------------------------------------------------------------------------------------------------------
+// A parent with both copies: the rows (columns) of the subgraph are what is left of the parent's selected rows (columns), each sorted by
+// itself.  Two passes over them, one that counts and one that sorts and writes, with the call's wait for the number of entries between:
+// seven launches and two waits up to the schedules' read-back, where making keys and sorting them by radix, twice, took 28 and three.  20 K of 2^18
+// R-MAT vertices, training step included: 398 -> 286 us (count 20, fill 36; the sorts, counts and copies they replace 190).
+//
+// A block takes the rows of one side, kIndLanes lanes each (a step of the chain vertex, ends, columns, numbers in the subgraph serves up to 64
+// entries), then those of up to kIndWave entries with a wavefront each, then the longer ones, cut into pieces of kIndWave entries, a wavefront
+// each.  What is kept of a row is ranked by comparing all pairs, out of LDS, up to kIndRank entries; longer lists are marked in a bitmap of
+// the subgraph's vertices, whose set bits are the sorted list (at most 2^20 vertices: 128 KB of LDS; several rows at a time where their bitmaps fit
+// 32 KB).
+constexpr int kIndLanes = 16, kIndShort = 64;              // lanes of a short row; its entries
+constexpr int kIndWave = 1024;                             // entries that a wavefront takes of a row
+constexpr int kIndRank = 256;
+constexpr int kIndU = 8;                                   // entries a lane asks for together
+// The number of entries is added up on so many words, whose sum the host takes: additions to one word are 14 ns each, one after the other
+constexpr int kIndSums = 128;
+constexpr int64_t kIndMaxSub = (int64_t)1 << 20;
+// Up to here a block adds up the counts before its rows itself (128 KB out of L2 at most): a scan is a launch of 12 us.  Bitmaps of more vertices
+// leave room for few blocks on a compute unit: the rows that take one are then done by a launch of their own.
+constexpr int64_t kIndOwnOffsets = (int64_t)1 << 15;
+constexpr int kIndThreadsRows = 512, kIndMany = 1024;
+// staging: 64 entries a row, or kIndRank a wavefront
+constexpr size_t ind_stage(int threads) { return sizeof(int32_t) * (size_t)(threads / kIndLanes * kIndShort); }
+static_assert(ind_stage(kIndThreadsRows) == sizeof(int32_t) * kIndThreadsRows / 64 * kIndRank, "one staging area");
+
+struct IndRows {
+  const int32_t* vertices; int64_t n_sub, n; const int32_t* lid;
+  const int64_t* ptr[2]; const int32_t* idx[2];            // the parent's rows, then its columns
+  int64_t blocks; int sides;                               // blocks of a side
+  uint32_t* cnt; int64_t cnt_ld;                           // [sides][cnt_ld] entries kept; sides start on 16 bytes
+  int32_t* deg; float* dinv;
+  int* bad; int64_t* nnz;
+  int64_t* out_ptr[2]; int scanned;                        // (scanned: out_ptr holds the sums already)
+  int32_t* out_idx[2]; float* out_val[2];
+  int maps;                                                // bitmaps side by side, a power of two up to the wavefronts
+  // rows that take one, where they are done by themselves: kIndSums lists of up to map_ld
+  int64_t* map_list; int64_t map_ld; int* map_count;
+};
+
+// a row of the parent: its ends
+struct IndJob { int64_t s, len; };
+__device__ __forceinline__ IndJob ind_job(const IndRows& a, int side, int64_t k) {
+  IndJob j{0, 0};
+  if (k >= a.n_sub) return j;
+  const int32_t v = a.vertices[k];
+  if (v < 0 || v >= a.n) return j;                         // (reported: it has no entries here)
+  j.s = a.ptr[side][v];
+  j.len = a.ptr[side][v + 1] - j.s;
+  return j;
+}
+// entries e0 + 64 u + lane of a row, of which those below `end` are asked for: their numbers in the subgraph, or -1
+__device__ __forceinline__ void ind_entries(const int32_t* __restrict__ idx, const int32_t* __restrict__ lid, int64_t s, int64_t e0, int64_t end,
+                                            int lane, int32_t (&c)[kIndU]) {
+#pragma unroll
+  for (int u = 0; u < kIndU; ++u) {
+    const int64_t e = e0 + 64 * u + lane;
+    c[u] = e < end ? idx[s + e] : -1;
+  }
+#pragma unroll
+  for (int u = 0; u < kIndU; ++u) c[u] = c[u] >= 0 ? lid[c[u]] : -1;
+}
+
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ind_count(IndRows a) {
+  constexpr int kIndWaves = THREADS / 64, kIndJobs = THREADS / kIndLanes;
+  __shared__ uint32_t kept[kIndJobs];
+  __shared__ int pieces[kIndJobs + 1];                     // (rows in pieces, their number; then a running sum)
+  __shared__ int piece_job[kIndJobs];
+  __shared__ int n_rows;
+  __shared__ IndJob ends[kIndJobs];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = threadIdx.x / kIndLanes, l = threadIdx.x % kIndLanes;
+  const int64_t blk = block_id();
+  if (blk >= a.sides * a.blocks) return;
+  const int side = blk >= a.blocks ? 1 : 0;
+  const int64_t k0 = (blk - side * a.blocks) * kIndJobs;
+  if (threadIdx.x == 0) n_rows = 0;
+  if (threadIdx.x < kIndJobs) kept[threadIdx.x] = 0u;
+  __syncthreads();
+  {
+    const int64_t k = k0 + g;
+    const IndJob j = ind_job(a, side, k);
+    if (k < a.n_sub && l == 0 && side == 0) {
+      const int32_t v = a.vertices[k];
+      if (v >= 0 && v < a.n && a.lid[v] != (int32_t)k) a.bad[1] = 1;         // listed twice: one of its places is not in lid
+    }
+    if (j.len > kIndShort) {
+      if (l == 0) {
+        ends[g] = j;
+        const int at = atomicAdd(&n_rows, 1);
+        piece_job[at] = g;
+        pieces[at] = (int)((j.len + kIndWave - 1) / kIndWave);
+      }
+    } else {
+      int32_t c[kIndShort / kIndLanes];
+#pragma unroll
+      for (int u = 0; u < kIndShort / kIndLanes; ++u) {
+        const int e = u * kIndLanes + l;
+        c[u] = e < j.len ? a.idx[side][j.s + e] : -1;
+      }
+      uint32_t n = 0;
+#pragma unroll
+      for (int u = 0; u < kIndShort / kIndLanes; ++u) n += c[u] >= 0 && a.lid[c[u]] >= 0 ? 1u : 0u;
+#pragma unroll
+      for (int o = 1; o < kIndLanes; o <<= 1) n += __shfl_xor(n, o, kIndLanes);
+      if (l == 0) kept[g] = n;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int run = 0;
+    for (int i = 0; i < n_rows; ++i) { const int c = pieces[i]; pieces[i] = run; run += c; }
+    pieces[n_rows] = run;
+  }
+  __syncthreads();
+  for (int i = w, row = 0; i < pieces[n_rows]; i += kIndWaves) {
+    while (pieces[row + 1] <= i) ++row;
+    const int at = piece_job[row];
+    const IndJob j = ends[at];
+    const int64_t e_lo = (int64_t)(i - pieces[row]) * kIndWave, e_hi = e_lo + kIndWave < j.len ? e_lo + kIndWave : j.len;
+    uint32_t n = 0;
+    for (int64_t e0 = e_lo; e0 < e_hi; e0 += 64 * kIndU) {
+      int32_t c[kIndU];
+      ind_entries(a.idx[side], a.lid, j.s, e0, e_hi, lane, c);
+#pragma unroll
+      for (int u = 0; u < kIndU; ++u) n += c[u] >= 0 ? 1u : 0u;
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) n += __shfl_xor(n, o, 64);
+    if (lane == 0) atomicAdd(&kept[at], n);
+  }
+  __syncthreads();
+  if (w == 0) {
+    static_assert(kIndJobs <= 64, "a row per lane");
+    const int64_t k = k0 + lane;
+    const bool mine = lane < kIndJobs && k < a.n_sub;
+    uint32_t n = mine ? kept[lane] : 0u;
+    if (mine) {
+      a.cnt[side * a.cnt_ld + k] = n;
+      if (side == 0) { a.deg[k] = (int32_t)n; a.dinv[k] = inv_sqrt_deg(n > 0 ? (int32_t)n : 1); }
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) n += __shfl_xor(n, o, 64);
+    if (lane == 0 && side == 0) atomicAdd(reinterpret_cast<unsigned long long*>(a.nnz + blk % kIndSums), (unsigned long long)n);
+  }
+}
+
+// An entry of a row at place `at`; its value is the product of the same two factors on both sides.
+__device__ __forceinline__ void ind_put(const IndRows& a, int side, float dk, int64_t at, int32_t v) {
+  a.out_idx[side][at] = v;
+  a.out_val[side][at] = __fmul_rn(dk, a.dinv[v]);
+}
+
+struct IndMapRow { IndJob ends; int64_t first, k; int side; };
+// `rows` rows side by side (written by threads of the block before), each with its bitmap: their pieces go round the wavefronts, then each bitmap
+// is read by its share of them.
+template <int THREADS>
+__device__ __forceinline__ void ind_maps(const IndRows& a, uint32_t* __restrict__ maps, const IndMapRow* row, int rows) {
+  constexpr int kWaves = THREADS / 64;
+  __shared__ int pieces[kWaves + 1];
+  __shared__ uint32_t wave_sum[kWaves];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int words = (int)((a.n_sub + 31) >> 5), per_map = kWaves / a.maps;
+  for (int q = threadIdx.x; q < rows * words; q += THREADS) maps[q] = 0u;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int run = 0;
+    for (int r = 0; r < rows; ++r) {
+      pieces[r] = run;
+      run += (int)((row[r].ends.len + kIndWave - 1) / kIndWave);
+    }
+    pieces[rows] = run;
+  }
+  __syncthreads();
+  for (int i = w, r = 0; i < pieces[rows]; i += kWaves) {
+    while (pieces[r + 1] <= i) ++r;
+    const IndJob j = row[r].ends;
+    uint32_t* __restrict__ map = maps + r * words;
+    const int64_t e_lo = (int64_t)(i - pieces[r]) * kIndWave, e_hi = e_lo + kIndWave < j.len ? e_lo + kIndWave : j.len;
+    for (int64_t e0 = e_lo; e0 < e_hi; e0 += 64 * kIndU) {
+      int32_t c[kIndU];
+      ind_entries(a.idx[row[r].side], a.lid, j.s, e0, e_hi, lane, c);
+#pragma unroll
+      for (int u = 0; u < kIndU; ++u)
+        if (c[u] >= 0) atomicOr(&map[c[u] >> 5], 1u << (c[u] & 31));
+    }
+  }
+  __syncthreads();
+  // the words of a wavefront are consecutive: 64 at a time, a word per lane
+  const int r = w / per_map, part = w % per_map;
+  const uint32_t* __restrict__ map = maps + r * words;
+  const int share = (words + 64 * per_map - 1) / (64 * per_map) * 64;
+  const int w0 = part * share, w1 = r < rows ? (w0 + share < words ? w0 + share : words) : 0;
+  uint32_t mine = 0;
+  for (int q = w0 + lane; q < w1; q += 64) mine += (uint32_t)__popc(map[q]);
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) mine += __shfl_xor(mine, o, 64);
+  if (lane == 0) wave_sum[w] = mine;
+  __syncthreads();
+  if (r < rows) {
+    int64_t at = row[r].first;
+    const float dk = a.dinv[row[r].k];
+    for (int q = r * per_map; q < w; ++q) at += wave_sum[q];
+    for (int q0 = w0; q0 < w1; q0 += 64) {
+      const int q = q0 + lane;
+      uint32_t bits = q < w1 ? map[q] : 0u;
+      uint32_t inc = (uint32_t)__popc(bits);
+      const uint32_t own = inc;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += x;
+      }
+      int64_t to = at + (inc - own);
+      for (; bits; bits &= bits - 1) ind_put(a, row[r].side, dk, to++, q * 32 + __ffs(bits) - 1);
+      at += __shfl(inc, 63, 64);
+    }
+  }
+  __syncthreads();
+}
+
+// MAPS: the rows that take a bitmap are done here too, else they are listed for k_ind_maps.
+template <int THREADS, bool MAPS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ind_fill(IndRows a) {
+  constexpr int kIndWaves = THREADS / 64, kIndJobs = THREADS / kIndLanes;
+  extern __shared__ __align__(16) int32_t ind_lds[];                     // staging, then the bitmaps
+  __shared__ int64_t offset[kIndJobs];                 // first entry of a row of the block
+  __shared__ uint32_t kept[kIndJobs];
+  __shared__ int wave_rows[kIndJobs], map_rows[kIndJobs];
+  __shared__ IndMapRow row[kIndWaves];
+  __shared__ int n_wave, n_map;
+  __shared__ IndJob ends[kIndJobs];
+  __shared__ uint64_t before[kIndWaves];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = threadIdx.x / kIndLanes, l = threadIdx.x % kIndLanes;
+  const int64_t blk = block_id();
+  if (blk >= a.sides * a.blocks) return;
+  const int side = blk >= a.blocks ? 1 : 0;
+  const int64_t k0 = (blk - side * a.blocks) * kIndJobs;
+  const uint32_t* __restrict__ cnt = a.cnt + side * a.cnt_ld;
+  if (threadIdx.x == 0) n_wave = n_map = 0;
+  {
+    uint64_t sum = 0;
+    static_assert(kIndJobs % 4 == 0, "whole requests before the first row");
+    if (!a.scanned)
+#pragma unroll 4
+      for (int64_t k = 4 * threadIdx.x; k < k0; k += 4 * THREADS) {
+        const uint4 x = *reinterpret_cast<const uint4*>(cnt + k);
+        sum += (uint64_t)x.x + x.y + x.z + x.w;
+      }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) before[w] = sum;
+  }
+  __syncthreads();
+  if (w == 0) {
+    const int64_t k = k0 + lane;
+    const bool mine = lane < kIndJobs && k < a.n_sub;
+    const uint32_t own = mine ? cnt[k] : 0u;
+    uint64_t inc = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint64_t x = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += x;
+    }
+    uint64_t base = 0;
+    if (a.scanned) base = (uint64_t)a.out_ptr[side][k0];
+    else
+      for (int i = 0; i < kIndWaves; ++i) base += before[i];
+    if (mine) {
+      kept[lane] = own;
+      offset[lane] = (int64_t)(base + inc - own);
+    }
+    if (!a.scanned && mine) {
+      a.out_ptr[side][k] = (int64_t)(base + inc - own);
+      if (k == a.n_sub - 1) a.out_ptr[side][a.n_sub] = (int64_t)(base + inc);
+    }
+  }
+  __syncthreads();
+  auto put = [&](float dk, int64_t at, int32_t v) { ind_put(a, side, dk, at, v); };
+  auto order = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  // the n numbers of a list, up to four a lane, to their places: as many of them are smaller (four a read; behind the list lies what is not)
+  auto rank = [&](const int32_t* __restrict__ list, int n, int me, auto lanes, float dk, int64_t first) {
+    constexpr int LANES = decltype(lanes)::value;
+    int32_t v[4];
+    int at[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = me + LANES * i < n ? list[me + LANES * i] : 0;
+    for (int q = 0; q < n; q += 4) {
+      const int4 x = *reinterpret_cast<const int4*>(list + q);
+      const int in = n - q;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        at[i] += (x.x < v[i] ? 1 : 0) + (in > 1 && x.y < v[i] ? 1 : 0) + (in > 2 && x.z < v[i] ? 1 : 0) + (in > 3 && x.w < v[i] ? 1 : 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (me + LANES * i < n) put(dk, first + at[i], v[i]);
+  };
+  {
+    const int64_t k = k0 + g;
+    const IndJob j = ind_job(a, side, k);
+    if (j.len > kIndShort) {
+      if (l == 0) {
+        ends[g] = j;
+        if (j.len <= kIndWave && kept[g] <= kIndRank) wave_rows[atomicAdd(&n_wave, 1)] = g;
+        else if constexpr (MAPS) map_rows[atomicAdd(&n_map, 1)] = g;
+        else a.map_list[blk % kIndSums * a.map_ld + atomicAdd(&a.map_count[blk % kIndSums], 1)] = side * a.n_sub + k;
+      }
+    } else if (j.len > 0) {
+      int32_t* stage = ind_lds + g * kIndShort;
+      int32_t c[kIndShort / kIndLanes];
+#pragma unroll
+      for (int u = 0; u < kIndShort / kIndLanes; ++u) {
+        const int e = u * kIndLanes + l;
+        c[u] = e < j.len ? a.idx[side][j.s + e] : -1;
+      }
+      const float dk = a.dinv[k];
+      int n = 0;
+#pragma unroll
+      for (int u = 0; u < kIndShort / kIndLanes; ++u) c[u] = c[u] >= 0 ? a.lid[c[u]] : -1;
+#pragma unroll
+      for (int u = 0; u < kIndShort / kIndLanes; ++u) {
+        const uint32_t some = (uint32_t)(__ballot(c[u] >= 0) >> (lane & ~(kIndLanes - 1))) & ((1u << kIndLanes) - 1u);
+        if (c[u] >= 0) stage[n + __popc(some & ((1u << l) - 1u))] = c[u];
+        n += __popc(some);
+      }
+      order();
+      rank(stage, n, l, std::integral_constant<int, kIndLanes>(), dk, offset[g]);
+    }
+  }
+  __syncthreads();
+  for (int i = w; i < n_wave; i += kIndWaves) {
+    const int at = wave_rows[i];
+    const IndJob j = ends[at];
+    int32_t* stage = ind_lds + w * kIndRank;
+    const float dk = a.dinv[k0 + at];
+    int n = 0;
+    for (int64_t e0 = 0; e0 < j.len; e0 += 64 * kIndU) {
+      int32_t c[kIndU];
+      ind_entries(a.idx[side], a.lid, j.s, e0, j.len, lane, c);
+#pragma unroll
+      for (int u = 0; u < kIndU; ++u) {
+        const uint64_t some = __ballot(c[u] >= 0);
+        const int to = n + __popcll(some & ((1ull << lane) - 1ull));
+        if (c[u] >= 0 && to < kIndRank) stage[to] = c[u];
+        n += __popcll(some);
+      }
+    }
+    n = n < kIndRank ? n : kIndRank;
+    order();
+    rank(stage, n, lane, std::integral_constant<int, 64>(), dk, offset[at]);
+    order();
+  }
+  if constexpr (MAPS) {
+    uint32_t* maps = reinterpret_cast<uint32_t*>(ind_lds) + ind_stage(THREADS) / sizeof(int32_t);
+    for (int i0 = 0; i0 < n_map; i0 += a.maps) {
+      const int rows = n_map - i0 < a.maps ? n_map - i0 : a.maps;
+      if (threadIdx.x < rows) {
+        const int at = map_rows[i0 + threadIdx.x];
+        row[threadIdx.x] = IndMapRow{ends[at], offset[at], k0 + at, side};
+      }
+      ind_maps<THREADS>(a, maps, row, rows);
+    }
+  }
+}
+
+// The rows left over by k_ind_fill<.., false>, whose bitmaps leave room for few blocks on a compute unit
+__global__ __launch_bounds__(kIndMany) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ind_maps(IndRows a) {
+  extern __shared__ __align__(16) int32_t ind_lds[];
+  __shared__ IndMapRow row[kIndMany / 64];
+  const int list = (int)blockIdx.x % kIndSums;
+  const int64_t total = a.map_count[list];
+  for (int64_t i0 = (int64_t)(blockIdx.x / kIndSums) * a.maps; i0 < total; i0 += (int64_t)(gridDim.x / kIndSums) * a.maps) {
+    const int rows = (int)(total - i0 < a.maps ? total - i0 : a.maps);
+    if (threadIdx.x < rows) {
+      const int64_t job = a.map_list[list * a.map_ld + i0 + threadIdx.x];
+      const int side = job >= a.n_sub ? 1 : 0;
+      const int64_t k = job - side * a.n_sub;
+      row[threadIdx.x] = IndMapRow{ind_job(a, side, k), a.out_ptr[side][k], k, side};
+    }
+    ind_maps<kIndMany>(a, reinterpret_cast<uint32_t*>(ind_lds), row, rows);
+  }
+}
+
+static int induced_by_rows(const gcn_csr_t* A, const int32_t* d_vertices, int64_t n_sub, int flags, hipStream_t s, gcn_csr* B) {
+  const int64_t n = A->nr;
+  const int sides = (flags & GCN_BUILD_CSC) ? 2 : 1;
+  CallScope sc(s);
+  DevBuf lid, cnt, dinv, words, tmp, rowptr, colptr, deg, halo_gid;
+  GCN_TRY(lid.alloc(sc, sizeof(int32_t) * (size_t)n));
+  GCN_TRY(cnt.alloc(sc, sizeof(uint32_t) * (size_t)(sides * round_up(n_sub, 4))));
+  GCN_TRY(dinv.alloc(sc, sizeof(float) * (size_t)n_sub));
+  GCN_TRY(words.alloc(sc, (1 + 2 * kIndSums) * sizeof(int64_t)));  // the flags; the number of entries, in parts; those of listed rows
+  GCN_TRY(rowptr.alloc(sc, sizeof(int64_t) * (size_t)(n_sub + 1)));
+  if (sides == 2) GCN_TRY(colptr.alloc(sc, sizeof(int64_t) * (size_t)(n_sub + 1)));
+  GCN_TRY(deg.alloc(sc, sizeof(int32_t) * (size_t)n_sub));
+  GCN_TRY(halo_gid.alloc(sc, sizeof(int32_t)));
+  PinnedPage page;
+  GCN_TRY(page.take(sc));
+  int64_t* read = page.words();
+  const int64_t map_bytes = (int64_t)sizeof(uint32_t) * ceil_div(n_sub, 32);
+  const bool few = n_sub <= kIndOwnOffsets;
+  int maps = (few ? kIndThreadsRows : kIndMany) / 64;
+  while (maps > 1 && maps * map_bytes > 32 * 1024) maps /= 2;
+  DevBuf map_list;
+  const int64_t blocks = ceil_div(n_sub, kIndThreadsRows / kIndLanes), map_ld = ceil_div(sides * blocks, kIndSums) * (kIndThreadsRows / kIndLanes);
+  if (!few) GCN_TRY(map_list.alloc(sc, sizeof(int64_t) * (size_t)(kIndSums * map_ld)));
+  IndRows a{d_vertices, n_sub, n, lid.as<int32_t>(), {A->rowptr, A->colptr}, {A->col, A->rowidx}, blocks, sides,
+            cnt.as<uint32_t>(), round_up(n_sub, 4), deg.as<int32_t>(), dinv.as<float>(), words.as<int>(), words.as<int64_t>() + 1,
+            {rowptr.as<int64_t>(), colptr.as<int64_t>()}, !few, {nullptr, nullptr}, {nullptr, nullptr}, maps, map_list.as<int64_t>(), map_ld,
+            (int*)(words.as<int64_t>() + 1 + kIndSums)};
+  const dim3 grid = fold_grid(sides * a.blocks);
+  k_ind_init<<<ind_grid(std::max<int64_t>(n, 2 * kIndSums)), kIndThreads, 0, s>>>(lid.as<int32_t>(), n, 0, a.bad, a.nnz, 2 * kIndSums);
+  k_ind_scatter<<<ind_grid(n_sub), kIndThreads, 0, s>>>(d_vertices, n_sub, n, lid.as<int32_t>(), a.bad);
+  k_ind_count<kIndThreadsRows><<<grid, kIndThreadsRows, 0, s>>>(a);
+  GCN_CHECK_LAUNCH();
+  GCN_HIP(hipMemcpyAsync(read, words.p, (1 + kIndSums) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  if (a.scanned) {
+    GCN_TRY(tmp.alloc(sc, scan_tmp_bytes(n_sub)));
+    for (int side = 0; side < sides; ++side) GCN_TRY(exclusive_scan_u32(a.cnt + side * a.cnt_ld, a.out_ptr[side], n_sub, tmp.p, s));
+  }
+  GCN_HIP(hipStreamSynchronize(s));
+  int64_t nnz = 0;
+  for (int i = 0; i < kIndSums; ++i) nnz += read[1 + i];
+  const int* h_bad = (const int*)read;
+  if (h_bad[0]) return fail(GCN_EINVAL, "gcn_csr_induced: a vertex id lies outside the graph");
+  if (h_bad[1]) return fail(GCN_EINVAL, "gcn_csr_induced: a vertex is listed twice");
+  if (nnz < n_sub) return fail(GCN_EHIP, "gcn_csr_induced: internal error (nnz %lld < rows %lld)", (long long)nnz, (long long)n_sub);
+
+  DevBuf col, val, rowidx, val_t, mid;
+  GCN_TRY(col.alloc(sc, sizeof(int32_t) * (size_t)nnz + kEntrySlack));
+  GCN_TRY(val.alloc(sc, sizeof(float) * (size_t)nnz + kEntrySlack));
+  if (sides == 2) {
+    GCN_TRY(rowidx.alloc(sc, sizeof(int32_t) * (size_t)nnz + kEntrySlack));
+    GCN_TRY(val_t.alloc(sc, sizeof(float) * (size_t)nnz + kEntrySlack));
+  }
+  a.out_idx[0] = col.as<int32_t>(); a.out_idx[1] = rowidx.as<int32_t>();
+  a.out_val[0] = val.as<float>(); a.out_val[1] = val_t.as<float>();
+  const size_t stage = ind_stage(kIndThreadsRows), map_lds = (size_t)(maps * map_bytes);
+  if (few) {
+    k_ind_fill<kIndThreadsRows, true><<<grid, kIndThreadsRows, stage + map_lds, s>>>(a);
+  } else {
+    k_ind_fill<kIndThreadsRows, false><<<grid, kIndThreadsRows, stage, s>>>(a);
+    GCN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_ind_maps), hipFuncAttributeMaxDynamicSharedMemorySize, (int)map_lds));
+    k_ind_maps<<<dim3(4 * kIndSums), kIndMany, map_lds, s>>>(a);
+  }
+  GCN_CHECK_LAUNCH();
+  HandleArrays h{n_sub, 0, n_sub, 0, nnz, &rowptr, &col, &val, &deg, &halo_gid, &colptr, &rowidx, &val_t, &mid};
+  return adopt_arrays(h, sc, page, B);
+}
+
+static int induced_by_keys(const gcn_csr_t* A, const int32_t* d_vertices, int64_t n_sub, int flags, hipStream_t s, gcn_csr* B) {
   const int64_t n = A->nr;
   CallScope sc(s);
   DevBuf lid, len, off, tmp;
@@ -135,7 +592,7 @@ static int induced_impl(const gcn_csr_t* A, const int32_t* d_vertices, int64_t n
   int64_t* read = page.words();
   int* bad = (int*)(off.as<int64_t>() + n_sub + 1);
   int64_t* cursor = off.as<int64_t>() + n_sub + 2;
-  k_ind_init<<<ind_grid(n), kIndThreads, 0, s>>>(lid.as<int32_t>(), n, n_sub, bad, cursor);
+  k_ind_init<<<ind_grid(n), kIndThreads, 0, s>>>(lid.as<int32_t>(), n, n_sub, bad, cursor, 1);
   k_ind_scatter<<<ind_grid(n_sub), kIndThreads, 0, s>>>(d_vertices, n_sub, n, lid.as<int32_t>(), bad);
   k_ind_rows<<<ind_grid(n_sub), kIndThreads, 0, s>>>(d_vertices, n_sub, n, lid.as<int32_t>(), A->rowptr, len.as<uint32_t>(), bad);
   GCN_CHECK_LAUNCH();
@@ -182,7 +639,14 @@ extern "C" int gcn_csr_induced(const gcn_csr_t* A, const int32_t* d_vertices, in
   gcn_csr* B = new (std::nothrow) gcn_csr();
   if (!B) return fail(GCN_ENOMEM, "gcn_csr_induced: host allocation failed");
   if (hipGetDevice(&B->device) != hipSuccess) { delete B; return fail(GCN_EHIP, "hipGetDevice failed"); }
-  const int rc = induced_impl(A, d_vertices, n_sub, flags, (hipStream_t)stream, B);
+  // Row by row, but from a parent without a column-major copy, for subgraphs whose vertices no bitmap in LDS holds, and where many rows take a
+  // bitmap of more than 16 KB: 500 K of 1 M vertices, R-MAT rows (one in 60 of 512 entries and more) 962 us by sorting keys, 1200 row by row;
+  // uniform rows 1816 and 1330.  131 K of 262 K, R-MAT 1013 and 874.
+  const int64_t long_rows = A->sched.class_begin[23] + A->sched.n_hub_rows + (A->colptr ? A->sched_t.class_begin[23] + A->sched_t.n_hub_rows : 0);
+  const bool by_rows = (A->colptr || !(flags & GCN_BUILD_CSC)) && n_sub <= kIndMaxSub && A->nnz + n_sub < 0xffffffffLL &&
+                       (n_sub <= 1 << 17 || long_rows * 200 <= A->nr);
+  const int rc = by_rows ? induced_by_rows(A, d_vertices, n_sub, flags, (hipStream_t)stream, B)
+                         : induced_by_keys(A, d_vertices, n_sub, flags, (hipStream_t)stream, B);
   if (rc != GCN_OK) { gcn_csr_free(B); return rc; }
   *out = B;
   return GCN_OK;

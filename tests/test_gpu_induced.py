@@ -180,3 +180,47 @@ def test_minibatch_training_on_a_directed_graph(gcn, dev):
         assert abs(a - b) <= 1e-5 * (1 + e) * abs(b), (e, a, b)
     for W, Wref in zip(Ws, Wo):
         assert np.max(np.abs(W.cpu().numpy() - Wref)) <= 1e-4
+
+
+@pytest.mark.parametrize("n_sub_all", [False, True])
+def test_induced_rows_of_every_length(gcn, dev, n_sub_all):
+    """Parent rows and what is kept of them at the bounds of the ways they are taken: 64 entries (16 lanes / a wavefront), 1024 (one piece /
+    several), 256 kept (ranked / marked in a bitmap); rows and columns of different lengths."""
+    lens = [0, 1, 62, 63, 64, 254, 255, 256, 257, 1022, 1023, 1024, 2048, 5000]
+    n = 12000
+    rng = np.random.default_rng(11)
+    rows = rng.permutation(n)[:6 * len(lens)]
+    src = np.concatenate([np.full(k, r) for r, k in zip(rows, 6 * lens)])
+    dst = np.concatenate([rng.permutation(n)[:k] for r, k in zip(rows, 6 * lens)])
+    back = rng.random(len(src)) < 0.5                                                  # half of them as columns
+    src, dst = np.where(back, dst, src), np.where(back, src, dst)
+    A = gcn.gcn_csr_build(dev_i32(src, dev), dev_i32(dst, dev), n)
+    V = rng.permutation(n) if n_sub_all else np.concatenate([rows, np.setdiff1d(rng.permutation(n)[:3000], rows)])
+    check_induced(gcn, dev, A, src, dst, n, V)
+
+
+@pytest.mark.parametrize("n_sub", [1, 15, 31, 32768, 32769, 70000])
+def test_induced_around_the_sizes_of_its_blocks(gcn, dev, n_sub):
+    """One block and less, and both sides of the line from which offsets are scanned and blocks are larger."""
+    n = 80000
+    rng = np.random.default_rng(n_sub)
+    src, dst = rng.integers(0, n, 400000), rng.integers(0, n, 400000)
+    hub = rng.integers(0, n, 30000)
+    src, dst = np.r_[src, hub, np.full(20000, 5)], np.r_[dst, np.full(30000, 7), hub[:20000]]
+    A = gcn.gcn_csr_build(dev_i32(src, dev), dev_i32(dst, dev), n)
+    check_induced(gcn, dev, A, src, dst, n, rng.permutation(n)[:n_sub])
+
+
+@pytest.mark.parametrize("parent_csc,csc", [(False, True), (False, False), (True, False)])
+def test_induced_with_and_without_column_major_arrays(gcn, dev, parent_csc, csc):
+    """A parent without them has its subgraphs sorted; a subgraph without them has its rows alone."""
+    n = 9000
+    rng = np.random.default_rng(5)
+    src, dst = rng.integers(0, n, 90000), rng.integers(0, n, 90000)
+    A = gcn.gcn_csr_build(dev_i32(src, dev), dev_i32(dst, dev), n, flags=gcn.BUILD_CSC if parent_csc else 0)
+    V = rng.permutation(n)[:4000]
+    og = oracle.graph_build(*oracle.induced_edges(src, dst, n, V), len(V))
+    arr = gcn.gcn_csr_induced(A, dev_i32(V, dev), flags=gcn.BUILD_CSC if csc else 0).arrays()
+    for name in NAMES if csc else NAMES[:3]:
+        assert np.array_equal(arr[name].cpu().numpy(), getattr(og, name)), name
+    assert np.array_equal(arr["val"].cpu().numpy().view(np.int32), og.val.view(np.int32))
