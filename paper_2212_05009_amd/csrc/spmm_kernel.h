@@ -419,17 +419,26 @@ __global__ __launch_bounds__(256) void k_spmm_hub_finish(SpmmK a) {
   if (f >= a.d) return;
   const int64_t row = a.hub_rows[h];
   const int64_t c_lo = a.hub_chunk_ptr[h], c_hi = a.hub_chunk_ptr[h + 1];
-  // chunk order, eight loads in flight at a time (a hub of a power-law graph has dozens of chunks)
+  // Chunk order.  A batch of requests is one round trip to memory, which is what bounds the launches on few rows of up to a hundred chunks:
+  // 32 at a time; what is left eight at a time, the last ones of the last batch the last chunk's again.  54 and 107 blocks, rows of up to 98
+  // chunks: eight at a time and the rest one by one 20.9 and 17.6 us, this way 12.4 and 10.1; 8.7 K blocks of shorter rows 22.7 and 19.5 (35 with
+  // batches of 32 alone).
   float v = 0.f;
   int64_t c = c_lo;
-  for (; c + 8 <= c_hi; c += 8) {
+  for (; c + 32 <= c_hi; c += 32) {
+    float p[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) p[u] = a.partial[(c + u) * a.d + f];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) v += p[u];
+  }
+  for (; c < c_hi; c += 8) {
     float p[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) p[u] = a.partial[(c + u) * a.d + f];
+    for (int u = 0; u < 8; ++u) p[u] = a.partial[(c + u < c_hi ? c + u : c_hi - 1) * a.d + f];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v += p[u];
+    for (int u = 0; u < 8; ++u) v = c + u < c_hi ? v + p[u] : v;
   }
-  for (; c < c_hi; ++c) v += a.partial[c * a.d + f];
   finish_element<T>(a, row, f, v);
 }
 
