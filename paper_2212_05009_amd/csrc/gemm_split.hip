@@ -53,6 +53,17 @@ __device__ __forceinline__ void split2(float lo, float hi, uint32_t (&p)[3]) {
     hi -= __uint_as_float(p[k] & 0xffff0000u);
   }
 }
+// Sums that are no finite number (a value beyond the bf16 range, an infinity, a NaN: inf = inf + NaN in parts), or below 2^-90 and not zero: a value
+// below 2^-110 has bits under the smallest bf16 number (2^-133), which its parts lack.
+struct RangeCheck {
+  uint32_t most = 0u, least = 0xffffffffu;             // least: of the sums that are not zero, less one
+  __device__ __forceinline__ void add(float v) {
+    const uint32_t b = __float_as_uint(v) & 0x7fffffffu;
+    most = b > most ? b : most;
+    least = b - 1u < least ? b - 1u : least;
+  }
+  __device__ __forceinline__ bool out() const { return most >= 0x7f800000u || least < ((127u - 90u) << 23) - 1u; }
+};
 __device__ __forceinline__ floatx4 mfma(const u32x4& w, const u32x4& x, floatx4 acc) {
   bf16x8 a, b;
   __builtin_memcpy(&a, &w, 16); __builtin_memcpy(&b, &x, 16);
@@ -273,16 +284,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
     }
     const int left = rows_left(tile);
-    // A sum that is no finite number: an operand or a product beyond the range, whose parts are not what they stand for (inf = inf + NaN).
-    // Those rows are multiplied again on the fp32 pipe.
-    float probe = 0.f;
+    // A sum out of the range in which the parts stand for their values: those rows are multiplied again on the fp32 pipe.
+    RangeCheck range;
 #pragma unroll
     for (int rt = 0; rt < kRT; ++rt)
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) probe = __builtin_fmaf(acc[rt][t][r], 0.f, probe);
-    if (__builtin_expect(__any(probe != probe), 0)) {
+        for (int r = 0; r < 4; ++r) range.add(acc[rt][t][r]);
+    if (__builtin_expect(__any(range.out()), 0)) {
       const RowsBuf ab = a_buf(tile);
       int ce = c, qe = q;
       asm volatile("" : "+v"(ce), "+v"(qe));
@@ -538,15 +548,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
     }
 
-    // A sum that is no finite number (see above): the rows of the split once more, on the fp32 pipe, by the first group
-    float probe = 0.f;
+    // A sum out of range (as above): the rows of the split once more, on the fp32 pipe
+    RangeCheck range;
 #pragma unroll
     for (int i = 0; i < TA; ++i)
 #pragma unroll
       for (int j = 0; j < TB; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) probe = __builtin_fmaf(acc[i][j][r], 0.f, probe);
-    const bool again = __syncthreads_or(probe != probe);
+        for (int r = 0; r < 16; ++r) range.add(acc[i][j][r]);
+    const bool again = __syncthreads_or(range.out());
     if (__builtin_expect(again, 0)) {
 #pragma unroll
       for (int i = 0; i < TA; ++i)
@@ -679,11 +689,11 @@ int tn_splits(int64_t Kd, int M, int N) {
 
 // Where the fp32 kernels take longer.  Measured, their time over this kernel's, rows of K elements to N columns:
 //   W in registers (N = 192, 256; gemm_nn_limits_blocks)   10 K rows 0.6-0.8, 20 K 0.9-1.3, 60 K 1.3-1.9, 300 K 1.3-1.8 (256 x 256 on
-//                   2.45 M rows 2.55 -> 1.95 ms, 100 x 256 1.44 -> 1.21): from 2^15 rows on;
+//                   2.45 M rows 2.56 -> 1.92 ms, 100 x 256 1.44 -> 1.21): from 2^15 rows on;
 //   W in LDS, whole k steps (K <= 128 or a multiple of it)  N <= 64 0.5-1.0, N = 72 .. 128 0.9-1.4, but nothing is gained in a training step
 //                   (the pipe's clock: 2^18 x 128 x 128 83 -> 69 us, what follows 14 us longer), N = 160 1.2-2.5: more than 128 columns;
 //   others (K = 160, 237, 300, 602, or W too large for LDS) N = 47 1.1-1.6, 64 1.2-1.8, 72-256 1.2-2.6, N <= 32 0.5-1.2 on up to
-//                   20 K rows, 1.0-1.5 from 60 K on (233 K rows 602 -> 128 421 -> 225 us, 722 K 505 -> 100 1175 -> 559).
+//                   20 K rows, 1.0-1.5 from 60 K on (233 K rows 602 -> 128 430 -> 236 us, 722 K 505 -> 100 1175 -> 585, 500 K 368 -> 173 967 -> 448).
 // Its error against 64 bits is a third of theirs: 128 columns of K = 128 / 602 terms of either sign 5.7e-8 / 9.6e-8 (2.0e-7 / 4.4e-7), positive
 // ones 4.2e-8 / 6.9e-8 (1.2e-7 / 2.6e-7).
 bool gemm_nn_split_ok(const void* A, int64_t lda, int64_t ldw, int64_t ldc, int64_t M, int N, int K, int dtype, const GemmEpilogue& epi) {

@@ -93,3 +93,25 @@ def test_infinities_nan_and_the_largest_numbers(gcn, dev, tuned, d_in, d_out):
         ok = ~(inf | nan)
         assert ok.any() and bool(((got.double() - ref).abs()[ok] <= 1e-5 * scale[ok]).all())
     case.A.free()
+
+
+# Operands (either of the two) so small that a part of theirs would lie below the smallest bf16 number, some of them below the smallest normal fp32
+# one: as on the fp32 pipe, to the rounding of numbers of that size.
+@pytest.mark.parametrize("small_x,small_w", [(1e-34, 1.0), (1e-36, 1e3), (1e-38, 1.0), (1.0, 1e-37), (1e-20, 1e-17)])
+def test_operands_near_the_smallest_number(gcn, dev, tuned, small_x, small_w):
+    import torch
+    rows, d_in, d_out = 2500, 100, 130
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(9)
+    X = torch.randn(rows, d_in, generator=gen, device=dev) * small_x
+    W = torch.randn(d_in, d_out, generator=gen, device=dev) * small_w
+    G = torch.randn(rows, d_out, generator=gen, device=dev) * small_w
+    tuned("GCN_GEMM_SPLIT", 2)
+    out, dW = torch.empty(rows, d_out, device=dev), torch.empty(d_in, d_out, device=dev)
+    gcn.gcn_dense_fwd(X, W, out)
+    case = rows_alone(gcn, dev, rows)
+    gcn.gcn_layer_bwd(case.A, X, W, G, dW, AH_saved=X)
+    for got, a, b in ((out, X.double(), W.double()), (dW, X.double().T, G.double())):
+        tiny = a.shape[1] * 2.0 ** -149                        # a rounding of each term to a multiple of the smallest number
+        assert bool(((got.double() - a @ b).abs() <= 1e-5 * (a.abs() @ b.abs()) + tiny).all())
+    case.A.free()
