@@ -724,7 +724,7 @@ int gemm_nn_split(const void* A, int64_t lda, const float* W, int64_t ldw, void*
 }
 
 // More than 64 columns on both sides, from 2 K rows on.  fp32 kernels / this one with the final sum, us: 2.5 K rows x 128 x 128 17.0 / 15.8,
-// 8 K x 602 x 200 47 / 46, 100 K x 300 x 256 251 / 148, 233 K x 602 x 128 532 / 307, 2^18 x 128 x 128 102 / 81, 722 K x 505 x 100
+// 8 K x 602 x 200 47 / 46, 100 K x 300 x 256 251 / 148, 233 K x 602 x 128 537 / 320, 2^18 x 128 x 128 104 / 83, 722 K x 505 x 100
 // 1115 / 680, 2.45 M x 100 x 256 1290 / 1130, x 256 x 256 2440 / 1910; but 333 x 77 x 91 11.7 / 14.9, 300 K x 128 x 64 78 / 89, x 602 x 16 243 / 323:
 // there the product waits for memory, and 32 rows in flight are too few.
 // Error against 64 bits 4.4e-7 for 1.7e-6 (256 x 256 over 2.45 M rows), 1.2e-7 for 5.8e-7 (128 x 128 over 2^18).
