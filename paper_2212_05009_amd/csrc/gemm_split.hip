@@ -692,6 +692,8 @@ int tn_splits(int64_t Kd, int M, int N) {
 //                   2.45 M rows 2.56 -> 1.92 ms, 100 x 256 1.44 -> 1.21): from 2^15 rows on;
 //   W in LDS, whole k steps (K <= 128 or a multiple of it)  N <= 64 0.5-1.0, N = 72 .. 128 0.9-1.4, but nothing is gained in a training step
 //                   (the pipe's clock: 2^18 x 128 x 128 83 -> 69 us, what follows 14 us longer), N = 160 1.2-2.5: more than 128 columns;
+//                   fewer rows: K = 61 to N = 256 on 16 K 19.1 / 20.0 us, 64 K 32.9 / 27.0, but with W transposed and a mask 20.4 / 28.8 on 16 K
+//                   (W is read and split once a launch, 8 us across its lines): from 2^17 rows on;
 //   others (K = 160, 237, 300, 602, or W too large for LDS) N = 47 1.1-1.6, 64 1.2-1.8, 72-256 1.2-2.6, N <= 32 0.5-1.2 on up to
 //                   20 K rows, 1.0-1.5 from 60 K on (233 K rows 602 -> 128 430 -> 236 us, 722 K 505 -> 100 1175 -> 585, 500 K 368 -> 173 967 -> 448).
 // Its error against 64 bits is a third of theirs: 128 columns of K = 128 / 602 terms of either sign 5.7e-8 / 9.6e-8 (2.0e-7 / 4.4e-7), positive
@@ -708,7 +710,7 @@ bool gemm_nn_split_ok(const void* A, int64_t lda, int64_t ldw, int64_t ldc, int6
   if (gemm_nn_limits_blocks(A, lda, M, N, K, dtype)) return M >= 1 << 15;
   const bool whole_steps = gemm_nn_direct_ok(N, K) && (K <= 128 || K % 128 == 0);
   if (!whole_steps) return N > 32 || M >= 1 << 16;
-  return N > 128 && K >= 48;
+  return N > 128 && K >= 48 && M >= 1 << 17;
 }
 
 int gemm_nn_split(const void* A, int64_t lda, const float* W, int64_t ldw, void* C, int64_t ldc, int64_t M, int N, int K,
