@@ -29,9 +29,12 @@ struct SplitArgs {
   int endC;                // nothing beyond column N of C and C2 may be written
 };
 
-// The six products of parts, the smallest first.  The matrix pipe aligns what it adds to the largest term and cuts off the rest: each step's sum
-// starts from zero and is added to the result by a rounded fp32 addition.  (Sums carried through the pipe over all steps: error of a
-// 256 x 256 gradient over 2.45 M rows 7.8e-6, 1.7e-6 on the fp32 pipe.)
+// The six products of parts, the smallest first.  The matrix pipe aligns what it adds to the largest term and cuts off the rest, downwards: each
+// step's sum starts from zero and is added to the result by a rounded fp32 addition.  (Sums carried through the pipe over all steps: error of a
+// 256 x 256 gradient over 2.45 M rows 7.8e-6, 1.7e-6 on the fp32 pipe.)  What is cut has the same sign everywhere, which no sum over
+// rows averages out: operands are taken with the other sign in every other step, and in rows of every other number of bits.  The product of 602
+// terms, summed over 512 rows as a sparse product sums it: 6.2e-7 off with one sign for all, 9.3e-8 with both, 4.4e-7 on the fp32 pipe; results
+// of a two-layer forward pass over neighbourhoods of 490: 7.4e-7, 6.5e-8 and 9e-8.
 __device__ constexpr int kTerm[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
 
 constexpr int kThreads = 512;
@@ -173,9 +176,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
   };
   const int tail = a.K - (32 * (steps - 1) + 8 * q);   // elements of the lane's part of the last step
-  // pair j of the values of row tile rt, of which `in` count
-  auto split_a = [&](const floatx4 (&v)[kRT][2], int rt, int j, int in, u32x4 (&x)[kRT][3]) {
-    const float lo = v[rt][j >> 1][2 * (j & 1)], hi = v[rt][j >> 1][2 * (j & 1) + 1];
+  // pair j of the values of row tile rt, of which `in` count, times `sign` in the first tile and -`sign` in the second
+  auto split_a = [&](const floatx4 (&v)[kRT][2], int rt, int j, int in, float sign, u32x4 (&x)[kRT][3]) {
+    const float by = rt & 1 ? -sign : sign;
+    const float lo = v[rt][j >> 1][2 * (j & 1)] * by, hi = v[rt][j >> 1][2 * (j & 1) + 1] * by;
     uint32_t u[3];
     split2(2 * j < in ? lo : 0.f, 2 * j + 1 < in ? hi : 0.f, u);
 #pragma unroll
@@ -190,6 +194,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   int64_t tile = gridDim.x % 8 == 0 ? (int64_t)(blockIdx.x / 8) * (8 * kWaves) + (w / kGroup) * (8 * kGroup) + (blockIdx.x % 8) * kGroup + w % kGroup
                                     : (int64_t)blockIdx.x * kWaves + w;
   const int64_t passes = (ntiles + stride - 1) / stride;
+  // The sign of a row in its first step: of an even number of bits of the row below 64, which a row keeps where the rows are handed over in
+  // parts (of whole 64).  The lane's tiles are all odd or all even (stride is a multiple of eight).
+  const float sign0 = (__popc(c) + (int)(tile & 1)) & 1 ? -1.f : 1.f;
   int64_t tile_l = tile;                               // of the step asked for last
   int step_l = 0;
   auto advance = [&] { if (++step_l == steps) { step_l = 0; tile_l += stride; } };
@@ -200,7 +207,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
   for (int rt = 0; rt < kRT; ++rt)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) split_a(raw, rt, j, steps == 1 ? tail : 8, x);
+    for (int j = 0; j < 4; ++j) split_a(raw, rt, j, steps == 1 ? tail : 8, sign0, x);
   advance();
 #pragma unroll
   for (int rt = 0; rt < kRT; ++rt) load_a(a_buf(tile_l), step_l, rt, raw[rt]);
@@ -211,8 +218,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int rt = 0; rt < kRT; ++rt)
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[rt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float sign = sign0;
     for (int s = 0; s < steps; ++s) {
       const int sn = s + 1 == steps ? 0 : s + 1;
+      const float sign_n = sn == 0 ? sign0 : -sign;
       const int in = sn == steps - 1 ? tail : 8;
       advance();
       const RowsBuf nb = a_buf(tile_l);
@@ -254,7 +263,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int u = g * kUnits / kGroups; u < (g + 1) * kUnits / kGroups; ++u) {
           if (u < kUnitsA) {
-            split_a(raw, u >> 2, u & 3, in, xn);
+            split_a(raw, u >> 2, u & 3, in, sign_n, xn);
             if ((u & 3) == 3) load_a(nb, step_l, u >> 2, raw[u >> 2]);
           } else {
             const int i = (u - kUnitsA) >> 2;
@@ -269,7 +278,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int t = 0; t < TB; ++t)
 #pragma unroll
           for (int rt = 0; rt < kRT; ++rt) {
-            acc[rt][g * TB + t] += sum[rt][t];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[rt][g * TB + t][r] = __builtin_fmaf(sum[rt][t][r], rt & 1 ? -sign : sign, acc[rt][g * TB + t][r]);
             asm volatile("" : "+v"(acc[rt][g * TB + t]));      // (here, not behind the loop)
           }
         __builtin_amdgcn_sched_barrier(0);
@@ -278,6 +288,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int rt = 0; rt < kRT; ++rt)
 #pragma unroll
         for (int k = 0; k < 3; ++k) x[rt][k] = xn[rt][k];
+      sign = sign_n;
       if constexpr (!RES) {
         lds_barrier();
         cur ^= 1;

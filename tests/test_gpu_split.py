@@ -67,6 +67,43 @@ def test_no_less_exact_than_the_fp32_pipe(gcn, dev, tuned, kind, rows, d_in, d_o
     case.A.free()
 
 
+# Errors that are small each but of one sign are not small in a sum over rows (what a sparse product forms of H W) or over columns (what the next
+# dense product forms): no larger there either than on the fp32 pipe.
+@pytest.mark.parametrize("kind", ["signed", "relu", "positive"])
+@pytest.mark.parametrize("d_in,d_out", [(48, 130), (100, 173), (602, 128), (256, 256)])
+def test_errors_average_out_in_sums(gcn, dev, tuned, kind, d_in, d_out):
+    import torch
+    rows = 512 * 128
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d_in + d_out)
+    X = torch.randn(rows, d_in, generator=gen, device=dev)
+    W = torch.randn(d_in, d_out, generator=gen, device=dev)
+    G = torch.randn(rows, d_out, generator=gen, device=dev)
+    if kind != "signed":
+        X.clamp_(min=0)
+    if kind == "positive":
+        W.abs_()
+    some = torch.randperm(rows, generator=gen, device=dev)
+    sums = {"neighbours": lambda t: t.view(-1, 512, d_out).sum(1), "any rows": lambda t: t[some].view(-1, 512, d_out).sum(1),
+            "every fourth": lambda t: t.view(-1, 4, d_out)[:, 0].reshape(-1, 128, d_out).sum(1)}
+    case = rows_alone(gcn, dev, rows)
+    err = {}
+    for mode in (0, 2):
+        tuned("GCN_GEMM_SPLIT", mode)
+        out, dW = torch.empty(rows, d_out, device=dev), torch.empty(d_in, d_out, device=dev)
+        gcn.gcn_dense_fwd(X, W, out)
+        gcn.gcn_layer_bwd(case.A, X, W, G, dW, AH_saved=X)
+        ref, ref_w = X.double() @ W.double(), X.double().T @ G.double()
+        err[mode] = {k: error(f(out.double()), f(ref)) for k, f in sums.items()}
+        if kind != "positive":             # (there both have the rounding of the sum over the workgroups' parts, 4e-9, and nothing else)
+            err[mode]["gradient's rows"] = error(dW.double().sum(0), ref_w.sum(0))
+            err[mode]["gradient's columns"] = error(dW.double().sum(1), ref_w.sum(1))
+    print(kind, d_in, d_out, err, flush=True)
+    for k in err[0]:
+        assert err[2][k] <= err[0][k], k
+    case.A.free()
+
+
 # Values beyond the range of their first part: the rows (for a gradient, the workgroups' ranges of rows) that hold one are multiplied on the fp32
 # pipe.  Infinities and NaN come out where 64 bits have them; a product next to the largest number as it is.
 @pytest.mark.parametrize("d_in,d_out", [(100, 173), (256, 256), (130, 64)])
