@@ -3,8 +3,8 @@
 //
 // An fp32 value is the exact sum of three bf16 values: its rounding, the rounding of what is left (2^-9 of it at most), and of what is
 // then left (2^-18; 24 bits of significand are 3 x 8).  A product of two values is nine products, of which the six of weight 2^-18 and
-// more are formed, each exact in fp32, and added by the matrix pipe in fp32: what is left out is 2^-26 of the product, a
-// quarter of one fp32 rounding.  Six bf16 operations at sixteen times the fp32 rate: the products are then bound by memory.
+// more are formed, each exact in fp32, and added by the matrix pipe in fp32: what is left out is up to 2^-24 of the product, 2^-27 as a
+// rule (a rounding: up to 2^-24, 2^-25 as a rule).  Six bf16 operations at sixteen times the fp32 rate: the products are then bound by memory.
 #include <algorithm>
 #include <type_traits>
 
@@ -31,7 +31,9 @@ struct SplitArgs {
 
 // The six products of parts, the smallest first.  The matrix pipe aligns what it adds to the largest term and cuts off the rest, downwards: each
 // step's sum starts from zero and is added to the result by a rounded fp32 addition.  (Sums carried through the pipe over all steps: error of a
-// 256 x 256 gradient over 2.45 M rows 7.8e-6, 1.7e-6 on the fp32 pipe.)  What is cut has the same sign everywhere, which no sum over
+// 256 x 256 gradient over 2.45 M rows 7.8e-6, 1.7e-6 on the fp32 pipe.)  The first parts' products are added by themselves, and to the others by
+// another rounded addition, or the pipe would cut the last bits of sums of few terms: one nonzero term of K 3.5e-8, this way 2.6e-8, as on the
+// fp32 pipe (2.5e-8); two to eight of 602 3.7e-8 .. 5.7e-8 for 3.1e-8 .. 5.4e-8, more terms less than there.  What is cut has the same sign everywhere, which no sum over
 // rows averages out: operands are taken with the other sign in every other step, and in rows of every other number of bits.  The product of 602
 // terms, summed over 512 rows as a sparse product sums it: 6.2e-7 off with one sign for all, 9.3e-8 with both, 4.4e-7 on the fp32 pipe; results
 // of a two-layer forward pass over neighbourhoods of 490: 7.4e-7, 6.5e-8 and 9e-8.
@@ -252,14 +254,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             for (int k = 0; k < 3; ++k) wn[t][k] = wl[(((g + 1) * TB + t) * 3 + k) * 64];
         }
         __builtin_amdgcn_sched_barrier(0);
-        floatx4 sum[kRT][TB];
+        floatx4 low[kRT][TB], high[kRT][TB];
 #pragma unroll
         for (int m = 0; m < 6; ++m)
 #pragma unroll
           for (int t = 0; t < TB; ++t)
 #pragma unroll
-            for (int rt = 0; rt < kRT; ++rt)
-              sum[rt][t] = mfma(wf[t][kTerm[m][0]], x[rt][kTerm[m][1]], m ? sum[rt][t] : floatx4{0.f, 0.f, 0.f, 0.f});
+            for (int rt = 0; rt < kRT; ++rt) {
+              const floatx4 none{0.f, 0.f, 0.f, 0.f};
+              if (m < 5) low[rt][t] = mfma(wf[t][kTerm[m][0]], x[rt][kTerm[m][1]], m ? low[rt][t] : none);
+              else high[rt][t] = mfma(wf[t][0], x[rt][0], none);
+            }
 #pragma unroll
         for (int u = g * kUnits / kGroups; u < (g + 1) * kUnits / kGroups; ++u) {
           if (u < kUnitsA) {
@@ -278,8 +283,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int t = 0; t < TB; ++t)
 #pragma unroll
           for (int rt = 0; rt < kRT; ++rt) {
+            const floatx4 sum = high[rt][t] + low[rt][t];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[rt][g * TB + t][r] = __builtin_fmaf(sum[rt][t][r], rt & 1 ? -sign : sign, acc[rt][g * TB + t][r]);
+            for (int r = 0; r < 4; ++r) acc[rt][g * TB + t][r] = __builtin_fmaf(sum[r], rt & 1 ? -sign : sign, acc[rt][g * TB + t][r]);
             asm volatile("" : "+v"(acc[rt][g * TB + t]));      // (here, not behind the loop)
           }
         __builtin_amdgcn_sched_barrier(0);
@@ -520,27 +526,26 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
           for (int p = 0; p < 3; ++p) an[p] = la[((i + 1) * 3 + p) * 64];
         }
-        __builtin_amdgcn_sched_barrier(0);
-        floatx16 sum[TB];
-#pragma unroll
-        for (int j = 0; j < TB; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sum[j][r] = 0.f;
-#pragma unroll
-        for (int m = 0; m < 6; ++m)
-#pragma unroll
-          for (int j = 0; j < TB; ++j) sum[j] = mfma32(af[kTerm[m][0]], bf[j][kTerm[m][1]], sum[j]);
-#pragma unroll
-        for (int u = i * kWork / TA; u < (i + 1) * kWork / TA; ++u) {
-          const int un = u >> 3, e = (u >> 2) & 1;
-          convert(raw[D == 1 ? 0 : P ^ 1], un, e, u & 3, -sign);
-          if ((u & 3) == 3) place(other, un, e);
-          if ((u & 7) == 7) load(k + (D + 1) * kRows, un, raw[D == 1 ? 0 : P ^ 1]);
-        }
 #pragma unroll
         for (int j = 0; j < TB; ++j) {
+          __builtin_amdgcn_sched_barrier(0);
+          floatx16 low, high;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = __builtin_fmaf(sum[j][r], sign, acc[i][j][r]);
+          for (int r = 0; r < 16; ++r) low[r] = high[r] = 0.f;
+#pragma unroll
+          for (int m = 0; m < 5; ++m) {
+            if (m == 1) high = mfma32(af[0], bf[j][0], high);
+            low = mfma32(af[kTerm[m][0]], bf[j][kTerm[m][1]], low);
+          }
+#pragma unroll
+          for (int u = (i * TB + j) * kWork / (TA * TB); u < (i * TB + j + 1) * kWork / (TA * TB); ++u) {
+            const int un = u >> 3, e = (u >> 2) & 1;
+            convert(raw[D == 1 ? 0 : P ^ 1], un, e, u & 3, -sign);
+            if ((u & 3) == 3) place(other, un, e);
+            if ((u & 7) == 7) load(k + (D + 1) * kRows, un, raw[D == 1 ? 0 : P ^ 1]);
+          }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = __builtin_fmaf(high[r] + low[r], sign, acc[i][j][r]);
           asm volatile("" : "+v"(acc[i][j]));          // (here, not behind the loop)
         }
         __builtin_amdgcn_sched_barrier(0);

@@ -67,6 +67,37 @@ def test_no_less_exact_than_the_fp32_pipe(gcn, dev, tuned, kind, rows, d_in, d_o
     case.A.free()
 
 
+# Rows (for a gradient, columns) of few terms, the others zero.  The six products of a term lack 2^-27 of it as a rule, a quarter of a rounding
+# (in the 2-norm sqrt(1 + 1/16) of one: 1.04 with its spread), and a step's sum is rounded before it is added: with two to eight terms one
+# rounding more for each but the first, of a part of the sum (at most sqrt(2) of the fp32 pipe's, where all roundings are as large).
+@pytest.mark.parametrize("terms,bound", [(1, 1.04), (2, 1.42), (3, 1.42), (8, 1.42), (32, 1.0)])
+@pytest.mark.parametrize("d_in,d_out", [(100, 130), (602, 128), (256, 256)])
+def test_sums_of_few_terms(gcn, dev, tuned, terms, bound, d_in, d_out):
+    import torch
+    rows = 8192
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(terms + d_in)
+    X = torch.randn(rows, d_in, generator=gen, device=dev)
+    W = torch.randn(d_in, d_out, generator=gen, device=dev)
+    G = torch.randn(rows, d_out, generator=gen, device=dev)
+    place = torch.rand(rows, d_in, generator=gen, device=dev)
+    by_row = torch.where(place.argsort(1).argsort(1) < terms, X, torch.zeros_like(X))
+    by_col = torch.where(place.argsort(0).argsort(0) < terms, X, torch.zeros_like(X))
+    case = rows_alone(gcn, dev, rows)
+    err = {}
+    for mode in (0, 2):
+        tuned("GCN_GEMM_SPLIT", mode)
+        out, dW = torch.empty(rows, d_out, device=dev), torch.empty(d_in, d_out, device=dev)
+        gcn.gcn_dense_fwd(by_row, W, out)
+        gcn.gcn_layer_bwd(case.A, by_col, W, G, dW, AH_saved=by_col)
+        err[mode] = (error(out, by_row.double() @ W.double()), error(dW, by_col.double().T @ G.double()))
+    print(terms, d_in, d_out, err, flush=True)
+    assert err[2][0] <= bound * err[0][0]
+    # (a gradient's terms lie in the parts of different workgroups: few terms each)
+    assert err[2][1] <= (1.04 if terms == 1 else 1.42) * err[0][1]
+    case.A.free()
+
+
 # Errors that are small each but of one sign are not small in a sum over rows (what a sparse product forms of H W) or over columns (what the next
 # dense product forms): no larger there either than on the fp32 pipe.
 @pytest.mark.parametrize("kind", ["signed", "relu", "positive"])
