@@ -342,15 +342,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       // (neither the places of the results nor the bias are worth registers over the products)
       int ce = c, qe = q;
       asm volatile("" : "+v"(ce), "+v"(qe) : : "memory");
-      const RowsBuf cb = rows_buf<float>(a.C + n0, row0, a.ldc, here);
+      const int cend = a.endC ? a.N : (a.N + 3) & ~3;  // where the last row may be written to
+      const RowsBuf cb = rows_part<float>(a.C, row0, a.ldc, here, n0, cend);
       RowsBuf cb2 = cb;
-      if constexpr (SAVE) cb2 = rows_buf<float>(a.C2 + n0, row0, a.ldc2, here);
+      if constexpr (SAVE) cb2 = rows_part<float>(a.C2, row0, a.ldc2, here, n0, cend);
       floatx4 keep[MASK ? NT : 1];
       const bool free_row = MASK && row0 + ce >= a.mask_rows;
       if constexpr (MASK) {
         const int64_t masked = a.mask_rows - row0;
         const int mrows = masked < here ? (masked > 0 ? (int)masked : 0) : here;
-        const RowsBuf mb = rows_buf<float>(a.mask + n0, row0, a.ldmask, mrows);
+        const RowsBuf mb = rows_part<float>(a.mask, row0, a.ldmask, mrows, n0, a.N);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           const auto v = __builtin_amdgcn_raw_buffer_load_b128(mb, (ce * (int)a.ldmask + 16 * t + 4 * qe) * 4, 0, 0);
