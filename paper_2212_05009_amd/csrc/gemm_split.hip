@@ -1,8 +1,8 @@
 // C[M x N] = A[M x K] W[K x N] of fp32 operands on the bf16 matrix pipe (Sec. 3.1: the dense product with W^k), for products whose
 // arithmetic takes longer than their bytes on the fp32 pipe.
 //
-// An fp32 value is the exact sum of three bf16 values: its rounding, the rounding of what is left (2^-9 of it at most), and of what is
-// then left (2^-18; 24 bits of significand are 3 x 8).  A product of two values is nine products, of which the six of weight 2^-18 and
+// An fp32 value from 2^-108 on is the exact sum of three bf16 values: its rounding, the rounding of what is left (2^-8 of it at most), and of
+// what is then left (2^-17; 24 bits of significand are 3 x 8).  Products with smaller operands are formed on the fp32 pipe.  A product of two values is nine products, of which the six of weight 2^-18 and
 // more are formed, each exact in fp32, and added by the matrix pipe in fp32: what is left out is up to 2^-24 of the product, 2^-27 as a
 // rule (a rounding: up to 2^-24, 2^-25 as a rule).  Six bf16 operations at sixteen times the fp32 rate: the products are then bound by memory.
 #include <algorithm>
@@ -58,8 +58,8 @@ __device__ __forceinline__ void split2(float lo, float hi, uint32_t (&p)[3]) {
     hi -= __uint_as_float(p[k] & 0xffff0000u);
   }
 }
-// Sums that are no finite number (a value beyond the bf16 range, an infinity, a NaN: inf = inf + NaN in parts), or below 2^-90 and not zero: a value
-// below 2^-110 has bits under the smallest bf16 number (2^-133), which its parts lack.
+// Sums that are no finite number (a value beyond the bf16 range, an infinity, a NaN: inf = inf + NaN in parts), or below 2^-90 and not zero: products of
+// parts may lie under the smallest fp32 number.
 struct RangeCheck {
   uint32_t most = 0u, least = 0xffffffffu;             // least: of the sums that are not zero, less one
   __device__ __forceinline__ void add(float v) {
@@ -68,6 +68,18 @@ struct RangeCheck {
     least = b - 1u < least ? b - 1u : least;
   }
   __device__ __forceinline__ bool out() const { return most >= 0x7f800000u || least < ((127u - 90u) << 23) - 1u; }
+};
+// The least magnitude of operands that are not zero.  The last part of one below 2^-108 may have bits under the smallest bf16 number (2^-133); what a
+// sum looks like says nothing about it, the other operand may be large.  Three integer operations for two values: 602 -> 128 on 233 K rows 256 ->
+// 278 us, 256 -> 256 on 2.45 M 2.03 -> 2.10 ms, A^T B 602 x 128 344 -> 350 us.
+struct LeastOperand {
+  uint32_t least = 0xffffffffu;                        // twice the bits, less one: zero is the largest
+  __device__ __forceinline__ void add(float lo, float hi) {
+    const uint32_t a = 2u * __float_as_uint(lo) - 1u, b = 2u * __float_as_uint(hi) - 1u;
+    const uint32_t c = a < b ? a : b;
+    least = c < least ? c : least;
+  }
+  __device__ __forceinline__ bool out() const { return least < 2u * ((127u - 108u) << 23) - 1u; }
 };
 __device__ __forceinline__ floatx4 mfma(const u32x4& w, const u32x4& x, floatx4 acc) {
   bf16x8 a, b;
@@ -127,14 +139,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int j = 0; j < 8; ++j) v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wb, at + 4 * j * ldw, 0, 0));
     }
   };
-  // pair j of its values, in three parts
-  auto split_w = [&](int s, int i, int j, const float (&v)[8], u32x4 (&o)[3]) {
-    float lo = v[2 * j], hi = v[2 * j + 1];
+  // pair j of its values
+  auto pair_w = [&](int s, int i, int j, const float (&v)[8], float& lo, float& hi) {
+    lo = v[2 * j];
+    hi = v[2 * j + 1];
     if (TRANS) {                                       // (behind K lies the row after it)
       const int in = a.K - 32 * s - 8 * (((((int)threadIdx.x + i * kThreads) % (NT * 64)) >> 4) & 3) - 2 * j;
       lo = in > 0 ? lo : 0.f;
       hi = in > 1 ? hi : 0.f;
     }
+  };
+  // in three parts
+  auto split_w = [&](int s, int i, int j, const float (&v)[8], u32x4 (&o)[3]) {
+    float lo, hi;
+    pair_w(s, i, j, v, lo, hi);
     uint32_t u[3];
     split2(lo, hi, u);
 #pragma unroll
@@ -145,19 +163,35 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int k = 0; k < 3; ++k) at[((p >> 6) * 3 + k) * 64 + (p & 63)] = o[k];
   };
-  for (int s = 0; s < (RES ? steps : 1); ++s) {
-    float v[kPieces][8];
+  // All of W is looked at, also where only its first step is placed; four steps at a time (one after the other: 11 us at K = 602).
+  LeastOperand least_w;
+  constexpr int kAhead = 4;
+  for (int s0 = 0; s0 < steps; s0 += kAhead) {
+    float v[kAhead][kPieces][8];
 #pragma unroll
-    for (int i = 0; i < kPieces; ++i) load_w(s, i, v[i]);
+    for (int h = 0; h < kAhead; ++h)
 #pragma unroll
-    for (int i = 0; i < kPieces; ++i) {
-      u32x4 o[3];
+      for (int i = 0; i < kPieces; ++i) load_w(s0 + h < steps ? s0 + h : steps - 1, i, v[h][i]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) split_w(s, i, j, v[i], o);
-      place_w(split_lds + s * kStep, i, o);
-    }
+    for (int h = 0; h < kAhead; ++h)
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i) {
+        const int s = s0 + h;
+        if (s >= steps) continue;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float lo, hi;
+          pair_w(s, i, j, v[h][i], lo, hi);
+          least_w.add(lo, hi);
+        }
+        if (!RES && s > 0) continue;
+        u32x4 o[3];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) split_w(s, i, j, v[h][i], o);
+        place_w(split_lds + s * kStep, i, o);
+      }
   }
-  __syncthreads();
+  const bool w_out = __syncthreads_or(least_w.out());
 
   const int64_t ntiles = (a.M + 16 * kRT - 1) / (16 * kRT);
   const int64_t stride = (int64_t)gridDim.x * kWaves;
@@ -179,11 +213,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   };
   const int tail = a.K - (32 * (steps - 1) + 8 * q);   // elements of the lane's part of the last step
   // pair j of the values of row tile rt, of which `in` count, times `sign` in the first tile and -`sign` in the second
-  auto split_a = [&](const floatx4 (&v)[kRT][2], int rt, int j, int in, float sign, u32x4 (&x)[kRT][3]) {
+  auto split_a = [&](const floatx4 (&v)[kRT][2], int rt, int j, int in, float sign, u32x4 (&x)[kRT][3], LeastOperand& least) {
     const float by = rt & 1 ? -sign : sign;
-    const float lo = v[rt][j >> 1][2 * (j & 1)] * by, hi = v[rt][j >> 1][2 * (j & 1) + 1] * by;
+    float lo = v[rt][j >> 1][2 * (j & 1)], hi = v[rt][j >> 1][2 * (j & 1) + 1];
+    lo = 2 * j < in ? lo : 0.f;
+    hi = 2 * j + 1 < in ? hi : 0.f;
+    least.add(lo, hi);
     uint32_t u[3];
-    split2(2 * j < in ? lo : 0.f, 2 * j + 1 < in ? hi : 0.f, u);
+    split2(lo * by, hi * by, u);
 #pragma unroll
     for (int k = 0; k < 3; ++k) x[rt][k][j] = u[k];
   };
@@ -204,22 +241,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   auto advance = [&] { if (++step_l == steps) { step_l = 0; tile_l += stride; } };
   floatx4 raw[kRT][2];
   u32x4 x[kRT][3];
+  LeastOperand first;                                  // of the first step of a pass
 #pragma unroll
   for (int rt = 0; rt < kRT; ++rt) load_a(a_buf(tile), 0, rt, raw[rt]);
 #pragma unroll
   for (int rt = 0; rt < kRT; ++rt)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) split_a(raw, rt, j, steps == 1 ? tail : 8, sign0, x);
+    for (int j = 0; j < 4; ++j) split_a(raw, rt, j, steps == 1 ? tail : 8, sign0, x, first);
   advance();
 #pragma unroll
   for (int rt = 0; rt < kRT; ++rt) load_a(a_buf(tile_l), step_l, rt, raw[rt]);
   int cur = 0;
+  bool first_out = __any(first.out());
   for (int64_t pass = 0; pass < passes; ++pass, tile += stride) {
     floatx4 acc[kRT][NT];
 #pragma unroll
     for (int rt = 0; rt < kRT; ++rt)
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[rt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    bool again = w_out || first_out;
     float sign = sign0;
     for (int s = 0; s < steps; ++s) {
       const int sn = s + 1 == steps ? 0 : s + 1;
@@ -230,6 +270,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       float wv[8];
       if constexpr (!RES) load_w(sn, 0, wv);
       u32x4 xn[kRT][3], wo[3];
+      LeastOperand least;
       const u32x4* __restrict__ wl = split_lds + (RES ? s : cur) * kStep + lane;
       constexpr int TB = NT > 8 ? 1 : 2;
       constexpr int kGroups = NT / TB;
@@ -268,7 +309,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int u = g * kUnits / kGroups; u < (g + 1) * kUnits / kGroups; ++u) {
           if (u < kUnitsA) {
-            split_a(raw, u >> 2, u & 3, in, sign_n, xn);
+            split_a(raw, u >> 2, u & 3, in, sign_n, xn, least);
             if ((u & 3) == 3) load_a(nb, step_l, u >> 2, raw[u >> 2]);
           } else {
             const int i = (u - kUnitsA) >> 2;
@@ -295,13 +336,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int k = 0; k < 3; ++k) x[rt][k] = xn[rt][k];
       sign = sign_n;
+      const bool out = __any(least.out());
+      if (sn != 0) again = again || out;
+      else first_out = out;
       if constexpr (!RES) {
         lds_barrier();
         cur ^= 1;
       }
     }
     const int left = rows_left(tile);
-    // A sum out of the range in which the parts stand for their values: those rows are multiplied again on the fp32 pipe.
+    // An operand or a sum out of the range in which the parts stand for their values: those rows are multiplied again on the fp32 pipe.
     RangeCheck range;
 #pragma unroll
     for (int rt = 0; rt < kRT; ++rt)
@@ -309,7 +353,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) range.add(acc[rt][t][r]);
-    if (__builtin_expect(__any(range.out()), 0)) {
+    const bool sums_out = __any(range.out());
+    if (__builtin_expect((int)again | (int)sums_out, 0)) {       // (one branch: two ways into it cost 50 registers)
       const RowsBuf ab = a_buf(tile);
       int ce = c, qe = q;
       asm volatile("" : "+v"(ce), "+v"(qe));
@@ -466,10 +511,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
     };
     // rows 2 j, 2 j + 1 of component e of unit i, those of A times `sign`, in three parts
+    LeastOperand least;
     u32x4 part[3];
     auto convert = [&](const floatx2w (&raw)[kUnits][8], int i, int e, int j, float sign) {
       uint32_t o[3];
       const float by = of_b[i] ? 1.f : sign;
+      least.add(raw[i][2 * j][e], raw[i][2 * j + 1][e]);
       split2(raw[i][2 * j][e] * by, raw[i][2 * j + 1][e] * by, o);
 #pragma unroll
       for (int k = 0; k < 3; ++k) part[k][j] = o[k];
@@ -565,7 +612,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
     }
 
-    // A sum out of range (as above): the rows of the split once more, on the fp32 pipe
+    // An operand or a sum out of range (as above): the rows of the split once more, on the fp32 pipe
     RangeCheck range;
 #pragma unroll
     for (int i = 0; i < TA; ++i)
@@ -573,7 +620,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int j = 0; j < TB; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) range.add(acc[i][j][r]);
-    const bool again = __syncthreads_or(range.out());
+    const bool again = __syncthreads_or(range.out() || least.out());
     if (__builtin_expect(again, 0)) {
 #pragma unroll
       for (int i = 0; i < TA; ++i)

@@ -164,8 +164,11 @@ def test_infinities_nan_and_the_largest_numbers(gcn, dev, tuned, d_in, d_out):
 
 
 # Operands (either of the two) so small that a part of theirs would lie below the smallest bf16 number, some of them below the smallest normal fp32
-# one: as on the fp32 pipe, to the rounding of numbers of that size.
-@pytest.mark.parametrize("small_x,small_w", [(1e-34, 1.0), (1e-36, 1e3), (1e-38, 1.0), (1.0, 1e-37), (1e-20, 1e-17)])
+# one: as on the fp32 pipe, to the rounding of numbers of that size.  Beside a large operand their sums are ordinary numbers; 1e-41 has no bf16 part
+# at all; 2^-107 is the least with all of its parts.
+@pytest.mark.parametrize("small_x,small_w", [(1e-34, 1.0), (1e-36, 1e3), (1e-38, 1.0), (1.0, 1e-37), (1e-20, 1e-17), (2.0**-120, 2.0**40), (2.0**40, 2.0**-120),
+                                             (2.0**-137, 2.0**60), (2.0**60, 2.0**-137), (1e-38, 1e12), (1e12, 1e-38), (1e-41, 1e30), (1e30, 1e-41),
+                                             (1e-41, 1.0), (1.0, 1e-41), (2.0**-107, 2.0**80), (2.0**80, 2.0**-107), (2.0**-70, 2.0**-70)])
 def test_operands_near_the_smallest_number(gcn, dev, tuned, small_x, small_w):
     import torch
     rows, d_in, d_out = 2500, 100, 130
@@ -182,4 +185,35 @@ def test_operands_near_the_smallest_number(gcn, dev, tuned, small_x, small_w):
     for got, a, b in ((out, X.double(), W.double()), (dW, X.double().T, G.double())):
         tiny = a.shape[1] * 2.0 ** -149                        # a rounding of each term to a multiple of the smallest number
         assert bool(((got.double() - a @ b).abs() <= 1e-5 * (a.abs() @ b.abs()) + tiny).all())
+    case.A.free()
+
+
+# One such operand among ordinary ones: in every place of the row tiles, steps and passes of H W, and of the chunks and workgroups of A^T B; and in W.
+@pytest.mark.parametrize("d_in,d_out", [(100, 130), (602, 65), (256, 256)])
+def test_one_small_operand_among_ordinary_ones(gcn, dev, tuned, d_in, d_out):
+    import torch
+    rows = 70001                                               # more than one pass over them
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d_in)
+    X = torch.randn(rows, d_in, generator=gen, device=dev)
+    W = torch.randn(d_in, d_out, generator=gen, device=dev)
+    G = torch.randn(rows, d_out, generator=gen, device=dev)
+    at = [(0, 0), (31, d_in - 1), (32, 33), (255, 64), (256, 1), (20000, 31), (65535, 32), (65536, 5), (65541, d_in - 2), (69999, 2), (70000, d_in - 3)]
+    for r, k in at + [(17, 40)]:                               # a row and a column for each, empty but for it, and its partner large
+        X[r], X[:, k] = 0, 0
+    for r, k in at:
+        X[r, k] = 1e-40
+        W[k] *= 1e32
+        G[r] *= 1e32
+    W[40, 3], X[17, 40] = 1e-40, 1e32
+    tuned("GCN_GEMM_SPLIT", 2)
+    out, dW = torch.empty(rows, d_out, device=dev), torch.empty(d_in, d_out, device=dev)
+    gcn.gcn_dense_fwd(X, W, out)
+    case = rows_alone(gcn, dev, rows)
+    gcn.gcn_layer_bwd(case.A, X, W, G, dW, AH_saved=X)
+    for got, a, b in ((out, X.double(), W.double()), (dW, X.double().T, G.double())):
+        assert bool(((got.double() - a @ b).abs() <= 1e-5 * (a.abs() @ b.abs())).all())
+    W[40, 3] = 1.0                                             # (W without one, A with: only the tiles that hold them are formed again)
+    gcn.gcn_dense_fwd(X, W, out)
+    assert bool(((out.double() - X.double() @ W.double()).abs() <= 1e-5 * (X.double().abs() @ W.double().abs())).all())
     case.A.free()
