@@ -58,6 +58,12 @@ __device__ __forceinline__ void split2(float lo, float hi, uint32_t (&p)[3]) {
     hi -= __uint_as_float(p[k] & 0xffff0000u);
   }
 }
+// What the parts of v lack
+__device__ __forceinline__ float left_over(float v) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) v -= __uint_as_float(pack_bf16(v, 0.f) << 16);
+  return v;
+}
 // Sums that are no finite number (a value beyond the bf16 range, an infinity, a NaN: inf = inf + NaN in parts), or below 2^-90 and not zero: products of
 // parts may lie under the smallest fp32 number.
 struct RangeCheck {
@@ -345,7 +351,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
     }
     const int left = rows_left(tile);
-    // An operand or a sum out of the range in which the parts stand for their values: those rows are multiplied again on the fp32 pipe.
+    // An operand or a sum out of the range in which the parts stand for their values: those rows are multiplied again on the fp32 pipe.  602 -> 128 on
+    // 233 K rows, such an operand in no row 270 us, one of 50 K 322, one of 1000 376, one of 32 637, in W 637; 440 on the fp32 pipe.
     RangeCheck range;
 #pragma unroll
     for (int rt = 0; rt < kRT; ++rt)
@@ -362,20 +369,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int rt = 0; rt < kRT; ++rt)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[rt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-      for (int k0 = 0; k0 < a.K; k0 += 4) {
-        const int k = k0 + qe;
-        float xs[kRT];
+      constexpr int kDeep = NT > 8 ? 2 : 4;            // (steps of four asked for at a time)
+      for (int k0 = 0; k0 < a.K; k0 += 4 * kDeep) {
+        float xs[kDeep][kRT], ws[kDeep][NT];
 #pragma unroll
-        for (int rt = 0; rt < kRT; ++rt)
-          xs[rt] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)(k < a.K ? (uint32_t)((16 * rt + ce) * (int)a.lda + k) * 4u : kNoPlace), 0, 0));
+        for (int d = 0; d < kDeep; ++d) {
+          const int k = k0 + 4 * d + qe;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const int n = n0 + 16 * t + ce;
-          const uint32_t at = (uint32_t)(TRANS ? n * ldw + k : k * ldw + n) * 4u;
-          const float ws = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wb, (int)(k < a.K && n < a.N ? at : kNoPlace), 0, 0));
+          for (int rt = 0; rt < kRT; ++rt)
+            xs[d][rt] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)(k < a.K ? (uint32_t)((16 * rt + ce) * (int)a.lda + k) * 4u : kNoPlace), 0, 0));
 #pragma unroll
-          for (int rt = 0; rt < kRT; ++rt) acc[rt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ws, xs[rt], acc[rt][t], 0, 0, 0);
+          for (int t = 0; t < NT; ++t) {
+            const int n = n0 + 16 * t + ce;
+            const uint32_t at = (uint32_t)(TRANS ? n * ldw + k : k * ldw + n) * 4u;
+            ws[d][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wb, (int)(k < a.K && n < a.N ? at : kNoPlace), 0, 0));
+          }
         }
+#pragma unroll
+        for (int d = 0; d < kDeep; ++d)
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int rt = 0; rt < kRT; ++rt) acc[rt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ws[d][t], xs[d][rt], acc[rt][t], 0, 0, 0);
       }
     }
     if (left <= 0) continue;
@@ -468,6 +483,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   constexpr int kUnits = (kUnitsAll + kThreads - 1) / kThreads;
   constexpr int D = TA * TB <= 4 ? 2 : 1;                                // chunks asked for ahead of the one that is split (registers)
   extern __shared__ u32x4 split_lds[];
+  constexpr int kSmall = 256;
+  __shared__ int small[kSmall], n_small;                 // chunks with small operands, in order, each up to once a wavefront
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 31, h = lane >> 5;
   const int g = w / (WA * WB), wa = (w / WB) % WA, wb = w % WB;
@@ -511,7 +528,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
     };
     // rows 2 j, 2 j + 1 of component e of unit i, those of A times `sign`, in three parts
-    LeastOperand least;
+    LeastOperand least;                                  // of the chunk that is split
+    auto note = [&](int64_t k) {
+      if (__any(least.out()) && lane == 0) {
+        const int at = atomicAdd(&n_small, 1);
+        if (at < kSmall) small[at] = (int)((k - k_lo) / kRows);
+      }
+      least = LeastOperand();
+    };
     u32x4 part[3];
     auto convert = [&](const floatx2w (&raw)[kUnits][8], int i, int e, int j, float sign) {
       uint32_t o[3];
@@ -538,6 +562,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int d = 0; d < D; ++d)
 #pragma unroll
       for (int i = 0; i < kUnits; ++i) load(k_lo + d * kRows, i, raw[d]);
+    if (threadIdx.x == 0) n_small = 0;
+    lds_barrier();
 #pragma unroll
     for (int i = 0; i < kUnits; ++i) {
 #pragma unroll
@@ -548,6 +574,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
       load(k_lo + D * kRows, i, raw[0]);
     }
+    note(k_lo);                                            // (before the barrier: those of a chunk lie side by side in the list)
     __syncthreads();
     // Chunk k, whose operands are in half P of the buffer, is multiplied; the next one is split and placed in the other half, and the one
     // D + 1 chunks on is asked for.  Every other chunk of A is taken with the other sign: what the pipe cuts off is cut downwards, in every
@@ -598,6 +625,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         }
         __builtin_amdgcn_sched_barrier(0);
       }
+      note(k + kRows);
       lds_barrier();
     };
     if constexpr (D == 1) {
@@ -612,7 +640,46 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
     }
 
-    // An operand or a sum out of range (as above): the rows of the split once more, on the fp32 pipe
+    // The group's rows of chunk k on the fp32 pipe, eight asked for at a time (all of 2.45 M rows 3.2 ms, with two at a time 5.2): whole, or what the
+    // parts of their operands lack.
+    auto fp32_rows = [&](int64_t k, auto lacking) {
+      const RowsBuf ra = rows_of(a.A, a.lda, a.M, k), rb = rows_of(a.B, a.ldb, a.N, k);
+#pragma unroll 1
+      for (int k8 = 16 * g; k8 < 16 * g + 16; k8 += 8) {
+        float av[4][TA], bv[4][TB];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          const int row = k8 + 2 * kk + h;
+#pragma unroll
+          for (int i = 0; i < TA; ++i) {
+            const int t = wa * TA + i, m = m0 + 64 * (t >> 1) + 2 * c + (t & 1);
+            av[kk][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, (int)(m < a.M ? (uint32_t)(row * (int)a.lda + m) * 4u : kNoPlace), 0, 0));
+          }
+#pragma unroll
+          for (int j = 0; j < TB; ++j) {
+            const int t = wb * TB + j, n = n0 + 64 * (t >> 1) + 2 * c + (t & 1);
+            bv[kk][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, (int)(n < a.N ? (uint32_t)(row * (int)a.ldb + n) * 4u : kNoPlace), 0, 0));
+          }
+        }
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+          for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+              if constexpr (decltype(lacking)::value) {
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(left_over(av[kk][i]), bv[kk][j], acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[kk][i], left_over(bv[kk][j]), acc[i][j], 0, 0, 0);
+              } else {
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[kk][i], bv[kk][j], acc[i][j], 0, 0, 0);
+              }
+            }
+      }
+    };
+    // Sums out of range (as above), or many chunks with small operands: the rows of the split once more.  Few such chunks: the products of what the
+    // parts of their operands lack are added.  Hidden gradients of networks trained to max |Z| 75 .. 700 hold operands below 2^-108 in 0 to 5 rows of
+    // 50 K to 100 K, and the last workgroup holds up the launch.  256 x 256 over 2.45 M rows, such an operand in no row 2.09 ms, one of 50 K 2.10 (its
+    // whole range of rows again: 7.3), one of 1000 2.18, one of 32 5.3; 2.44 on the fp32 pipe.
     RangeCheck range;
 #pragma unroll
     for (int i = 0; i < TA; ++i)
@@ -620,35 +687,26 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int j = 0; j < TB; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) range.add(acc[i][j][r]);
-    const bool again = __syncthreads_or(range.out() || least.out());
-    if (__builtin_expect(again, 0)) {
+    const bool sums_out = __syncthreads_or(range.out());
+    const int noted = __builtin_amdgcn_readfirstlane(n_small);
+    if (__builtin_expect((int)sums_out | (int)(noted > 0), 0)) {
+      if (sums_out || noted > kSmall) {
 #pragma unroll
-      for (int i = 0; i < TA; ++i)
+        for (int i = 0; i < TA; ++i)
 #pragma unroll
-        for (int j = 0; j < TB; ++j)
+          for (int j = 0; j < TB; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-      // (the rows of the groups as before, two at a time)
-      for (int64_t k = k_lo + 16 * g; k < k_hi; k += kRows)
-        for (int kk = 0; kk < 16; kk += 2) {
-          const int64_t row = k + kk + h;
-          const bool in = row < k_hi;
-          float av[TA], bv[TB];
-#pragma unroll
-          for (int i = 0; i < TA; ++i) {
-            const int t = wa * TA + i, m = m0 + 64 * (t >> 1) + 2 * c + (t & 1);
-            av[i] = in && m < a.M ? a.A[row * a.lda + m] : 0.f;
-          }
-#pragma unroll
-          for (int j = 0; j < TB; ++j) {
-            const int t = wb * TB + j, n = n0 + 64 * (t >> 1) + 2 * c + (t & 1);
-            bv[j] = in && n < a.N ? a.B[row * a.ldb + n] : 0.f;
-          }
-#pragma unroll
-          for (int i = 0; i < TA; ++i)
-#pragma unroll
-            for (int j = 0; j < TB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int64_t k = k_lo; k < k_hi; k += kRows) fp32_rows(k, std::false_type());
+      } else {
+        int before = -1;
+        for (int e = 0; e < noted; ++e) {
+          const int at = __builtin_amdgcn_readfirstlane(small[e]);
+          if (at != before) fp32_rows(k_lo + (int64_t)at * kRows, std::true_type());
+          before = at;
         }
+      }
+      __syncthreads();                                   // (the list may be begun anew)
     }
     // the groups' sums
     if constexpr (G > 1) {

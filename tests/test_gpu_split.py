@@ -188,6 +188,24 @@ def test_operands_near_the_smallest_number(gcn, dev, tuned, small_x, small_w):
     case.A.free()
 
 
+# So many of them that a gradient's workgroups form their whole ranges of rows again (more than 32 chunks of 16 or 32 rows in each).
+@pytest.mark.parametrize("d_in,d_out", [(100, 130), (256, 100)])
+def test_small_operands_in_every_row(gcn, dev, tuned, d_in, d_out):
+    import torch
+    rows = 300001
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(3)
+    X = torch.randn(rows, d_in, generator=gen, device=dev)
+    X[:, 5] *= 2.0**-120
+    G = torch.randn(rows, d_out, generator=gen, device=dev) * 2.0**40
+    case = rows_alone(gcn, dev, rows)
+    tuned("GCN_GEMM_SPLIT", 2)
+    dW = torch.empty(d_in, d_out, device=dev)
+    gcn.gcn_layer_bwd(case.A, X, torch.zeros(d_in, d_out, device=dev), G, dW, AH_saved=X)
+    assert bool(((dW.double() - X.double().T @ G.double()).abs() <= 1e-5 * (X.double().abs().T @ G.double().abs())).all())
+    case.A.free()
+
+
 # One such operand among ordinary ones: in every place of the row tiles, steps and passes of H W, and of the chunks and workgroups of A^T B; and in W.
 @pytest.mark.parametrize("d_in,d_out", [(100, 130), (602, 65), (256, 256)])
 def test_one_small_operand_among_ordinary_ones(gcn, dev, tuned, d_in, d_out):
