@@ -396,8 +396,9 @@ int gemm_nn(const void* A, int64_t lda, const float* B, int64_t ldb, void* C, in
 // C[M x N] (f32) = A[Kdim x M]^T * B[Kdim x N], Kdim huge: split over blocks, partial tiles in ws
 // (gemm_tn_ws_bytes), then summed in a fixed order.  A, B element type dtype.
 size_t gemm_tn_ws_bytes(int64_t Kdim, int M, int N);
-// max_blocks > 0: as GemmEpilogue::max_blocks, honoured when gemm_tn_limits_blocks says so; beside: as GemmEpilogue::beside
-bool gemm_tn_limits_blocks(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kdim, int M, int N, int dtype);
+// max_blocks > 0: as GemmEpilogue::max_blocks, honoured when gemm_tn_limits_blocks says so; beside: as GemmEpilogue::beside, and no wish where
+// the operands' form leaves no such kernel (gemm_tn_limits_blocks is false then: the product belongs behind the sparse one)
+bool gemm_tn_limits_blocks(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kdim, int M, int N, int dtype, bool beside);
 int gemm_tn(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc,
             int64_t Kdim, int M, int N, int dtype, void* ws, hipStream_t s, int max_blocks = 0, bool beside = false);
 // streaming variants (gemm_direct.hip): the long operand goes from global memory straight into the

@@ -506,9 +506,9 @@ int gemm_tn(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, in
   return GCN_OK;
 }
 
-bool gemm_tn_limits_blocks(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype) {
+bool gemm_tn_limits_blocks(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype, bool beside) {
   return use_direct() && !(dtype == GCN_BF16 && gemm_tn_bf16_ok(A, lda, B, ldb, Kd, M, N)) &&
-         (gemm_tn_split_ok(A, lda, B, ldb, Kd, M, N, dtype) || gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype));
+         ((!beside && gemm_tn_split_ok(A, lda, B, ldb, Kd, M, N, dtype)) || gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype));
 }
 
 // column sums: block b adds rows [b*kRows, ...) per column into partial[b][c]; then fp64 finish

@@ -990,8 +990,10 @@ int gemm_tn_direct_partials(const void* A, int64_t lda, const void* B, int64_t l
                             float* partial, int* nsplit_out, hipStream_t s, int max_blocks, bool beside) {
   if (dtype == GCN_BF16 && gemm_tn_bf16_ok(A, lda, B, ldb, Kd, M, N))
     return gemm_tn_bf16_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s);
-  if (!beside && gemm_tn_split_ok(A, lda, B, ldb, Kd, M, N, dtype)) return gemm_tn_split_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s, max_blocks);
-  if (gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype)) return gemm_tn_lds_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s, max_blocks);
+  const bool lds = gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype);
+  if (!(beside && lds) && gemm_tn_split_ok(A, lda, B, ldb, Kd, M, N, dtype))
+    return gemm_tn_split_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s, max_blocks);
+  if (lds) return gemm_tn_lds_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s, max_blocks);
   TnDirectArgs a{A, lda, B, ldb, Kd, M, N, 0, 0, partial};
   const bool narrow = tn_narrow_ok(A, lda, B, ldb, Kd, M, N, dtype);
   if (narrow || tn_wide_ok(A, lda, B, ldb, N, dtype)) {

@@ -271,10 +271,10 @@ static int layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
         GemmEpilogue epi;
         epi.bias = bias; epi.relu = relu; epi.C2 = Z; epi.ldc2 = ldz;
         epi.c_rows_padded = true;
-        epi.beside = !fused && long_sparse(A->nr, A->nnz, d_in) && !spmm_panel_wanted(sp);      // (the same kernel, beside or not)
         epi.rows = A->nr;
-        const bool pipelined = !fused && side_chunks() > 0 && overlap_worthwhile(A->nr, A->nnz, d_in) && !spmm_panel_wanted(sp) &&
-                               gemm_nn_limits_blocks(AH, ldAH, A->nr, d_out, d_in, dtype);
+        const bool can_follow = !fused && !spmm_panel_wanted(sp) && gemm_nn_limits_blocks(AH, ldAH, A->nr, d_out, d_in, dtype);
+        epi.beside = can_follow && long_sparse(A->nr, A->nnz, d_in);      // (the same kernel whether or not the overlap is switched off)
+        const bool pipelined = can_follow && side_chunks() > 0 && overlap_worthwhile(A->nr, A->nnz, d_in);
         if (fused) {
           GCN_TRY(spmm_dense(sp, hub, W, d_out, Hout, ldo, d_out, epi, s));
         } else if (!pipelined) {
@@ -402,11 +402,12 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
         sp.Y = T; sp.ldy = ldt;
         // dW from a saved A^ H needs nothing of this product: it runs beside it
         SideStream side;
+        const bool far = long_sparse(A->nc, A->nnz, d_out);
         const bool beside = AH_saved && overlap_worthwhile(A->nc, A->nnz, d_out) &&
-                            gemm_tn_limits_blocks(AH_saved, ldah, G, ldg, A->nr, d_in, d_out, dtype);
+                            gemm_tn_limits_blocks(AH_saved, ldah, G, ldg, A->nr, d_in, d_out, dtype, far);
         if (beside) {
           GCN_TRY(side.fork(Am, s));
-          GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, side.side, tune().overlap_cus, long_sparse(A->nc, A->nnz, d_out)));
+          GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, side.side, tune().overlap_cus, far));
         }
         if (fused) {
           GemmEpilogue epi;
@@ -431,7 +432,7 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
           }
         }
         if (beside) GCN_TRY(side.join());
-        else if (AH_saved) GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, s, 0, long_sparse(A->nc, A->nnz, d_out)));
+        else if (AH_saved) GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, s, 0, far));
         else GCN_TRY(gemm_tn(H, ldh, T, ldt, dW, d_out, A->nc, d_in, d_out, dtype, tn, s));
       }
     } else {
@@ -444,15 +445,16 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
       void* tn = ws.take(gemm_tn_ws_bytes(A->nr, d_in, d_out));
       if (pass) {
         SideStream side;
+        const bool far = dH && AH_saved && long_sparse(A->nc, A->nnz, d_in);
         const bool beside = dH && AH_saved && overlap_worthwhile(A->nc, A->nnz, d_in) &&
-                            gemm_tn_limits_blocks(AH_saved, ldah, G, ldg, A->nr, d_in, d_out, dtype);
+                            gemm_tn_limits_blocks(AH_saved, ldah, G, ldg, A->nr, d_in, d_out, dtype, far);
         if (dH) {
           GemmEpilogue epi;
           epi.b_trans = epi.c_rows_padded = true;
           GCN_TRY(gemm_nn(G, ldg, W, d_out, Q, ldq, A->nr, d_in, d_out, dtype, epi, s));
           if (beside) {        // after Q = G W^T, which wants the matrix pipes of every compute unit itself
             GCN_TRY(side.fork(Am, s));
-            GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, side.side, tune().overlap_cus, long_sparse(A->nc, A->nnz, d_in)));
+            GCN_TRY(gemm_tn(AH_saved, ldah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, side.side, tune().overlap_cus, far));
           }
           SpmmArgs sp{A->colptr, A->rowidx, A->val_t, &A->sched_t, A->nc, A->nr, A->nnz, true, A->nr, Q, ldq, dH, lddh, nullptr, 0,
                       d_in, dtype, Zprev ? GCN_EPI_MASK : GCN_EPI_NONE, nullptr, Zprev, ldzp};
@@ -472,7 +474,7 @@ static int layer_bwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
           ah = AH; ld_ah = ldq;
         }
         if (beside) GCN_TRY(side.join());
-        else GCN_TRY(gemm_tn(ah, ld_ah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, s, 0, dH && AH_saved && long_sparse(A->nc, A->nnz, d_in)));
+        else GCN_TRY(gemm_tn(ah, ld_ah, G, ldg, dW, d_out, A->nr, d_in, d_out, dtype, tn, s, 0, far));
       }
     }
     if (!pass) GCN_TRY(ensure_workspace(Am, ws.used));

@@ -1,0 +1,63 @@
+"""Where the dense products of a layer call on a large graph go, on the host: tests/host_routes.cpp writes down what the library launches."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2212_05009_amd")
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if not os.path.exists(os.path.join(PKG, "libgcn.so")):
+        import __graft_entry__
+        __graft_entry__.build()
+    out = str(tmp_path_factory.mktemp("host") / "host_routes")
+    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "--offload-host-only", "--offload-arch=gfx950", "-std=c++17", "-O1", "-I", os.path.join(PKG, "csrc"),
+           os.path.join(ROOT, "tests", "host_routes.cpp"), "-o", out, "-L", PKG, "-lgcn", "-Wl,-rpath," + PKG, "-rdynamic", "-pthread"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout + res.stderr
+    return out
+
+
+def dense(program, overlap, call, d_in, d_out, ld):
+    """The launches of dense kernels: (kernel's name, workgroups, stream)."""
+    res = subprocess.run([program, str(overlap), call, str(d_in), str(d_out), str(ld)], capture_output=True, text=True, timeout=60)
+    assert res.returncode == 0, res.stdout + res.stderr
+    launches = [line.split() for line in res.stdout.splitlines()]
+    return [(k, int(g), s) for k, g, s in launches if "gemm" in k]
+
+
+CUS = 64        # compute units of a dense product beside a sparse one (GCN_OVERLAP_CUS)
+
+
+# No kernel that keeps to a few compute units takes these products: of 173 columns, of 101 terms in rows of odd pitch.  They run alone, in three parts.
+@pytest.mark.parametrize("overlap", [0, 1])
+@pytest.mark.parametrize("d_in,d_out,ld", [(100, 173, 100), (101, 256, 101), (96, 130, 96)])
+def test_a_forward_product_that_cannot_follow_runs_alone_in_three_parts(program, overlap, d_in, d_out, ld):
+    launches = dense(program, overlap, "fwd", d_in, d_out, ld)
+    assert len(launches) == 1 and "k_gemm_nn_split" in launches[0][0] and launches[0][2] == "main", launches
+
+
+@pytest.mark.parametrize("d_in,d_out", [(256, 256), (100, 256), (128, 192)])
+def test_a_forward_product_that_follows_keeps_to_its_compute_units(program, d_in, d_out):
+    launches = dense(program, 1, "fwd", d_in, d_out, d_in)
+    assert len(launches) > 1 and all("k_gemm_nn_regw" in k and s == "side" for k, _, s in launches), launches
+    assert all(g <= CUS for _, g, _ in launches[:-1]), launches             # (the last has nothing beside it)
+    alone = dense(program, 0, "fwd", d_in, d_out, d_in)
+    assert {k for k, _, _ in alone} == {k for k, _, _ in launches}, (alone, launches)
+
+
+# A saved A^ H in rows of odd pitch: the gradient runs behind the sparse product, on the whole chip, in three parts; else beside it on its own units.
+@pytest.mark.parametrize("d_in,d_out,ld,apart", [(173, 128, 173, True), (101, 256, 101, True), (128, 101, 129, True), (256, 256, 256, False),
+                                                 (100, 256, 100, False), (256, 100, 256, False)])
+def test_a_gradient_is_beside_the_sparse_product_only_on_its_own_compute_units(program, d_in, d_out, ld, apart):
+    launches = [x for x in dense(program, 1, "bwd", d_in, d_out, ld) if "gemm_tn" in x[0]]
+    alone = [x for x in dense(program, 0, "bwd", d_in, d_out, ld) if "gemm_tn" in x[0]]
+    assert [k for k, _, _ in launches] == [k for k, _, _ in alone], (launches, alone)
+    main = [x for x in launches if "reduce" not in x[0] and "finish" not in x[0] and "sum" not in x[0]]
+    assert len(main) == 1, launches
+    assert ("k_gemm_tn_split" in main[0][0]) == apart, launches
+    assert main[0][2] == ("main" if apart else "side"), launches
+    assert apart or main[0][1] <= CUS, launches
