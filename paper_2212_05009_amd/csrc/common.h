@@ -434,6 +434,8 @@ bool gemm_tn_lds_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int6
 size_t gemm_tn_lds_ws_bytes(int64_t Kd, int M, int N);
 int gemm_tn_lds_partials(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, float* partial,
                          int* nsplit_out, hipStream_t s, int max_blocks = 0);
+// requests of four (two) elements of the rows of A (B)
+bool gemm_tn_wide_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int N, int dtype);
 size_t gemm_tn_direct_ws_bytes(int64_t Kd, int M, int N);
 int gemm_tn_direct_partials(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype,
                             float* partial, int* nsplit_out, hipStream_t s, int max_blocks = 0, bool beside = false);

@@ -916,7 +916,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
 
 constexpr int kWideUK1 = 8, kWideUK2 = 8;   // row pairs per request batch (TN = 1, TN = 2)
 
-static bool tn_wide_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int N, int dtype) {
+bool gemm_tn_wide_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int N, int dtype) {
   const bool off = tune().gemm_tn_wide == 0;
   const size_t es = dtype == GCN_BF16 ? 2 : 4;
   if (off || (lda % 4) != 0 || ((uintptr_t)A % (4 * es)) != 0) return false;
@@ -938,7 +938,7 @@ static bool tn_wide_ok(const void* A, int64_t lda, const void* B, int64_t ldb, i
 static bool tn_narrow_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype) {
   if (tune().gemm_tn_wide == 0 || dtype != GCN_F32 || M > 64) return false;
   if (M % 2 != 0 || (lda % 2) != 0 || ((uintptr_t)A % 8) != 0 || lda >= (1 << 28) || ldb >= (1 << 28)) return false;
-  if (tn_wide_ok(A, lda, B, ldb, N, dtype)) return N <= 32 || N % 2 == 0;
+  if (gemm_tn_wide_ok(A, lda, B, ldb, N, dtype)) return N <= 32 || N % 2 == 0;
   if (N <= 32 || N % 2 != 0 || (ldb % 2) != 0 || ((uintptr_t)B % 8) != 0) return false;
   if (N > 256 || (N > 128 && N <= 192)) return false;
   return Kd >= (N <= 64 ? 3 << 17 : N <= 128 ? 2 << 18 : 3 << 18);
@@ -996,7 +996,7 @@ int gemm_tn_direct_partials(const void* A, int64_t lda, const void* B, int64_t l
   if (lds) return gemm_tn_lds_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s, max_blocks);
   TnDirectArgs a{A, lda, B, ldb, Kd, M, N, 0, 0, partial};
   const bool narrow = tn_narrow_ok(A, lda, B, ldb, Kd, M, N, dtype);
-  if (narrow || tn_wide_ok(A, lda, B, ldb, N, dtype)) {
+  if (narrow || gemm_tn_wide_ok(A, lda, B, ldb, N, dtype)) {
     a.nsplit = tn_wide_splits(Kd, M, N);
     a.rows_per_split = round_up(ceil_div(Kd > 0 ? Kd : 1, a.nsplit), 2 * kTnMaxUK);
     *nsplit_out = a.nsplit;

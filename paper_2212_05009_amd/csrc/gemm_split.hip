@@ -809,15 +809,19 @@ int tn_splits(int64_t Kd, int M, int N) {
 
 }  // namespace
 
-// Where the fp32 kernels take longer.  Measured, their time over this kernel's, rows of K elements to N columns:
-//   W in registers (N = 192, 256; gemm_nn_limits_blocks)   10 K rows 0.6-0.8, 20 K 0.9-1.3, 60 K 1.3-1.9, 300 K 1.3-1.8 (256 x 256 on
-//                   2.45 M rows 2.56 -> 1.92 ms, 100 x 256 1.44 -> 1.21): from 2^15 rows on;
+// Where the fp32 kernels take longer.  Measured, their time over this kernel's for W as it is / transposed / transposed with a mask, on 4 K to 512 K rows
+// of K elements to N columns:
+//   W in registers (N = 192, 256; gemm_nn_limits_blocks)   128 -> 192 on 32 K rows 1.08 / 0.98 / 1.00, from 64 K 1.5-1.8 / 1.5-1.7 / 1.4-1.6; 256 -> 256
+//                   on 32 K 0.82 / 0.75 / 0.73, from 64 K 1.22-1.34 / 1.16-1.23 / 1.09-1.13; 128 -> 256 from 64 K 1.12-1.18 / 1.09-1.16 / 1.02-1.05,
+//                   100 -> 256 1.08-1.13 / 1.06 / 1.01, 104 -> 256 1.0 / 0.95-0.99 / 0.92-0.97: from 2^16 rows on, to 256 columns from K = 128 on;
 //   W in LDS, whole k steps (K <= 128 or a multiple of it)  N <= 64 0.5-1.0, N = 72 .. 128 0.9-1.4, but nothing is gained in a training step
-//                   (the pipe's clock: 2^18 x 128 x 128 83 -> 69 us, what follows 14 us longer), N = 160 1.2-2.5: more than 128 columns;
-//                   fewer rows: K = 61 to N = 256 on 16 K 19.1 / 20.0 us, 64 K 32.9 / 27.0, but with W transposed and a mask 20.4 / 28.8 on 16 K
-//                   (W is read and split once a launch, 8 us across its lines): from 2^17 rows on;
-//   others (K = 160, 237, 300, 602, or W too large for LDS) N = 47 1.1-1.6, 64 1.2-1.8, 72-256 1.2-2.6, N <= 32 0.5-1.2 on up to
-//                   20 K rows, 1.0-1.5 from 60 K on (233 K rows 602 -> 128 430 -> 236 us, 722 K 505 -> 100 1175 -> 585, 500 K 368 -> 173 967 -> 448).
+//                   (the pipe's clock: 2^18 x 128 x 128 83 -> 69 us, what follows 14 us longer); N = 129 .. 192 on 32 K 0.9-1.1 / 0.9-1.0 / 0.8-1.0, from 64 K
+//                   1.1-1.5 / 1.1-1.4 / 0.95-1.3 (the least at K = 48); N = 193 .. 256 on 64 K 1.06-1.19 / 1.02-1.16 / 0.88-1.04, on 512 K 1.04-1.11 / 1.01-1.11 /
+//                   0.96-1.06 up to K = 96, beyond (W's parts do not fit LDS) 0.9 / 0.9 / 0.8: from 2^16 rows on, no masks with many columns or few terms;
+//   others (K = 160, 237, 300, 602, or W too large for LDS) N <= 48 on up to 32 K 0.75-1.13 / 0.7-1.0 / 0.7-1.0, from 64 K 1.17-1.7 / 1.15-1.7 / 1.12-1.7;
+//                   N = 64 .. 128 on any number 1.1-2.3 / 1.0-2.3 / 1.05-2.5; N = 129 .. 192 on 4 K 0.9-1.14 / 0.84-1.02 / 1.2-1.3, from 8 K 1.0-2.3 /
+//                   0.97-2.3 / 1.2-2.8; N = 193 .. 400 on 4 K 0.75-0.85 / 0.66-0.75 / 0.86-0.94, on 32 K 1.1-1.65 / 1.04-1.5 / 1.3-1.6, from 64 K
+//                   1.4-1.8 / 1.3-1.8 / 1.6-2.0.
 // Its error against 64 bits is a third of theirs: 128 columns of K = 128 / 602 terms of either sign 5.7e-8 / 9.6e-8 (2.0e-7 / 4.4e-7), positive
 // ones 4.2e-8 / 6.9e-8 (1.2e-7 / 2.6e-7).
 bool gemm_nn_split_ok(const void* A, int64_t lda, int64_t ldw, int64_t ldc, int64_t M, int N, int K, int dtype, const GemmEpilogue& epi) {
@@ -829,10 +833,11 @@ bool gemm_nn_split_ok(const void* A, int64_t lda, int64_t ldw, int64_t ldc, int6
   if (t.gemm_split == 2) return true;
   if (t.gemm_fast != 1 || t.gemm_regw != 1 || epi.beside) return false;      // (an override is a choice between the fp32 kernels)
   if (epi.rows > 0) M = epi.rows;
-  if (gemm_nn_limits_blocks(A, lda, M, N, K, dtype)) return M >= 1 << 15;
-  const bool whole_steps = gemm_nn_direct_ok(N, K) && (K <= 128 || K % 128 == 0);
-  if (!whole_steps) return N > 32 || M >= 1 << 16;
-  return N > 128 && K >= 48 && M >= 1 << 17;
+  if (gemm_nn_limits_blocks(A, lda, M, N, K, dtype)) return M >= 1 << 16 && (N <= 192 || K >= 128);
+  if (gemm_nn_direct_ok(N, K) && (K <= 128 || K % 128 == 0))
+    return M >= 1 << 16 && N > 128 && (N <= 192 ? K >= (epi.mask ? 60 : 48) : !epi.mask && K >= 48 && K <= 96);
+  if (N <= 48) return M >= 1 << 16;
+  return N <= 128 || (N <= 192 ? M >= 1 << 13 : M * ceil_div(N, 256) >= 1 << 15);
 }
 
 int gemm_nn_split(const void* A, int64_t lda, const float* W, int64_t ldw, void* C, int64_t ldc, int64_t M, int N, int K,
@@ -847,17 +852,26 @@ int gemm_nn_split(const void* A, int64_t lda, const float* W, int64_t ldw, void*
   return split_launch<16>(a, epi.max_blocks, s);
 }
 
-// More than 64 columns on both sides, from 2 K rows on.  fp32 kernels / this one with the final sum, us: 2.5 K rows x 128 x 128 17.0 / 15.8,
-// 8 K x 602 x 200 47 / 46, 100 K x 300 x 256 251 / 148, 233 K x 602 x 128 537 / 320, 2^18 x 128 x 128 104 / 83, 722 K x 505 x 100
-// 1115 / 680, 2.45 M x 100 x 256 1290 / 1130, x 256 x 256 2440 / 1910; but 333 x 77 x 91 11.7 / 14.9, 300 K x 128 x 64 78 / 89, x 602 x 16 243 / 323:
-// there the product waits for memory, and 32 rows in flight are too few.
+// More than 64 columns on both sides (300 K rows x 128 x 64 78 / 89 us, x 602 x 16 243 / 323: there the product waits for memory, and 32 rows in flight
+// are too few); a workgroup's block is 128 x 128 at least.  fp32 kernels / this one with the final sum, us, by the kernel that it takes the place of:
+//   operands through LDS  both sides above 128, or one above 128 and up to 256: 2 K rows x 256 x 256 47 / 39, x 80 x 200 25.7 / 22.6, 20 K x 256 x 80 35 / 32,
+//                         100 K x 300 x 256 245 / 164, 2.45 M x 256 x 256 2440 / 2110, x 100 x 256 1306 / 1299: from 2 K rows on;
+//                         else 20 K x 72 x 72 19.6 / 20.0, 64 K 29.8 / 27.8, 300 K 105 / 88; 64 K x 128 x 128 36.0 / 36.4, 300 K 117 / 106; 16 K x 384 x 128 38.5 / 41.8,
+//                         32 K 58.5 / 57.3, 64 K 95 / 80;
+//   vector requests       2 K x 128 x 66 37 / 17, 8 K x 300 x 66 54 / 33, 300 K x 100 x 66 120 / 91: from 2 K rows on;
+//   single requests       (rows of A of no whole quads, of B of no whole pairs) 20 K x 65 x 65 17.4 / 20.3, 64 K 30.4 / 27.7, 300 K 141 / 87; 64 K x 173 x 128 51 / 55, 128 K
+//                         101 / 86; 16 K x 505 x 100 34 / 40, 32 K 63 / 58; 8 K x 602 x 128 33 / 40, 20 K 62 / 56; 8 K x 602 x 256 48 / 51, 16 K 83 / 72:
+//                         there, as with narrow outputs through LDS, from 1.5e9 products or 2^17 rows on.
 // Error against 64 bits 4.4e-7 for 1.7e-6 (256 x 256 over 2.45 M rows), 1.2e-7 for 5.8e-7 (128 x 128 over 2^18).
 bool gemm_tn_split_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype) {
   const Tuning& t = tune();
   if (t.gemm_split == 0 || dtype != GCN_F32 || Kd < 1 || M < 1 || N < 1) return false;
   if (lda >= 1 << 23 || ldb >= 1 << 23) return false;
   if (t.gemm_split == 2) return true;
-  return t.gemm_tn_wide == 1 && t.gemm_tn_lds == 1 && M > 64 && N > 64 && Kd >= 2048;
+  if (t.gemm_tn_wide != 1 || t.gemm_tn_lds != 1 || M <= 64 || N <= 64 || Kd < 2048) return false;
+  const int less = std::min(M, N), more = std::max(M, N);
+  const bool always = gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype) ? less > 128 || (more > 128 && more <= 256) : gemm_tn_wide_ok(A, lda, B, ldb, N, dtype);
+  return always || Kd >= 1 << 17 || (double)Kd * M * N >= 1.5e9;
 }
 
 size_t gemm_tn_split_ws_bytes(int64_t Kd, int M, int N) { return sizeof(float) * (size_t)tn_splits(Kd, M, N) * (size_t)M * (size_t)N; }

@@ -1,7 +1,8 @@
 // Host-side check of where the dense products of a layer call go, run without a GPU: this program brings its own HIP runtime (device memory is
 // host memory, kernels do nothing, launches are written down by name) and links the library.
-//   host_routes <overlap> <call> <d_in> <d_out> <ld>      one line per launch: kernel, workgroups, main | side
+//   host_routes <overlap> <call> <d_in> <d_out> <ld> [<rows>]      one line per launch: kernel, workgroups, main | side
 // call: fwd | bwd; the graph has 2^17 rows and 10^8 entries, long enough for dense products beside its sparse ones.  <ld>: the pitch of A^ H.
+//       dense: the dense product alone; grad: the weight gradient alone; on a graph of <rows> rows and entries.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -61,8 +62,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3, void**, size_t, hipStrea
 using namespace gcn;
 
 int main(int argc, char** argv) {
-  if (argc != 6) return 2;
-  const int64_t n = 1 << 17, nnz = 100000000;
+  if (argc < 6) return 2;
+  const int64_t n = argc > 6 ? atol(argv[6]) : 1 << 17, nnz = argc > 6 ? n : 100000000;
   const int d_in = atoi(argv[3]), d_out = atoi(argv[4]), ld = atoi(argv[5]);
   gcn_csr A;
   A.n_global = A.nr = A.nc = n;
@@ -82,7 +83,10 @@ int main(int argc, char** argv) {
   }
   if (gcn_debug_set_tuning("GCN_OVERLAP", atoi(argv[1])) != GCN_OK || gcn_debug_set_tuning("GCN_SPMM_PANEL", 0) != GCN_OK) return 2;
   float* p = (float*)any;
-  const int rc = !strcmp(argv[2], "fwd")
+  const int rc = !strcmp(argv[2], "dense") ? gcn_dense_fwd(p, ld, n, p, nullptr, d_in, d_out, GCN_ACT_RELU, GCN_F32, nullptr, p + 64, round_up(d_out, 4), nullptr)
+                 : !strcmp(argv[2], "grad") ? gcn_layer_bwd_ld(&A, p, round_up(d_in, 4), p + 64, ld, p, d_in, d_out, GCN_F32, p + 128, round_up(d_out, 2), nullptr, 0, p + 256,
+                                                             nullptr, nullptr, 0, nullptr)
+                 : !strcmp(argv[2], "fwd")
                      ? gcn_layer_fwd_ld(&A, p, round_up(d_in, 4), p, nullptr, d_in, d_out, GCN_ACT_RELU, GCN_F32, nullptr, 0, p + 64, round_up(d_out, 4), p + 128, ld, nullptr)
                      : gcn_layer_bwd_ld(&A, p, round_up(d_in, 4), p + 64, ld, p, d_in, d_out, GCN_F32, p + 128, round_up(d_out, 4), p + 192, round_up(d_in, 4), p + 256,
                                         nullptr, p + 320, round_up(d_in, 4), nullptr);

@@ -21,9 +21,9 @@ def program(tmp_path_factory):
     return out
 
 
-def dense(program, overlap, call, d_in, d_out, ld):
+def dense(program, overlap, call, d_in, d_out, ld, *rows):
     """The launches of dense kernels: (kernel's name, workgroups, stream)."""
-    res = subprocess.run([program, str(overlap), call, str(d_in), str(d_out), str(ld)], capture_output=True, text=True, timeout=60)
+    res = subprocess.run([program, str(overlap), call, str(d_in), str(d_out), str(ld), *map(str, rows)], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0, res.stdout + res.stderr
     launches = [line.split() for line in res.stdout.splitlines()]
     return [(k, int(g), s) for k, g, s in launches if "gemm" in k]
@@ -32,9 +32,9 @@ def dense(program, overlap, call, d_in, d_out, ld):
 CUS = 64        # compute units of a dense product beside a sparse one (GCN_OVERLAP_CUS)
 
 
-# No kernel that keeps to a few compute units takes these products: of 173 columns, of 101 terms in rows of odd pitch.  They run alone, in three parts.
+# No kernel that keeps to a few compute units takes these products: of 173 columns, of 201 terms in rows of odd pitch.  They run alone, in three parts.
 @pytest.mark.parametrize("overlap", [0, 1])
-@pytest.mark.parametrize("d_in,d_out,ld", [(100, 173, 100), (101, 256, 101), (96, 130, 96)])
+@pytest.mark.parametrize("d_in,d_out,ld", [(100, 173, 100), (201, 256, 201), (96, 130, 96)])
 def test_a_forward_product_that_cannot_follow_runs_alone_in_three_parts(program, overlap, d_in, d_out, ld):
     launches = dense(program, overlap, "fwd", d_in, d_out, ld)
     assert len(launches) == 1 and "k_gemm_nn_split" in launches[0][0] and launches[0][2] == "main", launches
@@ -61,3 +61,22 @@ def test_a_gradient_is_beside_the_sparse_product_only_on_its_own_compute_units(p
     assert ("k_gemm_tn_split" in main[0][0]) == apart, launches
     assert main[0][2] == ("main" if apart else "side"), launches
     assert apart or main[0][1] <= CUS, launches
+
+
+# Sizes from which the three-part kernels were measured to gain: on both sides of the lines, and where they never do.
+@pytest.mark.parametrize("d_in,d_out,rows,split", [(256, 256, 1 << 16, True), (256, 256, (1 << 16) - 1, False), (128, 192, 1 << 16, True), (100, 256, 500000, False),
+                                                   (101, 256, 500000, False), (61, 256, 1 << 16, True), (61, 256, (1 << 16) - 1, False), (47, 256, 500000, False),
+                                                   (128, 128, 500000, False), (300, 41, 1 << 16, True), (300, 41, 1 << 15, False), (300, 64, 4096, True), (368, 173, 8192, True), (368, 173, 8191, False),
+                                                   (300, 256, 1 << 15, True), (300, 256, (1 << 15) - 1, False), (600, 400, 1 << 14, True), (600, 400, 4096, False)])
+def test_sizes_of_products_in_three_parts(program, d_in, d_out, rows, split):
+    launches = dense(program, 1, "dense", d_in, d_out, d_in, rows)
+    assert len(launches) == 1 and ("k_gemm_nn_split" in launches[0][0]) == split, launches
+
+
+@pytest.mark.parametrize("d_in,d_out,rows,split", [(256, 256, 2048, True), (256, 256, 2047, False), (80, 200, 2048, True), (72, 72, 20000, False), (72, 72, 1 << 17, True),
+                                                   (128, 128, 1 << 16, False), (128, 128, 100000, True), (384, 128, 1 << 14, False), (384, 128, 1 << 15, True),
+                                                   (128, 66, 2048, True), (65, 65, 1 << 16, False), (65, 65, 1 << 17, True), (173, 128, 1 << 15, False),
+                                                   (602, 128, 8192, False), (602, 128, 20000, True), (128, 64, 500000, False)])
+def test_sizes_of_gradients_in_three_parts(program, d_in, d_out, rows, split):
+    launches = [k for k, _, _ in dense(program, 1, "grad", d_in, d_out, d_in, rows) if "gemm_tn" in k]
+    assert any("k_gemm_tn_split" in k for k in launches) == split, launches
