@@ -377,9 +377,6 @@ struct GemmEpilogue {
   // the rows of C (and C2) may be written up to the next multiple of 16 bytes where their pitch reaches that far: buffers
   // of the library and those of the _ld calls; else what follows column N belongs to the caller
   bool c_rows_padded = false;
-  // the product may run beside a sparse one, whose requests hold up its own: a kernel that asks for its operand far ahead
-  bool beside = false;
-  int64_t rows = 0;              // rows of the whole product where this is a part of it (0: M): a part takes the kernel of the whole
 };
 // C = epilogue((A X) W) in one launch (spmm_dense.hip): sparse rows through LDS into the dense product; they are also stored
 // to a.Y where that is not null.  ws as spmm_launch; W and epi as gemm_nn's (K = a.d).
@@ -396,8 +393,9 @@ int gemm_nn(const void* A, int64_t lda, const float* B, int64_t ldb, void* C, in
 // C[M x N] (f32) = A[Kdim x M]^T * B[Kdim x N], Kdim huge: split over blocks, partial tiles in ws
 // (gemm_tn_ws_bytes), then summed in a fixed order.  A, B element type dtype.
 size_t gemm_tn_ws_bytes(int64_t Kdim, int M, int N);
-// max_blocks > 0: as GemmEpilogue::max_blocks, honoured when gemm_tn_limits_blocks says so; beside: as GemmEpilogue::beside, and no wish where
-// the operands' form leaves no such kernel (gemm_tn_limits_blocks is false then: the product belongs behind the sparse one)
+// max_blocks > 0: as GemmEpilogue::max_blocks, honoured when gemm_tn_limits_blocks says so.  beside: the product may run beside a sparse one,
+// whose requests hold up its own: a kernel that asks for its operands far ahead, where their form leaves one (else gemm_tn_limits_blocks is
+// false: the product belongs behind the sparse one)
 bool gemm_tn_limits_blocks(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kdim, int M, int N, int dtype, bool beside);
 int gemm_tn(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc,
             int64_t Kdim, int M, int N, int dtype, void* ws, hipStream_t s, int max_blocks = 0, bool beside = false);
@@ -408,7 +406,7 @@ bool gemm_nn_direct_ok(int N, int K);
 bool gemm_nn_regw_ok(const void* A, int64_t lda, int64_t M, int N, int K, int dtype);
 int gemm_nn_regw(const void* A, int64_t lda, const float* W, int64_t ldw, void* C, int64_t ldc, int64_t M, int N, int K,
                  const GemmEpilogue& epi, hipStream_t s);
-// fp32 operands on the bf16 matrix pipe, every value in three parts (gemm_split.hip)
+// fp32 operands on the bf16 matrix pipe, every value in three parts (gemm_split.hip): A W^T, and A^T B below
 bool gemm_nn_split_ok(const void* A, int64_t lda, int64_t ldw, int64_t ldc, int64_t M, int N, int K, int dtype, const GemmEpilogue& epi);
 int gemm_nn_split(const void* A, int64_t lda, const float* W, int64_t ldw, void* C, int64_t ldc, int64_t M, int N, int K,
                   const GemmEpilogue& epi, hipStream_t s);

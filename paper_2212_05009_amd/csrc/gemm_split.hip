@@ -1,5 +1,7 @@
-// C[M x N] = A[M x K] W[K x N] of fp32 operands on the bf16 matrix pipe (Sec. 3.1: the dense product with W^k), for products whose
-// arithmetic takes longer than their bytes on the fp32 pipe.
+// C[M x N] = A[M x K] W^T and dW = A^T B of fp32 operands on the bf16 matrix pipe (Sec. 3.2: the gradient handed down and that of W^k), for
+// products whose arithmetic takes longer than their bytes on the fp32 pipe.  Not the forward pass's H W: what it rounds otherwise changes
+// the sign of hidden values next to zero, and each such sign switches an element of the gradient on or off (neighbourhoods of 490: 3.5e-4 of
+// dW's norm, next to nothing of it error), so that a training step would not repeat what it gave.
 //
 // An fp32 value from 2^-108 on is the exact sum of three bf16 values: its rounding, the rounding of what is left (2^-8 of it at most), and of
 // what is then left (2^-17; 24 bits of significand are 3 x 8).  Products with smaller operands are formed on the fp32 pipe.  A product of two values is nine products, of which the six of weight 2^-18 and
@@ -24,9 +26,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct SplitArgs {
   const float* A; int64_t lda; const float* W; int64_t ldw; float* C; int64_t ldc;
   int64_t M; int N; int K;
-  const float* bias; int relu; const float* mask; int64_t ldmask; int64_t mask_rows; float* C2; int64_t ldc2;
-  int trans;               // W is stored [N x K]
-  int endC;                // nothing beyond column N of C and C2 may be written
+  const float* mask; int64_t ldmask; int64_t mask_rows;
+  int endC;                // nothing beyond column N of C may be written
 };
 
 // The six products of parts, the smallest first.  The matrix pipe aligns what it adds to the largest term and cuts off the rest, downwards: each
@@ -109,7 +110,7 @@ __device__ __forceinline__ void lds_barrier() {
 // MFMA operand and column 16 t + c of W as the first: register r of its accumulator t is column 16 t + 4 q + r of row c.
 // LDS holds W as operands, [step][tile][part][lane], 16 bytes each: all of it (RES), or two steps in turn, which the workgroup reads
 // from L2 and splits again for every pass over its rows.
-template <int NT, bool RES, bool TRANS, bool MASK, bool SAVE>
+template <int NT, bool RES, bool MASK>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_nn_split(SplitArgs a) {
   extern __shared__ u32x4 split_lds[];
   constexpr int kStep = NT * 3 * 64;                   // u32x4 of a step of W
@@ -118,42 +119,30 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int n0 = (int)blockIdx.y * (NT * 16);
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, q = lane >> 4;
-  float* bias = reinterpret_cast<float*>(split_lds + (RES ? steps : 2) * kStep);
-  for (int n = threadIdx.x; n < NT * 16; n += kThreads) bias[n] = a.bias && n0 + n < a.N ? a.bias[n0 + n] : 0.f;
 
   // piece p of a step: the eight k of one lane's operand of one tile; what lies behind K or N is answered with zeros
-  const RowsBuf wb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.W), 0, (int)((((TRANS ? a.N : a.K) - 1) * a.ldw + (TRANS ? a.K : a.N)) * 4), 0x00020000);
+  const RowsBuf wb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.W), 0, (int)(((a.N - 1) * a.ldw + a.K) * 4), 0x00020000);
   const int ldw = (int)a.ldw;
   int w_at[kPieces];
 #pragma unroll
   for (int i = 0; i < kPieces; ++i) {
     const int p = ((int)threadIdx.x + i * kThreads) % (NT * 64);      // (threads left over do another's work over again)
     const int n = n0 + 16 * (p >> 6) + (p & 15), pq = (p >> 4) & 3;
-    w_at[i] = n < a.N ? (TRANS ? n * ldw + 8 * pq : 8 * pq * ldw + n) * 4 : (int)0x80000000u;
+    w_at[i] = n < a.N ? (n * ldw + 8 * pq) * 4 : (int)0x80000000u;
   }
   auto load_w = [&](int s, int i, float (&v)[8]) {
-    if constexpr (TRANS) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const auto x = __builtin_amdgcn_raw_buffer_load_b128(wb, w_at[i] + 128 * s + 16 * h, 0, 0);
+    for (int h = 0; h < 2; ++h) {
+      const auto x = __builtin_amdgcn_raw_buffer_load_b128(wb, w_at[i] + 128 * s + 16 * h, 0, 0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[4 * h + j] = __uint_as_float(x[j]);
-      }
-    } else {
-      const int at = w_at[i] + 128 * s * ldw;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wb, at + 4 * j * ldw, 0, 0));
+      for (int j = 0; j < 4; ++j) v[4 * h + j] = __uint_as_float(x[j]);
     }
   };
-  // pair j of its values
+  // pair j of its values (behind K lies the row after it)
   auto pair_w = [&](int s, int i, int j, const float (&v)[8], float& lo, float& hi) {
-    lo = v[2 * j];
-    hi = v[2 * j + 1];
-    if (TRANS) {                                       // (behind K lies the row after it)
-      const int in = a.K - 32 * s - 8 * (((((int)threadIdx.x + i * kThreads) % (NT * 64)) >> 4) & 3) - 2 * j;
-      lo = in > 0 ? lo : 0.f;
-      hi = in > 1 ? hi : 0.f;
-    }
+    const int in = a.K - 32 * s - 8 * (((((int)threadIdx.x + i * kThreads) % (NT * 64)) >> 4) & 3) - 2 * j;
+    lo = in > 0 ? v[2 * j] : 0.f;
+    hi = in > 1 ? v[2 * j + 1] : 0.f;
   };
   // in three parts
   auto split_w = [&](int s, int i, int j, const float (&v)[8], u32x4 (&o)[3]) {
@@ -201,7 +190,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   const int64_t ntiles = (a.M + 16 * kRT - 1) / (16 * kRT);
   const int64_t stride = (int64_t)gridDim.x * kWaves;
-  const uint32_t neg = a.relu ? 0u : 0xffffffffu;
   // rows past M are answered with zeros, what a row is asked for past K is cleared
   auto rows_left = [&](int64_t tile) { return (int)(a.M - tile * (16 * kRT) < 16 * kRT ? a.M - tile * (16 * kRT) : 16 * kRT); };
   auto a_buf = [&](int64_t tile) {
@@ -239,8 +227,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   int64_t tile = gridDim.x % 8 == 0 ? (int64_t)(blockIdx.x / 8) * (8 * kWaves) + (w / kGroup) * (8 * kGroup) + (blockIdx.x % 8) * kGroup + w % kGroup
                                     : (int64_t)blockIdx.x * kWaves + w;
   const int64_t passes = (ntiles + stride - 1) / stride;
-  // The sign of a row in its first step: of an even number of bits of the row below 64, which a row keeps where the rows are handed over in
-  // parts (of whole 64).  The lane's tiles are all odd or all even (stride is a multiple of eight).
+  // The sign of a row in its first step: of an even number of bits of the row below 64.  The lane's tiles are all odd or all even (stride is a multiple of eight).
   const float sign0 = (__popc(c) + (int)(tile & 1)) & 1 ? -1.f : 1.f;
   int64_t tile_l = tile;                               // of the step asked for last
   int step_l = 0;
@@ -381,7 +368,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
           for (int t = 0; t < NT; ++t) {
             const int n = n0 + 16 * t + ce;
-            const uint32_t at = (uint32_t)(TRANS ? n * ldw + k : k * ldw + n) * 4u;
+            const uint32_t at = (uint32_t)(n * ldw + k) * 4u;
             ws[d][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wb, (int)(k < a.K && n < a.N ? at : kNoPlace), 0, 0));
           }
         }
@@ -399,13 +386,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       const int64_t row0 = tile * (16 * kRT) + 16 * rt;
       const int here = left - 16 * rt < 16 ? left - 16 * rt : 16;
       if (here <= 0) continue;
-      // (neither the places of the results nor the bias are worth registers over the products)
+      // (the places of the results are not worth registers over the products)
       int ce = c, qe = q;
       asm volatile("" : "+v"(ce), "+v"(qe) : : "memory");
       const int cend = a.endC ? a.N : (a.N + 3) & ~3;  // where the last row may be written to
       const RowsBuf cb = rows_part<float>(a.C, row0, a.ldc, here, n0, cend);
-      RowsBuf cb2 = cb;
-      if constexpr (SAVE) cb2 = rows_part<float>(a.C2, row0, a.ldc2, here, n0, cend);
       floatx4 keep[MASK ? NT : 1];
       const bool free_row = MASK && row0 + ce >= a.mask_rows;
       if constexpr (MASK) {
@@ -424,26 +409,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           const int n = 16 * t + 4 * qe;
-          const floatx4 bv = *reinterpret_cast<const floatx4*>(bias + n);
-          float pre[4], v[4];
+          u32x4 v;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            pre[r] = acc[rt][t][r] + bv[r];
-            v[r] = pre[r] > 0.f ? pre[r] : __uint_as_float(__float_as_uint(pre[r]) & neg);
-            if constexpr (MASK) v[r] = keep[t][r] > 0.f || free_row ? v[r] : 0.f;
+            v[r] = __float_as_uint(acc[rt][t][r]);
+            if constexpr (MASK) v[r] = keep[t][r] > 0.f || free_row ? v[r] : 0u;
           }
           const int left_n = a.N - n0 - n;
-          auto put = [&](RowsBuf b, int64_t ld, const float (&o)[4]) {
-            const uint32_t off = (uint32_t)(ce * (int)ld + n) * 4u;
-            __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])}, b,
-                                                   (int)(left_n > (CUT ? 3 : 0) ? off : kNoPlace), 0, 0);
-            if constexpr (CUT)
+          const uint32_t off = (uint32_t)(ce * (int)a.ldc + n) * 4u;
+          __builtin_amdgcn_raw_buffer_store_b128(v, cb, (int)(left_n > (CUT ? 3 : 0) ? off : kNoPlace), 0, 0);
+          if constexpr (CUT)
 #pragma unroll
-              for (int r = 0; r < 3; ++r)
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o[r]), b, (int)(left_n < 4 && r < left_n ? off + 4u * r : kNoPlace), 0, 0);
-          };
-          if constexpr (SAVE) put(cb2, a.ldc2, pre);
-          put(cb, a.ldc, v);
+            for (int r = 0; r < 3; ++r)
+              __builtin_amdgcn_raw_buffer_store_b32(v[r], cb, (int)(left_n < 4 && r < left_n ? off + 4u * r : kNoPlace), 0, 0);
         }
       };
       if (a.endC) finish(std::true_type());
@@ -759,12 +737,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 constexpr size_t kSplitLds = 160 * 1024;
 
 template <int NT>
-int split_launch(const SplitArgs& a, int max_blocks, hipStream_t s) {
-  const int64_t lim = max_blocks > 0 && max_blocks < 256 ? max_blocks : 256;      // (a workgroup has a compute unit to itself)
-  const size_t step = (size_t)NT * 3 * 1024, bias = sizeof(float) * 16 * NT;
+int split_launch(const SplitArgs& a, hipStream_t s) {
+  constexpr int64_t lim = 256;                         // (a workgroup has a compute unit to itself)
+  const size_t step = (size_t)NT * 3 * 1024;
   const int steps = (a.K + 31) / 32;
-  const bool res = steps * step + bias <= kSplitLds;
-  const size_t lds = (res ? steps : 2) * step + bias;
+  const bool res = steps * step <= kSplitLds;
+  const size_t lds = (res ? steps : 2) * step;
   const int64_t wgs = ceil_div(a.M, 16 * kRT * kWaves);
   const int panels = (int)ceil_div(a.N, NT * 16);
   const unsigned blocks = (unsigned)std::min<int64_t>(wgs, std::max<int64_t>(1, lim / panels));
@@ -774,14 +752,8 @@ int split_launch(const SplitArgs& a, int max_blocks, hipStream_t s) {
     GCN_CHECK_LAUNCH();
     return GCN_OK;
   };
-  auto pick = [&](auto r, auto t) -> int {
-    constexpr bool R = decltype(r)::value, T = decltype(t)::value;
-    if (a.mask) return go(k_gemm_nn_split<NT, R, T, true, false>);
-    return a.C2 ? go(k_gemm_nn_split<NT, R, T, false, true>) : go(k_gemm_nn_split<NT, R, T, false, false>);
-  };
-  using std::true_type; using std::false_type;
-  if (res) return a.trans ? pick(true_type(), true_type()) : pick(true_type(), false_type());
-  return a.trans ? pick(false_type(), true_type()) : pick(false_type(), false_type());
+  if (res) return a.mask ? go(k_gemm_nn_split<NT, true, true>) : go(k_gemm_nn_split<NT, true, false>);
+  return a.mask ? go(k_gemm_nn_split<NT, false, true>) : go(k_gemm_nn_split<NT, false, false>);
 }
 
 // tiles per wavefront, wavefronts, groups; blocks of MB x NB elements of C
@@ -809,30 +781,28 @@ int tn_splits(int64_t Kd, int M, int N) {
 
 }  // namespace
 
-// Where the fp32 kernels take longer.  Measured, their time over this kernel's for W as it is / transposed / transposed with a mask, on 4 K to 512 K rows
-// of K elements to N columns:
-//   W in registers (N = 192, 256; gemm_nn_limits_blocks)   128 -> 192 on 32 K rows 1.08 / 0.98 / 1.00, from 64 K 1.5-1.8 / 1.5-1.7 / 1.4-1.6; 256 -> 256
-//                   on 32 K 0.82 / 0.75 / 0.73, from 64 K 1.22-1.34 / 1.16-1.23 / 1.09-1.13; 128 -> 256 from 64 K 1.12-1.18 / 1.09-1.16 / 1.02-1.05,
-//                   100 -> 256 1.08-1.13 / 1.06 / 1.01, 104 -> 256 1.0 / 0.95-0.99 / 0.92-0.97: from 2^16 rows on, to 256 columns from K = 128 on;
+// Where the fp32 kernels take longer.  Measured, their time over this kernel's for W^T without / with a mask, on 4 K to 512 K rows of K elements to N
+// columns:
+//   W in registers (N = 192, 256; gemm_nn_limits_blocks)   128 -> 192 on 32 K rows 0.98 / 1.00, from 64 K 1.5-1.7 / 1.4-1.6; 256 -> 256 on 32 K
+//                   0.75 / 0.73, from 64 K 1.16-1.23 / 1.09-1.13; 128 -> 256 from 64 K 1.09-1.16 / 1.02-1.05, 100 -> 256 1.06 / 1.01, 104 -> 256
+//                   0.95-0.99 / 0.92-0.97: from 2^16 rows on, to 256 columns from K = 128 on;
 //   W in LDS, whole k steps (K <= 128 or a multiple of it)  N <= 64 0.5-1.0, N = 72 .. 128 0.9-1.4, but nothing is gained in a training step
-//                   (the pipe's clock: 2^18 x 128 x 128 83 -> 69 us, what follows 14 us longer); N = 129 .. 192 on 32 K 0.9-1.1 / 0.9-1.0 / 0.8-1.0, from 64 K
-//                   1.1-1.5 / 1.1-1.4 / 0.95-1.3 (the least at K = 48); N = 193 .. 256 on 64 K 1.06-1.19 / 1.02-1.16 / 0.88-1.04, on 512 K 1.04-1.11 / 1.01-1.11 /
-//                   0.96-1.06 up to K = 96, beyond (W's parts do not fit LDS) 0.9 / 0.9 / 0.8: from 2^16 rows on, no masks with many columns or few terms;
-//   others (K = 160, 237, 300, 602, or W too large for LDS) N <= 48 on up to 32 K 0.75-1.13 / 0.7-1.0 / 0.7-1.0, from 64 K 1.17-1.7 / 1.15-1.7 / 1.12-1.7;
-//                   N = 64 .. 128 on any number 1.1-2.3 / 1.0-2.3 / 1.05-2.5; N = 129 .. 192 on 4 K 0.9-1.14 / 0.84-1.02 / 1.2-1.3, from 8 K 1.0-2.3 /
-//                   0.97-2.3 / 1.2-2.8; N = 193 .. 400 on 4 K 0.75-0.85 / 0.66-0.75 / 0.86-0.94, on 32 K 1.1-1.65 / 1.04-1.5 / 1.3-1.6, from 64 K
-//                   1.4-1.8 / 1.3-1.8 / 1.6-2.0.
+//                   (the pipe's clock: 2^18 x 128 x 128 83 -> 69 us, what follows 14 us longer); N = 129 .. 192 on 32 K 0.9-1.0 / 0.8-1.0, from 64 K
+//                   1.1-1.4 / 0.95-1.3 (the least at K = 48); N = 193 .. 256 on 64 K 1.02-1.16 / 0.88-1.04, on 512 K 1.01-1.11 / 0.96-1.06 up to
+//                   K = 96, beyond (W's parts do not fit LDS) 0.9 / 0.8: from 2^16 rows on, no masks with many columns or few terms;
+//   others (K = 160, 237, 300, 602, or W too large for LDS) N <= 48 on up to 32 K 0.7-1.0 / 0.7-1.0, from 64 K 1.15-1.7 / 1.12-1.7;
+//                   N = 64 .. 128 on any number 1.0-2.3 / 1.05-2.5; N = 129 .. 192 on 4 K 0.84-1.02 / 1.2-1.3, from 8 K 0.97-2.3 / 1.2-2.8;
+//                   N = 193 .. 400 on 4 K 0.66-0.75 / 0.86-0.94, on 32 K 1.04-1.5 / 1.3-1.6, from 64 K 1.3-1.8 / 1.6-2.0.
 // Its error against 64 bits is a third of theirs: 128 columns of K = 128 / 602 terms of either sign 5.7e-8 / 9.6e-8 (2.0e-7 / 4.4e-7), positive
 // ones 4.2e-8 / 6.9e-8 (1.2e-7 / 2.6e-7).
 bool gemm_nn_split_ok(const void* A, int64_t lda, int64_t ldw, int64_t ldc, int64_t M, int N, int K, int dtype, const GemmEpilogue& epi) {
   const Tuning& t = tune();
-  if (t.gemm_split == 0 || dtype != GCN_F32 || (epi.mask && epi.C2)) return false;
+  if (t.gemm_split == 0 || dtype != GCN_F32 || !epi.b_trans || epi.bias || epi.relu || epi.C2) return false;
   // (tiles of rows, and W, are buffers with 32-bit offsets)
-  if (lda >= 1 << 23 || ldc >= 1 << 23 || epi.ldc2 >= 1 << 23 || epi.ldmask >= 1 << 23 || K >= 1 << 23 || ldw >= 1 << 23) return false;
-  if ((double)(epi.b_trans ? N : K) * (double)ldw * 4 >= 1 << 30) return false;
+  if (lda >= 1 << 23 || ldc >= 1 << 23 || epi.ldmask >= 1 << 23 || K >= 1 << 23 || ldw >= 1 << 23) return false;
+  if ((double)N * (double)ldw * 4 >= 1 << 30) return false;
   if (t.gemm_split == 2) return true;
-  if (t.gemm_fast != 1 || t.gemm_regw != 1 || epi.beside) return false;      // (an override is a choice between the fp32 kernels)
-  if (epi.rows > 0) M = epi.rows;
+  if (t.gemm_fast != 1 || t.gemm_regw != 1) return false;      // (an override is a choice between the fp32 kernels)
   if (gemm_nn_limits_blocks(A, lda, M, N, K, dtype)) return M >= 1 << 16 && (N <= 192 || K >= 128);
   if (gemm_nn_direct_ok(N, K) && (K <= 128 || K % 128 == 0))
     return M >= 1 << 16 && N > 128 && (N <= 192 ? K >= (epi.mask ? 60 : 48) : !epi.mask && K >= 48 && K <= 96);
@@ -842,14 +812,12 @@ bool gemm_nn_split_ok(const void* A, int64_t lda, int64_t ldw, int64_t ldc, int6
 
 int gemm_nn_split(const void* A, int64_t lda, const float* W, int64_t ldw, void* C, int64_t ldc, int64_t M, int N, int K,
                   const GemmEpilogue& epi, hipStream_t s) {
-  auto quads = [](const void* p, int64_t ld) { return ((uintptr_t)p % 16) == 0 && ld % 4 == 0; };
-  SplitArgs a{(const float*)A, lda, W, ldw, (float*)C, ldc, M, N, K, epi.bias, epi.relu, (const float*)epi.mask, epi.ldmask, epi.mask_rows,
-              (float*)epi.C2, epi.ldc2, epi.b_trans ? 1 : 0,
-              N % 4 != 0 && (!epi.c_rows_padded || !quads(C, ldc) || (epi.C2 && !quads(epi.C2, epi.ldc2)))};
-  if (N <= 64) return split_launch<4>(a, epi.max_blocks, s);
-  if (N <= 128) return split_launch<8>(a, epi.max_blocks, s);
-  if (N <= 192) return split_launch<12>(a, epi.max_blocks, s);
-  return split_launch<16>(a, epi.max_blocks, s);
+  SplitArgs a{(const float*)A, lda, W, ldw, (float*)C, ldc, M, N, K, (const float*)epi.mask, epi.ldmask, epi.mask_rows,
+              N % 4 != 0 && (!epi.c_rows_padded || ((uintptr_t)C % 16) != 0 || ldc % 4 != 0)};
+  if (N <= 64) return split_launch<4>(a, s);
+  if (N <= 128) return split_launch<8>(a, s);
+  if (N <= 192) return split_launch<12>(a, s);
+  return split_launch<16>(a, s);
 }
 
 // More than 64 columns on both sides (300 K rows x 128 x 64 78 / 89 us, x 602 x 16 243 / 323: there the product waits for memory, and 32 rows in flight

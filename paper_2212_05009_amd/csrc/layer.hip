@@ -271,10 +271,8 @@ static int layer_fwd(const gcn_csr_t* A, const void* H, int64_t ldh, bool h_back
         GemmEpilogue epi;
         epi.bias = bias; epi.relu = relu; epi.C2 = Z; epi.ldc2 = ldz;
         epi.c_rows_padded = true;
-        epi.rows = A->nr;
-        const bool can_follow = !fused && !spmm_panel_wanted(sp) && gemm_nn_limits_blocks(AH, ldAH, A->nr, d_out, d_in, dtype);
-        epi.beside = can_follow && long_sparse(A->nr, A->nnz, d_in);      // (the same kernel whether or not the overlap is switched off)
-        const bool pipelined = can_follow && side_chunks() > 0 && overlap_worthwhile(A->nr, A->nnz, d_in);
+        const bool pipelined = !fused && side_chunks() > 0 && overlap_worthwhile(A->nr, A->nnz, d_in) && !spmm_panel_wanted(sp) &&
+                               gemm_nn_limits_blocks(AH, ldAH, A->nr, d_out, d_in, dtype);
         if (fused) {
           GCN_TRY(spmm_dense(sp, hub, W, d_out, Hout, ldo, d_out, epi, s));
         } else if (!pipelined) {

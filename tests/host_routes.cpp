@@ -2,7 +2,8 @@
 // host memory, kernels do nothing, launches are written down by name) and links the library.
 //   host_routes <overlap> <call> <d_in> <d_out> <ld> [<rows>]      one line per launch: kernel, workgroups, main | side
 // call: fwd | bwd; the graph has 2^17 rows and 10^8 entries, long enough for dense products beside its sparse ones.  <ld>: the pitch of A^ H.
-//       dense: the dense product alone; grad: the weight gradient alone; on a graph of <rows> rows and entries.
+//       dense: the dense product alone; grad: the weight gradient alone; down, masked: the gradient handed down as well, without and with the mask of
+//       the layer before; on a graph of <rows> rows and entries.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -86,6 +87,9 @@ int main(int argc, char** argv) {
   const int rc = !strcmp(argv[2], "dense") ? gcn_dense_fwd(p, ld, n, p, nullptr, d_in, d_out, GCN_ACT_RELU, GCN_F32, nullptr, p + 64, round_up(d_out, 4), nullptr)
                  : !strcmp(argv[2], "grad") ? gcn_layer_bwd_ld(&A, p, round_up(d_in, 4), p + 64, ld, p, d_in, d_out, GCN_F32, p + 128, round_up(d_out, 2), nullptr, 0, p + 256,
                                                              nullptr, nullptr, 0, nullptr)
+                 : !strcmp(argv[2], "down") || !strcmp(argv[2], "masked")
+                     ? gcn_layer_bwd_ld(&A, p, round_up(d_in, 4), p + 64, ld, p, d_in, d_out, GCN_F32, p + 128, round_up(d_out, 4), argv[2][0] == 'm' ? p + 192 : nullptr,
+                                        round_up(d_in, 4), p + 256, nullptr, p + 320, round_up(d_in, 4), nullptr)
                  : !strcmp(argv[2], "fwd")
                      ? gcn_layer_fwd_ld(&A, p, round_up(d_in, 4), p, nullptr, d_in, d_out, GCN_ACT_RELU, GCN_F32, nullptr, 0, p + 64, round_up(d_out, 4), p + 128, ld, nullptr)
                      : gcn_layer_bwd_ld(&A, p, round_up(d_in, 4), p + 64, ld, p, d_in, d_out, GCN_F32, p + 128, round_up(d_out, 4), p + 192, round_up(d_in, 4), p + 256,

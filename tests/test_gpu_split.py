@@ -235,3 +235,112 @@ def test_one_small_operand_among_ordinary_ones(gcn, dev, tuned, d_in, d_out):
     gcn.gcn_dense_fwd(X, W, out)
     assert bool(((out.double() - X.double() @ W.double()).abs() <= 1e-5 * (X.double().abs() @ W.double().abs())).all())
     case.A.free()
+
+
+# The same of G W^T, which a layer hands down (A^ = I: the sparse product changes nothing): K = d_out terms to d_in columns.
+def handed_down(gcn, dev, G, W, Zprev=None):
+    import torch
+    rows, d_in = G.shape[0], W.shape[0]
+    case = rows_alone(gcn, dev, rows)
+    dH = torch.empty(rows, d_in, device=dev)
+    H = torch.zeros(rows, d_in, device=dev)
+    gcn.gcn_layer_bwd(case.A, H, W, G, torch.empty_like(W), dH=dH, Zprev=Zprev)
+    torch.cuda.synchronize()
+    case.A.free()
+    return dH
+
+
+def draw(dev, seed, rows, d_in, d_out, kind="signed"):
+    import torch
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(seed)
+    G = torch.randn(rows, d_out, generator=gen, device=dev)
+    W = torch.randn(d_in, d_out, generator=gen, device=dev)
+    if kind != "signed":
+        G.clamp_(min=0)
+    if kind == "positive":
+        W.abs_()
+    return gen, G, W
+
+
+@pytest.mark.parametrize("kind", ["signed", "relu", "positive"])
+@pytest.mark.parametrize("rows,d_in,d_out", [(20000, 200, 128), (20000, 128, 602), (70144, 256, 256), (65536, 130, 48)])
+def test_gradient_handed_down_is_no_less_exact(gcn, dev, tuned, kind, rows, d_in, d_out):
+    gen, G, W = draw(dev, rows + d_in, rows, d_in, d_out, kind)
+    ref, err, summed = G.double() @ W.double().T, {}, {}
+    few = rows // 512 * 512
+    for mode in (0, 2):
+        tuned("GCN_GEMM_SPLIT", mode)
+        dH = handed_down(gcn, dev, G, W)
+        err[mode] = error(dH, ref)
+        summed[mode] = error(dH[:few].double().view(-1, 512, d_in).sum(1), ref[:few].view(-1, 512, d_in).sum(1))
+    print(kind, rows, d_in, d_out, err, summed, flush=True)
+    assert err[2] <= err[0] and summed[2] <= summed[0]
+
+
+@pytest.mark.parametrize("terms,bound", [(1, 1.04), (2, 1.42), (3, 1.42), (8, 1.42), (32, 1.0)])
+@pytest.mark.parametrize("d_in,d_out", [(130, 100), (128, 602), (256, 256)])
+def test_gradient_handed_down_of_few_terms(gcn, dev, tuned, terms, bound, d_in, d_out):
+    import torch
+    rows = 8193
+    gen, G, W = draw(dev, terms + d_in, rows, d_in, d_out)
+    G = torch.where(torch.rand(rows, d_out, generator=gen, device=dev).argsort(1).argsort(1) < terms, G, torch.zeros_like(G))
+    err = {}
+    for mode in (0, 2):
+        tuned("GCN_GEMM_SPLIT", mode)
+        err[mode] = error(handed_down(gcn, dev, G, W), G.double() @ W.double().T)
+    print(terms, d_in, d_out, err, flush=True)
+    assert err[2] <= bound * err[0]
+
+
+@pytest.mark.parametrize("d_in,d_out", [(173, 100), (256, 256), (64, 130), (300, 64)])
+@pytest.mark.parametrize("masked", [False, True])
+def test_gradient_handed_down_of_infinities_nan_and_the_largest_numbers(gcn, dev, tuned, d_in, d_out, masked):
+    import torch
+    rows = 9000
+    gen, G, W = draw(dev, 7, rows, d_in, d_out)
+    G[3, 5], G[40, 0], G[41, d_out - 1], G[rows - 1, 7] = float("inf"), float("-inf"), float("nan"), float("inf")
+    G[100] = 0
+    G[100, 2], W[:, 2] = 3.4e38, W[:, 2].sign()                # a product next to the largest number; its first part is none
+    Z = torch.randn(rows, d_in, generator=gen, device=dev) if masked else None
+    ref, scale = G.double() @ W.double().T, G.double().abs() @ W.double().abs().T
+    tuned("GCN_GEMM_SPLIT", 2)
+    got = handed_down(gcn, dev, G, W, Zprev=Z)
+    if masked:
+        assert bool((got[Z <= 0] == 0).all())                  # whatever the product was
+        got, ref, scale = got[Z > 0], ref[Z > 0], scale[Z > 0]
+    inf, nan = torch.isinf(ref), torch.isnan(ref)
+    assert inf.any() and nan.any() and torch.equal(torch.isnan(got), nan)
+    assert torch.equal(got[inf].double(), ref[inf])
+    ok = ~(inf | nan)
+    assert bool(((got.double() - ref).abs()[ok] <= 1e-5 * scale[ok]).all())
+
+
+@pytest.mark.parametrize("small_g,small_w", [(1e-34, 1.0), (1e-38, 1.0), (1.0, 1e-37), (1e-20, 1e-17), (2.0**-120, 2.0**40), (2.0**40, 2.0**-120), (2.0**-137, 2.0**60),
+                                             (2.0**60, 2.0**-137), (1e-41, 1e30), (1e30, 1e-41), (2.0**-107, 2.0**80), (2.0**-70, 2.0**-70)])
+def test_gradient_handed_down_of_operands_near_the_smallest_number(gcn, dev, tuned, small_g, small_w):
+    gen, G, W = draw(dev, 11, 9000, 130, 100)
+    G, W = G * small_g, W * small_w
+    tuned("GCN_GEMM_SPLIT", 2)
+    got, a, b = handed_down(gcn, dev, G, W), G.double(), W.double().T
+    tiny = a.shape[1] * 2.0 ** -149
+    assert bool(((got.double() - a @ b).abs() <= 1e-5 * (a.abs() @ b.abs()) + tiny).all())
+
+
+@pytest.mark.parametrize("d_in,d_out", [(130, 100), (65, 602), (256, 256)])
+def test_gradient_handed_down_of_one_small_operand_among_ordinary_ones(gcn, dev, tuned, d_in, d_out):
+    rows = 70001
+    gen, G, W = draw(dev, d_in, rows, d_in, d_out)
+    at = [(0, 0), (31, d_out - 1), (32, 33), (255, 64), (256, 1), (20000, 31), (65535, 32), (65536, 5), (65541, d_out - 2), (69999, 2), (70000, d_out - 3)]
+    for r, k in at + [(17, 40)]:
+        G[r], G[:, k] = 0, 0
+    for r, k in at:
+        G[r, k] = 1e-40
+        W[:, k] *= 1e32
+    W[3, 40], G[17, 40] = 1e-40, 1e32
+    tuned("GCN_GEMM_SPLIT", 2)
+    for last in (1e-40, 1.0):                                  # W with one, and without: then only the tiles that hold them are formed again
+        W[3, 40] = last
+        a, b = G.double(), W.double().T
+        got = handed_down(gcn, dev, G, W).double()
+        assert bool(((got - a @ b).abs() <= 1e-5 * (a.abs() @ b.abs())).all())

@@ -32,12 +32,14 @@ def dense(program, overlap, call, d_in, d_out, ld, *rows):
 CUS = 64        # compute units of a dense product beside a sparse one (GCN_OVERLAP_CUS)
 
 
-# No kernel that keeps to a few compute units takes these products: of 173 columns, of 201 terms in rows of odd pitch.  They run alone, in three parts.
+# The forward pass keeps the rounding of the fp32 pipe (hidden values next to zero keep their sign), beside a sparse product, behind one, or alone.
 @pytest.mark.parametrize("overlap", [0, 1])
-@pytest.mark.parametrize("d_in,d_out,ld", [(100, 173, 100), (201, 256, 201), (96, 130, 96)])
-def test_a_forward_product_that_cannot_follow_runs_alone_in_three_parts(program, overlap, d_in, d_out, ld):
-    launches = dense(program, overlap, "fwd", d_in, d_out, ld)
-    assert len(launches) == 1 and "k_gemm_nn_split" in launches[0][0] and launches[0][2] == "main", launches
+@pytest.mark.parametrize("call,d_in,d_out,ld,rows", [("fwd", 100, 173, 100, []), ("fwd", 201, 256, 201, []), ("fwd", 96, 130, 96, []), ("fwd", 602, 128, 602, []),
+                                                     ("fwd", 256, 256, 256, []), ("dense", 602, 128, 602, [232965]), ("dense", 256, 256, 256, [500000]),
+                                                     ("dense", 300, 256, 300, [1 << 18]), ("dense", 600, 400, 600, [1 << 18])])
+def test_forward_products_are_not_in_three_parts(program, overlap, call, d_in, d_out, ld, rows):
+    launches = dense(program, overlap, call, d_in, d_out, ld, *rows)
+    assert launches and not any("split" in k for k, _, _ in launches), launches
 
 
 @pytest.mark.parametrize("d_in,d_out", [(256, 256), (100, 256), (128, 192)])
@@ -64,13 +66,16 @@ def test_a_gradient_is_beside_the_sparse_product_only_on_its_own_compute_units(p
 
 
 # Sizes from which the three-part kernels were measured to gain: on both sides of the lines, and where they never do.
-@pytest.mark.parametrize("d_in,d_out,rows,split", [(256, 256, 1 << 16, True), (256, 256, (1 << 16) - 1, False), (128, 192, 1 << 16, True), (100, 256, 500000, False),
-                                                   (101, 256, 500000, False), (61, 256, 1 << 16, True), (61, 256, (1 << 16) - 1, False), (47, 256, 500000, False),
-                                                   (128, 128, 500000, False), (300, 41, 1 << 16, True), (300, 41, 1 << 15, False), (300, 64, 4096, True), (368, 173, 8192, True), (368, 173, 8191, False),
-                                                   (300, 256, 1 << 15, True), (300, 256, (1 << 15) - 1, False), (600, 400, 1 << 14, True), (600, 400, 4096, False)])
-def test_sizes_of_products_in_three_parts(program, d_in, d_out, rows, split):
-    launches = dense(program, 1, "dense", d_in, d_out, d_in, rows)
-    assert len(launches) == 1 and ("k_gemm_nn_split" in launches[0][0]) == split, launches
+@pytest.mark.parametrize("terms,columns,rows,split,masked", [
+    (256, 256, 1 << 16, True, True), (256, 256, (1 << 16) - 1, False, False), (128, 192, 1 << 16, True, True), (100, 256, 500000, False, False),
+    (101, 256, 500000, False, False), (61, 256, 1 << 16, True, False), (61, 256, (1 << 16) - 1, False, False), (47, 256, 500000, False, False),
+    (128, 128, 500000, False, False), (300, 41, 1 << 16, True, True), (300, 41, 1 << 15, False, False), (300, 64, 20000, True, True), (368, 173, 8193, True, True),
+    (368, 173, 8191, False, False), (300, 256, 1 << 15, True, True), (300, 256, (1 << 15) - 1, False, False), (600, 400, 1 << 14, True, True),
+    (600, 400, 9000, False, False)])
+def test_sizes_of_products_in_three_parts(program, terms, columns, rows, split, masked):
+    for call, want in (("down", split), ("masked", masked if columns > terms else split)):       # (else the sparse product is last, and takes the mask)
+        launches = [k for k, _, _ in dense(program, 1, call, columns, terms, columns, rows) if "gemm_nn" in k]
+        assert len(launches) == 1 and ("k_gemm_nn_split" in launches[0]) == want, (call, launches)
 
 
 @pytest.mark.parametrize("d_in,d_out,rows,split", [(256, 256, 2048, True), (256, 256, 2047, False), (80, 200, 2048, True), (72, 72, 20000, False), (72, 72, 1 << 17, True),
