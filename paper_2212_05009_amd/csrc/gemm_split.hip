@@ -791,7 +791,8 @@ int tn_splits(int64_t Kd, int M, int N) {
 //                   1.1-1.4 / 0.95-1.3 (the least at K = 48); N = 193 .. 256 on 64 K 1.02-1.16 / 0.88-1.04, on 512 K 1.01-1.11 / 0.96-1.06 up to
 //                   K = 96, beyond (W's parts do not fit LDS) 0.9 / 0.8: from 2^16 rows on, no masks with many columns or few terms;
 //   others (K = 160, 237, 300, 602, or W too large for LDS) N <= 48 on up to 32 K 0.7-1.0 / 0.7-1.0, from 64 K 1.15-1.7 / 1.12-1.7;
-//                   N = 64 .. 128 on any number 1.0-2.3 / 1.05-2.5; N = 129 .. 192 on 4 K 0.84-1.02 / 1.2-1.3, from 8 K 0.97-2.3 / 1.2-2.8;
+//                   N = 64 .. 128 with W in LDS on up to 64 rows 0.80-0.95, from 128 1.05-1.17, but N = 50, 64 and rows of whole quads up to 3 K 0.94-1.0;
+//                   else on any number 1.0-2.3 / 1.05-2.5; N = 129 .. 192 on 4 K 0.84-1.02 / 1.2-1.3, from 8 K 0.97-2.3 / 1.2-2.8;
 //                   N = 193 .. 400 on 4 K 0.66-0.75 / 0.86-0.94, on 32 K 1.04-1.5 / 1.3-1.6, from 64 K 1.3-1.8 / 1.6-2.0.
 // Its error against 64 bits is a third of theirs: 128 columns of K = 128 / 602 terms of either sign 5.7e-8 / 9.6e-8 (2.0e-7 / 4.4e-7), positive
 // ones 4.2e-8 / 6.9e-8 (1.2e-7 / 2.6e-7).
@@ -807,6 +808,7 @@ bool gemm_nn_split_ok(const void* A, int64_t lda, int64_t ldw, int64_t ldc, int6
   if (gemm_nn_direct_ok(N, K) && (K <= 128 || K % 128 == 0))
     return M >= 1 << 16 && N > 128 && (N <= 192 ? K >= (epi.mask ? 60 : 48) : !epi.mask && K >= 48 && K <= 96);
   if (N <= 48) return M >= 1 << 16;
+  if (gemm_nn_direct_ok(N, K) && M < (N <= 64 && K % 4 == 0 ? 1 << 13 : 65)) return false;
   return N <= 128 || (N <= 192 ? M >= 1 << 13 : M * ceil_div(N, 256) >= 1 << 15);
 }
 

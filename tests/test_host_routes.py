@@ -71,7 +71,8 @@ def test_a_gradient_is_beside_the_sparse_product_only_on_its_own_compute_units(p
     (101, 256, 500000, False, False), (61, 256, 1 << 16, True, False), (61, 256, (1 << 16) - 1, False, False), (47, 256, 500000, False, False),
     (128, 128, 500000, False, False), (300, 41, 1 << 16, True, True), (300, 41, 1 << 15, False, False), (300, 64, 20000, True, True), (368, 173, 8193, True, True),
     (368, 173, 8191, False, False), (300, 256, 1 << 15, True, True), (300, 256, (1 << 15) - 1, False, False), (600, 400, 1 << 14, True, True),
-    (600, 400, 9000, False, False)])
+    (600, 400, 9000, False, False), (237, 100, 65, True, True), (237, 100, 64, False, False), (300, 64, 8191, False, False), (300, 64, 8192, True, True),
+    (237, 64, 65, True, True), (602, 100, 1, True, True)])
 def test_sizes_of_products_in_three_parts(program, terms, columns, rows, split, masked):
     for call, want in (("down", split), ("masked", masked if columns > terms else split)):       # (else the sparse product is last, and takes the mask)
         launches = [k for k, _, _ in dense(program, 1, call, columns, terms, columns, rows) if "gemm_nn" in k]
