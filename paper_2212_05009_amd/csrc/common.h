@@ -189,6 +189,7 @@ template <typename T> __device__ __forceinline__ void store_one(T* p, float v) {
 // and the chunking; the matrix arrays stay in row order.
 constexpr int kHubRowNnz = 2048;
 constexpr int kHubChunkNnz = 1024;
+constexpr int kGiantChunks = 192;   // rows of more chunks than these are giant rows (induced.hip)
 
 constexpr int kRowChunks = 8;      // row ranges a sparse product can be launched on separately (or on runs of them)
 
@@ -200,6 +201,7 @@ struct Schedule {
   int64_t* hub_chunk_ptr = nullptr;  // [n_hub_rows+1] first chunk of each hub row
   int32_t* chunk_hub = nullptr;      // [n_chunks] index into hub_rows of each chunk
   int64_t n_chunks = 0;
+  int64_t n_giant_rows = 0;          // of more than kGiantChunks chunks
   // host copy: rows of length class c (lengths in [2^(31-c), 2^(32-c)); class 32 = empty rows) are
   // wave_rows[class_begin[c] .. class_begin[c+1]); classes are stored longest first.
   int64_t class_begin[34] = {0};

@@ -276,22 +276,22 @@ __global__ void k_finish_csc(const uint64_t* __restrict__ tkeys, int64_t nnz, in
 
 // ---- schedules ------------------------------------------------------------------------------------------
 // A schedule is a stable counting sort of the rows by length class.  Ordinary rows have at most kHubRowNnz entries: 13
-// classes, code 0 for [2^11, 2^12) down to 11 for one entry, 12 for none; code 13 are the hub rows, and slot 14 counts their
-// chunks of entries.  Three launches serve both schedules of a handle: rows of each code per block, one scan, placement.
+// classes, code 0 for [2^11, 2^12) down to 11 for one entry, 12 for none; code 13 are the hub rows, slot 14 counts their
+// chunks of entries, slot 15 those of more than kGiantChunks (as a code: no row).  Three launches serve both schedules of a handle: rows of each code per block, one scan, placement.
 // What bounds this is the launches, about 5 us each whatever they do, not the 16 bytes a row: against keys, scans, a radix
 // pass and list kernels per schedule (28 launches) an R-MAT 2^18 build takes 1170 instead of 1287 us, a training step on a
 // mini-batch of 20 K vertices 525 instead of 649.
 constexpr int kSchedSlots = 16;
 constexpr int kSchedCodes = 13;                      // classes of ordinary rows
-constexpr int kHubCode = 13, kChunkSlot = 14;
+constexpr int kHubCode = 13, kChunkSlot = 14, kGiantSlot = 15;
 constexpr int kSchedSteps = 2;                       // rows per lane (8: longer code, 13 instead of 5 us for 40 K rows)
 constexpr int kSchedTile = kThreads * kSchedSteps;   // rows per block; a wavefront takes 64 kSchedSteps consecutive ones
 // What the host keeps: kSchedCodes + 1 class boundaries, then for each row boundary of the launches on row ranges the first
-// position of every class, the first hub row and its first chunk at or behind that row, then the number of hub rows and of chunks.
+// position of every class, the first hub row and its first chunk at or behind that row, then the number of hub rows, of chunks and of giant rows.
 constexpr int kSchedTable = kSchedCodes + 1;
 constexpr int kSchedCounts = kSchedTable + (kRowChunks + 1) * (kSchedCodes + 2);
-constexpr int kSchedWords = kSchedCounts + 2;
-static_assert(kHubRowNnz == 2048 && kChunkSlot < kSchedSlots && kThreads == 256, "the codes above");
+constexpr int kSchedWords = kSchedCounts + 3;
+static_assert(kHubRowNnz == 2048 && kGiantSlot == kSchedSlots - 1 && kThreads == 256, "the codes above");
 static_assert(2 * kSchedWords * sizeof(int64_t) <= kPinnedBytes, "both schedules of a handle are read back in one page");
 
 struct SchedJob {
@@ -311,7 +311,7 @@ __device__ __forceinline__ uint32_t row_chunks(int64_t len) {
 }
 
 struct SchedRank { uint32_t row, chunk; };     // rows of the lane's code, chunks, in the lanes before it
-// 64 rows, one per lane: adds those of code `lane` (the chunks, in lane kChunkSlot) to *seen
+// 64 rows, one per lane: adds those of code `lane` (the chunks, in lane kChunkSlot, the giant rows, in lane kGiantSlot) to *seen
 __device__ __forceinline__ SchedRank sched_step(int code, uint32_t chunks, int lane, uint32_t* seen) {
   const uint64_t lt = (1ull << lane) - 1ull;
   uint64_t peers = ~0ull, mine = ~0ull;    // lanes with this lane's code; lanes of code `lane`
@@ -333,6 +333,8 @@ __device__ __forceinline__ SchedRank sched_step(int code, uint32_t chunks, int l
     r.chunk = inc - chunks;
     const uint32_t all = __shfl(inc, 63, 64);
     if (lane == kChunkSlot) *seen += all;
+    const uint32_t giants = (uint32_t)__popcll(__ballot(chunks > (uint32_t)kGiantChunks));
+    if (lane == kGiantSlot) *seen += giants;
   }
   return r;
 }
@@ -350,7 +352,7 @@ __global__ __launch_bounds__(kThreads) void k_sched_count(SchedJobs jobs) {
   for (int k = 0; k < kSchedSteps; ++k) {
     const int64_t i = blk * kSchedTile + k * kThreads + threadIdx.x;
     const int64_t len = i < a.n ? a.ptr[i + 1] - a.ptr[i] : 0;
-    sched_step(i < a.n ? row_code(len) : kSchedSlots - 1, row_chunks(len), lane, &seen);
+    sched_step(i < a.n ? row_code(len) : kGiantSlot, row_chunks(len), lane, &seen);
   }
   if (lane < kSchedSlots) wave_cnt[w][lane] = seen;
   __syncthreads();
@@ -403,6 +405,7 @@ __global__ __launch_bounds__(64 * kSchedSlots) void k_sched_scan(SchedJobs jobs)
   }
   a.info[kSchedCounts] = total[kHubCode];
   a.info[kSchedCounts + 1] = total[kChunkSlot];
+  a.info[kSchedCounts + 2] = total[kGiantSlot];
   a.hub_chunk_ptr[0] = 0;
   for (int j = 0; j <= kRowChunks; ++j) {
     if (a.bound[j] < a.n) continue;
@@ -431,7 +434,7 @@ __global__ __launch_bounds__(kThreads) void k_sched_place(SchedJobs jobs) {
   for (int k = 0; k < kSchedSteps; ++k) {
     const int64_t i = row0 + 64 * k + lane;
     const int64_t len = i < a.n ? a.ptr[i + 1] - a.ptr[i] : 0;
-    code[k] = i < a.n ? row_code(len) : kSchedSlots - 1;
+    code[k] = i < a.n ? row_code(len) : kGiantSlot;
     chunks[k] = row_chunks(len);
   }
   uint32_t seen = 0;
@@ -535,6 +538,7 @@ struct ScheduleBuild {
     *out = Schedule();
     out->n_hub_rows = h[kSchedCounts];
     out->n_chunks = h[kSchedCounts + 1];
+    out->n_giant_rows = h[kSchedCounts + 2];
     out->n_wave_rows = jobs.j[k].n - out->n_hub_rows;
     for (int c = 0; c < 34; ++c) out->class_begin[c] = c < kFirst ? 0 : h[c - kFirst];
     for (int j = 0; j <= kRowChunks; ++j) {

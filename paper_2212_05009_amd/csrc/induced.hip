@@ -4,9 +4,11 @@
 //
 // The subgraph is a graph of its own: vertex k is vertices[k], its edges are the stored entries
 // (vertices[a], vertices[b]) of the parent, and degrees, self-loops and D^-1/2 (A'+I) D^-1/2 are
-// those of the subgraph.  The entries of the selected rows whose columns are selected too become
-// (row, column) keys in subgraph numbering, one pass over those rows, and the keys go through the
-// builder's second half, so sorting, normalisation and the column-major copy are the builder's.
+// those of the subgraph.  Two ways, the same arrays:
+//   row by row   the parent's selected rows and columns, each filtered and sorted by itself, two passes over them;
+//   by keys      the entries of the selected rows whose columns are selected too become (row, column) keys in subgraph
+//                numbering, one pass over those rows, and the keys go through the builder's second half, so sorting,
+//                normalisation and the column-major copy are the builder's.
 #include <algorithm>
 #include <new>
 #include <type_traits>
@@ -139,6 +141,14 @@ __global__ __launch_bounds__(kIndThreads) void k_ind_keys(const int32_t* __restr
 constexpr int kIndLanes = 16, kIndShort = 64;              // lanes of a short row; its entries
 constexpr int kIndWave = 1024;                             // entries that a wavefront takes of a row
 constexpr int kIndRank = 256;
+// A block with more pieces than these, and one more for every 1024 vertices, leaves its hub rows to launches of their own, whose blocks share the
+// pieces of every such row: the call would wait for that one block, 1.1 us a piece in both passes.  Us with the pieces of a block as they come / this way /
+// by keys: the 1000 vertices of 2^20 R-MAT ones with the longest rows, longest first 1735 / 399 / 534, in random order 737 / 371 / 535; 20 K of 2^18
+// 869 / 422 / 681, 400 / 401 / 670; random ones 118 / 119 / 214.  Leaving every hub row to them costs a launch and a longer chain of requests
+// where none is that long (134).  Slower than by keys: 20 K of 2.45 M, longest first, 50 M entries of which few stay, 5202 / 2791 / 2139 (columns are
+// read too, and both twice).
+constexpr int kIndOver = 96, kIndShare = 16;               // (blocks that share a row)
+static_assert(kIndOver >= 32 * kHubRowNnz / kIndWave, "what a block keeps is fewer pieces");
 constexpr int kIndU = 8;                                   // entries a lane asks for together
 // The number of entries is added up on so many words, whose sum the host takes: additions to one word are 14 ns each, one after the other
 constexpr int kIndSums = 128;
@@ -147,9 +157,10 @@ constexpr int64_t kIndMaxSub = (int64_t)1 << 20;
 // leave room for few blocks on a compute unit: the rows that take one are then done by a launch of their own.
 constexpr int64_t kIndOwnOffsets = (int64_t)1 << 15;
 constexpr int kIndThreadsRows = 512, kIndMany = 1024;
+constexpr int kIndWaves = kIndThreadsRows / 64, kIndJobs = kIndThreadsRows / kIndLanes;      // of a block: wavefronts, rows
 // staging: 64 entries a row, or kIndRank a wavefront
-constexpr size_t ind_stage(int threads) { return sizeof(int32_t) * (size_t)(threads / kIndLanes * kIndShort); }
-static_assert(ind_stage(kIndThreadsRows) == sizeof(int32_t) * kIndThreadsRows / 64 * kIndRank, "one staging area");
+constexpr size_t kIndStage = sizeof(int32_t) * kIndJobs * kIndShort;
+static_assert(kIndStage == sizeof(int32_t) * kIndWaves * kIndRank, "one staging area");
 
 struct IndRows {
   const int32_t* vertices; int64_t n_sub, n; const int32_t* lid;
@@ -163,6 +174,9 @@ struct IndRows {
   int maps;                                                // bitmaps side by side, a power of two up to the wavefronts
   // rows that take one, where they are done by themselves: kIndSums lists of up to map_ld
   int64_t* map_list; int64_t map_ld; int* map_count;
+  // hub rows left over by the counting blocks: their number, [rows], and of each the pieces counted (from bit 40 on) and entries kept
+  int64_t* n_over; int64_t* over; unsigned long long* over_kept; int64_t max_over;
+  int hubs_listed;                                         // every hub row is left to k_ind_maps
 };
 
 // a row of the parent: its ends
@@ -188,9 +202,13 @@ __device__ __forceinline__ void ind_entries(const int32_t* __restrict__ idx, con
   for (int u = 0; u < kIndU; ++u) c[u] = c[u] >= 0 ? lid[c[u]] : -1;
 }
 
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ind_count(IndRows a) {
-  constexpr int kIndWaves = THREADS / 64, kIndJobs = THREADS / kIndLanes;
+constexpr uint32_t kIndHub = 0xffffffffu;                  // in the place of a count
+__device__ __forceinline__ void ind_counted(const IndRows& a, int side, int64_t k, uint32_t n) {
+  a.cnt[side * a.cnt_ld + k] = n;
+  if (side == 0) { a.deg[k] = (int32_t)n; a.dinv[k] = inv_sqrt_deg(n > 0 ? (int32_t)n : 1); }
+}
+
+__global__ __launch_bounds__(kIndThreadsRows) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ind_count(IndRows a) {
   __shared__ uint32_t kept[kIndJobs];
   __shared__ int pieces[kIndJobs + 1];                     // (rows in pieces, their number; then a running sum)
   __shared__ int piece_job[kIndJobs];
@@ -240,10 +258,19 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
     pieces[n_rows] = run;
   }
   __syncthreads();
+  const bool over = pieces[n_rows] > kIndOver + (int)(a.n_sub >> 10);
   for (int i = w, row = 0; i < pieces[n_rows]; i += kIndWaves) {
     while (pieces[row + 1] <= i) ++row;
     const int at = piece_job[row];
     const IndJob j = ends[at];
+    if (over && j.len > kHubRowNnz) {
+      if (i == pieces[row] && lane == 0) {
+        kept[at] = kIndHub;
+        const int64_t to = (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(a.n_over), 1ull);
+        if (to < a.max_over) a.over[to] = side * a.n_sub + k0 + at;            // (more only of a vertex listed again)
+      }
+      continue;
+    }
     const int64_t e_lo = (int64_t)(i - pieces[row]) * kIndWave, e_hi = e_lo + kIndWave < j.len ? e_lo + kIndWave : j.len;
     uint32_t n = 0;
     for (int64_t e0 = e_lo; e0 < e_hi; e0 += 64 * kIndU) {
@@ -260,15 +287,44 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
   if (w == 0) {
     static_assert(kIndJobs <= 64, "a row per lane");
     const int64_t k = k0 + lane;
-    const bool mine = lane < kIndJobs && k < a.n_sub;
+    const bool mine = lane < kIndJobs && k < a.n_sub && kept[lane] != kIndHub;
     uint32_t n = mine ? kept[lane] : 0u;
-    if (mine) {
-      a.cnt[side * a.cnt_ld + k] = n;
-      if (side == 0) { a.deg[k] = (int32_t)n; a.dinv[k] = inv_sqrt_deg(n > 0 ? (int32_t)n : 1); }
-    }
+    if (mine) ind_counted(a, side, k, n);
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) n += __shfl_xor(n, o, 64);
     if (lane == 0 && side == 0) atomicAdd(reinterpret_cast<unsigned long long*>(a.nnz + blk % kIndSums), (unsigned long long)n);
+  }
+}
+
+// The hub rows left over: whoever counts a row's last piece writes its number down.
+__global__ __launch_bounds__(kIndThreadsRows) void k_ind_count_over(IndRows a, int64_t rows) {
+  const int lane = threadIdx.x & 63;
+  for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
+    const int64_t job = a.over[r], side = job >= a.n_sub ? 1 : 0, k = job - side * a.n_sub;
+    const IndJob j = ind_job(a, (int)side, k);
+    const int64_t pieces = (j.len + kIndWave - 1) / kIndWave;
+    uint32_t n = 0;
+    int64_t done = 0;
+    for (int64_t p = (int64_t)blockIdx.y * kIndWaves + (threadIdx.x >> 6); p < pieces; p += kIndShare * kIndWaves, ++done) {
+      const int64_t e_hi = (p + 1) * kIndWave < j.len ? (p + 1) * kIndWave : j.len;
+      for (int64_t e0 = p * kIndWave; e0 < e_hi; e0 += 64 * kIndU) {
+        int32_t c[kIndU];
+        ind_entries(a.idx[side], a.lid, j.s, e0, e_hi, lane, c);
+#pragma unroll
+        for (int u = 0; u < kIndU; ++u) n += c[u] >= 0 ? 1u : 0u;
+      }
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) n += __shfl_xor(n, o, 64);
+    if (lane == 0 && done > 0) {
+      typedef unsigned long long u64;
+      const u64 mine = ((u64)done << 40) + n, now = atomicAdd(a.over_kept + r, mine) + mine;
+      if ((int64_t)(now >> 40) == pieces) {
+        const uint32_t all = (uint32_t)(now & (((u64)1 << 40) - 1));
+        ind_counted(a, (int)side, k, all);
+        if (side == 0) atomicAdd(reinterpret_cast<u64*>(a.nnz + k % kIndSums), (u64)all);
+      }
+    }
   }
 }
 
@@ -346,10 +402,9 @@ __device__ __forceinline__ void ind_maps(const IndRows& a, uint32_t* __restrict_
   __syncthreads();
 }
 
-// MAPS: the rows that take a bitmap are done here too, else they are listed for k_ind_maps.
-template <int THREADS, bool MAPS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ind_fill(IndRows a) {
-  constexpr int kIndWaves = THREADS / 64, kIndJobs = THREADS / kIndLanes;
+// MAPS: the rows that take a bitmap are done here too, but for listed hub rows; else they are listed for k_ind_maps.
+template <bool MAPS>
+__global__ __launch_bounds__(kIndThreadsRows) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ind_fill(IndRows a) {
   extern __shared__ __align__(16) int32_t ind_lds[];                     // staging, then the bitmaps
   __shared__ int64_t offset[kIndJobs];                 // first entry of a row of the block
   __shared__ uint32_t kept[kIndJobs];
@@ -370,7 +425,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
     static_assert(kIndJobs % 4 == 0, "whole requests before the first row");
     if (!a.scanned)
 #pragma unroll 4
-      for (int64_t k = 4 * threadIdx.x; k < k0; k += 4 * THREADS) {
+      for (int64_t k = 4 * threadIdx.x; k < k0; k += 4 * kIndThreadsRows) {
         const uint4 x = *reinterpret_cast<const uint4*>(cnt + k);
         sum += (uint64_t)x.x + x.y + x.z + x.w;
       }
@@ -432,9 +487,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
     if (j.len > kIndShort) {
       if (l == 0) {
         ends[g] = j;
+        // (neighbours, which may all be long, in different ones; so too a vertex's row and its column)
+        const int list = (int)((k + side * (kIndSums / 2)) % kIndSums);
         if (j.len <= kIndWave && kept[g] <= kIndRank) wave_rows[atomicAdd(&n_wave, 1)] = g;
-        else if constexpr (MAPS) map_rows[atomicAdd(&n_map, 1)] = g;
-        else a.map_list[blk % kIndSums * a.map_ld + atomicAdd(&a.map_count[blk % kIndSums], 1)] = side * a.n_sub + k;
+        else if (MAPS && !(a.hubs_listed && j.len > kHubRowNnz)) map_rows[atomicAdd(&n_map, 1)] = g;
+        else a.map_list[list * a.map_ld + atomicAdd(&a.map_count[list], 1)] = side * a.n_sub + k;
       }
     } else if (j.len > 0) {
       int32_t* stage = ind_lds + g * kIndShort;
@@ -482,19 +539,19 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
     order();
   }
   if constexpr (MAPS) {
-    uint32_t* maps = reinterpret_cast<uint32_t*>(ind_lds) + ind_stage(THREADS) / sizeof(int32_t);
+    uint32_t* maps = reinterpret_cast<uint32_t*>(ind_lds) + kIndStage / sizeof(int32_t);
     for (int i0 = 0; i0 < n_map; i0 += a.maps) {
       const int rows = n_map - i0 < a.maps ? n_map - i0 : a.maps;
       if (threadIdx.x < rows) {
         const int at = map_rows[i0 + threadIdx.x];
         row[threadIdx.x] = IndMapRow{ends[at], offset[at], k0 + at, side};
       }
-      ind_maps<THREADS>(a, maps, row, rows);
+      ind_maps<kIndThreadsRows>(a, maps, row, rows);
     }
   }
 }
 
-// The rows left over by k_ind_fill<.., false>, whose bitmaps leave room for few blocks on a compute unit
+// The rows left over by k_ind_fill: hub rows, and those whose bitmaps leave room for few blocks on a compute unit
 __global__ __launch_bounds__(kIndMany) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_ind_maps(IndRows a) {
   extern __shared__ __align__(16) int32_t ind_lds[];
   __shared__ IndMapRow row[kIndMany / 64];
@@ -512,15 +569,42 @@ __global__ __launch_bounds__(kIndMany) __attribute__((amdgpu_waves_per_eu(8, 8))
   }
 }
 
+__global__ void k_ind_giant(const int32_t* __restrict__ vertices, int64_t n_sub, int64_t n, const int64_t* __restrict__ ptr,
+                            const int64_t* __restrict__ ptr_t, int64_t most, int64_t* __restrict__ host) {
+  const int64_t k = block_id() * blockDim.x + threadIdx.x;
+  if (k >= n_sub) return;
+  const int32_t v = vertices[k];
+  if (v < 0 || v >= n) return;                             // (reported by the passes)
+  if (ptr[v + 1] - ptr[v] > most || (ptr_t && ptr_t[v + 1] - ptr_t[v] > most)) *host = 1;
+}
+
+// Of a parent that has giant rows: is one of them selected?  A launch and a wait, 10 us.  The list of such a row is written by one block: 2000 of 2^18
+// vertices with one row of all of them 195 us by keys, 20 K of 2^22 330, in one block with its counting 320 and 4612.
+static int giant_selected(const gcn_csr_t* A, const int32_t* d_vertices, int64_t n_sub, int flags, hipStream_t s, bool* yes) {
+  CallScope sc(s);
+  PinnedPage page;
+  GCN_TRY(page.take(sc));
+  int64_t* word = page.words();
+  *word = 0;
+  k_ind_giant<<<ind_grid(n_sub), kIndThreads, 0, s>>>(d_vertices, n_sub, A->nr, A->rowptr, (flags & GCN_BUILD_CSC) ? A->colptr : nullptr,
+                                                       (int64_t)kGiantChunks * kHubChunkNnz, word);
+  GCN_CHECK_LAUNCH();
+  GCN_HIP(hipStreamSynchronize(s));
+  sc.done = true;
+  *yes = *(volatile int64_t*)word != 0;
+  return GCN_OK;
+}
+
 static int induced_by_rows(const gcn_csr_t* A, const int32_t* d_vertices, int64_t n_sub, int flags, hipStream_t s, gcn_csr* B) {
   const int64_t n = A->nr;
   const int sides = (flags & GCN_BUILD_CSC) ? 2 : 1;
+  const int64_t n_hubs = A->sched.n_hub_rows + (sides == 2 ? A->sched_t.n_hub_rows : 0);
   CallScope sc(s);
   DevBuf lid, cnt, dinv, words, tmp, rowptr, colptr, deg, halo_gid;
   GCN_TRY(lid.alloc(sc, sizeof(int32_t) * (size_t)n));
   GCN_TRY(cnt.alloc(sc, sizeof(uint32_t) * (size_t)(sides * round_up(n_sub, 4))));
   GCN_TRY(dinv.alloc(sc, sizeof(float) * (size_t)n_sub));
-  GCN_TRY(words.alloc(sc, (1 + 2 * kIndSums) * sizeof(int64_t)));  // the flags; the number of entries, in parts; those of listed rows
+  GCN_TRY(words.alloc(sc, (2 + 2 * kIndSums + n_hubs) * sizeof(int64_t)));  // flags; rows left over; entries, in parts; listed rows; entries of rows left over
   GCN_TRY(rowptr.alloc(sc, sizeof(int64_t) * (size_t)(n_sub + 1)));
   if (sides == 2) GCN_TRY(colptr.alloc(sc, sizeof(int64_t) * (size_t)(n_sub + 1)));
   GCN_TRY(deg.alloc(sc, sizeof(int32_t) * (size_t)n_sub));
@@ -533,28 +617,41 @@ static int induced_by_rows(const gcn_csr_t* A, const int32_t* d_vertices, int64_
   int maps = (few ? kIndThreadsRows : kIndMany) / 64;
   while (maps > 1 && maps * map_bytes > 32 * 1024) maps /= 2;
   DevBuf map_list;
-  const int64_t blocks = ceil_div(n_sub, kIndThreadsRows / kIndLanes), map_ld = ceil_div(sides * blocks, kIndSums) * (kIndThreadsRows / kIndLanes);
-  if (!few) GCN_TRY(map_list.alloc(sc, sizeof(int64_t) * (size_t)(kIndSums * map_ld)));
+  const int64_t blocks = ceil_div(n_sub, kIndJobs), map_ld = sides * ceil_div(n_sub, kIndSums);
+  DevBuf over;
+  GCN_TRY(over.alloc(sc, sizeof(int64_t) * (size_t)(n_hubs + 1)));
+  if (!few || n_hubs > 0) GCN_TRY(map_list.alloc(sc, sizeof(int64_t) * (size_t)(kIndSums * map_ld)));
   IndRows a{d_vertices, n_sub, n, lid.as<int32_t>(), {A->rowptr, A->colptr}, {A->col, A->rowidx}, blocks, sides,
-            cnt.as<uint32_t>(), round_up(n_sub, 4), deg.as<int32_t>(), dinv.as<float>(), words.as<int>(), words.as<int64_t>() + 1,
+            cnt.as<uint32_t>(), round_up(n_sub, 4), deg.as<int32_t>(), dinv.as<float>(), words.as<int>(), words.as<int64_t>() + 2,
             {rowptr.as<int64_t>(), colptr.as<int64_t>()}, !few, {nullptr, nullptr}, {nullptr, nullptr}, maps, map_list.as<int64_t>(), map_ld,
-            (int*)(words.as<int64_t>() + 1 + kIndSums)};
+            (int*)(words.as<int64_t>() + 2 + kIndSums), words.as<int64_t>() + 1, over.as<int64_t>(),
+            words.as<unsigned long long>() + 2 + 2 * kIndSums, n_hubs, 0};
   const dim3 grid = fold_grid(sides * a.blocks);
-  k_ind_init<<<ind_grid(std::max<int64_t>(n, 2 * kIndSums)), kIndThreads, 0, s>>>(lid.as<int32_t>(), n, 0, a.bad, a.nnz, 2 * kIndSums);
+  k_ind_init<<<ind_grid(std::max<int64_t>(n, 1 + 2 * kIndSums + n_hubs)), kIndThreads, 0, s>>>(lid.as<int32_t>(), n, 0, a.bad, a.n_over, (int)(1 + 2 * kIndSums + n_hubs));
   k_ind_scatter<<<ind_grid(n_sub), kIndThreads, 0, s>>>(d_vertices, n_sub, n, lid.as<int32_t>(), a.bad);
-  k_ind_count<kIndThreadsRows><<<grid, kIndThreadsRows, 0, s>>>(a);
+  k_ind_count<<<grid, kIndThreadsRows, 0, s>>>(a);
   GCN_CHECK_LAUNCH();
-  GCN_HIP(hipMemcpyAsync(read, words.p, (1 + kIndSums) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  if (a.scanned) {
-    GCN_TRY(tmp.alloc(sc, scan_tmp_bytes(n_sub)));
-    for (int side = 0; side < sides; ++side) GCN_TRY(exclusive_scan_u32(a.cnt + side * a.cnt_ld, a.out_ptr[side], n_sub, tmp.p, s));
-  }
-  GCN_HIP(hipStreamSynchronize(s));
-  int64_t nnz = 0;
-  for (int i = 0; i < kIndSums; ++i) nnz += read[1 + i];
+  if (a.scanned) GCN_TRY(tmp.alloc(sc, scan_tmp_bytes(n_sub)));
+  auto counted = [&]() -> int {
+    GCN_HIP(hipMemcpyAsync(read, words.p, (2 + kIndSums) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    if (a.scanned)
+      for (int side = 0; side < sides; ++side) GCN_TRY(exclusive_scan_u32(a.cnt + side * a.cnt_ld, a.out_ptr[side], n_sub, tmp.p, s));
+    GCN_HIP(hipStreamSynchronize(s));
+    return GCN_OK;
+  };
+  GCN_TRY(counted());
   const int* h_bad = (const int*)read;
   if (h_bad[0]) return fail(GCN_EINVAL, "gcn_csr_induced: a vertex id lies outside the graph");
   if (h_bad[1]) return fail(GCN_EINVAL, "gcn_csr_induced: a vertex is listed twice");
+  if (read[1] > n_hubs) return fail(GCN_EHIP, "gcn_csr_induced: internal error (%lld long rows of %lld)", (long long)read[1], (long long)n_hubs);
+  a.hubs_listed = read[1] > 0;
+  if (a.hubs_listed) {
+    k_ind_count_over<<<dim3((unsigned)std::min<int64_t>(read[1], 1024), kIndShare), kIndThreadsRows, 0, s>>>(a, read[1]);
+    GCN_CHECK_LAUNCH();
+    GCN_TRY(counted());
+  }
+  int64_t nnz = 0;
+  for (int i = 0; i < kIndSums; ++i) nnz += read[2 + i];
   if (nnz < n_sub) return fail(GCN_EHIP, "gcn_csr_induced: internal error (nnz %lld < rows %lld)", (long long)nnz, (long long)n_sub);
 
   DevBuf col, val, rowidx, val_t, mid;
@@ -566,11 +663,10 @@ static int induced_by_rows(const gcn_csr_t* A, const int32_t* d_vertices, int64_
   }
   a.out_idx[0] = col.as<int32_t>(); a.out_idx[1] = rowidx.as<int32_t>();
   a.out_val[0] = val.as<float>(); a.out_val[1] = val_t.as<float>();
-  const size_t stage = ind_stage(kIndThreadsRows), map_lds = (size_t)(maps * map_bytes);
-  if (few) {
-    k_ind_fill<kIndThreadsRows, true><<<grid, kIndThreadsRows, stage + map_lds, s>>>(a);
-  } else {
-    k_ind_fill<kIndThreadsRows, false><<<grid, kIndThreadsRows, stage, s>>>(a);
+  const size_t stage = kIndStage, map_lds = (size_t)(maps * map_bytes);
+  if (few) k_ind_fill<true><<<grid, kIndThreadsRows, stage + map_lds, s>>>(a);
+  else k_ind_fill<false><<<grid, kIndThreadsRows, stage, s>>>(a);
+  if (!few || a.hubs_listed) {
     GCN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_ind_maps), hipFuncAttributeMaxDynamicSharedMemorySize, (int)map_lds));
     k_ind_maps<<<dim3(4 * kIndSums), kIndMany, map_lds, s>>>(a);
   }
@@ -641,12 +737,19 @@ extern "C" int gcn_csr_induced(const gcn_csr_t* A, const int32_t* d_vertices, in
   if (hipGetDevice(&B->device) != hipSuccess) { delete B; return fail(GCN_EHIP, "hipGetDevice failed"); }
   // Row by row, but from a parent without a column-major copy, for subgraphs whose vertices no bitmap in LDS holds, and where many rows take a
   // bitmap of more than 16 KB: 500 K of 1 M vertices, R-MAT rows (one in 60 of 512 entries and more) 962 us by sorting keys, 1200 row by row;
-  // uniform rows 1816 and 1330.  131 K of 262 K, R-MAT 1013 and 874.
+  // uniform rows 1816 and 1330.  131 K of 262 K, R-MAT 1013 and 874.  The table of numbers is asked for four times an entry, by keys once: where it is
+  // more than an XCD's L2 holds, R-MAT rows gain up to fewer vertices (of 2.45 M ones 50 K 280 and 268, 65 K 306 and 330, 131 K 387 and 468; of 4 M
+  // 65 K 259 and 260, 131 K 335 and 415; of 1.5 M 90 K 335 and 308, 131 K 397 and 420).
   const int64_t long_rows = A->sched.class_begin[23] + A->sched.n_hub_rows + (A->colptr ? A->sched_t.class_begin[23] + A->sched_t.n_hub_rows : 0);
+  // Nor where a giant row is likely to be among the selected ones (in one call of four).
+  const int64_t giants = std::max(A->sched.n_giant_rows, (flags & GCN_BUILD_CSC) && A->colptr ? A->sched_t.n_giant_rows : 0);
   const bool by_rows = (A->colptr || !(flags & GCN_BUILD_CSC)) && n_sub <= kIndMaxSub && A->nnz + n_sub < 0xffffffffLL &&
-                       (n_sub <= 1 << 17 || long_rows * 200 <= A->nr);
-  const int rc = by_rows ? induced_by_rows(A, d_vertices, n_sub, flags, (hipStream_t)stream, B)
-                         : induced_by_keys(A, d_vertices, n_sub, flags, (hipStream_t)stream, B);
+                       (n_sub <= (A->nr > 1 << 20 ? 1 << 16 : 1 << 17) || long_rows * 200 <= A->nr) && (double)giants * (double)n_sub <= 0.25 * (double)A->nr;
+  bool by_keys = !by_rows;
+  int rc = GCN_OK;
+  if (!by_keys && giants > 0) rc = giant_selected(A, d_vertices, n_sub, flags, (hipStream_t)stream, &by_keys);
+  if (!by_keys && rc == GCN_OK) rc = induced_by_rows(A, d_vertices, n_sub, flags, (hipStream_t)stream, B);
+  if (by_keys && rc == GCN_OK) rc = induced_by_keys(A, d_vertices, n_sub, flags, (hipStream_t)stream, B);
   if (rc != GCN_OK) { gcn_csr_free(B); return rc; }
   *out = B;
   return GCN_OK;

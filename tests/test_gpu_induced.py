@@ -224,3 +224,31 @@ def test_induced_with_and_without_column_major_arrays(gcn, dev, parent_csc, csc)
     for name in NAMES if csc else NAMES[:3]:
         assert np.array_equal(arr[name].cpu().numpy(), getattr(og, name)), name
     assert np.array_equal(arr["val"].cpu().numpy().view(np.int32), og.val.view(np.int32))
+
+
+@pytest.mark.parametrize("rows,length", [(1, 98304), (1, 98400), (1, 196500), (1, 196700), (1, 300000), (33, 6000)])
+@pytest.mark.parametrize("n_sub", [500, 20000, 40000])
+@pytest.mark.parametrize("csc", [True, False])
+def test_induced_with_more_entries_than_a_block_takes(gcn, dev, rows, length, n_sub, csc):
+    """Rows (for an edge list turned round: columns) of more than 96 pieces of 1024 entries (and one for every 1024 vertices) among the 32 that a block has,
+    alone and several in a row, at the line and beyond it, and at that of giant rows (192 pieces); a vertex out of range and one listed twice (or 5000 times) are refused there as elsewhere."""
+    n = 400_000
+    rng = np.random.default_rng(rows + length)
+    long = rng.permutation(n)[:rows]
+    src = np.r_[rng.integers(0, n, 800_000), np.repeat(long, length)].astype(np.int32)
+    dst = np.r_[rng.integers(0, n, 800_000), np.concatenate([rng.permutation(n)[:length] for _ in long])].astype(np.int32)
+    V = np.concatenate([np.setdiff1d(rng.permutation(n)[:n_sub], long)[:100], long])
+    V = np.concatenate([V, np.setdiff1d(rng.permutation(n), V)[:n_sub - len(V)]])
+    for s, d in ((src, dst), (dst, src)):
+        A = gcn.gcn_csr_build(dev_i32(s, dev), dev_i32(d, dev), n)
+        og = oracle.graph_build(*oracle.induced_edges(s, d, n, V), len(V))
+        B = gcn.gcn_csr_induced(A, dev_i32(V, dev), flags=gcn.BUILD_CSC if csc else 0)
+        arr = B.arrays()
+        for name in NAMES if csc else NAMES[:3]:
+            assert np.array_equal(arr[name].cpu().numpy(), getattr(og, name)), name
+        assert np.array_equal(arr["val"].cpu().numpy().view(np.int32), og.val.view(np.int32))
+        B.free()
+        for bad, what in ((np.r_[V[:-1], n], "outside"), (np.r_[V[:-1], V[0]], "twice"), (np.r_[V[:-1], np.full(5000, long[0])], "twice")):
+            with pytest.raises(Exception, match=what):
+                gcn.gcn_csr_induced(A, dev_i32(bad, dev))
+        A.free()
