@@ -101,15 +101,15 @@ __global__ void k_ps_pairs(const uint64_t* __restrict__ keys, const int64_t* __r
 // figures of a column are kept in registers and LDS.  A column costs a chain of dependent requests (its number, its ends and part,
 // its rows, their parts), so it gets the lanes that leave it one step of that chain: a wavefront for 64 entries and more (8 a lane), 16
 // lanes for 16 to 63, four lanes below, where equal parts are found by comparing registers.  Columns come in the order of the schedule,
-// // whose length classes are those bounds.  Whole calls, against 16 lanes for every column, the pair table in memory and its word asked for
+// whose length classes are those bounds.  Whole calls, against 16 lanes for every column, the pair table in memory and its word asked for
 // entry by entry, 2048 workgroups and the ids checked by a launch and a wait of their own, us before / now: 2^18 R-MAT columns of
 // 45 entries, 512 parts 226 / 131 (this kernel 130 / 92); 1.2 M of 13, 27 parts 702 / 185; 82 K uniform ones of 24, 15 parts 621 / 78; 67 K
 // log-normal ones of 444, 1692 parts 519 / 275.
 constexpr int kPsColThreads = 1024, kPsWaves = kPsColThreads / 64;
 constexpr int kPsLanes = 16, kPsFew = 4;         // lanes of a column of 16 to 63 entries; of fewer
 constexpr int kPsGroups = kPsColThreads / kPsLanes;
-// The counters of a workgroup (entries, rows sent and rows received of every part) and its 64 bitmaps have to fit its LDS twice a
-// compute unit: 3 p words + 2 p words.
+// The counters of a workgroup (entries, rows sent and rows received of every part) and its 64 bitmaps take 3 p + 2 words and 2 p words of its
+// LDS: 80 KB at most, and up to 4095 parts a second workgroup fits the compute unit.
 constexpr int kPsMaxParts = 4096;
 // The pair table fits LDS up to 512 parts: a workgroup marks its pairs there and looks at the table in memory once, at the end.
 constexpr int kPsPairLds = 512;

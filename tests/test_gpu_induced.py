@@ -226,6 +226,42 @@ def test_induced_with_and_without_column_major_arrays(gcn, dev, parent_csc, csc)
     assert np.array_equal(arr["val"].cpu().numpy().view(np.int32), og.val.view(np.int32))
 
 
+def sparse_parent_with_long_rows(n, degree, long_rows, length, seed):
+    rng = np.random.default_rng(seed)
+    m = n * degree // 2
+    src, dst = rng.integers(0, n, m), rng.integers(0, n, m)
+    hubs = rng.permutation(n)[:long_rows]
+    src = np.r_[src, np.repeat(hubs, length)]
+    dst = np.r_[dst, rng.integers(0, n, long_rows * length)]
+    return src.astype(np.int32), dst.astype(np.int32), hubs, rng
+
+
+@pytest.mark.parametrize("n_sub", [1 << 17, (1 << 17) + 1, 600_000, (1 << 20) + 1])
+def test_induced_with_large_bitmaps(gcn, dev, n_sub):
+    """Long rows whose bitmaps stand two and one in a block's LDS, take more than 64 KB of it, and no longer fit (subgraphs by keys)."""
+    n = max(200_000, n_sub + 5)
+    src, dst, hubs, rng = sparse_parent_with_long_rows(n, 4, 40, 3000, n_sub)
+    A = gcn.gcn_csr_build(dev_i32(src, dev), dev_i32(dst, dev), n)
+    V = np.concatenate([hubs, np.setdiff1d(rng.permutation(n)[:n_sub], hubs)])[:n_sub]
+    V = np.concatenate([V, np.setdiff1d(np.arange(n), V)[:n_sub - len(V)]])
+    _, B = check_induced(gcn, dev, A, src, dst, n, rng.permutation(V))
+    B.free()
+    A.free()
+
+
+@pytest.mark.parametrize("n,n_sub,long_rows", [(150_000, 1 << 17, 300), (150_000, 1 << 17, 1200), (150_000, (1 << 17) + 1, 300), (150_000, (1 << 17) + 1, 1200),
+                                               ((1 << 20) + 1, 1 << 16, 3000), ((1 << 20) + 1, (1 << 16) + 1, 3000)])
+def test_induced_of_parents_with_many_long_rows(gcn, dev, n, n_sub, long_rows):
+    """Both sides of the line between the two ways: subgraphs of more than 2^17 vertices (2^16 of parents of more than 2^20) of a parent whose long rows
+    (512 entries and more, rows and columns counted) are fewer or more than one in 200."""
+    src, dst, hubs, rng = sparse_parent_with_long_rows(n, 4, long_rows, 700, long_rows)
+    A = gcn.gcn_csr_build(dev_i32(np.r_[src, dst], dev), dev_i32(np.r_[dst, src], dev), n)
+    V = rng.permutation(n)[:n_sub]
+    _, B = check_induced(gcn, dev, A, np.r_[src, dst], np.r_[dst, src], n, V)
+    B.free()
+    A.free()
+
+
 @pytest.mark.parametrize("rows,length", [(1, 98304), (1, 98400), (1, 196500), (1, 196700), (1, 300000), (33, 6000)])
 @pytest.mark.parametrize("n_sub", [500, 20000, 40000])
 @pytest.mark.parametrize("csc", [True, False])
