@@ -356,6 +356,7 @@ int gcn_sgd_update(float* W, const float* dW, int64_t n, float lr, void* stream)
  *              time it is read (what caches and HBM together serve); else equal to alg_bytes.
  *   flops      2 * multiply-adds.
  *   ms         elapsed time between the two events.
+ *   parts      3: an fp32 dense product on the bf16 matrix pipe, six operations for one; else 0.
  */
 /* The sparse kinds: also the launch that multiplies a small layer's sparse rows by W (or W^T) as it goes, with the bytes and operations of
  * both products; there is no GCN_K_GEMM_NN record then. */
@@ -370,7 +371,7 @@ int gcn_sgd_update(float* W, const float* dW, int64_t n, float lr, void* stream)
 #define GCN_K_OTHER 8         /* column sums, padded copies of operands, the weight update */
 
 typedef struct {
-  int32_t kind, d, dtype, reserved;
+  int32_t kind, d, dtype, parts;
   int64_t rows, inner;
   double alg_bytes, touched_bytes, flops, ms;
 } gcn_profile_rec;

@@ -22,7 +22,7 @@ class GcnError(RuntimeError):
 
 class ProfileRec(C.Structure):
     """Mirror of gcn_profile_rec."""
-    _fields_ = [("kind", C.c_int32), ("d", C.c_int32), ("dtype", C.c_int32), ("reserved", C.c_int32),
+    _fields_ = [("kind", C.c_int32), ("d", C.c_int32), ("dtype", C.c_int32), ("parts", C.c_int32),
                 ("rows", C.c_int64), ("inner", C.c_int64), ("alg_bytes", C.c_double),
                 ("touched_bytes", C.c_double), ("flops", C.c_double), ("ms", C.c_double)]
 
@@ -519,5 +519,6 @@ def gcn_profile_records():
     for i in range(n):
         _check(_lib.gcn_profile_get(i, C.byref(rec)), "gcn_profile_get")
         out.append({"kind": KIND_NAMES[rec.kind], "d": rec.d, "dtype": rec.dtype, "rows": rec.rows, "inner": rec.inner,
-                    "alg_bytes": rec.alg_bytes, "touched_bytes": rec.touched_bytes, "flops": rec.flops, "ms": rec.ms})
+                    "alg_bytes": rec.alg_bytes, "touched_bytes": rec.touched_bytes, "flops": rec.flops, "ms": rec.ms,
+                    "parts": rec.parts})
     return out, dropped.value

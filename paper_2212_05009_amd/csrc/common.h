@@ -63,7 +63,7 @@ const Tuning& tune();
 // goes out of scope, both on `s`, if profiling is enabled; otherwise costs one relaxed load.
 struct ProfScope {
   ProfScope(int kind, hipStream_t s, int d, int dtype, int64_t rows, int64_t inner, double alg_bytes,
-            double touched_bytes, double flops);
+            double touched_bytes, double flops, int parts = 0);
   ~ProfScope();
   ProfScope(const ProfScope&) = delete;
   ProfScope& operator=(const ProfScope&) = delete;
@@ -414,6 +414,7 @@ int gemm_nn_split(const void* A, int64_t lda, const float* W, int64_t ldw, void*
                   const GemmEpilogue& epi, hipStream_t s);
 bool gemm_tn_split_ok(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype);
 size_t gemm_tn_split_ws_bytes(int64_t Kd, int M, int N);
+bool gemm_tn_takes_split(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype, bool beside);
 int gemm_tn_split_partials(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, float* partial, int* nsplit_out,
                            hipStream_t s, int max_blocks = 0);
 // bf16 features on the bf16 matrix pipe (gemm_bf16.hip): W rounded to bf16 in LDS, fp32 accumulation

@@ -269,7 +269,7 @@ int gemm_nn(const void* A, int64_t lda, const float* B, int64_t ldb, void* C, in
   }
   if (use_direct() && gemm_nn_split_ok(A, lda, ldb, ldc, M, N, K, dtype, epi)) {
     const double nb = 4.0 * (double)M * (K + N + (epi.mask ? N : 0)) + 4.0 * (double)K * N;
-    ProfScope ps(GCN_K_GEMM_NN, s, N, dtype, M, K, nb, nb, 2.0 * (double)M * N * K);
+    ProfScope ps(GCN_K_GEMM_NN, s, N, dtype, M, K, nb, nb, 2.0 * (double)M * N * K, 3);
     return gemm_nn_split(A, lda, B, ldb, C, ldc, M, N, K, epi, s);
   }
   // Wide weight matrices (transposed: below 2^16 rows, or with few terms) are held in registers, the operand rows streamed past them through
@@ -475,7 +475,7 @@ int gemm_tn(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, in
   int nsplit = 0;
   if (use_direct()) {
     const double nb = (double)es * (double)Kd * (M + N) + 4.0 * (double)mn;
-    ProfScope ps(GCN_K_GEMM_TN, s, N, dtype, M, Kd, nb, nb, 2.0 * (double)Kd * M * N);
+    ProfScope ps(GCN_K_GEMM_TN, s, N, dtype, M, Kd, nb, nb, 2.0 * (double)Kd * M * N, gemm_tn_takes_split(A, lda, B, ldb, Kd, M, N, dtype, beside) ? 3 : 0);
     GCN_TRY(gemm_tn_direct_partials(A, lda, B, ldb, Kd, M, N, dtype, (float*)ws, &nsplit, s, max_blocks, beside));
   } else {
     TnArgs a{A, lda, B, ldb, Kd, M, N, pick_vec(A, lda, M, es), pick_vec(B, ldb, N, es), 0, 0, (float*)ws};

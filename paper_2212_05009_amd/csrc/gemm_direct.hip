@@ -986,14 +986,17 @@ size_t gemm_tn_direct_ws_bytes(int64_t Kd, int M, int N) {
   return std::max(std::max(sizeof(float) * (size_t)ns * (size_t)M * (size_t)N, gemm_tn_lds_ws_bytes(Kd, M, N)), gemm_tn_split_ws_bytes(Kd, M, N));
 }
 
+bool gemm_tn_takes_split(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype, bool beside) {
+  return !(beside && gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype)) && gemm_tn_split_ok(A, lda, B, ldb, Kd, M, N, dtype);
+}
+
 int gemm_tn_direct_partials(const void* A, int64_t lda, const void* B, int64_t ldb, int64_t Kd, int M, int N, int dtype,
                             float* partial, int* nsplit_out, hipStream_t s, int max_blocks, bool beside) {
   if (dtype == GCN_BF16 && gemm_tn_bf16_ok(A, lda, B, ldb, Kd, M, N))
     return gemm_tn_bf16_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s);
-  const bool lds = gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype);
-  if (!(beside && lds) && gemm_tn_split_ok(A, lda, B, ldb, Kd, M, N, dtype))
+  if (gemm_tn_takes_split(A, lda, B, ldb, Kd, M, N, dtype, beside))
     return gemm_tn_split_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s, max_blocks);
-  if (lds) return gemm_tn_lds_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s, max_blocks);
+  if (gemm_tn_lds_ok(A, lda, B, ldb, Kd, M, N, dtype)) return gemm_tn_lds_partials(A, lda, B, ldb, Kd, M, N, partial, nsplit_out, s, max_blocks);
   TnDirectArgs a{A, lda, B, ldb, Kd, M, N, 0, 0, partial};
   const bool narrow = tn_narrow_ok(A, lda, B, ldb, Kd, M, N, dtype);
   if (narrow || gemm_tn_wide_ok(A, lda, B, ldb, N, dtype)) {

@@ -27,7 +27,7 @@ ProfSuppress::ProfSuppress() { ++t_suppress; }
 ProfSuppress::~ProfSuppress() { --t_suppress; }
 
 ProfScope::ProfScope(int kind, hipStream_t s, int d, int dtype, int64_t rows, int64_t inner, double alg_bytes,
-                     double touched_bytes, double flops)
+                     double touched_bytes, double flops, int parts)
     : s_(s) {
   if (!g_enabled.load(std::memory_order_relaxed) || t_suppress > 0) return;
   if (!((g_kind_mask.load(std::memory_order_relaxed) >> kind) & 1)) return;
@@ -41,7 +41,7 @@ ProfScope::ProfScope(int kind, hipStream_t s, int d, int dtype, int64_t rows, in
     g_slots.push_back(sl);
   }
   Slot& sl = g_slots[g_used];
-  sl.rec = gcn_profile_rec{kind, d, dtype, 0, rows, inner, alg_bytes, touched_bytes, flops, 0.0};
+  sl.rec = gcn_profile_rec{kind, d, dtype, parts, rows, inner, alg_bytes, touched_bytes, flops, 0.0};
   sl.closed = false;
   if (hipEventRecord(sl.start, s) != hipSuccess) { ++g_dropped; return; }
   slot_ = g_used++;
