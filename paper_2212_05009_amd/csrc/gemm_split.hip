@@ -78,7 +78,7 @@ struct RangeCheck {
 };
 // The least magnitude of operands that are not zero.  The last part of one below 2^-108 may have bits under the smallest bf16 number (2^-133); what a
 // sum looks like says nothing about it, the other operand may be large.  Three integer operations for two values: 602 -> 128 on 233 K rows 256 ->
-// 278 us, 256 -> 256 on 2.45 M 2.03 -> 2.10 ms, A^T B 602 x 128 344 -> 350 us.
+// 278 us, 256 -> 256 on 2.45 M 2.03 -> 2.10 ms (both with W stored [K x N]), A^T B 602 x 128 344 -> 350 us.
 struct LeastOperand {
   uint32_t least = 0xffffffffu;                        // twice the bits, less one: zero is the largest
   __device__ __forceinline__ void add(float lo, float hi) {
@@ -100,12 +100,13 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// What bounds it: the matrix pipe and its clock.  2.45 M rows x 256 x 256: 1.84 M of its 3.0 M cycles the pipe is busy, at 1.8 GHz
-// (2.2 in kernels that wait for memory); LDS is read in half of them.  While a step is multiplied (192 operations a wavefront at 256
-// columns) the next one is split (88 vector operations, in their shadow) and the one after asked for, its own registers' places
-// as they fall free; splitting first and multiplying then took 1.96 ms for 1.68, W in plain loads with their addresses in registers,
-// spilled, 2.42; 1.68 is 1.95 with the sums of each step added by vector operations, without which the error grows to that of the fp32
-// pipe and beyond (terms of one sign).
+// What bounds it: a wavefront's own instructions, of the matrix and the vector pipe in turn (two wavefronts a SIMD), and the clock.  2.45 M rows x
+// 256 x 256: 2.28 ms, the matrix pipe busy for 34 % of what the nominal clock has (at 1.8 GHz; 2.2 in kernels that wait for memory).  While a
+// step is multiplied (192 operations a wavefront at 256 columns) the next one is split, in their shadow, and the one after asked for, its
+// own registers' places as they fall free.  Bare sums took 1.68 ms (1.96 with splitting first and multiplying then; 2.42 with W in plain loads, their
+// addresses in registers, spilled); 1.80 with the sums of each step added by vector operations, without which the error grows to that of the fp32 pipe
+// and beyond (terms of one sign); 2.28 with the other sign in every other step and row, the first parts' products by themselves, and small operands
+// found.
 // Lane (c, q) = (lane % 16, lane / 16) supplies row c of a tile of 16 rows, k = 8 q .. 8 q + 7 of a step of 32, as the second
 // MFMA operand and column 16 t + c of W as the first: register r of its accumulator t is column 16 t + 4 q + r of row c.
 // LDS holds W as operands, [step][tile][part][lane], 16 bytes each: all of it (RES), or two steps in turn, which the workgroup reads
@@ -338,8 +339,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
     }
     const int left = rows_left(tile);
-    // An operand or a sum out of the range in which the parts stand for their values: those rows are multiplied again on the fp32 pipe.  602 -> 128 on
-    // 233 K rows, such an operand in no row 270 us, one of 50 K 322, one of 1000 376, one of 32 637, in W 637; 440 on the fp32 pipe.
+    // An operand or a sum out of the range in which the parts stand for their values: those rows are multiplied again on the fp32 pipe.  602 terms to 128
+    // columns on 233 K rows, such an operand in no row 314 us, one of 50 K 376, one of 1000 449, one of 32 660 (1027 with requests of one k), in W 745
+    // (1179); 419 on the fp32 pipe.  256 to 256 on 2.45 M rows 2.44 ms, 2.67, 3.41, 5.7 (9.1), 6.5 (11.9); 2.60.
     RangeCheck range;
 #pragma unroll
     for (int rt = 0; rt < kRT; ++rt)
@@ -356,28 +358,35 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int rt = 0; rt < kRT; ++rt)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[rt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-      constexpr int kDeep = NT > 8 ? 2 : 4;            // (steps of four asked for at a time)
-      for (int k0 = 0; k0 < a.K; k0 += 4 * kDeep) {
-        float xs[kDeep][kRT], ws[kDeep][NT];
+      // sixteen k at a time, four in a row a lane: step i of them takes k = k0 + 4 q + i of both operands
+      constexpr int kAtOnce = NT > 8 ? NT / 2 : NT;    // (tiles of W asked for together)
+      for (int k0 = 0; k0 < a.K; k0 += 16) {
+        const int k = k0 + 4 * qe, in = a.K - k;
+        float xs[kRT][4];
 #pragma unroll
-        for (int d = 0; d < kDeep; ++d) {
-          const int k = k0 + 4 * d + qe;
+        for (int rt = 0; rt < kRT; ++rt) {
+          const auto v = __builtin_amdgcn_raw_buffer_load_b128(ab, ((16 * rt + ce) * (int)a.lda + k) * 4, 0, 0);
 #pragma unroll
-          for (int rt = 0; rt < kRT; ++rt)
-            xs[d][rt] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ab, (int)(k < a.K ? (uint32_t)((16 * rt + ce) * (int)a.lda + k) * 4u : kNoPlace), 0, 0));
-#pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            const int n = n0 + 16 * t + ce;
-            const uint32_t at = (uint32_t)(n * ldw + k) * 4u;
-            ws[d][t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wb, (int)(k < a.K && n < a.N ? at : kNoPlace), 0, 0));
-          }
+          for (int i = 0; i < 4; ++i) xs[rt][i] = i < in ? __uint_as_float(v[i]) : 0.f;
         }
 #pragma unroll
-        for (int d = 0; d < kDeep; ++d)
+        for (int t0 = 0; t0 < NT; t0 += kAtOnce) {
+          float ws[kAtOnce][4];
 #pragma unroll
-          for (int t = 0; t < NT; ++t)
+          for (int t = 0; t < kAtOnce; ++t) {
+            const int n = n0 + 16 * (t0 + t) + ce;
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(wb, (int)(n < a.N ? (uint32_t)(n * ldw + k) * 4u : kNoPlace), 0, 0);
 #pragma unroll
-            for (int rt = 0; rt < kRT; ++rt) acc[rt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ws[d][t], xs[d][rt], acc[rt][t], 0, 0, 0);
+            for (int i = 0; i < 4; ++i) ws[t][i] = i < in ? __uint_as_float(v[i]) : 0.f;
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int t = 0; t < kAtOnce; ++t)
+#pragma unroll
+              for (int rt = 0; rt < kRT; ++rt)
+                acc[rt][t0 + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ws[t][i], xs[rt][i], acc[rt][t0 + t], 0, 0, 0);
+        }
       }
     }
     if (left <= 0) continue;
