@@ -739,12 +739,15 @@ extern "C" int gcn_csr_induced(const gcn_csr_t* A, const int32_t* d_vertices, in
   // bitmap of more than 16 KB: 500 K of 1 M vertices, R-MAT rows (one in 60 of 512 entries and more) 962 us by sorting keys, 1200 row by row;
   // uniform rows 1816 and 1330.  131 K of 262 K, R-MAT 1013 and 874.  The table of numbers is asked for four times an entry, by keys once: where it is
   // more than an XCD's L2 holds, R-MAT rows gain up to fewer vertices (of 2.45 M ones 50 K 280 and 268, 65 K 306 and 330, 131 K 387 and 468; of 4 M
-  // 65 K 259 and 260, 131 K 335 and 415; of 1.5 M 90 K 335 and 308, 131 K 397 and 420).
+  // 65 K 259 and 260, 131 K 335 and 415; of 1.5 M 90 K 335 and 308, 131 K 397 and 420).  Beyond 2^21 vertices uniform rows too, up to some 2e13
+  // vertices times entries: 300 K of 2.45 M with 24 each 544 and 517, 400 K 643 and 670, 800 K 1179 and 1335; 400 K of 4 M with 12 498 and 475, 600 K
+  // 634 and 684 (of 1.5 M with 24 up to 2^20 vertices 1.1 to 1.5 times as fast).
   const int64_t long_rows = A->sched.class_begin[23] + A->sched.n_hub_rows + (A->colptr ? A->sched_t.class_begin[23] + A->sched_t.n_hub_rows : 0);
   // Nor where a giant row is likely to be among the selected ones (in one call of four).
   const int64_t giants = std::max(A->sched.n_giant_rows, (flags & GCN_BUILD_CSC) && A->colptr ? A->sched_t.n_giant_rows : 0);
   const bool by_rows = (A->colptr || !(flags & GCN_BUILD_CSC)) && n_sub <= kIndMaxSub && A->nnz + n_sub < 0xffffffffLL &&
-                       (n_sub <= (A->nr > 1 << 20 ? 1 << 16 : 1 << 17) || long_rows * 200 <= A->nr) && (double)giants * (double)n_sub <= 0.25 * (double)A->nr;
+                       (n_sub <= (A->nr > 1 << 20 ? 1 << 16 : 1 << 17) || long_rows * 200 <= A->nr) && (double)giants * (double)n_sub <= 0.25 * (double)A->nr &&
+                       (A->nr <= 1 << 21 || (double)A->nnz * (double)n_sub <= 2e13);
   bool by_keys = !by_rows;
   int rc = GCN_OK;
   if (!by_keys && giants > 0) rc = giant_selected(A, d_vertices, n_sub, flags, (hipStream_t)stream, &by_keys);
