@@ -143,9 +143,9 @@ constexpr int kIndWave = 1024;                             // entries that a wav
 constexpr int kIndRank = 256;
 // A block with more pieces than these, and one more for every 1024 vertices, leaves its hub rows to launches of their own, whose blocks share the
 // pieces of every such row: the call would wait for that one block, 1.1 us a piece in both passes.  Us with the pieces of a block as they come / this way /
-// by keys: the 1000 vertices of 2^20 R-MAT ones with the longest rows, longest first 1735 / 399 / 534, in random order 737 / 371 / 535; 20 K of 2^18
-// 869 / 422 / 681, 400 / 401 / 670; random ones 118 / 119 / 214.  Leaving every hub row to them costs a launch and a longer chain of requests
-// where none is that long (134).  Slower than by keys: 20 K of 2.45 M, longest first, 50 M entries of which few stay, 5202 / 2791 / 2139 (columns are
+// by keys: the 1000 vertices of 2^20 R-MAT ones with the longest rows, longest first 1738 / 375 / 520, in random order 741 / 347 / 526; 20 K of 2^18
+// 871 / 406 / 661, 405 / 395 / 670; random ones 119 / 118 / 204.  Leaving every hub row to them costs a launch and a longer chain of requests
+// where none is that long (134).  Slower than by keys: 20 K of 2.45 M, longest first, 50 M entries of which few stay, 5177 / 2727 / 2141 (columns are
 // read too, and both twice).
 constexpr int kIndOver = 96, kIndShare = 16;               // (blocks that share a row)
 static_assert(kIndOver >= 32 * kHubRowNnz / kIndWave, "what a block keeps is fewer pieces");
